@@ -1,10 +1,12 @@
 // Attention forward over the gathered lists on bf16 MFMA, variant that shares the coarse levels
-// (B = 16, 32 or 64, d = 64 or 128, N a multiple of 256, at most 64 level-0 tiles of 16 tokens per list).
+// (B = 16, 32 or 64, d = 64 or 128, at most 64 level-0 tiles of 16 tokens per list).
 //
 // 256 consecutive queries (B = 16: the 16 fine query blocks under one level-1 query block) use the same lists at
 // every level >= 1 (Alg. 1, enrichment loop: block i reads row i / B^l of I^(l)), i.e. the same coarse key/value
 // tokens.  One workgroup of 4 or 8 waves owns such a group or half of one; every wave owns one or two of its
-// 16-query tiles.
+// 16-query tiles.  A length that is no multiple of 128 has one coarse level (N is a multiple of B^L, and B^2 >= 256), which
+// every query of a head uses whole: the last workgroup of a head then holds fewer tiles, and its spare waves work on the
+// head's last tile without storing it.
 //   Phase A (levels >= 1): the workgroup stages each tile of two 16-token blocks (K and V rows) once in
 //     LDS, double-buffered; every wave reads the K operand once and multiplies it with both of its query
 //     blocks, likewise the transposed V operand, so the gather traffic of the coarse tokens is paid once
@@ -54,9 +56,11 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int i16 = lane & 15, g = lane >> 4;
-    const int64_t groups = N / (16 * NW * NB);                        // workgroups per head
+    const int64_t nblk = N >> 4;                                      // query tiles per head
+    const int64_t groups = (nblk + NW * NB - 1) / (NW * NB);          // workgroups per head
     const int64_t wg = xcd_contiguous(blockIdx.x, total_wgs);
     const int64_t bh = wg / groups, blk0 = (wg % groups) * (NW * NB);
+    auto tile_of = [&](int b) { return min(blk0 + NB * wave + b, nblk - 1); };
     const float sc2 = t.scale * kLog2e;
 
     bf16x8 qop[NB][KS];
@@ -64,7 +68,7 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D 
     float m[NB], mthr[NB], lsum[NB];                                  // reference, reference + kLazy, this lane's row-sum share
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
-        const uint16_t *qrow = Q + (bh * N + (blk0 + NB * wave + b) * 16 + i16) * D + g * 8;
+        const uint16_t *qrow = Q + (bh * N + tile_of(b) * 16 + i16) * D + g * 8;
 #pragma unroll
         for (int s = 0; s < KS; ++s) qop[b][s] = ld_bf16x8(qrow + 32 * s);
 #pragma unroll
@@ -138,7 +142,7 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D 
     {
         const int b = lane / (64 / NB), j = lane % (64 / NB);
         if (j < nb0) {
-            const int64_t row = (blk0 + NB * wave + b) >> t.ls;
+            const int64_t row = tile_of(b) >> t.ls;
             tok0 = (t.I[0][(bh * t.rows[0] + row) * t.Kl[0] + (j >> t.ls)] << t.lb) + ((j & ((1 << t.ls) - 1)) << 4);
         }
     }
@@ -298,6 +302,7 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D 
     for (int b = 0; b < NB; ++b) {
         const float l = rows_sum(lsum[b]);
         const float inv = 1.f / l;
+        if (blk0 + NB * wave + b >= nblk) break;                      // a spare wave's copy of the head's last tile
         const int64_t row = bh * N + (blk0 + NB * wave + b) * 16 + i16;
         uint16_t *orow = O + row * D + 4 * g;
 #pragma unroll
@@ -313,18 +318,16 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D 
 
 hipError_t launch_attn_fwd_shared(const Plan &p, const LevelTable &t, const void *Q, void *O, float *LSE,
                                   hipStream_t s) {
+    const int64_t wgs = (int64_t)p.bh * ((p.N + 127) / 128);
     if (p.d == 64 && (p.Kl[0] << (p.lb - 4)) <= 32) { // two query blocks per wave (measured faster than one)
         // workgroups of four waves (8 query blocks), four per CU: same occupancy as two of eight waves, cheaper barriers
         // (measured 225 against 229 us)
-        const int64_t wgs = (int64_t)p.bh * (p.N / 128);
         attn_fwd_shared_kernel<64, 2, 4><<<dim3((unsigned)wgs), 256, 0, s>>>(t, (const uint16_t *)Q, (uint16_t *)O, LSE, p.N,
                                                                               wgs);
     } else if (p.d == 64) {                           // K_0 > 32: both level-0 lists would not fit one register
-        const int64_t wgs = (int64_t)p.bh * (p.N / 128);
         attn_fwd_shared_kernel<64, 1><<<dim3((unsigned)wgs), 512, 0, s>>>(t, (const uint16_t *)Q, (uint16_t *)O, LSE, p.N,
                                                                            wgs);
     } else {                                          // d = 128: one query block per wave (registers), 8 per workgroup
-        const int64_t wgs = (int64_t)p.bh * (p.N / 128);
         attn_fwd_shared_kernel<128, 1><<<dim3((unsigned)wgs), 512, 0, s>>>(t, (const uint16_t *)Q, (uint16_t *)O, LSE,
                                                                             p.N, wgs);
     }

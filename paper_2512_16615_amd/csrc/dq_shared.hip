@@ -1,5 +1,5 @@
-// dQ on bf16 MFMA, variant that shares the coarse levels (B = 16, 32 or 64, d = 64 or 128, N a multiple of 256,
-// at most 64 level-0 tiles per list); see attn_fwd_shared.hip for the decomposition (a workgroup of 8 waves owns
+// dQ on bf16 MFMA, variant that shares the coarse levels (B = 16, 32 or 64, d = 64 or 128, at most
+// 64 level-0 tiles per list); see attn_fwd_shared.hip for the decomposition (a workgroup of 8 waves owns
 // 128 consecutive queries, which use the same lists at every level >= 1, every wave one 16-query tile; the coarse
 // key/value tiles are staged once per workgroup in LDS, the level-0 tiles are walked per query tile).
 // Per tile and query block:  S^T = K Q^T, dP^T = V dO^T  ->  dS^T = P^T o (dP^T - D)  ->  dQ^T += K^T dS^T,
@@ -43,9 +43,12 @@ dq_shared_kernel(LevelTable t, const uint16_t *__restrict__ Q, const uint16_t *_
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int i16 = lane & 15, g = lane >> 4;
-    const int64_t groups = N / (128 * NB);                            // workgroups per head (8 * NB query blocks each)
+    const int64_t nblk = N >> 4;                                      // query tiles per head
+    const int64_t groups = (nblk + 8 * NB - 1) / (8 * NB);            // workgroups per head (8 * NB query tiles each)
     const int64_t wg = xcd_contiguous(blockIdx.x, total_wgs);
     const int64_t bh = wg / groups, blk0 = (wg % groups) * (8 * NB);
+    // a spare wave of a head's last workgroup works on the head's last tile without storing it
+    auto tile_of = [&](int b) { return min(blk0 + NB * wave + b, nblk - 1); };
     const float sc2 = t.scale * kLog2e;
 
     bf16x8 qop[NB][KS], gop[NB][KS];
@@ -53,7 +56,7 @@ dq_shared_kernel(LevelTable t, const uint16_t *__restrict__ Q, const uint16_t *_
     float lse2[NB], delta[NB];
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
-        const int64_t qrow = bh * N + (blk0 + NB * wave + b) * 16 + i16;
+        const int64_t qrow = bh * N + tile_of(b) * 16 + i16;
         float dl = 0.f;
 #pragma unroll
         for (int s = 0; s < KS; ++s) {
@@ -68,7 +71,7 @@ dq_shared_kernel(LevelTable t, const uint16_t *__restrict__ Q, const uint16_t *_
             gop[b][s] = to_bf16x8(gw);
         }
         delta[b] = rows_sum(dl);
-        if (g == 0) Dsum[qrow] = delta[b];
+        if (g == 0 && blk0 + NB * wave + b < nblk) Dsum[qrow] = delta[b];
         lse2[b] = LSE[qrow] * kLog2e;
 #pragma unroll
         for (int n = 0; n < NT; ++n) acc[b][n] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -112,7 +115,7 @@ dq_shared_kernel(LevelTable t, const uint16_t *__restrict__ Q, const uint16_t *_
     {
         const int b = lane / (64 / NB), j = lane % (64 / NB);
         if (j < nb0) {
-            const int64_t row = (blk0 + NB * wave + b) >> t.ls;
+            const int64_t row = tile_of(b) >> t.ls;
             tok0 = (t.I[0][(bh * t.rows[0] + row) * t.Kl[0] + (j >> t.ls)] << t.lb) + ((j & ((1 << t.ls) - 1)) << 4);
         }
     }
@@ -261,6 +264,7 @@ dq_shared_kernel(LevelTable t, const uint16_t *__restrict__ Q, const uint16_t *_
 
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
+        if (blk0 + NB * wave + b >= nblk) break;
         uint16_t *orow = dQ + (bh * N + (blk0 + NB * wave + b) * 16 + i16) * D + 4 * g;
 #pragma unroll
         for (int n = 0; n < NT; ++n) {
@@ -274,7 +278,7 @@ dq_shared_kernel(LevelTable t, const uint16_t *__restrict__ Q, const uint16_t *_
 
 hipError_t launch_dq_shared(const Plan &p, const LevelTable &t, const void *Q, const void *O, const void *dO,
                             const float *LSE, float *D, void *dQ, hipStream_t s) {
-    const int64_t wgs = (int64_t)p.bh * (p.N / 128);                  // one query block per wave: 8 per workgroup
+    const int64_t wgs = (int64_t)p.bh * ((p.N + 127) / 128);          // one query tile per wave: 8 per workgroup
     if (p.d == 128) {
         dq_shared_kernel<128, 1><<<dim3((unsigned)wgs), 512, 0, s>>>(t, (const uint16_t *)Q, (const uint16_t *)O,
                                                                       (const uint16_t *)dO, LSE, D, (uint16_t *)dQ, p.N, wgs);

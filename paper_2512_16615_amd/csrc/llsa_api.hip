@@ -82,9 +82,9 @@ static llsa_status build_plan(const llsa_desc &d, Plan &p) {
         off += (size_t)p.bh * p.n[l + 1] * p.Kl[l] * sizeof(int32_t);
     }
     p.idx_bytes = off;
-    // MFMA kernels: bf16, blocks of 1, 2 or 4 16-token tiles, d = 64 / 128, and whole workgroups of 4 query tiles per head
+    // MFMA kernels: bf16, blocks of 1, 2 or 4 16-token tiles (so N is a multiple of 16), d = 64 / 128
     p.fast = d.kernel_path == 0 && d.dtype == LLSA_BF16 && (d.B == 16 || d.B == 32 || d.B == 64) &&
-             (d.d == 64 || d.d == 128) && d.N % 64 == 0;
+             (d.d == 64 || d.d == 128);
     p.lb = !p.fast ? 0 : d.B == 16 ? 4 : d.B == 32 ? 5 : 6;
     // the portable selection holds one row of candidate scores per wave in LDS (the fast one takes any number)
     for (int l = 1; l <= p.L; ++l) {
