@@ -281,7 +281,7 @@ def main():
     ap.add_argument("--no-cpu", action="store_true", help="skip the CPU-oracle leg")
     ap.add_argument("--all-stages", action="store_true", help="after the timed region, one more pass timing every stage")
     ap.add_argument("--dense-compare", action="store_true", help="also time dense bf16 SDPA (forward) on this GPU")
-    ap.add_argument("--force-generic", action="store_true", help="run the portable scalar kernels")
+    ap.add_argument("--force-generic", action="store_true", help="run the fp32-arithmetic kernels that take any shape")
     ap.add_argument("--no-graph", action="store_true", help="time eager launches instead of HIP-graph replays of the step")
     ap.add_argument("--order", default="raster", choices=["raster", "nested"],
                     help="token order of the pixel grid: raster (BASELINE's) or the paper's nested-patch index reordering, "

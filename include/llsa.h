@@ -60,8 +60,8 @@ typedef struct {
     int32_t bwd_repool; /* 1: llsa_backward rebuilds the pooled K/V levels from K, V, so the
                            workspace need not survive between the two calls; 0: backward is
                            given the very workspace llsa_forward filled                     */
-    int32_t kernel_path;/* 0: fastest kernels available for the shape; 1: force the portable
-                           scalar kernels (any supported shape, used as a cross-check)      */
+    int32_t kernel_path;/* 0: fastest kernels available for the shape; 1: force the kernels in
+                           fp32 arithmetic that take any shape (used as a cross-check)      */
     int32_t single_stream; /* 0: llsa_backward may run the index transpose, which depends on
                            the indices only, on one auxiliary stream the plan owns, beside
                            kernels that do not read its lists; the stream is forked from

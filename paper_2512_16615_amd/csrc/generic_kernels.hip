@@ -1,7 +1,5 @@
-// Portable scalar (VALU) kernels for every step of the LLSA layer, any supported shape and both I/O
-// types.  The pooling, selection, index-transpose, D = rowsum(dO*O) and un-pooling kernels here are the
-// ones every configuration uses; the attention / dQ / dK,dV kernels here are the fallback (and the fp32
-// path), the bf16 B=16 shapes normally run the MFMA kernels instead.
+// The steps around the attention, for any supported shape and both I/O types: pooling, the layer glue fused with it, the
+// portable selection, the index transpose, the mask comparator and the index reordering.
 #include "llsa_internal.h"
 
 #include <math.h>
@@ -52,28 +50,6 @@ template <> __device__ __forceinline__ void store_vec<bf16_t>(bf16_t *p, const f
     for (int i = 0; i < 4; ++i)
         w[i] = (uint32_t)from_f<bf16_t>(in[2 * i]).v | ((uint32_t)from_f<bf16_t>(in[2 * i + 1]).v << 16);
     *reinterpret_cast<uint4 *>(p) = make_uint4(w[0], w[1], w[2], w[3]);
-}
-
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-    return v;
-}
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
-
-// plain fp32 dot of a row in global memory with a vector held in LDS (fp32)
-template <class T> __device__ __forceinline__ float dot_row(const T *row, const float *x, int d) {
-    float s = 0.f, tmp[Vec<T>::n];
-    for (int c = 0; c < d; c += Vec<T>::n) {
-        load_vec<T>(row + c, tmp);
-#pragma unroll
-        for (int e = 0; e < Vec<T>::n; ++e) s = fmaf(tmp[e], x[c + e], s);
-    }
-    return s;
 }
 
 // ------------------------------------------------------------------------------------------------ pooling
@@ -383,104 +359,6 @@ hipError_t launch_select(const Plan &p, int l, const void *ws, const int32_t *pa
     return hipGetLastError();
 }
 
-// -------------------------------------------------------------------------------------- gathered-list walk
-// Position `pos` of the list of fine query block `blk` (Alg. 1, enrichment loop): level and token id.
-__device__ __forceinline__ void list_entry(const LevelTable &t, int64_t bh, int64_t blk, int pos, int &lev,
-                                           int &tok) {
-    int l = 0;
-    while (l + 1 < t.nlev && pos >= t.seg[l + 1]) ++l;
-    const int off = pos - t.seg[l];
-    if (l < t.L) {
-        const int64_t row = blk / t.Bpow[l];
-        const int k = off / t.B, u = off % t.B;
-        tok = t.I[l][(bh * t.rows[l] + row) * t.Kl[l] + k] * t.B + u;
-    } else {
-        tok = off;
-    }
-    lev = l;
-}
-
-// ------------------------------------------------------------------------------ attention forward (scalar)
-// Eq. 1-5 restricted to the gathered list, one wave per query row, online softmax over chunks of 64 list
-// entries (lane = entry for the logits, lane = channel for the value accumulation).
-template <class T>
-__global__ void __launch_bounds__(256) attn_fwd_generic(LevelTable t, const T *Q, T *O, float *LSE, int64_t N,
-                                                         int64_t total_rows) {
-    __shared__ float qs[4][128];
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, d = t.d;
-    int64_t row = (int64_t)blockIdx.x * 4 + wave;
-    const bool active = row < total_rows;
-    if (!active) row = total_rows - 1;
-    const int64_t bh = row / N, q = row % N, blk = q / t.B;
-    for (int c = lane; c < d; c += 64) qs[wave][c] = to_f(Q[row * d + c]);
-    __syncthreads();
-    const int M = t.seg[t.nlev];
-    float m = -INFINITY, lsum = 0.f, acc0 = 0.f, acc1 = 0.f;
-    for (int base = 0; base < M; base += 64) {
-        const int pos = base + lane;
-        const bool valid = pos < M;
-        int lev = 0, tok = 0;
-        float z = -INFINITY;
-        if (valid) {
-            list_entry(t, bh, blk, pos, lev, tok);
-            const T *k = static_cast<const T *>(t.K[lev]) + (bh * t.n[lev] + tok) * d;
-            z = t.scale * dot_row<T>(k, qs[wave], d) + t.bias[lev];
-        }
-        const float m_new = fmaxf(m, wave_max(z));
-        const float pr = valid ? expf(z - m_new) : 0.f;
-        const float alpha = expf(m - m_new);
-        lsum = lsum * alpha + wave_sum(pr);
-        acc0 *= alpha;
-        acc1 *= alpha;
-        m = m_new;
-        const int cnt = min(64, M - base);
-        for (int j = 0; j < cnt; ++j) {
-            const float pj = __shfl(pr, j, 64);
-            const int lj = __shfl(lev, j, 64), tj = __shfl(tok, j, 64);
-            const T *v = static_cast<const T *>(t.V[lj]) + (bh * t.n[lj] + tj) * d;
-            if (lane < d) acc0 = fmaf(pj, to_f(v[lane]), acc0);
-            if (lane + 64 < d) acc1 = fmaf(pj, to_f(v[lane + 64]), acc1);
-        }
-    }
-    if (active) {
-        const float inv = 1.f / lsum;
-        if (lane < d) O[row * d + lane] = from_f<T>(acc0 * inv);
-        if (lane + 64 < d) O[row * d + lane + 64] = from_f<T>(acc1 * inv);
-        if (lane == 0) LSE[row] = m + logf(lsum);
-    }
-}
-
-hipError_t launch_attn_fwd_generic(const Plan &p, const LevelTable &t, const void *Q, void *O, float *LSE,
-                                   hipStream_t s) {
-    const int64_t rows = (int64_t)p.bh * p.N;
-    dim3 grid((unsigned)((rows + 3) / 4));
-    if (p.elt == 4) attn_fwd_generic<float><<<grid, 256, 0, s>>>(t, (const float *)Q, (float *)O, LSE, p.N, rows);
-    else attn_fwd_generic<bf16_t><<<grid, 256, 0, s>>>(t, (const bf16_t *)Q, (bf16_t *)O, LSE, p.N, rows);
-    return hipGetLastError();
-}
-
-// ------------------------------------------------------------------------------------- D = rowsum(dO * O)
-template <class T>
-__global__ void __launch_bounds__(256) bwd_pre_kernel(const T *O, const T *dO, float *D, int64_t rows, int d) {
-    const int sub = threadIdx.x & 15;
-    int64_t row = (int64_t)blockIdx.x * 16 + (threadIdx.x >> 4);
-    const bool active = row < rows;
-    if (!active) row = rows - 1;
-    float s = 0.f;
-    for (int c = sub; c < d; c += 16) s = fmaf(to_f(O[row * d + c]), to_f(dO[row * d + c]), s);
-#pragma unroll
-    for (int o = 8; o >= 1; o >>= 1) s += __shfl_xor(s, o, 64);
-    if (active && sub == 0) D[row] = s;
-}
-
-hipError_t launch_bwd_pre(const Plan &p, const void *O, const void *dO, float *D, hipStream_t s) {
-    const int64_t rows = (int64_t)p.bh * p.N;
-    dim3 grid((unsigned)((rows + 15) / 16));
-    if (p.elt == 4) bwd_pre_kernel<float><<<grid, 256, 0, s>>>((const float *)O, (const float *)dO, D, rows, p.d);
-    else bwd_pre_kernel<bf16_t><<<grid, 256, 0, s>>>((const bf16_t *)O, (const bf16_t *)dO, D, rows, p.d);
-    return hipGetLastError();
-}
-
 // -------------------------------------------------------------------------------- index transpose (Alg. 2)
 // count -> exclusive scan -> fill -> per-key ascending order.  Counting and filling use integer atomics;
 // the order they leave inside a key's list depends on timing, so a last pass sorts every list (an entry counts the
@@ -676,159 +554,6 @@ hipError_t launch_csc(const Plan &p, int top, const int32_t *indices, void *ws, 
     return hipGetLastError();
 }
 
-// --------------------------------------------------------------------------------------- dQ (scalar path)
-// Query-major: same list walk as the forward; P recomputed from the saved logsumexp.
-template <class T>
-__global__ void __launch_bounds__(256) dq_generic(LevelTable t, const T *Q, const T *dO, const float *LSE,
-                                                   const float *D, T *dQ, int64_t N, int64_t total_rows) {
-    __shared__ float qs[4][128], gs[4][128];
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, d = t.d;
-    int64_t row = (int64_t)blockIdx.x * 4 + wave;
-    const bool active = row < total_rows;
-    if (!active) row = total_rows - 1;
-    const int64_t bh = row / N, q = row % N, blk = q / t.B;
-    for (int c = lane; c < d; c += 64) { qs[wave][c] = to_f(Q[row * d + c]); gs[wave][c] = to_f(dO[row * d + c]); }
-    __syncthreads();
-    const float lse = LSE[row], delta = D[row];
-    const int M = t.seg[t.nlev];
-    float acc0 = 0.f, acc1 = 0.f;
-    for (int base = 0; base < M; base += 64) {
-        const int pos = base + lane;
-        int lev = 0, tok = 0;
-        float ds = 0.f;
-        if (pos < M) {
-            list_entry(t, bh, blk, pos, lev, tok);
-            const int64_t off = (bh * t.n[lev] + tok) * d;
-            const float z = t.scale * dot_row<T>(static_cast<const T *>(t.K[lev]) + off, qs[wave], d) + t.bias[lev];
-            const float pr = expf(z - lse);
-            const float dp = dot_row<T>(static_cast<const T *>(t.V[lev]) + off, gs[wave], d);
-            ds = pr * (dp - delta);
-        }
-        const int cnt = min(64, M - base);
-        for (int j = 0; j < cnt; ++j) {
-            const float dj = __shfl(ds, j, 64);
-            const int lj = __shfl(lev, j, 64), tj = __shfl(tok, j, 64);
-            const T *k = static_cast<const T *>(t.K[lj]) + (bh * t.n[lj] + tj) * d;
-            if (lane < d) acc0 = fmaf(dj, to_f(k[lane]), acc0);
-            if (lane + 64 < d) acc1 = fmaf(dj, to_f(k[lane + 64]), acc1);
-        }
-    }
-    if (active) {
-        if (lane < d) dQ[row * d + lane] = from_f<T>(t.scale * acc0);
-        if (lane + 64 < d) dQ[row * d + lane + 64] = from_f<T>(t.scale * acc1);
-    }
-}
-
-hipError_t launch_dq_generic(const Plan &p, const LevelTable &t, const void *Q, const void *dO, const float *LSE,
-                             const float *D, void *dQ, hipStream_t s) {
-    const int64_t rows = (int64_t)p.bh * p.N;
-    dim3 grid((unsigned)((rows + 3) / 4));
-    if (p.elt == 4)
-        dq_generic<float><<<grid, 256, 0, s>>>(t, (const float *)Q, (const float *)dO, LSE, D, (float *)dQ, p.N, rows);
-    else
-        dq_generic<bf16_t><<<grid, 256, 0, s>>>(t, (const bf16_t *)Q, (const bf16_t *)dO, LSE, D, (bf16_t *)dQ, p.N,
-                                                rows);
-    return hipGetLastError();
-}
-
-// ------------------------------------------------------------------------------------ dK, dV (scalar path)
-// Key-major (Sec. 4.3): one wave per level-l key token walks the query blocks that listed its block
-// (lists from Alg. 2; at the coarsest enriched level L every query).  Level >= 1 results go to fp32
-// buffers; level 0 adds its parent's share (adjoint of mean pooling) and rounds once to the I/O type.
-template <class T>
-__global__ void __launch_bounds__(256) dkv_generic(LevelTable t, int l, const T *Q, const T *dO, const float *LSE,
-                                                    const float *D, const int32_t *C, const int32_t *Iq,
-                                                    float *dKacc, float *dVacc, const float *parK, const float *parV,
-                                                    T *dK, T *dV, int64_t N, int64_t total_tokens) {
-    __shared__ float ks[4][128], vs[4][128];
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, d = t.d, B = t.B;
-    int64_t tf = (int64_t)blockIdx.x * 4 + wave;           // flat key token over bh * n_l
-    const bool active = tf < total_tokens;
-    if (!active) tf = total_tokens - 1;
-    const int64_t n_l = t.n[l], bh = tf / n_l, tok = tf % n_l;
-    const T *Kl = static_cast<const T *>(t.K[l]), *Vl = static_cast<const T *>(t.V[l]);
-    for (int c = lane; c < d; c += 64) { ks[wave][c] = to_f(Kl[tf * d + c]); vs[wave][c] = to_f(Vl[tf * d + c]); }
-    __syncthreads();
-    const bool dense = (l == t.L);
-    const int64_t span = dense ? 1 : t.Bpow[l + 1];        // fine queries per listed query block
-    int64_t qcount;
-    const int32_t *lst = nullptr;
-    if (dense) {
-        qcount = N;
-    } else {
-        const int64_t T_keys = t.rows[l], j = tok / B;
-        const int32_t beg = C[bh * (T_keys + 1) + j], end = C[bh * (T_keys + 1) + j + 1];
-        lst = Iq + bh * T_keys * t.Kl[l] + beg;
-        qcount = (int64_t)(end - beg) * span;
-    }
-    float dk0 = 0.f, dk1 = 0.f, dv0 = 0.f, dv1 = 0.f;
-    for (int64_t base = 0; base < qcount; base += 64) {
-        const int64_t g = base + lane;
-        float pr = 0.f, ds = 0.f;
-        int64_t qrow = 0;
-        if (g < qcount) {
-            const int64_t q = dense ? g : (int64_t)lst[g / span] * span + g % span;
-            qrow = bh * N + q;
-            const float z = t.scale * dot_row<T>(Q + qrow * d, ks[wave], d) + t.bias[l];
-            pr = expf(z - LSE[qrow]);
-            const float dp = dot_row<T>(dO + qrow * d, vs[wave], d);
-            ds = pr * (dp - D[qrow]);
-        }
-        const int cnt = (int)min((int64_t)64, qcount - base);
-        for (int j = 0; j < cnt; ++j) {
-            const float pj = __shfl(pr, j, 64), dj = __shfl(ds, j, 64);
-            const int64_t rj = __shfl(qrow, j, 64);
-            if (lane < d) {
-                dv0 = fmaf(pj, to_f(dO[rj * d + lane]), dv0);
-                dk0 = fmaf(dj, to_f(Q[rj * d + lane]), dk0);
-            }
-            if (lane + 64 < d) {
-                dv1 = fmaf(pj, to_f(dO[rj * d + lane + 64]), dv1);
-                dk1 = fmaf(dj, to_f(Q[rj * d + lane + 64]), dk1);
-            }
-        }
-    }
-    if (!active) return;
-    dk0 *= t.scale; dk1 *= t.scale;
-    if (l > 0) {
-        if (lane < d) { dKacc[tf * d + lane] = dk0; dVacc[tf * d + lane] = dv0; }
-        if (lane + 64 < d) { dKacc[tf * d + lane + 64] = dk1; dVacc[tf * d + lane + 64] = dv1; }
-    } else {
-        const float invB = 1.f / (float)B;
-        const int64_t par = (bh * t.n[1] + tok / B) * d;   // parent token at level 1
-        if (lane < d) {
-            const float pk = parK ? parK[par + lane] * invB : 0.f, pv = parV ? parV[par + lane] * invB : 0.f;
-            dK[tf * d + lane] = from_f<T>(dk0 + pk);
-            dV[tf * d + lane] = from_f<T>(dv0 + pv);
-        }
-        if (lane + 64 < d) {
-            const float pk = parK ? parK[par + lane + 64] * invB : 0.f, pv = parV ? parV[par + lane + 64] * invB : 0.f;
-            dK[tf * d + lane + 64] = from_f<T>(dk1 + pk);
-            dV[tf * d + lane + 64] = from_f<T>(dv1 + pv);
-        }
-    }
-}
-
-hipError_t launch_dkv_generic(const Plan &p, const LevelTable &t, int l, const void *Q, const void *dO,
-                              const float *LSE, const float *D, void *ws, void *dK, void *dV, hipStream_t s) {
-    char *w = static_cast<char *>(ws);
-    const int64_t total = (int64_t)p.bh * p.n[l];
-    dim3 grid((unsigned)((total + 3) / 4));
-    const int32_t *C = l < p.L ? (const int32_t *)(w + p.C_off[l]) : nullptr;
-    const int32_t *Iq = l < p.L ? (const int32_t *)(w + p.Iq_off[l]) : nullptr;
-    float *ka = l > 0 ? (float *)(w + p.dKacc_off[l]) : nullptr, *va = l > 0 ? (float *)(w + p.dVacc_off[l]) : nullptr;
-    const bool has_parent = (l == 0 && p.Le >= 1);
-    const float *pk = has_parent ? (const float *)(w + p.dKacc_off[1]) : nullptr;
-    const float *pv = has_parent ? (const float *)(w + p.dVacc_off[1]) : nullptr;
-    if (p.elt == 4)
-        dkv_generic<float><<<grid, 256, 0, s>>>(t, l, (const float *)Q, (const float *)dO, LSE, D, C, Iq, ka, va, pk, pv,
-                                                (float *)dK, (float *)dV, p.N, total);
-    else
-        dkv_generic<bf16_t><<<grid, 256, 0, s>>>(t, l, (const bf16_t *)Q, (const bf16_t *)dO, LSE, D, C, Iq, ka, va, pk,
-                                                 pv, (bf16_t *)dK, (bf16_t *)dV, p.N, total);
-    return hipGetLastError();
-}
-
 // ------------------------------------------------------- key-major lists through a dense block mask (comparator)
 // The mask-based baseline of Sec. 5.4 ("Efficient Backward Implementation", Fig. 4): the row-major lists I^(0) are
 // turned into a dense binary T x T block mask and the key/value backward scans it, skipping the unmarked blocks.
@@ -902,29 +627,6 @@ hipError_t launch_mask_lists(const Plan &p, const int32_t *indices, void *ws, vo
     mask_mark_kernel<<<dim3((unsigned)((total + 255) / 256)), 256, 0, s>>>(L.I, static_cast<uint8_t *>(mask), L.cnt, T, L.Kl, total);
     csc_scan_kernel<<<dim3(p.bh, 1), kScanThreads, 0, s>>>(a);
     mask_scan_kernel<<<dim3((unsigned)((nk + 3) / 4)), 256, 0, s>>>(static_cast<const uint8_t *>(mask), L.C, L.Iq, T, eph, nk);
-    return hipGetLastError();
-}
-
-// ------------------------------------------------------------------------------------------------ un-pool
-// Adjoint of one pooling step on the fp32 gradient buffers: level l-1 token t*B + r gains (1/B) of level-l
-// token t (l >= 2 here; the step into level 0 is folded into the level-0 dK/dV epilogue).
-__global__ void __launch_bounds__(256) unpool_kernel(float *dstK, float *dstV, const float *srcK, const float *srcV,
-                                                     int64_t total, int d, int B) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= total) return;
-    const int64_t tok = i / d, c = i % d;
-    const int64_t src = (tok / B) * d + c;                 // flat over bh: n_{l-1} = B * n_l per head
-    const float invB = 1.f / (float)B;
-    dstK[i] += srcK[src] * invB;
-    dstV[i] += srcV[src] * invB;
-}
-
-hipError_t launch_unpool(const Plan &p, int l, void *ws, hipStream_t s) {
-    char *w = static_cast<char *>(ws);
-    const int64_t total = (int64_t)p.bh * p.n[l - 1] * p.d;
-    unpool_kernel<<<(unsigned)((total + 255) / 256), 256, 0, s>>>(
-        (float *)(w + p.dKacc_off[l - 1]), (float *)(w + p.dVacc_off[l - 1]), (const float *)(w + p.dKacc_off[l]),
-        (const float *)(w + p.dVacc_off[l]), total, p.d, p.B);
     return hipGetLastError();
 }
 

@@ -112,7 +112,7 @@ static llsa_status build_plan(const llsa_desc &d, Plan &p) {
         p.Iq_off[l] = ws;    ws = align_up(ws + ent * sizeof(int32_t));
         p.Iqtmp_off[l] = ws; ws = align_up(ws + ent * sizeof(int32_t));
     }
-    for (int l = 1; l <= p.L; ++l) {
+    for (int l = 1; p.fast && l <= p.L; ++l) {
         const size_t bytes = (size_t)p.bh * p.n[l] * p.d * sizeof(float);
         p.dKacc_off[l] = ws; ws = align_up(ws + bytes);
         p.dVacc_off[l] = ws; ws = align_up(ws + bytes);
@@ -130,7 +130,7 @@ static llsa_status build_plan(const llsa_desc &d, Plan &p) {
         p.grp_red_off[1] = ws; ws = align_up(ws + red);
     }
     p.part_off = ws;
-    p.part_bytes = 0;
+    p.part_bytes = p.fast ? 0 : dkv_tile_bytes(p);
     if (p.fast)
         for (int l = p.group ? dkv_group_top(p) + 1 : 1; l <= p.Le; ++l) {   // split slabs of the key-major kernels
             const size_t slab = (size_t)p.bh * ((p.n[l] + 15) / 16) * 16 * p.d * sizeof(float);
@@ -328,7 +328,7 @@ llsa_status llsa_attention(const llsa_plan_t *plan, const void *Q, const void *K
     const Plan &p = plan->p;
     LevelTable t = make_level_table(p, K, V, indices, workspace);
     if (p.fast) LLSA_TRY(launch_attn_fwd_mfma(p, t, Q, O, LSE, (hipStream_t)hip_stream));
-    else LLSA_TRY(launch_attn_fwd_generic(p, t, Q, O, LSE, (hipStream_t)hip_stream));
+    else LLSA_TRY(launch_attn_fwd_tile(p, t, Q, O, LSE, (hipStream_t)hip_stream));
     return LLSA_OK;
 }
 
@@ -430,10 +430,6 @@ llsa_status llsa_backward(const llsa_plan_t *plan, const void *Q, const void *K,
     std::lock_guard<std::mutex> lock(plan->aux.mu);
     Aux *aux = (g_timer.on && g_timer.filter < 0) ? nullptr : aux_for_call(plan, s);
     hipStream_t side = aux ? aux->side : s;
-    if (!p.fast) {                                          // the MFMA dQ kernel produces D itself
-        StageScope sc(kBwdPre, call, s);
-        LLSA_TRY(launch_bwd_pre(p, O, dO, D, s));
-    }
     // Alg. 2 needs only the indices, so it runs on the auxiliary stream beside kernels that do not read its
     // lists.  Where the coarse levels use the grouped kernels (they write per-query-block partials, need no list,
     // and a level above their range is dense and has none), that is behind dQ, in the shadow of those kernels:
@@ -460,7 +456,7 @@ llsa_status llsa_backward(const llsa_plan_t *plan, const void *Q, const void *K,
         {
             StageScope sc(kDq, call, s);
             if (p.fast) LLSA_TRY(launch_dq_mfma(p, t, Q, O, dO, LSE, D, dQ, s));
-            else LLSA_TRY(launch_dq_generic(p, t, Q, dO, LSE, D, dQ, s));
+            else LLSA_TRY(launch_dq_tile(p, t, Q, O, dO, LSE, D, dQ, s));   // both also write D
         }
         if (shadow) LLSA_TRY_ST(transpose());
         // the caller's stream waits for the key-major lists where it first reads them (which also joins the streams)
@@ -468,6 +464,11 @@ llsa_status llsa_backward(const llsa_plan_t *plan, const void *Q, const void *K,
         if (lists && !shadow) {
             LLSA_TRY(hipStreamWaitEvent(s, lists, 0));
             joined = true;
+        }
+        if (!p.fast) {                                      // every level at once
+            StageScope sc(kDkvFine, call, s);
+            LLSA_TRY(launch_dkv_tile(p, t, Q, dO, LSE, D, workspace, dK, dV, s));
+            return LLSA_OK;
         }
         // coarse levels first (fp32), fold them down level by level, then level 0 adds its parent's share
         {
@@ -477,19 +478,10 @@ llsa_status llsa_backward(const llsa_plan_t *plan, const void *Q, const void *K,
                 LLSA_TRY(launch_dkv_group(p, t, Q, dO, LSE, D, workspace, s, shadow ? lists : nullptr, shadow ? side : nullptr,
                                           shadow ? aux->ev[2] : nullptr));
                 if (shadow) joined = true;                  // the grouped launcher waits for the lists before its gathers
-            } else for (int l = p.Le; l >= 1; --l) {
-                if (p.fast) LLSA_TRY(launch_dkv_mfma(p, t, l, Q, dO, LSE, D, workspace, dK, dV, s));
-                else LLSA_TRY(launch_dkv_generic(p, t, l, Q, dO, LSE, D, workspace, dK, dV, s));
-            }
-        }
-        {
-            StageScope sc(kUnpool, call, s);
-            if (!p.fast)                                    // the MFMA path folds this into its slab reduction
-                for (int l = p.Le; l >= 2; --l) LLSA_TRY(launch_unpool(p, l, workspace, s));
+            } else for (int l = p.Le; l >= 1; --l) LLSA_TRY(launch_dkv_mfma(p, t, l, Q, dO, LSE, D, workspace, dK, dV, s));
         }
         StageScope sc(kDkvFine, call, s);
-        if (p.fast) LLSA_TRY(launch_dkv_mfma(p, t, 0, Q, dO, LSE, D, workspace, dK, dV, s));
-        else LLSA_TRY(launch_dkv_generic(p, t, 0, Q, dO, LSE, D, workspace, dK, dV, s));
+        LLSA_TRY(launch_dkv_mfma(p, t, 0, Q, dO, LSE, D, workspace, dK, dV, s));
         return LLSA_OK;
     };
     const llsa_status st = enqueue();

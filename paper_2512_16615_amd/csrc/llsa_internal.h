@@ -25,7 +25,7 @@ struct Plan {
     size_t D_off;                   // [bh, N] fp32: rowsum(dO * O)
     size_t C_off[kMaxL], cnt_off[kMaxL], Iq_off[kMaxL], Iqtmp_off[kMaxL];
     size_t dKacc_off[kMaxL + 1], dVacc_off[kMaxL + 1]; // fp32 gradients of pooled level l (1..L)
-    size_t part_off, part_bytes;    // partial sums of split key-major reductions
+    size_t part_off, part_bytes;    // partial sums of the key-major reductions
     size_t grp_slab_off, grp_red_off[2];   // partials of the query-grouped coarse dK/dV kernel and its reductions
     bool group;                     // coarse levels' dK/dV run grouped by level-1 query block
     size_t ws_fwd, ws_bwd;
@@ -55,7 +55,7 @@ struct LevelTable {
 LevelTable make_level_table(const Plan &p, const void *K0, const void *V0, const int32_t *indices,
                             const void *workspace);
 
-// ---- portable scalar kernels (any supported shape) ----
+// ---- any supported shape ----
 hipError_t launch_pool(const Plan &p, const void *Q, const void *K, const void *V, void *ws, bool q_too,
                        hipStream_t s);
 // QK-Norm + RoPE of Q and K fused with level-1 pooling, then the remaining pooled levels (fills Qout, Kout and ws)
@@ -63,20 +63,20 @@ hipError_t launch_qknorm_rope_pool(const Plan &p, const void *Qpre, const void *
                                    const float *gamma_q, const float *gamma_k, const float *cos_t, const float *sin_t,
                                    float eps, void *Qout, void *Kout, void *ws, hipStream_t s);
 hipError_t launch_select(const Plan &p, int l, const void *ws, const int32_t *parent, int32_t *out, hipStream_t s);
-hipError_t launch_attn_fwd_generic(const Plan &p, const LevelTable &t, const void *Q, void *O, float *LSE,
-                                   hipStream_t s);
-hipError_t launch_bwd_pre(const Plan &p, const void *O, const void *dO, float *D, hipStream_t s);
 hipError_t launch_csc(const Plan &p, int top_level, const int32_t *I, void *ws, hipStream_t s);  // levels 0..top_level
 // level 0's key-major lists through a dense T x T block mask (`mask`: bh * T * T bytes, rounded up to 16) instead of Alg. 2
 hipError_t launch_mask_lists(const Plan &p, const int32_t *indices, void *ws, void *mask, hipStream_t s);
-hipError_t launch_dq_generic(const Plan &p, const LevelTable &t, const void *Q, const void *dO, const float *LSE,
-                             const float *D, void *dQ, hipStream_t s);
-hipError_t launch_dkv_generic(const Plan &p, const LevelTable &t, int l, const void *Q, const void *dO,
-                              const float *LSE, const float *D, void *ws, void *dK, void *dV, hipStream_t s);
-hipError_t launch_unpool(const Plan &p, int l, void *ws, hipStream_t s);
 // nested-patch token order of a 2^bits x 2^bits grid (or back); rows of row_bytes (a multiple of 16) bytes
 hipError_t launch_reorder(int64_t bh, int64_t N, int row_bytes, int bits, int inverse, const void *in, void *out,
                           hipStream_t s);
+
+// ---- attention, dQ (and D = rowsum(dO * O)) and dK / dV of every level in fp32 arithmetic (tile_kernels.hip) ----
+hipError_t launch_attn_fwd_tile(const Plan &p, const LevelTable &t, const void *Q, void *O, float *LSE, hipStream_t s);
+hipError_t launch_dq_tile(const Plan &p, const LevelTable &t, const void *Q, const void *O, const void *dO, const float *LSE,
+                          float *D, void *dQ, hipStream_t s);
+hipError_t launch_dkv_tile(const Plan &p, const LevelTable &t, const void *Q, const void *dO, const float *LSE, const float *D,
+                           void *ws, void *dK, void *dV, hipStream_t s);
+size_t dkv_tile_bytes(const Plan &p);    // workspace of its partial sums
 
 // ---- fast selection (bf16, B = 16 / 32 / 64, K <= 64; any number of candidates, 256 at a time) ----
 bool select_fast_ok(const Plan &p, int l);

@@ -25,3 +25,24 @@ def _bf16(name, N, L=1, heads=3, d=64, B=16, K=8, kind="gaussian", **kw):
 ], ids=lambda c: c["name"])
 def test_lengths_that_fill_no_workgroup(cfg):
     _full_parity(cfg, 0xD15A + cfg["N"])
+
+
+def _tile(name, N, B, K, L, d=64, dtype="f32", heads=2, **kw):
+    return dict(name=name, batch=1, heads=heads, d=d, N=N, B=B, K=K, L=L, dtype=dtype, kind="gaussian", **kw)
+
+
+@pytest.mark.parametrize("cfg", [
+    # fp32 tiles: blocks of one and a quarter tile, of two, of less than one; every channel count; lists of 64 and of 65 tokens;
+    # a dense level with a ragged last tile; coarse lists split over many workgroups; no coarse level in the list
+    _tile("B20_d128", 800, 20, 3, 2, d=128),
+    _tile("B32_d16", 2048, 32, 2, 2, d=16),
+    _tile("B5_d32", 625, 5, 7, 3, d=32),
+    _tile("list_64", 256, 16, 3, 1),
+    _tile("list_65", 17 * 16, 16, 3, 1, heads=3),
+    _tile("split_lists", 8192, 16, 8, 2, heads=1),
+    _tile("B64_Le0", 4096, 64, 2, 2, Le=0),
+    _tile("bf16_B8_d64", 512, 8, 4, 3, dtype="bf16"),
+    _tile("bf16_B16_d32_Le0", 1024, 16, 4, 2, d=32, dtype="bf16", Le=0),
+], ids=lambda c: c["name"])
+def test_fp32_tiles(cfg):
+    _full_parity(cfg, 0xD15B + cfg["N"])
