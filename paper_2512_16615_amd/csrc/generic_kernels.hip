@@ -339,7 +339,8 @@ __global__ void select_kernel(const T *Ql, const T *Kl, int64_t n_l, int d, int 
 }
 
 hipError_t launch_select(const Plan &p, int l, const void *ws, const int32_t *parent, int32_t *out, hipStream_t s) {
-    if (p.desc.kernel_path == 0 && select_fast_ok(p, l)) return launch_select_fast(p, l, ws, parent, out, s);
+    if (select_mfma_ok(p, l)) return launch_select_mfma(p, l, ws, parent, out, s);
+    if (p.desc.kernel_path == 0 && select_dense_ok(p, l)) return launch_select_dense(p, l, ws, parent, out, s);
     const char *w = static_cast<const char *>(ws);
     const bool top = (l == p.L);
     const int C = top ? (int)p.n[l] : p.Kl[l] * p.B;

@@ -86,10 +86,10 @@ static llsa_status build_plan(const llsa_desc &d, Plan &p) {
     p.fast = d.kernel_path == 0 && d.dtype == LLSA_BF16 && (d.B == 16 || d.B == 32 || d.B == 64) &&
              (d.d == 64 || d.d == 128);
     p.lb = !p.fast ? 0 : d.B == 16 ? 4 : d.B == 32 ? 5 : 6;
-    // the portable selection holds one row of candidate scores per wave in LDS (the fast one takes any number)
+    // the portable selection holds one row of candidate scores per wave in LDS (the bf16 ones take any number)
     for (int l = 1; l <= p.L; ++l) {
         const int64_t cand = (l == p.L) ? p.n[l] : (int64_t)p.Kl[l] * p.B;
-        if (cand > kMaxCand && !select_fast_ok(p, l)) return LLSA_ERR_UNSUPPORTED;
+        if (cand > kMaxCand && !select_dense_ok(p, l)) return LLSA_ERR_UNSUPPORTED;
     }
     int64_t m = 0;
     for (int l = 0; l <= p.Le; ++l) m += (l < p.L) ? (int64_t)p.Kl[l] * p.B : p.n[l];
@@ -377,7 +377,7 @@ static llsa_status forward_impl(const llsa_plan_t *plan, const void *Q, const vo
         char *idx = reinterpret_cast<char *>(indices);
         int l = p.L;
         if (select_top_fused(p)) {                          // levels L and L-1 in one launch
-            LLSA_TRY(launch_select_fast(p, p.L - 1, workspace, nullptr, reinterpret_cast<int32_t *>(idx + p.idx_off[p.L - 2]), s,
+            LLSA_TRY(launch_select_mfma(p, p.L - 1, workspace, nullptr, reinterpret_cast<int32_t *>(idx + p.idx_off[p.L - 2]), s,
                                         reinterpret_cast<int32_t *>(idx + p.idx_off[p.L - 1])));
             l = p.L - 2;
         }

@@ -78,10 +78,12 @@ hipError_t launch_dkv_tile(const Plan &p, const LevelTable &t, const void *Q, co
                            void *ws, void *dK, void *dV, hipStream_t s);
 size_t dkv_tile_bytes(const Plan &p);    // workspace of its partial sums
 
-// ---- fast selection (bf16, B = 16 / 32 / 64, K <= 64; any number of candidates, 256 at a time) ----
-bool select_fast_ok(const Plan &p, int l);
+// ---- selection: K <= 16 (any shape), bf16 with B = 16 / 32 / 64 and K <= 64 ----
+bool select_mfma_ok(const Plan &p, int l);
+bool select_dense_ok(const Plan &p, int l);
+hipError_t launch_select_dense(const Plan &p, int l, const void *ws, const int32_t *parent, int32_t *out, hipStream_t s);
 // top_out != null: l = L - 1 and the launch also does level L, writing I^(L-1) to top_out (allowed if select_top_fused)
-hipError_t launch_select_fast(const Plan &p, int l, const void *ws, const int32_t *parent, int32_t *out, hipStream_t s,
+hipError_t launch_select_mfma(const Plan &p, int l, const void *ws, const int32_t *parent, int32_t *out, hipStream_t s,
                               int32_t *top_out = nullptr);
 bool select_top_fused(const Plan &p);
 

@@ -46,3 +46,28 @@ def _tile(name, N, B, K, L, d=64, dtype="f32", heads=2, **kw):
 ], ids=lambda c: c["name"])
 def test_fp32_tiles(cfg):
     _full_parity(cfg, 0xD15B + cfg["N"])
+
+
+@pytest.mark.parametrize("cfg", [
+    # candidates per query at the edges of a wave's 64 and of four waves': 64, 65, 128, 256, 257 and 1024; picks at the edges of
+    # the 8- and 16-entry lists; tiles of fewer queries than 16
+    _bf16("dense_64", 1024, K=8, heads=2),
+    _bf16("dense_65", 1040, K=9, heads=2),
+    _bf16("dense_128_K16", 2048, K=16, heads=1),
+    _bf16("dense_257_K1", 4112, K=1, heads=1),
+    _bf16("sparse_256_K16", 4096, K=16, L=2, heads=1, d=128),
+    _bf16("sparse_1024_B64", 65536, K=16, L=2, heads=1, B=64),
+    _tile("f32_B4_dense_4", 1024, 4, 3, 4, d=16),
+    _tile("f32_B20_dense_340", 6800, 20, 16, 1, d=32, heads=1),
+    _tile("f32_B48_d128", 48 * 48, 48, 5, 2, d=128, heads=1),
+    _tile("f32_K17", 1024, 4, 17, 2, heads=1),
+], ids=lambda c: c["name"])
+def test_selection_of_tied_scores(cfg):
+    """Inputs of a few integers: many equal scores, so the tie rule (lower key id) decides most rows; lists must be exact."""
+    import numpy as np
+    from tests import harness as H
+    x = {n: np.clip(np.round(v), -1, 1) for n, v in H.make_inputs(cfg, 0xD15C).items()}
+    gpu = H.gpu_forward_backward(cfg, x, backward=False)
+    for (b, h), r in H.oracle_all_heads(cfg, x, backward=False).items():
+        for l in range(cfg["L"]):
+            assert np.array_equal(gpu["plan"].level_indices(gpu["indices"], l)[b, h].cpu().numpy(), r["I"][l]), f"level {l}"
