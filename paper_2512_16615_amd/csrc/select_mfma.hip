@@ -72,11 +72,8 @@ template <int CTRL> __device__ __forceinline__ double dpp(double x) {
     const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(x), CTRL, 0xf, 0xf, true);
     return __hiloint2double(hi, lo);
 }
-// both lanes of a pair get the KL best of their two sorted lists of N (all of them while 2 N <= KL)
-template <int CTRL, int N, int KL> __device__ __forceinline__ void merge_lanes(double (&l)[KL]) {
-    double o[N];
-#pragma unroll
-    for (int i = 0; i < N; ++i) o[i] = dpp<CTRL>(l[N - 1 - i]);
+// the KL best of a sorted list of N (in l) and another (o, reversed): all of them while 2 N <= KL
+template <int N, int KL> __device__ __forceinline__ void merge_list(double (&l)[KL], const double (&o)[N]) {
     if constexpr (2 * N <= KL) {
 #pragma unroll
         for (int i = 0; i < N; ++i) {
@@ -91,13 +88,40 @@ template <int CTRL, int N, int KL> __device__ __forceinline__ void merge_lanes(d
         bitonic<N>(l);
     }
 }
-// the 16 lanes of a query, whose lists hold N entries each: pairs, quads (quad_perm), halves (row_half_mirror), row (row_mirror)
+template <int CTRL, int N, int KL> __device__ __forceinline__ void merge_lanes(double (&l)[KL]) {
+    double o[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) o[i] = dpp<CTRL>(l[N - 1 - i]);
+    merge_list<N, KL>(l, o);
+}
+// Two lists a, b (of two queries) per lane of a pair: the lane with `second` keeps b and merges its partner's b into it, the
+// other one keeps a and merges its partner's a, so that every lane goes on with one list instead of two.
+template <int CTRL, int N, int KL> __device__ __forceinline__ void merge_swap(double (&a)[KL], const double (&b)[KL], bool second) {
+    double o[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) o[i] = dpp<CTRL>(second ? a[N - 1 - i] : b[N - 1 - i]);
+#pragma unroll
+    for (int i = 0; i < N; ++i) a[i] = second ? b[i] : a[i];
+    merge_list<N, KL>(a, o);
+}
+// The lists (N sorted entries each) of queries 4g .. 4g+3 in the 16 lanes of group g: afterwards l[0] of lane i16 is the merged
+// list of query 4g + (i16 & 3).  Pairs and quads (quad_perm) halve the number of lists a lane carries, then the quads
+// are merged (row_ror by 4 and by 8 lanes, which keeps the query).
+template <int N, int KL> __device__ __forceinline__ void merge_rows(double (&l)[4][KL], int i16) {
+    constexpr int N1 = 2 * N < KL ? 2 * N : KL, N2 = 2 * N1 < KL ? 2 * N1 : KL, N3 = 2 * N2 < KL ? 2 * N2 : KL;
+    merge_swap<0xb1, N, KL>(l[0], l[1], (i16 & 1) != 0);
+    merge_swap<0xb1, N, KL>(l[2], l[3], (i16 & 1) != 0);
+    merge_swap<0x4e, N1, KL>(l[0], l[2], (i16 & 2) != 0);
+    merge_lanes<0x124, N2, KL>(l[0]);
+    merge_lanes<0x128, N3, KL>(l[0]);
+}
+// one list per lane, all of the same query
 template <int N, int KL> __device__ __forceinline__ void merge_row(double (&l)[KL]) {
     constexpr int N1 = 2 * N < KL ? 2 * N : KL, N2 = 2 * N1 < KL ? 2 * N1 : KL, N3 = 2 * N2 < KL ? 2 * N2 : KL;
     merge_lanes<0xb1, N, KL>(l);
     merge_lanes<0x4e, N1, KL>(l);
-    merge_lanes<0x141, N2, KL>(l);
-    merge_lanes<0x140, N3, KL>(l);
+    merge_lanes<0x124, N2, KL>(l);
+    merge_lanes<0x128, N3, KL>(l);
 }
 __device__ __forceinline__ void sort4(double &a, double &b, double &c, double &d) {
     cmp_swap(a, b); cmp_swap(c, d); cmp_swap(a, c); cmp_swap(b, d); cmp_swap(b, c);
@@ -157,18 +181,20 @@ __device__ __forceinline__ f32x16 score_chunk(const T *qrow, const T *Kb, char *
     return acc;
 }
 
-// position of entry `i16` of the list (its first Kout entries are the winners) and how many winners lie below it
-template <int KL> __device__ __forceinline__ int winner(const double (&l)[KL], int i16, int Kout, int &rank) {
-    int pos[KL], mine = 0;
-    rank = 0;
+// Entries first, first + 4, ... of a list whose first Kout entries are the winners: emit(position, winners below it).
+template <int KL, class Emit> __device__ __forceinline__ void winners(const double (&l)[KL], int first, int Kout, Emit emit) {
+    int pos[KL];
 #pragma unroll
-    for (int i = 0; i < KL; ++i) {
-        pos[i] = i < Kout ? key_pos(l[i]) : 0x7fffffff;
-        mine = i16 == i ? pos[i] : mine;
+    for (int i = 0; i < KL; ++i) pos[i] = i < Kout ? key_pos(l[i]) : 0x7fffffff;
+#pragma unroll
+    for (int j = 0; j < KL; j += 4) {
+        int mine = pos[j], rank = 0;
+#pragma unroll
+        for (int x = 1; x < 4; ++x) mine = first == x ? pos[j + x] : mine;
+#pragma unroll
+        for (int i = 0; i < KL; ++i) rank += pos[i] < mine ? 1 : 0;
+        if (j + first < Kout) emit(mine, rank);
     }
-#pragma unroll
-    for (int i = 0; i < KL; ++i) rank += pos[i] < mine ? 1 : 0;
-    return mine;
 }
 
 // NW waves; ONE: at most one chunk of 64 candidates each.  TOP: the launch is level L-1 and also does level L, dense over at most 64 tokens: the first wave of every
@@ -193,6 +219,7 @@ __global__ void __launch_bounds__(64 * NW) select_mfma_kernel(SelLevel a, int B,
     const T *Kb = static_cast<const T *>(a.K) + bh * a.n * D;
     const T *qrow = static_cast<const T *>(a.Q) + (bh * a.n + first + min(i16, nq - 1)) * D;
     char *my = lds + wave * 64 * S::STRIDE;
+    const unsigned magic = 0xffffffffu / (unsigned)B + 1;        // ceil(2^32 / B), also for powers of two
 
     if constexpr (TOP) {
         if (wave == 0) {
@@ -210,12 +237,11 @@ __global__ void __launch_bounds__(64 * NW) select_mfma_kernel(SelLevel a, int B,
             }
             sort4(l[0], l[1], l[2], l[3]);
             merge_row<4, KL>(l);
-            int rank;
-            const int mine = winner<KL>(l, i16, top.Kout, rank);
-            if (g == (int)((blk & 15) >> 2) && i16 < top.Kout) {
-                prow[rank] = mine;
-                if (sub == 0) top.out[(bh * nt + blk) * top.Kout + rank] = mine;
-            }
+            if (g == (int)((blk & 15) >> 2) && i16 < 4)
+                winners<KL>(l, i16, top.Kout, [&](int pos, int rank) {
+                    prow[rank] = pos;
+                    if (sub == 0) top.out[(bh * nt + blk) * top.Kout + rank] = pos;
+                });
         }
         __syncthreads();
     } else if (!dense) {
@@ -224,48 +250,30 @@ __global__ void __launch_bounds__(64 * NW) select_mfma_kernel(SelLevel a, int B,
     }
     auto id_of = [&](int p) -> int {
         if (dense) return p;
-        const int k = (int)((unsigned)p / (unsigned)B);
+        const int k = (int)__umulhi((unsigned)p, magic);         // p / B: exact for p < 2^20, B <= 64
         return prow[k] * B + (p - k * B);
     };
 
-    // A query's list: the wave's own merged one goes to LDS (its staged rows are done with), then wave w merges the waves'
-    // lists of queries 4g + r, r % NW == w, and writes their rows.
-    double *ex = reinterpret_cast<double *>(my);                 // [query][KL]
-    auto finish = [&](int r, double (&l)[KL]) {
-        int rank;
-        const int mine = winner<KL>(l, i16, a.Kout, rank);
-        if (i16 < a.Kout && 4 * g + r < nq) a.out[(bh * a.n + first + 4 * g + r) * a.Kout + rank] = id_of(mine);
-    };
-    auto publish = [&](int r, double (&l)[KL]) {
-        if constexpr (NW == 1) finish(r, l);
-        else if (i16 == r) {
-#pragma unroll
-            for (int i = 0; i < KL; ++i) ex[(4 * g + r) * KL + i] = l[i];
-        }
-    };
     auto keys = [&](const f32x16 &acc, int c, int r, double (&k)[4]) {
 #pragma unroll
-        for (int b = 0; b < 4; ++b) {
-            const int p = 64 * c + 16 * b + i16;
-            k[b] = p < a.C ? make_key(acc[4 * b + r], (uint32_t)p) : 0.0;
-        }
+        for (int b = 0; b < 4; ++b) k[b] = make_key(acc[4 * b + r], (uint32_t)(64 * c + 16 * b + i16));
+        if (64 * c + 64 > a.C)                                   // the last chunk: positions past the candidates
+#pragma unroll
+            for (int b = 0; b < 4; ++b) k[b] = 64 * c + 16 * b + i16 < a.C ? k[b] : 0.0;
     };
-    if constexpr (ONE) {                                         // at most one chunk per wave: one query's list at a time
-        const int p = 64 * wave + lane;
-        const f32x16 acc = score_chunk<T, D>(qrow, Kb, my, lane, id_of(min(p, a.C - 1)));
-        __builtin_amdgcn_wave_barrier();
+    double l[4][KL];                                             // this lane's lists of queries 4g + r
+    if constexpr (ONE) {                                         // at most one chunk per wave
+        const f32x16 acc = score_chunk<T, D>(qrow, Kb, my, lane, id_of(min(64 * wave + lane, a.C - 1)));
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            double l[KL], k[4];
+            double k[4];
             keys(acc, wave, r, k);
             sort4(k[0], k[1], k[2], k[3]);
 #pragma unroll
-            for (int b = 0; b < 4; ++b) l[b] = k[b];
-            merge_row<4, KL>(l);
-            publish(r, l);
+            for (int b = 0; b < 4; ++b) l[r][b] = k[b];
         }
+        merge_rows<4, KL>(l, i16);
     } else {
-        double l[4][KL];
 #pragma unroll
         for (int r = 0; r < 4; ++r)
 #pragma unroll
@@ -279,29 +287,29 @@ __global__ void __launch_bounds__(64 * NW) select_mfma_kernel(SelLevel a, int B,
                 insert4<KL>(l[r], k[0], k[1], k[2], k[3]);
             }
         }
-        __builtin_amdgcn_wave_barrier();
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            merge_row<KL, KL>(l[r]);
-            publish(r, l[r]);
-        }
+        merge_rows<KL, KL>(l, i16);
     }
+    // lane i16 holds the wave's list of query 4g + i16 % 4; the first wave merges in the other waves' lists, through LDS
+    const int qi = 4 * g + (i16 & 3);
     if constexpr (NW > 1) {
+        double *ex = reinterpret_cast<double *>(my) + qi * KL;   // (the wave's staged rows are done with)
+        __builtin_amdgcn_wave_barrier();
+        if (wave > 0 && i16 < 4)
+#pragma unroll
+            for (int i = 0; i < KL; ++i) ex[i] = l[0][i];
         __syncthreads();
+        if (wave > 0) return;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            if (r % NW != wave) continue;
-            double l[KL];
+        for (int x = 1; x < NW; ++x) {
+            const double *src = reinterpret_cast<const double *>(lds + x * 64 * S::STRIDE) + qi * KL;
+            double o[KL];
 #pragma unroll
-            for (int x = 0; x < NW; ++x) {
-                const double *o = reinterpret_cast<const double *>(lds + x * 64 * S::STRIDE) + (4 * g + r) * KL;
-#pragma unroll
-                for (int i = 0; i < KL; ++i) l[i] = x == 0 ? o[i] : fmax(l[i], o[KL - 1 - i]);
-                if (x > 0) bitonic<KL>(l);
-            }
-            finish(r, l);
+            for (int i = 0; i < KL; ++i) o[i] = src[KL - 1 - i];
+            merge_list<KL, KL>(l[0], o);
         }
     }
+    if (qi < nq)
+        winners<KL>(l[0], i16 >> 2, a.Kout, [&](int pos, int rank) { a.out[(bh * a.n + first + qi) * a.Kout + rank] = id_of(pos); });
 }
 
 // K <= 16 and positions that fit their 20 bits
