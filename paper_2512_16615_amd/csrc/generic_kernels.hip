@@ -361,11 +361,8 @@ hipError_t launch_select(const Plan &p, int l, const void *ws, const int32_t *pa
 }
 
 // -------------------------------------------------------------------------------- index transpose (Alg. 2)
-// count -> exclusive scan -> fill -> per-key ascending order.  Counting and filling use integer atomics;
-// the order they leave inside a key's list depends on timing, so a last pass sorts every list (an entry counts the
-// smaller ones of its list; lists of more than 4096 entries: a bitmap of the list's rows), which makes
-// the result (and with it the summation order of dK / dV) the same on every run.
-// All levels run in the same launches: blockIdx.y selects the level.
+// Key-major lists, every list ascending, so that the result (and with it the summation order of dK / dV) is the same on
+// every run.  All levels run in the same launches.
 struct CscLevel {
     const int32_t *I;            // I^(l) [bh, T, Kl]
     int32_t *cnt, *C, *Iq, *Iq_tmp;
@@ -374,6 +371,102 @@ struct CscLevel {
 };
 struct CscLevels { CscLevel lv[kMaxL]; };
 
+// Levels of at most kBitmapRows rows (keys and query blocks per head), one launch, no scratch memory: a workgroup makes the
+// lists of kRangeKeys consecutive keys of one head.  It reads all of the head's entries (from L2: 32 KB .. 256 KB), marks the
+// rows that list one of its keys in a bitmap of a row per key in LDS and counts the entries of the keys below its own (their
+// number is where its lists start); then every group of lanes turns a key's bitmap into its ascending list.  Marking has no
+// order, so neither a fill in order nor a sort is needed.  Against count, scan, fill and sort in launches of their own this
+// saves four launches, which is most of the time up to 1024 rows, and the sort's passes over the lists beyond.  Reading grows
+// with rows^2, hence the limit; 32 keys keep the bitmap at 16 KB for 4096 rows, so that a workgroup finds room beside the
+// LDS-bound dK/dV kernels it runs in the shadow of.
+// grid.x: ranges of level 0's heads, then level 1's, ...
+constexpr int kBitmapRows = 8192, kRangeKeys = 32;
+struct CscRanges { CscLevel lv[kMaxL]; unsigned wg_end[kMaxL]; };
+__global__ void __launch_bounds__(256) csc_bitmap_kernel(CscRanges a) {
+    extern __shared__ __attribute__((aligned(16))) uint32_t bm[];   // [kRangeKeys][words], words = rows in 64s, times 2
+    __shared__ int32_t tot[kRangeKeys], below_sh[4];
+    int l = 0;
+    while (blockIdx.x >= a.wg_end[l]) ++l;
+    const CscLevel &L = a.lv[l];
+    const unsigned id = blockIdx.x - (l ? a.wg_end[l - 1] : 0), T = (unsigned)L.T, E = (unsigned)L.eph;
+    const unsigned ranges = (T + kRangeKeys - 1) / kRangeKeys, bh = id / ranges, r0 = (id - bh * ranges) * kRangeKeys;
+    const unsigned words = ((T + 63) >> 6) * 2;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    for (unsigned i = tid; i < kRangeKeys * words; i += 256) bm[i] = 0;
+    if (tid < kRangeKeys) tot[tid] = 0;
+    __syncthreads();
+    const int32_t *I = L.I + (int64_t)bh * E;
+    int32_t below = 0;
+    auto mark = [&](unsigned e, unsigned key) {
+        below += key < r0 ? 1 : 0;
+        if (key - r0 < (unsigned)kRangeKeys) {
+            const unsigned row = e / (unsigned)L.Kl;
+            atomicOr(&bm[(key - r0) * words + (row >> 5)], 1u << (row & 31));
+            atomicAdd(&tot[key - r0], 1);
+        }
+    };
+    unsigned e = tid;
+    for (; e + 7 * 256 < E; e += 8 * 256) {                 // eight loads in flight
+        int32_t k[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) k[u] = I[e + 256 * u];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) mark(e + 256 * u, (unsigned)k[u]);
+    }
+    for (; e < E; e += 256) mark(e, (unsigned)I[e]);
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) below += __shfl_xor(below, o, 64);
+    if (lane == 0) below_sh[wave] = below;
+    __syncthreads();
+    // every wave scans the 32 counts for itself
+    const int32_t n = lane < kRangeKeys ? tot[lane] : 0;
+    int32_t start = n;
+#pragma unroll
+    for (int o = 1; o < kRangeKeys; o <<= 1) {
+        const int32_t y = __shfl_up(start, o, 64);
+        if (lane >= o) start += y;
+    }
+    start += below_sh[0] + below_sh[1] + below_sh[2] + below_sh[3] - n;
+    int32_t *C = L.C + (int64_t)bh * (T + 1);
+    if (wave == 0 && lane < kRangeKeys && r0 + lane < T) C[r0 + lane] = start;
+    if (tid == 0 && r0 + kRangeKeys >= T) C[T] = (int32_t)E;
+    // G lanes per key, each over 64-row words G apart
+    int32_t *Iq = L.Iq + (int64_t)bh * E;
+    const unsigned w64 = words / 2;
+    int G = 1;
+    while (G < 64 && (unsigned)G < w64) G <<= 1;
+    const int sub = lane & (G - 1), per = 64 / G;           // keys of a wave at a time
+    for (int k0 = wave * per; k0 < kRangeKeys; k0 += 4 * per) {
+        const int k = k0 + lane / G;                        // 64 / G <= 32 keys or, for one word, two passes' worth of lanes
+        const int kk = min(k, kRangeKeys - 1);
+        const int32_t cnt = k < kRangeKeys ? __shfl(n, kk, 64) : 0;
+        int32_t pos = __shfl(start, kk, 64);
+        const int32_t end = pos + cnt;
+        if (__ballot(cnt > 0) == 0) continue;
+        for (unsigned w0 = 0; w0 < w64; w0 += G) {
+            uint64_t bits = 0;
+            if (cnt > 0 && w0 + sub < w64) bits = *reinterpret_cast<const uint64_t *>(&bm[kk * words + 2 * (w0 + sub)]);
+            int32_t mine = __popcll(bits), incl = mine;
+            for (int o = 1; o < G; o <<= 1) {
+                const int32_t y = __shfl_up(incl, o, 64);
+                if (sub >= o) incl += y;
+            }
+            int32_t at = pos + incl - mine;
+            while (bits) {
+                Iq[at++] = (int32_t)(64 * (w0 + sub)) + (int32_t)__builtin_ctzll(bits);
+                bits &= bits - 1;
+            }
+            pos += __shfl(incl, (lane & ~(G - 1)) + G - 1, 64);
+        }
+        // a key listed twice by one row (no valid selection has that) is marked once: fill its list with the last row
+        if (sub == 0)
+            for (; pos < end; ++pos) Iq[pos] = (int32_t)T - 1;
+    }
+}
+
+// Larger levels: count -> exclusive scan -> fill -> per-key ascending order.  Counting and filling use integer atomics; the
+// order they leave inside a key's list depends on timing, so a last pass sorts every list (an entry counts the smaller ones of
+// its list; lists of more than 4096 entries: a bitmap of the list's rows).  blockIdx.y selects the level.
 __global__ void csc_zero_kernel(CscLevels a) {
     const CscLevel &L = a.lv[blockIdx.y];
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
@@ -439,8 +532,7 @@ __global__ void csc_fill_kernel(CscLevels a) {
 }
 // one thread per list entry: its rank among the entries of the same key (entries are distinct query rows)
 // is its place in the key's ascending list.  The unsorted list is re-read through the caches.
-// Lists longer than kLongList are left to csc_sort_long_kernel (this pass costs len reads per entry).  A list is no
-// longer than the level has rows, so levels of up to kLongList rows (the headline's level 0 has 4096) need no second pass.
+// Lists longer than kLongList are left to csc_sort_long_kernel (this pass costs len reads per entry).
 constexpr int kLongList = 4096;
 __global__ void __launch_bounds__(256) csc_sort_kernel(CscLevels a) {
     const CscLevel &L = a.lv[blockIdx.y];
@@ -524,7 +616,7 @@ __global__ void __launch_bounds__(256) csc_sort_long_kernel(CscLevels a) {
     }
 }
 
-// Alg. 2 for levels 0 .. top (the levels whose lists the backward uses), five launches in all (six for long levels)
+// Alg. 2 for levels 0 .. top (the levels whose lists the backward uses)
 hipError_t launch_csc(const Plan &p, int top, const int32_t *indices, void *ws, hipStream_t s) {
     char *w = static_cast<char *>(ws);
     CscLevels a;
@@ -544,14 +636,25 @@ hipError_t launch_csc(const Plan &p, int top, const int32_t *indices, void *ws, 
         if (L.nk > max_nk) max_nk = L.nk;
         if (L.total > max_total) max_total = L.total;
     }
+    if (p.n[1] <= kBitmapRows) {                            // level 0 has the most rows
+        CscRanges r;
+        int64_t wg = 0;
+        for (int l = 0; l <= top; ++l) {
+            r.lv[l] = a.lv[l];
+            wg += p.bh * ((a.lv[l].T + kRangeKeys - 1) / kRangeKeys);
+            r.wg_end[l] = (unsigned)wg;
+        }
+        const size_t lds = (size_t)kRangeKeys * ((p.n[1] + 63) / 64) * 8;
+        csc_bitmap_kernel<<<(unsigned)wg, 256, lds, s>>>(r);
+        return hipGetLastError();
+    }
     const unsigned nl = (unsigned)(top + 1);
     csc_zero_kernel<<<dim3((unsigned)((max_nk + 255) / 256), nl), 256, 0, s>>>(a);
     csc_count_kernel<<<dim3((unsigned)((max_total + 255) / 256), nl), 256, 0, s>>>(a);
     csc_scan_kernel<<<dim3(p.bh, nl), kScanThreads, 0, s>>>(a);
     csc_fill_kernel<<<dim3((unsigned)((max_total + 255) / 256), nl), 256, 0, s>>>(a);
     csc_sort_kernel<<<dim3((unsigned)((max_total + 255) / 256), nl), 256, 0, s>>>(a);
-    if (p.n[1] > kLongList)                                 // level 0 has the most rows; no list is longer than its level's rows
-        csc_sort_long_kernel<<<dim3((unsigned)((max_nk + 255) / 256), nl), 256, 0, s>>>(a);
+    csc_sort_long_kernel<<<dim3((unsigned)((max_nk + 255) / 256), nl), 256, 0, s>>>(a);
     return hipGetLastError();
 }
 

@@ -71,3 +71,34 @@ def test_selection_of_tied_scores(cfg):
     for (b, h), r in H.oracle_all_heads(cfg, x, backward=False).items():
         for l in range(cfg["L"]):
             assert np.array_equal(gpu["plan"].level_indices(gpu["indices"], l)[b, h].cpu().numpy(), r["I"][l]), f"level {l}"
+
+
+@pytest.mark.parametrize("T,K,heads", [(1, 1, 2), (33, 3, 3), (64, 8, 2), (65, 5, 2), (4096, 8, 2), (8191, 2, 1), (8192, 8, 1), (8193, 3, 1)])
+def test_index_transpose_by_size(T, K, heads):
+    """Alg. 2 on forced lists at the edges of its two paths: few rows, rows that fill no 64-row word, the largest level of the
+    one-launch path and the smallest beyond it; one key listed by every row, the last keys listed by none."""
+    import numpy as np
+    import torch
+    from oracle import llsa_oracle as orc
+    from tests import harness as H
+    from paper_2512_16615_amd import llsa
+    cfg = dict(batch=1, heads=heads, d=64, N=16 * T, B=16, K=K, L=1, dtype="bf16")
+    plan = H.make_plan(cfg)
+    ws, idx = plan.alloc_workspace(True), plan.alloc_indices()
+    rng = np.random.default_rng(T)
+    top = max(K, T - T // 8)
+    I = np.stack([np.stack([np.sort(rng.choice(min(top, 4 * K) if r % 3 else top, K, replace=False)) for r in range(T)])
+                  for _ in range(heads)]).astype(np.int32)
+    I[0, :, 0] = 0
+    for r in range(T):                                       # keep the rows ascending and distinct with key 0 in each
+        if K > 1 and I[0, r, 1] == 0:
+            I[0, r] = np.arange(K)
+    plan.level_indices(idx, 0).copy_(torch.from_numpy(I).cuda().view(1, heads, T, K))
+    ws.fill_(0x7F)
+    llsa.index_transpose(plan, idx, ws)
+    torch.cuda.synchronize()
+    C, Iq = plan.csc_level(ws, 0)
+    for h in range(heads):
+        iq_ref, c_ref = orc.transpose(I[h], T)
+        assert np.array_equal(C[h].cpu().numpy(), c_ref)
+        assert np.array_equal(Iq[h].cpu().numpy(), iq_ref)
