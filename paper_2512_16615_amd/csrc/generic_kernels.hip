@@ -368,10 +368,13 @@ struct CscLevel {
     int32_t *cnt, *C, *Iq, *Iq_tmp;
     int64_t T, eph, total, nk;   // keys per head, entries per head, entries, keys
     int Kl;
+    uint32_t *cnt8;              // segment path: [bh][group][Tp][kSegPerGroup] bytes
+    int32_t *tot;                // [bh][group][Tp]: a group's entries of a key, then where they start
+    int Tp, ngrp;                // T rounded up to 4; groups
 };
 struct CscLevels { CscLevel lv[kMaxL]; };
 
-// Levels of at most kBitmapRows rows (keys and query blocks per head), one launch, no scratch memory: a workgroup makes the
+// Few rows (csc_one_launch), one launch, no scratch memory: a workgroup makes the
 // lists of kRangeKeys consecutive keys of one head.  It reads all of the head's entries (from L2: 32 KB .. 256 KB), marks the
 // rows that list one of its keys in a bitmap of a row per key in LDS and counts the entries of the keys below its own (their
 // number is where its lists start); then every group of lanes turns a key's bitmap into its ascending list.  Marking has no
@@ -379,8 +382,8 @@ struct CscLevels { CscLevel lv[kMaxL]; };
 // saves four launches, which is most of the time up to 1024 rows, and the sort's passes over the lists beyond.  Reading grows
 // with rows^2, hence the limit; 32 keys keep the bitmap at 16 KB for 4096 rows, so that a workgroup finds room beside the
 // LDS-bound dK/dV kernels it runs in the shadow of.
-// grid.x: ranges of level 0's heads, then level 1's, ...
-constexpr int kBitmapRows = 8192, kRangeKeys = 32;
+// grid.x: ranges of level 0's heads, then level 1's, ... (also in the kernels of the segment path)
+constexpr int kRangeKeys = 32;
 struct CscRanges { CscLevel lv[kMaxL]; unsigned wg_end[kMaxL]; };
 __global__ void __launch_bounds__(256) csc_bitmap_kernel(CscRanges a) {
     extern __shared__ __attribute__((aligned(16))) uint32_t bm[];   // [kRangeKeys][words], words = rows in 64s, times 2
@@ -464,7 +467,134 @@ __global__ void __launch_bounds__(256) csc_bitmap_kernel(CscRanges a) {
     }
 }
 
-// Larger levels: count -> exclusive scan -> fill -> per-key ascending order.  Counting and filling use integer atomics; the
+// More rows, up to kSegRowsMax, three launches, O(T K) work: rows are taken in segments of 128, and segments in groups of 16.
+//   count: per (group of 2048 rows, 1024 keys) the number of entries of every (segment, key), one byte each, counted in LDS,
+//     and the group's sum per key;
+//   scan: per head, the sums over the groups and then over the keys: C, and where each group's entries of a key start;
+//   fill: per (segment, 1024 keys) a bitmap of 128 rows per key in LDS; an entry's place is the start of its group, plus the
+//     counts of the group's earlier segments (one 16-byte load, summed bytewise), plus the marked rows below its own.
+// Nothing is sorted and every place follows from counts, so the lists are ascending and the same on every run.  The kernels
+// stay below 48 registers: that is what the upper-level dK/dV kernel, in whose shadow they run, leaves of a SIMD's 512.
+constexpr int kSegRowsMax = 16384, kSegR = 128, kSegPerGroup = 16, kGroupRows = kSegR * kSegPerGroup, kKeyRange = 1024;
+// every entry of rows row0 .. row1 - 1 with key - k0 < kKeyRange: f(row, key - k0)
+template <class F> __device__ __forceinline__ void range_entries(const int32_t *I, unsigned Kl, unsigned row0, unsigned row1, unsigned k0, F f) {
+    const unsigned e1 = row1 * Kl;
+    for (unsigned e = row0 * Kl + threadIdx.x; e < e1; e += 4 * 256) {
+        int32_t k[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) k[u] = e + 256 * u < e1 ? I[e + 256 * u] : -1;
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if ((unsigned)k[u] - k0 < (unsigned)kKeyRange) f((e + 256 * u) / Kl, (unsigned)k[u] - k0);
+    }
+}
+__global__ void __launch_bounds__(256) csc_seg_count_kernel(CscRanges a) {
+    __shared__ __attribute__((aligned(16))) uint32_t cnt[kKeyRange * 4];
+    int l = 0;
+    while (blockIdx.x >= a.wg_end[l]) ++l;
+    const CscLevel &L = a.lv[l];
+    const unsigned id = blockIdx.x - (l ? a.wg_end[l - 1] : 0), T = (unsigned)L.T, Tp = (unsigned)L.Tp;
+    const unsigned ranges = (T + kKeyRange - 1) / kKeyRange, hg = id / ranges, k0 = (id - hg * ranges) * kKeyRange;
+    const unsigned bh = hg / (unsigned)L.ngrp, grp = hg - bh * L.ngrp;
+    for (unsigned i = threadIdx.x; i < kKeyRange; i += 256) reinterpret_cast<uint4 *>(cnt)[i] = make_uint4(0u, 0u, 0u, 0u);
+    __syncthreads();
+    range_entries(L.I + (int64_t)bh * L.eph, (unsigned)L.Kl, grp * kGroupRows, min(T, (grp + 1) * kGroupRows), k0, [&](unsigned row, unsigned k) {
+        const unsigned seg = (row / kSegR) % kSegPerGroup;
+        atomicAdd(&cnt[4 * k + (seg >> 2)], 1u << (8 * (seg & 3)));
+    });
+    __syncthreads();
+    for (unsigned i = threadIdx.x; i < kKeyRange && k0 + i < T; i += 256) {
+        const uint4 c = reinterpret_cast<const uint4 *>(cnt)[i];
+        const int64_t o = (int64_t)hg * Tp + k0 + i;
+        reinterpret_cast<uint4 *>(L.cnt8)[o] = c;
+        L.tot[o] = (int32_t)__builtin_amdgcn_sad_u8(c.x, 0u, __builtin_amdgcn_sad_u8(c.y, 0u, __builtin_amdgcn_sad_u8(c.z, 0u, __builtin_amdgcn_sad_u8(c.w, 0u, 0u))));
+    }
+}
+__global__ void __launch_bounds__(256) csc_seg_scan_kernel(CscLevels a) {
+    __shared__ int32_t wsum[2][4];
+    const CscLevel &L = a.lv[blockIdx.y];
+    const int64_t bh = blockIdx.x;
+    const int T = (int)L.T, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    int32_t *Co = L.C + bh * (T + 1), *tot = L.tot + bh * L.ngrp * L.Tp;
+    int32_t carry = 0;
+    for (int base = 0, turn = 0; base < T; base += 1024, turn ^= 1) {
+        const int i0 = base + 4 * threadIdx.x;              // four consecutive keys per thread
+        auto group = [&](int g) {                           // a group's entries of the keys
+            int4 v = make_int4(0, 0, 0, 0);
+            if (i0 < T) v = *reinterpret_cast<const int4 *>(tot + g * L.Tp + i0);
+            if (i0 + 1 >= T) v.y = 0;
+            if (i0 + 2 >= T) v.z = 0;
+            if (i0 + 3 >= T) v.w = 0;
+            return v;
+        };
+        int4 key = make_int4(0, 0, 0, 0);                   // the keys' totals
+#pragma unroll 2
+        for (int g = 0; g < L.ngrp; ++g) {
+            const int4 v = group(g);
+            key.x += v.x; key.y += v.y; key.z += v.z; key.w += v.w;
+        }
+        const int32_t mine = key.x + key.y + key.z + key.w;
+        int32_t x = mine;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {                  // inclusive scan of the threads' sums inside the wave
+            const int32_t y = __shfl_up(x, o, 64);
+            if (lane >= o) x += y;
+        }
+        if (lane == 63) wsum[turn][wave] = x;
+        __syncthreads();                                    // (two buffers: the next turn may write before this one is read)
+        int32_t pre = carry;
+        for (int w = 0; w < wave; ++w) pre += wsum[turn][w];
+        for (int w = 0; w < 4; ++w) carry += wsum[turn][w];
+        int4 at;                                            // where each key's list starts
+        at.x = pre + x - mine; at.y = at.x + key.x; at.z = at.y + key.y; at.w = at.z + key.z;
+        if (i0 < T) Co[i0] = at.x;
+        if (i0 + 1 < T) Co[i0 + 1] = at.y;
+        if (i0 + 2 < T) Co[i0 + 2] = at.z;
+        if (i0 + 3 < T) Co[i0 + 3] = at.w;
+        for (int g = 0; g < L.ngrp; ++g) {
+            const int4 v = group(g);
+            if (i0 < T) *reinterpret_cast<int4 *>(tot + g * L.Tp + i0) = at;
+            at.x += v.x; at.y += v.y; at.z += v.z; at.w += v.w;
+        }
+    }
+    if (threadIdx.x == 0) Co[T] = carry;
+}
+__global__ void __launch_bounds__(256) csc_seg_fill_kernel(CscRanges a) {
+    __shared__ __attribute__((aligned(16))) uint32_t bm[kKeyRange * 4];
+    int l = 0;
+    while (blockIdx.x >= a.wg_end[l]) ++l;
+    const CscLevel &L = a.lv[l];
+    const unsigned id = blockIdx.x - (l ? a.wg_end[l - 1] : 0), T = (unsigned)L.T, Tp = (unsigned)L.Tp;
+    const unsigned ranges = (T + kKeyRange - 1) / kKeyRange, segs = (T + kSegR - 1) / kSegR;
+    const unsigned hs = id / ranges, k0 = (id - hs * ranges) * kKeyRange, bh = hs / segs, seg = hs - bh * segs;
+    const int32_t *I = L.I + (int64_t)bh * L.eph;
+    for (unsigned i = threadIdx.x; i < kKeyRange; i += 256) reinterpret_cast<uint4 *>(bm)[i] = make_uint4(0u, 0u, 0u, 0u);
+    __syncthreads();
+    const unsigned row0 = seg * kSegR, row1 = min(T, row0 + kSegR), grp = seg / kSegPerGroup, s = seg % kSegPerGroup;
+    range_entries(I, (unsigned)L.Kl, row0, row1, k0, [&](unsigned row, unsigned k) {
+        const unsigned r = row - row0;
+        atomicOr(&bm[4 * k + (r >> 5)], 1u << (r & 31));
+    });
+    __syncthreads();
+    const int64_t slab = ((int64_t)bh * L.ngrp + grp) * Tp + k0;
+    int32_t *Iq = L.Iq + (int64_t)bh * L.eph;
+    range_entries(I, (unsigned)L.Kl, row0, row1, k0, [&](unsigned row, unsigned k) {
+        const unsigned r = row - row0;
+        const uint4 m = reinterpret_cast<const uint4 *>(bm)[k], c = reinterpret_cast<const uint4 *>(L.cnt8)[slab + k];
+        const uint32_t mw[4] = {m.x, m.y, m.z, m.w}, cw[4] = {c.x, c.y, c.z, c.w};
+        uint32_t at = (uint32_t)L.tot[slab + k];
+#pragma unroll
+        for (unsigned w = 0; w < 4; ++w) {                  // bits / bytes below this row / segment
+            const uint32_t mb = w < (r >> 5) ? ~0u : w == (r >> 5) ? (1u << (r & 31)) - 1u : 0u;
+            const uint32_t cb = w < (s >> 2) ? ~0u : w == (s >> 2) ? (1u << (8 * (s & 3))) - 1u : 0u;
+            at += __popc(mw[w] & mb);
+            at = __builtin_amdgcn_sad_u8(cw[w] & cb, 0u, at);
+        }
+        Iq[at] = (int32_t)row;
+    });
+}
+
+// Larger levels still: count -> exclusive scan -> fill -> per-key ascending order.  Counting and filling use integer atomics; the
 // order they leave inside a key's list depends on timing, so a last pass sorts every list (an entry counts the smaller ones of
 // its list; lists of more than 4096 entries: a bitmap of the list's rows).  blockIdx.y selects the level.
 __global__ void csc_zero_kernel(CscLevels a) {
@@ -616,6 +746,17 @@ __global__ void __launch_bounds__(256) csc_sort_long_kernel(CscLevels a) {
     }
 }
 
+// one launch while its O(T^2) reading is cheap (measured with the dK/dV kernels it runs beside)
+static bool csc_one_launch(const Plan &p) { return p.n[1] <= 512; }
+
+// bytes of scratch memory the transpose of level l needs
+size_t csc_scratch_bytes(const Plan &p, int l) {
+    const int64_t T = p.n[l + 1];
+    if (csc_one_launch(p)) return 0;
+    if (p.n[1] <= kSegRowsMax) return (size_t)p.bh * ((T + kGroupRows - 1) / kGroupRows) * ((T + 3) & ~(int64_t)3) * (kSegPerGroup + 4);
+    return (size_t)p.bh * T * p.Kl[l] * sizeof(int32_t);
+}
+
 // Alg. 2 for levels 0 .. top (the levels whose lists the backward uses)
 hipError_t launch_csc(const Plan &p, int top, const int32_t *indices, void *ws, hipStream_t s) {
     char *w = static_cast<char *>(ws);
@@ -633,19 +774,37 @@ hipError_t launch_csc(const Plan &p, int top, const int32_t *indices, void *ws, 
         L.C = (int32_t *)(w + p.C_off[l]);
         L.Iq = (int32_t *)(w + p.Iq_off[l]);
         L.Iq_tmp = (int32_t *)(w + p.Iqtmp_off[l]);
+        L.Tp = (int)((L.T + 3) & ~(int64_t)3);
+        L.ngrp = (int)((L.T + kGroupRows - 1) / kGroupRows);
+        L.cnt8 = (uint32_t *)(w + p.Iqtmp_off[l]);          // the segment path's counts, 16-byte aligned both
+        L.tot = (int32_t *)(L.cnt8 + (size_t)p.bh * L.ngrp * L.Tp * (kSegPerGroup / 4));
         if (L.nk > max_nk) max_nk = L.nk;
         if (L.total > max_total) max_total = L.total;
     }
-    if (p.n[1] <= kBitmapRows) {                            // level 0 has the most rows
-        CscRanges r;
+    // level 0 has the most rows
+    CscRanges r;
+    auto ranges = [&](auto wgs) -> unsigned {               // lays the levels' workgroups one after the other
         int64_t wg = 0;
         for (int l = 0; l <= top; ++l) {
             r.lv[l] = a.lv[l];
-            wg += p.bh * ((a.lv[l].T + kRangeKeys - 1) / kRangeKeys);
+            wg += p.bh * wgs(a.lv[l].T);
             r.wg_end[l] = (unsigned)wg;
         }
+        return (unsigned)wg;
+    };
+    if (csc_one_launch(p)) {
         const size_t lds = (size_t)kRangeKeys * ((p.n[1] + 63) / 64) * 8;
-        csc_bitmap_kernel<<<(unsigned)wg, 256, lds, s>>>(r);
+        const unsigned wgs = ranges([](int64_t T) { return (T + kRangeKeys - 1) / kRangeKeys; });
+        csc_bitmap_kernel<<<wgs, 256, lds, s>>>(r);
+        return hipGetLastError();
+    }
+    if (p.n[1] <= kSegRowsMax) {
+        auto kr = [](int64_t T) { return (T + kKeyRange - 1) / kKeyRange; };
+        unsigned wgs = ranges([&](int64_t T) { return kr(T) * ((T + kGroupRows - 1) / kGroupRows); });
+        csc_seg_count_kernel<<<wgs, 256, 0, s>>>(r);
+        csc_seg_scan_kernel<<<dim3(p.bh, top + 1), 256, 0, s>>>(a);
+        wgs = ranges([&](int64_t T) { return kr(T) * ((T + kSegR - 1) / kSegR); });
+        csc_seg_fill_kernel<<<wgs, 256, 0, s>>>(r);
         return hipGetLastError();
     }
     const unsigned nl = (unsigned)(top + 1);

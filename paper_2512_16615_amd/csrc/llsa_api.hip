@@ -110,7 +110,7 @@ static llsa_status build_plan(const llsa_desc &d, Plan &p) {
         p.C_off[l] = ws;     ws = align_up(ws + ((size_t)p.bh * (p.n[l + 1] + 1)) * sizeof(int32_t));
         p.cnt_off[l] = ws;   ws = align_up(ws + keys * sizeof(int32_t));
         p.Iq_off[l] = ws;    ws = align_up(ws + ent * sizeof(int32_t));
-        p.Iqtmp_off[l] = ws; ws = align_up(ws + ent * sizeof(int32_t));
+        p.Iqtmp_off[l] = ws; ws = align_up(ws + csc_scratch_bytes(p, l));
     }
     for (int l = 1; p.fast && l <= p.L; ++l) {
         const size_t bytes = (size_t)p.bh * p.n[l] * p.d * sizeof(float);

@@ -64,6 +64,7 @@ hipError_t launch_qknorm_rope_pool(const Plan &p, const void *Qpre, const void *
                                    float eps, void *Qout, void *Kout, void *ws, hipStream_t s);
 hipError_t launch_select(const Plan &p, int l, const void *ws, const int32_t *parent, int32_t *out, hipStream_t s);
 hipError_t launch_csc(const Plan &p, int top_level, const int32_t *I, void *ws, hipStream_t s);  // levels 0..top_level
+size_t csc_scratch_bytes(const Plan &p, int l);   // scratch memory at Iqtmp_off[l]
 // level 0's key-major lists through a dense T x T block mask (`mask`: bh * T * T bytes, rounded up to 16) instead of Alg. 2
 hipError_t launch_mask_lists(const Plan &p, const int32_t *indices, void *ws, void *mask, hipStream_t s);
 // nested-patch token order of a 2^bits x 2^bits grid (or back); rows of row_bytes (a multiple of 16) bytes

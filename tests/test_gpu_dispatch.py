@@ -73,10 +73,11 @@ def test_selection_of_tied_scores(cfg):
             assert np.array_equal(gpu["plan"].level_indices(gpu["indices"], l)[b, h].cpu().numpy(), r["I"][l]), f"level {l}"
 
 
-@pytest.mark.parametrize("T,K,heads", [(1, 1, 2), (33, 3, 3), (64, 8, 2), (65, 5, 2), (4096, 8, 2), (8191, 2, 1), (8192, 8, 1), (8193, 3, 1)])
+@pytest.mark.parametrize("T,K,heads", [(1, 1, 2), (33, 3, 3), (64, 8, 2), (65, 5, 2), (512, 8, 2), (513, 3, 2), (1025, 8, 2),
+                                         (2048, 64, 1), (4099, 7, 2), (16384, 8, 1), (16385, 2, 1)])
 def test_index_transpose_by_size(T, K, heads):
-    """Alg. 2 on forced lists at the edges of its two paths: few rows, rows that fill no 64-row word, the largest level of the
-    one-launch path and the smallest beyond it; one key listed by every row, the last keys listed by none."""
+    """Alg. 2 on forced lists at the edges of its paths: few rows, rows that fill no 64-row word, segment, group or key range, the
+    largest level of each path and the smallest beyond it; one key listed by every row, the last keys listed by none."""
     import numpy as np
     import torch
     from oracle import llsa_oracle as orc
