@@ -14,9 +14,11 @@
 //   dkv_upper_kernel: levels >= 2 only.  The 16 level-1 blocks under one level-2 query block list the same
 //     key blocks at every level >= 2, so a workgroup of 8 waves walks G of them (G divides 16; the next one's
 //     rows are prefetched into registers) and keeps its accumulators in registers meanwhile: every wave owns
-//     one or two of the listed blocks, and (d = 64) the single block of the coarsest level is shared: wave w takes
-//     query tile w of every R and the 8 waves' sums are added through LDS at the end.  G times fewer partials,
-//     and no idle rounds when the number of key blocks is not a multiple of the waves.
+//     one or two of the listed blocks, and (d = 64) the single block of a coarsest level of at most 16 tokens is shared:
+//     wave w takes query tile w of every R and the 8 waves' sums are added through LDS at the end.  G times fewer partials,
+//     and no idle rounds when the number of key blocks is not a multiple of the waves.  The blocks of a larger dense level
+//     are owned by waves like listed ones (N = 65536 with 256 coarsest tokens: without this, every level-1 query block
+//     wrote 24 partials, 805 MB, and the coarse stage took 593 us instead of 335).
 // The partials are then added up in a fixed order:
 //   1. levels l >= 2: the query groups under one level-l query block list the same key blocks, so their
 //      partials are summed up to 16 at a time (slab_reduce_kernel) until one partial per level-l query
@@ -47,7 +49,7 @@ struct GroupArgs {
     int lev_end;                                        // levels below lev_end are processed (from 1, or from 2 in the upper kernel)
     int G;                                              // level-1 query blocks per workgroup (upper kernel)
     int GC;                                             // level-1 query blocks a workgroup of the chain kernel walks
-    int nbs, nbd;                                       // upper kernel: listed blocks of its sparse levels / of the dense level
+    int nbs, nbd;                                       // upper kernel: listed blocks the waves own / shared dense block (0 or 1)
     int sparse_begin, do_dense;                         // upper kernel: first sparse block of this launch; does it take the dense one
     float sc2, scale;
 };
@@ -347,7 +349,7 @@ __global__ void __launch_bounds__(512) dkv_upper_kernel(LevelTable t, GroupArgs 
             const int jb = a.sparse_begin + wave + 8 * s;
             const bool have = jb < a.nbs;
             if (have && (jb >> 6) != chunk) { chunk = jb >> 6; ctab.fill(t, bh, R0 * 16, u_begin, chunk, lane, D, nlev); }
-            sp[s][0].load(have ? ctab.K(jb & 63) : nullptr, ctab.V(jb & 63), 16, ctab.bias(jb & 63), lane);
+            sp[s][0].load(have ? ctab.K(jb & 63) : nullptr, ctab.V(jb & 63), ctab.count(jb & 63), ctab.bias(jb & 63), lane);
             sp[s][0].clear();
         }
         if (dense) {
@@ -504,7 +506,8 @@ int dkv_group_top(const Plan &p) {
     return p.Le;
 }
 
-// Listed blocks of levels 2 .. top: sparse levels (nbs) and the dense coarsest level (nbd).
+// Blocks of levels 2 .. top: owned by waves (nbs: the sparse levels' listed ones and a dense level's, if it has several blocks or
+// a wave has nothing else to do meanwhile) and shared by them (nbd: the block of a dense level, when the others fill all waves).
 static void upper_blocks(const Plan &p, int *nbs, int *nbd) {
     const int top = dkv_group_top(p);
     *nbs = *nbd = 0;
@@ -512,14 +515,14 @@ static void upper_blocks(const Plan &p, int *nbs, int *nbd) {
         if (l < p.L) *nbs += p.Kl[l];
         else *nbd = (int)((p.n[l] + 15) / 16);
     }
+    if (*nbd > 1 || *nbs % 8 != 0) { *nbs += *nbd; *nbd = 0; }
 }
 
-// Level-1 query blocks per workgroup of the upper kernel, or 0 if levels >= 2 stay with dkv_group_kernel
-// (a dense level of more than one block).
+// Level-1 query blocks per workgroup of the upper kernel, or 0 if the group has no level >= 2.
 static int upper_G(const Plan &p) {
     int nbs, nbd;
     upper_blocks(p, &nbs, &nbd);
-    if (dkv_group_top(p) < 2 || nbs + nbd == 0 || nbd > 1) return 0;
+    if (dkv_group_top(p) < 2 || nbs + nbd == 0) return 0;
     const int64_t NR = p.N / 256;
     int G = 16;                                             // divides 16, so a group never straddles a level-2 query block
     while (G > 1 && (NR % G != 0 || (int64_t)p.bh * (NR / G) < 256)) G >>= 1;  // one workgroup of 8 waves per CU
@@ -659,6 +662,7 @@ hipError_t launch_dkv_group(const Plan &p, const LevelTable &t, const void *Q, c
             up.sparse_begin = sb;
             up.do_dense = (sb == 0 && up.nbd > 0) ? 1 : 0;
             if (p.d == 128) dkv_upper_kernel<128, 1, false><<<grid, 512, 0, s>>>(t, up);
+            else if (up.nbs - sb > 8 && !up.do_dense) dkv_upper_kernel<64, 2, false><<<grid, 512, 0, s>>>(t, up);
             else if (up.nbs - sb > 8) dkv_upper_kernel<64, 2, true><<<grid, 512, 0, s>>>(t, up);
             else dkv_upper_kernel<64, 1, true><<<grid, 512, 0, s>>>(t, up);
             GRP_TRY(hipGetLastError());

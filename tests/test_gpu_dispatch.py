@@ -103,3 +103,17 @@ def test_index_transpose_by_size(T, K, heads):
         iq_ref, c_ref = orc.transpose(I[h], T)
         assert np.array_equal(C[h].cpu().numpy(), c_ref)
         assert np.array_equal(Iq[h].cpu().numpy(), iq_ref)
+
+
+@pytest.mark.parametrize("cfg", [
+    # levels >= 2 of the grouped dK/dV kernels: a dense level of two blocks (17 tokens), of 16 blocks behind no sparse level, of
+    # two blocks behind 8 listed ones; its single block owned by a wave (3 and 12 listed blocks) and shared by all (8)
+    _bf16("dense_17", 17 * 256, L=2, heads=2),
+    _bf16("dense_256", 65536, L=2, heads=1, K=4),
+    _bf16("dense_18_K8", 18 * 4096, L=3, heads=1),
+    _bf16("dense_13_K3", 13 * 4096, L=3, heads=1, K=3),
+    _bf16("dense_12_K12", 12 * 4096, L=3, heads=1, K=12),
+    _bf16("dense_8_K8", 8 * 4096, L=3, heads=1),
+], ids=lambda c: c["name"])
+def test_grouped_upper_levels(cfg):
+    _full_parity(cfg, 0xD15E)
