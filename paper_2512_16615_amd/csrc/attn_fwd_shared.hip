@@ -26,7 +26,7 @@ __device__ __forceinline__ u32x4 gload16(const char *base, unsigned off) {
     return *reinterpret_cast<gvec_ptr>(reinterpret_cast<const __attribute__((address_space(1))) char *>(
         reinterpret_cast<uintptr_t>(base)) + off);
 }
-constexpr float kLazy = 12.f;       // a query's softmax reference is raised only when a logit exceeds it by 2^kLazy
+constexpr float kMaxSum = 4096.f;   // a query's softmax reference is raised only when a tile's probabilities exceed this
 
 __device__ __forceinline__ bf16x8 as_bf16x8(u32x4 v) {
     union { u32x4 u; bf16x8 b; } c;
@@ -37,9 +37,9 @@ __device__ __forceinline__ bf16x8 as_bf16x8(u32x4 v) {
 // NB = fine query blocks per wave (1 or 2), NW = waves per workgroup (4 or 8); a workgroup owns NW * NB consecutive
 // blocks, all siblings
 template <int D, int NB, int NW = 8>
-__global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 64 ? 4 : 2))) attn_fwd_shared_kernel(LevelTable t, const uint16_t *__restrict__ Q,
+__global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 64 ? 4 : 2))) attn_fwd_shared_kernel(ListArgs args, const uint16_t *__restrict__ Q,
                                                                uint16_t *__restrict__ O, float *__restrict__ LSE,
-                                                               int64_t N, int64_t total_wgs) {
+                                                               int64_t N, FastDiv groups) {
     constexpr int KS = D / 32, NT = D / 16, STRIDE = D * 2 + 32, PARTS = D / 8, TILE = 32 * STRIDE;
     constexpr int NTHR = 64 * NW;
     constexpr int RND = (2 * 32 * PARTS) / NTHR;        // staging rounds of the workgroup per shared tile (K and V)
@@ -50,22 +50,23 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D 
     // memory; a workgroup barrier separates the phases.
     constexpr int VSTRIDE = D * 2 + 16, VTILE = 32 * VSTRIDE;
     __shared__ __attribute__((aligned(16))) char lds[NW * (TILE + VTILE)];
-    static_assert(4 * TILE + 6 * 64 * 4 <= NW * (TILE + VTILE), "phase A's buffers and the block table must fit");
+    static_assert(4 * TILE <= NW * (TILE + VTILE), "phase A's buffers must fit");
     auto sh = [&](int buf, int which) { return lds + (buf * 2 + which) * TILE; };
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int i16 = lane & 15, g = lane >> 4;
     const int64_t nblk = N >> 4;                                      // query tiles per head
-    const int64_t groups = (nblk + NW * NB - 1) / (NW * NB);          // workgroups per head
-    const int64_t wg = xcd_contiguous(blockIdx.x, total_wgs);
-    const int64_t bh = wg / groups, blk0 = (wg % groups) * (NW * NB);
+    const unsigned wg = xcd_contiguous32(blockIdx.x, gridDim.x);
+    const int64_t bh = groups(wg), blk0 = (wg - (unsigned)bh * groups.d) * (NW * NB);   // groups.d workgroups per head
     auto tile_of = [&](int b) { return min(blk0 + NB * wave + b, nblk - 1); };
-    const float sc2 = t.scale * kLog2e;
+    (void)args;                                                       // read through the pointer: fields of a level by scalar loads
+    const list_args_ptr t = kernel_list_args();
+    const float sc2 = t->scale * kLog2e;
 
     bf16x8 qop[NB][KS];
     f32x4 acc[NB][NT];
-    float m[NB], mthr[NB], lsum[NB];                                  // reference, reference + kLazy, this lane's row-sum share
+    float m[NB], lsum[NB];                                            // reference; this lane's share of the row sum
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
         const uint16_t *qrow = Q + (bh * N + tile_of(b) * 16 + i16) * D + g * 8;
@@ -73,22 +74,22 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D 
         for (int s = 0; s < KS; ++s) qop[b][s] = ld_bf16x8(qrow + 32 * s);
 #pragma unroll
         for (int n = 0; n < NT; ++n) acc[b][n] = f32x4{0.f, 0.f, 0.f, 0.f};
-        m[b] = mthr[b] = -INFINITY;
+        m[b] = -INFINITY;
         lsum[b] = 0.f;
     }
 
-    // softmax update of query block b for one tile (s0 / s1: raw S^T of the two halves) and O^T += V^T P^T
-    // with the V tile at `vt` (row-major, VS bytes per key row).  The running reference m[b] of a query is not its
-    // exact maximum: it is raised (and the accumulators rescaled) only when a logit exceeds it by more than kLazy
-    // (log2 units), so probabilities stay below 2^kLazy, which costs fp32 / bf16 no precision, and a tile's usual
-    // cost is a lane-local maximum and one compare.  Scale, level weight and reference are folded into the one
-    // multiply-add in front of the exponential.
-    auto softmax_pv = [&](auto bsel, f32x4 s0, f32x4 s1, int c0, int c1, float b0, float b1, const char *vt, auto vstride,
-                          auto joint) -> bf16x8 {
+    // Softmax update of query block b for one tile (s0 / s1: raw S^T of the two halves; b0 / b1: log2 weights of their levels,
+    // -inf for an absent half): the probabilities as the B operand of O^T += V^T P^T.  The reference m[b] of a query is not
+    // its exact maximum, and the usual tile does not even look for one: it takes the exponentials against the reference as
+    // it is and checks their sum, which a later row sum needs anyway.  Only if that exceeds kMaxSum in some lane (or is inf
+    // or nan; always in the first tile, where the reference is -inf) is the maximum found, the accumulators rescaled and
+    // the exponentials taken again.  Probabilities up to 2^12 cost fp32 sums and bf16 operands no precision.  Scale, level
+    // weight and reference are folded into the one multiply-add in front of the exponential.  31 vector instructions per
+    // 16 x 32 tile where finding the maximum first took 52.
+    auto probs = [&](auto bsel, f32x4 s0, f32x4 s1, int c0, int c1, float b0, float b1) -> bf16x8 {
         constexpr int b = decltype(bsel)::value;
-        constexpr int VS = decltype(vstride)::value;                  // bytes between the V tile's key rows
-        f32x4 s[2] = {s0, s1};
-        if (c0 < 16 || c1 < 16) {                                     // ragged or absent block: mask
+        f32x4 s[2] = {s0, s1}, p[2];
+        if (c0 < 16 || c1 < 16) {                                     // ragged block: mask
             const int c[2] = {c0, c1};
 #pragma unroll
             for (int h = 0; h < 2; ++h)
@@ -96,10 +97,20 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D 
                 for (int r = 0; r < 4; ++r)
                     if (4 * g + r >= c[h]) s[h][r] = -INFINITY;
         }
-        const float mx0 = fmaxf(fmaxf(s[0][0], s[0][1]), fmaxf(s[0][2], s[0][3]));
-        const float mx1 = fmaxf(fmaxf(s[1][0], s[1][1]), fmaxf(s[1][2], s[1][3]));
-        const float z = fmaxf(fmaf(mx0, sc2, b0), fmaf(mx1, sc2, b1));       // this lane's largest logit (log2 units)
-        if (__builtin_amdgcn_ballot_w64(z > mthr[b]) != 0) {          // some row outgrew its reference: rescale
+        float sum;
+        auto exps = [&]() {
+            const float cb[2] = {b0 - m[b], b1 - m[b]};
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) p[h][r] = __builtin_amdgcn_exp2f(fmaf(s[h][r], sc2, cb[h]));
+            sum = ((p[0][0] + p[0][1]) + (p[0][2] + p[0][3])) + ((p[1][0] + p[1][1]) + (p[1][2] + p[1][3]));
+        };
+        exps();
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(sum <= kMaxSum)) != 0, 0)) {
+            float z = -INFINITY;                                      // this lane's largest logit (log2 units)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) z = fmaxf(z, fmaxf(fmaf(s[0][r], sc2, b0), fmaf(s[1][r], sc2, b1)));
             const float m_new = fmaxf(m[b], rows_max(z));
             const float alpha = __builtin_amdgcn_exp2f(m[b] - m_new);
             lsum[b] *= alpha;
@@ -108,26 +119,18 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D 
 #pragma unroll
                 for (int r = 0; r < 4; ++r) acc[b][n][r] *= alpha;
             m[b] = m_new;
-            mthr[b] = m_new + kLazy;
+            exps();
         }
-        const float cb[2] = {b0 - m[b], b1 - m[b]};
+        lsum[b] += sum;
+        return pack8(p[0], p[1]);
+    };
+    // O^T += V^T P^T with the V tile at `vt` (row-major, VS bytes per key row)
+    auto pv = [&](auto bsel, const bf16x8 pop, const char *vt, auto vstride) {
+        constexpr int b = decltype(bsel)::value;
+        constexpr int VS = decltype(vstride)::value;
+        const char *base = vt + (4 * g + (i16 >> 2)) * VS + (i16 & 3) * 8;
 #pragma unroll
-        for (int h = 0; h < 2; ++h)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                s[h][r] = __builtin_amdgcn_exp2f(fmaf(s[h][r], sc2, cb[h]));
-                lsum[b] += s[h][r];
-            }
-        const bf16x8 pop = pack8(s[0], s[1]);
-        if constexpr (decltype(joint)::value) {
-            return pop;                                               // the caller multiplies both blocks' P with one read of V
-        } else {
-            const char *base = vt + (4 * g + (i16 >> 2)) * VS + (i16 & 3) * 8;
-#pragma unroll
-            for (int n = 0; n < NT; ++n)
-                acc[b][n] = mfma16(lds_tr_pair(base + n * 32, base + 16 * VS + n * 32), pop, acc[b][n]);
-            return pop;
-        }
+        for (int n = 0; n < NT; ++n) acc[b][n] = mfma16(lds_tr_pair(base + n * 32, base + 16 * VS + n * 32), pop, acc[b][n]);
     };
     using StrideA = std::integral_constant<int, STRIDE>;
     using StrideB = std::integral_constant<int, VSTRIDE>;
@@ -137,22 +140,21 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D 
     // The level-0 lists of this wave's NB query blocks, fetched now so that phase B does not wait for them:
     // lane (64 / NB) b + j holds the first token of 16-token tile j of query tile b's list (at most 64 / NB tiles;
     // a listed block of B tokens is B / 16 consecutive tiles, and B / 16 consecutive query tiles share a row of I^(0)).
-    const int nb0 = t.bseg[1];                                        // level-0 tiles (the list always holds level 0)
+    const int nb0 = t->lev[0].end;                                        // level-0 tiles (the list always holds level 0)
     int tok0 = 0;
     {
         const int b = lane / (64 / NB), j = lane % (64 / NB);
         if (j < nb0) {
-            const int64_t row = tile_of(b) >> t.ls;
-            tok0 = (t.I[0][(bh * t.rows[0] + row) * t.Kl[0] + (j >> t.ls)] << t.lb) + ((j & ((1 << t.ls) - 1)) << 4);
+            const int64_t row = tile_of(b) >> t->ls;
+            tok0 = (t->lev[0].I[(bh * t->lev[0].rows + row) * t->lev[0].Kl + (j >> t->ls)] << t->lb) + ((j & ((1 << t->ls) - 1)) << 4);
         }
     }
 
     // ------------------------------------------------------------------ phase A: shared coarse levels
-    const int c_begin = t.nlev > 1 ? t.bseg[1] : t.bseg[t.nlev];     // first coarse block of the list
-    const int nbc = t.bseg[t.nlev] - c_begin;                         // coarse blocks
+    const int nbc = t->lev[t->nlev - 1].end - nb0;                    // coarse tiles of the list
     if (nbc > 0) {
-        BlockTable ctab;                                              // lane j: coarse block 64 * chunk + j
-        ctab.fill_once(t, bh, blk0, c_begin, lane, wave, D, reinterpret_cast<uint32_t *>(lds + 4 * TILE));
+        CoarseTable ctab;                                              // lane j: coarse block 64 * chunk + j
+        ctab.fill<D>(t, bh, (unsigned)blk0, 0, lane);
         // Staging round r of this wave: 64 consecutive 16-byte chunks of the [K | V] tile, i.e. 64 / PARTS key rows of
         // one half of K or of V, the same choice for the whole wave.
         // (d = 64: one round, waves 0-3 stage K, waves 4-7 V; d = 128: round 0 stages K, round 1 V.)
@@ -167,21 +169,24 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D 
         }
         const bool v_wave = RND == 1 && wave >= 4;
         uint64_t sptr = v_wave ? ctab.vptr : ctab.kptr;               // d = 64: the tensor this wave stages
+        const int ntile = (nbc + 1) >> 1;                             // only the last tile may be ragged or lack its second half
         auto load_shared = [&](int u) {                               // coarse blocks 2u, 2u + 1 -> registers
             if (u > 0 && ((2 * u) & 63) == 0) {
-                ctab.fill(t, bh, blk0, c_begin, (2 * u) >> 6, lane, D);
+                ctab.fill<D>(t, bh, (unsigned)blk0, (2 * u) >> 6, lane);
                 sptr = v_wave ? ctab.vptr : ctab.kptr;
             }
 #pragma unroll
             for (int r = 0; r < RND; ++r) {
                 const bool have = 2 * u + s_half[r] < nbc;
                 const int j = (have ? 2 * u + s_half[r] : 2 * u) & 63;
-                const int cnt = have ? ctab.count(j) : 0;
                 const char *src = RND == 1 ? BlockTable::rl_ptr(sptr, j) : (r == 0 ? ctab.K(j) : ctab.V(j));
                 unsigned off = s_off[r];
-                if (cnt < 16) {                                       // ragged or absent block: re-read its last valid row
-                    const int row = min((int)(off / (D * 2)), max(cnt, 1) - 1);
-                    off = (unsigned)(row * D * 2) + off % (D * 2);
+                if (u + 1 == ntile) {
+                    const int cnt = have ? ctab.count(j) : 0;
+                    if (cnt < 16) {                                   // ragged or absent block: re-read its last valid row
+                        const int row = min((int)(off / (D * 2)), max(cnt, 1) - 1);
+                        off = (unsigned)(row * D * 2) + off % (D * 2);
+                    }
                 }
                 sreg[r] = gload16(src, off);
             }
@@ -193,20 +198,17 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D 
                 *reinterpret_cast<u32x4 *>(sh(buf, which) + (c / PARTS) * STRIDE + (c % PARTS) * 16) = sreg[r];
             }
         };
-        const int ntile = (nbc + 1) >> 1;
         load_shared(0);
         for (int u = 0; u < ntile; ++u) {
             const int buf = u & 1;
             store_shared(buf);
             // per-half fields of this tile, before the table may be refilled for the next one
-            int cnt[2];
-            float bias2[2];
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const bool have = 2 * u + h < nbc;
-                const int j = have ? 2 * u + h : 2 * u;
-                cnt[h] = have ? ctab.count(j & 63) : 0;
-                bias2[h] = ctab.bias(j & 63);
+            int cnt[2] = {16, 16};
+            float bias2[2] = {ctab.bias((2 * u) & 63), ctab.bias((2 * u + 1) & 63)};
+            if (u + 1 == ntile) {
+                cnt[0] = ctab.count((2 * u) & 63);
+                if (2 * u + 1 < nbc) cnt[1] = ctab.count((2 * u + 1) & 63);
+                else bias2[1] = -INFINITY;                            // an absent half: probabilities 0
             }
             __syncthreads();                                          // tile u visible; buffer buf^1 free again
             if (u + 1 < ntile) load_shared(u + 1);
@@ -227,8 +229,8 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D 
                     for (int ks = 0; ks < KS; ++ks) s[b][h] = mfma16(kop[h][ks], qop[b][ks], s[b][h]);
                 }
             if constexpr (NB > 1) {                                   // both blocks' P first, then one transposing read of V for both
-                const bf16x8 p0 = softmax_pv(B0{}, s[0][0], s[0][1], cnt[0], cnt[1], bias2[0], bias2[1], vt, StrideA{}, std::true_type{});
-                const bf16x8 p1 = softmax_pv(B1{}, s[NB - 1][0], s[NB - 1][1], cnt[0], cnt[1], bias2[0], bias2[1], vt, StrideA{}, std::true_type{});
+                const bf16x8 p0 = probs(B0{}, s[0][0], s[0][1], cnt[0], cnt[1], bias2[0], bias2[1]);
+                const bf16x8 p1 = probs(B1{}, s[NB - 1][0], s[NB - 1][1], cnt[0], cnt[1], bias2[0], bias2[1]);
                 const char *base = vt + (4 * g + (i16 >> 2)) * STRIDE + (i16 & 3) * 8;
 #pragma unroll
                 for (int n = 0; n < NT; ++n) {
@@ -237,7 +239,7 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D 
                     acc[NB - 1][n] = mfma16(vtr, p1, acc[NB - 1][n]);
                 }
             } else {
-                softmax_pv(B0{}, s[0][0], s[0][1], cnt[0], cnt[1], bias2[0], bias2[1], vt, StrideA{}, std::false_type{});
+                pv(B0{}, probs(B0{}, s[0][0], s[0][1], cnt[0], cnt[1], bias2[0], bias2[1]), vt, StrideA{});
             }
         }
     }
@@ -255,7 +257,7 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D 
     // The tiles of the wave's NB query blocks form one stream: the next tile's rows are in flight during the
     // current tile's math, also across the border between the two blocks (tok0: fetched before phase A).
     u32x4 kreg[VCH], vreg[VCH];
-    const char *K0 = static_cast<const char *>(t.K[0]), *V0 = static_cast<const char *>(t.V[0]);
+    const char *K0 = static_cast<const char *>(t->lev[0].K), *V0 = static_cast<const char *>(t->lev[0].V);
     auto load_tile = [&](int b, int j0) {
         int64_t off[2];
 #pragma unroll
@@ -289,8 +291,8 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D 
                 for (int ks = 0; ks < KS; ++ks)
                     s[h] = mfma16(*reinterpret_cast<const bf16x8 *>(my_k + (h * 16 + i16) * STRIDE + g * 16 + ks * 64), qop[b][ks], s[h]);
             }
-            const int c1 = (j0 + 1 < nb0) ? 16 : 0;                   // level-0 blocks are always full
-            softmax_pv(bsel, s[0], s[1], 16, c1, 0.f, 0.f, my_v, StrideB{}, std::false_type{});
+            // level-0 blocks are always full; an absent second half has weight 0
+            pv(bsel, probs(bsel, s[0], s[1], 16, 16, 0.f, j0 + 1 < nb0 ? 0.f : -INFINITY), my_v, StrideB{});
         }
     };
     load_tile(0, 0);
@@ -318,18 +320,18 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D 
 
 hipError_t launch_attn_fwd_shared(const Plan &p, const LevelTable &t, const void *Q, void *O, float *LSE,
                                   hipStream_t s) {
-    const int64_t wgs = (int64_t)p.bh * ((p.N + 127) / 128);
+    const FastDiv groups((p.N + 127) / 128);
+    const unsigned wgs = (unsigned)p.bh * groups.d;
+    const ListArgs a = make_list_args(t);
     if (p.d == 64 && (p.Kl[0] << (p.lb - 4)) <= 32) { // two query blocks per wave (measured faster than one)
         // workgroups of four waves (8 query blocks), four per CU: same occupancy as two of eight waves, cheaper barriers
         // (measured 225 against 229 us)
-        attn_fwd_shared_kernel<64, 2, 4><<<dim3((unsigned)wgs), 256, 0, s>>>(t, (const uint16_t *)Q, (uint16_t *)O, LSE, p.N,
-                                                                              wgs);
+        attn_fwd_shared_kernel<64, 2, 4><<<wgs, 256, 0, s>>>(a, (const uint16_t *)Q, (uint16_t *)O, LSE, p.N, groups);
     } else if (p.d == 64) {                           // K_0 > 32: both level-0 lists would not fit one register
-        attn_fwd_shared_kernel<64, 1><<<dim3((unsigned)wgs), 512, 0, s>>>(t, (const uint16_t *)Q, (uint16_t *)O, LSE, p.N,
-                                                                           wgs);
+        attn_fwd_shared_kernel<64, 1><<<wgs, 512, 0, s>>>(a, (const uint16_t *)Q, (uint16_t *)O, LSE, p.N, groups);
     } else {                                          // d = 128: one query block per wave (registers), 8 per workgroup
-        attn_fwd_shared_kernel<128, 1><<<dim3((unsigned)wgs), 512, 0, s>>>(t, (const uint16_t *)Q, (uint16_t *)O, LSE,
-                                                                            p.N, wgs);
+        attn_fwd_shared_kernel<128, 1><<<wgs, 512, 0, s>>>(a, (const uint16_t *)Q, (uint16_t *)O, LSE,
+                                                                            p.N, groups);
     }
     return hipGetLastError();
 }

@@ -27,9 +27,9 @@ __device__ __forceinline__ float bf_hi(uint32_t w) { return __uint_as_float(w & 
 // NB = fine query blocks per wave (1 or 2); a workgroup owns 8 * NB consecutive blocks, all siblings
 template <int D, int NB>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(D == 64 ? 4 : 2)))
-dq_shared_kernel(LevelTable t, const uint16_t *__restrict__ Q, const uint16_t *__restrict__ O,
+dq_shared_kernel(ListArgs args, const uint16_t *__restrict__ Q, const uint16_t *__restrict__ O,
                  const uint16_t *__restrict__ dO, const float *__restrict__ LSE, float *__restrict__ Dsum,
-                 uint16_t *__restrict__ dQ, int64_t N, int64_t total_wgs) {
+                 uint16_t *__restrict__ dQ, int64_t N, FastDiv groups) {
     constexpr int KS = D / 32, NT = D / 16, STRIDE = D * 2 + 32, PARTS = D / 8, TILE = 32 * STRIDE;
     constexpr int RND = (2 * 32 * PARTS) / 512, VCH = D / 16, KPU = 64 / PARTS;
     // Phase B: per wave a K tile (row-wise and transposed reads) and a V tile (row-wise reads only; 16 bytes of
@@ -44,16 +44,18 @@ dq_shared_kernel(LevelTable t, const uint16_t *__restrict__ Q, const uint16_t *_
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int i16 = lane & 15, g = lane >> 4;
     const int64_t nblk = N >> 4;                                      // query tiles per head
-    const int64_t groups = (nblk + 8 * NB - 1) / (8 * NB);            // workgroups per head (8 * NB query tiles each)
-    const int64_t wg = xcd_contiguous(blockIdx.x, total_wgs);
-    const int64_t bh = wg / groups, blk0 = (wg % groups) * (8 * NB);
+    const unsigned wg = xcd_contiguous32(blockIdx.x, gridDim.x);
+    const int64_t bh = groups(wg), blk0 = (wg - (unsigned)bh * groups.d) * (8 * NB);   // groups.d workgroups per head
     // a spare wave of a head's last workgroup works on the head's last tile without storing it
     auto tile_of = [&](int b) { return min(blk0 + NB * wave + b, nblk - 1); };
-    const float sc2 = t.scale * kLog2e;
+    (void)args;                                                       // read through the pointer: fields of a level by scalar loads
+    const list_args_ptr t = kernel_list_args();
+    const float sc2 = t->scale * kLog2e;
 
     bf16x8 qop[NB][KS], gop[NB][KS];
     f32x4 acc[NB][NT];
-    float lse2[NB], delta[NB];
+    float lse2[NB];
+    f32x4 ndelta[NB];                                                 // -D in every register: what dP^T's sums start from
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
         const int64_t qrow = bh * N + tile_of(b) * 16 + i16;
@@ -70,14 +72,16 @@ dq_shared_kernel(LevelTable t, const uint16_t *__restrict__ Q, const uint16_t *_
             }
             gop[b][s] = to_bf16x8(gw);
         }
-        delta[b] = rows_sum(dl);
-        if (g == 0 && blk0 + NB * wave + b < nblk) Dsum[qrow] = delta[b];
+        dl = rows_sum(dl);
+        ndelta[b] = f32x4{-dl, -dl, -dl, -dl};
+        if (g == 0 && blk0 + NB * wave + b < nblk) Dsum[qrow] = dl;
         lse2[b] = LSE[qrow] * kLog2e;
 #pragma unroll
         for (int n = 0; n < NT; ++n) acc[b][n] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
 
-    // dS^T of query block b for one tile and dQ^T += K^T dS^T with the K tile at `kt`
+    // dS^T of query block b for one tile (dp: dP^T - D) and dQ^T += K^T dS^T with the K tile at `kt`; a half of weight -inf is
+    // absent
     auto ds_dq = [&](auto bsel, f32x4 s0, f32x4 s1, f32x4 dp0, f32x4 dp1, int c0, int c1, float b0, float b1,
                      const char *kt) {
         constexpr int b = decltype(bsel)::value;
@@ -90,9 +94,9 @@ dq_shared_kernel(LevelTable t, const uint16_t *__restrict__ Q, const uint16_t *_
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const float p = __builtin_amdgcn_exp2f(fmaf(s[h][r], sc2, c2[h]));
-                s[h][r] = p * (dp[h][r] - delta[b]);
+                s[h][r] = p * dp[h][r];
             }
-        if (c[0] < 16 || c[1] < 16) {                                 // ragged or absent block contributes nothing
+        if (c[0] < 16 || c[1] < 16) {                                 // rows past the end of a ragged block contribute nothing
 #pragma unroll
             for (int h = 0; h < 2; ++h)
 #pragma unroll
@@ -110,22 +114,21 @@ dq_shared_kernel(LevelTable t, const uint16_t *__restrict__ Q, const uint16_t *_
 
     // The level-0 lists of this wave's NB query blocks, fetched now so that phase B does not wait for them:
     // lane (64 / NB) b + j holds the first token of 16-token tile j of query tile b's list (as in the forward kernel).
-    const int nb0 = t.bseg[1];
+    const int nb0 = t->lev[0].end;
     int tok0 = 0;
     {
         const int b = lane / (64 / NB), j = lane % (64 / NB);
         if (j < nb0) {
-            const int64_t row = tile_of(b) >> t.ls;
-            tok0 = (t.I[0][(bh * t.rows[0] + row) * t.Kl[0] + (j >> t.ls)] << t.lb) + ((j & ((1 << t.ls) - 1)) << 4);
+            const int64_t row = tile_of(b) >> t->ls;
+            tok0 = (t->lev[0].I[(bh * t->lev[0].rows + row) * t->lev[0].Kl + (j >> t->ls)] << t->lb) + ((j & ((1 << t->ls) - 1)) << 4);
         }
     }
 
     // ------------------------------------------------------------------ phase A: shared coarse levels
-    const int c_begin = t.nlev > 1 ? t.bseg[1] : t.bseg[t.nlev];
-    const int nbc = t.bseg[t.nlev] - c_begin;
+    const int nbc = t->lev[t->nlev - 1].end - nb0;                    // coarse tiles of the list
     if (nbc > 0) {
-        BlockTable ctab;
-        ctab.fill_once(t, bh, blk0, c_begin, lane, wave, D, reinterpret_cast<uint32_t *>(lds + 4 * TILE));
+        CoarseTable ctab;
+        ctab.fill<D>(t, bh, (unsigned)blk0, 0, lane);
         // Staging round r of this wave: 64 consecutive 16-byte chunks of the [K | V] tile, i.e. 64 / PARTS key rows of
         // one half of K or of V, the same choice for the whole wave (d = 64: one round, waves 0-3 stage K, waves 4-7
         // V; d = 128: round 0 stages K, round 1 V).
@@ -140,21 +143,24 @@ dq_shared_kernel(LevelTable t, const uint16_t *__restrict__ Q, const uint16_t *_
         }
         const bool v_wave = RND == 1 && wave >= 4;
         uint64_t sptr = v_wave ? ctab.vptr : ctab.kptr;               // d = 64: the tensor this wave stages
+        const int ntile = (nbc + 1) >> 1;                             // only the last tile may be ragged or lack its second half
         auto load_shared = [&](int u) {
             if (u > 0 && ((2 * u) & 63) == 0) {
-                ctab.fill(t, bh, blk0, c_begin, (2 * u) >> 6, lane, D);
+                ctab.fill<D>(t, bh, (unsigned)blk0, (2 * u) >> 6, lane);
                 sptr = v_wave ? ctab.vptr : ctab.kptr;
             }
 #pragma unroll
             for (int r = 0; r < RND; ++r) {
                 const bool have = 2 * u + s_half[r] < nbc;
                 const int j = (have ? 2 * u + s_half[r] : 2 * u) & 63;
-                const int cnt = have ? ctab.count(j) : 0;
                 const char *src = RND == 1 ? BlockTable::rl_ptr(sptr, j) : (r == 0 ? ctab.K(j) : ctab.V(j));
                 unsigned off = s_off[r];
-                if (cnt < 16) {                                       // ragged or absent block: re-read its last valid row
-                    const int row = min((int)(off / (D * 2)), max(cnt, 1) - 1);
-                    off = (unsigned)(row * D * 2) + off % (D * 2);
+                if (u + 1 == ntile) {
+                    const int cnt = have ? ctab.count(j) : 0;
+                    if (cnt < 16) {                                   // ragged or absent block: re-read its last valid row
+                        const int row = min((int)(off / (D * 2)), max(cnt, 1) - 1);
+                        off = (unsigned)(row * D * 2) + off % (D * 2);
+                    }
                 }
                 sreg[r] = gload16b(src, off);
             }
@@ -166,19 +172,16 @@ dq_shared_kernel(LevelTable t, const uint16_t *__restrict__ Q, const uint16_t *_
                 *reinterpret_cast<u32x4 *>(sh(buf, which) + (c / PARTS) * STRIDE + (c % PARTS) * 16) = sreg[r];
             }
         };
-        const int ntile = (nbc + 1) >> 1;
         load_shared(0);
         for (int u = 0; u < ntile; ++u) {
             const int buf = u & 1;
             store_shared(buf);
-            int cnt[2];
-            float bias2[2];
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const bool have = 2 * u + h < nbc;
-                const int j = have ? 2 * u + h : 2 * u;
-                cnt[h] = have ? ctab.count(j & 63) : 0;
-                bias2[h] = ctab.bias(j & 63);
+            int cnt[2] = {16, 16};
+            float bias2[2] = {ctab.bias((2 * u) & 63), ctab.bias((2 * u + 1) & 63)};
+            if (u + 1 == ntile) {
+                cnt[0] = ctab.count((2 * u) & 63);
+                if (2 * u + 1 < nbc) cnt[1] = ctab.count((2 * u + 1) & 63);
+                else bias2[1] = -INFINITY;                            // an absent half: P = 0
             }
             __syncthreads();
             if (u + 1 < ntile) load_shared(u + 1);
@@ -191,7 +194,7 @@ dq_shared_kernel(LevelTable t, const uint16_t *__restrict__ Q, const uint16_t *_
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
                     s[h] = f32x4{0.f, 0.f, 0.f, 0.f};
-                    dp[h] = f32x4{0.f, 0.f, 0.f, 0.f};
+                    dp[h] = ndelta[b];
 #pragma unroll
                     for (int ks = 0; ks < KS; ++ks) {
                         const int off = (h * 16 + i16) * STRIDE + g * 16 + ks * 64;
@@ -212,7 +215,7 @@ dq_shared_kernel(LevelTable t, const uint16_t *__restrict__ Q, const uint16_t *_
     // third of what the L2 delivers) and reach the operand layouts through the wave's own LDS tiles.
     __syncthreads();                                                  // phase A's buffers are free
     char *my = lds + wave * (TILE + VTILE), *my_v = my + TILE;
-    const char *K0 = static_cast<const char *>(t.K[0]), *V0 = static_cast<const char *>(t.V[0]);
+    const char *K0 = static_cast<const char *>(t->lev[0].K), *V0 = static_cast<const char *>(t->lev[0].V);
     unsigned voff[VCH];
 #pragma unroll
     for (int u = 0; u < VCH; ++u) voff[u] = (unsigned)((((lane / PARTS + KPU * u) & 15) * D + (lane % PARTS) * 8) * 2);
@@ -247,7 +250,7 @@ dq_shared_kernel(LevelTable t, const uint16_t *__restrict__ Q, const uint16_t *_
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 s[h] = f32x4{0.f, 0.f, 0.f, 0.f};
-                dp[h] = f32x4{0.f, 0.f, 0.f, 0.f};
+                dp[h] = ndelta[b];
                 const char *krow = my + (h * 16 + i16) * STRIDE + g * 16, *vrow = my_v + (h * 16 + i16) * VSTRIDE + g * 16;
 #pragma unroll
                 for (int ks = 0; ks < KS; ++ks) {
@@ -255,8 +258,7 @@ dq_shared_kernel(LevelTable t, const uint16_t *__restrict__ Q, const uint16_t *_
                     dp[h] = mfma16(*reinterpret_cast<const bf16x8 *>(vrow + ks * 64), gop[b][ks], dp[h]);
                 }
             }
-            const int c1 = (j0 + 1 < nb0) ? 16 : 0;
-            ds_dq(bsel, s[0], s[1], dp[0], dp[1], 16, c1, 0.f, 0.f, my);
+            ds_dq(bsel, s[0], s[1], dp[0], dp[1], 16, 16, 0.f, j0 + 1 < nb0 ? 0.f : -INFINITY, my);
         }
     };
     phase_b(B0{});
@@ -269,8 +271,8 @@ dq_shared_kernel(LevelTable t, const uint16_t *__restrict__ Q, const uint16_t *_
 #pragma unroll
         for (int n = 0; n < NT; ++n) {
             u32x2 w;
-            w[0] = pack_bf16(acc[b][n][0] * t.scale, acc[b][n][1] * t.scale);
-            w[1] = pack_bf16(acc[b][n][2] * t.scale, acc[b][n][3] * t.scale);
+            w[0] = pack_bf16(acc[b][n][0] * t->scale, acc[b][n][1] * t->scale);
+            w[1] = pack_bf16(acc[b][n][2] * t->scale, acc[b][n][3] * t->scale);
             *reinterpret_cast<u32x2 *>(orow + n * 16) = w;
         }
     }
@@ -278,14 +280,16 @@ dq_shared_kernel(LevelTable t, const uint16_t *__restrict__ Q, const uint16_t *_
 
 hipError_t launch_dq_shared(const Plan &p, const LevelTable &t, const void *Q, const void *O, const void *dO,
                             const float *LSE, float *D, void *dQ, hipStream_t s) {
-    const int64_t wgs = (int64_t)p.bh * ((p.N + 127) / 128);          // one query tile per wave: 8 per workgroup
+    const FastDiv groups((p.N + 127) / 128);
+    const unsigned wgs = (unsigned)p.bh * groups.d;
+    const ListArgs a = make_list_args(t);                             // one query tile per wave: 8 per workgroup
     if (p.d == 128) {
-        dq_shared_kernel<128, 1><<<dim3((unsigned)wgs), 512, 0, s>>>(t, (const uint16_t *)Q, (const uint16_t *)O,
-                                                                      (const uint16_t *)dO, LSE, D, (uint16_t *)dQ, p.N, wgs);
+        dq_shared_kernel<128, 1><<<wgs, 512, 0, s>>>(a, (const uint16_t *)Q, (const uint16_t *)O,
+                                                                      (const uint16_t *)dO, LSE, D, (uint16_t *)dQ, p.N, groups);
         return hipGetLastError();
     }
-    dq_shared_kernel<64, 1><<<dim3((unsigned)wgs), 512, 0, s>>>(t, (const uint16_t *)Q, (const uint16_t *)O,
-                                                             (const uint16_t *)dO, LSE, D, (uint16_t *)dQ, p.N, wgs);
+    dq_shared_kernel<64, 1><<<wgs, 512, 0, s>>>(a, (const uint16_t *)Q, (const uint16_t *)O,
+                                                             (const uint16_t *)dO, LSE, D, (uint16_t *)dQ, p.N, groups);
     return hipGetLastError();
 }
 

@@ -51,6 +51,29 @@ LevelTable make_level_table(const Plan &p, const void *K0, const void *V0, const
     return t;
 }
 
+ListArgs make_list_args(const LevelTable &t) {
+    ListArgs a;
+    memset(&a, 0, sizeof(a));
+    for (int l = 0; l < t.nlev; ++l) {
+        ListLevel &v = a.lev[l];
+        v.K = t.K[l];
+        v.V = t.V[l];
+        v.I = l < t.L ? t.I[l] : nullptr;
+        v.n = (int32_t)t.n[l];
+        v.rows = (int32_t)t.rows[l];
+        v.Kl = t.Kl[l];
+        v.first = t.bseg[l];
+        v.end = t.bseg[l + 1];
+        v.shift = t.lb * (l + 1) - 4;
+        v.bias2 = t.bias[l] * 1.4426950408889634f;
+    }
+    a.nlev = t.nlev;
+    a.lb = t.lb;
+    a.ls = t.ls;
+    a.scale = t.scale;
+    return a;
+}
+
 static llsa_status build_plan(const llsa_desc &d, Plan &p) {
     memset(&p, 0, sizeof(p));
     p.desc = d;

@@ -52,6 +52,35 @@ struct LevelTable {
     float scale;
 };
 
+// x / d for x < 2^31 by one 32-bit multiplication (a workgroup's first instructions: the compiler's division of two 64-bit
+// numbers is more than a hundred)
+struct FastDiv {
+    uint32_t d, m, s;
+    FastDiv() = default;
+    explicit FastDiv(int64_t div) : d((uint32_t)div), m(0), s(0) {
+        while (((int64_t)1 << s) < div) ++s;
+        m = (uint32_t)((((uint64_t)1 << (31 + s)) + d - 1) / d);
+    }
+    __host__ __device__ uint32_t operator()(uint32_t x) const { return (uint32_t)(((uint64_t)x * m) >> (31 + s)); }
+};
+
+// A level of the list as the workgroups of the shared-level kernels read it: one 64-byte scalar load from the kernel arguments.
+struct __attribute__((aligned(64))) ListLevel {
+    const void *K, *V;
+    const int32_t *I;               // null for a dense level
+    int32_t n, rows, Kl;
+    int32_t first, end;             // its 16-token tiles in the list
+    int32_t shift;                  // query tile q reads row q >> shift of I
+    float bias2;                    // log2 of its tokens' weight
+    int32_t pad[3];
+};
+struct ListArgs {
+    ListLevel lev[kMaxL + 1];
+    int32_t nlev, lb, ls;
+    float scale;
+};
+ListArgs make_list_args(const LevelTable &t);
+
 LevelTable make_level_table(const Plan &p, const void *K0, const void *V0, const int32_t *indices,
                             const void *workspace);
 

@@ -115,6 +115,11 @@ __device__ __forceinline__ int64_t xcd_contiguous(int64_t w, int64_t total) {
     return (w < per * 8) ? (w & 7) * per + (w >> 3) : w;
 }
 
+__device__ __forceinline__ unsigned xcd_contiguous32(unsigned w, unsigned total) {
+    const unsigned per = total >> 3;
+    return w < per * 8 ? (w & 7) * per + (w >> 3) : w;
+}
+
 // The 16-token key tiles of one 16-query tile's list (Alg. 1, enrichment loop), 64 at a time: lane j of the wave
 // describes tile 64 * chunk + j.  A listed block of B = 16 * 2^ls tokens is 2^ls consecutive tiles; query tile `blk`
 // (queries 16 blk ...) reads row 16 blk / B^(l+1) of I^(l).  The main loops fetch a block's fields with
@@ -183,6 +188,59 @@ struct BlockTable {
     }
     __device__ __forceinline__ const char *K(int j) const { return rl_ptr(kptr, j); }
     __device__ __forceinline__ const char *V(int j) const { return rl_ptr(vptr, j); }
+    __device__ __forceinline__ int count(int j) const { return __builtin_amdgcn_readlane(cnt, j); }
+    __device__ __forceinline__ float bias(int j) const {
+        return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(bias2), j));
+    }
+};
+
+// The coarse tiles (levels >= 1) of a query tile's list, 64 at a time: lane j describes tile 64 * chunk + j.  Every wave of a
+// workgroup builds its own copy: with the levels' fields as scalars straight from the kernel arguments that is about 15
+// instructions a level and one load in all, less than handing one wave's copy round through LDS and a barrier.
+typedef const __attribute__((address_space(4))) ListArgs *list_args_ptr;
+// the kernel's arguments begin with its ListArgs
+__device__ __forceinline__ list_args_ptr kernel_list_args() { return (list_args_ptr)__builtin_amdgcn_kernarg_segment_ptr(); }
+
+struct CoarseTable {
+    uint64_t kptr, vptr;     // address of the tile's first key / value row
+    float bias2;             // log2 of the level's token weight
+    int cnt;                 // valid rows: 16, fewer in the last tile of a ragged coarsest level, 0 past the end
+
+    template <int D> __device__ __forceinline__ void fill(list_args_ptr t, int64_t bh, unsigned tile, int chunk, int lane) {
+        const int j = t->lev[0].end + 64 * chunk + lane;
+        uint64_t listed = 0;                                 // where the lane's block id is to be found
+        int k = 0, n = 0;
+        kptr = vptr = 0;
+        bias2 = 0.f;
+        for (int l = 1; l < t->nlev; ++l) {
+            const auto &v = t->lev[l];
+            const int first = v.first;
+            const bool in = j >= first && j < v.end;
+            const int kk = j - first;
+            const int64_t head = bh * v.n * (2 * D);
+            kptr = in ? reinterpret_cast<uint64_t>(v.K) + head : kptr;
+            vptr = in ? reinterpret_cast<uint64_t>(v.V) + head : vptr;
+            bias2 = in ? v.bias2 : bias2;
+            k = in ? kk : k;
+            if (v.I) {
+                const uint64_t row = reinterpret_cast<uint64_t>(v.I) + (uint64_t)((bh * v.rows + (tile >> v.shift)) * v.Kl) * 4;
+                listed = in ? row + (uint64_t)(kk >> t->ls) * 4 : listed;
+            } else {
+                n = in ? v.n : n;
+            }
+        }
+        int tok = k << 4;                                    // dense level
+        cnt = min(16, n - tok);
+        if (listed) {
+            tok = (*reinterpret_cast<const int32_t *>(listed) << t->lb) + ((k & ((1 << t->ls) - 1)) << 4);
+            cnt = 16;
+        }
+        if (kptr == 0) cnt = 0;
+        kptr += (uint64_t)tok * (2 * D);
+        vptr += (uint64_t)tok * (2 * D);
+    }
+    __device__ __forceinline__ const char *K(int j) const { return BlockTable::rl_ptr(kptr, j); }
+    __device__ __forceinline__ const char *V(int j) const { return BlockTable::rl_ptr(vptr, j); }
     __device__ __forceinline__ int count(int j) const { return __builtin_amdgcn_readlane(cnt, j); }
     __device__ __forceinline__ float bias(int j) const {
         return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(bias2), j));
