@@ -34,9 +34,9 @@ __device__ __forceinline__ bf16x8 as_bf16x8(u32x4 v) {
     return c.b;
 }
 
-// NB = fine query blocks per wave (1 or 2), NW = waves per workgroup (4 or 8); a workgroup owns NW * NB consecutive
-// blocks, all siblings
-template <int D, int NB, int NW = 8>
+// NB = fine query tiles per wave (1 or 2), NW = waves per workgroup (4 or 8); a workgroup owns NW * NB consecutive
+// tiles, all siblings.  GW = waves whose tiles make up a block of 32 or 64 queries and share a level-0 list (0: B = 16)
+template <int D, int NB, int NW, int GW>
 __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 64 ? 4 : 2))) attn_fwd_shared_kernel(ListArgs args, const uint16_t *__restrict__ Q,
                                                                uint16_t *__restrict__ O, float *__restrict__ LSE,
                                                                int64_t N, FastDiv groups) {
@@ -78,6 +78,10 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D 
         lsum[b] = 0.f;
     }
 
+    using StrideA = std::integral_constant<int, STRIDE>;
+    using StrideB = std::integral_constant<int, VSTRIDE>;
+    using B0 = std::integral_constant<int, 0>;
+    using B1 = std::integral_constant<int, 1>;
     // Softmax update of query block b for one tile (s0 / s1: raw S^T of the two halves; b0 / b1: log2 weights of their levels,
     // -inf for an absent half): the probabilities as the B operand of O^T += V^T P^T.  The reference m[b] of a query is not
     // its exact maximum, and the usual tile does not even look for one: it takes the exponentials against the reference as
@@ -132,18 +136,48 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D 
 #pragma unroll
         for (int n = 0; n < NT; ++n) acc[b][n] = mfma16(lds_tr_pair(base + n * 32, base + 16 * VS + n * 32), pop, acc[b][n]);
     };
-    using StrideA = std::integral_constant<int, STRIDE>;
-    using StrideB = std::integral_constant<int, VSTRIDE>;
-    using B0 = std::integral_constant<int, 0>;
-    using B1 = std::integral_constant<int, 1>;
+    // One tile of 32 staged keys against all query tiles of the wave: every K operand and every transposed V operand is read
+    // from LDS once.
+    auto shared_tile = [&](const char *kt, const char *vt, auto vstride, int c0, int c1, float b0, float b1) {
+        constexpr int VS = decltype(vstride)::value;
+        bf16x8 kop[2][KS];
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks)
+                kop[h][ks] = *reinterpret_cast<const bf16x8 *>(kt + (h * 16 + i16) * STRIDE + g * 16 + ks * 64);
+        f32x4 s[NB][2];
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                s[b][h] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks) s[b][h] = mfma16(kop[h][ks], qop[b][ks], s[b][h]);
+            }
+        if constexpr (NB > 1) {                                       // both tiles' P first, then one transposing read of V for both
+            const bf16x8 p0 = probs(B0{}, s[0][0], s[0][1], c0, c1, b0, b1);
+            const bf16x8 p1 = probs(B1{}, s[NB - 1][0], s[NB - 1][1], c0, c1, b0, b1);
+            const char *base = vt + (4 * g + (i16 >> 2)) * VS + (i16 & 3) * 8;
+#pragma unroll
+            for (int n = 0; n < NT; ++n) {
+                const bf16x8 vtr = lds_tr_pair(base + n * 32, base + 16 * VS + n * 32);
+                acc[0][n] = mfma16(vtr, p0, acc[0][n]);
+                acc[NB - 1][n] = mfma16(vtr, p1, acc[NB - 1][n]);
+            }
+        } else {
+            pv(B0{}, probs(B0{}, s[0][0], s[0][1], c0, c1, b0, b1), vt, vstride);
+        }
+    };
 
     // The level-0 lists of this wave's NB query blocks, fetched now so that phase B does not wait for them:
-    // lane (64 / NB) b + j holds the first token of 16-token tile j of query tile b's list (at most 64 / NB tiles;
-    // a listed block of B tokens is B / 16 consecutive tiles, and B / 16 consecutive query tiles share a row of I^(0)).
+    // lane LL b + j holds the first token of 16-token tile j of query tile b's list (at most LL tiles; a listed block of B
+    // tokens is B / 16 consecutive tiles, and B / 16 consecutive query tiles share a row of I^(0): one list for all if GW > 0).
+    constexpr int LL = GW > 0 ? 64 : 64 / NB;
     const int nb0 = t->lev[0].end;                                        // level-0 tiles (the list always holds level 0)
     int tok0 = 0;
     {
-        const int b = lane / (64 / NB), j = lane % (64 / NB);
+        const int b = lane / LL, j = lane % LL;
         if (j < nb0) {
             const int64_t row = tile_of(b) >> t->ls;
             tok0 = (t->lev[0].I[(bh * t->lev[0].rows + row) * t->lev[0].Kl + (j >> t->ls)] << t->lb) + ((j & ((1 << t->ls) - 1)) << 4);
@@ -212,38 +246,49 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D 
             }
             __syncthreads();                                          // tile u visible; buffer buf^1 free again
             if (u + 1 < ntile) load_shared(u + 1);
-            const char *kt = sh(buf, 0), *vt = sh(buf, 1);
-            bf16x8 kop[2][KS];
-#pragma unroll
-            for (int h = 0; h < 2; ++h)
-#pragma unroll
-                for (int ks = 0; ks < KS; ++ks)
-                    kop[h][ks] = *reinterpret_cast<const bf16x8 *>(kt + (h * 16 + i16) * STRIDE + g * 16 + ks * 64);
-            f32x4 s[NB][2];
-#pragma unroll
-            for (int b = 0; b < NB; ++b)
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    s[b][h] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                    for (int ks = 0; ks < KS; ++ks) s[b][h] = mfma16(kop[h][ks], qop[b][ks], s[b][h]);
-                }
-            if constexpr (NB > 1) {                                   // both blocks' P first, then one transposing read of V for both
-                const bf16x8 p0 = probs(B0{}, s[0][0], s[0][1], cnt[0], cnt[1], bias2[0], bias2[1]);
-                const bf16x8 p1 = probs(B1{}, s[NB - 1][0], s[NB - 1][1], cnt[0], cnt[1], bias2[0], bias2[1]);
-                const char *base = vt + (4 * g + (i16 >> 2)) * STRIDE + (i16 & 3) * 8;
-#pragma unroll
-                for (int n = 0; n < NT; ++n) {
-                    const bf16x8 vtr = lds_tr_pair(base + n * 32, base + 16 * STRIDE + n * 32);
-                    acc[0][n] = mfma16(vtr, p0, acc[0][n]);
-                    acc[NB - 1][n] = mfma16(vtr, p1, acc[NB - 1][n]);
-                }
-            } else {
-                pv(B0{}, probs(B0{}, s[0][0], s[0][1], cnt[0], cnt[1], bias2[0], bias2[1]), vt, StrideA{});
-            }
+            shared_tile(sh(buf, 0), sh(buf, 1), StrideA{}, cnt[0], cnt[1], bias2[0], bias2[1]);
         }
     }
 
+    if constexpr (GW > 0) {
+        // -------------------------------------------------------------- phase B, blocks of 32 or 64 tokens
+        // The B queries of a block use one level-0 list: the GW waves that hold them stage its tiles together, as phase A does
+        // for the whole workgroup, double-buffered per group (GW = 1: a wave alone, whose LDS operations stay in order).  A
+        // list is whole blocks of B >= 32 tokens: no half of a tile is ever absent.  16 heads x 65536 tokens in blocks of 64, K = 8:
+        // 512 -> 365 us.
+        constexpr int R = 2 * 32 * PARTS / (64 * GW), BUF = TILE + VTILE, NBUF = GW > 1 ? 2 : 1;
+        static_assert((NW / GW) * NBUF * BUF <= NW * (TILE + VTILE), "the groups' buffers must fit");
+        __syncthreads();                                              // phase A's buffers are free
+        const int wg_in = wave % GW;
+        char *base = lds + (wave / GW) * (NBUF * BUF);
+        const int64_t head = bh * N;
+        const char *K0 = static_cast<const char *>(t->lev[0].K), *V0 = static_cast<const char *>(t->lev[0].V);
+        u32x4 sreg[R];
+        auto load_group = [&](int u) {                                // 64 chunks a round: rows of one half of K or of V
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const int c0 = 64 * (wg_in + GW * r), key0 = (c0 % (32 * PARTS)) / PARTS;
+                const char *src = c0 >= 32 * PARTS ? V0 : K0;
+                const int64_t row = head + __builtin_amdgcn_readlane(tok0, 2 * u + (key0 >> 4));
+                sreg[r] = gload16(src + row * (D * 2), (unsigned)((((key0 & 15) + lane / PARTS) * D + (lane % PARTS) * 8) * 2));
+            }
+        };
+        load_group(0);
+        for (int u = 0; 2 * u < nb0; ++u) {
+            char *buf = base + (u % NBUF) * BUF;
+            if constexpr (GW == 1) __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const int c0 = 64 * (wg_in + GW * r), row = (c0 % (32 * PARTS)) / PARTS + lane / PARTS;
+                char *dst = c0 >= 32 * PARTS ? buf + TILE + row * VSTRIDE : buf + row * STRIDE;
+                *reinterpret_cast<u32x4 *>(dst + (lane % PARTS) * 16) = sreg[r];
+            }
+            if constexpr (GW > 1) __syncthreads();
+            else __builtin_amdgcn_wave_barrier();
+            if (2 * u + 2 < nb0) load_group(u + 1);
+            shared_tile(buf, buf + TILE, StrideB{}, 16, 16, 0.f, 0.f);
+        }
+    } else {
     // ------------------------------------------------------------------ phase B: own level-0 blocks
     // K and V rows are fetched with 8 consecutive lanes per 128-byte row (whole cache lines per instruction: loading
     // the MFMA operand layout straight from memory, 16 rows x half a line per instruction, caps the gather rate at a
@@ -263,7 +308,7 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D 
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             const int j = (j0 + h < nb0) ? j0 + h : j0;               // an absent second half re-reads the first
-            off[h] = (bh * N + __builtin_amdgcn_readlane(tok0, (64 / NB) * b + j)) * (D * 2);
+            off[h] = (bh * N + __builtin_amdgcn_readlane(tok0, LL * b + j)) * (D * 2);
         }
 #pragma unroll
         for (int u = 0; u < VCH; ++u) {
@@ -298,6 +343,7 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D 
     load_tile(0, 0);
     phase_b(B0{});
     if constexpr (NB > 1) phase_b(B1{});
+    }
 
     // ------------------------------------------------------------------ epilogue
 #pragma unroll
@@ -323,15 +369,21 @@ hipError_t launch_attn_fwd_shared(const Plan &p, const LevelTable &t, const void
     const FastDiv groups((p.N + 127) / 128);
     const unsigned wgs = (unsigned)p.bh * groups.d;
     const ListArgs a = make_list_args(t);
-    if (p.d == 64 && (p.Kl[0] << (p.lb - 4)) <= 32) { // two query blocks per wave (measured faster than one)
-        // workgroups of four waves (8 query blocks), four per CU: same occupancy as two of eight waves, cheaper barriers
+    const uint16_t *q = (const uint16_t *)Q;
+    uint16_t *o = (uint16_t *)O;
+    const int ls = p.lb - 4;
+    if (p.d == 64 && (ls > 0 || p.Kl[0] <= 32)) {     // two query tiles per wave (measured faster than one)
+        // workgroups of four waves (8 query tiles), four per CU: same occupancy as two of eight waves, cheaper barriers
         // (measured 225 against 229 us)
-        attn_fwd_shared_kernel<64, 2, 4><<<wgs, 256, 0, s>>>(a, (const uint16_t *)Q, (uint16_t *)O, LSE, p.N, groups);
-    } else if (p.d == 64) {                           // K_0 > 32: both level-0 lists would not fit one register
-        attn_fwd_shared_kernel<64, 1><<<wgs, 512, 0, s>>>(a, (const uint16_t *)Q, (uint16_t *)O, LSE, p.N, groups);
-    } else {                                          // d = 128: one query block per wave (registers), 8 per workgroup
-        attn_fwd_shared_kernel<128, 1><<<wgs, 512, 0, s>>>(a, (const uint16_t *)Q, (uint16_t *)O, LSE,
-                                                                            p.N, groups);
+        if (ls == 0) attn_fwd_shared_kernel<64, 2, 4, 0><<<wgs, 256, 0, s>>>(a, q, o, LSE, p.N, groups);
+        else if (ls == 1) attn_fwd_shared_kernel<64, 2, 4, 1><<<wgs, 256, 0, s>>>(a, q, o, LSE, p.N, groups);
+        else attn_fwd_shared_kernel<64, 2, 4, 2><<<wgs, 256, 0, s>>>(a, q, o, LSE, p.N, groups);
+    } else if (p.d == 64) {                           // B = 16, K_0 > 32: both level-0 lists would not fit one register
+        attn_fwd_shared_kernel<64, 1, 8, 0><<<wgs, 512, 0, s>>>(a, q, o, LSE, p.N, groups);
+    } else {                                          // d = 128: one query tile per wave (registers), 8 per workgroup
+        if (ls == 0) attn_fwd_shared_kernel<128, 1, 8, 0><<<wgs, 512, 0, s>>>(a, q, o, LSE, p.N, groups);
+        else if (ls == 1) attn_fwd_shared_kernel<128, 1, 8, 2><<<wgs, 512, 0, s>>>(a, q, o, LSE, p.N, groups);
+        else attn_fwd_shared_kernel<128, 1, 8, 4><<<wgs, 512, 0, s>>>(a, q, o, LSE, p.N, groups);
     }
     return hipGetLastError();
 }

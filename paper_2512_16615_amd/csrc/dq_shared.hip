@@ -24,8 +24,9 @@ __device__ __forceinline__ bf16x8 to_bf16x8(u32x4 v) {
 __device__ __forceinline__ float bf_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
 
-// NB = fine query blocks per wave (1 or 2); a workgroup owns 8 * NB consecutive blocks, all siblings
-template <int D, int NB>
+// NB = fine query tiles per wave (1 or 2); a workgroup owns 8 * NB consecutive tiles, all siblings.  GW = waves whose tiles
+// make up a block of 32 or 64 queries and share a level-0 list (0: B = 16)
+template <int D, int NB, int GW>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(D == 64 ? 4 : 2)))
 dq_shared_kernel(ListArgs args, const uint16_t *__restrict__ Q, const uint16_t *__restrict__ O,
                  const uint16_t *__restrict__ dO, const float *__restrict__ LSE, float *__restrict__ Dsum,
@@ -111,13 +112,34 @@ dq_shared_kernel(ListArgs args, const uint16_t *__restrict__ Q, const uint16_t *
     };
     using B0 = std::integral_constant<int, 0>;
     using B1 = std::integral_constant<int, 1>;
+    // scores, dP - D and dQ of query tile b for one tile of 32 staged keys (V rows VS bytes apart); one query tile at a time
+    // keeps the live score registers low (the row-wise operands are re-read from LDS for a second one)
+    auto tile = [&](auto bsel, const char *kt, const char *vt, auto vstride, int c0, int c1, float b0, float b1) {
+        constexpr int b = decltype(bsel)::value, VS = decltype(vstride)::value;
+        f32x4 s[2], dp[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            s[h] = f32x4{0.f, 0.f, 0.f, 0.f};
+            dp[h] = ndelta[b];
+            const char *krow = kt + (h * 16 + i16) * STRIDE + g * 16, *vrow = vt + (h * 16 + i16) * VS + g * 16;
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                s[h] = mfma16(*reinterpret_cast<const bf16x8 *>(krow + ks * 64), qop[b][ks], s[h]);
+                dp[h] = mfma16(*reinterpret_cast<const bf16x8 *>(vrow + ks * 64), gop[b][ks], dp[h]);
+            }
+        }
+        ds_dq(bsel, s[0], s[1], dp[0], dp[1], c0, c1, b0, b1, kt);
+    };
+    using StrideA = std::integral_constant<int, STRIDE>;
+    using StrideB = std::integral_constant<int, VSTRIDE>;
 
     // The level-0 lists of this wave's NB query blocks, fetched now so that phase B does not wait for them:
-    // lane (64 / NB) b + j holds the first token of 16-token tile j of query tile b's list (as in the forward kernel).
+    // lane LL b + j holds the first token of 16-token tile j of query tile b's list (as in the forward kernel).
+    constexpr int LL = GW > 0 ? 64 : 64 / NB;
     const int nb0 = t->lev[0].end;
     int tok0 = 0;
     {
-        const int b = lane / (64 / NB), j = lane % (64 / NB);
+        const int b = lane / LL, j = lane % LL;
         if (j < nb0) {
             const int64_t row = tile_of(b) >> t->ls;
             tok0 = (t->lev[0].I[(bh * t->lev[0].rows + row) * t->lev[0].Kl + (j >> t->ls)] << t->lb) + ((j & ((1 << t->ls) - 1)) << 4);
@@ -185,30 +207,47 @@ dq_shared_kernel(ListArgs args, const uint16_t *__restrict__ Q, const uint16_t *
             }
             __syncthreads();
             if (u + 1 < ntile) load_shared(u + 1);
-            const char *kt = sh(buf, 0), *vt = sh(buf, 1);
-            // one query block at a time keeps the live score registers low (the row-wise operands are
-            // re-read from LDS for the second block)
-            auto scores = [&](auto bsel) {
-                constexpr int b = decltype(bsel)::value;
-                f32x4 s[2], dp[2];
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    s[h] = f32x4{0.f, 0.f, 0.f, 0.f};
-                    dp[h] = ndelta[b];
-#pragma unroll
-                    for (int ks = 0; ks < KS; ++ks) {
-                        const int off = (h * 16 + i16) * STRIDE + g * 16 + ks * 64;
-                        s[h] = mfma16(*reinterpret_cast<const bf16x8 *>(kt + off), qop[b][ks], s[h]);
-                        dp[h] = mfma16(*reinterpret_cast<const bf16x8 *>(vt + off), gop[b][ks], dp[h]);
-                    }
-                }
-                ds_dq(bsel, s[0], s[1], dp[0], dp[1], cnt[0], cnt[1], bias2[0], bias2[1], kt);
-            };
-            scores(B0{});
-            if constexpr (NB > 1) scores(B1{});
+            tile(B0{}, sh(buf, 0), sh(buf, 1), StrideA{}, cnt[0], cnt[1], bias2[0], bias2[1]);
+            if constexpr (NB > 1) tile(B1{}, sh(buf, 0), sh(buf, 1), StrideA{}, cnt[0], cnt[1], bias2[0], bias2[1]);
         }
     }
 
+    if constexpr (GW > 0) {
+        // -------------------------------------------------------------- phase B, blocks of 32 or 64 tokens
+        // The GW waves that hold the B queries of a block stage the tiles of their one level-0 list together, double-buffered
+        // per group, as in the forward kernel (16 heads x 65536 tokens in blocks of 64, K = 8: 677 -> 554 us).
+        constexpr int R = 2 * 32 * PARTS / (64 * GW), BUF = TILE + VTILE;
+        static_assert(GW > 1 && (8 / GW) * 2 * BUF <= 8 * (TILE + VTILE), "the groups' buffers must fit");
+        __syncthreads();                                              // phase A's buffers are free
+        const int wg_in = wave % GW;
+        char *base = lds + (wave / GW) * (2 * BUF);
+        const int64_t head = bh * N;
+        const char *K0 = static_cast<const char *>(t->lev[0].K), *V0 = static_cast<const char *>(t->lev[0].V);
+        u32x4 sreg[R];
+        auto load_group = [&](int u) {                                // 64 chunks a round: rows of one half of K or of V
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const int c0 = 64 * (wg_in + GW * r), key0 = (c0 % (32 * PARTS)) / PARTS;
+                const char *src = c0 >= 32 * PARTS ? V0 : K0;
+                const int64_t row = head + __builtin_amdgcn_readlane(tok0, 2 * u + (key0 >> 4));
+                sreg[r] = gload16b(src + row * (D * 2), (unsigned)((((key0 & 15) + lane / PARTS) * D + (lane % PARTS) * 8) * 2));
+            }
+        };
+        load_group(0);
+        for (int u = 0; 2 * u < nb0; ++u) {
+            char *buf = base + (u & 1) * BUF;
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const int c0 = 64 * (wg_in + GW * r), row = (c0 % (32 * PARTS)) / PARTS + lane / PARTS;
+                char *dst = c0 >= 32 * PARTS ? buf + TILE + row * VSTRIDE : buf + row * STRIDE;
+                *reinterpret_cast<u32x4 *>(dst + (lane % PARTS) * 16) = sreg[r];
+            }
+            __syncthreads();
+            if (2 * u + 2 < nb0) load_group(u + 1);
+            tile(B0{}, buf, buf + TILE, StrideB{}, 16, 16, 0.f, 0.f);
+            if constexpr (NB > 1) tile(B1{}, buf, buf + TILE, StrideB{}, 16, 16, 0.f, 0.f);
+        }
+    } else {
     // ------------------------------------------------------------------ phase B: own level-0 blocks
     // K and V rows are fetched with 8 consecutive lanes per 128-byte row (whole cache lines per instruction: loading
     // the MFMA operand layout straight from memory, 16 rows x half a line per instruction, caps the gather rate at a
@@ -228,7 +267,7 @@ dq_shared_kernel(ListArgs args, const uint16_t *__restrict__ Q, const uint16_t *
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 const int j = (j0 + h < nb0) ? j0 + h : j0;           // an absent second half re-reads the first
-                off[h] = (bh * N + __builtin_amdgcn_readlane(tok0, (64 / NB) * b + j)) * (D * 2);
+                off[h] = (bh * N + __builtin_amdgcn_readlane(tok0, LL * b + j)) * (D * 2);
             }
 #pragma unroll
             for (int u = 0; u < VCH; ++u) {
@@ -246,23 +285,12 @@ dq_shared_kernel(ListArgs args, const uint16_t *__restrict__ Q, const uint16_t *
             }
             __builtin_amdgcn_wave_barrier();
             if (j0 + 2 < nb0) load_tile(j0 + 2);                      // the registers are free again
-            f32x4 s[2], dp[2];
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                s[h] = f32x4{0.f, 0.f, 0.f, 0.f};
-                dp[h] = ndelta[b];
-                const char *krow = my + (h * 16 + i16) * STRIDE + g * 16, *vrow = my_v + (h * 16 + i16) * VSTRIDE + g * 16;
-#pragma unroll
-                for (int ks = 0; ks < KS; ++ks) {
-                    s[h] = mfma16(*reinterpret_cast<const bf16x8 *>(krow + ks * 64), qop[b][ks], s[h]);
-                    dp[h] = mfma16(*reinterpret_cast<const bf16x8 *>(vrow + ks * 64), gop[b][ks], dp[h]);
-                }
-            }
-            ds_dq(bsel, s[0], s[1], dp[0], dp[1], 16, 16, 0.f, j0 + 1 < nb0 ? 0.f : -INFINITY, my);
+            tile(bsel, my, my_v, StrideB{}, 16, 16, 0.f, j0 + 1 < nb0 ? 0.f : -INFINITY);
         }
     };
     phase_b(B0{});
     if constexpr (NB > 1) phase_b(B1{});
+    }
 
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
@@ -283,13 +311,18 @@ hipError_t launch_dq_shared(const Plan &p, const LevelTable &t, const void *Q, c
     const FastDiv groups((p.N + 127) / 128);
     const unsigned wgs = (unsigned)p.bh * groups.d;
     const ListArgs a = make_list_args(t);                             // one query tile per wave: 8 per workgroup
-    if (p.d == 128) {
-        dq_shared_kernel<128, 1><<<wgs, 512, 0, s>>>(a, (const uint16_t *)Q, (const uint16_t *)O,
-                                                                      (const uint16_t *)dO, LSE, D, (uint16_t *)dQ, p.N, groups);
-        return hipGetLastError();
-    }
-    dq_shared_kernel<64, 1><<<wgs, 512, 0, s>>>(a, (const uint16_t *)Q, (const uint16_t *)O,
-                                                             (const uint16_t *)dO, LSE, D, (uint16_t *)dQ, p.N, groups);
+    const int ls = p.lb - 4;
+    auto go = [&](auto d, auto gw) {
+        dq_shared_kernel<decltype(d)::value, 1, decltype(gw)::value><<<wgs, 512, 0, s>>>(
+            a, (const uint16_t *)Q, (const uint16_t *)O, (const uint16_t *)dO, LSE, D, (uint16_t *)dQ, p.N, groups);
+    };
+    auto by_block = [&](auto d) {
+        if (ls == 0) go(d, std::integral_constant<int, 0>{});
+        else if (ls == 1) go(d, std::integral_constant<int, 2>{});
+        else go(d, std::integral_constant<int, 4>{});
+    };
+    if (p.d == 128) by_block(std::integral_constant<int, 128>{});
+    else by_block(std::integral_constant<int, 64>{});
     return hipGetLastError();
 }
 
