@@ -28,16 +28,9 @@
 //      (Alg. 2's key-major lists, ascending), adds the share of its parent token (adjoint of mean
 //      pooling) and writes the level's fp32 gradient (dkv_gather_kernel).
 // No floating-point atomics; every sum has a fixed order.
-#include "mfma_common.h"
+#include "dkv_common.h"
 
 namespace llsa {
-
-template <int D> struct GShape {
-    static constexpr int ROWB = 2 * D;                  // bytes of a staged row
-    static constexpr int CH = D / 8;                    // 16-byte chunks per row
-    static constexpr int KS = D / 32, NT = D / 16;
-    static constexpr int UNIT = 2 * 16 * D;             // floats of one partial: [dK | dV][16 keys][D channels]
-};
 
 struct GroupArgs {
     const uint16_t *Q, *dO;
@@ -53,9 +46,6 @@ struct GroupArgs {
     int sparse_begin, do_dense;                         // upper kernel: first sparse block of this launch; does it take the dense one
     float sc2, scale;
 };
-
-// ---- the staged group: 256 rows of Q and of dO, unpadded, 16-byte chunks XOR-swizzled by row (swz_key)
-template <int D> __device__ __forceinline__ int swz(int r, int c) { return r * GShape<D>::ROWB + ((c ^ swz_key<D>(r)) << 4); }
 
 // The 256 Q and dO rows from row0 on, and their LSE and D, in the registers of NTHR threads ...
 template <int D, int NTHR> struct StageRegs {
@@ -77,7 +67,7 @@ __device__ __forceinline__ void stage_load(StageRegs<D, NTHR> &r, const GroupArg
         r.s[k] = i < 256 ? a.LSE[row0 + i] : a.Dsum[row0 + i - 256];
     }
 }
-// ... and from there into LDS (qs, gs: swizzled rows; st: -LSE log2(e) [256] | D [256])
+// ... and from there into LDS (qs, gs: swizzled rows; st: -LSE log2(e) [256] | -D [256])
 template <int D, int NTHR>
 __device__ __forceinline__ void stage_store(const StageRegs<D, NTHR> &r, char *qs, char *gs, float *st, int tid) {
     constexpr int CH = GShape<D>::CH;
@@ -87,84 +77,9 @@ __device__ __forceinline__ void stage_store(const StageRegs<D, NTHR> &r, char *q
         *reinterpret_cast<u32x4 *>(qs + swz<D>(cc / CH, cc % CH)) = r.q[k];
         *reinterpret_cast<u32x4 *>(gs + swz<D>(cc / CH, cc % CH)) = r.g[k];
     }
-    // LSE goes in as -LSE log2(e), the form the tiles' exponentials take it in
+    // the forms the tiles take them in
 #pragma unroll
-    for (int k = 0; k < 512 / NTHR; ++k) st[tid + NTHR * k] = (tid + NTHR * k < 256) ? r.s[k] * -kLog2e : r.s[k];
-}
-
-// One key block held by a wave: its K / V rows as B operands, the level's log2 weight, its gradient sums.
-// The tiles compute P = exp(z - LSE) without the level's weight B^l (a power of two for the block sizes of this
-// path: scaling by it commutes with the bf16 rounding of P and dS); the sums take it when they are written.
-template <int D> struct BlockAcc {
-    bf16x8 kop[D / 32], vop[D / 32];
-    float bias2;
-    f32x4 accK[D / 16], accV[D / 16];
-
-    __device__ __forceinline__ void clear() {
-#pragma unroll
-        for (int n = 0; n < D / 16; ++n) { accK[n] = f32x4{0.f, 0.f, 0.f, 0.f}; accV[n] = f32x4{0.f, 0.f, 0.f, 0.f}; }
-    }
-    // rows past a ragged end re-read the last row; an absent block (kp = null) gets zero operands
-    __device__ __forceinline__ void load(const char *kp, const char *vp, int cnt, float b2, int lane) {
-        bias2 = b2;
-        const int off = (min(lane & 15, max(cnt, 1) - 1) * D + (lane >> 4) * 8) * 2;
-#pragma unroll
-        for (int ks = 0; ks < D / 32; ++ks) {
-            kop[ks] = kp ? ld_bf16x8(kp + off + 64 * ks) : bf16x8{};
-            vop[ks] = kp ? ld_bf16x8(vp + off + 64 * ks) : bf16x8{};
-        }
-    }
-};
-
-// queries 32u .. 32u+31 of the staged group against NB key blocks: accK += Q^T dS, accV += dO^T P.
-// Every LDS operand is read once and used for all NB blocks.
-template <int D, int NB>
-__device__ __forceinline__ void group_tile(const char *qs, const char *gs, const float *st, int u, const TileOffsets<D> &o,
-                                           BlockAcc<D> (&blk)[NB], float sc2, int g) {
-    using S = GShape<D>;
-    f32x4 s[NB][2], dp[NB][2];
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const int base = (32 * u + 16 * h) * S::ROWB;
-        bf16x8 aq[S::KS], ag[S::KS];
-#pragma unroll
-        for (int ks = 0; ks < S::KS; ++ks) {
-            aq[ks] = *reinterpret_cast<const bf16x8 *>(qs + base + o.row[ks]);
-            ag[ks] = *reinterpret_cast<const bf16x8 *>(gs + base + o.row[ks]);
-        }
-        const f32x4 l2 = *reinterpret_cast<const f32x4 *>(st + 32 * u + 16 * h + 4 * g);
-        const f32x4 dl = *reinterpret_cast<const f32x4 *>(st + 256 + 32 * u + 16 * h + 4 * g);
-#pragma unroll
-        for (int b = 0; b < NB; ++b) {
-            s[b][h] = f32x4{0.f, 0.f, 0.f, 0.f};
-            dp[b][h] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int ks = 0; ks < S::KS; ++ks) {
-                s[b][h] = mfma16(aq[ks], blk[b].kop[ks], s[b][h]);
-                dp[b][h] = mfma16(ag[ks], blk[b].vop[ks], dp[b][h]);
-            }
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const float p = __builtin_amdgcn_exp2f(fmaf(s[b][h][r], sc2, l2[r]));   // without the level's weight
-                s[b][h][r] = p;
-                dp[b][h][r] = p * (dp[b][h][r] - dl[r]);
-            }
-        }
-    }
-    bf16x8 pop[NB], dsop[NB];
-#pragma unroll
-    for (int b = 0; b < NB; ++b) { pop[b] = pack8(s[b][0], s[b][1]); dsop[b] = pack8(dp[b][0], dp[b][1]); }
-    const int b0 = 32 * u * S::ROWB, b1 = b0 + 16 * S::ROWB;
-#pragma unroll
-    for (int n = 0; n < S::NT; ++n) {
-        const bf16x8 tg = lds_tr_pair(gs + b0 + o.tr[n], gs + b1 + o.tr[n]);
-        const bf16x8 tq = lds_tr_pair(qs + b0 + o.tr[n], qs + b1 + o.tr[n]);
-#pragma unroll
-        for (int b = 0; b < NB; ++b) {
-            blk[b].accV[n] = mfma16(tg, pop[b], blk[b].accV[n]);
-            blk[b].accK[n] = mfma16(tq, dsop[b], blk[b].accK[n]);
-        }
-    }
+    for (int k = 0; k < 512 / NTHR; ++k) st[tid + NTHR * k] = (tid + NTHR * k < 256) ? r.s[k] * -kLog2e : -r.s[k];
 }
 
 // where the partial of list block jl (counted from the start of the list) of query group `grp` goes
@@ -197,7 +112,7 @@ __global__ void __launch_bounds__(64 * NW) dkv_group_kernel(LevelTable t, GroupA
     using S = GShape<D>;
     __shared__ __attribute__((aligned(16))) char qs[256 * S::ROWB];   // Q rows of the group, chunk-swizzled
     __shared__ __attribute__((aligned(16))) char gs[256 * S::ROWB];   // dO rows
-    __shared__ __attribute__((aligned(16))) float st[512];            // LSE | D
+    __shared__ __attribute__((aligned(16))) float st[512];            // -LSE log2(e) | -D
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -225,7 +140,7 @@ __global__ void __launch_bounds__(64 * NW) dkv_group_kernel(LevelTable t, GroupA
             blk[b].load(jb + b < nbc ? ctab.K(j) : nullptr, ctab.V(j), ctab.count(j), ctab.bias(j), lane);
             blk[b].clear();
         }
-        for (int u = 0; u < 8; ++u) group_tile<D, NB>(qs, gs, st, u, o, blk, a.sc2, g);
+        for (int u = 0; u < 8; ++u) group_tile<D, NB>(qs, gs, st, st + 256, u, o, blk, a.sc2, g);
 #pragma unroll
         for (int b = 0; b < NB; ++b)
             if (jb + b < nbc) store_partial<D>(partial_ptr<D>(t, a, nlev, jb + b + c_begin, R), blk[b], a.scale, lane);
@@ -311,7 +226,7 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2)
         __syncthreads();                                              // everyone is done with the previous rows
         stage_store<D, 64 * NW>(sr, qs, gs, st, tid);
         __syncthreads();
-        for (int u = 0; u < 8; ++u) group_tile<D, NB>(qs, gs, st, u, o, blk, a.sc2, g);
+        for (int u = 0; u < 8; ++u) group_tile<D, NB>(qs, gs, st, st + 256, u, o, blk, a.sc2, g);
     }
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
@@ -370,8 +285,9 @@ __global__ void __launch_bounds__(512) dkv_upper_kernel(LevelTable t, GroupArgs 
 #pragma unroll
         for (int s = 0; s < SS; ++s)
             if (a.sparse_begin + wave + 8 * s < a.nbs)
-                for (int u = 0; u < 8; ++u) group_tile<D, 1>(qs, gs, st, u, o, sp[s], a.sc2, g);
-        if (dense) group_tile<D, 1>(qs, gs, st, wave, o, dn, a.sc2, g);
+#pragma unroll 1                                                      // unrolled it takes 251 registers: none left beside it
+                for (int u = 0; u < 8; ++u) group_tile<D, 1>(qs, gs, st, st + 256, u, o, sp[s], a.sc2, g);
+        if (dense) group_tile<D, 1>(qs, gs, st, st + 256, wave, o, dn, a.sc2, g);
         __syncthreads();                                              // everyone is done with this R's rows
     }
 

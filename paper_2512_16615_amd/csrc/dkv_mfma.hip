@@ -18,24 +18,9 @@
 //     own; a key block whose list is long is instead worked on by all four waves together afterwards.
 //     The epilogue adds the parent token's share and rounds once to bf16.
 // Every sum has a fixed order, so results do not depend on timing.
-#include "mfma_common.h"
+#include "dkv_common.h"
 
 namespace llsa {
-
-struct DkvArgs {
-    const uint16_t *Q, *dO, *Kl, *Vl;     // Kl, Vl: the level's keys / values [bh, n_l, D]
-    const float *LSE, *Dsum;
-    const int32_t *C, *Iq;                // key-major lists (unused when dense)
-    float *partK, *partV;                 // [splits][slab] fp32 (levels >= 1)
-    const float *parK, *parV;             // level-1 totals [bh, n_1, D] fp32 or null (level 0)
-    uint16_t *dK, *dV;                    // level-0 outputs
-    int64_t N, n_l, total_kb, rows, slab; // total_kb = key tiles of all heads; rows = key blocks of this level per head that have lists
-    int span_shift;                       // log2 of the 16-query groups per listed query block: log2(B^(level+1) / 16)
-    int ls, lb;                           // log2(B / 16), log2 B: 16-key tile j lies in listed block j >> ls
-    float inv_B;
-    int Kl_cnt, dense, splits;
-    float sc2, bias2, scale;
-};
 
 template <int D> struct DkvShape {
     static constexpr int KS = D / 32, NT = D / 16, STRIDE = D * 2 + 32, VCH = D / 16, PARTS = D / 8, KPU = 64 / PARTS;
@@ -368,6 +353,7 @@ __global__ void __launch_bounds__(256) dkv_reduce_kernel(const float *partK, con
 
 int dkv_splits(const Plan &p, int l) {
     if (l == 0) return 1;
+    if (dkv_block_tiles(p, l)) return dkv_block_splits(p, l);
     // aim for a few thousand workgroups per level; a workgroup should still see several tiles
     const int64_t key_blocks = (int64_t)p.bh * ((p.n[l] + 15) / 16);
     const int64_t tiles_per_block = (l == p.L) ? p.N / 32 : (int64_t)p.K * (p.N / p.n[l + 1]) / 32;  // average
@@ -404,17 +390,24 @@ hipError_t launch_dkv_mfma(const Plan &p, const LevelTable &t, int l, const void
     a.ls = p.lb - 4; a.lb = p.lb; a.inv_B = 1.f / (float)p.B;
     a.Kl_cnt = a.dense ? 0 : p.Kl[l];
     a.sc2 = p.scale * kLog2e; a.bias2 = t.bias[l] * kLog2e; a.scale = p.scale;
-    if (l == 0) {                                           // four key tiles per workgroup
+    const bool block = dkv_block_tiles(p, l) > 0;
+    if (block) {
+        if (l > 0) a.dK = a.dV = nullptr;
+        const hipError_t e = launch_dkv_block(p, l, a, s);
+        if (l == 0 || e != hipSuccess) return e;
+    } else if (l == 0) {                                    // four key tiles per workgroup
         dim3 grid((unsigned)((key_blocks + 3) / 4));
         if (p.d == 64) dkv_fine_kernel<64><<<grid, 256, 0, s>>>(a);
         else dkv_fine_kernel<128><<<grid, 256, 0, s>>>(a);
         return hipGetLastError();
     }
-    dim3 grid((unsigned)(key_blocks * a.splits));
-    if (p.d == 64) dkv_coarse_kernel<64><<<grid, 256, 0, s>>>(a);
-    else dkv_coarse_kernel<128><<<grid, 256, 0, s>>>(a);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+    if (!block) {
+        dim3 grid((unsigned)(key_blocks * a.splits));
+        if (p.d == 64) dkv_coarse_kernel<64><<<grid, 256, 0, s>>>(a);
+        else dkv_coarse_kernel<128><<<grid, 256, 0, s>>>(a);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
     // fold the slabs (and the level above) into this level's fp32 gradient
     const int64_t total4 = (int64_t)p.bh * p.n[l] * p.d / 4;
     const bool has_up = l < p.Le;

@@ -132,6 +132,7 @@ hipError_t launch_dq_shared(const Plan &p, const LevelTable &t, const void *Q, c
 hipError_t launch_dkv_mfma(const Plan &p, const LevelTable &t, int l, const void *Q, const void *dO, const float *LSE,
                            const float *D, void *ws, void *dK, void *dV, hipStream_t s, bool level0_alone = false);
 int dkv_splits(const Plan &p, int l);    // workgroups sharing one key block's query list at level l
+int dkv_block_tiles(const Plan &p, int l), dkv_block_splits(const Plan &p, int l);   // the same for dkv_block.hip's levels
 // all coarse levels (dkv_group_top .. 1) at once, grouped by level-1 query block; fills the levels' fp32
 // gradients.  `lists` (or null): event after which the key-major lists are complete, recorded on another stream;
 // `s` waits for it behind the kernels that need no list, before the gathers.  `side`, `upper_done` (or null): the

@@ -117,3 +117,20 @@ def test_index_transpose_by_size(T, K, heads):
 ], ids=lambda c: c["name"])
 def test_grouped_upper_levels(cfg):
     _full_parity(cfg, 0xD15E)
+
+
+@pytest.mark.parametrize("cfg", [
+    # dK/dV of key blocks of several tiles: blocks of 32 (two waves a tile) and 64, at d = 64 and 128; lists split over
+    # workgroups; dense levels of 33, 65 and 129 tokens (a ragged tile, a spare wave, a spare block) under an odd number of query
+    # tiles; no coarse level in the list
+    _bf16("B32_L2", 32 * 1024, L=2, heads=1, B=32, K=4),
+    _bf16("B32_d128", 32 * 33, heads=2, B=32, K=4, d=128),
+    _bf16("B64_d128", 64 * 65, heads=1, B=64, K=2, d=128),
+    _bf16("B64_L2_split", 64 * 64 * 33, L=2, heads=1, B=64, K=3),
+    _bf16("B64_Le0", 64 * 20, heads=2, B=64, K=4, Le=0),
+    _bf16("dense_129", 16 * 129, heads=2),
+    _bf16("dense_33_d128", 16 * 33, heads=2, d=128),
+    _bf16("dense_65_L2_d128", 256 * 65, L=2, heads=1, d=128, K=4),
+], ids=lambda c: c["name"])
+def test_key_blocks_of_several_tiles(cfg):
+    _full_parity(cfg, 0xD15F)
