@@ -43,7 +43,6 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D 
     constexpr int KS = D / 32, NT = D / 16, STRIDE = D * 2 + 32, PARTS = D / 8, TILE = 32 * STRIDE;
     constexpr int NTHR = 64 * NW;
     constexpr int RND = (2 * 32 * PARTS) / NTHR;        // staging rounds of the workgroup per shared tile (K and V)
-    static_assert(RND == 1 || NTHR == 32 * PARTS, "with two rounds, round 0 is the K half and round 1 the V half");
     constexpr int VCH = D / 16, KPU = 64 / PARTS;       // private V staging of one wave (phase B)
     // Phase B: per wave a K tile (row-wise reads: rows 32 bytes apart in the banks) and a V tile (transposed reads only:
     // 16 bytes of padding do).  Phase A's two double-buffered [K | V] tiles live in the first 4 TILE bytes of the same
@@ -191,7 +190,7 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D 
         ctab.fill<D>(t, bh, (unsigned)blk0, 0, lane);
         // Staging round r of this wave: 64 consecutive 16-byte chunks of the [K | V] tile, i.e. 64 / PARTS key rows of
         // one half of K or of V, the same choice for the whole wave.
-        // (d = 64: one round, waves 0-3 stage K, waves 4-7 V; d = 128: round 0 stages K, round 1 V.)
+        // (One round: the first half of the waves stages K, the other V; more: the first half of the rounds stages K.)
         u32x4 sreg[RND];
         int s_half[RND];
         unsigned s_off[RND];
@@ -201,7 +200,7 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D 
             s_half[r] = key0 >> 4;
             s_off[r] = (unsigned)((((key0 & 15) + lane / PARTS) * D + (lane % PARTS) * 8) * 2);
         }
-        const bool v_wave = RND == 1 && wave >= 4;
+        const bool v_wave = RND == 1 && wave >= NW / 2;
         uint64_t sptr = v_wave ? ctab.vptr : ctab.kptr;               // d = 64: the tensor this wave stages
         const int ntile = (nbc + 1) >> 1;                             // only the last tile may be ragged or lack its second half
         auto load_shared = [&](int u) {                               // coarse blocks 2u, 2u + 1 -> registers
@@ -213,7 +212,7 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D 
             for (int r = 0; r < RND; ++r) {
                 const bool have = 2 * u + s_half[r] < nbc;
                 const int j = (have ? 2 * u + s_half[r] : 2 * u) & 63;
-                const char *src = RND == 1 ? BlockTable::rl_ptr(sptr, j) : (r == 0 ? ctab.K(j) : ctab.V(j));
+                const char *src = RND == 1 ? BlockTable::rl_ptr(sptr, j) : (r < RND / 2 ? ctab.K(j) : ctab.V(j));
                 unsigned off = s_off[r];
                 if (u + 1 == ntile) {
                     const int cnt = have ? ctab.count(j) : 0;
@@ -372,18 +371,31 @@ hipError_t launch_attn_fwd_shared(const Plan &p, const LevelTable &t, const void
     const uint16_t *q = (const uint16_t *)Q;
     uint16_t *o = (uint16_t *)O;
     const int ls = p.lb - 4;
-    if (p.d == 64 && (ls > 0 || p.Kl[0] <= 32)) {     // two query tiles per wave (measured faster than one)
-        // workgroups of four waves (8 query tiles), four per CU: same occupancy as two of eight waves, cheaper barriers
-        // (measured 225 against 229 us)
-        if (ls == 0) attn_fwd_shared_kernel<64, 2, 4, 0><<<wgs, 256, 0, s>>>(a, q, o, LSE, p.N, groups);
-        else if (ls == 1) attn_fwd_shared_kernel<64, 2, 4, 1><<<wgs, 256, 0, s>>>(a, q, o, LSE, p.N, groups);
-        else attn_fwd_shared_kernel<64, 2, 4, 2><<<wgs, 256, 0, s>>>(a, q, o, LSE, p.N, groups);
-    } else if (p.d == 64) {                           // B = 16, K_0 > 32: both level-0 lists would not fit one register
-        attn_fwd_shared_kernel<64, 1, 8, 0><<<wgs, 512, 0, s>>>(a, q, o, LSE, p.N, groups);
-    } else {                                          // d = 128: one query tile per wave (registers), 8 per workgroup
-        if (ls == 0) attn_fwd_shared_kernel<128, 1, 8, 0><<<wgs, 512, 0, s>>>(a, q, o, LSE, p.N, groups);
-        else if (ls == 1) attn_fwd_shared_kernel<128, 1, 8, 2><<<wgs, 512, 0, s>>>(a, q, o, LSE, p.N, groups);
-        else attn_fwd_shared_kernel<128, 1, 8, 4><<<wgs, 512, 0, s>>>(a, q, o, LSE, p.N, groups);
+    auto go = [&](auto d, auto nb, auto gw) {
+        constexpr int NB = decltype(nb)::value, NW = 8 / NB;
+        attn_fwd_shared_kernel<decltype(d)::value, NB, NW, decltype(gw)::value><<<wgs, 64 * NW, 0, s>>>(a, q, o, LSE, p.N, groups);
+    };
+    using I0 = std::integral_constant<int, 0>;
+    using I1 = std::integral_constant<int, 1>;
+    using I2 = std::integral_constant<int, 2>;
+    using D64 = std::integral_constant<int, 64>;
+    using D128 = std::integral_constant<int, 128>;
+    // Two query tiles per wave read every coarse operand from LDS once for both: half the LDS reads, which bound d = 128
+    // (16 heads x 262144 tokens, K = 16: 1977 -> 1512 us; 4096 tokens: 33.9 -> 30.1).  At d = 64 they pay from four
+    // workgroups per CU on (131072 queries: 33.6 -> 30.4 us); with fewer, eight waves with a tile each hide more of the
+    // latency (65536 queries: 18.2 against 18.9, 32768: 12.6 against 14.1).  Both tiles' level-0 lists have to fit one register.
+    if (ls == 1) {
+        if (p.d == 64) go(D64{}, I2{}, I1{});
+        else go(D128{}, I2{}, I1{});
+    } else if (ls == 2) {
+        if (p.d == 64) go(D64{}, I2{}, I2{});
+        else go(D128{}, I2{}, I2{});
+    } else if (p.d == 64) {
+        if (p.Kl[0] <= 32 && wgs >= 1024) go(D64{}, I2{}, I0{});
+        else go(D64{}, I1{}, I0{});
+    } else {
+        if (p.Kl[0] <= 32) go(D128{}, I2{}, I0{});
+        else go(D128{}, I1{}, I0{});
     }
     return hipGetLastError();
 }

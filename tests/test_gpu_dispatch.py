@@ -134,3 +134,17 @@ def test_grouped_upper_levels(cfg):
 ], ids=lambda c: c["name"])
 def test_key_blocks_of_several_tiles(cfg):
     _full_parity(cfg, 0xD15F)
+
+
+@pytest.mark.parametrize("cfg", [
+    # query tiles per wave: a chip full of workgroups whose last one per head is ragged (25 query tiles, blocks of 32 and of 64),
+    # lists longer than a pair of tiles may have, blocks of 32 at d = 128
+    _bf16("B16_1024_wgs", 400, heads=256),
+    _bf16("B32_1024_wgs", 416, heads=256, B=32, K=3),
+    _bf16("B64_1026_wgs", 320, heads=342, B=64, K=2),
+    _bf16("K33", 16 * 43, heads=2, K=33),
+    _bf16("K33_d128", 16 * 43, heads=2, K=33, d=128),
+    _bf16("B32_odd_d128", 32 * 21, heads=2, B=32, K=5, d=128),
+], ids=lambda c: c["name"])
+def test_query_tiles_per_wave(cfg):
+    _full_parity(cfg, 0xD160)
