@@ -9,7 +9,7 @@
 // queries: a fp32 partial of 2 x 16 x d values.  Three kernels produce the partials:
 //   dkv_group_kernel: one R per workgroup; a wave takes NB list blocks at a time (d = 64: 4 waves x 2 blocks fed
 //     from one LDS read of each tile; d = 128: 8 waves x 1 block) of the levels it is given;
-//   dkv_chain_kernel: level 1 with 8 listed blocks at d = 64.  The same tile loop, but a workgroup walks several
+//   dkv_chain_kernel: level 1 with at most 8 listed blocks.  The same tile loop, but a workgroup walks several
 //     consecutive R and a key block listed by a run of them keeps its sums in registers: one partial per run;
 //   dkv_upper_kernel: levels >= 2 only.  The 16 level-1 blocks under one level-2 query block list the same
 //     key blocks at every level >= 2, so a workgroup of 8 waves walks G of them (G divides 16; the next one's
@@ -147,14 +147,14 @@ __global__ void __launch_bounds__(64 * NW) dkv_group_kernel(LevelTable t, GroupA
     }
 }
 
-// Level 1 alone, rows of I^(1) with exactly NW * NB entries.  Neighbouring level-1 query blocks list mostly the same
+// Level 1 alone, rows of I^(1) with at most NW * NB entries.  Neighbouring level-1 query blocks list mostly the same
 // level-1 key blocks (for spatially smooth inputs a block stays listed over many consecutive rows), and a partial per
 // (query block, listed block) then carries the same key block's sums to memory again and again.  Here a workgroup
 // walks GC consecutive level-1 query blocks and keeps one listed block per register slot, as dkv_group_kernel does
 // for a single query block.  From one query block R to the next, a slot whose key block is listed again goes on
 // accumulating; a slot whose block is not listed by R + 1 writes its partial to the place of (R, the block's
-// position in R's row) and takes one of the blocks that are new in R + 1 (both rows have NW * NB distinct entries,
-// so as many slots come free as blocks are new).  A partial therefore covers a run of consecutive query blocks of
+// position in R's row) and takes one of the blocks that are new in R + 1 (both rows have Kl distinct entries,
+// so as many slots come free as blocks are new; slots from Kl on compute on block 0 and are never stored).  A partial therefore covers a run of consecutive query blocks of
 // one chain that all list the key block, and sits where the last of them would have put its own; the gather skips
 // a lister whose successor in the same chain lists the block too.  Same arithmetic per tile, fewer partials.
 template <int D, int NW, int NB>
@@ -171,37 +171,39 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2)
     const int64_t per_head = a.NR / a.GC;
     const int64_t grp = xcd_contiguous(blockIdx.x, gridDim.x);
     const int64_t bh = grp / per_head, R0 = (grp % per_head) * a.GC;
+    const int slot0 = NB * wave;                                    // this wave's first slot
+    const int Kl = t.Kl[1];
     const TileOffsets<D> o = tile_offsets<D>(lane);
-    const int32_t *I1 = t.I[1] + (bh * a.NR + R0) * SL;               // I^(1) has one row per level-1 query block
+    const int32_t *I1 = t.I[1] + (bh * a.NR + R0) * Kl;               // I^(1) has one row per level-1 query block
     const char *K1 = static_cast<const char *>(t.K[1]) + bh * t.n[1] * D * 2;
     const char *V1 = static_cast<const char *>(t.V[1]) + bh * t.n[1] * D * 2;
     const float bias2 = t.bias[1] * kLog2e;
-    float *slab1 = a.slab + a.lvl_off[1] + (bh * a.NR + R0) * SL * S::UNIT;
+    float *slab1 = a.slab + a.lvl_off[1] + (bh * a.NR + R0) * Kl * S::UNIT;
 
-    int sblk = -1, spos = 0;                                          // lane s < SL: the block slot s holds, its place in the row
-    BlockAcc<D> blk[NB];                                              // this wave's slots NB * wave ...
+    int sblk = -1, spos = 0;                                          // lane s < Kl: the block slot s holds, its place in the row
+    BlockAcc<D> blk[NB];                                              // this wave's slots slot0 ...
     for (int r = 0; r < a.GC; ++r) {
         StageRegs<D, 64 * NW> sr;
         stage_load<D, 64 * NW>(sr, a, bh * a.N + (R0 + r) * 256, tid);   // in flight during the bookkeeping below
-        const int nb = lane < SL ? I1[r * SL + lane] : -1;            // lane p: entry p of this query block's row
+        const int nb = lane < Kl ? I1[r * Kl + lane] : -1;            // lane p: entry p of this query block's row
         if (r == 0) {
             sblk = nb;
             spos = lane;
 #pragma unroll
             for (int b = 0; b < NB; ++b) {
-                const int64_t id = __builtin_amdgcn_readlane(nb, NB * wave + b);
+                const int64_t id = max(__builtin_amdgcn_readlane(nb, slot0 + b), 0);
                 blk[b].load(K1 + id * 16 * D * 2, V1 + id * 16 * D * 2, 16, bias2, lane);
                 blk[b].clear();
             }
         } else {
-            bool keep = false, fresh = lane < SL;
+            bool keep = false, fresh = lane < Kl;                  // (slots without a block keep it: -1 on both sides)
             int npos = 0;
 #pragma unroll
             for (int x = 0; x < SL; ++x) {
                 if (sblk == __builtin_amdgcn_readlane(nb, x)) { keep = true; npos = x; }
                 if (nb == __builtin_amdgcn_readlane(sblk, x)) fresh = false;
             }
-            const uint64_t kept = __ballot(keep), freed = __ballot(lane < SL && !keep), news = __ballot(fresh);
+            const uint64_t kept = __ballot(keep), freed = __ballot(lane < Kl && !keep), news = __ballot(fresh);
             // the k-th slot that comes free takes the k-th new entry of the row
             const int k = __popcll(freed & ((1ull << lane) - 1));
             uint64_t m = news;
@@ -211,10 +213,10 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2)
             const int nid = __shfl(nb, src, 64);
 #pragma unroll
             for (int b = 0; b < NB; ++b) {
-                const int s = NB * wave + b;
+                const int s = slot0 + b;
                 if (!((kept >> s) & 1)) {                             // wave-uniform
                     const int oldpos = __builtin_amdgcn_readlane(spos, s);
-                    store_partial<D>(slab1 + ((int64_t)(r - 1) * SL + oldpos) * S::UNIT, blk[b], a.scale, lane);
+                    store_partial<D>(slab1 + ((int64_t)(r - 1) * Kl + oldpos) * S::UNIT, blk[b], a.scale, lane);
                     const int64_t id = __builtin_amdgcn_readlane(nid, s);
                     blk[b].load(K1 + id * 16 * D * 2, V1 + id * 16 * D * 2, 16, bias2, lane);
                     blk[b].clear();
@@ -230,8 +232,9 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2)
     }
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
-        const int pos = __builtin_amdgcn_readlane(spos, NB * wave + b);
-        store_partial<D>(slab1 + ((int64_t)(a.GC - 1) * SL + pos) * S::UNIT, blk[b], a.scale, lane);
+        if (slot0 + b >= Kl) continue;
+        const int pos = __builtin_amdgcn_readlane(spos, slot0 + b);
+        store_partial<D>(slab1 + ((int64_t)(a.GC - 1) * Kl + pos) * S::UNIT, blk[b], a.scale, lane);
     }
 }
 
@@ -446,11 +449,14 @@ static int upper_G(const Plan &p) {
 }
 
 // Level-1 query blocks one workgroup of the chain kernel walks (1: the plain group kernel takes level 1).
-// d = 64 with rows of 8 level-1 blocks, level 1 sparse and the only level the kernel is given.
+// Rows of at most 8 level-1 blocks, level 1 sparse and the only level the kernel is given.  16 heads x 65536 tokens, smooth
+// inputs, steps without and with it: K = 4 958 -> 875 us, K = 6 1105 -> 1017, d = 128 2677 -> 2463; Gaussian ones, which share few
+// blocks: K = 4 970 -> 951, d = 128 2903 -> 2868.  Rows of 9 to 16 would need two workgroups that stage the same rows: 1994 ->
+// 1845 us at 65536 tokens (K = 16), but 2270 -> 2310 for Gaussian inputs and 8506 -> 8631 at 262144 tokens, d = 128.
 // Measured at the headline: 8 query blocks per workgroup in 512 workgroups (two per CU) 259 us for the coarse stage,
 // 4 in 1024: 275 us, 2: 297 us, 16 in 256 workgroups: 286 us, one query block per workgroup (no carrying): 357 us.
 static int chain_len(const Plan &p) {
-    if (p.d != 64 || p.L < 2 || p.Kl[1] != 8) return 1;
+    if (p.L < 2 || p.Kl[1] > 8) return 1;
     if (upper_G(p) == 0 && dkv_group_top(p) > 1) return 1;
     const int64_t NR = p.N / 256;
     int GC = 8;
@@ -539,7 +545,10 @@ static hipError_t finish_level(const Plan &p, const LevelTable &t, const GroupAr
 
 static hipError_t launch_group_kernel(const Plan &p, const LevelTable &t, const GroupArgs &a, hipStream_t s) {
     if (a.GC > 1) {
-        dkv_chain_kernel<64, 4, 2><<<dim3((unsigned)(p.bh * (a.NR / a.GC))), 256, 0, s>>>(t, a);
+        const unsigned wgs = (unsigned)(p.bh * (a.NR / a.GC));
+        if (p.d == 128) dkv_chain_kernel<128, 8, 1><<<wgs, 512, 0, s>>>(t, a);
+        else if (p.Kl[1] <= 4) dkv_chain_kernel<64, 4, 1><<<wgs, 256, 0, s>>>(t, a);
+        else dkv_chain_kernel<64, 4, 2><<<wgs, 256, 0, s>>>(t, a);
         return hipGetLastError();
     }
     const dim3 grid((unsigned)(p.bh * a.NR));

@@ -148,3 +148,17 @@ def test_key_blocks_of_several_tiles(cfg):
 ], ids=lambda c: c["name"])
 def test_query_tiles_per_wave(cfg):
     _full_parity(cfg, 0xD160)
+
+
+@pytest.mark.parametrize("cfg", [
+    # level-1 dK/dV carried along 2 or 4 query blocks (heads x level-1 query blocks >= 1024): rows shorter than the register
+    # slots, rows of all slots, rows one too long for it, at d = 64 and 128
+    _bf16("chain_K3", 8192, L=2, heads=32, K=3),
+    _bf16("chain_K4", 8192, L=2, heads=64, K=4),
+    _bf16("chain_K6", 8192, L=2, heads=32, K=6),
+    _bf16("chain_K9", 8192, L=2, heads=32, K=9),
+    _bf16("chain_K6_d128", 8192, L=2, heads=32, K=6, d=128),
+    _bf16("chain_K8_d128", 8192, L=2, heads=32, K=8, d=128),
+], ids=lambda c: c["name"])
+def test_level1_sums_carried_along_query_blocks(cfg):
+    _full_parity(cfg, 0xD161)
