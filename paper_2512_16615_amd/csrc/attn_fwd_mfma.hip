@@ -17,7 +17,7 @@ namespace llsa {
 template <int D>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 64 ? 4 : 2))) attn_fwd_mfma_kernel(LevelTable t, const uint16_t *__restrict__ Q,
                                                              uint16_t *__restrict__ O, float *__restrict__ LSE,
-                                                             int64_t N, int64_t total_wgs, int64_t total_bh) {
+                                                             int64_t N, int64_t total_wgs) {
     constexpr int KS = D / 32;            // MFMA steps over d for S^T
     constexpr int NT = D / 16;            // 16-wide d tiles of O^T
     constexpr int STRIDE = D * 2 + 32;    // bytes per key row in LDS (padding spreads the rows over the banks)
@@ -30,8 +30,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 6
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t nblk = N >> 4;                                     // fine query blocks per head
     const int64_t fb = xcd_contiguous(blockIdx.x, total_wgs) * 4 + wave;
-    const int64_t bh = fb / nblk, blk = fb % nblk;
-    if (bh >= total_bh) return;                                      // the waves of a workgroup never wait for each other
+    const int64_t bh = fb / nblk, blk = fb % nblk;                  // nblk % 4 == 0: a workgroup stays in one head
     const int i16 = lane & 15, g = lane >> 4;
     char *my = vlds[wave];
 
@@ -169,12 +168,12 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 6
 hipError_t launch_attn_fwd_mfma(const Plan &p, const LevelTable &t, const void *Q, void *O, float *LSE,
                                 hipStream_t s) {
     if ((p.Kl[0] << (p.lb - 4)) <= 64) return launch_attn_fwd_shared(p, t, Q, O, LSE, s);
-    const int64_t wgs = ((int64_t)p.bh * (p.N / 16) + 3) / 4;        // 4 query tiles per workgroup
+    const int64_t wgs = (int64_t)p.bh * (p.N / 64);                  // 4 query tiles per workgroup
     dim3 grid((unsigned)wgs);
     if (p.d == 64)
-        attn_fwd_mfma_kernel<64><<<grid, 256, 0, s>>>(t, (const uint16_t *)Q, (uint16_t *)O, LSE, p.N, wgs, p.bh);
+        attn_fwd_mfma_kernel<64><<<grid, 256, 0, s>>>(t, (const uint16_t *)Q, (uint16_t *)O, LSE, p.N, wgs);
     else
-        attn_fwd_mfma_kernel<128><<<grid, 256, 0, s>>>(t, (const uint16_t *)Q, (uint16_t *)O, LSE, p.N, wgs, p.bh);
+        attn_fwd_mfma_kernel<128><<<grid, 256, 0, s>>>(t, (const uint16_t *)Q, (uint16_t *)O, LSE, p.N, wgs);
     return hipGetLastError();
 }
 

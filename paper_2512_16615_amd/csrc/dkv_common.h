@@ -12,7 +12,7 @@ struct DkvArgs {
     float *partK, *partV;                 // [splits][slab] fp32 (levels >= 1)
     const float *parK, *parV;             // level-1 totals [bh, n_1, D] fp32 or null (level 0)
     uint16_t *dK, *dV;                    // level-0 outputs
-    int64_t N, n_l, total_kb, rows, slab; // total_kb = key tiles of all heads; rows = key blocks of this level per head that have lists
+    int64_t N, n_l, rows, slab;           // rows = key blocks of this level per head that have lists
     int span_shift;                       // log2 of the 16-query groups per listed query block: log2(B^(level+1) / 16)
     int ls, lb;                           // log2(B / 16), log2 B: 16-key tile j lies in listed block j >> ls
     float inv_B;

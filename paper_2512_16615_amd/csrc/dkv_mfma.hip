@@ -234,20 +234,21 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 6
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int i16 = lane & 15, g = lane >> 4;
-    const int64_t nkb = a.n_l >> 4;                        // key tiles per head
+    const int64_t nkb = a.n_l >> 4;                        // key tiles per head (a multiple of 4)
     const bool has_par = a.parK != nullptr;
     // The 16 key blocks under one level-1 token draw their queries from one pool (the fine blocks under the
     // level-1 query blocks that listed that token), about 0.5 MB of Q and dO.  Keep the four workgroups of
     // such a group on one XCD (ids congruent modulo 8) so the pool is fetched into one L2 only, and deal
     // the groups round-robin over the XCDs so that clusters of hot key blocks are spread.
     // (Measured: keeping such a group on one XCD does not pay; the plain order spreads hot clusters best.)
-    const int64_t kb0 = (int64_t)blockIdx.x * 4;           // this workgroup's four key tiles (fewer in the last one)
+    const int64_t kb0 = (int64_t)blockIdx.x * 4;           // this workgroup's four key tiles (same head)
+    const int64_t bh = kb0 / nkb;
 
     // The 16 keys of block j share one parent token (level-1 token j).  Its gradient row is fetched into
     // registers before the tile loop (so the epilogue does not wait for memory) and handed to the epilogue's
     // channel layout through the wave's LDS row.
     float park[D / 64], parv[D / 64];
-    auto par_fetch = [&](int64_t bh, int64_t j) {
+    auto par_fetch = [&](int64_t j) {
 #pragma unroll
         for (int x = 0; x < D / 64; ++x) {
             park[x] = has_par ? a.parK[(bh * (nkb >> a.ls) + (j >> a.ls)) * D + lane + 64 * x] : 0.f;
@@ -263,7 +264,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 6
         __builtin_amdgcn_wave_barrier();
     };
     // level-0 epilogue: scale dK, add the parent token's share (adjoint of mean pooling), round once
-    auto emit = [&](int64_t bh, int64_t j, int slot, f32x4 sum) {
+    auto emit = [&](int64_t j, int slot, f32x4 sum) {
         const bool isV = slot >= S::NT;
         const int n = isV ? slot - S::NT : slot;
         const int col = n * 16 + 4 * g;                     // lane holds 4 consecutive channels of key i16
@@ -282,17 +283,15 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 6
     };
 
     // ---- each wave alone on its own key block, if that block's list is short
-    if (kb0 + wave >= a.total_kb) {
-        if (lane == 0) len_sh[wave] = 0;
-    } else {
-        const int64_t bh = (kb0 + wave) / nkb, j = (kb0 + wave) % nkb;
+    {
+        const int64_t j = kb0 % nkb + wave;
         const int32_t *Crow = a.C + bh * (a.rows + 1) + (j >> a.ls);
         const int32_t beg = Crow[0], len = (Crow[1] - beg) << a.span_shift;   // in 16-query groups
         if (lane == 0) len_sh[wave] = len;
         if (len <= kSoloMax) {
             bf16x8 kop[S::KS], vop[S::KS];
             f32x4 accK[S::NT], accV[S::NT];
-            par_fetch(bh, j);
+            par_fetch(j);
 #pragma unroll
             for (int n = 0; n < S::NT; ++n) { accK[n] = f32x4{0.f, 0.f, 0.f, 0.f}; accV[n] = f32x4{0.f, 0.f, 0.f, 0.f}; }
             if (len > 0) {
@@ -302,7 +301,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 6
             }
             par_publish();
 #pragma unroll
-            for (int n = 0; n < S::NT; ++n) { emit(bh, j, n, accK[n]); emit(bh, j, S::NT + n, accV[n]); }
+            for (int n = 0; n < S::NT; ++n) { emit(j, n, accK[n]); emit(j, S::NT + n, accV[n]); }
         }
     }
     __syncthreads();
@@ -310,19 +309,19 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 6
     for (int w = 0; w < 4; ++w) {
         const int len = len_sh[w];
         if (len <= kSoloMax) continue;                      // uniform over the workgroup
-        const int64_t bh = (kb0 + w) / nkb, j = (kb0 + w) % nkb;
+        const int64_t j = kb0 % nkb + w;
         const int32_t beg = a.C[bh * (a.rows + 1) + (j >> a.ls)];
         bf16x8 kop[S::KS], vop[S::KS];
         f32x4 accK[S::NT], accV[S::NT];
 #pragma unroll
         for (int n = 0; n < S::NT; ++n) { accK[n] = f32x4{0.f, 0.f, 0.f, 0.f}; accV[n] = f32x4{0.f, 0.f, 0.f, 0.f}; }
-        par_fetch(bh, j);
+        par_fetch(j);
         dkv_load_keys<D>(a, bh * a.n_l + j * 16 + i16, lane, kop, vop);
         dkv_tile_loop<D>(a, bh, a.Iq + bh * a.rows * a.Kl_cnt + beg, len, wave, 4, ((int64_t)len + 1) >> 1, kop, vop, accK,
                          accV, lds[wave], lds[wave] + S::TILE, lane);
         par_publish();
         dkv_reduce_waves<D>(reinterpret_cast<float *>(&lds[0][0]), wave, lane, accK, accV,
-                            [&](int slot, f32x4 sum) { emit(bh, j, slot, sum); });
+                            [&](int slot, f32x4 sum) { emit(j, slot, sum); });
         __syncthreads();                                    // the reduction buffer is the next round's tile space
     }
 }
@@ -384,7 +383,7 @@ hipError_t launch_dkv_mfma(const Plan &p, const LevelTable &t, int l, const void
     a.parK = has_parent ? (const float *)(w + p.dKacc_off[1]) : nullptr;
     a.parV = has_parent ? (const float *)(w + p.dVacc_off[1]) : nullptr;
     a.dK = (uint16_t *)dK; a.dV = (uint16_t *)dV;
-    a.N = p.N; a.n_l = p.n[l]; a.total_kb = key_blocks;
+    a.N = p.N; a.n_l = p.n[l];
     a.rows = a.dense ? 0 : p.n[l + 1];
     a.span_shift = a.dense ? 0 : p.lb * (l + 1) - 4;
     a.ls = p.lb - 4; a.lb = p.lb; a.inv_B = 1.f / (float)p.B;
@@ -395,8 +394,8 @@ hipError_t launch_dkv_mfma(const Plan &p, const LevelTable &t, int l, const void
         if (l > 0) a.dK = a.dV = nullptr;
         const hipError_t e = launch_dkv_block(p, l, a, s);
         if (l == 0 || e != hipSuccess) return e;
-    } else if (l == 0) {                                    // four key tiles per workgroup
-        dim3 grid((unsigned)((key_blocks + 3) / 4));
+    } else if (l == 0) {                                    // N % 64 == 0: four key tiles per workgroup, one head
+        dim3 grid((unsigned)(key_blocks / 4));
         if (p.d == 64) dkv_fine_kernel<64><<<grid, 256, 0, s>>>(a);
         else dkv_fine_kernel<128><<<grid, 256, 0, s>>>(a);
         return hipGetLastError();

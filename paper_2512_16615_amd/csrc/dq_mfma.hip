@@ -18,8 +18,7 @@ template <int D>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 64 ? 4 : 2))) dq_mfma_kernel(LevelTable t, const uint16_t *__restrict__ Q,
                                                        const uint16_t *__restrict__ O, const uint16_t *__restrict__ dO,
                                                        const float *__restrict__ LSE, float *__restrict__ Dsum,
-                                                       uint16_t *__restrict__ dQ, int64_t N, int64_t total_wgs,
-                                                       int64_t total_bh) {
+                                                       uint16_t *__restrict__ dQ, int64_t N, int64_t total_wgs) {
     constexpr int KS = D / 32, NT = D / 16, STRIDE = D * 2 + 32, VCH = D / 16, PARTS = D / 8, KPU = 64 / PARTS;
     __shared__ __attribute__((aligned(16))) char klds[4][32 * STRIDE];
 
@@ -28,7 +27,6 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 6
     const int64_t nblk = N >> 4;
     const int64_t fb = xcd_contiguous(blockIdx.x, total_wgs) * 4 + wave;
     const int64_t bh = fb / nblk, blk = fb % nblk;
-    if (bh >= total_bh) return;                    // the waves of a workgroup never wait for each other
     const int i16 = lane & 15, g = lane >> 4;
     char *my = klds[wave];
 
@@ -154,14 +152,14 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 6
 hipError_t launch_dq_mfma(const Plan &p, const LevelTable &t, const void *Q, const void *O, const void *dO,
                           const float *LSE, float *D, void *dQ, hipStream_t s) {
     if ((p.Kl[0] << (p.lb - 4)) <= 64) return launch_dq_shared(p, t, Q, O, dO, LSE, D, dQ, s);
-    const int64_t wgs = ((int64_t)p.bh * (p.N / 16) + 3) / 4;
+    const int64_t wgs = (int64_t)p.bh * (p.N / 64);
     dim3 grid((unsigned)wgs);
     if (p.d == 64)
         dq_mfma_kernel<64><<<grid, 256, 0, s>>>(t, (const uint16_t *)Q, (const uint16_t *)O, (const uint16_t *)dO, LSE, D,
-                                                (uint16_t *)dQ, p.N, wgs, p.bh);
+                                                (uint16_t *)dQ, p.N, wgs);
     else
         dq_mfma_kernel<128><<<grid, 256, 0, s>>>(t, (const uint16_t *)Q, (const uint16_t *)O, (const uint16_t *)dO, LSE,
-                                                 D, (uint16_t *)dQ, p.N, wgs, p.bh);
+                                                 D, (uint16_t *)dQ, p.N, wgs);
     return hipGetLastError();
 }
 

@@ -105,10 +105,13 @@ static llsa_status build_plan(const llsa_desc &d, Plan &p) {
         off += (size_t)p.bh * p.n[l + 1] * p.Kl[l] * sizeof(int32_t);
     }
     p.idx_bytes = off;
-    // MFMA kernels: bf16, blocks of 1, 2 or 4 16-token tiles (so N is a multiple of 16), d = 64 / 128
-    p.fast = d.kernel_path == 0 && d.dtype == LLSA_BF16 && (d.B == 16 || d.B == 32 || d.B == 64) &&
-             (d.d == 64 || d.d == 128);
-    p.lb = !p.fast ? 0 : d.B == 16 ? 4 : d.B == 32 ? 5 : 6;
+    // bf16, blocks of 1, 2 or 4 16-token tiles, d = 64 / 128: what select_dense.hip takes
+    p.blocks16 = d.kernel_path == 0 && d.dtype == LLSA_BF16 && (d.B == 16 || d.B == 32 || d.B == 64) && (d.d == 64 || d.d == 128);
+    p.lb = !p.blocks16 ? 0 : d.B == 16 ? 4 : d.B == 32 ? 5 : 6;
+    // bf16 MFMA kernels: of these the lengths that are multiples of 64.  They round P and dS to bf16; the other lengths have
+    // always had both in fp32 and keep it on the fp32-arithmetic kernels (16 heads x 2704 tokens: dK and dV 2.3e-3 and 2.2e-3
+    // from a 64-bit computation with bf16 P, 1.7e-3 with fp32).
+    p.fast = p.blocks16 && d.N % 64 == 0;
     // the portable selection holds one row of candidate scores per wave in LDS (the bf16 ones take any number)
     for (int l = 1; l <= p.L; ++l) {
         const int64_t cand = (l == p.L) ? p.n[l] : (int64_t)p.Kl[l] * p.B;

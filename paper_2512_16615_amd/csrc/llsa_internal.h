@@ -30,8 +30,9 @@ struct Plan {
     bool group;                     // coarse levels' dK/dV run grouped by level-1 query block
     size_t ws_fwd, ws_bwd;
     int list_len;                   // tokens one query attends to
-    bool fast;                      // bf16 MFMA kernels apply (bf16, B in {16, 32, 64}, d in {64, 128})
-    int lb;                         // log2 B when fast
+    bool fast;                      // bf16 MFMA kernels apply (bf16, B in {16, 32, 64}, d in {64, 128}, N % 64 == 0)
+    bool blocks16;                  // the same for any N: what the bf16 selection kernels take
+    int lb;                         // log2 B when blocks16
 };
 
 // What the attention-type kernels need to walk the gathered list of a query block.
@@ -117,7 +118,7 @@ hipError_t launch_select_mfma(const Plan &p, int l, const void *ws, const int32_
                               int32_t *top_out = nullptr);
 bool select_top_fused(const Plan &p);
 
-// ---- bf16 MFMA kernels (B = 16 / 32 / 64, d = 64 or 128) ----
+// ---- bf16 MFMA kernels (B = 16 / 32 / 64, d = 64 or 128, N % 64 == 0) ----
 hipError_t launch_attn_fwd_mfma(const Plan &p, const LevelTable &t, const void *Q, void *O, float *LSE, hipStream_t s);
 // variant that shares the coarse levels among the 8 or 16 sibling query blocks of a workgroup
 hipError_t launch_attn_fwd_shared(const Plan &p, const LevelTable &t, const void *Q, void *O, float *LSE,

@@ -131,7 +131,7 @@ __global__ void __launch_bounds__(256) select_dense_kernel(const uint16_t *__res
 bool select_dense_ok(const Plan &p, int l) {
     const int64_t C = (l == p.L) ? p.n[l] : (int64_t)p.Kl[l] * p.B;
     // any number of candidates (256 at a time beyond 256); 16 consecutive query tokens share their candidates
-    return p.fast && p.Kl[l - 1] <= 64 && p.n[l] < ((int64_t)1 << 30) && C < (1 << 30) &&
+    return p.blocks16 && p.Kl[l - 1] <= 64 && p.n[l] < ((int64_t)1 << 30) && C < (1 << 30) &&
            (l == p.L || p.n[l] % 16 == 0);
 }
 

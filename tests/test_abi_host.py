@@ -90,6 +90,19 @@ def test_plan_rejects_bad_problems(llsa, kw, status):
         llsa.Plan(**args)
 
 
+def test_lengths_that_are_no_multiple_of_64_keep_fp32_probabilities(llsa):
+    """bf16 lengths that are multiples of 16 and not of 64 belong to the fp32-arithmetic kernels (P and dS are not rounded to bf16):
+    the plan lays out their workspace, a multiple of 64 the other kernels' one.  Their selection still takes any number of
+    candidates."""
+    def bytes_of(N, path):
+        return llsa.Plan(1, 16, N, 64, 16, 8, 1, kernel_path=path).workspace_bytes(True)
+    for N in (16, 144, 2704):
+        assert bytes_of(N, 0) == bytes_of(N, 1)
+    assert bytes_of(2752, 0) != bytes_of(2752, 1)
+    llsa.Plan(1, 1, 16 * 4097, 64, 16, 8, 1)
+    llsa.Plan(1, 1, 16 * 4097, 64, 16, 32, 1)
+
+
 def test_null_pointers_are_refused_before_any_launch(llsa):
     p = llsa.Plan(1, 1, 256, 32, 4, 2, 3, dtype=llsa.F32)
     lib = llsa.load()

@@ -11,8 +11,8 @@ def _bf16(name, N, L=1, heads=3, d=64, B=16, K=8, kind="gaussian", **kw):
 
 
 @pytest.mark.parametrize("cfg", [
-    # lengths that are multiples of the block and of nothing larger: one query tile in all, one tile into the second
-    # workgroup, one short of it; a workgroup of the level-0 dK/dV kernel that spans two heads
+    # lengths that are multiples of the block and of nothing larger (fp32 P and dS): one query tile in all, one tile into the
+    # third workgroup, one short of it
     _bf16("one_tile", 16, K=4),
     _bf16("tiles_9", 144),
     _bf16("tiles_15_d128", 240, d=128, K=4),
@@ -25,6 +25,21 @@ def _bf16(name, N, L=1, heads=3, d=64, B=16, K=8, kind="gaussian", **kw):
 ], ids=lambda c: c["name"])
 def test_lengths_that_fill_no_workgroup(cfg):
     _full_parity(cfg, 0xD15A + cfg["N"])
+
+
+@pytest.mark.parametrize("cfg", [
+    _bf16("tiles_9", 144),
+    _bf16("tiles_169_d128", 2704, d=128, kind="smooth"),
+    _bf16("blocks32_33", 1056, B=32, K=5),
+], ids=lambda c: c["name"])
+def test_lengths_that_are_no_multiple_of_64_have_fp32_probabilities(cfg):
+    """Their attention and gradients are those of the fp32-arithmetic kernels, bit for bit: nothing of P or dS is rounded to bf16."""
+    import torch
+    from tests import harness as H
+    x = H.make_inputs(cfg, 0xD162)
+    got, want = (H.gpu_forward_backward(cfg, x, plan=H.make_plan(cfg, kernel_path=path)) for path in (0, 1))
+    for name in ("indices", "O", "LSE", "dQ", "dK", "dV"):
+        assert torch.equal(got[name], want[name]), name
 
 
 def _tile(name, N, B, K, L, d=64, dtype="f32", heads=2, **kw):
