@@ -1,12 +1,10 @@
 // Attention forward over the gathered lists on bf16 MFMA, variant that shares the coarse levels
-// (B = 16, 32 or 64, d = 64 or 128, at most 64 level-0 tiles of 16 tokens per list).
+// (B = 16, 32 or 64, d = 64 or 128, N a multiple of 256, at most 64 level-0 tiles of 16 tokens per list).
 //
 // 256 consecutive queries (B = 16: the 16 fine query blocks under one level-1 query block) use the same lists at
 // every level >= 1 (Alg. 1, enrichment loop: block i reads row i / B^l of I^(l)), i.e. the same coarse key/value
 // tokens.  One workgroup of 4 or 8 waves owns such a group or half of one; every wave owns one or two of its
-// 16-query tiles.  A length that is no multiple of 128 has one coarse level (N is a multiple of B^L, and B^2 >= 256), which
-// every query of a head uses whole: the last workgroup of a head then holds fewer tiles, and its spare waves work on the
-// head's last tile without storing it.
+// 16-query tiles.
 //   Phase A (levels >= 1): the workgroup stages each tile of two 16-token blocks (K and V rows) once in
 //     LDS, double-buffered; every wave reads the K operand once and multiplies it with both of its query
 //     blocks, likewise the transposed V operand, so the gather traffic of the coarse tokens is paid once
@@ -55,10 +53,9 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int i16 = lane & 15, g = lane >> 4;
-    const int64_t nblk = N >> 4;                                      // query tiles per head
     const unsigned wg = xcd_contiguous32(blockIdx.x, gridDim.x);
     const int64_t bh = groups(wg), blk0 = (wg - (unsigned)bh * groups.d) * (NW * NB);   // groups.d workgroups per head
-    auto tile_of = [&](int b) { return min(blk0 + NB * wave + b, nblk - 1); };
+    auto tile_of = [&](int b) { return blk0 + NB * wave + b; };
     (void)args;                                                       // read through the pointer: fields of a level by scalar loads
     const list_args_ptr t = kernel_list_args();
     const float sc2 = t->scale * kLog2e;
@@ -349,8 +346,7 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D 
     for (int b = 0; b < NB; ++b) {
         const float l = rows_sum(lsum[b]);
         const float inv = 1.f / l;
-        if (blk0 + NB * wave + b >= nblk) break;                      // a spare wave's copy of the head's last tile
-        const int64_t row = bh * N + (blk0 + NB * wave + b) * 16 + i16;
+        const int64_t row = bh * N + tile_of(b) * 16 + i16;
         uint16_t *orow = O + row * D + 4 * g;
 #pragma unroll
         for (int n = 0; n < NT; ++n) {
@@ -365,7 +361,7 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D 
 
 hipError_t launch_attn_fwd_shared(const Plan &p, const LevelTable &t, const void *Q, void *O, float *LSE,
                                   hipStream_t s) {
-    const FastDiv groups((p.N + 127) / 128);
+    const FastDiv groups(p.N / 128);
     const unsigned wgs = (unsigned)p.bh * groups.d;
     const ListArgs a = make_list_args(t);
     const uint16_t *q = (const uint16_t *)Q;
