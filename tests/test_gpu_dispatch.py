@@ -63,6 +63,36 @@ def test_largest_probability_takes_no_rounding(d, B):
     assert float((O != want).float().mean()) < 0.1
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_fp32_arithmetic_takes_exponentials_to_the_last_place(dtype):
+    """Logits of 16 to 64, equal for all 64 keys of a query: a factor of log2(e) rounded at that size costs the logsumexp more than a
+    unit of its last place and P up to 3e-6.  LSE: logf and the sum, below one unit.  dV holds single P's: a unit of expf (2 x 2^-24)
+    and two roundings.  dQ holds the sum of 64 equal ones: partial sum k is rounded at k / 64 of the result, 32.5 x 2^-24 in all, on
+    top of expf and three factors."""
+    import torch
+    from paper_2512_16615_amd import llsa
+    N = d = 64
+    gen = torch.Generator().manual_seed(7)
+    sign = torch.tensor([1.0, -1.0]).repeat(N // 2)
+    Q, K = torch.zeros(2, 1, 3, N, d)
+    Q[..., 0] = 16 + 48 * torch.rand(1, 3, N, generator=gen)
+    K[..., 0], K[..., 1] = 1.0, sign
+    V = sign[:, None].expand(1, 3, N, d)
+    dO = torch.eye(N).expand(1, 3, N, d)
+    t = torch.float32 if dtype == "f32" else torch.bfloat16
+    Q, K, V, dO = (x.to(t).contiguous().cuda() for x in (Q, K, V, dO))
+    plan = llsa.Plan(1, 3, N, d, 16, N // 16, 1, Le=0, sm_scale=1.0, dtype=llsa.F32 if dtype == "f32" else llsa.BF16, kernel_path=1)
+    O, LSE, idx, ws = llsa.forward(plan, Q, K, V, workspace=plan.alloc_workspace(True))
+    dQ, dK, dV = llsa.backward(plan, Q, K, V, O, LSE, idx, dO, ws)
+    z = Q[..., 0].double()
+    want = z + torch.log(torch.tensor(64.0, dtype=torch.float64, device="cuda"))
+    assert float(((LSE.double() - want).abs() / torch.exp2(torch.floor(torch.log2(want)) - 23)).max()) < 1.0
+    P = torch.exp(z - LSE.double())
+    out = 0 if dtype == "f32" else 2.0 ** -8                # bf16: the output's own rounding
+    assert float((dV.double() / P[..., None, :] - 1).abs().max()) < 4 * 2.0 ** -24 + out
+    assert float((dQ[..., 1].double() / (64 * P) - 1).abs().max()) < 38 * 2.0 ** -24 + out
+
+
 def _tile(name, N, B, K, L, d=64, dtype="f32", heads=2, **kw):
     return dict(name=name, batch=1, heads=heads, d=d, N=N, B=B, K=K, L=L, dtype=dtype, kind="gaussian", **kw)
 
