@@ -402,9 +402,11 @@ static llsa_status forward_impl(const llsa_plan_t *plan, const void *Q, const vo
         StageScope sc(kSelect, call, s);
         char *idx = reinterpret_cast<char *>(indices);
         int l = p.L;
-        if (select_top_fused(p)) {                          // levels L and L-1 in one launch
-            LLSA_TRY(launch_select_mfma(p, p.L - 1, workspace, nullptr, reinterpret_cast<int32_t *>(idx + p.idx_off[p.L - 2]), s,
-                                        reinterpret_cast<int32_t *>(idx + p.idx_off[p.L - 1])));
+        const bool mfma_top = select_top_fused(p);
+        if (mfma_top || select_dense_top_ok(p)) {           // levels L and L-1 in one launch
+            auto *launch = mfma_top ? launch_select_mfma : launch_select_dense;
+            LLSA_TRY(launch(p, p.L - 1, workspace, nullptr, reinterpret_cast<int32_t *>(idx + p.idx_off[p.L - 2]), s,
+                            reinterpret_cast<int32_t *>(idx + p.idx_off[p.L - 1])));
             l = p.L - 2;
         }
         for (; l >= 1; --l) {

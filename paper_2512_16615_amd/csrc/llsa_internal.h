@@ -112,8 +112,11 @@ size_t dkv_tile_bytes(const Plan &p);    // workspace of its partial sums
 // ---- selection: K <= 16 (any shape), bf16 with B = 16 / 32 / 64 and K <= 64 ----
 bool select_mfma_ok(const Plan &p, int l);
 bool select_dense_ok(const Plan &p, int l);
-hipError_t launch_select_dense(const Plan &p, int l, const void *ws, const int32_t *parent, int32_t *out, hipStream_t s);
-// top_out != null: l = L - 1 and the launch also does level L, writing I^(L-1) to top_out (allowed if select_top_fused)
+bool select_dense_top_ok(const Plan &p);
+hipError_t launch_select_dense(const Plan &p, int l, const void *ws, const int32_t *parent, int32_t *out, hipStream_t s,
+                               int32_t *top_out = nullptr);
+// top_out != null (here and above): l = L - 1 and the launch also does level L, writing I^(L-1) to top_out (allowed if
+// select_top_fused, or above select_dense_top_ok)
 hipError_t launch_select_mfma(const Plan &p, int l, const void *ws, const int32_t *parent, int32_t *out, hipStream_t s,
                               int32_t *top_out = nullptr);
 bool select_top_fused(const Plan &p);

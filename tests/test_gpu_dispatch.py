@@ -139,6 +139,43 @@ def test_selection_of_tied_scores(cfg):
             assert np.array_equal(gpu["plan"].level_indices(gpu["indices"], l)[b, h].cpu().numpy(), r["I"][l]), f"level {l}"
 
 
+_MANY_PICKS = [
+    # one pass: 18 and 256 candidates, blocks of 32; two passes with one candidate in the second
+    _bf16("K17_of_18", 288, K=17),
+    _bf16("K64_of_256", 4096, K=64),
+    _bf16("K48_of_128_B32_d128", 4096, B=32, K=48, d=128),
+    _bf16("K64_of_257", 4112, K=64),
+    # the coarsest level in the same launch: 16 tokens above 256 candidates, 4 above 64
+    _bf16("K20_top16_d128", 4096, L=2, K=20, d=128),
+    _bf16("K64_top4", 16384, L=3, K=64, heads=1),
+]
+
+
+@pytest.mark.parametrize("cfg", _MANY_PICKS, ids=lambda c: c["name"])
+def test_selection_of_more_than_16(cfg):
+    _full_parity(cfg, 0xD165)
+
+
+@pytest.mark.parametrize("cfg", _MANY_PICKS + [_bf16("K8", 4096, L=2), _tile("f32_K8", 1024, 4, 8, 2)], ids=lambda c: c["name"])
+def test_lists_hold_different_blocks_whatever_the_scores_are(cfg):
+    """NaN and infinite scores: every list is still K_l different blocks of its range, in ascending order (the attention reads
+    what they name)."""
+    import torch
+    from paper_2512_16615_amd import llsa
+    from tests import harness as H
+    plan = H.make_plan(cfg)
+    x = H.make_inputs(cfg, 0xD166)
+    Q, K, V = (H.to_dev(x[n], cfg) for n in ("Q", "K", "V"))
+    N, B = cfg["N"], cfg["B"]
+    K[:, :, :B, 0], K[:, :, 2 * B:3 * B, 1], K[:, :, 5 * B:6 * B, 2] = float("nan"), float("-inf"), float("inf")
+    Q[:, :, B:2 * B], Q[:, :, N // 2:] = float("nan"), float("inf")
+    idx = llsa.forward(plan, Q, K, V)[2]
+    for l in range(cfg["L"]):
+        lists = plan.level_indices(idx, l).cpu()
+        assert int(lists.min()) >= 0 and int(lists.max()) < N // B ** (l + 1)
+        assert bool((lists.diff(dim=-1) > 0).all())
+
+
 @pytest.mark.parametrize("T,K,heads", [(1, 1, 2), (33, 3, 3), (64, 8, 2), (65, 5, 2), (512, 8, 2), (513, 3, 2), (1025, 8, 2),
                                          (2048, 64, 1), (4099, 7, 2), (16384, 8, 1), (16385, 2, 1)])
 def test_index_transpose_by_size(T, K, heads):
