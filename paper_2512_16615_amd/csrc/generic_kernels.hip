@@ -838,7 +838,8 @@ __global__ void __launch_bounds__(256) mask_mark_kernel(const int32_t *I, uint8_
     mask[(bh * T + key) * T + row] = 1;
     atomicAdd(&cnt[bh * T + key], 1);
 }
-// one wave per key block: scans its T mask bytes, 1024 at a time, and appends the marked query blocks to its list
+// one wave per key block: scans its T mask bytes, 1024 at a time, and appends the marked query blocks to its list.  A row begins at
+// a multiple of T bytes: it is read in vectors of 16 or 4 bytes only if T is a multiple of that.
 __global__ void __launch_bounds__(256) mask_scan_kernel(const uint8_t *mask, const int32_t *C, int32_t *Iq, int64_t T,
                                                         int64_t eph, int64_t nk) {
     const int lane = threadIdx.x & 63;
@@ -850,10 +851,21 @@ __global__ void __launch_bounds__(256) mask_scan_kernel(const uint8_t *mask, con
     int written = 0;
     for (int64_t base = 0; base < T; base += 1024) {
         const int64_t i0 = base + 16 * lane;
-        uint4 v = make_uint4(0u, 0u, 0u, 0u);
-        if (i0 + 16 <= T) v = *reinterpret_cast<const uint4 *>(row + i0);
-        else for (int k = 0; k < 16 && i0 + k < T; ++k) reinterpret_cast<uint8_t *>(&v)[k] = row[i0 + k];
-        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+        uint32_t w[4] = {0u, 0u, 0u, 0u};
+        if (T % 16 == 0) {
+            if (i0 < T) {
+                const uint4 v = *reinterpret_cast<const uint4 *>(row + i0);
+                w[0] = v.x; w[1] = v.y; w[2] = v.z; w[3] = v.w;
+            }
+        } else if (T % 4 == 0) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                if (i0 + 4 * k < T) w[k] = *reinterpret_cast<const uint32_t *>(row + i0 + 4 * k);
+        } else {
+#pragma unroll
+            for (int k = 0; k < 16; ++k)
+                if (i0 + k < T) w[k >> 2] |= (uint32_t)row[i0 + k] << (8 * (k & 3));
+        }
         int mine = 0;
 #pragma unroll
         for (int k = 0; k < 4; ++k) mine += __popc(w[k] & 0x01010101u);

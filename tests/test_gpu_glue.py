@@ -75,6 +75,9 @@ def test_qknorm_rope_pool_matches_oracle(cfg):
     dict(name="kv0_n4096", batch=1, heads=2, d=64, N=4096, B=16, K=8, L=2, dtype="bf16", kind="smooth"),
     dict(name="kv0_n16384_d128", batch=1, heads=1, d=128, N=16384, B=16, K=4, L=3, dtype="bf16", kind="gaussian"),
     dict(name="kv0_b32_odd_T", batch=1, heads=1, d=64, N=3072, B=32, K=4, L=1, dtype="bf16", kind="gaussian"),
+    # rows of the mask that begin at no multiple of 16 bytes (T = 172) and of no 4 (T = 17)
+    dict(name="kv0_T172", batch=1, heads=2, d=64, N=2752, B=16, K=4, L=1, dtype="bf16", kind="gaussian"),
+    dict(name="kv0_T17", batch=1, heads=2, d=64, N=1088, B=64, K=4, L=1, dtype="bf16", kind="gaussian"),
 ], ids=lambda c: c["name"])
 def test_kv_backward_level0_csc_and_mask_agree_with_the_oracle(cfg):
     x = H.make_inputs(cfg, 0x115A3100)
