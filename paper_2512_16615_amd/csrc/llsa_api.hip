@@ -169,9 +169,9 @@ static llsa_status build_plan(const llsa_desc &d, Plan &p) {
 }
 
 // ---- optional stage timing (benchmark aid) ----
-enum Stage { kPool = 0, kSelect, kAttnFwd, kBwdPre, kTranspose, kDq, kDkvCoarse, kUnpool, kDkvFine, kStages };
+enum Stage { kPool = 0, kSelect, kAttnFwd, kBwdPre, kTranspose, kDq, kDkvCoarse, kUnpool, kDkvFine, kDkvAll, kStages };
 static const char *const kStageNames[kStages] = {"pool", "select", "attn_fwd", "bwd_pre", "index_transpose",
-                                                 "dq", "dkv_coarse", "unpool", "dkv_fine"};
+                                                 "dq", "dkv_coarse", "unpool", "dkv_fine", "dkv_all"};
 struct StageTimer {
     bool on = false;
     int filter = -1, max_calls = 0, fwd_calls = 0, bwd_calls = 0;
@@ -494,8 +494,14 @@ llsa_status llsa_backward(const llsa_plan_t *plan, const void *Q, const void *K,
             joined = true;
         }
         if (!p.fast) {                                      // every level at once
-            StageScope sc(kDkvFine, call, s);
-            LLSA_TRY(launch_dkv_tile(p, t, Q, dO, LSE, D, workspace, dK, dV, s));
+            {
+                StageScope sc(kDkvAll, call, s);
+                LLSA_TRY(launch_dkv_tile(p, t, Q, dO, LSE, D, workspace, dK, dV, s));
+            }
+            if (dkv_tile_folds(p)) {
+                StageScope sc(kUnpool, call, s);
+                LLSA_TRY(launch_dkv_tile_fold(p, t, workspace, dK, dV, s));
+            }
             return LLSA_OK;
         }
         // coarse levels first (fp32), fold them down level by level, then level 0 adds its parent's share

@@ -107,6 +107,8 @@ hipError_t launch_dq_tile(const Plan &p, const LevelTable &t, const void *Q, con
                           float *D, void *dQ, hipStream_t s);
 hipError_t launch_dkv_tile(const Plan &p, const LevelTable &t, const void *Q, const void *dO, const float *LSE, const float *D,
                            void *ws, void *dK, void *dV, hipStream_t s);
+bool dkv_tile_folds(const Plan &p);      // is there anything to fold behind it?
+hipError_t launch_dkv_tile_fold(const Plan &p, const LevelTable &t, void *ws, void *dK, void *dV, hipStream_t s);
 size_t dkv_tile_bytes(const Plan &p);    // workspace of its partial sums
 
 // ---- selection: K <= 16 (any shape), bf16 with B = 16 / 32 / 64 and K <= 64 ----

@@ -507,12 +507,10 @@ size_t dkv_tile_bytes(const Plan &p) {
     return b;
 }
 
-hipError_t launch_dkv_tile(const Plan &p, const LevelTable &t, const void *Q, const void *dO, const float *LSE, const float *D,
-                           void *ws, void *dK, void *dV, hipStream_t s) {
+// the arguments of both launches; returns the workgroups of the first
+static int64_t dkv_tile_args(const Plan &p, const LevelTable &t, void *ws, void *dK, void *dV, DkvTileArgs &a, DkvFoldArgs &f) {
     char *w = static_cast<char *>(ws);
     float *part = reinterpret_cast<float *>(w + p.part_off);
-    DkvTileArgs a;
-    DkvFoldArgs f;
     a.B = f.B = p.B;
     a.N = p.N;
     a.scale = p.scale;
@@ -544,12 +542,30 @@ hipError_t launch_dkv_tile(const Plan &p, const LevelTable &t, const void *Q, co
         f.partK[l] = L.partK; f.partV[l] = L.partV;
         f.n[l] = L.n; f.slab[l] = L.slab; f.splits[l] = L.splits;
     }
+    return wg;
+}
+
+hipError_t launch_dkv_tile(const Plan &p, const LevelTable &t, const void *Q, const void *dO, const float *LSE, const float *D,
+                           void *ws, void *dK, void *dV, hipStream_t s) {
+    DkvTileArgs a;
+    DkvFoldArgs f;
+    const int64_t wg = dkv_tile_args(p, t, ws, dK, dV, a, f);
     if (wg >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
-    const bool fold = p.Le >= 1 || p.elt != 4;              // fp32 without coarse levels: the sums are the result
     return by_shape(p, [&](auto ty, auto d) {
         using T = decltype(ty);
         tile_dkv_kernel<T, d.value><<<(unsigned)wg, 256, 0, s>>>(a, (const T *)Q, (const T *)dO, LSE, D);
-        if (fold) tile_dkv_fold_kernel<T, d.value><<<(unsigned)(p.bh * p.n[1]), 256, 0, s>>>(f, (T *)dK, (T *)dV);
+    });
+}
+
+bool dkv_tile_folds(const Plan &p) { return p.Le >= 1 || p.elt != 4; }   // fp32 without coarse levels: the sums are the result
+
+hipError_t launch_dkv_tile_fold(const Plan &p, const LevelTable &t, void *ws, void *dK, void *dV, hipStream_t s) {
+    DkvTileArgs a;
+    DkvFoldArgs f;
+    dkv_tile_args(p, t, ws, dK, dV, a, f);
+    return by_shape(p, [&](auto ty, auto d) {
+        using T = decltype(ty);
+        tile_dkv_fold_kernel<T, d.value><<<(unsigned)(p.bh * p.n[1]), 256, 0, s>>>(f, (T *)dK, (T *)dV);
     });
 }
 

@@ -6,7 +6,7 @@ configurations: longer sequences at the d = 64 head geometry, the paper's own ch
 import pytest
 
 from tests import harness as H
-from paper_2512_16615_amd import inputs
+from paper_2512_16615_amd import inputs, llsa
 
 pytestmark = pytest.mark.gpu
 
@@ -172,3 +172,20 @@ def test_level1_partials_carried_across_query_blocks():
     # all copies of a head get bit-identical gradients (different workgroups, same arithmetic)
     for t_ in (dK, dV):
         assert torch.equal(t_[0, 0], t_[3, 14]) and torch.equal(t_[0, 1], t_[2, 7])
+
+
+@pytest.mark.parametrize("cfg,runs", [
+    (dict(name="stages_f32", batch=1, heads=1, d=32, N=256, B=4, K=2, L=3, dtype="f32", kind="gaussian"), {"dkv_all", "unpool"}),
+    (dict(name="stages_f32_Le0", batch=1, heads=1, d=32, N=256, B=4, K=2, L=3, Le=0, dtype="f32", kind="gaussian"), {"dkv_all"}),
+    (dict(name="stages_ragged", batch=1, heads=1, d=64, N=2704, B=16, K=8, L=1, dtype="bf16", kind="gaussian"), {"dkv_all", "unpool"}),
+    (dict(name="stages_bf16", batch=1, heads=1, d=64, N=4096, B=16, K=8, L=2, dtype="bf16", kind="gaussian"), {"dkv_coarse", "dkv_fine"}),
+], ids=lambda c: c["name"] if isinstance(c, dict) else "")
+def test_stages_that_are_bracketed(cfg, runs):
+    """The stage timer's contract: a launch that holds every level's dK / dV is not passed off as level 0's."""
+    x = H.make_inputs(cfg, 0xD167)
+    llsa.stage_timing_begin(-1, max_calls=1)
+    try:
+        H.gpu_forward_backward(cfg, x)
+    finally:
+        st = llsa.stage_timing_end()
+    assert {k for k, (ms, n) in st.items() if n} == {"pool", "select", "attn_fwd", "index_transpose", "dq"} | runs
