@@ -265,3 +265,25 @@ def test_query_tiles_per_wave(cfg):
 ], ids=lambda c: c["name"])
 def test_level1_sums_carried_along_query_blocks(cfg):
     _full_parity(cfg, 0xD161)
+
+
+@pytest.mark.parametrize("heads,K,d", [(64, 3, 64), (64, 6, 64), (32, 8, 64), (64, 6, 128), (64, 8, 128)])
+def test_level1_sums_carried_through_several_query_blocks(heads, K, d):
+    """Chains of 8 (heads x level-1 query blocks >= 4096) or 4 query blocks on smooth inputs, whose blocks stay listed: slots are kept,
+    released and taken again several times.  Two heads' inputs, repeated, so that the oracle has two to do."""
+    import torch
+    from paper_2512_16615_amd import llsa
+    from tests import harness as H
+    two = _bf16(f"chain_K{K}_d{d}", 16384, L=2, heads=2, K=K, d=d, kind="smooth")
+    x = H.make_inputs(two, 0xD168)
+    Q, Kt, V, dO = (H.to_dev(x[n], two).repeat(1, heads // 2, 1, 1) for n in ("Q", "K", "V", "dO"))
+    plan = H.make_plan(dict(two, heads=heads))
+    O, LSE, idx, ws = llsa.forward(plan, Q, Kt, V, workspace=plan.alloc_workspace(True))
+    got = dict(zip(("dQ", "dK", "dV"), llsa.backward(plan, Q, Kt, V, O, LSE, idx, dO, ws)))
+    tol = H.TOL["bf16"]
+    for (b, h), r in H.oracle_all_heads(two, x).items():
+        for l in range(2):
+            assert (plan.level_indices(idx, l)[b, h].cpu().numpy() == r["I"][l]).all(), f"level {l}"
+        for n, t in got.items():
+            H.check_close(f"{n}{(b, h)}", H.f32(t[b, h]), r[n], tol["out"], tol["ulp"])
+            assert torch.equal(t[:, h::2], t[:, h:h + 1].expand_as(t[:, h::2])), n
