@@ -26,12 +26,6 @@ __device__ __forceinline__ u32x4 gload16(const char *base, unsigned off) {
 }
 constexpr float kMaxSum = 4096.f;   // a query's softmax reference is raised only when a tile's probabilities exceed this
 
-__device__ __forceinline__ bf16x8 as_bf16x8(u32x4 v) {
-    union { u32x4 u; bf16x8 b; } c;
-    c.u = v;
-    return c.b;
-}
-
 // NB = fine query tiles per wave (1 or 2), NW = waves per workgroup (4 or 8); a workgroup owns NW * NB consecutive
 // tiles, all siblings.  GW = waves whose tiles make up a block of 32 or 64 queries and share a level-0 list (0: B = 16)
 template <int D, int NB, int NW, int GW>

@@ -14,7 +14,6 @@ struct DkvArgs {
     uint16_t *dK, *dV;                    // level-0 outputs
     int64_t N, n_l, rows, slab;           // rows = key blocks of this level per head that have lists
     int span_shift;                       // log2 of the 16-query groups per listed query block: log2(B^(level+1) / 16)
-    int ls, lb;                           // log2(B / 16), log2 B: 16-key tile j lies in listed block j >> ls
     float inv_B;
     int Kl_cnt, dense, splits;
     float sc2, bias2, scale;

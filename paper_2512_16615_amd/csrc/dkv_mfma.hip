@@ -1,9 +1,9 @@
-// dK, dV of the gathered-list attention on bf16 MFMA (B = 16, 32 or 64, d = 64 or 128), Sec. 4.3: key-major over
-// the transposed lists of Alg. 2 (or over every query at the coarsest enriched level), with no mask and
-// no floating-point atomics.
+// dK, dV of the gathered-list attention on bf16 MFMA (d = 64 or 128), Sec. 4.3: key-major over the transposed lists of Alg. 2
+// where blocks have 16 keys, or over every query at a dense level of at most 32 tokens (any block size; dkv_block.hip has the
+// lists of larger blocks and the wider dense levels), with no mask and no floating-point atomics.
 // With P = exp(z - LSE), dP = dO V^T, dS = P o (dP - D):  dK = scale dS^T Q,  dV = P^T dO.
 //
-// The unit of work is a tile of 16 level-l keys (a listed block of B keys is B / 16 tiles with one list).  The
+// The unit of work is a tile of 16 level-l keys, a listed block or a piece of a dense level.  The
 // queries that attend to it are the fine queries under the level-l query blocks listed for its block, walked in
 // groups of 16 consecutive queries; a tile of the loop is two groups.  Per tile a wave
 // computes
@@ -196,7 +196,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 6
     if (a.dense) {
         groups = a.N >> 4;
     } else {
-        const int32_t *Crow = a.C + bh * (a.rows + 1) + (j >> a.ls);
+        const int32_t *Crow = a.C + bh * (a.rows + 1) + j;
         const int32_t beg = Crow[0], end = Crow[1];
         lst = a.Iq + bh * a.rows * a.Kl_cnt + beg;
         groups = (int64_t)(end - beg) << a.span_shift;
@@ -237,10 +237,9 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 6
     const int64_t nkb = a.n_l >> 4;                        // key tiles per head (a multiple of 4)
     const bool has_par = a.parK != nullptr;
     // The 16 key blocks under one level-1 token draw their queries from one pool (the fine blocks under the
-    // level-1 query blocks that listed that token), about 0.5 MB of Q and dO.  Keep the four workgroups of
-    // such a group on one XCD (ids congruent modulo 8) so the pool is fetched into one L2 only, and deal
-    // the groups round-robin over the XCDs so that clusters of hot key blocks are spread.
-    // (Measured: keeping such a group on one XCD does not pay; the plain order spreads hot clusters best.)
+    // level-1 query blocks that listed that token), about 0.5 MB of Q and dO.  Keeping their four workgroups on one
+    // XCD, so that its L2 alone fetches the pool, was measured and does not pay: the plain order spreads clusters of
+    // hot key blocks best.
     const int64_t kb0 = (int64_t)blockIdx.x * 4;           // this workgroup's four key tiles (same head)
     const int64_t bh = kb0 / nkb;
 
@@ -251,8 +250,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 6
     auto par_fetch = [&](int64_t j) {
 #pragma unroll
         for (int x = 0; x < D / 64; ++x) {
-            park[x] = has_par ? a.parK[(bh * (nkb >> a.ls) + (j >> a.ls)) * D + lane + 64 * x] : 0.f;
-            parv[x] = has_par ? a.parV[(bh * (nkb >> a.ls) + (j >> a.ls)) * D + lane + 64 * x] : 0.f;
+            park[x] = has_par ? a.parK[(bh * nkb + j) * D + lane + 64 * x] : 0.f;
+            parv[x] = has_par ? a.parV[(bh * nkb + j) * D + lane + 64 * x] : 0.f;
         }
     };
     auto par_publish = [&]() {                              // the wave's own row; its LDS operations stay in order
@@ -285,8 +284,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 6
     // ---- each wave alone on its own key block, if that block's list is short
     {
         const int64_t j = kb0 % nkb + wave;
-        const int32_t *Crow = a.C + bh * (a.rows + 1) + (j >> a.ls);
-        const int32_t beg = Crow[0], len = (Crow[1] - beg) << a.span_shift;   // in 16-query groups
+        const int32_t *Crow = a.C + bh * (a.rows + 1) + j;
+        const int32_t beg = Crow[0], len = Crow[1] - beg;   // in 16-query groups
         if (lane == 0) len_sh[wave] = len;
         if (len <= kSoloMax) {
             bf16x8 kop[S::KS], vop[S::KS];
@@ -310,7 +309,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 6
         const int len = len_sh[w];
         if (len <= kSoloMax) continue;                      // uniform over the workgroup
         const int64_t j = kb0 % nkb + w;
-        const int32_t beg = a.C[bh * (a.rows + 1) + (j >> a.ls)];
+        const int32_t beg = a.C[bh * (a.rows + 1) + j];
         bf16x8 kop[S::KS], vop[S::KS];
         f32x4 accK[S::NT], accV[S::NT];
 #pragma unroll
@@ -386,7 +385,7 @@ hipError_t launch_dkv_mfma(const Plan &p, const LevelTable &t, int l, const void
     a.N = p.N; a.n_l = p.n[l];
     a.rows = a.dense ? 0 : p.n[l + 1];
     a.span_shift = a.dense ? 0 : p.lb * (l + 1) - 4;
-    a.ls = p.lb - 4; a.lb = p.lb; a.inv_B = 1.f / (float)p.B;
+    a.inv_B = 1.f / (float)p.B;
     a.Kl_cnt = a.dense ? 0 : p.Kl[l];
     a.sc2 = p.scale * kLog2e; a.bias2 = t.bias[l] * kLog2e; a.scale = p.scale;
     const bool block = dkv_block_tiles(p, l) > 0;

@@ -375,13 +375,12 @@ struct CscLevel {
 struct CscLevels { CscLevel lv[kMaxL]; };
 
 // Few rows (csc_one_launch), one launch, no scratch memory: a workgroup makes the
-// lists of kRangeKeys consecutive keys of one head.  It reads all of the head's entries (from L2: 32 KB .. 256 KB), marks the
+// lists of kRangeKeys consecutive keys of one head.  It reads all of the head's entries (from L2: 16 KB at 512 rows of 8), marks the
 // rows that list one of its keys in a bitmap of a row per key in LDS and counts the entries of the keys below its own (their
 // number is where its lists start); then every group of lanes turns a key's bitmap into its ascending list.  Marking has no
 // order, so neither a fill in order nor a sort is needed.  Against count, scan, fill and sort in launches of their own this
-// saves four launches, which is most of the time up to 1024 rows, and the sort's passes over the lists beyond.  Reading grows
-// with rows^2, hence the limit; 32 keys keep the bitmap at 16 KB for 4096 rows, so that a workgroup finds room beside the
-// LDS-bound dK/dV kernels it runs in the shadow of.
+// saves four launches, which is most of the time at these sizes.  Reading grows with rows^2, hence the limit; the bitmap of 32
+// keys is 2 KB at 512 rows.
 // grid.x: ranges of level 0's heads, then level 1's, ... (also in the kernels of the segment path)
 constexpr int kRangeKeys = 32;
 struct CscRanges { CscLevel lv[kMaxL]; unsigned wg_end[kMaxL]; };
@@ -475,6 +474,9 @@ __global__ void __launch_bounds__(256) csc_bitmap_kernel(CscRanges a) {
 //     counts of the group's earlier segments (one 16-byte load, summed bytewise), plus the marked rows below its own.
 // Nothing is sorted and every place follows from counts, so the lists are ascending and the same on every run.  The kernels
 // stay below 48 registers: that is what the upper-level dK/dV kernel, in whose shadow they run, leaves of a SIMD's 512.
+// Each range of 1024 keys reads its rows again, so the time grows with rows^2 for few heads; the sort's grows with the lists,
+// which smooth inputs make long.  Either side of the limit, sort against segments, smooth and Gaussian inputs, K = 8: one head of
+// 17408 rows 114 : 89 and 50 : 90 us, two of 32768 rows 224 : 247 and 90 : 250, one of 65536 rows 336 : 834 and 127 : 841.
 constexpr int kSegRowsMax = 16384, kSegR = 128, kSegPerGroup = 16, kGroupRows = kSegR * kSegPerGroup, kKeyRange = 1024;
 // every entry of rows row0 .. row1 - 1 with key - k0 < kKeyRange: f(row, key - k0)
 template <class F> __device__ __forceinline__ void range_entries(const int32_t *I, unsigned Kl, unsigned row0, unsigned row1, unsigned k0, F f) {

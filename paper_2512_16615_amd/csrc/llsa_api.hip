@@ -19,7 +19,6 @@ LevelTable make_level_table(const Plan &p, const void *K0, const void *V0, const
     memset(&t, 0, sizeof(t));
     const char *w = static_cast<const char *>(workspace);
     const char *idx = reinterpret_cast<const char *>(indices);
-    int64_t bp = 1;
     int pos = 0, bpos = 0;
     for (int l = 0; l <= p.L; ++l) {
         t.K[l] = (l == 0) ? K0 : (const void *)(w + p.pyr_off[1][l]);
@@ -28,7 +27,6 @@ LevelTable make_level_table(const Plan &p, const void *K0, const void *V0, const
         t.n[l] = p.n[l];
         t.rows[l] = (l < p.L) ? p.n[l + 1] : 0;
         t.Kl[l] = (l < p.L) ? p.Kl[l] : 0;
-        t.Bpow[l] = bp;
         t.bias[l] = p.desc.reweight ? (float)(l * log((double)p.B)) : 0.f;
         if (l <= p.Le) {
             t.seg[l] = pos;
@@ -36,9 +34,7 @@ LevelTable make_level_table(const Plan &p, const void *K0, const void *V0, const
             t.bseg[l] = bpos;
             bpos += (l < p.L) ? p.Kl[l] * ((p.B + 15) / 16) : (int)((p.n[l] + 15) / 16);
         }
-        bp *= p.B;
     }
-    t.Bpow[p.L + 1] = bp;
     t.nlev = p.Le + 1;
     t.seg[t.nlev] = pos;
     t.bseg[t.nlev] = bpos;

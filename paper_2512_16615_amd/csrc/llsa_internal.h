@@ -42,7 +42,6 @@ struct LevelTable {
     const int32_t *I[kMaxL + 1];    // I^(l) [bh, rows_l, K_l]; unused for l = L
     int64_t n[kMaxL + 1];
     int64_t rows[kMaxL + 1];
-    int64_t Bpow[kMaxL + 2];        // B^l
     int Kl[kMaxL + 1];
     int seg[kMaxL + 2];             // list position where level l starts; seg[nlev] = list length
     int bseg[kMaxL + 2];            // same in units of 16-token key blocks (used when B = 16)

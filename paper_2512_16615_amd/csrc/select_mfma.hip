@@ -7,8 +7,8 @@
 // wide-range and denormal inputs).  Lane (b, i) supplies channel c of query i (A) and of candidate 16 b + i of the chunk (B),
 // and lane (g, i) receives the scores of queries 4g .. 4g+3 against candidates 16 b + i.
 //
-// A score and its position become one number of type double, larger = better: the score's bits made monotonic (40 of the
-// mantissa's bits together with the position, complemented so that the lower position wins a tie) under a constant exponent.
+// A score and its position become one number of type double, larger = better: the score's 32 bits made monotonic, then 20
+// bits of position, complemented so that the lower position wins a tie: the 52 bits of the mantissa, under a constant exponent.
 // v_max_f64 / v_min_f64 then compare and exchange in one instruction each.  Every lane keeps the sorted K best (KL = 8 or 16) of
 // its own candidates per query; at the end the 16 lanes of a query merge theirs pairwise (maximum of one list and the reversed
 // other one, then a bitonic clean-up), and so do the waves of the workgroup.

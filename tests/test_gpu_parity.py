@@ -120,7 +120,7 @@ def test_edge_shapes(cfg):
 
 
 def test_portable_kernels_on_a_fast_path_shape():
-    """desc.kernel_path = 1 forces the scalar kernels on a shape the MFMA kernels would take: same bars."""
+    """desc.kernel_path = 1 forces the fp32-arithmetic kernels on a shape the MFMA kernels would take: same bars."""
     cfg = dict(name="portable", batch=1, heads=2, d=64, N=4096, B=16, K=8, L=2, dtype="bf16", kind="smooth")
     _full_parity(cfg, 0x5EED77, plan_kw=dict(kernel_path=1))
     cfg = dict(name="portable_B64", batch=1, heads=1, d=64, N=4096, B=64, K=2, L=1, dtype="bf16", kind="gaussian")
