@@ -101,9 +101,18 @@ template <int D, class Emit> __device__ __forceinline__ void col_emit(const f32x
         }
 }
 
-// Logits, maxima and logsumexps are in natural units, and P comes from expf: scale and weight folded into base-2 units for the
-// bare hardware exponential (each factor rounded on its own, at the size of the whole exponent) put dQ 1.05 to 1.35 times and
-// the logsumexp 1.05 to 1.4 times as far from a 64-bit computation.
+// Logits, maxima and logsumexps are in natural units: scale and weight folded into base-2 units for the bare hardware
+// exponential (each factor rounded on its own, at the size of the whole exponent) put dQ 1.05 to 1.35 times and the logsumexp
+// 1.05 to 1.4 times as far from a 64-bit computation.
+
+// exp(x) to about a unit: x log2(e) in two parts, the hardware's 2^t of the rounded one, the rest to first order.  (Below -104
+// the result is 0; a NaN stays one.)  Forward with it and with expf: one head of 256 tokens 8.8 : 9.2 us, 16 x 4096 62.9 : 65.5.
+__device__ __forceinline__ float exp_nat(float x) {
+    constexpr float kHi = 1.44269504f, kLo = (float)(1.4426950408889634 - (double)kHi);
+    x = x < -104.f ? -104.f : x;
+    const float t = x * kHi, rest = fmaf(x, kLo, fmaf(x, kHi, -t)), p = __builtin_amdgcn_exp2f(t);
+    return fmaf(p, rest * kLn2, p);
+}
 
 // 64 positions of a query block's gathered list (Alg. 1, enrichment loop): addresses of the tokens' key and value rows, log of
 // the weight (-inf past the end of the list, whose rows repeat the last one).
@@ -193,7 +202,7 @@ __global__ void __launch_bounds__(256) tile_fwd_kernel(LevelTable t, const T *__
             }
             mx = rows_max(mx);
             if (__builtin_amdgcn_ballot_w64(mx > m) != 0) {
-                const float m_new = fmaxf(m, mx), alpha = expf(m - m_new);
+                const float m_new = fmaxf(m, mx), alpha = exp_nat(m - m_new);
                 lsum *= alpha;
 #pragma unroll
                 for (int n = 0; n < S::NT; ++n)
@@ -202,23 +211,28 @@ __global__ void __launch_bounds__(256) tile_fwd_kernel(LevelTable t, const T *__
                 m = m_new;
             }
 #pragma unroll
-            for (int r = 0; r < 4; ++r) s[r] = expf(s[r] - m);
+            for (int r = 0; r < 4; ++r) s[r] = exp_nat(s[r] - m);
             lsum += (s[0] + s[1]) + (s[2] + s[3]);
             col_product<D>(acc, v, s);
         }
     }
     lsum = rows_sum(lsum);
     if (i16 >= qt.nq) return;
+    const float inv = 1.f / lsum;
     col_emit<D>(acc, g, [&](int ch, FVec<S::E> x) {
 #pragma unroll
-        for (int e = 0; e < S::E; ++e) x.v[e] /= lsum;
+        for (int e = 0; e < S::E; ++e) {                    // x / lsum: the product and one correction (not of an infinity)
+            const float q = x.v[e] * inv, c = fmaf(fmaf(-q, lsum, x.v[e]), inv, q);
+            x.v[e] = c == c ? c : q;
+        }
         st_e<S::E>(O + row * D + ch, x);
     });
-    if (g == 0) LSE[row] = m + logf(lsum);
+    if (g == 0) LSE[row] = fmaf(__builtin_amdgcn_logf(lsum), kLn2, m);
 }
 
 // ----------------------------------------------------------------------------------------------------- dQ
-// Same walk; P from the saved logsumexp.  Also produces D = rowsum(dO o O) of its queries for the key-major kernel.
+// Same walk; P from the saved logsumexp.  Also produces D = rowsum(dO o O) of its queries for the key-major kernel.  (expf at
+// d = 128: as exact, and around exp_nat the compiler schedules that loop worse, 2 heads x 4096 tokens 104 against 137 us.)
 template <class T, int D>
 __global__ void __launch_bounds__(256) tile_dq_kernel(LevelTable t, const T *__restrict__ Q, const T *__restrict__ O,
                                                        const T *__restrict__ dO, const float *__restrict__ LSE, float *__restrict__ Dsum,
@@ -260,8 +274,10 @@ __global__ void __launch_bounds__(256) tile_dq_kernel(LevelTable t, const T *__r
             f32x4 s = row_product<D>(k, q);
             const f32x4 dp = row_product<D>(v, go);
 #pragma unroll
-            for (int r = 0; r < 4; ++r)                     // past the end of the list: weight -inf, P = 0
-                s[r] = expf(fmaf(s[r], t.scale, tab.bias[c + 4 * g + r]) - lse) * (dp[r] - delta);
+            for (int r = 0; r < 4; ++r) {                   // past the end of the list: weight -inf, P = 0
+                const float x = fmaf(s[r], t.scale, tab.bias[c + 4 * g + r]) - lse;
+                s[r] = (D == 128 ? expf(x) : exp_nat(x)) * (dp[r] - delta);
+            }
             col_product<D>(acc, kc, s);
         }
     }
@@ -363,7 +379,7 @@ __global__ void __launch_bounds__(256) tile_dkv_kernel(DkvTileArgs a, const T *_
             f32x4 s = row_product<D>(qo, k), dp = row_product<D>(go, v);
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                s[r] = expf(fmaf(s[r], a.scale, L.bias) - lse[r]);
+                s[r] = exp_nat(fmaf(s[r], a.scale, L.bias) - lse[r]);
                 dp[r] = s[r] * (dp[r] - dl[r]);
             }
             col_product<D>(accV, gc, s);
