@@ -7,9 +7,10 @@
 // turn and are added up through LDS in order.  Two tiles per group are in flight in registers.  A block of level 0 is finished here (the parent token's share added, one
 // rounding); levels >= 1 write fp32 sums, one slab per share of the list, for dkv_reduce_kernel.
 // Bound: LDS reads (16 KB per 32 x 16 score tile at TPW = 1, half of that at 2) and the latency of the gathered rows; 16 heads
-// x 65536 tokens in blocks of 64, K = 8: level 1 363 us (TPW = 1: 407), level 0 483 us (TPW = 2: 538), 224 us each at the rate of
-// a large matrix product; with one tile in flight 487 and 594.  (Blocks of 32 at d = 64: two tiles a wave would be a wave alone with 255 registers and spills.)  The kernels of
-// dkv_mfma.hip, which these replace here, staged every query tile once per key tile: 555 and 743 us.
+// x 65536 tokens in blocks of 64, K = 8: level 1 340 us, level 0 423 us (profiled; 224 us each at the rate of a large matrix product).  Relative to that, when written:
+// level 1 with TPW = 1 1.12 times as long, level 0 with TPW = 2 1.11 times; with one tile in flight 1.34 and 1.23; the kernels
+// of dkv_mfma.hip, which these replace here and which staged every query tile once per key tile, 1.53 and 1.54.  (Blocks of 32 at
+// d = 64: two tiles a wave would be a wave alone with 255 registers and spills.)
 #include <type_traits>
 
 #include "dkv_common.h"
