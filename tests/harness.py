@@ -8,7 +8,7 @@ Tolerances (written here once, used by every parity test):
   * O, dQ, dK, dV: plain max-abs error <= 2e-2 (bf16 I/O) or 1e-4 (fp32 I/O), as stated for this build; no
     scaling with the magnitude of the value.  (check_close can add a term `ulp * |ref|`; every parity test passes
     ulp = 0.)  Every comparison records the max-abs error, the largest |ref| and the number of elements above the
-    bound (`STATS`, written to gpurun_out/parity_stats.json at the end of a GPU test session);
+    bound (`STATS`, written to parity_stats.json at the end of a GPU test session);
   * LSE (always fp32): plain 1e-4 (fp32 I/O) or 1e-3 (bf16 I/O).
 """
 from __future__ import annotations
