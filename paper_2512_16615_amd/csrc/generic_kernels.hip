@@ -275,14 +275,15 @@ hipError_t launch_qknorm_rope_pool(const Plan &p, const void *Qpre, const void *
 // Alg. 1, selection loop, one level: every wave scores one level-l query token against its candidates
 // (all n_L tokens at the coarsest level, the K_l*B children of the parent's picks below it) and keeps the
 // Kout best.  Scores are fp32 fused-multiply-add chains over channels 0..d-1 in order, so they do not
-// depend on the launch shape; ties go to the lower key id; rows are written in ascending id order.
+// depend on the launch shape; ties go to the lower key id; rows are written in ascending id order.  A score is kept as its bits made
+// monotonic, 1 at least (0: taken already), so that the winners are different candidates also where scores are infinite or NaN.
 template <class T>
 __global__ void select_kernel(const T *Ql, const T *Kl, int64_t n_l, int d, int B, const int32_t *parent, int Kp,
                               int Kout, int32_t *out, int C, int64_t nblk) {
     extern __shared__ float smem[];
     const int W = blockDim.x >> 6, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     float *qs = smem + wave * d;
-    float *sc = smem + W * d + (size_t)wave * C;
+    uint32_t *sc = reinterpret_cast<uint32_t *>(smem + W * d) + (size_t)wave * C;
     const int64_t bh = blockIdx.x / nblk, r = blockIdx.x % nblk;
     const T *Kb = Kl + bh * n_l * d;
     const int32_t *prow = parent ? parent + (bh * nblk + r) * Kp : nullptr;
@@ -305,25 +306,26 @@ __global__ void select_kernel(const T *Ql, const T *Kl, int64_t n_l, int d, int 
 #pragma unroll
                     for (int e = 0; e < Vec<T>::n; ++e) s = __builtin_fmaf(qs[c + e], tmp[e], s);
                 }
-                sc[p] = s;
+                const uint32_t b = __float_as_uint(s + 0.f);     // -0 ties with +0
+                sc[p] = max(b ^ (uint32_t)(((int32_t)b >> 31) | (int32_t)0x80000000), 1u);
             }
         int mine = 0;                                      // lane k keeps the k-th winner's position
         for (int k = 0; k < Kout; ++k) {
             __syncthreads();
-            float bs = -INFINITY;
+            uint32_t bs = 0;
             int bp = 0x7fffffff;
             if (active)
                 for (int p = lane; p < C; p += 64) {
-                    const float v = sc[p];
+                    const uint32_t v = sc[p];
                     if (v > bs) { bs = v; bp = p; }        // ascending p: strict '>' keeps the lowest position
                 }
 #pragma unroll
             for (int o = 32; o >= 1; o >>= 1) {
-                const float os = __shfl_xor(bs, o, 64);
+                const uint32_t os = __shfl_xor(bs, o, 64);
                 const int op = __shfl_xor(bp, o, 64);
                 if (os > bs || (os == bs && op < bp)) { bs = os; bp = op; }
             }
-            if (active && lane == (bp & 63)) sc[bp] = -INFINITY;
+            if (active && lane == (bp & 63)) sc[bp] = 0;
             if (lane == k) mine = bp;
         }
         if (active) {

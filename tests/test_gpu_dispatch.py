@@ -156,14 +156,15 @@ def test_selection_of_more_than_16(cfg):
     _full_parity(cfg, 0xD165)
 
 
-@pytest.mark.parametrize("cfg", _MANY_PICKS + [_bf16("K8", 4096, L=2), _tile("f32_K8", 1024, 4, 8, 2)], ids=lambda c: c["name"])
+@pytest.mark.parametrize("cfg", _MANY_PICKS + [_bf16("K8", 4096, L=2), _tile("f32_K8", 1024, 4, 8, 2), _tile("f32_K17", 1024, 4, 17, 2),
+                                               dict(_bf16("K8_path1", 4096, L=2), kernel_path=1)], ids=lambda c: c["name"])
 def test_lists_hold_different_blocks_whatever_the_scores_are(cfg):
     """NaN and infinite scores: every list is still K_l different blocks of its range, in ascending order (the attention reads
     what they name)."""
     import torch
     from paper_2512_16615_amd import llsa
     from tests import harness as H
-    plan = H.make_plan(cfg)
+    plan = H.make_plan(cfg, kernel_path=cfg.get("kernel_path", 0))
     x = H.make_inputs(cfg, 0xD166)
     Q, K, V = (H.to_dev(x[n], cfg) for n in ("Q", "K", "V"))
     N, B = cfg["N"], cfg["B"]
