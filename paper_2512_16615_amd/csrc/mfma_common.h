@@ -30,6 +30,14 @@ __device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 
+// A load through an address that came as a number (from LDS, a lane table, a kernel argument's struct): named as global memory.
+// The compiler makes a flat load of it otherwise, which also counts as an LDS operation, so that every LDS wait behind it waits
+// for memory and nothing is in flight during the math.
+template <class T> __device__ __forceinline__ T gload(uint64_t addr) {
+    return *reinterpret_cast<const __attribute__((address_space(1))) T *>(addr);
+}
+template <class T> __device__ __forceinline__ T gload(const void *p) { return gload<T>(reinterpret_cast<uint64_t>(p)); }
+
 __device__ __forceinline__ bf16x8 ld_bf16x8(const void *p) { return *reinterpret_cast<const bf16x8 *>(p); }
 
 // two fp32 -> packed bf16 (round to nearest even; one v_cvt_pk_bf16_f32)
@@ -45,6 +53,27 @@ __device__ __forceinline__ bf16x8 pack8(const f32x4 &a, const f32x4 &b) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) { r[i] = (__bf16)a[i]; r[4 + i] = (__bf16)b[i]; }
     return r;
+}
+
+// fp32 values as three bf16 parts, x = p[0] + p[1] + p[2] exactly: each part is the upper half of what the ones before it leave,
+// and each difference is exact.  A product of a bf16 operand with the three parts, summed in fp32, is the product with x itself.
+// (What is not finite stays so, but may become a NaN where it was an infinity: an infinite x has a NaN for its second part, and
+// a part that is 0 times an infinite operand is one.)
+struct Parts3 { bf16x8 p[3]; };
+__device__ __forceinline__ Parts3 split8(const f32x4 &a, const f32x4 &b) {
+    union { uint32_t u[4]; bf16x8 v; } r[3];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        float x0 = i < 2 ? a[2 * i] : b[2 * i - 4], x1 = i < 2 ? a[2 * i + 1] : b[2 * i - 3];
+#pragma unroll
+        for (int p = 0; p < 3; ++p) {
+            const uint32_t u0 = __float_as_uint(x0), u1 = __float_as_uint(x1);
+            r[p].u[i] = __builtin_amdgcn_perm(u1, u0, 0x07060302);      // the upper halves, x0's first
+            x0 -= __uint_as_float(u0 & 0xffff0000u);
+            x1 -= __uint_as_float(u1 & 0xffff0000u);
+        }
+    }
+    return {{r[0].v, r[1].v, r[2].v}};
 }
 
 // Two transposing LDS reads glued into one 8-slot MFMA operand.
@@ -85,22 +114,24 @@ __device__ __forceinline__ T pick(const T (&arr)[n], int idx) {
 // transposed 8-byte reads of a half wave was timed: those reads did not get faster, the row-wise ones got slower.)
 // d = 128 (256-byte rows, all banks): the key is a bijection of 16 consecutive rows onto the 16 chunks, and its
 // upper three bits differ among the 8 rows a half wave reads transposed.
+// d = 32: 4 rows to a pass over the banks, so the key changes every 4 rows; d = 16 (tile kernels only): none.
 template <int D> __device__ __forceinline__ int swz_key(int r) {
-    return D == 64 ? ((r >> 1) & 7) : (((r & 7) << 1) | ((r >> 3) & 1));
+    return D == 64 ? ((r >> 1) & 7) : D == 128 ? (((r & 7) << 1) | ((r >> 3) & 1)) : D == 32 ? ((r >> 2) & 3) : 0;
 }
 
 // Per-lane byte offsets of the MFMA operand reads inside a 16-row slice of such unpadded, swizzled rows (2 D bytes
 // each): row[ks] = the 16-byte row-wise read of row lane % 16, contraction step ks (A or B operand with the rows as
-// the 16-wide dimension); tr[n] = the address a lane supplies to the transposing 64-bit read for the n-th group of 16
-// channels (rows 4 (lane / 16) + (lane % 16) / 4).  The swizzle key of a row depends on the lane only.
-template <int D> struct TileOffsets { int row[D / 32], tr[D / 16]; };
+// the 16-wide dimension; d = 16: lanes 32 .. 63 repeat the row's two chunks); tr[n] = the address a lane supplies to the
+// transposing 64-bit read for the n-th group of 16 channels (rows 4 (lane / 16) + (lane % 16) / 4).  The swizzle key of a
+// row depends on the lane only.
+template <int D> struct TileOffsets { int row[(D + 31) / 32], tr[D / 16]; };
 template <int D> __device__ __forceinline__ TileOffsets<D> tile_offsets(int lane) {
     constexpr int ROWB = 2 * D;
     const int i16 = lane & 15, g = lane >> 4;
     const int key_row = swz_key<D>(i16), key_tr = swz_key<D>(4 * g + (i16 >> 2));
     TileOffsets<D> o;
 #pragma unroll
-    for (int ks = 0; ks < D / 32; ++ks) o.row[ks] = i16 * ROWB + (((g + 4 * ks) ^ key_row) << 4);
+    for (int ks = 0; ks < (D + 31) / 32; ++ks) o.row[ks] = i16 * ROWB + ((((g + 4 * ks) & (D / 8 - 1)) ^ key_row) << 4);
 #pragma unroll
     for (int n = 0; n < D / 16; ++n)
         o.tr[n] = (4 * g + (i16 >> 2)) * ROWB + (((2 * n + ((i16 >> 1) & 1)) ^ key_tr) << 4) + ((i16 & 1) << 3);
@@ -146,7 +177,7 @@ struct BlockTable {
                 int64_t tok0;
                 if (l < t.L) {
                     const int64_t row = blk >> (t.lb * (l + 1) - 4);
-                    const int32_t listed = pick(t.I, l)[(bh * pick(t.rows, l) + row) * pick(t.Kl, l) + (k >> t.ls)];
+                    const int32_t listed = gload<int32_t>(pick(t.I, l) + (bh * pick(t.rows, l) + row) * pick(t.Kl, l) + (k >> t.ls));
                     tok0 = ((int64_t)listed << t.lb) + ((k & ((1 << t.ls) - 1)) << 4);
                     cnt = 16;
                 } else {
@@ -211,7 +242,7 @@ struct CoarseTable {
         int tok = k << 4;                                    // dense level
         cnt = min(16, n - tok);
         if (listed) {
-            tok = (*reinterpret_cast<const int32_t *>(listed) << t->lb) + ((k & ((1 << t->ls) - 1)) << 4);
+            tok = (gload<int32_t>(listed) << t->lb) + ((k & ((1 << t->ls) - 1)) << 4);
             cnt = 16;
         }
         if (kptr == 0) cnt = 0;
