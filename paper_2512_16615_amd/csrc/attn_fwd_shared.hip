@@ -5,12 +5,16 @@
 // every level >= 1 (Alg. 1, enrichment loop: block i reads row i / B^l of I^(l)), i.e. the same coarse key/value
 // tokens.  One workgroup of 4 or 8 waves owns such a group or half of one; every wave owns one or two of its
 // 16-query tiles.
-//   Phase A (levels >= 1): the workgroup stages each tile of two 16-token blocks (K and V rows) once in
-//     LDS, double-buffered; every wave reads the K operand once and multiplies it with both of its query
+//   Phase A (levels >= 1): the workgroup brings each tile of two 16-token blocks (K and V rows) once into
+//     LDS, in a ring of four; every wave reads the K operand once and multiplies it with both of its query
 //     blocks, likewise the transposed V operand, so the gather traffic of the coarse tokens is paid once
 //     per 128 or 256 queries instead of once per 16.
 //   Phase B (level 0): each wave walks the level-0 tiles of each of its query tiles' lists; their K and V rows are
 //     fetched as whole cache lines and reach the operand layouts through the wave's private LDS tiles.
+// All rows go from memory straight into LDS (load_lds): through registers and LDS writes the writes alone held the LDS for a third
+// (d = 64) to half (d = 128) of the kernel's time.  16 heads x 65536 tokens, d = 64, K = 8: 204 -> 195 us; 8 x 65536, d = 128, K = 16:
+// 362 -> 328; 8 x 262144: 1510 -> 1390.  What is left of it, d = 64: 21 % of the matrix pipe, half of the vector issue slots; level 0 by
+// itself (Le = 0) takes 162 us as before, at a third of the rate its gathers reach without any arithmetic.
 // Score tiles are computed transposed (S^T = K Q^T) so that the accumulator layout (4 keys x 1 query per
 // lane) is the B operand of O^T += V^T P^T; see mfma_common.h for the register layouts.
 #include <type_traits>
@@ -19,11 +23,6 @@
 
 namespace llsa {
 
-typedef const __attribute__((address_space(1))) u32x4 *gvec_ptr;
-__device__ __forceinline__ u32x4 gload16(const char *base, unsigned off) {
-    return *reinterpret_cast<gvec_ptr>(reinterpret_cast<const __attribute__((address_space(1))) char *>(
-        reinterpret_cast<uintptr_t>(base)) + off);
-}
 constexpr float kMaxSum = 4096.f;   // a query's softmax reference is raised only when a tile's probabilities exceed this
 
 // NB = fine query tiles per wave (1 or 2), NW = waves per workgroup (4 or 8); a workgroup owns NW * NB consecutive
@@ -32,20 +31,15 @@ template <int D, int NB, int NW, int GW>
 __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 64 ? 4 : 2))) attn_fwd_shared_kernel(ListArgs args, const uint16_t *__restrict__ Q,
                                                                uint16_t *__restrict__ O, float *__restrict__ LSE,
                                                                int64_t N, FastDiv groups) {
-    constexpr int KS = D / 32, NT = D / 16, STRIDE = D * 2 + 32, PARTS = D / 8, TILE = 32 * STRIDE;
-    constexpr int NTHR = 64 * NW;
-    constexpr int RND = (2 * 32 * PARTS) / NTHR;        // staging rounds of the workgroup per shared tile (K and V)
-    constexpr int VCH = D / 16, KPU = 64 / PARTS;       // private V staging of one wave (phase B)
-    // Phase B: per wave a K tile (row-wise reads: rows 32 bytes apart in the banks) and a V tile (transposed reads only:
-    // 16 bytes of padding do).  Phase A's two double-buffered [K | V] tiles live in the first 4 TILE bytes of the same
-    // memory; a workgroup barrier separates the phases.
-    constexpr int VSTRIDE = D * 2 + 16, VTILE = 32 * VSTRIDE;
-    __shared__ __attribute__((aligned(16))) char lds[NW * (TILE + VTILE)];
-    static_assert(4 * TILE <= NW * (TILE + VTILE), "phase A's buffers must fit");
-    auto sh = [&](int buf, int which) { return lds + (buf * 2 + which) * TILE; };
+    constexpr int KS = D / 32, NT = D / 16, ROWB = 2 * D, HALF = 16 * ROWB, TILE = 2 * HALF;   // 16 rows, 32 rows
+    constexpr int CPH = HALF / 1024;                    // load_lds steps of 16 rows
+    constexpr int CPW = 4 * CPH / NW;                   // of a [K | V] tile that the workgroup shares, per wave
+    constexpr int RING = 4, NBUF = GW > 1 ? 2 : 1;      // phase A's tiles; phase B's tiles per group of waves
+    constexpr int OWN = (GW > 0 ? NW / GW : NW) * NBUF;
+    __shared__ __attribute__((aligned(16))) char lds[(OWN > RING ? OWN : RING) * 2 * TILE];
 
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int i16 = lane & 15, g = lane >> 4;
     const unsigned wg = xcd_contiguous32(blockIdx.x, gridDim.x);
     const int64_t bh = groups(wg), blk0 = (wg - (unsigned)bh * groups.d) * (NW * NB);   // groups.d workgroups per head
@@ -53,6 +47,8 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D 
     (void)args;                                                       // read through the pointer: fields of a level by scalar loads
     const list_args_ptr t = kernel_list_args();
     const float sc2 = t->scale * kLog2e;
+    const TileOffsets<D> o = tile_offsets<D>(lane);
+    const RowSource<D> src(lane);
 
     bf16x8 qop[NB][KS];
     f32x4 acc[NB][NT];
@@ -68,8 +64,6 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D 
         lsum[b] = 0.f;
     }
 
-    using StrideA = std::integral_constant<int, STRIDE>;
-    using StrideB = std::integral_constant<int, VSTRIDE>;
     using B0 = std::integral_constant<int, 0>;
     using B1 = std::integral_constant<int, 1>;
     // Softmax update of query block b for one tile (s0 / s1: raw S^T of the two halves; b0 / b1: log2 weights of their levels,
@@ -118,47 +112,42 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D 
         lsum[b] += sum;
         return pack8(p[0], p[1]);
     };
-    // O^T += V^T P^T with the V tile at `vt` (row-major, VS bytes per key row)
-    auto pv = [&](auto bsel, const bf16x8 pop, const char *vt, auto vstride) {
-        constexpr int b = decltype(bsel)::value;
-        constexpr int VS = decltype(vstride)::value;
-        const char *base = vt + (4 * g + (i16 >> 2)) * VS + (i16 & 3) * 8;
-#pragma unroll
-        for (int n = 0; n < NT; ++n) acc[b][n] = mfma16(lds_tr_pair(base + n * 32, base + 16 * VS + n * 32), pop, acc[b][n]);
-    };
-    // One tile of 32 staged keys against all query tiles of the wave: every K operand and every transposed V operand is read
-    // from LDS once.
-    auto shared_tile = [&](const char *kt, const char *vt, auto vstride, int c0, int c1, float b0, float b1) {
-        constexpr int VS = decltype(vstride)::value;
-        bf16x8 kop[2][KS];
+    // Query tiles first .. first + count - 1 of the wave against one tile of 32 keys in LDS; every operand is read once for all of
+    // them.  early: V's operands are read before the scores are worked on, and `have_read` is called when LDS holds nothing
+    // more of the tile that is wanted.
+    auto tile = [&](auto first, auto count, auto early, const char *kt, const char *vt, int c0, int c1, float w0, float w1, auto have_read) {
+        constexpr int b0 = decltype(first)::value, n = decltype(count)::value;
+        constexpr bool E = decltype(early)::value;
+        f32x4 s[n][2];
+        bf16x8 vtr[E ? NT : 1];
 #pragma unroll
         for (int h = 0; h < 2; ++h)
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks)
-                kop[h][ks] = *reinterpret_cast<const bf16x8 *>(kt + (h * 16 + i16) * STRIDE + g * 16 + ks * 64);
-        f32x4 s[NB][2];
+            for (int ks = 0; ks < KS; ++ks) {
+                const bf16x8 kop = ld_bf16x8(kt + h * HALF + o.row[ks]);
 #pragma unroll
-        for (int b = 0; b < NB; ++b)
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                s[b][h] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int ks = 0; ks < KS; ++ks) s[b][h] = mfma16(kop[h][ks], qop[b][ks], s[b][h]);
+                for (int b = 0; b < n; ++b) s[b][h] = mfma16(kop, qop[b0 + b][ks], ks == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : s[b][h]);
             }
-        if constexpr (NB > 1) {                                       // both tiles' P first, then one transposing read of V for both
-            const bf16x8 p0 = probs(B0{}, s[0][0], s[0][1], c0, c1, b0, b1);
-            const bf16x8 p1 = probs(B1{}, s[NB - 1][0], s[NB - 1][1], c0, c1, b0, b1);
-            const char *base = vt + (4 * g + (i16 >> 2)) * VS + (i16 & 3) * 8;
+        if constexpr (E) {
 #pragma unroll
-            for (int n = 0; n < NT; ++n) {
-                const bf16x8 vtr = lds_tr_pair(base + n * 32, base + 16 * VS + n * 32);
-                acc[0][n] = mfma16(vtr, p0, acc[0][n]);
-                acc[NB - 1][n] = mfma16(vtr, p1, acc[NB - 1][n]);
-            }
-        } else {
-            pv(B0{}, probs(B0{}, s[0][0], s[0][1], c0, c1, b0, b1), vt, vstride);
+            for (int x = 0; x < NT; ++x) vtr[x] = lds_tr_pair(vt + o.tr[x], vt + HALF + o.tr[x]);
+            have_read();
+        }
+        bf16x8 p[n];
+        p[0] = probs(first, s[0][0], s[0][1], c0, c1, w0, w1);
+        if constexpr (n > 1) p[n - 1] = probs(B1{}, s[n - 1][0], s[n - 1][1], c0, c1, w0, w1);
+#pragma unroll
+        for (int x = 0; x < NT; ++x) {
+            const bf16x8 v = E ? vtr[E ? x : 0] : lds_tr_pair(vt + o.tr[x], vt + HALF + o.tr[x]);
+#pragma unroll
+            for (int b = 0; b < n; ++b) acc[b0 + b][x] = mfma16(v, p[b], acc[b0 + b][x]);
         }
     };
+    using One = std::integral_constant<int, 1>;
+    using All = std::integral_constant<int, NB>;
+    using Early = std::true_type;
+    using Late = std::false_type;
+    auto nothing = []() {};
 
     // The level-0 lists of this wave's NB query blocks, fetched now so that phase B does not wait for them:
     // lane LL b + j holds the first token of 16-token tile j of query tile b's list (at most LL tiles; a listed block of B
@@ -176,163 +165,117 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D 
 
     // ------------------------------------------------------------------ phase A: shared coarse levels
     const int nbc = t->lev[t->nlev - 1].end - nb0;                    // coarse tiles of the list
+    const unsigned lds0 = lds_address(lds);
     if (nbc > 0) {
-        CoarseTable ctab;                                              // lane j: coarse block 64 * chunk + j
+        CoarseTable ctab;                                              // lane j: coarse block 64 * chunk + j, of the tile issued last
         ctab.fill<D>(t, bh, (unsigned)blk0, 0, lane);
-        // Staging round r of this wave: 64 consecutive 16-byte chunks of the [K | V] tile, i.e. 64 / PARTS key rows of
-        // one half of K or of V, the same choice for the whole wave.
-        // (One round: the first half of the waves stages K, the other V; more: the first half of the rounds stages K.)
-        u32x4 sreg[RND];
-        int s_half[RND];
-        unsigned s_off[RND];
-#pragma unroll
-        for (int r = 0; r < RND; ++r) {
-            const int key0 = ((64 * wave + NTHR * r) % (32 * PARTS)) / PARTS;   // the wave's first key row in round r
-            s_half[r] = key0 >> 4;
-            s_off[r] = (unsigned)((((key0 & 15) + lane / PARTS) * D + (lane % PARTS) * 8) * 2);
-        }
-        const bool v_wave = RND == 1 && wave >= NW / 2;
-        uint64_t sptr = v_wave ? ctab.vptr : ctab.kptr;               // d = 64: the tensor this wave stages
+        const bool v_wave = wave >= NW / 2;                           // this wave brings in V rows
+        uint64_t rows = v_wave ? +ctab.vptr : +ctab.kptr;
+        float w_now = ctab.bias2, w_next = 0.f;                       // the weights, of the tile worked on
+        int c0 = 16, c1 = 16;                                         // rows of the last tile's halves
         const int ntile = (nbc + 1) >> 1;                             // only the last tile may be ragged or lack its second half
-        auto load_shared = [&](int u) {                               // coarse blocks 2u, 2u + 1 -> registers
+        // this wave's share of a tile: load_lds steps of one half of K or of V
+        const int part = wave * CPW / CPH, sub = wave * CPW % CPH, half = part & 1;
+        auto issue = [&](int u) {                                     // coarse blocks 2u, 2u + 1
             if (u > 0 && ((2 * u) & 63) == 0) {
                 ctab.fill<D>(t, bh, (unsigned)blk0, (2 * u) >> 6, lane);
-                sptr = v_wave ? ctab.vptr : ctab.kptr;
+                rows = v_wave ? +ctab.vptr : +ctab.kptr;
+                w_next = ctab.bias2;
             }
-#pragma unroll
-            for (int r = 0; r < RND; ++r) {
-                const bool have = 2 * u + s_half[r] < nbc;
-                const int j = (have ? 2 * u + s_half[r] : 2 * u) & 63;
-                const char *src = RND == 1 ? BlockTable::rl_ptr(sptr, j) : (r < RND / 2 ? ctab.K(j) : ctab.V(j));
-                unsigned off = s_off[r];
-                if (u + 1 == ntile) {
-                    const int cnt = have ? ctab.count(j) : 0;
-                    if (cnt < 16) {                                   // ragged or absent block: re-read its last valid row
-                        const int row = min((int)(off / (D * 2)), max(cnt, 1) - 1);
-                        off = (unsigned)(row * D * 2) + off % (D * 2);
-                    }
-                }
-                sreg[r] = gload16(src, off);
-            }
-        };
-        auto store_shared = [&](int buf) {
-#pragma unroll
-            for (int r = 0; r < RND; ++r) {
-                const int cc = tid + NTHR * r, which = cc / (32 * PARTS), c = cc % (32 * PARTS);
-                *reinterpret_cast<u32x4 *>(sh(buf, which) + (c / PARTS) * STRIDE + (c % PARTS) * 16) = sreg[r];
-            }
-        };
-        load_shared(0);
-        for (int u = 0; u < ntile; ++u) {
-            const int buf = u & 1;
-            store_shared(buf);
-            // per-half fields of this tile, before the table may be refilled for the next one
-            int cnt[2] = {16, 16};
-            float bias2[2] = {ctab.bias((2 * u) & 63), ctab.bias((2 * u + 1) & 63)};
+            const int j = (2 * u + half < nbc ? 2 * u + half : 2 * u) & 63;
+            const uint64_t base = reinterpret_cast<uint64_t>(BlockTable::rl_ptr(rows, j));
+            const unsigned dst = lds0 + (u % RING) * (2 * TILE) + wave * CPW * 1024;
             if (u + 1 == ntile) {
-                cnt[0] = ctab.count((2 * u) & 63);
-                if (2 * u + 1 < nbc) cnt[1] = ctab.count((2 * u + 1) & 63);
-                else bias2[1] = -INFINITY;                            // an absent half: probabilities 0
+                const int n0 = ctab.count((2 * u) & 63), n1 = 2 * u + 1 < nbc ? ctab.count((2 * u + 1) & 63) : 16;
+                const int cnt = ctab.count(j);
+                c0 = n0;
+                c1 = n1;
+                if (cnt < 16) {                                       // rows past a ragged end repeat the last one
+#pragma unroll
+                    for (int x = 0; x < CPW; ++x) {
+                        const int r = (sub + x) * (512 / D) + lane / (D / 8);
+                        const unsigned v = (unsigned)(min(r, cnt - 1) * ROWB + (((lane % (D / 8)) ^ swz_key<D>(r)) << 4));
+                        load_lds<1>(base, v, v, dst + x * 1024);
+                    }
+                    return;
+                }
             }
-            __syncthreads();                                          // tile u visible; buffer buf^1 free again
-            if (u + 1 < ntile) load_shared(u + 1);
-            shared_tile(sh(buf, 0), sh(buf, 1), StrideA{}, cnt[0], cnt[1], bias2[0], bias2[1]);
+            load_lds<CPW>(base + sub * 1024, src.v0, src.v1, dst);
+        };
+        for (int u = 0; u < RING - 1 && u < ntile; ++u) issue(u);
+        for (int u = 0; u < ntile; ++u) {
+            // tile u is there, and tile u - 1, whose place tile u + 3 takes, has been read by every wave
+            if (u + 2 < ntile) vm_wait_barrier<2 * CPW>();
+            else vm_wait_barrier<0>();
+            if (u + RING - 1 < ntile) issue(u + RING - 1);
+            if (u > 0 && ((2 * u) & 63) == 0) w_now = w_next;
+            auto weight = [&](int j) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w_now), j & 63)); };
+            const bool last = u + 1 == ntile;
+            const char *kt = lds + (u % RING) * (2 * TILE);
+            // an absent half: probabilities 0
+            tile(B0{}, All{}, Late{}, kt, kt + TILE, last ? c0 : 16, last ? c1 : 16, weight(2 * u),
+                 2 * u + 1 < nbc ? weight(2 * u + 1) : -INFINITY, nothing);
         }
+        vm_wait_barrier<0>();                                         // phase A's buffers are free
     }
 
-    if constexpr (GW > 0) {
-        // -------------------------------------------------------------- phase B, blocks of 32 or 64 tokens
-        // The B queries of a block use one level-0 list: the GW waves that hold them stage its tiles together, as phase A does
-        // for the whole workgroup, double-buffered per group (GW = 1: a wave alone, whose LDS operations stay in order).  A
-        // list is whole blocks of B >= 32 tokens: no half of a tile is ever absent.  16 heads x 65536 tokens in blocks of 64, K = 8:
-        // 512 -> 365 us.
-        constexpr int R = 2 * 32 * PARTS / (64 * GW), BUF = TILE + VTILE, NBUF = GW > 1 ? 2 : 1;
-        static_assert((NW / GW) * NBUF * BUF <= NW * (TILE + VTILE), "the groups' buffers must fit");
-        __syncthreads();                                              // phase A's buffers are free
+    // ------------------------------------------------------------------ phase B: level 0
+    // half h of the K (or V, T0) rows of tile j0 of the list that begins at lane l0, by the wave alone
+    auto load_half = [&](const void *T0, int l0, int j0, int h, unsigned dst) {
+        const int j = j0 + h < nb0 ? j0 + h : j0;                     // an absent second half re-reads the first
+        const int64_t row = bh * N + __builtin_amdgcn_readlane(tok0, l0 + j);
+        load_lds<CPH>(reinterpret_cast<uint64_t>(T0) + (uint64_t)row * ROWB, src.v0, src.v1, dst + h * HALF);
+    };
+    const void *K0 = t->lev[0].K, *V0 = t->lev[0].V;
+    if constexpr (GW > 1) {
+        // Blocks of 32 or 64 tokens: the B queries of a block use one level-0 list, whose tiles the GW waves that hold them bring in
+        // together, double-buffered.  A list is whole blocks of B >= 32 tokens: no half of a tile is ever absent.
         const int wg_in = wave % GW;
-        char *base = lds + (wave / GW) * (NBUF * BUF);
-        const int64_t head = bh * N;
-        const char *K0 = static_cast<const char *>(t->lev[0].K), *V0 = static_cast<const char *>(t->lev[0].V);
-        u32x4 sreg[R];
-        auto load_group = [&](int u) {                                // 64 chunks a round: rows of one half of K or of V
+        const char *buf = lds + (wave / GW) * (2 * 2 * TILE);
+        const unsigned dst = lds0 + (wave / GW) * (2 * 2 * TILE);
+        auto issue = [&](int u) {
 #pragma unroll
-            for (int r = 0; r < R; ++r) {
-                const int c0 = 64 * (wg_in + GW * r), key0 = (c0 % (32 * PARTS)) / PARTS;
-                const char *src = c0 >= 32 * PARTS ? V0 : K0;
-                const int64_t row = head + __builtin_amdgcn_readlane(tok0, 2 * u + (key0 >> 4));
-                sreg[r] = gload16(src + row * (D * 2), (unsigned)((((key0 & 15) + lane / PARTS) * D + (lane % PARTS) * 8) * 2));
+            for (int x = 0; x < 4 / GW; ++x) {
+                const int part = wg_in * (4 / GW) + x;                // K, K, V, V: its halves
+                load_half(part < 2 ? K0 : V0, 0, 2 * u, part & 1, dst + (u & 1) * (2 * TILE) + (part >> 1) * TILE);
             }
         };
-        load_group(0);
+        issue(0);
         for (int u = 0; 2 * u < nb0; ++u) {
-            char *buf = base + (u % NBUF) * BUF;
-            if constexpr (GW == 1) __builtin_amdgcn_wave_barrier();
-#pragma unroll
-            for (int r = 0; r < R; ++r) {
-                const int c0 = 64 * (wg_in + GW * r), row = (c0 % (32 * PARTS)) / PARTS + lane / PARTS;
-                char *dst = c0 >= 32 * PARTS ? buf + TILE + row * VSTRIDE : buf + row * STRIDE;
-                *reinterpret_cast<u32x4 *>(dst + (lane % PARTS) * 16) = sreg[r];
-            }
-            if constexpr (GW > 1) __syncthreads();
-            else __builtin_amdgcn_wave_barrier();
-            if (2 * u + 2 < nb0) load_group(u + 1);
-            shared_tile(buf, buf + TILE, StrideB{}, 16, 16, 0.f, 0.f);
+            vm_wait_barrier<0>();
+            if (2 * u + 2 < nb0) issue(u + 1);
+            const char *kt = buf + (u & 1) * (2 * TILE);
+            tile(B0{}, All{}, Late{}, kt, kt + TILE, 16, 16, 0.f, 0.f, nothing);
         }
     } else {
-    // ------------------------------------------------------------------ phase B: own level-0 blocks
-    // K and V rows are fetched with 8 consecutive lanes per 128-byte row (whole cache lines per instruction: loading
-    // the MFMA operand layout straight from memory, 16 rows x half a line per instruction, caps the gather rate at a
-    // third of what the L2 delivers) and reach the operand layouts through the wave's own LDS tiles.
-    __syncthreads();                                                  // phase A's buffers are free
-    char *my_k = lds + wave * (TILE + VTILE), *my_v = my_k + TILE;
-    unsigned voff[VCH];
-#pragma unroll
-    for (int u = 0; u < VCH; ++u) voff[u] = (unsigned)((((lane / PARTS + KPU * u) & 15) * D + (lane % PARTS) * 8) * 2);
-
-    // The tiles of the wave's NB query blocks form one stream: the next tile's rows are in flight during the
-    // current tile's math, also across the border between the two blocks (tok0: fetched before phase A).
-    u32x4 kreg[VCH], vreg[VCH];
-    const char *K0 = static_cast<const char *>(t->lev[0].K), *V0 = static_cast<const char *>(t->lev[0].V);
-    auto load_tile = [&](int b, int j0) {
-        int64_t off[2];
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int j = (j0 + h < nb0) ? j0 + h : j0;               // an absent second half re-reads the first
-            off[h] = (bh * N + __builtin_amdgcn_readlane(tok0, LL * b + j)) * (D * 2);
-        }
-#pragma unroll
-        for (int u = 0; u < VCH; ++u) {
-            kreg[u] = gload16(K0 + off[(KPU * u) >> 4], voff[u]);
-            vreg[u] = gload16(V0 + off[(KPU * u) >> 4], voff[u]);
-        }
-    };
-    auto phase_b = [&](auto bsel) {
-        constexpr int b = decltype(bsel)::value;
-        for (int j0 = 0; j0 < nb0; j0 += 2) {
-            __builtin_amdgcn_wave_barrier();                          // one wave's LDS operations stay in order
-#pragma unroll
-            for (int u = 0; u < VCH; ++u) {
-                *reinterpret_cast<u32x4 *>(my_k + (lane / PARTS + KPU * u) * STRIDE + (lane % PARTS) * 16) = kreg[u];
-                *reinterpret_cast<u32x4 *>(my_v + (lane / PARTS + KPU * u) * VSTRIDE + (lane % PARTS) * 16) = vreg[u];
+        // Every wave alone: the tiles of its query tiles (GW = 1: of all of them at once) form one stream.  The next tile's rows are
+        // asked for as soon as the current one's have been read, so they fly during all of its math.
+        const char *my = lds + wave * (2 * TILE);
+        const unsigned dst = lds0 + wave * (2 * TILE);
+        auto load_tile = [&](int l0, int j0) {
+            load_half(K0, l0, j0, 0, dst);
+            load_half(K0, l0, j0, 1, dst);
+            load_half(V0, l0, j0, 0, dst + TILE);
+            load_half(V0, l0, j0, 1, dst + TILE);
+        };
+        auto walk = [&](auto first, auto count, bool end) {
+            const int l0 = LL * decltype(first)::value;
+            for (int j0 = 0; j0 < nb0; j0 += 2) {
+                const bool here = j0 + 2 < nb0;
+                vm_wait<0>();
+                // level-0 blocks are always full; an absent second half has weight 0
+                tile(first, count, Early{}, my, my + TILE, 16, 16, 0.f, j0 + 1 < nb0 ? 0.f : -INFINITY, [&]() {
+                    if (here) load_tile(l0, j0 + 2);
+                    else if (!end) load_tile(l0 + LL, 0);
+                });
             }
-            __builtin_amdgcn_wave_barrier();
-            if (j0 + 2 < nb0) load_tile(b, j0 + 2);                   // the registers are free again: next tile's rows
-            else if (b + 1 < NB) load_tile(b + 1, 0);                 // fly during all of this tile's math
-            f32x4 s[2];
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                s[h] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int ks = 0; ks < KS; ++ks)
-                    s[h] = mfma16(*reinterpret_cast<const bf16x8 *>(my_k + (h * 16 + i16) * STRIDE + g * 16 + ks * 64), qop[b][ks], s[h]);
-            }
-            // level-0 blocks are always full; an absent second half has weight 0
-            pv(bsel, probs(bsel, s[0], s[1], 16, 16, 0.f, j0 + 1 < nb0 ? 0.f : -INFINITY), my_v, StrideB{});
+        };
+        load_tile(0, 0);
+        if constexpr (GW == 1) walk(B0{}, All{}, true);
+        else {
+            walk(B0{}, One{}, NB == 1);
+            if constexpr (NB > 1) walk(B1{}, One{}, true);
         }
-    };
-    load_tile(0, 0);
-    phase_b(B0{});
-    if constexpr (NB > 1) phase_b(B1{});
     }
 
     // ------------------------------------------------------------------ epilogue

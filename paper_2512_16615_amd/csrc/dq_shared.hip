@@ -4,6 +4,8 @@
 // key/value tiles are staged once per workgroup in LDS, the level-0 tiles are walked per query tile).
 // Per tile and query block:  S^T = K Q^T, dP^T = V dO^T  ->  dS^T = P^T o (dP^T - D)  ->  dQ^T += K^T dS^T,
 // with K read from LDS both row-wise (first product) and transposed (last product).
+// Rows go from memory straight into LDS, as in the forward kernel (16 heads x 65536 tokens, d = 64: 269 -> 249 us; 8 x 65536, d = 128,
+// K = 16: 447 -> 383).
 // The kernel also produces D = rowsum(dO o O) for its queries and stores it for the key-major kernels.
 #include <type_traits>
 
@@ -11,11 +13,6 @@
 
 namespace llsa {
 
-typedef const __attribute__((address_space(1))) u32x4 *gvec_ptr_t;
-__device__ __forceinline__ u32x4 gload16b(const char *base, unsigned off) {
-    return *reinterpret_cast<gvec_ptr_t>(reinterpret_cast<const __attribute__((address_space(1))) char *>(
-        reinterpret_cast<uintptr_t>(base)) + off);
-}
 __device__ __forceinline__ bf16x8 to_bf16x8(u32x4 v) {
     union { u32x4 u; bf16x8 b; } c;
     c.u = v;
@@ -27,24 +24,21 @@ __device__ __forceinline__ float bf_hi(uint32_t w) { return __uint_as_float(w & 
 // NB = fine query tiles per wave (1 or 2), NW = waves; a workgroup owns NW * NB consecutive tiles, all siblings.  GW = waves
 // whose tiles make up a block of 32 or 64 queries and share a level-0 list (0: B = 16; 1: one wave holds the whole block).
 // Three waves per SIMD leave two tiles at d = 64 the registers they need (four spill: 572 against 477 us at 65536 tokens in
-// blocks of 64; two: 480).
+// blocks of 64; two: 480; with rows straight into LDS 294 against 249 at 65536 tokens in blocks of 16).
 template <int D, int NB, int NW, int GW>
 __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 64 ? (NB == 2 ? 3 : 4) : 2)))
 dq_shared_kernel(ListArgs args, const uint16_t *__restrict__ Q, const uint16_t *__restrict__ O,
                  const uint16_t *__restrict__ dO, const float *__restrict__ LSE, float *__restrict__ Dsum,
                  uint16_t *__restrict__ dQ, int64_t N, FastDiv groups) {
-    constexpr int KS = D / 32, NT = D / 16, STRIDE = D * 2 + 32, PARTS = D / 8, TILE = 32 * STRIDE;
-    constexpr int NTHR = 64 * NW, RND = (2 * 32 * PARTS) / NTHR, VCH = D / 16, KPU = 64 / PARTS;
-    // Phase B: per wave a K tile (row-wise and transposed reads) and a V tile (row-wise reads only; 16 bytes of
-    // padding keep it smaller).  Phase A's two double-buffered [K | V] tiles live in the first 4 TILE bytes of the
-    // same memory; a workgroup barrier separates the phases.
-    constexpr int VSTRIDE = D * 2 + 16, VTILE = 32 * VSTRIDE;
-    __shared__ __attribute__((aligned(16))) char lds[NW * (TILE + VTILE)];
-    static_assert(4 * TILE <= NW * (TILE + VTILE), "phase A's buffers must fit");
-    auto sh = [&](int buf, int which) { return lds + (buf * 2 + which) * TILE; };
+    constexpr int KS = D / 32, NT = D / 16, ROWB = 2 * D, HALF = 16 * ROWB, TILE = 2 * HALF;   // 16 rows, 32 rows
+    constexpr int CPH = HALF / 1024;                    // load_lds steps of 16 rows
+    constexpr int CPW = 4 * CPH / NW;                   // of a [K | V] tile that the workgroup shares, per wave
+    constexpr int RING = 4, NBUF = GW > 1 ? 2 : 1;      // phase A's tiles; phase B's tiles per group of waves
+    constexpr int OWN = (GW > 0 ? NW / GW : NW) * NBUF;
+    __shared__ __attribute__((aligned(16))) char lds[(OWN > RING ? OWN : RING) * 2 * TILE];
 
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int i16 = lane & 15, g = lane >> 4;
     const int64_t nblk = N >> 4;                                      // query tiles per head
     const unsigned wg = xcd_contiguous32(blockIdx.x, gridDim.x);
@@ -54,6 +48,8 @@ dq_shared_kernel(ListArgs args, const uint16_t *__restrict__ Q, const uint16_t *
     (void)args;                                                       // read through the pointer: fields of a level by scalar loads
     const list_args_ptr t = kernel_list_args();
     const float sc2 = t->scale * kLog2e;
+    const TileOffsets<D> o = tile_offsets<D>(lane);
+    const RowSource<D> src(lane);
 
     bf16x8 qop[NB][KS], gop[NB][KS];
     f32x4 acc[NB][NT];
@@ -108,19 +104,21 @@ dq_shared_kernel(ListArgs args, const uint16_t *__restrict__ Q, const uint16_t *
     };
     using B0 = std::integral_constant<int, 0>;
     using B1 = std::integral_constant<int, 1>;
-    // Scores, dP - D and dQ^T += K^T dS^T of query tiles b0 .. b0 + n - 1 for one tile of 32 staged keys (V rows VS bytes apart):
-    // every LDS read serves all of them.
-    auto tile = [&](auto first, auto count, const char *kt, const char *vt, auto vstride, int c0, int c1, float w0, float w1) {
-        constexpr int b0 = decltype(first)::value, n = decltype(count)::value, VS = decltype(vstride)::value;
+    // Scores, dP - D and dQ^T += K^T dS^T of query tiles first .. first + count - 1 for one tile of 32 keys in LDS: every read
+    // serves all of them.  early: K's transposed operands are read before the scores are worked on, and `have_read` is called when
+    // LDS holds nothing more of the tile that is wanted.
+    auto tile = [&](auto first, auto count, auto early, const char *kt, const char *vt, int c0, int c1, float w0, float w1, auto have_read) {
+        constexpr int b0 = decltype(first)::value, n = decltype(count)::value;
+        constexpr bool E = decltype(early)::value;
         f32x4 s[n][2], dp[n][2];
+        bf16x8 ktr[E ? NT : 1];
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-            const char *krow = kt + (h * 16 + i16) * STRIDE + g * 16, *vrow = vt + (h * 16 + i16) * VS + g * 16;
 #pragma unroll
             for (int b = 0; b < n; ++b) { s[b][h] = f32x4{0.f, 0.f, 0.f, 0.f}; dp[b][h] = ndelta[b0 + b]; }
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) {
-                const bf16x8 k = *reinterpret_cast<const bf16x8 *>(krow + ks * 64), v = *reinterpret_cast<const bf16x8 *>(vrow + ks * 64);
+                const bf16x8 k = ld_bf16x8(kt + h * HALF + o.row[ks]), v = ld_bf16x8(vt + h * HALF + o.row[ks]);
 #pragma unroll
                 for (int b = 0; b < n; ++b) {
                     s[b][h] = mfma16(k, qop[b0 + b][ks], s[b][h]);
@@ -128,21 +126,26 @@ dq_shared_kernel(ListArgs args, const uint16_t *__restrict__ Q, const uint16_t *
                 }
             }
         }
+        if constexpr (E) {
+#pragma unroll
+            for (int x = 0; x < NT; ++x) ktr[x] = lds_tr_pair(kt + o.tr[x], kt + HALF + o.tr[x]);
+            have_read();
+        }
         bf16x8 ds[n];
         ds[0] = ds_of(first, s[0][0], s[0][1], dp[0][0], dp[0][1], c0, c1, w0, w1);
         if constexpr (n > 1) ds[n - 1] = ds_of(B1{}, s[n - 1][0], s[n - 1][1], dp[n - 1][0], dp[n - 1][1], c0, c1, w0, w1);
-        const char *base = kt + (4 * g + (i16 >> 2)) * STRIDE + (i16 & 3) * 8;
 #pragma unroll
         for (int x = 0; x < NT; ++x) {
-            const bf16x8 ktr = lds_tr_pair(base + x * 32, base + 16 * STRIDE + x * 32);
+            const bf16x8 k = E ? ktr[E ? x : 0] : lds_tr_pair(kt + o.tr[x], kt + HALF + o.tr[x]);
 #pragma unroll
-            for (int b = 0; b < n; ++b) acc[b0 + b][x] = mfma16(ktr, ds[b], acc[b0 + b][x]);
+            for (int b = 0; b < n; ++b) acc[b0 + b][x] = mfma16(k, ds[b], acc[b0 + b][x]);
         }
     };
     using One = std::integral_constant<int, 1>;
     using All = std::integral_constant<int, NB>;
-    using StrideA = std::integral_constant<int, STRIDE>;
-    using StrideB = std::integral_constant<int, VSTRIDE>;
+    using Early = std::true_type;
+    using Late = std::false_type;
+    auto nothing = []() {};
 
     // The level-0 lists of this wave's NB query blocks, fetched now so that phase B does not wait for them:
     // lane LL b + j holds the first token of 16-token tile j of query tile b's list (as in the forward kernel).
@@ -159,148 +162,117 @@ dq_shared_kernel(ListArgs args, const uint16_t *__restrict__ Q, const uint16_t *
 
     // ------------------------------------------------------------------ phase A: shared coarse levels
     const int nbc = t->lev[t->nlev - 1].end - nb0;                    // coarse tiles of the list
+    const unsigned lds0 = lds_address(lds);
     if (nbc > 0) {
-        CoarseTable ctab;
+        CoarseTable ctab;                                              // lane j: coarse block 64 * chunk + j, of the tile issued last
         ctab.fill<D>(t, bh, (unsigned)blk0, 0, lane);
-        // Staging round r of this wave: 64 consecutive 16-byte chunks of the [K | V] tile, i.e. 64 / PARTS key rows of
-        // one half of K or of V, the same choice for the whole wave (one round: the first half of the waves stages K, the
-        // other V; more: the first half of the rounds stages K).
-        u32x4 sreg[RND];
-        int s_half[RND];
-        unsigned s_off[RND];
-#pragma unroll
-        for (int r = 0; r < RND; ++r) {
-            const int key0 = ((64 * wave + NTHR * r) % (32 * PARTS)) / PARTS;   // the wave's first key row in round r
-            s_half[r] = key0 >> 4;
-            s_off[r] = (unsigned)((((key0 & 15) + lane / PARTS) * D + (lane % PARTS) * 8) * 2);
-        }
-        const bool v_wave = RND == 1 && wave >= NW / 2;
-        uint64_t sptr = v_wave ? ctab.vptr : ctab.kptr;               // d = 64: the tensor this wave stages
+        const bool v_wave = wave >= NW / 2;                           // this wave brings in V rows
+        uint64_t rows = v_wave ? +ctab.vptr : +ctab.kptr;
+        float w_now = ctab.bias2, w_next = 0.f;                       // the weights, of the tile worked on
+        int c0 = 16, c1 = 16;                                         // rows of the last tile's halves
         const int ntile = (nbc + 1) >> 1;                             // only the last tile may be ragged or lack its second half
-        auto load_shared = [&](int u) {
+        // this wave's share of a tile: load_lds steps of one half of K or of V
+        const int part = wave * CPW / CPH, sub = wave * CPW % CPH, half = part & 1;
+        auto issue = [&](int u) {                                     // coarse blocks 2u, 2u + 1
             if (u > 0 && ((2 * u) & 63) == 0) {
                 ctab.fill<D>(t, bh, (unsigned)blk0, (2 * u) >> 6, lane);
-                sptr = v_wave ? ctab.vptr : ctab.kptr;
+                rows = v_wave ? +ctab.vptr : +ctab.kptr;
+                w_next = ctab.bias2;
             }
-#pragma unroll
-            for (int r = 0; r < RND; ++r) {
-                const bool have = 2 * u + s_half[r] < nbc;
-                const int j = (have ? 2 * u + s_half[r] : 2 * u) & 63;
-                const char *src = RND == 1 ? BlockTable::rl_ptr(sptr, j) : (r < RND / 2 ? ctab.K(j) : ctab.V(j));
-                unsigned off = s_off[r];
-                if (u + 1 == ntile) {
-                    const int cnt = have ? ctab.count(j) : 0;
-                    if (cnt < 16) {                                   // ragged or absent block: re-read its last valid row
-                        const int row = min((int)(off / (D * 2)), max(cnt, 1) - 1);
-                        off = (unsigned)(row * D * 2) + off % (D * 2);
-                    }
-                }
-                sreg[r] = gload16b(src, off);
-            }
-        };
-        auto store_shared = [&](int buf) {
-#pragma unroll
-            for (int r = 0; r < RND; ++r) {
-                const int cc = tid + NTHR * r, which = cc / (32 * PARTS), c = cc % (32 * PARTS);
-                *reinterpret_cast<u32x4 *>(sh(buf, which) + (c / PARTS) * STRIDE + (c % PARTS) * 16) = sreg[r];
-            }
-        };
-        load_shared(0);
-        for (int u = 0; u < ntile; ++u) {
-            const int buf = u & 1;
-            store_shared(buf);
-            int cnt[2] = {16, 16};
-            float bias2[2] = {ctab.bias((2 * u) & 63), ctab.bias((2 * u + 1) & 63)};
+            const int j = (2 * u + half < nbc ? 2 * u + half : 2 * u) & 63;
+            const uint64_t base = reinterpret_cast<uint64_t>(BlockTable::rl_ptr(rows, j));
+            const unsigned dst = lds0 + (u % RING) * (2 * TILE) + wave * CPW * 1024;
             if (u + 1 == ntile) {
-                cnt[0] = ctab.count((2 * u) & 63);
-                if (2 * u + 1 < nbc) cnt[1] = ctab.count((2 * u + 1) & 63);
-                else bias2[1] = -INFINITY;                            // an absent half: P = 0
+                const int n0 = ctab.count((2 * u) & 63), n1 = 2 * u + 1 < nbc ? ctab.count((2 * u + 1) & 63) : 16;
+                const int cnt = ctab.count(j);
+                c0 = n0;
+                c1 = n1;
+                if (cnt < 16) {                                       // rows past a ragged end repeat the last one
+#pragma unroll
+                    for (int x = 0; x < CPW; ++x) {
+                        const int r = (sub + x) * (512 / D) + lane / (D / 8);
+                        const unsigned v = (unsigned)(min(r, cnt - 1) * ROWB + (((lane % (D / 8)) ^ swz_key<D>(r)) << 4));
+                        load_lds<1>(base, v, v, dst + x * 1024);
+                    }
+                    return;
+                }
             }
-            __syncthreads();
-            if (u + 1 < ntile) load_shared(u + 1);
-            tile(B0{}, All{}, sh(buf, 0), sh(buf, 1), StrideA{}, cnt[0], cnt[1], bias2[0], bias2[1]);
+            load_lds<CPW>(base + sub * 1024, src.v0, src.v1, dst);
+        };
+        for (int u = 0; u < RING - 1 && u < ntile; ++u) issue(u);
+        for (int u = 0; u < ntile; ++u) {
+            // tile u is there, and tile u - 1, whose place tile u + 3 takes, has been read by every wave
+            if (u + 2 < ntile) vm_wait_barrier<2 * CPW>();
+            else vm_wait_barrier<0>();
+            if (u + RING - 1 < ntile) issue(u + RING - 1);
+            if (u > 0 && ((2 * u) & 63) == 0) w_now = w_next;
+            auto weight = [&](int j) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w_now), j & 63)); };
+            const bool last = u + 1 == ntile;
+            const char *kt = lds + (u % RING) * (2 * TILE);
+            // an absent half: P = 0
+            tile(B0{}, All{}, Late{}, kt, kt + TILE, last ? c0 : 16, last ? c1 : 16, weight(2 * u),
+                 2 * u + 1 < nbc ? weight(2 * u + 1) : -INFINITY, nothing);
         }
+        vm_wait_barrier<0>();                                         // phase A's buffers are free
     }
 
-    if constexpr (GW > 0) {
-        // -------------------------------------------------------------- phase B, blocks of 32 or 64 tokens
-        // The GW waves that hold the B queries of a block stage the tiles of their one level-0 list together, double-buffered
-        // per group, as in the forward kernel (16 heads x 65536 tokens in blocks of 64, K = 8: 677 -> 554 us).
-        constexpr int R = 2 * 32 * PARTS / (64 * GW), BUF = TILE + VTILE, NBUF = GW > 1 ? 2 : 1;
-        static_assert((NW / GW) * NBUF * BUF <= NW * (TILE + VTILE), "the groups' buffers must fit");
-        __syncthreads();                                              // phase A's buffers are free
+    // ------------------------------------------------------------------ phase B: level 0
+    // half h of the K (or V, T0) rows of tile j0 of the list that begins at lane l0, by the wave alone
+    auto load_half = [&](const void *T0, int l0, int j0, int h, unsigned dst) {
+        const int j = j0 + h < nb0 ? j0 + h : j0;                     // an absent second half re-reads the first
+        const int64_t row = bh * N + __builtin_amdgcn_readlane(tok0, l0 + j);
+        load_lds<CPH>(reinterpret_cast<uint64_t>(T0) + (uint64_t)row * ROWB, src.v0, src.v1, dst + h * HALF);
+    };
+    const void *K0 = t->lev[0].K, *V0 = t->lev[0].V;
+    if constexpr (GW > 1) {
+        // Blocks of 32 or 64 tokens: the B queries of a block use one level-0 list, whose tiles the GW waves that hold them bring in
+        // together, double-buffered.  A list is whole blocks of B >= 32 tokens: no half of a tile is ever absent.
         const int wg_in = wave % GW;
-        char *base = lds + (wave / GW) * (NBUF * BUF);
-        const int64_t head = bh * N;
-        const char *K0 = static_cast<const char *>(t->lev[0].K), *V0 = static_cast<const char *>(t->lev[0].V);
-        u32x4 sreg[R];
-        auto load_group = [&](int u) {                                // 64 chunks a round: rows of one half of K or of V
+        const char *buf = lds + (wave / GW) * (2 * 2 * TILE);
+        const unsigned dst = lds0 + (wave / GW) * (2 * 2 * TILE);
+        auto issue = [&](int u) {
 #pragma unroll
-            for (int r = 0; r < R; ++r) {
-                const int c0 = 64 * (wg_in + GW * r), key0 = (c0 % (32 * PARTS)) / PARTS;
-                const char *src = c0 >= 32 * PARTS ? V0 : K0;
-                const int64_t row = head + __builtin_amdgcn_readlane(tok0, 2 * u + (key0 >> 4));
-                sreg[r] = gload16b(src + row * (D * 2), (unsigned)((((key0 & 15) + lane / PARTS) * D + (lane % PARTS) * 8) * 2));
+            for (int x = 0; x < 4 / GW; ++x) {
+                const int part = wg_in * (4 / GW) + x;                // K, K, V, V: its halves
+                load_half(part < 2 ? K0 : V0, 0, 2 * u, part & 1, dst + (u & 1) * (2 * TILE) + (part >> 1) * TILE);
             }
         };
-        load_group(0);
+        issue(0);
         for (int u = 0; 2 * u < nb0; ++u) {
-            char *buf = base + (u % NBUF) * BUF;
-            if constexpr (GW == 1) __builtin_amdgcn_wave_barrier();
-#pragma unroll
-            for (int r = 0; r < R; ++r) {
-                const int c0 = 64 * (wg_in + GW * r), row = (c0 % (32 * PARTS)) / PARTS + lane / PARTS;
-                char *dst = c0 >= 32 * PARTS ? buf + TILE + row * VSTRIDE : buf + row * STRIDE;
-                *reinterpret_cast<u32x4 *>(dst + (lane % PARTS) * 16) = sreg[r];
-            }
-            if constexpr (GW > 1) __syncthreads();
-            else __builtin_amdgcn_wave_barrier();
-            if (2 * u + 2 < nb0) load_group(u + 1);
-            tile(B0{}, All{}, buf, buf + TILE, StrideB{}, 16, 16, 0.f, 0.f);
+            vm_wait_barrier<0>();
+            if (2 * u + 2 < nb0) issue(u + 1);
+            const char *kt = buf + (u & 1) * (2 * TILE);
+            tile(B0{}, All{}, Late{}, kt, kt + TILE, 16, 16, 0.f, 0.f, nothing);
         }
     } else {
-    // ------------------------------------------------------------------ phase B: own level-0 blocks
-    // K and V rows are fetched with 8 consecutive lanes per 128-byte row (whole cache lines per instruction: loading
-    // the MFMA operand layout straight from memory, 16 rows x half a line per instruction, caps the gather rate at a
-    // third of what the L2 delivers) and reach the operand layouts through the wave's own LDS tiles.
-    __syncthreads();                                                  // phase A's buffers are free
-    char *my = lds + wave * (TILE + VTILE), *my_v = my + TILE;
-    const char *K0 = static_cast<const char *>(t->lev[0].K), *V0 = static_cast<const char *>(t->lev[0].V);
-    unsigned voff[VCH];
-#pragma unroll
-    for (int u = 0; u < VCH; ++u) voff[u] = (unsigned)((((lane / PARTS + KPU * u) & 15) * D + (lane % PARTS) * 8) * 2);
-
-    auto phase_b = [&](auto bsel) {
-        constexpr int b = decltype(bsel)::value;
-        u32x4 kreg[VCH], vreg[VCH];
-        auto load_tile = [&](int j0) {
-            int64_t off[2];
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const int j = (j0 + h < nb0) ? j0 + h : j0;           // an absent second half re-reads the first
-                off[h] = (bh * N + __builtin_amdgcn_readlane(tok0, LL * b + j)) * (D * 2);
-            }
-#pragma unroll
-            for (int u = 0; u < VCH; ++u) {
-                kreg[u] = gload16b(K0 + off[(KPU * u) >> 4], voff[u]);
-                vreg[u] = gload16b(V0 + off[(KPU * u) >> 4], voff[u]);
+        // Every wave alone: the tiles of its query tiles (GW = 1: of all of them at once) form one stream.  The next tile's rows are
+        // asked for as soon as the current one's have been read, so they fly during all of its math.
+        const char *my = lds + wave * (2 * TILE);
+        const unsigned dst = lds0 + wave * (2 * TILE);
+        auto load_tile = [&](int l0, int j0) {
+            load_half(K0, l0, j0, 0, dst);
+            load_half(K0, l0, j0, 1, dst);
+            load_half(V0, l0, j0, 0, dst + TILE);
+            load_half(V0, l0, j0, 1, dst + TILE);
+        };
+        auto walk = [&](auto first, auto count, bool end) {
+            const int l0 = LL * decltype(first)::value;
+            for (int j0 = 0; j0 < nb0; j0 += 2) {
+                const bool here = j0 + 2 < nb0;
+                vm_wait<0>();
+                // level-0 blocks are always full; an absent second half has weight 0
+                tile(first, count, Early{}, my, my + TILE, 16, 16, 0.f, j0 + 1 < nb0 ? 0.f : -INFINITY, [&]() {
+                    if (here) load_tile(l0, j0 + 2);
+                    else if (!end) load_tile(l0 + LL, 0);
+                });
             }
         };
-        load_tile(0);
-        for (int j0 = 0; j0 < nb0; j0 += 2) {
-            __builtin_amdgcn_wave_barrier();
-#pragma unroll
-            for (int u = 0; u < VCH; ++u) {
-                *reinterpret_cast<u32x4 *>(my + (lane / PARTS + KPU * u) * STRIDE + (lane % PARTS) * 16) = kreg[u];
-                *reinterpret_cast<u32x4 *>(my_v + (lane / PARTS + KPU * u) * VSTRIDE + (lane % PARTS) * 16) = vreg[u];
-            }
-            __builtin_amdgcn_wave_barrier();
-            if (j0 + 2 < nb0) load_tile(j0 + 2);                      // the registers are free again
-            tile(bsel, One{}, my, my_v, StrideB{}, 16, 16, 0.f, j0 + 1 < nb0 ? 0.f : -INFINITY);
+        load_tile(0, 0);
+        if constexpr (GW == 1) walk(B0{}, All{}, true);
+        else {
+            walk(B0{}, One{}, NB == 1);
+            if constexpr (NB > 1) walk(B1{}, One{}, true);
         }
-    };
-    phase_b(B0{});
-    if constexpr (NB > 1) phase_b(B1{});
     }
 
 #pragma unroll

@@ -108,15 +108,14 @@ __device__ __forceinline__ T pick(const T (&arr)[n], int idx) {
     return v;
 }
 
-// Rows of D bf16 kept unpadded in LDS, the 16-byte chunk c of row r stored at chunk c ^ swz_key(r).
-// d = 64 (128-byte rows, half a row of the 64 LDS banks): the key gives 16 consecutive rows 8 distinct values per
-// row parity, so the row-wise 16-byte reads of 16 lanes hit 16 different bank groups.  (A key that also spreads the
-// transposed 8-byte reads of a half wave was timed: those reads did not get faster, the row-wise ones got slower.)
-// d = 128 (256-byte rows, all banks): the key is a bijection of 16 consecutive rows onto the 16 chunks, and its
-// upper three bits differ among the 8 rows a half wave reads transposed.
-// d = 32: 4 rows to a pass over the banks, so the key changes every 4 rows; d = 16 (tile kernels only): none.
+// Rows of D bf16 kept unpadded in LDS, the 16-byte chunk c of row r stored at chunk c ^ swz_key(r).  The LDS serves a row-wise
+// 16-byte read (lane 16 g + i: row i, chunk g + const) in four passes of 16 lanes over its 64 banks, lanes 0-3, 12-15 and 20-27 first:
+// all 16 rows, the middle eight at the next chunk; a transposed 8-byte read in two passes of 32 lanes: 32 bytes each of 8 rows.
+// Both are free of conflicts if the key spreads 8 consecutive rows over the 32-byte pieces of the 256 bytes the banks span and
+// leaves the lowest bit alone: d = 64 (two rows span the banks) 4 keys, one per row pair, d = 128 8 keys, d = 32 2.  Measured per read
+// of a wave: 4.6 cycles row-wise, 2.5 transposed; a key per row instead ((r >> 1) & 7) 4.6 and 4.9, at d = 128 8.6 and 2.5.
 template <int D> __device__ __forceinline__ int swz_key(int r) {
-    return D == 64 ? ((r >> 1) & 7) : D == 128 ? (((r & 7) << 1) | ((r >> 3) & 1)) : D == 32 ? ((r >> 2) & 3) : 0;
+    return D == 64 ? ((r >> 1) & 3) << 1 : D == 128 ? (r & 7) << 1 : D == 32 ? ((r >> 2) & 1) << 1 : 0;
 }
 
 // Per-lane byte offsets of the MFMA operand reads inside a 16-row slice of such unpadded, swizzled rows (2 D bytes
@@ -137,6 +136,41 @@ template <int D> __device__ __forceinline__ TileOffsets<D> tile_offsets(int lane
         o.tr[n] = (4 * g + (i16 >> 2)) * ROWB + (((2 * n + ((i16 >> 1) & 1)) ^ key_tr) << 4) + ((i16 & 1) << 3);
     return o;
 }
+
+// Memory straight into LDS: every lane fetches 16 bytes at base + v, the wave's 1024 bytes land in lane order at `lds`; N times, each time
+// 1024 bytes further on both sides, v0 and v1 taken in turn.  A tile brought in this way costs no registers and next to none of the
+// LDS's time: a wave that fetches 8 KB and reads them 2 or 4 times, as the tiles do, took 1.4 to 1.6 times as long through registers
+// and LDS writes (ds_write_b128: 13.5 cycles of the CU per 1024 bytes, a read 4.6).  Rows are swizzled by choosing each lane's source
+// chunk (row_source).  The compiler does not know of these loads (it would wait for all of them at every LDS read): vm_wait before the
+// data is read, and nothing may still be reading what they overwrite, which lgkmcnt(0) sees to for the wave's own reads.
+template <int N> __device__ __forceinline__ void load_lds(uint64_t base, unsigned v0, unsigned v1, unsigned lds) {
+    static_assert(N == 1 || N == 2 || N == 4, "");
+    if constexpr (N == 1)
+        asm volatile("s_mov_b32 m0, %0\n\ts_waitcnt lgkmcnt(0)\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(v0), "s"(base) : "memory", "m0");
+    else if constexpr (N == 2)
+        asm volatile("s_mov_b32 m0, %0\n\ts_waitcnt lgkmcnt(0)\n\tglobal_load_lds_dwordx4 %1, %2\n\tglobal_load_lds_dwordx4 %3, %2 offset:1024"
+                     ::"s"(lds), "v"(v0), "s"(base), "v"(v1) : "memory", "m0");
+    else
+        asm volatile("s_mov_b32 m0, %0\n\ts_waitcnt lgkmcnt(0)\n\tglobal_load_lds_dwordx4 %1, %2\n\tglobal_load_lds_dwordx4 %3, %2 offset:1024\n\t"
+                     "global_load_lds_dwordx4 %1, %2 offset:2048\n\tglobal_load_lds_dwordx4 %3, %2 offset:3072"
+                     ::"s"(lds), "v"(v0), "s"(base), "v"(v1) : "memory", "m0");
+}
+// Rows of D bf16 brought into LDS as swz_key wants them, 1024 bytes (512 / D rows) at a time: what a lane adds to the address of the
+// first of them.  Of two 1024 bytes of a 16-row slice in turn (v0, v1): at d = 128 the second four rows have other keys.
+template <int D> struct RowSource {
+    unsigned v0, v1;
+    __device__ __forceinline__ explicit RowSource(int lane) {
+        constexpr int PARTS = D / 8, KPU = 64 / PARTS;
+        const int r = lane / PARTS, c = lane % PARTS;
+        v0 = (unsigned)(r * 2 * D + ((c ^ swz_key<D>(r)) << 4));
+        v1 = (unsigned)(r * 2 * D + ((c ^ swz_key<D>(r + KPU)) << 4));
+    }
+};
+// at most N of the wave's loads are still on their way (they complete in order)
+template <int N> __device__ __forceinline__ void vm_wait() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
+// the same, and every wave of the workgroup has come this far and read what it wanted from LDS
+template <int N> __device__ __forceinline__ void vm_wait_barrier() { asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory"); }
+__device__ __forceinline__ unsigned lds_address(const void *p) { return (unsigned)(uintptr_t)(const LLSA_LDS char *)p; }
 
 // Workgroup id -> work item so that the workgroups one XCD receives (ids congruent modulo 8) cover a
 // contiguous range of work items: neighbouring query blocks gather overlapping keys, which then stay in
