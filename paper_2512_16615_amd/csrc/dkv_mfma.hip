@@ -23,25 +23,29 @@
 namespace llsa {
 
 template <int D> struct DkvShape {
-    static constexpr int KS = D / 32, NT = D / 16, STRIDE = D * 2 + 32, VCH = D / 16, PARTS = D / 8, KPU = 64 / PARTS;
-    static constexpr int TILE = 32 * STRIDE;
+    static constexpr int KS = D / 32, NT = D / 16, HALF = 32 * D, TILE = 2 * HALF;   // bytes of 16 and of 32 rows
+    static constexpr int CPH = HALF / 1024;                 // load_lds steps of 16 rows
+    static constexpr int WAVE = 2 * TILE + 256;             // LDS of a wave: Q rows | dO rows | LSE [32], D [32]
 };
 
 // Tiles t_first, t_first + t_step, ... < t_end of one key block's query list, accumulated into accK / accV.
 // lst: the block's listed query-block rows (null when dense); groups: 16-query groups in the list.
+// Rows go from memory straight into the wave's LDS.  Every operand of a tile is read before its exponentials, so that the next
+// tile's rows, for which there is only this one place, fly during the rest.  FINE_FIG
 template <int D>
 __device__ __forceinline__ void dkv_tile_loop(const DkvArgs &a, int64_t bh, const int32_t *lst, int64_t groups,
                                               int64_t t_first, int64_t t_step, int64_t t_end,
                                               const bf16x8 (&kop)[D / 32], const bf16x8 (&vop)[D / 32],
-                                              f32x4 (&accK)[D / 16], f32x4 (&accV)[D / 16], char *qt, char *gt,
-                                              int lane) {
+                                              f32x4 (&accK)[D / 16], f32x4 (&accV)[D / 16], char *qt, int lane) {
     using S = DkvShape<D>;
     const int i16 = lane & 15, g = lane >> 4;
     const int64_t span_mask = ((int64_t)1 << a.span_shift) - 1;
     const int64_t entries = groups >> a.span_shift;
-    unsigned voff[S::VCH];
-#pragma unroll
-    for (int u = 0; u < S::VCH; ++u) voff[u] = (unsigned)((((lane / S::PARTS + S::KPU * u) & 15) * D + (lane % S::PARTS) * 8) * 2);
+    const TileOffsets<D> o = tile_offsets<D>(lane);
+    const RowSource<D> src(lane);
+    char *gt = qt + S::TILE;
+    float *st = reinterpret_cast<float *>(gt + S::TILE);
+    const unsigned dst = lds_address(qt);
 
     // the list entries, 64 at a time in one register (lane e: entry 64 * chunk + e)
     int ecache = 0;
@@ -55,12 +59,9 @@ __device__ __forceinline__ void dkv_tile_loop(const DkvArgs &a, int64_t bh, cons
         return __builtin_amdgcn_readlane(ecache, (int)(e & 63));
     };
 
-    u32x4 qreg[S::VCH], greg[S::VCH];
     float stat = 0.f;                                       // lane x: LSE (x < 32) or D (x >= 32) of tile query x % 32
-    int valid1 = 0;                                         // does the tile have its second group?
-    float *st = reinterpret_cast<float *>(gt + S::TILE);    // 64 floats behind the two tiles
+    int valid1 = 0;                                         // does the tile on its way have its second group?
     auto load_tile = [&](int64_t tile) {
-        const char *qp[2], *gp[2];
         valid1 = 2 * tile + 1 < groups;
         int64_t row0[2];
 #pragma unroll
@@ -68,69 +69,62 @@ __device__ __forceinline__ void dkv_tile_loop(const DkvArgs &a, int64_t bh, cons
             const int64_t gi = (h == 0 || valid1) ? 2 * tile + h : 2 * tile;   // an absent group re-reads the first
             const int64_t q0 = a.dense ? gi * 16 : ((entry(gi >> a.span_shift) << a.span_shift) + (gi & span_mask)) * 16;
             row0[h] = bh * a.N + q0;
-            qp[h] = reinterpret_cast<const char *>(a.Q + row0[h] * D);
-            gp[h] = reinterpret_cast<const char *>(a.dO + row0[h] * D);
         }
         stat = ((lane & 32) ? a.Dsum : a.LSE)[((lane & 16) ? row0[1] : row0[0]) + i16];
 #pragma unroll
-        for (int u = 0; u < S::VCH; ++u) {
-            const int h = (S::KPU * u) >> 4;
-            qreg[u] = *reinterpret_cast<const u32x4 *>(qp[h] + voff[u]);
-            greg[u] = *reinterpret_cast<const u32x4 *>(gp[h] + voff[u]);
+        for (int h = 0; h < 2; ++h) {
+            load_lds<S::CPH>(reinterpret_cast<uint64_t>(a.Q + row0[h] * D), src.v0, src.v1, dst + h * S::HALF);
+            load_lds<S::CPH>(reinterpret_cast<uint64_t>(a.dO + row0[h] * D), src.v0, src.v1, dst + S::TILE + h * S::HALF);
         }
     };
 
     int64_t tile = t_first;
     if (tile < t_end) load_tile(tile);
     while (tile < t_end) {
-        __builtin_amdgcn_wave_barrier();                    // one wave's LDS operations stay in order
-#pragma unroll
-        for (int u = 0; u < S::VCH; ++u) {
-            const int q = lane / S::PARTS + S::KPU * u, part = lane % S::PARTS;
-            *reinterpret_cast<u32x4 *>(qt + q * S::STRIDE + part * 16) = qreg[u];
-            *reinterpret_cast<u32x4 *>(gt + q * S::STRIDE + part * 16) = greg[u];
-        }
-        st[lane] = stat;
-        __builtin_amdgcn_wave_barrier();
-
-        f32x4 s[2], dp[2];
+        st[lane] = stat;                                    // one wave's LDS operations stay in order
+        vm_wait<0>();
+        f32x4 s[2], dp[2], l2[2], dl[2];
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             s[h] = f32x4{0.f, 0.f, 0.f, 0.f};
             dp[h] = f32x4{0.f, 0.f, 0.f, 0.f};
-            const char *qrow = qt + (h * 16 + i16) * S::STRIDE + g * 16, *grow = gt + (h * 16 + i16) * S::STRIDE + g * 16;
 #pragma unroll
             for (int ks = 0; ks < S::KS; ++ks) {
-                s[h] = mfma16(*reinterpret_cast<const bf16x8 *>(qrow + ks * 64), kop[ks], s[h]);
-                dp[h] = mfma16(*reinterpret_cast<const bf16x8 *>(grow + ks * 64), vop[ks], dp[h]);
+                s[h] = mfma16(ld_bf16x8(qt + h * S::HALF + o.row[ks]), kop[ks], s[h]);
+                dp[h] = mfma16(ld_bf16x8(gt + h * S::HALF + o.row[ks]), vop[ks], dp[h]);
             }
         }
-        // this lane's 4 queries per half: rows 4g .. 4g+3
-        const f32x4 l2[2] = {*reinterpret_cast<const f32x4 *>(st + 4 * g), *reinterpret_cast<const f32x4 *>(st + 16 + 4 * g)};
-        const f32x4 dl[2] = {*reinterpret_cast<const f32x4 *>(st + 32 + 4 * g),
-                             *reinterpret_cast<const f32x4 *>(st + 48 + 4 * g)};
+        bf16x8 tg[S::NT], tq[S::NT];
+#pragma unroll
+        for (int n = 0; n < S::NT; ++n) {
+            tg[n] = lds_tr_pair(gt + o.tr[n], gt + S::HALF + o.tr[n]);
+            tq[n] = lds_tr_pair(qt + o.tr[n], qt + S::HALF + o.tr[n]);
+        }
         const int v1 = valid1;
         const int64_t next = tile + t_step;
         if (next < t_end) load_tile(next);
 
 #pragma unroll
-        for (int h = 0; h < 2; ++h)
+        for (int h = 0; h < 2; ++h) {
+            // this lane's 4 queries: rows 4g .. 4g+3 (the next tile's are written at the head of the loop)
+            l2[h] = *reinterpret_cast<const f32x4 *>(st + 16 * h + 4 * g);
+            dl[h] = *reinterpret_cast<const f32x4 *>(st + 32 + 16 * h + 4 * g);
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const float p = __builtin_amdgcn_exp2f(fmaf(s[h][r], a.sc2, fmaf(l2[h][r], -kLog2e, a.bias2)));
                 s[h][r] = p;
                 dp[h][r] = p * (dp[h][r] - dl[h][r]);
             }
+        }
         if (!v1) {                                          // the list ends with a single group
             s[1] = f32x4{0.f, 0.f, 0.f, 0.f};
             dp[1] = f32x4{0.f, 0.f, 0.f, 0.f};
         }
         const bf16x8 pop = pack8(s[0], s[1]), dsop = pack8(dp[0], dp[1]);
-        const int boff = (4 * g + (i16 >> 2)) * S::STRIDE + (i16 & 3) * 8;
 #pragma unroll
         for (int n = 0; n < S::NT; ++n) {
-            accV[n] = mfma16(lds_tr_pair(gt + boff + n * 32, gt + boff + 16 * S::STRIDE + n * 32), pop, accV[n]);
-            accK[n] = mfma16(lds_tr_pair(qt + boff + n * 32, qt + boff + 16 * S::STRIDE + n * 32), dsop, accK[n]);
+            accV[n] = mfma16(tg[n], pop, accV[n]);
+            accK[n] = mfma16(tq[n], dsop, accK[n]);
         }
         tile = next;
     }
@@ -176,7 +170,7 @@ __device__ __forceinline__ void dkv_load_keys(const DkvArgs &a, int64_t row, int
 template <int D>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 64 ? 3 : 2))) dkv_coarse_kernel(DkvArgs a) {
     using S = DkvShape<D>;
-    __shared__ __attribute__((aligned(16))) char lds[4][2 * S::TILE + 256];   // per wave: Q tile | dO tile | LSE, D
+    __shared__ __attribute__((aligned(16))) char lds[4][S::WAVE];
     static_assert(4 * 2 * S::NT * 64 * 16 <= 4 * 2 * S::TILE, "reduction buffer must fit in the tile buffers");
 
     const int lane = threadIdx.x & 63;
@@ -207,7 +201,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 6
     f32x4 accK[S::NT], accV[S::NT];
 #pragma unroll
     for (int n = 0; n < S::NT; ++n) { accK[n] = f32x4{0.f, 0.f, 0.f, 0.f}; accV[n] = f32x4{0.f, 0.f, 0.f, 0.f}; }
-    dkv_tile_loop<D>(a, bh, lst, groups, t_beg + wave, 4, t_end, kop, vop, accK, accV, lds[wave], lds[wave] + S::TILE, lane);
+    dkv_tile_loop<D>(a, bh, lst, groups, t_beg + wave, 4, t_end, kop, vop, accK, accV, lds[wave], lane);
 
     dkv_reduce_waves<D>(reinterpret_cast<float *>(&lds[0][0]), wave, lane, accK, accV, [&](int slot, f32x4 sum) {
         const bool isV = slot >= S::NT;
@@ -227,7 +221,7 @@ constexpr int kSoloMax = 24;                                // longest list (16-
 template <int D>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 64 ? 3 : 2))) dkv_fine_kernel(DkvArgs a) {
     using S = DkvShape<D>;
-    __shared__ __attribute__((aligned(16))) char lds[4][2 * S::TILE + 256];
+    __shared__ __attribute__((aligned(16))) char lds[4][S::WAVE];
     __shared__ int len_sh[4];
     __shared__ __attribute__((aligned(16))) float par_sh[4][2 * D];   // per wave: the parent token's dK | dV
 
@@ -296,7 +290,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 6
             if (len > 0) {
                 dkv_load_keys<D>(a, bh * a.n_l + j * 16 + i16, lane, kop, vop);
                 dkv_tile_loop<D>(a, bh, a.Iq + bh * a.rows * a.Kl_cnt + beg, len, 0, 1, ((int64_t)len + 1) >> 1, kop, vop,
-                                 accK, accV, lds[wave], lds[wave] + S::TILE, lane);
+                                 accK, accV, lds[wave], lane);
             }
             par_publish();
 #pragma unroll
@@ -317,7 +311,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 6
         par_fetch(j);
         dkv_load_keys<D>(a, bh * a.n_l + j * 16 + i16, lane, kop, vop);
         dkv_tile_loop<D>(a, bh, a.Iq + bh * a.rows * a.Kl_cnt + beg, len, wave, 4, ((int64_t)len + 1) >> 1, kop, vop, accK,
-                         accV, lds[wave], lds[wave] + S::TILE, lane);
+                         accV, lds[wave], lane);
         par_publish();
         dkv_reduce_waves<D>(reinterpret_cast<float *>(&lds[0][0]), wave, lane, accK, accV,
                             [&](int slot, f32x4 sum) { emit(j, slot, sum); });

@@ -143,8 +143,12 @@ template <int D> __device__ __forceinline__ TileOffsets<D> tile_offsets(int lane
 // and LDS writes (ds_write_b128: 13.5 cycles of the CU per 1024 bytes, a read 4.6).  Rows are swizzled by choosing each lane's source
 // chunk (row_source).  The compiler does not know of these loads (it would wait for all of them at every LDS read): vm_wait before the
 // data is read, and nothing may still be reading what they overwrite, which lgkmcnt(0) sees to for the wave's own reads.
+// `base` and `lds` are the same in every lane.
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"         // m0 is on the clobber list so that nothing else is kept in it meanwhile
 template <int N> __device__ __forceinline__ void load_lds(uint64_t base, unsigned v0, unsigned v1, unsigned lds) {
     static_assert(N == 1 || N == 2 || N == 4, "");
+    base = (uint64_t)(unsigned)__builtin_amdgcn_readfirstlane((int)(base >> 32)) << 32 | (unsigned)__builtin_amdgcn_readfirstlane((int)base);
     if constexpr (N == 1)
         asm volatile("s_mov_b32 m0, %0\n\ts_waitcnt lgkmcnt(0)\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(v0), "s"(base) : "memory", "m0");
     else if constexpr (N == 2)
@@ -155,6 +159,7 @@ template <int N> __device__ __forceinline__ void load_lds(uint64_t base, unsigne
                      "global_load_lds_dwordx4 %1, %2 offset:2048\n\tglobal_load_lds_dwordx4 %3, %2 offset:3072"
                      ::"s"(lds), "v"(v0), "s"(base), "v"(v1) : "memory", "m0");
 }
+#pragma clang diagnostic pop
 // Rows of D bf16 brought into LDS as swz_key wants them, 1024 bytes (512 / D rows) at a time: what a lane adds to the address of the
 // first of them.  Of two 1024 bytes of a 16-row slice in turn (v0, v1): at d = 128 the second four rows have other keys.
 template <int D> struct RowSource {
