@@ -9,8 +9,8 @@
 // queries: a fp32 partial of 2 x 16 x d values.  Three kernels produce the partials:
 //   dkv_group_kernel: one R per workgroup; a wave takes NB list blocks at a time (d = 64: 4 waves x 2 blocks fed
 //     from one LDS read of each tile; d = 128: 8 waves x 1 block) of the levels it is given;
-//   dkv_chain_kernel: level 1 with at most 8 listed blocks.  The same tile loop, but a workgroup walks several
-//     consecutive R and a key block listed by a run of them keeps its sums in registers: one partial per run;
+//   dkv_chain_kernel: level 1 with at most 16 listed blocks.  The same tile loop, but a workgroup walks several
+//     neighbouring R and a key block listed by a run of them keeps its sums in registers: one partial per run;
 //   dkv_upper_kernel: levels >= 2 only.  The 16 level-1 blocks under one level-2 query block list the same
 //     key blocks at every level >= 2, so a workgroup of 8 waves walks G of them (G divides 16; the next one's
 //     rows are prefetched into registers) and keeps its accumulators in registers meanwhile: every wave owns
@@ -41,7 +41,7 @@ struct GroupArgs {
     int64_t N, NR;                                      // NR = level-1 query blocks per head
     int lev_end;                                        // levels below lev_end are processed (from 1, or from 2 in the upper kernel)
     int G;                                              // level-1 query blocks per workgroup (upper kernel)
-    int GC;                                             // level-1 query blocks a workgroup of the chain kernel walks
+    int GC, GS;                                         // level-1 query blocks a workgroup of the chain kernel walks, how far apart
     int nbs, nbd;                                       // upper kernel: listed blocks the waves own / shared dense block (0 or 1)
     int sparse_begin, do_dense;                         // upper kernel: first sparse block of this launch; does it take the dense one
     float sc2, scale;
@@ -143,24 +143,25 @@ __global__ void __launch_bounds__(64 * NW) dkv_group_kernel(LevelTable t, GroupA
         for (int u = 0; u < 8; ++u) group_tile<D, NB>(qs, gs, st, st + 256, u, o, blk, a.sc2, g);
 #pragma unroll
         for (int b = 0; b < NB; ++b)
-            if (jb + b < nbc) store_partial<D>(partial_ptr<D>(t, a, nlev, jb + b + c_begin, R), blk[b], a.scale, lane);
+            if (jb + b < nbc) store_partial(partial_ptr<D>(t, a, nlev, jb + b + c_begin, R), blk[b], a.scale, lane);
     }
 }
 
-// Level 1 alone, rows of I^(1) with at most NW * NB entries.  Neighbouring level-1 query blocks list mostly the same
+// Level 1 alone, rows of I^(1) with at most NW * NB * P entries.  Neighbouring level-1 query blocks list mostly the same
 // level-1 key blocks (for spatially smooth inputs a block stays listed over many consecutive rows), and a partial per
 // (query block, listed block) then carries the same key block's sums to memory again and again.  Here a workgroup
-// walks GC consecutive level-1 query blocks and keeps one listed block per register slot, as dkv_group_kernel does
+// walks GC level-1 query blocks, GS apart, and keeps one listed block per register slot, as dkv_group_kernel does
 // for a single query block.  From one query block R to the next, a slot whose key block is listed again goes on
-// accumulating; a slot whose block is not listed by R + 1 writes its partial to the place of (R, the block's
-// position in R's row) and takes one of the blocks that are new in R + 1 (both rows have Kl distinct entries,
-// so as many slots come free as blocks are new; slots from Kl on compute on block 0 and are never stored).  A partial therefore covers a run of consecutive query blocks of
+// accumulating; a slot whose block is not listed by R + GS writes its partial to the place of (R, the block's
+// position in R's row) and takes one of the blocks that are new in R + GS (both rows have Kl distinct entries,
+// so as many slots come free as blocks are new; slots from Kl on compute on block 0 and are never stored).  A partial therefore covers a run of query blocks of
 // one chain that all list the key block, and sits where the last of them would have put its own; the gather skips
 // a lister whose successor in the same chain lists the block too.  Same arithmetic per tile, fewer partials.
-template <int D, int NW, int NB>
+// P workgroups share the slots of a row of more than NW * NB entries; each walks the same rows and keeps the same books.
+template <int D, int NW, int NB, int P>
 __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) dkv_chain_kernel(LevelTable t, GroupArgs a) {
     using S = GShape<D>;
-    constexpr int SL = NW * NB;
+    constexpr int SL = NW * NB * P;
     __shared__ __attribute__((aligned(16))) char qs[256 * S::ROWB];
     __shared__ __attribute__((aligned(16))) char gs[256 * S::ROWB];
     __shared__ __attribute__((aligned(16))) float st[512];
@@ -169,9 +170,9 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2)
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int g = lane >> 4;
     const int64_t per_head = a.NR / a.GC;
-    const int64_t grp = xcd_contiguous(blockIdx.x, gridDim.x);
-    const int64_t bh = grp / per_head, R0 = (grp % per_head) * a.GC;
-    const int slot0 = NB * wave;                                    // this wave's first slot
+    const int64_t wg = xcd_contiguous(blockIdx.x, gridDim.x), chain = wg / P, bh = chain / per_head, c = chain % per_head;
+    const int64_t R0 = c / a.GS * (a.GS * a.GC) + c % a.GS;           // the chain: R0, R0 + GS, ...
+    const int slot0 = NB * (NW * (int)(wg % P) + wave);               // this wave's first slot
     const int Kl = t.Kl[1];
     const TileOffsets<D> o = tile_offsets<D>(lane);
     const int32_t *I1 = t.I[1] + (bh * a.NR + R0) * Kl;               // I^(1) has one row per level-1 query block
@@ -179,13 +180,14 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2)
     const char *V1 = static_cast<const char *>(t.V[1]) + bh * t.n[1] * D * 2;
     const float bias2 = t.bias[1] * kLog2e;
     float *slab1 = a.slab + a.lvl_off[1] + (bh * a.NR + R0) * Kl * S::UNIT;
+    const int64_t far = (int64_t)a.GS * Kl;                           // from a row of the chain to the next
 
     int sblk = -1, spos = 0;                                          // lane s < Kl: the block slot s holds, its place in the row
     BlockAcc<D> blk[NB];                                              // this wave's slots slot0 ...
     for (int r = 0; r < a.GC; ++r) {
         StageRegs<D, 64 * NW> sr;
-        stage_load<D, 64 * NW>(sr, a, bh * a.N + (R0 + r) * 256, tid);   // in flight during the bookkeeping below
-        const int nb = lane < Kl ? I1[r * Kl + lane] : -1;            // lane p: entry p of this query block's row
+        stage_load<D, 64 * NW>(sr, a, bh * a.N + (R0 + (int64_t)r * a.GS) * 256, tid);   // in flight during the bookkeeping below
+        const int nb = lane < Kl ? I1[r * far + lane] : -1;            // lane p: entry p of this query block's row
         if (r == 0) {
             sblk = nb;
             spos = lane;
@@ -216,7 +218,7 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2)
                 const int s = slot0 + b;
                 if (!((kept >> s) & 1)) {                             // wave-uniform
                     const int oldpos = __builtin_amdgcn_readlane(spos, s);
-                    store_partial<D>(slab1 + ((int64_t)(r - 1) * Kl + oldpos) * S::UNIT, blk[b], a.scale, lane);
+                    store_partial(slab1 + ((r - 1) * far + oldpos) * S::UNIT, blk[b], a.scale, lane);
                     const int64_t id = __builtin_amdgcn_readlane(nid, s);
                     blk[b].load(K1 + id * 16 * D * 2, V1 + id * 16 * D * 2, 16, bias2, lane);
                     blk[b].clear();
@@ -234,7 +236,7 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2)
     for (int b = 0; b < NB; ++b) {
         if (slot0 + b >= Kl) continue;
         const int pos = __builtin_amdgcn_readlane(spos, slot0 + b);
-        store_partial<D>(slab1 + ((int64_t)(a.GC - 1) * Kl + pos) * S::UNIT, blk[b], a.scale, lane);
+        store_partial(slab1 + ((a.GC - 1) * far + pos) * S::UNIT, blk[b], a.scale, lane);
     }
 }
 
@@ -297,7 +299,7 @@ __global__ void __launch_bounds__(512) dkv_upper_kernel(LevelTable t, GroupArgs 
 #pragma unroll
     for (int s = 0; s < SS; ++s) {
         const int jb = a.sparse_begin + wave + 8 * s;
-        if (jb < a.nbs) store_partial<D>(partial_ptr<D>(t, a, nlev, u_begin + jb, grp), sp[s][0], a.scale, lane);
+        if (jb < a.nbs) store_partial(partial_ptr<D>(t, a, nlev, u_begin + jb, grp), sp[s][0], a.scale, lane);
     }
     if constexpr (DENSE) {
         if (dense) {                                                  // the shared block: add the 8 waves' sums in wave order
@@ -353,7 +355,7 @@ struct GatherArgs {
     float *dstK, *dstV;          // [bh, n_l, D]
     int64_t cnt, n_l, nkb, rows; // listers per head, tokens, key blocks per head, rows of I^(l)
     int nblk, Kl, dense;
-    int chain;                   // > 1: partials come from the chain kernel, which walked `chain` consecutive listers
+    int chain, apart;            // chain > 1: partials come from the chain kernel, which walked `chain` listers, `apart` apart
 };
 template <int D, int NT>
 __global__ void __launch_bounds__(NT) dkv_gather_kernel(GatherArgs a) {
@@ -383,9 +385,9 @@ __global__ void __launch_bounds__(NT) dkv_gather_kernel(GatherArgs a) {
                 int pos = 0;
                 for (int x = 0; x < a.Kl; ++x) pos += (row[x] < (int32_t)j) ? 1 : 0;   // rows are ascending
                 int64_t un = ((bh * a.cnt + r) * a.nblk + pos) * U4;
-                if (a.chain > 1 && r % a.chain != a.chain - 1) {                  // carried on by the next lister of the chain?
+                if (a.chain > 1 && r / a.apart % a.chain != a.chain - 1) {        // carried on by the next lister of the chain?
                     bool cont = false;
-                    for (int x = 0; x < a.Kl; ++x) cont |= row[a.Kl + x] == (int32_t)j;
+                    for (int x = 0; x < a.Kl; ++x) cont |= row[a.apart * a.Kl + x] == (int32_t)j;
                     if (cont) un = -1;
                 }
                 unit[tid] = un;
@@ -448,20 +450,29 @@ static int upper_G(const Plan &p) {
     return G;
 }
 
-// Level-1 query blocks one workgroup of the chain kernel walks (1: the plain group kernel takes level 1).
-// Rows of at most 8 level-1 blocks, level 1 sparse and the only level the kernel is given.  16 heads x 65536 tokens, smooth
-// inputs, steps without and with it: K = 4 958 -> 875 us, K = 6 1105 -> 1017, d = 128 2677 -> 2463; Gaussian ones, which share few
-// blocks: K = 4 970 -> 951, d = 128 2903 -> 2868.  Rows of 9 to 16 would need two workgroups that stage the same rows: 1994 ->
-// 1845 us at 65536 tokens (K = 16), but 2270 -> 2310 for Gaussian inputs and 8506 -> 8631 at 262144 tokens, d = 128.
-// Measured at the headline: 8 query blocks per workgroup in 512 workgroups (two per CU) 259 us for the coarse stage,
+// Level-1 query blocks one workgroup of the chain kernel walks (1: the plain group kernel takes level 1), and how far apart they are.
+// Rows of at most 16 level-1 blocks (beyond 8: two workgroups that stage the same rows), level 1 sparse and the only level the kernel
+// is given.
+// GS: 256 tokens of a square grid in raster order are a row's part from 262144 tokens on, and the query block next to R in the
+// list of tokens lies beside it, 256 pixels away; the one below it, which lists 90 % of the same blocks on smooth inputs where
+// the next one lists 3 to 11 %, is sqrt(N) / 256 further on.  On other grids it only costs what the shared blocks would have saved.
+// Coarse stage, before (one workgroup per query block where a row has more than 8 blocks, GS = 1) and after: 8 heads x 262144 tokens, K = 16,
+// d = 128 2860 -> 2166 us; d = 64, K = 8 800 -> 587; 16 heads x 65536, K = 16 621 -> 425, Gaussian inputs 617 -> 611.
+// With chains and without, GS = 1, steps: 16 heads x 65536 tokens, smooth K = 4 958 -> 875 us, K = 6 1105 -> 1017, d = 128 2677 ->
+// 2463; Gaussian, which share few blocks: K = 4 970 -> 951, d = 128 2903 -> 2868.
+// Measured at 16 heads x 65536 tokens: 8 query blocks per workgroup in 512 workgroups (two per CU) 259 us for the coarse stage,
 // 4 in 1024: 275 us, 2: 297 us, 16 in 256 workgroups: 286 us, one query block per workgroup (no carrying): 357 us.
-static int chain_len(const Plan &p) {
-    if (p.L < 2 || p.Kl[1] > 8) return 1;
-    if (upper_G(p) == 0 && dkv_group_top(p) > 1) return 1;
+// (Rows straight into LDS in a ring of eight tiles that runs on from query block to query block: 245 -> 272 us.)
+static void chain_shape(const Plan &p, int *GC, int *GS) {
+    *GC = *GS = 1;
+    if (p.L < 2 || p.Kl[1] > 16) return;
+    if (upper_G(p) == 0 && dkv_group_top(p) > 1) return;
     const int64_t NR = p.N / 256;
-    int GC = 8;
-    while (GC > 1 && (NR % GC != 0 || (int64_t)p.bh * (NR / GC) < 512)) GC >>= 1;   // at least two workgroups per CU
-    return GC;
+    int gc = 8, gs = 1;
+    while (gc > 1 && (NR % gc != 0 || (int64_t)p.bh * (NR / gc) < 512)) gc >>= 1;   // at least two workgroups per CU
+    while ((int64_t)(2 * gs) * (2 * gs) * 65536 <= p.N && NR % (2 * gs * gc) == 0) gs *= 2;
+    *GC = gc;
+    *GS = gs;
 }
 
 // partial-slab layout: level 1 has one partial per (level-1 query block, list position), levels >= 2 one per
@@ -536,6 +547,7 @@ static hipError_t finish_level(const Plan &p, const LevelTable &t, const GroupAr
     ga.cnt = cnt; ga.n_l = p.n[l]; ga.nkb = (p.n[l] + 15) / 16; ga.rows = dense ? 0 : p.n[l + 1];
     ga.nblk = a.nblk[l]; ga.Kl = dense ? 0 : p.Kl[l];
     ga.chain = l == 1 ? a.GC : 1;
+    ga.apart = a.GS;
     const dim3 grid((unsigned)(p.bh * ga.nkb));
     // latency-bound (lists -> rows of I -> partials): more, smaller workgroups per CU shorten the launch
     if (p.d == 64) dkv_gather_kernel<64, 128><<<grid, 128, 0, s>>>(ga);
@@ -546,9 +558,12 @@ static hipError_t finish_level(const Plan &p, const LevelTable &t, const GroupAr
 static hipError_t launch_group_kernel(const Plan &p, const LevelTable &t, const GroupArgs &a, hipStream_t s) {
     if (a.GC > 1) {
         const unsigned wgs = (unsigned)(p.bh * (a.NR / a.GC));
-        if (p.d == 128) dkv_chain_kernel<128, 8, 1><<<wgs, 512, 0, s>>>(t, a);
-        else if (p.Kl[1] <= 4) dkv_chain_kernel<64, 4, 1><<<wgs, 256, 0, s>>>(t, a);
-        else dkv_chain_kernel<64, 4, 2><<<wgs, 256, 0, s>>>(t, a);
+        if (p.d == 128) {
+            if (p.Kl[1] <= 8) dkv_chain_kernel<128, 8, 1, 1><<<wgs, 512, 0, s>>>(t, a);
+            else dkv_chain_kernel<128, 8, 1, 2><<<2 * wgs, 512, 0, s>>>(t, a);
+        } else if (p.Kl[1] <= 4) dkv_chain_kernel<64, 4, 1, 1><<<wgs, 256, 0, s>>>(t, a);
+        else if (p.Kl[1] <= 8) dkv_chain_kernel<64, 4, 2, 1><<<wgs, 256, 0, s>>>(t, a);
+        else dkv_chain_kernel<64, 4, 2, 2><<<2 * wgs, 256, 0, s>>>(t, a);
         return hipGetLastError();
     }
     const dim3 grid((unsigned)(p.bh * a.NR));
@@ -571,7 +586,7 @@ hipError_t launch_dkv_group(const Plan &p, const LevelTable &t, const void *Q, c
     a.sc2 = p.scale * kLog2e; a.scale = p.scale;
     slab_layout(p, a.lvl_off, a.nblk, groups);
     a.G = G;
-    a.GC = chain_len(p);
+    chain_shape(p, &a.GC, &a.GS);
     upper_blocks(p, &a.nbs, &a.nbd);
     a.sparse_begin = 0;
     a.do_dense = 0;

@@ -292,6 +292,8 @@ def test_query_tiles_per_wave(cfg):
     _bf16("chain_K4", 8192, L=2, heads=64, K=4),
     _bf16("chain_K6", 8192, L=2, heads=32, K=6),
     _bf16("chain_K9", 8192, L=2, heads=32, K=9),
+    _bf16("chain_K16", 8192, L=2, heads=32, K=16),
+    _bf16("chain_K9_d128", 8192, L=2, heads=32, K=9, d=128),
     _bf16("chain_K6_d128", 8192, L=2, heads=32, K=6, d=128),
     _bf16("chain_K8_d128", 8192, L=2, heads=32, K=8, d=128),
 ], ids=lambda c: c["name"])
@@ -299,7 +301,7 @@ def test_level1_sums_carried_along_query_blocks(cfg):
     _full_parity(cfg, 0xD161)
 
 
-@pytest.mark.parametrize("heads,K,d", [(64, 3, 64), (64, 6, 64), (32, 8, 64), (64, 6, 128), (64, 8, 128)])
+@pytest.mark.parametrize("heads,K,d", [(64, 3, 64), (64, 6, 64), (32, 8, 64), (64, 6, 128), (64, 8, 128), (64, 12, 64), (32, 16, 128)])
 def test_level1_sums_carried_through_several_query_blocks(heads, K, d):
     """Chains of 8 (heads x level-1 query blocks >= 4096) or 4 query blocks on smooth inputs, whose blocks stay listed: slots are kept,
     released and taken again several times.  Two heads' inputs, repeated, so that the oracle has two to do."""
@@ -319,3 +321,46 @@ def test_level1_sums_carried_through_several_query_blocks(heads, K, d):
         for n, t in got.items():
             H.check_close(f"{n}{(b, h)}", H.f32(t[b, h]), r[n], tol["out"], tol["ulp"])
             assert torch.equal(t[:, h::2], t[:, h:h + 1].expand_as(t[:, h::2])), n
+
+
+@pytest.mark.parametrize("K,d,side", [(8, 64, 512), (12, 64, 512), (16, 128, 512), (5, 64, 1024)])
+def test_level1_sums_carried_to_the_query_block_below(K, d, side):
+    """Chains of query blocks 2 (262144 tokens) and 4 (1048576) apart, whose partials the gather finds: dV with all of dO equal to 1 sums to the
+    number of queries, and every token's dV is that of a computation in 64 bits from the lists and the logsumexp."""
+    import torch
+    from paper_2512_16615_amd import llsa
+    N, L = side * side, 2
+    gen = torch.Generator().manual_seed(K)
+    y, x = torch.meshgrid(torch.arange(side), torch.arange(side), indexing="ij")
+    wave = torch.stack([torch.sin(2 * torch.pi * (a * x + b * y) / side + c) for a, b, c in [(1, 0, 0), (0, 1, 1), (2, 1, 2), (1, 2, 3)]], -1)
+    Q, Kt = ((wave.reshape(N, 4) @ torch.randn(4, d, generator=gen) + 0.1 * torch.randn(N, d, generator=gen)).bfloat16().cuda()[None, None]
+             for _ in range(2))
+    V = torch.randn(1, 1, N, d, generator=gen).bfloat16().cuda()
+    dO = torch.ones_like(V)
+    heads = 16 if side == 512 else 8                         # heads enough for chains of at least two
+    Q, Kt, V, dO = (t.expand(1, heads, N, d).contiguous() for t in (Q, Kt, V, dO))
+    plan = llsa.Plan(1, heads, N, d, 16, K, L)
+    O, LSE, idx, ws = llsa.forward(plan, Q, Kt, V, workspace=plan.alloc_workspace(True))
+    dV = llsa.backward(plan, Q, Kt, V, O, LSE, idx, dO, ws)[2]
+    assert torch.equal(dV, dV[:, :1].expand_as(dV))
+    q, lse = Q[0, 0].double(), LSE[0, 0].double()
+    kp = [Kt[0, 0].double()] + [plan.pyramid_level(ws, 1, l)[0, 0].double() for l in (1, 2)]
+    want = [torch.zeros(N >> 4 * l, dtype=torch.float64, device="cuda") for l in range(3)]   # sum over queries of P, per token of a level
+    for l in range(3):
+        rows = N >> 4 * (l + 1) if l < L else 1
+        toks = (plan.level_indices(idx, l)[0, 0].long()[:, :, None] * 16 + torch.arange(16, device="cuda")).reshape(rows, -1) if l < L else \
+            torch.arange(N >> 4 * l, device="cuda")[None]
+        step = max(1, min(rows, (1 << 24) // (toks.shape[1] * d)))
+        for r in range(0, rows, step):
+            tk, n = toks[r:r + step], N // rows
+            for c in range(0, n, 4096):
+                qq = q.view(rows, n, d)[r:r + step, c:c + 4096]
+                z = torch.matmul(qq, kp[l][tk].transpose(1, 2).contiguous()) * d ** -0.5 + l * 2.772588722239781
+                p = torch.exp(z - lse.view(rows, n)[r:r + step, c:c + 4096, None]).sum(1)
+                want[l].index_add_(0, tk.reshape(-1), p.reshape(-1))
+    for l in (1, 0):
+        want[l] += want[l + 1].repeat_interleave(16) / 16
+    got = dV[0, 0].double()
+    assert abs(float(want[0].sum()) / N - 1) < 1e-5
+    # P rounded to bf16 (2^-9 each, of a sum of positive terms) and dV rounded once
+    assert float(((got - want[0][:, None]).abs() - 2.0 ** -8 * want[0][:, None]).max()) < 1e-3
