@@ -56,109 +56,137 @@ template <> __device__ __forceinline__ void store_vec<bf16_t>(bf16_t *p, const f
 // Alg. 1, compression loop: out[t] = (x[tB] + x[tB+1] + ... + x[tB+B-1]) / B, summed in that order in
 // fp32, one IEEE division, one rounding to the I/O type.  The order is part of the contract: the
 // selection below is decided on these values, so they must not depend on the launch shape.
-struct PoolArgs { const void *in[3]; void *out[3]; void *out2[3]; };
+//
+// A workgroup also pools its own output further (up[0], up[1], ..: the levels above).  Its 256 / (d / VN) output tokens
+// are whole groups of B, of B * B, .. as far as B divides them: their rounded values pass through LDS and are summed in
+// the same ascending order, so every level is bit for bit what a launch of its own would write.  What bounds these
+// kernels beyond level 1 is the launch (3 to 4 us each, one after the other), not the few MB that they read: a training
+// step on 256 fp32 tokens at B = 4, three levels in one launch instead of three, 46.4 -> 40.2 us.
+constexpr int kPoolUp = kMaxL - 1;
+struct PoolArgs { const void *in[3]; void *out[3]; void *up[3][kPoolUp]; int n_up; };
 
-// BC: block size known at compile time (the row loop is unrolled, so all B loads of a thread are in flight at once),
-// or 0 to take it from the argument.  Same order of additions either way.
-// TWO: the workgroup also pools its own output once more (out2 = the level above): its 256 / (d / VN) output tokens
-// are whole groups of B, their rounded values pass through LDS and are summed in the same ascending order, so out2
-// is bit for bit what a second launch on `out` would write, without that launch.
-template <class T, int BC, bool TWO>
+// How many of the levels above `l` a workgroup whose output is level l can make: whole groups only.
+static int pool_up_levels(const Plan &p, int l) {
+    const int vpr = p.d / (16 / p.elt);
+    int n = 0;
+    for (int tok = 256 / vpr; l + n < p.L && tok % p.B == 0; tok /= p.B) ++n;
+    return n;
+}
+
+// s: the mean that this thread holds of (token first + threadIdx.x / vpr, channels cv * VN ..), live where that token
+// exists.  lds: 256 * VN floats.  The whole workgroup calls.  `left`: the existing tokens from `first` on.
+template <class T>
+__device__ __forceinline__ void pool_above(float (&s)[Vec<T>::n], float *lds, void *const *up, int n_up, int64_t first,
+                                           int64_t left, int d, int B) {
+    constexpr int VN = Vec<T>::n;
+    const int vpr = d / VN, tl = threadIdx.x / vpr, cv = threadIdx.x % vpr;
+    int live = (int)min((int64_t)(256 / vpr), left);       // a multiple of B for each level that is still to come
+    const float Bf = (float)B;
+    for (int k = 0; k < n_up; ++k) {
+        if (tl < live)
+#pragma unroll
+            for (int e = 0; e < VN; ++e) lds[threadIdx.x * VN + e] = to_f(from_f<T>(s[e]));   // what was stored, as fp32
+        __syncthreads();
+        live /= B;
+        first /= B;
+        if (tl < live) {
+#pragma unroll
+            for (int e = 0; e < VN; ++e) s[e] = 0.f;
+            for (int r = 0; r < B; ++r)
+#pragma unroll
+                for (int e = 0; e < VN; ++e) s[e] = s[e] + lds[((tl * B + r) * vpr + cv) * VN + e];
+#pragma unroll
+            for (int e = 0; e < VN; ++e) s[e] = __fdiv_rn(s[e], Bf);
+            store_vec<T>(static_cast<T *>(up[k]) + (first + tl) * (int64_t)d + cv * VN, s);
+        }
+        __syncthreads();                                   // read before the next level overwrites it
+    }
+}
+
+// One token's mean over its B rows.  BC: block size known at compile time (the row loop is unrolled, so all B loads of a
+// thread are in flight at once), or 0 to take it from the argument.  Same order of additions either way.
+template <class T, int BC>
+__device__ __forceinline__ void pool_rows(const T *in, int d, int B, float (&s)[Vec<T>::n]) {
+    constexpr int VN = Vec<T>::n;
+    if constexpr (BC != 0) {
+        float x[BC][VN];
+#pragma unroll
+        for (int r = 0; r < BC; ++r) load_vec<T>(in + (int64_t)r * d, x[r]);
+#pragma unroll
+        for (int r = 0; r < BC; ++r)
+#pragma unroll
+            for (int e = 0; e < VN; ++e) s[e] = s[e] + x[r][e];
+    } else {
+        int r0 = 0;
+        for (; r0 + 16 <= B; r0 += 16) {                   // 16 rows in flight at a time, added in row order
+            float x[16][VN];
+#pragma unroll
+            for (int r = 0; r < 16; ++r) load_vec<T>(in + (int64_t)(r0 + r) * d, x[r]);
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+#pragma unroll
+                for (int e = 0; e < VN; ++e) s[e] = s[e] + x[r][e];
+        }
+        float x[VN];
+        for (int r = r0; r < B; ++r) {
+            load_vec<T>(in + (int64_t)r * d, x);
+#pragma unroll
+            for (int e = 0; e < VN; ++e) s[e] = s[e] + x[e];
+        }
+    }
+    const float Bf = (float)B;
+#pragma unroll
+    for (int e = 0; e < VN; ++e) s[e] = __fdiv_rn(s[e], Bf);
+}
+
+template <class T, int BC>
 __global__ void __launch_bounds__(256) pool_kernel(PoolArgs a, int64_t n_out_total, int d, int B_arg) {
     constexpr int VN = Vec<T>::n;
-    __shared__ float lvl[TWO ? 256 * VN : 1];
+    __shared__ float lds[256 * VN];
     const int B = BC ? BC : B_arg;
     const int vpr = d / VN;
     const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
     const int64_t t = idx / vpr;
-    const int cv = (int)(idx % vpr);
-    const bool live = t < n_out_total;
-    if (!TWO && !live) return;
+    const int cv = (int)(idx % vpr), y = blockIdx.y;
     float s[VN];
 #pragma unroll
     for (int e = 0; e < VN; ++e) s[e] = 0.f;
-    if (live) {
-        const T *in = static_cast<const T *>(a.in[blockIdx.y]) + (t * B) * (int64_t)d + cv * VN;
-        if constexpr (BC != 0) {
-            float x[BC][VN];
-#pragma unroll
-            for (int r = 0; r < BC; ++r) load_vec<T>(in + (int64_t)r * d, x[r]);
-#pragma unroll
-            for (int r = 0; r < BC; ++r)
-#pragma unroll
-                for (int e = 0; e < VN; ++e) s[e] = s[e] + x[r][e];
-        } else {
-            int r0 = 0;
-            for (; r0 + 16 <= B; r0 += 16) {                   // 16 rows in flight at a time, added in row order
-                float x[16][VN];
-#pragma unroll
-                for (int r = 0; r < 16; ++r) load_vec<T>(in + (int64_t)(r0 + r) * d, x[r]);
-#pragma unroll
-                for (int r = 0; r < 16; ++r)
-#pragma unroll
-                    for (int e = 0; e < VN; ++e) s[e] = s[e] + x[r][e];
-            }
-            float x[VN];
-            for (int r = r0; r < B; ++r) {
-                load_vec<T>(in + (int64_t)r * d, x);
-#pragma unroll
-                for (int e = 0; e < VN; ++e) s[e] = s[e] + x[e];
-            }
-        }
-        const float Bf = (float)B;
-#pragma unroll
-        for (int e = 0; e < VN; ++e) s[e] = __fdiv_rn(s[e], Bf);
-        store_vec<T>(static_cast<T *>(a.out[blockIdx.y]) + t * (int64_t)d + cv * VN, s);
+    if (t < n_out_total) {
+        pool_rows<T, BC>(static_cast<const T *>(a.in[y]) + (t * B) * (int64_t)d + cv * VN, d, B, s);
+        store_vec<T>(static_cast<T *>(a.out[y]) + t * (int64_t)d + cv * VN, s);
     }
-    if constexpr (TWO) {
-#pragma unroll
-        for (int e = 0; e < VN; ++e) lvl[threadIdx.x * VN + e] = to_f(from_f<T>(s[e]));   // what was stored, as fp32
-        __syncthreads();
-        const int tpw = 256 / vpr;                         // output tokens of this workgroup: tpw / B whole groups
-        const int t2l = threadIdx.x / vpr;                 // group this thread sums (threads beyond the groups idle)
-        const int64_t first = (int64_t)blockIdx.x * tpw;   // the workgroup's first output token: a multiple of B
-        if (t2l < tpw / B && first + (int64_t)(t2l + 1) * B <= n_out_total) {
-            float u[VN];
-#pragma unroll
-            for (int e = 0; e < VN; ++e) u[e] = 0.f;
-            for (int r = 0; r < B; ++r)
-#pragma unroll
-                for (int e = 0; e < VN; ++e) u[e] = u[e] + lvl[((t2l * B + r) * vpr + cv) * VN + e];
-            const float Bf = (float)B;
-#pragma unroll
-            for (int e = 0; e < VN; ++e) u[e] = __fdiv_rn(u[e], Bf);
-            store_vec<T>(static_cast<T *>(a.out2[blockIdx.y]) + (first / B + t2l) * (int64_t)d + cv * VN, u);
+    if (a.n_up == 0) return;
+    const int64_t first = (int64_t)blockIdx.x * (256 / vpr);
+    pool_above<T>(s, lds, a.up[y], a.n_up, first, n_out_total - first, d, B);
+}
+
+// Levels `from` .. L of the tensors x0 .. 2 (0 = Q, 1 = K, 2 = V; src: their level 0, used where from is 1).
+static hipError_t pool_levels(const Plan &p, const void *const *src, char *w, int from, int x0, hipStream_t s) {
+    for (int l = from; l <= p.L;) {
+        PoolArgs a{};
+        a.n_up = pool_up_levels(p, l);
+        for (int x = x0; x < 3; ++x) {
+            a.in[x - x0] = (l == 1) ? src[x] : (const void *)(w + p.pyr_off[x][l - 1]);
+            a.out[x - x0] = w + p.pyr_off[x][l];
+            for (int k = 0; k < a.n_up; ++k) a.up[x - x0][k] = w + p.pyr_off[x][l + 1 + k];
         }
+        const int64_t n_out_total = (int64_t)p.bh * p.n[l];
+        const int64_t threads = n_out_total * (p.d / (16 / p.elt));
+        dim3 grid((unsigned)((threads + 255) / 256), 3 - x0);
+        if (p.elt == 4)     pool_kernel<float, 0><<<grid, 256, 0, s>>>(a, n_out_total, p.d, p.B);
+        else if (p.B == 16) pool_kernel<bf16_t, 16><<<grid, 256, 0, s>>>(a, n_out_total, p.d, p.B);
+        else                pool_kernel<bf16_t, 0><<<grid, 256, 0, s>>>(a, n_out_total, p.d, p.B);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        l += 1 + a.n_up;
     }
+    return hipSuccess;
 }
 
 hipError_t launch_pool(const Plan &p, const void *Q, const void *K, const void *V, void *ws, bool q_too,
                        hipStream_t s) {
     const void *src[3] = {Q, K, V};
-    char *w = static_cast<char *>(ws);
-    const int vn = 16 / p.elt;
-    // levels 1 and 2 in one launch where a workgroup's 256 / (d / vn) level-1 tokens are whole groups of B
-    const bool two = p.L >= 2 && p.elt == 2 && p.B == 16 && (256 / (p.d / vn)) % p.B == 0;
-    for (int l = 1; l <= p.L; ++l) {
-        if (two && l == 2) continue;
-        PoolArgs a;
-        int cnt = 0;
-        for (int x = q_too ? 0 : 1; x < 3; ++x, ++cnt) {
-            a.in[cnt] = (l == 1) ? src[x] : (const void *)(w + p.pyr_off[x][l - 1]);
-            a.out[cnt] = w + p.pyr_off[x][l];
-            a.out2[cnt] = (two && l == 1) ? (void *)(w + p.pyr_off[x][2]) : nullptr;
-        }
-        const int64_t n_out_total = (int64_t)p.bh * p.n[l];
-        const int64_t threads = n_out_total * (p.d / vn);
-        dim3 grid((unsigned)((threads + 255) / 256), cnt);
-        if (p.elt == 4) pool_kernel<float, 0, false><<<grid, 256, 0, s>>>(a, n_out_total, p.d, p.B);
-        else if (two && l == 1) pool_kernel<bf16_t, 16, true><<<grid, 256, 0, s>>>(a, n_out_total, p.d, p.B);
-        else if (p.B == 16) pool_kernel<bf16_t, 16, false><<<grid, 256, 0, s>>>(a, n_out_total, p.d, p.B);
-        else                pool_kernel<bf16_t, 0, false><<<grid, 256, 0, s>>>(a, n_out_total, p.d, p.B);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
+    return pool_levels(p, src, static_cast<char *>(ws), 1, q_too ? 0 : 1, s);
 }
 
 // ----------------------------------------------------------------------- layer glue fused with pooling
@@ -171,104 +199,101 @@ hipError_t launch_pool(const Plan &p, const void *Q, const void *K, const void *
 // out is rounded to the I/O type; the level-1 token is pooled from those rounded values exactly as pool_kernel
 // does it (ascending fp32 sum, one division, one rounding), so it equals pool_kernel's result on `out` bit for bit.
 // One thread per (level-1 token, 16-byte channel vector); the d / VN threads of a token are neighbouring lanes and
-// reduce the sum of squares of a row with xor shuffles.  grid.y: 0 = Q, 1 = K.
-struct GlueArgs { const void *in[2]; void *out[2]; void *lvl1[2]; const float *gamma[2]; };
+// reduce the sum of squares of a row with xor shuffles.  grid.y: 0 = Q, 1 = K, 2 = V, which is only pooled.
+// The levels above come from the same workgroup where its tokens are whole groups: 32 x 16384 tokens, d = 64, three
+// levels, glue and layer 206 -> 194.5 us, with two launches before the selection where there were four.
+struct GlueArgs { const void *in[2]; void *out[2]; const float *gamma[2]; PoolArgs pool; };
 
 template <class T>
 __global__ void __launch_bounds__(256) qknorm_rope_pool_kernel(GlueArgs a, const float *__restrict__ cos_t,
                                                                const float *__restrict__ sin_t, float eps,
                                                                int64_t n1_total, int64_t N, int d, int B) {
     constexpr int VN = Vec<T>::n, ROWS = 4;                // rows of one token group in flight at a time
+    __shared__ float lds[256 * VN];
     const int vpr = d / VN;
     const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
     const int64_t t1 = idx / vpr;                          // level-1 token, flat over (batch, head)
     const int cv = (int)(idx % vpr);
-    if (t1 >= n1_total) return;                            // whole token groups leave together (vpr divides 64)
     const int y = blockIdx.y;
-    const T *in = static_cast<const T *>(a.in[y]) + (t1 * B) * (int64_t)d + cv * VN;
-    T *out = static_cast<T *>(a.out[y]) + (t1 * B) * (int64_t)d + cv * VN;
-    const int64_t tok0 = (t1 * B) % N;                     // position of the group's first token inside its head
-    float gam[VN];
-#pragma unroll
-    for (int e = 0; e < VN; ++e) gam[e] = a.gamma[y][cv * VN + e];
-    const float inv_d = 1.f / (float)d;
     float s[VN];
 #pragma unroll
     for (int e = 0; e < VN; ++e) s[e] = 0.f;
-    for (int r0 = 0; r0 < B; r0 += ROWS) {
-        float x[ROWS][VN], cs[ROWS][VN / 2], sn[ROWS][VN / 2];
+    if (t1 < n1_total) {                                   // whole token groups are in or out together (vpr divides 64)
+        if (y == 2) {
+            pool_rows<T, 0>(static_cast<const T *>(a.pool.in[2]) + (t1 * B) * (int64_t)d + cv * VN, d, B, s);
+        } else {
+            const T *in = static_cast<const T *>(a.in[y]) + (t1 * B) * (int64_t)d + cv * VN;
+            T *out = static_cast<T *>(a.out[y]) + (t1 * B) * (int64_t)d + cv * VN;
+            const int64_t tok0 = (t1 * B) % N;                     // position of the group's first token inside its head
+            float gam[VN];
 #pragma unroll
-        for (int r = 0; r < ROWS; ++r) {
-            const int rr = min(r0 + r, B - 1);             // B need not be a multiple of ROWS: the tail re-reads
-            load_vec<T>(in + (int64_t)rr * d, x[r]);
-            const int64_t tab = (tok0 + rr) * (d / 2) + cv * (VN / 2);
+            for (int e = 0; e < VN; ++e) gam[e] = a.gamma[y][cv * VN + e];
+            const float inv_d = 1.f / (float)d;
+            for (int r0 = 0; r0 < B; r0 += ROWS) {
+                float x[ROWS][VN], cs[ROWS][VN / 2], sn[ROWS][VN / 2];
 #pragma unroll
-            for (int e = 0; e < VN / 2; ++e) { cs[r][e] = cos_t[tab + e]; sn[r][e] = sin_t[tab + e]; }
-        }
+                for (int r = 0; r < ROWS; ++r) {
+                    const int rr = min(r0 + r, B - 1);             // B need not be a multiple of ROWS: the tail re-reads
+                    load_vec<T>(in + (int64_t)rr * d, x[r]);
+                    const int64_t tab = (tok0 + rr) * (d / 2) + cv * (VN / 2);
 #pragma unroll
-        for (int r = 0; r < ROWS; ++r) {
-            float ss = 0.f;
+                    for (int e = 0; e < VN / 2; ++e) { cs[r][e] = cos_t[tab + e]; sn[r][e] = sin_t[tab + e]; }
+                }
 #pragma unroll
-            for (int e = 0; e < VN; ++e) ss = fmaf(x[r][e], x[r][e], ss);
-            for (int o = 1; o < vpr; o <<= 1) ss += __shfl_xor(ss, o, 64);
-            const float rinv = 1.f / sqrtf(fmaf(ss, inv_d, eps));
-            float o8[VN];
+                for (int r = 0; r < ROWS; ++r) {
+                    float ss = 0.f;
 #pragma unroll
-            for (int e = 0; e < VN / 2; ++e) {
-                const float y0 = x[r][2 * e] * rinv * gam[2 * e], y1 = x[r][2 * e + 1] * rinv * gam[2 * e + 1];
-                o8[2 * e] = to_f(from_f<T>(y0 * cs[r][e] - y1 * sn[r][e]));
-                o8[2 * e + 1] = to_f(from_f<T>(y0 * sn[r][e] + y1 * cs[r][e]));
+                    for (int e = 0; e < VN; ++e) ss = fmaf(x[r][e], x[r][e], ss);
+                    for (int o = 1; o < vpr; o <<= 1) ss += __shfl_xor(ss, o, 64);
+                    const float rinv = 1.f / sqrtf(fmaf(ss, inv_d, eps));
+                    float o8[VN];
+#pragma unroll
+                    for (int e = 0; e < VN / 2; ++e) {
+                        const float y0 = x[r][2 * e] * rinv * gam[2 * e], y1 = x[r][2 * e + 1] * rinv * gam[2 * e + 1];
+                        o8[2 * e] = to_f(from_f<T>(y0 * cs[r][e] - y1 * sn[r][e]));
+                        o8[2 * e + 1] = to_f(from_f<T>(y0 * sn[r][e] + y1 * cs[r][e]));
+                    }
+                    if (r0 + r < B) {
+                        store_vec<T>(out + (int64_t)(r0 + r) * d, o8);
+#pragma unroll
+                        for (int e = 0; e < VN; ++e) s[e] = s[e] + o8[e];
+                    }
+                }
             }
-            if (r0 + r < B) {
-                store_vec<T>(out + (int64_t)(r0 + r) * d, o8);
+            const float Bf = (float)B;
 #pragma unroll
-                for (int e = 0; e < VN; ++e) s[e] = s[e] + o8[e];
-            }
+            for (int e = 0; e < VN; ++e) s[e] = __fdiv_rn(s[e], Bf);
         }
+        store_vec<T>(static_cast<T *>(a.pool.out[y]) + t1 * (int64_t)d + cv * VN, s);
     }
-    const float Bf = (float)B;
-#pragma unroll
-    for (int e = 0; e < VN; ++e) s[e] = __fdiv_rn(s[e], Bf);
-    store_vec<T>(static_cast<T *>(a.lvl1[y]) + t1 * (int64_t)d + cv * VN, s);
+    if (a.pool.n_up == 0) return;
+    const int64_t first = (int64_t)blockIdx.x * (256 / vpr);
+    pool_above<T>(s, lds, a.pool.up[y], a.pool.n_up, first, n1_total - first, d, B);
 }
 
-// Q and K through the fused kernel, V's level 1 and every level above through pool_kernel.
+// One launch for everything up to the last level that whole groups of a workgroup reach, pool_kernel for the rest.
 hipError_t launch_qknorm_rope_pool(const Plan &p, const void *Qpre, const void *Kpre, const void *V,
                                    const float *gamma_q, const float *gamma_k, const float *cos_t, const float *sin_t,
                                    float eps, void *Qout, void *Kout, void *ws, hipStream_t s) {
     char *w = static_cast<char *>(ws);
-    GlueArgs g;
+    GlueArgs g{};
     g.in[0] = Qpre; g.in[1] = Kpre;
     g.out[0] = Qout; g.out[1] = Kout;
-    g.lvl1[0] = w + p.pyr_off[0][1]; g.lvl1[1] = w + p.pyr_off[1][1];
     g.gamma[0] = gamma_q; g.gamma[1] = gamma_k;
-    const int vn = 16 / p.elt;
+    g.pool.in[2] = V;
+    g.pool.n_up = pool_up_levels(p, 1);
+    for (int x = 0; x < 3; ++x) {
+        g.pool.out[x] = w + p.pyr_off[x][1];
+        for (int k = 0; k < g.pool.n_up; ++k) g.pool.up[x][k] = w + p.pyr_off[x][2 + k];
+    }
     const int64_t n1_total = (int64_t)p.bh * p.n[1];
-    const int64_t threads = n1_total * (p.d / vn);
-    dim3 grid((unsigned)((threads + 255) / 256), 2);
+    const int64_t threads = n1_total * (p.d / (16 / p.elt));
+    dim3 grid((unsigned)((threads + 255) / 256), 3);
     if (p.elt == 4) qknorm_rope_pool_kernel<float><<<grid, 256, 0, s>>>(g, cos_t, sin_t, eps, n1_total, p.N, p.d, p.B);
-    else qknorm_rope_pool_kernel<bf16_t><<<grid, 256, 0, s>>>(g, cos_t, sin_t, eps, n1_total, p.N, p.d, p.B);
+    else            qknorm_rope_pool_kernel<bf16_t><<<grid, 256, 0, s>>>(g, cos_t, sin_t, eps, n1_total, p.N, p.d, p.B);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const void *src[3] = {Qout, Kout, V};
-    for (int l = 1; l <= p.L; ++l) {
-        PoolArgs a;
-        int cnt = 0;
-        for (int x = (l == 1) ? 2 : 0; x < 3; ++x, ++cnt) {    // level 1 of Q and K is already there
-            a.in[cnt] = (l == 1) ? src[x] : (const void *)(w + p.pyr_off[x][l - 1]);
-            a.out[cnt] = w + p.pyr_off[x][l];
-            a.out2[cnt] = nullptr;
-        }
-        const int64_t n_out_total = (int64_t)p.bh * p.n[l];
-        const int64_t th = n_out_total * (p.d / vn);
-        dim3 pg((unsigned)((th + 255) / 256), cnt);
-        if (p.elt == 4) pool_kernel<float, 0, false><<<pg, 256, 0, s>>>(a, n_out_total, p.d, p.B);
-        else if (p.B == 16) pool_kernel<bf16_t, 16, false><<<pg, 256, 0, s>>>(a, n_out_total, p.d, p.B);
-        else                pool_kernel<bf16_t, 0, false><<<pg, 256, 0, s>>>(a, n_out_total, p.d, p.B);
-        e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
+    return pool_levels(p, nullptr, w, 2 + g.pool.n_up, 0, s);
 }
 
 // ---------------------------------------------------------------------------------------------- selection

@@ -69,6 +69,40 @@ def test_qknorm_rope_pool_matches_oracle(cfg):
     H.check_close("LSE_glued(0, 0)", H.f32(LSE1[0, 0]), f["LSE"], tol["lse"])
 
 
+# levels that one workgroup of the pooling makes from its own tokens: all, some or none of them; a last workgroup that is
+# not full; a first level outside such a workgroup's whole groups (B = 3, 32); more levels than one workgroup reaches
+@pytest.mark.parametrize("cfg", [
+    dict(name="f32_b2_L8", batch=1, heads=3, d=16, N=768, B=2, K=2, L=8, dtype="f32", kind="gaussian"),
+    dict(name="f32_b4_d32", batch=1, heads=5, d=32, N=320, B=4, K=2, L=3, dtype="f32", kind="gaussian"),
+    dict(name="f32_b16_d64", batch=1, heads=3, d=64, N=4096, B=16, K=2, L=3, dtype="f32", kind="gaussian"),
+    dict(name="f32_b16_d128", batch=1, heads=1, d=128, N=4096, B=16, K=2, L=2, dtype="f32", kind="gaussian"),
+    dict(name="bf16_b2_d128_L6", batch=1, heads=3, d=128, N=576, B=2, K=2, L=6, dtype="bf16", kind="gaussian"),
+    dict(name="bf16_b16_d16", batch=1, heads=1, d=16, N=256 * 17, B=16, K=2, L=2, dtype="bf16", kind="gaussian"),
+    dict(name="bf16_b16_d64_L3", batch=1, heads=3, d=64, N=4096, B=16, K=2, L=3, dtype="bf16", kind="gaussian"),
+    dict(name="bf16_b3_d64", batch=1, heads=2, d=64, N=27 * 7, B=3, K=2, L=3, dtype="bf16", kind="gaussian"),
+    dict(name="bf16_b32_d64", batch=1, heads=3, d=64, N=3072, B=32, K=2, L=2, dtype="bf16", kind="gaussian"),
+], ids=lambda c: c["name"])
+def test_every_pooled_level_is_exact(cfg):
+    bf16 = cfg["dtype"] == "bf16"
+    x = H.make_inputs(cfg, 0x115A3100)
+    if bf16:
+        x = {n: orc.to_bf16(v) for n, v in x.items()}
+    plan, g = H.make_plan(cfg), H.geometry(cfg)
+    Q, K, V = (H.to_dev(x[n], cfg) for n in ("Q", "K", "V"))
+    cos, sin = inputs.rope_tables(cfg["N"], cfg["d"])
+    dev = lambda a: torch.from_numpy(a).cuda()
+    ws = llsa.forward(plan, Q, K, V)[3]
+    Qg, Kg, wg = llsa.qknorm_rope_pool(plan, Q, K, V, dev(inputs.norm_gain(1, "Q", cfg["d"])),
+                                       dev(inputs.norm_gain(1, "K", cfg["d"])), dev(cos), dev(sin), 1e-6)
+    torch.cuda.synchronize()
+    for w, tensors in ((ws, (Q, K, V)), (wg, (Qg, Kg, V))):
+        for i, t in enumerate(tensors):
+            for h in range(cfg["heads"]):
+                lev = orc.pyramid(H.f32(t[0, h]), g, bf16)
+                for l in range(1, g.L + 1):
+                    assert np.array_equal(H.f32(plan.pyramid_level(w, i, l)[0, h]), lev[l]), (i, h, l)
+
+
 # ---- key/value backward of level 0 with its lists from Alg. 2 or from a dense block mask (Sec. 5.4, Fig. 4)
 
 @pytest.mark.parametrize("cfg", [
