@@ -31,7 +31,8 @@ template <int D> struct DkvShape {
 // Tiles t_first, t_first + t_step, ... < t_end of one key block's query list, accumulated into accK / accV.
 // lst: the block's listed query-block rows (null when dense); groups: 16-query groups in the list.
 // Rows go from memory straight into the wave's LDS.  Every operand of a tile is read before its exponentials, so that the next
-// tile's rows, for which there is only this one place, fly during the rest.  FINE_FIG
+// tile's rows, for which there is only this one place, fly during the rest: through registers 317 us at 16 x 65536 tokens, K = 8,
+// this way 309 (a second place in LDS was worth a wave less per SIMD); 8 x 262144, d = 128, K = 16: 1780 -> 1660.
 template <int D>
 __device__ __forceinline__ void dkv_tile_loop(const DkvArgs &a, int64_t bh, const int32_t *lst, int64_t groups,
                                               int64_t t_first, int64_t t_step, int64_t t_end,
@@ -230,12 +231,10 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 6
     const int i16 = lane & 15, g = lane >> 4;
     const int64_t nkb = a.n_l >> 4;                        // key tiles per head (a multiple of 4)
     const bool has_par = a.parK != nullptr;
-    // The 16 key blocks under one level-1 token draw their queries from one pool (the fine blocks under the
-    // level-1 query blocks that listed that token), about 0.5 MB of Q and dO.  Keeping their four workgroups on one
-    // XCD, so that its L2 alone fetches the pool, was measured and does not pay: the plain order spreads clusters of
-    // hot key blocks best.
-    const int64_t kb0 = (int64_t)blockIdx.x * 4;           // this workgroup's four key tiles (same head)
-    const int64_t bh = kb0 / nkb;
+    // This workgroup's four key tiles (same head) lie a.apart tiles from each other (launch_dkv_mfma says why).
+    const unsigned per_head = (unsigned)(nkb >> 2), q = blockIdx.x % per_head;
+    const int64_t bh = blockIdx.x / per_head;
+    const unsigned j0 = q / a.apart * (4 * a.apart) + q % a.apart;
 
     // The 16 keys of block j share one parent token (level-1 token j).  Its gradient row is fetched into
     // registers before the tile loop (so the epilogue does not wait for memory) and handed to the epilogue's
@@ -277,7 +276,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 6
 
     // ---- each wave alone on its own key block, if that block's list is short
     {
-        const int64_t j = kb0 % nkb + wave;
+        const int64_t j = j0 + wave * a.apart;
         const int32_t *Crow = a.C + bh * (a.rows + 1) + j;
         const int32_t beg = Crow[0], len = Crow[1] - beg;   // in 16-query groups
         if (lane == 0) len_sh[wave] = len;
@@ -302,7 +301,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 6
     for (int w = 0; w < 4; ++w) {
         const int len = len_sh[w];
         if (len <= kSoloMax) continue;                      // uniform over the workgroup
-        const int64_t j = kb0 % nkb + w;
+        const int64_t j = j0 + w * a.apart;
         const int32_t beg = a.C[bh * (a.rows + 1) + j];
         bf16x8 kop[S::KS], vop[S::KS];
         f32x4 accK[S::NT], accV[S::NT];
@@ -356,6 +355,20 @@ int dkv_splits(const Plan &p, int l) {
     return (int)s;
 }
 
+// How far apart the four key tiles of a dkv_fine_kernel workgroup are.  Neighbouring tiles are listed about equally often, so that
+// hot ones, one beside the other, fill whole workgroups, which hold their place until the longest list is done, while others run
+// empty.  A quarter of the head apart, lists of a workgroup are as different as they can be; but then the workgroups in flight
+// read query rows from all over the head, which only pays while a head's Q and dO stay in an XCD's 4 MB of L2, or nearly.
+// Beyond, 4 tiles.  us at distance 1 / 4 / N / 64, smooth inputs, K = 8: 16 x 4096 tokens 34.2 / 35.3 / 28.0, 32 x 16384
+// 169 / 156 / 149, 16 x 16384 with d = 128 172 / 156 / 150, 16 x 32768 156 / 160 / 154, 16 x 65536 305 / 299 / 316, 4 x 262144
+// 349 / 312 / 472, 8 x 262144 with d = 128 and K = 16 1666 / 1634 / 2475; gaussian 8 x 16384 48.0 / 48.8 / 47.5, 16 x 65536
+// 328 / 331 / 334.
+static unsigned fine_apart(const Plan &p) {
+    const int64_t tiles = p.N / 16;
+    if (p.N * p.d * 4 <= (int64_t)8 << 20) return (unsigned)(tiles / 4);
+    return tiles % 16 == 0 ? 4 : 1;
+}
+
 // level0_alone: level 0's own gradient only, without the share of its parent tokens (the pooled levels' gradients)
 hipError_t launch_dkv_mfma(const Plan &p, const LevelTable &t, int l, const void *Q, const void *dO, const float *LSE,
                            const float *D, void *ws, void *dK, void *dV, hipStream_t s, bool level0_alone) {
@@ -388,6 +401,7 @@ hipError_t launch_dkv_mfma(const Plan &p, const LevelTable &t, int l, const void
         const hipError_t e = launch_dkv_block(p, l, a, s);
         if (l == 0 || e != hipSuccess) return e;
     } else if (l == 0) {                                    // N % 64 == 0: four key tiles per workgroup, one head
+        a.apart = fine_apart(p);
         dim3 grid((unsigned)(key_blocks / 4));
         if (p.d == 64) dkv_fine_kernel<64><<<grid, 256, 0, s>>>(a);
         else dkv_fine_kernel<128><<<grid, 256, 0, s>>>(a);

@@ -112,6 +112,9 @@ def test_every_pooled_level_is_exact(cfg):
     # rows of the mask that begin at no multiple of 16 bytes (T = 172) and of no 4 (T = 17)
     dict(name="kv0_T172", batch=1, heads=2, d=64, N=2752, B=16, K=4, L=1, dtype="bf16", kind="gaussian"),
     dict(name="kv0_T17", batch=1, heads=2, d=64, N=1088, B=64, K=4, L=1, dtype="bf16", kind="gaussian"),
+    # more than 8 MB of Q and dO in a head: key blocks of a workgroup next to each other, and four apart
+    dict(name="kv0_n16448_d128", batch=1, heads=2, d=128, N=16448, B=16, K=4, L=1, dtype="bf16", kind="gaussian"),
+    dict(name="kv0_n16640_d128", batch=1, heads=2, d=128, N=16640, B=16, K=4, L=1, dtype="bf16", kind="gaussian"),
 ], ids=lambda c: c["name"])
 def test_kv_backward_level0_csc_and_mask_agree_with_the_oracle(cfg):
     x = H.make_inputs(cfg, 0x115A3100)
