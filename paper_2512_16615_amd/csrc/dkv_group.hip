@@ -43,7 +43,7 @@ struct GroupArgs {
     int G;                                              // level-1 query blocks per workgroup (upper kernel)
     int GC, GS;                                         // level-1 query blocks a workgroup of the chain kernel walks, how far apart
     int nbs, nbd;                                       // upper kernel: listed blocks the waves own / shared dense block (0 or 1)
-    int sparse_begin, do_dense;                         // upper kernel: first sparse block of this launch; does it take the dense one
+    int passes;                                         // upper kernel: workgroups that share the listed blocks of a query group
     float sc2, scale;
 };
 
@@ -240,8 +240,11 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2)
     }
 }
 
-// SS = sparse blocks a wave owns in one launch (blocks sparse_begin + wave, + 8, ...): a launch covers 8 SS of them;
-// DENSE: may this instantiation take the shared dense block
+// SS = listed blocks a wave owns (block wave of the workgroup's share, + 8, ...): a workgroup takes 8 SS of them, and where a
+// query group has more, a.passes workgroups take a share each.  All of them read the group's rows: they run at about the same
+// time, eight ids apart and so on one XCD, for the rows to come from memory once.  As launches of their own the three passes of
+// 8 x 262144 tokens, d = 128, K = 16 took 430 + 440 + 290 us and read 1.07 GB each; in one, the coarse levels' dK / dV take 2098 us
+// instead of 2185.  DENSE: may this instantiation take the shared dense block (the first pass does).
 template <int D, int SS, bool DENSE>
 __global__ void __launch_bounds__(512) dkv_upper_kernel(LevelTable t, GroupArgs a) {
     using S = GShape<D>;
@@ -253,20 +256,23 @@ __global__ void __launch_bounds__(512) dkv_upper_kernel(LevelTable t, GroupArgs 
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int i16 = lane & 15, g = lane >> 4;
     const int64_t per_head = a.NR / a.G;
-    const int64_t grp = blockIdx.x;                                   // query group: G consecutive level-1 query blocks
+    const unsigned ngrp = gridDim.x / (unsigned)a.passes, c0 = blockIdx.x / (8u * a.passes) * 8u;   // eight groups, pass by pass
+    const unsigned width = min(8u, ngrp - c0), rem = blockIdx.x - c0 * a.passes;
+    const int pass = (int)(rem / width), first = pass * 8 * SS;       // first listed block of this workgroup
+    const int64_t grp = c0 + rem % width;                             // query group: G consecutive level-1 query blocks
     const int64_t bh = grp / per_head, R0 = (grp % per_head) * a.G;
     const TileOffsets<D> o = tile_offsets<D>(lane);
 
     const int nlev = min(t.nlev, a.lev_end);
     const int u_begin = t.bseg[2];                                    // first listed block of level 2
-    const bool dense = DENSE && a.do_dense;
+    const bool dense = DENSE && a.nbd > 0 && pass == 0;
     BlockAcc<D> sp[SS][1], dn[DENSE ? 1 : 1];                         // this wave's sparse blocks; the dense block
     {
         BlockTable ctab;                                              // lane j: listed block u_begin + 64 * chunk + j
         int chunk = -1;
 #pragma unroll
         for (int s = 0; s < SS; ++s) {
-            const int jb = a.sparse_begin + wave + 8 * s;
+            const int jb = first + wave + 8 * s;
             const bool have = jb < a.nbs;
             if (have && (jb >> 6) != chunk) { chunk = jb >> 6; ctab.fill(t, bh, R0 * 16, u_begin, chunk, lane, D, nlev); }
             sp[s][0].load(have ? ctab.K(jb & 63) : nullptr, ctab.V(jb & 63), ctab.count(jb & 63), ctab.bias(jb & 63), lane);
@@ -289,7 +295,7 @@ __global__ void __launch_bounds__(512) dkv_upper_kernel(LevelTable t, GroupArgs 
         if (r + 1 < a.G) stage_load<D, 512>(sr, a, bh * a.N + (R0 + r + 1) * 256, tid);   // flies during the math
 #pragma unroll
         for (int s = 0; s < SS; ++s)
-            if (a.sparse_begin + wave + 8 * s < a.nbs)
+            if (first + wave + 8 * s < a.nbs)
 #pragma unroll 1                                                      // unrolled it takes 251 registers: none left beside it
                 for (int u = 0; u < 8; ++u) group_tile<D, 1>(qs, gs, st, st + 256, u, o, sp[s], a.sc2, g);
         if (dense) group_tile<D, 1>(qs, gs, st, st + 256, wave, o, dn, a.sc2, g);
@@ -298,7 +304,7 @@ __global__ void __launch_bounds__(512) dkv_upper_kernel(LevelTable t, GroupArgs 
 
 #pragma unroll
     for (int s = 0; s < SS; ++s) {
-        const int jb = a.sparse_begin + wave + 8 * s;
+        const int jb = first + wave + 8 * s;
         if (jb < a.nbs) store_partial(partial_ptr<D>(t, a, nlev, u_begin + jb, grp), sp[s][0], a.scale, lane);
     }
     if constexpr (DENSE) {
@@ -588,25 +594,21 @@ hipError_t launch_dkv_group(const Plan &p, const LevelTable &t, const void *Q, c
     a.G = G;
     chain_shape(p, &a.GC, &a.GS);
     upper_blocks(p, &a.nbs, &a.nbd);
-    a.sparse_begin = 0;
-    a.do_dense = 0;
+    a.passes = 1;
 
     // first the kernels that write the partials (they read no list), then, top-down, the reductions and gathers
     // (a level adds the share of the one above)
     if (G) {                                                // levels >= 2 in their own kernel
         GroupArgs up = a;
         up.lev_end = top + 1;
-        const dim3 grid((unsigned)(p.bh * (NR / G)));
-        const int per_launch = p.d == 64 ? 16 : 8;          // sparse blocks one launch covers
-        for (int sb = 0; sb == 0 || sb < up.nbs; sb += per_launch) {   // the first launch also takes the dense block (d = 64)
-            up.sparse_begin = sb;
-            up.do_dense = (sb == 0 && up.nbd > 0) ? 1 : 0;
-            if (p.d == 128) dkv_upper_kernel<128, 1, false><<<grid, 512, 0, s>>>(t, up);
-            else if (up.nbs - sb > 8 && !up.do_dense) dkv_upper_kernel<64, 2, false><<<grid, 512, 0, s>>>(t, up);
-            else if (up.nbs - sb > 8) dkv_upper_kernel<64, 2, true><<<grid, 512, 0, s>>>(t, up);
-            else dkv_upper_kernel<64, 1, true><<<grid, 512, 0, s>>>(t, up);
-            GRP_TRY(hipGetLastError());
-        }
+        const int share = up.nbs > 8 && p.d == 64 ? 16 : 8;
+        up.passes = max(1, (up.nbs + share - 1) / share);
+        const dim3 grid((unsigned)(p.bh * (NR / G) * up.passes));
+        if (p.d == 128) dkv_upper_kernel<128, 1, false><<<grid, 512, 0, s>>>(t, up);
+        else if (share == 8) dkv_upper_kernel<64, 1, true><<<grid, 512, 0, s>>>(t, up);
+        else if (up.nbd == 0) dkv_upper_kernel<64, 2, false><<<grid, 512, 0, s>>>(t, up);
+        else dkv_upper_kernel<64, 2, true><<<grid, 512, 0, s>>>(t, up);
+        GRP_TRY(hipGetLastError());
     }
     // With a side stream (the one the lists are made on), the small reductions and gathers of levels >= 2 follow the
     // lists there, beside the level-1 kernel, and `lists` is recorded again behind them.
