@@ -144,21 +144,28 @@ template <int D> __device__ __forceinline__ TileOffsets<D> tile_offsets(int lane
 // chunk (row_source).  The compiler does not know of these loads (it would wait for all of them at every LDS read): vm_wait before the
 // data is read, and nothing may still be reading what they overwrite, which lgkmcnt(0) sees to for the wave's own reads.
 // `base` and `lds` are the same in every lane.
+// Where the compiler has `base` in vector registers, v_readfirstlane writes it right before the asm, into which the compiler's own
+// wait states do not reach: a vector memory instruction must not read an SGPR within five wait states of the vector instruction that
+// wrote it, and the hardware does not look.  Scalar instructions may read it at once and what they write may be read at once, so the loads
+// take a scalar copy.  (s_nop 3 in its place: 0.3 to 0.6 % slower steps at 16 heads x 4096, 32 x 16384 and 16 x 65536 tokens.)
+#define LLSA_LOAD_LDS "s_mov_b64 %0, %3\n\ts_mov_b32 m0, %1\n\ts_waitcnt lgkmcnt(0)\n\tglobal_load_lds_dwordx4 %2, %0"
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"         // m0 is on the clobber list so that nothing else is kept in it meanwhile
 template <int N> __device__ __forceinline__ void load_lds(uint64_t base, unsigned v0, unsigned v1, unsigned lds) {
     static_assert(N == 1 || N == 2 || N == 4, "");
     base = (uint64_t)(unsigned)__builtin_amdgcn_readfirstlane((int)(base >> 32)) << 32 | (unsigned)__builtin_amdgcn_readfirstlane((int)base);
+    uint64_t copy;
     if constexpr (N == 1)
-        asm volatile("s_mov_b32 m0, %0\n\ts_waitcnt lgkmcnt(0)\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(v0), "s"(base) : "memory", "m0");
+        asm volatile(LLSA_LOAD_LDS : "=&s"(copy) : "s"(lds), "v"(v0), "s"(base) : "memory", "m0");
     else if constexpr (N == 2)
-        asm volatile("s_mov_b32 m0, %0\n\ts_waitcnt lgkmcnt(0)\n\tglobal_load_lds_dwordx4 %1, %2\n\tglobal_load_lds_dwordx4 %3, %2 offset:1024"
-                     ::"s"(lds), "v"(v0), "s"(base), "v"(v1) : "memory", "m0");
+        asm volatile(LLSA_LOAD_LDS "\n\tglobal_load_lds_dwordx4 %4, %0 offset:1024"
+                     : "=&s"(copy) : "s"(lds), "v"(v0), "s"(base), "v"(v1) : "memory", "m0");
     else
-        asm volatile("s_mov_b32 m0, %0\n\ts_waitcnt lgkmcnt(0)\n\tglobal_load_lds_dwordx4 %1, %2\n\tglobal_load_lds_dwordx4 %3, %2 offset:1024\n\t"
-                     "global_load_lds_dwordx4 %1, %2 offset:2048\n\tglobal_load_lds_dwordx4 %3, %2 offset:3072"
-                     ::"s"(lds), "v"(v0), "s"(base), "v"(v1) : "memory", "m0");
+        asm volatile(LLSA_LOAD_LDS "\n\tglobal_load_lds_dwordx4 %4, %0 offset:1024\n\tglobal_load_lds_dwordx4 %2, %0 offset:2048\n\t"
+                     "global_load_lds_dwordx4 %4, %0 offset:3072"
+                     : "=&s"(copy) : "s"(lds), "v"(v0), "s"(base), "v"(v1) : "memory", "m0");
 }
+#undef LLSA_LOAD_LDS
 #pragma clang diagnostic pop
 // Rows of D bf16 brought into LDS as swz_key wants them, 1024 bytes (512 / D rows) at a time: what a lane adds to the address of the
 // first of them.  Of two 1024 bytes of a 16-row slice in turn (v0, v1): at d = 128 the second four rows have other keys.
