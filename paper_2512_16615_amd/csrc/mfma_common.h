@@ -57,8 +57,8 @@ __device__ __forceinline__ bf16x8 pack8(const f32x4 &a, const f32x4 &b) {
 
 // fp32 values as three bf16 parts, x = p[0] + p[1] + p[2] exactly: each part is the upper half of what the ones before it leave,
 // and each difference is exact.  A product of a bf16 operand with the three parts, summed in fp32, is the product with x itself.
-// (What is not finite stays so, but may become a NaN where it was an infinity: an infinite x has a NaN for its second part, and
-// a part that is 0 times an infinite operand is one.)
+// (Finite values only: an infinite x has a NaN for its second part, and a part that is 0 times an infinite operand is one; the callers
+// look for a NaN.)
 struct Parts3 { bf16x8 p[3]; };
 __device__ __forceinline__ Parts3 split8(const f32x4 &a, const f32x4 &b) {
     union { uint32_t u[4]; bf16x8 v; } r[3];

@@ -10,7 +10,7 @@
 // Bound: the vector instructions (softmax and splitting, about 150 a tile) and the latency of a wave's chain.
 // 16 heads x 2704 tokens, d = 64, 297 tokens a list, against the fp32 matrix instruction on operands straight from memory: forward
 // 54 -> 23 us, dQ 82 -> 24 us.
-#include "tile_common.h"
+#include "tile_f32.h"
 
 namespace llsa {
 
@@ -19,6 +19,10 @@ template <int D> struct BShape {
     static constexpr int NT = D / 16, ROWB = 2 * D, PARTS = D / 8;
     static constexpr int KPU = 64 / PARTS, VCH = 32 / KPU;   // staging: rows per round, rounds per 32 rows
 };
+
+// Where an input is not finite, a part that is 0 meets an infinite row, or an infinite dS has no parts, and the sum is a NaN where
+// the product of fp32 values is an infinity.  So a pass that ends with a NaN in any lane is walked again with the fp32 matrix
+// instruction, whose results then stand (finite inputs give no NaN: they pay for looking, 1 % of a tile's vector instructions).
 
 // contraction step ks of a row as an operand; d = 16 fills half of the 32 slots, the others are zero
 template <int D> __device__ __forceinline__ bf16x8 row_step(const char *row, int g, int ks) {
@@ -30,14 +34,24 @@ template <int D> __device__ __forceinline__ bf16x8 row_zero(bf16x8 x, int g) {
     else return x;
 }
 
-// acc += X^T p with the 32 rows of X at `xt` (swizzled), p in three parts, smallest first
-template <int D>
-__device__ __forceinline__ void add_product(f32x4 (&acc)[D / 16], const char *xt, const TileOffsets<D> &o, const Parts3 &p) {
+// The lane number for a pass: computed from it in the second pass, addresses are not kept in registers throughout the first.
+template <bool Exact> __device__ __forceinline__ int pass_lane(int lane) {
+    if constexpr (Exact) asm volatile("" : "+v"(lane));
+    return lane;
+}
+
+// acc += X^T p with the 32 rows of X at `xt` (swizzled), p in three parts, smallest first (Exact: as it is)
+template <int D, bool Exact>
+__device__ __forceinline__ void add_product(f32x4 (&acc)[D / 16], const char *xt, const TileOffsets<D> &o, const f32x4 (&p)[2], int rows, int g) {
+    Parts3 parts;
+    if constexpr (!Exact) parts = split8(p[0], p[1]);
 #pragma unroll
     for (int n = 0; n < D / 16; ++n) {
         const bf16x8 x = lds_tr_pair(xt + o.tr[n], xt + 32 * D + o.tr[n]);
+        if constexpr (Exact) acc[n] = product_fp32(x, p, rows, g, acc[n]);
+        else
 #pragma unroll
-        for (int i = 2; i >= 0; --i) acc[n] = mfma16(x, p.p[i], acc[n]);
+            for (int i = 2; i >= 0; --i) acc[n] = mfma16(x, parts.p[i], acc[n]);
     }
 }
 
@@ -48,93 +62,101 @@ tile_fwd_bf16_kernel(TokArgs args, const uint16_t *__restrict__ Q, uint16_t *__r
     constexpr int TILE = 32 * S::ROWB;
     __shared__ __attribute__((aligned(16))) char lds[4][2 * TILE];   // per wave: K rows | V rows
     __shared__ __attribute__((aligned(16))) TokTable tabs[4];
-    const int lane = threadIdx.x & 63, i16 = lane & 15, g = lane >> 4;
+    const int lane0 = threadIdx.x & 63, i16 = lane0 & 15, g = lane0 >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const unsigned tile = xcd_contiguous32(blockIdx.x, gridDim.x) * 4 + wave;
     if (tile >= (unsigned)args.total) return;               // the waves of a workgroup never wait for each other
     const tok_args_ptr t = kernel_tok_args();
     const QTile qt = query_tile(args, tile, N);
     TokWalk<S::ROWB> walk;
-    walk.begin(t, qt.bh, qt.blk, lane);
+    walk.begin(t, qt.bh, qt.blk, lane0);
     const int64_t row = qt.row + min(i16, qt.nq - 1);
     char *kt = lds[wave], *vt = kt + TILE;
     TokTable &tab = tabs[wave];
-    const TileOffsets<D> o = tile_offsets<D>(lane);
 
     bf16x8 q[S::KS];
 #pragma unroll
     for (int ks = 0; ks < S::KS; ++ks) q[ks] = row_step<D>(reinterpret_cast<const char *>(Q + row * D), g, ks);
     f32x4 acc[S::NT];
-#pragma unroll
-    for (int n = 0; n < S::NT; ++n) acc[n] = f32x4{0.f, 0.f, 0.f, 0.f};
-    float m = -INFINITY, lsum = 0.f;                        // running maximum; this lane's share of the row sum
+    float m, lsum;                                          // running maximum; this lane's share of the row sum
     const int len = args.len, ntile = (len + 31) >> 5;
     const float scale = args.scale;
 
-    walk.put(tab, t, qt.bh, qt.blk, 0, lane);
-    u32x4 kreg[S::VCH], vreg[S::VCH];
-    auto load = [&](int j) {
+    auto pass = [&](auto exact) {
+        constexpr bool Exact = decltype(exact)::value;
+        const int lane = pass_lane<Exact>(lane0), g = lane >> 4;
+        const TileOffsets<D> o = tile_offsets<D>(lane);
+        m = -INFINITY;
+        lsum = 0.f;
 #pragma unroll
-        for (int u = 0; u < S::VCH; ++u) {
-            const int x = 32 * (j & 1) + lane / S::PARTS + S::KPU * u;
-            kreg[u] = gload<u32x4>(tab.k[x] + (lane % S::PARTS) * 16);
-            vreg[u] = gload<u32x4>(tab.v[x] + (lane % S::PARTS) * 16);
+        for (int n = 0; n < S::NT; ++n) acc[n] = f32x4{0.f, 0.f, 0.f, 0.f};
+        walk.put(tab, t, qt.bh, qt.blk, 0, lane);
+        u32x4 kreg[S::VCH], vreg[S::VCH];
+        auto load = [&](int j) {
+#pragma unroll
+            for (int u = 0; u < S::VCH; ++u) {
+                const int x = 32 * (j & 1) + lane / S::PARTS + S::KPU * u;
+                kreg[u] = gload<u32x4>(tab.k[x] + (lane % S::PARTS) * 16);
+                vreg[u] = gload<u32x4>(tab.v[x] + (lane % S::PARTS) * 16);
+            }
+        };
+        __builtin_amdgcn_wave_barrier();                        // one wave's LDS operations stay in order
+        load(0);
+        for (int j = 0; j < ntile; ++j) {
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int u = 0; u < S::VCH; ++u) {
+                const int r = lane / S::PARTS + S::KPU * u, off = r * S::ROWB + (((lane % S::PARTS) ^ swz_key<D>(r)) << 4);
+                *reinterpret_cast<u32x4 *>(kt + off) = kreg[u];
+                *reinterpret_cast<u32x4 *>(vt + off) = vreg[u];
+            }
+            __builtin_amdgcn_wave_barrier();
+            f32x4 bias[2];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) bias[h] = *reinterpret_cast<const f32x4 *>(&tab.bias[32 * (j & 1) + 16 * h + 4 * g]);
+            if (j + 1 < ntile) {                                // the registers are free: the next rows fly during all of the math
+                if (j & 1) {
+                    __builtin_amdgcn_wave_barrier();
+                    walk.put(tab, t, qt.bh, qt.blk, 32 * (j + 1), lane);
+                    __builtin_amdgcn_wave_barrier();
+                }
+                load(j + 1);
+            }
+            f32x4 s[2];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                s[h] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int ks = 0; ks < S::KS; ++ks) s[h] = mfma16(row_zero<D>(ld_bf16x8(kt + 16 * h * S::ROWB + o.row[ks]), g), q[ks], s[h]);
+            }
+            float mx = -INFINITY;
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    s[h][r] = fmaf(s[h][r], scale, bias[h][r]);
+                    mx = fmaxf(mx, s[h][r]);
+                }
+            mx = rows_max(mx);
+            if (__builtin_amdgcn_ballot_w64(mx > m) != 0) {
+                const float m_new = fmaxf(m, mx), alpha = exp_nat(m - m_new);
+                lsum *= alpha;
+#pragma unroll
+                for (int n = 0; n < S::NT; ++n)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) acc[n][r] *= alpha;
+                m = m_new;
+            }
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) s[h][r] = exp_nat(s[h][r] - m);
+            lsum += ((s[0][0] + s[0][1]) + (s[0][2] + s[0][3])) + ((s[1][0] + s[1][1]) + (s[1][2] + s[1][3]));
+            add_product<D, Exact>(acc, vt, o, s, len - 32 * j, g);
         }
     };
-    __builtin_amdgcn_wave_barrier();                        // one wave's LDS operations stay in order
-    load(0);
-    for (int j = 0; j < ntile; ++j) {
-        __builtin_amdgcn_wave_barrier();
-#pragma unroll
-        for (int u = 0; u < S::VCH; ++u) {
-            const int r = lane / S::PARTS + S::KPU * u, off = r * S::ROWB + (((lane % S::PARTS) ^ swz_key<D>(r)) << 4);
-            *reinterpret_cast<u32x4 *>(kt + off) = kreg[u];
-            *reinterpret_cast<u32x4 *>(vt + off) = vreg[u];
-        }
-        __builtin_amdgcn_wave_barrier();
-        f32x4 bias[2];
-#pragma unroll
-        for (int h = 0; h < 2; ++h) bias[h] = *reinterpret_cast<const f32x4 *>(&tab.bias[32 * (j & 1) + 16 * h + 4 * g]);
-        if (j + 1 < ntile) {                                // the registers are free: the next rows fly during all of the math
-            if (j & 1) {
-                __builtin_amdgcn_wave_barrier();
-                walk.put(tab, t, qt.bh, qt.blk, 32 * (j + 1), lane);
-                __builtin_amdgcn_wave_barrier();
-            }
-            load(j + 1);
-        }
-        f32x4 s[2];
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            s[h] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int ks = 0; ks < S::KS; ++ks) s[h] = mfma16(row_zero<D>(ld_bf16x8(kt + 16 * h * S::ROWB + o.row[ks]), g), q[ks], s[h]);
-        }
-        float mx = -INFINITY;
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                s[h][r] = fmaf(s[h][r], scale, bias[h][r]);
-                mx = fmaxf(mx, s[h][r]);
-            }
-        mx = rows_max(mx);
-        if (__builtin_amdgcn_ballot_w64(mx > m) != 0) {
-            const float m_new = fmaxf(m, mx), alpha = exp_nat(m - m_new);
-            lsum *= alpha;
-#pragma unroll
-            for (int n = 0; n < S::NT; ++n)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) acc[n][r] *= alpha;
-            m = m_new;
-        }
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) s[h][r] = exp_nat(s[h][r] - m);
-        lsum += ((s[0][0] + s[0][1]) + (s[0][2] + s[0][3])) + ((s[1][0] + s[1][1]) + (s[1][2] + s[1][3]));
-        add_product<D>(acc, vt, o, split8(s[0], s[1]));
-    }
+    pass(std::false_type{});
+    if (any_nan(acc)) pass(std::true_type{});
     lsum = rows_sum(lsum);
     if (i16 >= qt.nq) return;
     const float inv = 1.f / lsum;
@@ -161,18 +183,17 @@ tile_dq_bf16_kernel(TokArgs args, const uint16_t *__restrict__ Q, const uint16_t
     constexpr int TILE = 32 * S::ROWB;
     __shared__ __attribute__((aligned(16))) char lds[4][2 * TILE];   // per wave: K rows | V rows
     __shared__ __attribute__((aligned(16))) TokTable tabs[4];
-    const int lane = threadIdx.x & 63, i16 = lane & 15, g = lane >> 4;
+    const int lane0 = threadIdx.x & 63, i16 = lane0 & 15, g = lane0 >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const unsigned tile = xcd_contiguous32(blockIdx.x, gridDim.x) * 4 + wave;
     if (tile >= (unsigned)args.total) return;
     const tok_args_ptr t = kernel_tok_args();
     const QTile qt = query_tile(args, tile, N);
     TokWalk<S::ROWB> walk;
-    walk.begin(t, qt.bh, qt.blk, lane);
+    walk.begin(t, qt.bh, qt.blk, lane0);
     const int64_t row = qt.row + min(i16, qt.nq - 1);
     char *kt = lds[wave], *vt = kt + TILE;
     TokTable &tab = tabs[wave];
-    const TileOffsets<D> o = tile_offsets<D>(lane);
 
     bf16x8 q[S::KS], go[S::KS];
     float delta = 0.f;
@@ -188,60 +209,67 @@ tile_dq_bf16_kernel(TokArgs args, const uint16_t *__restrict__ Q, const uint16_t
     if (g == 0 && i16 < qt.nq) Dsum[row] = delta;
     const float lse = LSE[row], scale = args.scale;
     f32x4 acc[S::NT];
-#pragma unroll
-    for (int n = 0; n < S::NT; ++n) acc[n] = f32x4{0.f, 0.f, 0.f, 0.f};
     const int len = args.len, ntile = (len + 31) >> 5;
 
-    walk.put(tab, t, qt.bh, qt.blk, 0, lane);
-    u32x4 kreg[S::VCH], vreg[S::VCH];
-    auto load = [&](int j) {
+    auto pass = [&](auto exact) {
+        constexpr bool Exact = decltype(exact)::value;
+        const int lane = pass_lane<Exact>(lane0), g = lane >> 4;
+        const TileOffsets<D> o = tile_offsets<D>(lane);
 #pragma unroll
-        for (int u = 0; u < S::VCH; ++u) {
-            const int x = 32 * (j & 1) + lane / S::PARTS + S::KPU * u;
-            kreg[u] = gload<u32x4>(tab.k[x] + (lane % S::PARTS) * 16);
-            vreg[u] = gload<u32x4>(tab.v[x] + (lane % S::PARTS) * 16);
+        for (int n = 0; n < S::NT; ++n) acc[n] = f32x4{0.f, 0.f, 0.f, 0.f};
+        walk.put(tab, t, qt.bh, qt.blk, 0, lane);
+        u32x4 kreg[S::VCH], vreg[S::VCH];
+        auto load = [&](int j) {
+#pragma unroll
+            for (int u = 0; u < S::VCH; ++u) {
+                const int x = 32 * (j & 1) + lane / S::PARTS + S::KPU * u;
+                kreg[u] = gload<u32x4>(tab.k[x] + (lane % S::PARTS) * 16);
+                vreg[u] = gload<u32x4>(tab.v[x] + (lane % S::PARTS) * 16);
+            }
+        };
+        __builtin_amdgcn_wave_barrier();
+        load(0);
+        for (int j = 0; j < ntile; ++j) {
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int u = 0; u < S::VCH; ++u) {
+                const int r = lane / S::PARTS + S::KPU * u, off = r * S::ROWB + (((lane % S::PARTS) ^ swz_key<D>(r)) << 4);
+                *reinterpret_cast<u32x4 *>(kt + off) = kreg[u];
+                *reinterpret_cast<u32x4 *>(vt + off) = vreg[u];
+            }
+            __builtin_amdgcn_wave_barrier();
+            f32x4 bias[2];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) bias[h] = *reinterpret_cast<const f32x4 *>(&tab.bias[32 * (j & 1) + 16 * h + 4 * g]);
+            if (j + 1 < ntile) {                                // the registers are free: the next rows fly during all of the math
+                if (j & 1) {
+                    __builtin_amdgcn_wave_barrier();
+                    walk.put(tab, t, qt.bh, qt.blk, 32 * (j + 1), lane);
+                    __builtin_amdgcn_wave_barrier();
+                }
+                load(j + 1);
+            }
+            f32x4 s[2], dp[2];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                s[h] = f32x4{0.f, 0.f, 0.f, 0.f};
+                dp[h] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int ks = 0; ks < S::KS; ++ks) {
+                    s[h] = mfma16(row_zero<D>(ld_bf16x8(kt + 16 * h * S::ROWB + o.row[ks]), g), q[ks], s[h]);
+                    dp[h] = mfma16(row_zero<D>(ld_bf16x8(vt + 16 * h * S::ROWB + o.row[ks]), g), go[ks], dp[h]);
+                }
+            }
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)                     // past the end of the list: weight -inf, P = 0
+                    s[h][r] = exp_nat(fmaf(s[h][r], scale, bias[h][r]) - lse) * (dp[h][r] - delta);
+            add_product<D, Exact>(acc, kt, o, s, len - 32 * j, g);
         }
     };
-    __builtin_amdgcn_wave_barrier();
-    load(0);
-    for (int j = 0; j < ntile; ++j) {
-        __builtin_amdgcn_wave_barrier();
-#pragma unroll
-        for (int u = 0; u < S::VCH; ++u) {
-            const int r = lane / S::PARTS + S::KPU * u, off = r * S::ROWB + (((lane % S::PARTS) ^ swz_key<D>(r)) << 4);
-            *reinterpret_cast<u32x4 *>(kt + off) = kreg[u];
-            *reinterpret_cast<u32x4 *>(vt + off) = vreg[u];
-        }
-        __builtin_amdgcn_wave_barrier();
-        f32x4 bias[2];
-#pragma unroll
-        for (int h = 0; h < 2; ++h) bias[h] = *reinterpret_cast<const f32x4 *>(&tab.bias[32 * (j & 1) + 16 * h + 4 * g]);
-        if (j + 1 < ntile) {                                // the registers are free: the next rows fly during all of the math
-            if (j & 1) {
-                __builtin_amdgcn_wave_barrier();
-                walk.put(tab, t, qt.bh, qt.blk, 32 * (j + 1), lane);
-                __builtin_amdgcn_wave_barrier();
-            }
-            load(j + 1);
-        }
-        f32x4 s[2], dp[2];
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            s[h] = f32x4{0.f, 0.f, 0.f, 0.f};
-            dp[h] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int ks = 0; ks < S::KS; ++ks) {
-                s[h] = mfma16(row_zero<D>(ld_bf16x8(kt + 16 * h * S::ROWB + o.row[ks]), g), q[ks], s[h]);
-                dp[h] = mfma16(row_zero<D>(ld_bf16x8(vt + 16 * h * S::ROWB + o.row[ks]), g), go[ks], dp[h]);
-            }
-        }
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-#pragma unroll
-            for (int r = 0; r < 4; ++r)                     // past the end of the list: weight -inf, P = 0
-                s[h][r] = exp_nat(fmaf(s[h][r], scale, bias[h][r]) - lse) * (dp[h][r] - delta);
-        add_product<D>(acc, kt, o, split8(s[0], s[1]));
-    }
+    pass(std::false_type{});
+    if (any_nan(acc)) pass(std::true_type{});
     if (i16 >= qt.nq) return;
 #pragma unroll
     for (int n = 0; n < S::NT; ++n)

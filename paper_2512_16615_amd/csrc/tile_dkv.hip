@@ -37,7 +37,7 @@ template <int D> struct MathF32 {
     using S = TShape<D>;
     static constexpr int TQ = 16, CH = D / 4, RPR = 64 / CH, R = 16 / RPR;   // queries, 16-byte chunks a row, rows a round, rounds
     static constexpr int ROWB = 4 * D, BUF = 2 * TQ * ROWB;
-    static constexpr bool AHEAD = D < 128;              // 64 more registers for the next chunk's rows would spill
+    static constexpr bool PARTS = false, AHEAD = D < 128;   // 64 more registers for the next chunk's rows would spill
     static constexpr int NT = D / 16, GS = S::E, NG = S::H, E = S::E;    // sums come in NG groups of GS accumulators
     using RT = RowTile<D>;
     static __device__ __forceinline__ int at(int r, int c) { return RT::at(r, c); }
@@ -45,9 +45,9 @@ template <int D> struct MathF32 {
         RowOp<D> k, v;
         __device__ __forceinline__ void load(const T *kr, const T *vr, int g) { k = row_op<D>(kr, g); v = row_op<D>(vr, g); }
     };
-    template <class Next>
+    template <bool Exact, class Next>
     static __device__ __forceinline__ void tile(const char *buf, const float *st, const Keys &key, f32x4 (&accK)[NT], f32x4 (&accV)[NT],
-                                                float scale, float bias, int i16, int g, Next next) {
+                                                float scale, float bias, unsigned, int i16, int g, Next next) {
         f32x4 s = row_product<D>(RT::row(buf, i16, g), key.k);
         f32x4 dp = row_product<D>(RT::row(buf + TQ * ROWB, i16, g), key.v);
         const f32x4 lse = *reinterpret_cast<const f32x4 *>(st + 4 * g), dl = *reinterpret_cast<const f32x4 *>(st + TQ + 4 * g);
@@ -77,7 +77,7 @@ template <int D> struct MathBF16 {
     using T = uint16_t;
     static constexpr int TQ = 32, CH = D / 8, RPR = 64 / CH, R = 32 / RPR;
     static constexpr int ROWB = 2 * D, BUF = 2 * TQ * ROWB;
-    static constexpr bool AHEAD = true;
+    static constexpr bool PARTS = true, AHEAD = true;
     static constexpr int KS = (D + 31) / 32, NT = D / 16, GS = 1, NG = NT, E = 4;
     static __device__ __forceinline__ int at(int r, int c) { return r * ROWB + ((c ^ swz_key<D>(r)) << 4); }
     // d = 16 fills half of the 32 contraction slots, the others are zero
@@ -93,9 +93,10 @@ template <int D> struct MathBF16 {
             for (int ks = 0; ks < KS; ++ks) { k[ks] = half(ld_bf16x8(kr + c + 32 * ks), g); v[ks] = half(ld_bf16x8(vr + c + 32 * ks), g); }
         }
     };
-    template <class Next>
+    // rows: how many of the 32 queries exist.  Exact: P and dS as they are on the fp32 matrix instruction (inputs that are not finite)
+    template <bool Exact, class Next>
     static __device__ __forceinline__ void tile(const char *buf, const float *st, const Keys &key, f32x4 (&accK)[NT], f32x4 (&accV)[NT],
-                                                float scale, float bias, int i16, int g, Next next) {
+                                                float scale, float bias, unsigned rows, int i16, int g, Next next) {
         const char *gbuf = buf + TQ * ROWB;
         const TileOffsets<D> o = tile_offsets<D>(16 * g + i16);
         f32x4 s[2], dp[2], lse[2], dl[2];
@@ -119,16 +120,21 @@ template <int D> struct MathBF16 {
                 s[h][r] = exp_nat(fmaf(s[h][r], scale, bias) - lse[h][r]);
                 dp[h][r] = s[h][r] * (dp[h][r] - dl[h][r]);
             }
-        const Parts3 p = split8(s[0], s[1]), ds = split8(dp[0], dp[1]);
+        Parts3 p, ds;
+        if constexpr (!Exact) p = split8(s[0], s[1]), ds = split8(dp[0], dp[1]);
 #pragma unroll
         for (int n = 0; n < NT; ++n) {
             const bf16x8 tg = lds_tr_pair(gbuf + o.tr[n], gbuf + 16 * ROWB + o.tr[n]);
             const bf16x8 tq = lds_tr_pair(buf + o.tr[n], buf + 16 * ROWB + o.tr[n]);
+            if constexpr (Exact) {
+                accV[n] = product_fp32(tg, s, (int)min(rows, 32u), g, accV[n]);
+                accK[n] = product_fp32(tq, dp, (int)min(rows, 32u), g, accK[n]);
+            } else
 #pragma unroll
-            for (int i = 2; i >= 0; --i) {
-                accV[n] = mfma16(tg, p.p[i], accV[n]);
-                accK[n] = mfma16(tq, ds.p[i], accK[n]);
-            }
+                for (int i = 2; i >= 0; --i) {
+                    accV[n] = mfma16(tg, p.p[i], accV[n]);
+                    accK[n] = mfma16(tq, ds.p[i], accK[n]);
+                }
         }
     }
     template <class Emit> static __device__ __forceinline__ void emit(const f32x4 (&t)[GS], int h, int g, Emit f) {
@@ -148,13 +154,15 @@ __device__ __forceinline__ QueryList query_list(const DkvTileLevel &L, int64_t b
     return q;
 }
 
-// Chunks c_beg, c_beg + step, ... < c_end of a list against one key tile, added to accK / accV.
-template <class M>
+// Chunks c_beg, c_beg + step, ... < c_end of a list against one key tile: their sums accK / accV.
+template <class M, bool Exact>
 __device__ __forceinline__ void accumulate(const DkvTileArgs &a, const typename M::T *Q, const typename M::T *dO, const float *LSE,
                                            const float *Dsum, int64_t bh, const QueryList &ql, FastDiv span, float bias, unsigned c_beg,
                                            unsigned step, unsigned c_end, const typename M::Keys &key, f32x4 (&accK)[M::NT],
                                            f32x4 (&accV)[M::NT], char *buf, float *st, int lane) {
     constexpr int TQ = M::TQ;
+#pragma unroll
+    for (int n = 0; n < M::NT; ++n) { accK[n] = f32x4{0.f, 0.f, 0.f, 0.f}; accV[n] = f32x4{0.f, 0.f, 0.f, 0.f}; }
     if (c_beg >= c_end) return;
     const char *Qb = reinterpret_cast<const char *>(Q) + bh * a.N * M::ROWB, *Gb = reinterpret_cast<const char *>(dO) + bh * a.N * M::ROWB;
     const float *stat_src = (lane & TQ ? Dsum : LSE) + bh * a.N;
@@ -196,7 +204,7 @@ __device__ __forceinline__ void accumulate(const DkvTileArgs &a, const typename 
         }
         if (lane < 2 * TQ) st[lane] = stat;
         __builtin_amdgcn_wave_barrier();
-        M::tile(buf, st, key, accK, accV, a.scale, bias, lane & 15, lane >> 4, [&]() {
+        M::template tile<Exact>(buf, st, key, accK, accV, a.scale, bias, ql.count - TQ * c, lane & 15, lane >> 4, [&]() {
             if (M::AHEAD && c + step < c_end) {
                 load(qi, c + step);
                 qi = query(min(c + 2 * step, c_end - 1));
@@ -234,13 +242,12 @@ tile_dkv_kernel(DkvTileArgs a, const typename M::T *__restrict__ Q, const typena
     const QueryList ql = query_list(L, bh, blk, a.N);
     const unsigned chunks = (ql.count + M::TQ - 1) / M::TQ;
     const unsigned c_beg = (unsigned)((uint64_t)chunks * split / L.splits.d), c_end = (unsigned)((uint64_t)chunks * (split + 1) / L.splits.d);
-#pragma unroll
-    for (int n = 0; n < NT; ++n) { accK[n] = f32x4{0.f, 0.f, 0.f, 0.f}; accV[n] = f32x4{0.f, 0.f, 0.f, 0.f}; }
-    if (c_beg + wave < c_end) {
-        typename M::Keys key;
-        key.load(static_cast<const T *>(L.K) + krow * D, static_cast<const T *>(L.V) + krow * D, g);
-        accumulate<M>(a, Q, dO, LSE, Dsum, bh, ql, L.span, L.bias, c_beg + wave, 4, c_end, key, accK, accV, buf, st, lane);
-    }
+    typename M::Keys key;
+    if (c_beg + wave < c_end) key.load(static_cast<const T *>(L.K) + krow * D, static_cast<const T *>(L.V) + krow * D, g);
+    accumulate<M, false>(a, Q, dO, LSE, Dsum, bh, ql, L.span, L.bias, c_beg + wave, 4, c_end, key, accK, accV, buf, st, lane);
+    if constexpr (M::PARTS)                                 // an input is not finite (tile_bf16.hip says why)
+        if (any_nan(accK) || any_nan(accV))
+            accumulate<M, true>(a, Q, dO, LSE, Dsum, bh, ql, L.span, L.bias, c_beg + wave, 4, c_end, key, accK, accV, buf, st, lane);
     // the four waves' sums in wave order; wave w finishes groups w, w + 4, ... of [dK | dV]
     __syncthreads();                                        // everyone is done with the tile buffers
 #pragma unroll

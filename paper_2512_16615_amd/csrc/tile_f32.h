@@ -89,6 +89,28 @@ template <int D> struct RowTile {
     }
 };
 
+// bf16 tiles, where an input is not finite: acc += x^T p with fp32 operands.  x: 16 channels of 32 rows as two transposing reads leave
+// them (lds_tr_pair; slots 4h .. 4h + 3: rows 16h + 4g ..), of which the first `rows` exist; the others count as zeros.
+__device__ __forceinline__ f32x4 product_fp32(bf16x8 x, const f32x4 (&p)[2], int rows, int g, f32x4 acc) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const bool row = 16 * h + 4 * g + r < rows;
+            acc = mfma4(row ? (float)x[4 * h + r] : 0.f, row ? p[h][r] : 0.f, acc);
+        }
+    __builtin_amdgcn_sched_barrier(0);                      // one operand at a time: this is no place to spend registers
+    return acc;
+}
+// is one of these sums a NaN in any lane of the wave (or the sum of infinities of both signs)?
+template <int n> __device__ __forceinline__ bool any_nan(const f32x4 (&acc)[n]) {
+    f32x4 x = acc[0];
+#pragma unroll
+    for (int i = 1; i < n; ++i) x += acc[i];
+    const float y = (x[0] + x[1]) + (x[2] + x[3]);
+    return __builtin_amdgcn_ballot_w64(y != y) != 0;
+}
+
 // the lane's results of a second product: channels 16 E h + E (4g + r) .. + E - 1 of column i16, handed out as vectors
 template <int D, class Emit> __device__ __forceinline__ void col_emit(const f32x4 (&acc)[D / 16], int g, Emit emit) {
     using S = TShape<D>;

@@ -364,3 +364,61 @@ def test_level1_sums_carried_to_the_query_block_below(K, d, side):
     assert abs(float(want[0].sum()) / N - 1) < 1e-5
     # P rounded to bf16 (2^-9 each, of a sum of positive terms) and dV rounded once
     assert float(((got - want[0][:, None]).abs() - 2.0 ** -8 * want[0][:, None]).max()) < 1e-3
+
+
+def _all_listed_64(plan, ws, Q, K, V, O, dO):
+    """Attention and gradients in 64 bits where every block is listed: softmax over all tokens and, with Le = 1, the pooled ones.  D from
+    the O given, as in the backward."""
+    import math
+    import torch
+    q, k, v, o, g = (x.double().cpu() for x in (Q, K, V, O, dO))
+    bias = torch.zeros(plan.N, dtype=torch.float64)
+    if plan.Le:
+        k, v = (torch.cat([x, plan.pyramid_level(ws, i, 1).double().cpu()], 2) for x, i in ((k, 1), (v, 2)))
+        bias = torch.cat([bias, torch.full((plan.N // plan.B,), math.log(plan.B), dtype=torch.float64)])
+    scale = plan.d ** -0.5
+    P = torch.softmax(torch.matmul(q, k.transpose(2, 3)) * scale + bias, -1)
+    dS = P * (torch.matmul(g, v.transpose(2, 3)) - (g * o).sum(-1, keepdim=True)) * scale
+    out = {"O": torch.matmul(P, v), "dQ": torch.matmul(dS, k), "dK": torch.matmul(dS.transpose(2, 3), q), "dV": torch.matmul(P.transpose(2, 3), g)}
+    if plan.Le:
+        for n in ("dK", "dV"):
+            out[n] = out[n][:, :, :plan.N] + out[n][:, :, plan.N:].repeat_interleave(plan.B, 2) / plan.B
+    return out
+
+
+def _check_infinities(got, want, tol=2e-2):
+    """An infinity where 64 bits give one, a value where they give one (where they give a NaN, anything)."""
+    import torch
+    for n, t in got.items():
+        x, w = t.double().cpu(), want[n]
+        inf, fin = torch.isinf(w), torch.isfinite(w)
+        assert torch.equal(x[inf], w[inf]), f"{n}: {int((x[inf] != w[inf]).sum())} of {int(inf.sum())} infinities are something else"
+        assert bool(((x[fin] - w[fin]).abs() <= tol).all()), n
+
+
+@pytest.mark.parametrize("d,B,N,Le,path", [
+    # lists of an odd multiple of 16 tokens (half a tile of 32 past the end), with and without a dense level, every channel count, lists
+    # that end inside 16 tokens, a length that the bf16 MFMA kernels take
+    (64, 16, 144, 0, 0), (64, 16, 144, 1, 0), (128, 16, 144, 0, 0), (32, 8, 104, 0, 0), (16, 16, 80, 1, 0), (64, 5, 105, 1, 0),
+    (128, 20, 180, 1, 0), (64, 16, 512, 1, 1), (16, 4, 208, 0, 0), (64, 32, 96, 0, 0),
+])
+def test_infinite_values_in_bf16_tiles(d, B, N, Le, path):
+    """bf16 shapes in fp32 arithmetic, whose P and dS enter their products in three parts: an infinite row times a part that is 0, or
+    an infinite dS, must not become a NaN.  Heads: an infinite V at the last key; at another; an infinite dO at the last query; at
+    another; neither.  A query of zeros has P = 1 before the sum: two of its parts are 0."""
+    import torch
+    from paper_2512_16615_amd import llsa
+    gen = torch.Generator().manual_seed(N + d)
+    Q, K, V, dO = torch.randn(4, 1, 5, N, d, generator=gen)
+    c = d // 2 + 1
+    Q[..., 0], dO[..., c] = Q[..., 0].abs() + 0.1, dO[..., c].abs() + 0.1     # so that infinite dS add up with one sign
+    Q[:, :, 3] = 0
+    V[:, 0, N - 1, c] = V[:, 1, 7, c] = dO[:, 2, N - 1, c] = float("inf")
+    dO[:, 3, 5, c] = float("-inf")
+    Q, K, V, dO = (x.bfloat16().cuda() for x in (Q, K, V, dO))
+    plan = llsa.Plan(1, 5, N, d, B, N // B, 1, Le=Le, kernel_path=path)
+    O, LSE, idx, ws = llsa.forward(plan, Q, K, V, workspace=plan.alloc_workspace(True))
+    got = dict(zip(("dQ", "dK", "dV"), llsa.backward(plan, Q, K, V, O, LSE, idx, dO, ws)), O=O)
+    want = _all_listed_64(plan, ws, Q, K, V, O, dO)
+    assert int(torch.isinf(want["O"]).sum()) and int(torch.isinf(want["dV"]).sum()) and int(torch.isinf(want["dK"]).sum())
+    _check_infinities(got, want)
