@@ -601,7 +601,12 @@ hipError_t launch_dkv_group(const Plan &p, const LevelTable &t, const void *Q, c
     if (G) {                                                // levels >= 2 in their own kernel
         GroupArgs up = a;
         up.lev_end = top + 1;
-        const int share = up.nbs > 8 && p.d == 64 ? 16 : 8;
+        // d = 64: 16 listed blocks to a workgroup, two a wave, where that fills the passes.  A last pass of 8 or fewer keeps one wave in two
+        // busy or less, at the one workgroup a CU that the registers of two blocks allow: 8 to a workgroup then, of which two fit.
+        // Backward, 16 / 8 to a workgroup: 8 heads x 589824 tokens (17 blocks) 5264 / 5081 us, Gaussian 5610 / 5320, 16 x 66560 (17)
+        // 1198 / 1095, 16 x 69632, K = 16 (18) 1726 / 1588; 8 x 131072 (32) 1215 / 1258, 16 x 33280 (9) 309 / 323.
+        const bool rest = up.nbs > 16 && (up.nbs - 1) % 16 < 8;
+        const int share = p.d == 64 && up.nbs > 8 && !rest ? 16 : 8;
         up.passes = max(1, (up.nbs + share - 1) / share);
         const dim3 grid((unsigned)(p.bh * (NR / G) * up.passes));
         if (p.d == 128) dkv_upper_kernel<128, 1, false><<<grid, 512, 0, s>>>(t, up);

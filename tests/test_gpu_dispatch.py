@@ -323,6 +323,62 @@ def test_level1_sums_carried_through_several_query_blocks(heads, K, d):
             assert torch.equal(t[:, h::2], t[:, h:h + 1].expand_as(t[:, h::2])), n
 
 
+def _key_gradients_64(plan, ws, idx, Q, K, V, O, LSE, dO):
+    """dK and dV of head 0 in 64 bits from the forward's lists, pooled levels, O and logsumexp, and the root of the sum of the squares of
+    the terms that each of their elements adds up."""
+    import math
+    import torch
+    B, N, d, scale = plan.B, plan.N, plan.d, plan.d ** -0.5
+    q, g, lse = Q[0, 0].double(), dO[0, 0].double(), LSE[0, 0].double()
+    D = (g * O[0, 0].double()).sum(-1)
+    levels = []
+    for l in range(plan.Le + 1):
+        k, v = ((t if l == 0 else plan.pyramid_level(ws, x, l))[0, 0].double() for t, x in ((K, 1), (V, 2)))
+        toks = torch.arange(len(k), device="cuda")[None]
+        if l < plan.L:
+            toks = (plan.level_indices(idx, l)[0, 0].long()[:, :, None] * B + torch.arange(B, device="cuda")).flatten(1)
+        rows, n, T = len(toks), N // len(toks), toks.shape[1]
+        dk, dv, k2, v2 = (torch.zeros_like(k) for _ in range(4))
+        c = min(n, 4096)
+        step = max(1, (1 << 24) // (T * max(c, d)))
+        for r in range(0, rows, step):
+            tk = toks[r:r + step]
+            kt, vt = k[tk].transpose(1, 2).contiguous(), v[tk].transpose(1, 2).contiguous()
+            for x in range(0, n, c):
+                qq, gg, ll, dd = (t.view(rows, n, -1)[r:r + step, x:x + c] for t in (q, g, lse, D))
+                P = torch.exp(torch.matmul(qq, kt) * scale + l * math.log(B) - ll)
+                dS = P * (torch.matmul(gg, vt) - dd) * scale
+                for out, w, t in ((dk, dS, qq), (dv, P, gg), (k2, dS * dS, qq * qq), (v2, P * P, gg * gg)):
+                    out.index_add_(0, tk.flatten(), torch.matmul(w.transpose(1, 2), t.contiguous()).flatten(0, 1))
+        levels.append([dk, dv, k2, v2])
+    for l in range(plan.Le, 0, -1):
+        for x in range(4):
+            levels[l - 1][x] += levels[l][x].repeat_interleave(B, 0) / (B if x < 2 else B * B)
+    return {"dK": (levels[0][0], levels[0][2].sqrt()), "dV": (levels[0][1], levels[0][3].sqrt())}
+
+
+def _check_key_gradients(N, d, K, L, heads, side):
+    """Heads alike, so that one is enough for 64 bits.  dS and P enter their products rounded to bf16 (each term off by up to 2^-9 of
+    itself, independently: 2^-9 / sqrt(3) of the root of the sum of their squares, of which 8 are allowed for the largest of some
+    10^7 elements), the result is rounded once, and fp32 sums and exponentials are off by some 1e-6 of values of up to 10."""
+    import torch
+    from paper_2512_16615_amd import llsa
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(K)
+    rand = lambda *shape: torch.randn(*shape, generator=gen, device="cuda")
+    y, x = torch.meshgrid(torch.arange(N // side, device="cuda"), torch.arange(side, device="cuda"), indexing="ij")
+    wave = torch.stack([torch.sin(2 * torch.pi * (a * x + b * y) / side + c) for a, b, c in [(1, 0, 0), (0, 1, 1), (2, 1, 2), (1, 2, 3)]], -1)
+    Q, Kt = (wave.reshape(N, 4) @ rand(4, d) + 0.1 * rand(N, d) for _ in range(2))
+    Q, Kt, V, dO = (t.bfloat16().expand(1, heads, N, d).contiguous() for t in (Q, Kt, rand(N, d), rand(N, d)))
+    plan = llsa.Plan(1, heads, N, d, 16, K, L)
+    O, LSE, idx, ws = llsa.forward(plan, Q, Kt, V, workspace=plan.alloc_workspace(True))
+    got = dict(zip(("dK", "dV"), llsa.backward(plan, Q, Kt, V, O, LSE, idx, dO, ws)[1:]))
+    for n, (want, rms) in _key_gradients_64(plan, ws, idx, Q, Kt, V, O, LSE, dO).items():
+        assert torch.equal(got[n], got[n][:, :1].expand_as(got[n])), n
+        over = (got[n][0, 0].double() - want).abs() - (8 / 3 ** 0.5 * 2.0 ** -9 * rms + 2.0 ** -8 * want.abs())
+        assert float(over.max()) < 5e-6, n
+
+
 @pytest.mark.parametrize("K,d,side", [(8, 64, 512), (12, 64, 512), (16, 128, 512), (5, 64, 1024)])
 def test_level1_sums_carried_to_the_query_block_below(K, d, side):
     """Chains of query blocks 2 (262144 tokens) and 4 (1048576) apart, whose partials the gather finds: dV with all of dO equal to 1 sums to the
@@ -364,6 +420,13 @@ def test_level1_sums_carried_to_the_query_block_below(K, d, side):
     assert abs(float(want[0].sum()) / N - 1) < 1e-5
     # P rounded to bf16 (2^-9 each, of a sum of positive terms) and dV rounded once
     assert float(((got - want[0][:, None]).abs() - 2.0 ** -8 * want[0][:, None]).max()) < 1e-3
+
+
+@pytest.mark.parametrize("N,d,K,L", [(260 * 256, 64, 4, 2), (262144, 64, 20, 4), (262144, 128, 20, 4), (36864, 64, 12, 3), (139264, 64, 16, 3)])
+def test_listed_blocks_of_the_upper_levels_shared_by_workgroups(N, d, K, L):
+    """Listed blocks of levels >= 2 of a query group: 17 (three workgroups of eight, the last with a ragged block of four tokens), 24 and a
+    dense block that all waves share (three of eight, the first takes it), 24 at d = 128, 13 (one of 16), 18 (three of eight)."""
+    _check_key_gradients(N, d, K, L, heads=2, side=256)
 
 
 def _all_listed_64(plan, ws, Q, K, V, O, dO):
