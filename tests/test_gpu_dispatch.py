@@ -272,14 +272,32 @@ def test_key_blocks_of_several_tiles(cfg):
 
 
 @pytest.mark.parametrize("cfg", [
-    # query tiles per wave: a chip full of workgroups whose last one per head is ragged (25 query tiles, blocks of 32 and of 64),
-    # lists longer than a pair of tiles may have, blocks of 32 at d = 128
-    _bf16("B16_1024_wgs", 400, heads=256),
-    _bf16("B32_1024_wgs", 416, heads=256, B=32, K=3),
-    _bf16("B64_1026_wgs", 320, heads=342, B=64, K=2),
+    # the fp32-arithmetic kernels (no multiple of 64) on a chip full of query tiles, on lists of 33 blocks, on blocks of two tiles
+    _bf16("B16_400_heads256", 400, heads=256),
+    _bf16("B32_416_heads256", 416, heads=256, B=32, K=3),
     _bf16("K33", 16 * 43, heads=2, K=33),
     _bf16("K33_d128", 16 * 43, heads=2, K=33, d=128),
     _bf16("B32_odd_d128", 32 * 21, heads=2, B=32, K=5, d=128),
+], ids=lambda c: c["name"])
+def test_bf16_tiles_by_size(cfg):
+    _full_parity(cfg, 0xD160)
+
+
+@pytest.mark.parametrize("cfg", [
+    # query tiles per wave of the shared forward (multiples of 256) and dQ (of 64): from 1024 workgroups on two at d = 64, the
+    # last workgroup of a head ragged, blocks of 16, 32 and 64; lists longer than a pair of tiles may have (33 and 64 blocks)
+    # at d = 64 and, with 128 KB of rows in LDS, at d = 128, spare waves among them (1088 tokens); blocks of 32 at d = 128
+    _bf16("B16_1024_wgs", 448, heads=256),
+    _bf16("B32_1024_wgs", 448, heads=256, B=32, K=3),
+    _bf16("B64_1026_wgs", 320, heads=342, B=64, K=2),
+    _bf16("B16_256_1024_wgs", 256, heads=512),
+    _bf16("K33", 1024, heads=2, K=33),
+    _bf16("K33_d128", 1024, heads=2, K=33, d=128),
+    _bf16("K64_d128", 1280, heads=2, K=64, d=128),
+    _bf16("K33_d128_17", 1088, heads=2, K=33, d=128),
+    _bf16("K64_d128_17", 1088, heads=2, K=64, d=128),
+    _bf16("B32_d128_11", 32 * 22, heads=2, B=32, K=5, d=128),
+    _bf16("B32_d128", 1280, heads=2, B=32, K=32, d=128),
 ], ids=lambda c: c["name"])
 def test_query_tiles_per_wave(cfg):
     _full_parity(cfg, 0xD160)
@@ -287,7 +305,7 @@ def test_query_tiles_per_wave(cfg):
 
 @pytest.mark.parametrize("cfg", [
     # level-1 dK/dV carried along 2 or 4 query blocks (heads x level-1 query blocks >= 1024): rows shorter than the register
-    # slots, rows of all slots, rows one too long for it, at d = 64 and 128
+    # slots, rows of all slots, rows that two workgroups share, at d = 64 and 128
     _bf16("chain_K3", 8192, L=2, heads=32, K=3),
     _bf16("chain_K4", 8192, L=2, heads=64, K=4),
     _bf16("chain_K6", 8192, L=2, heads=32, K=6),
@@ -379,47 +397,10 @@ def _check_key_gradients(N, d, K, L, heads, side):
         assert float(over.max()) < 5e-6, n
 
 
-@pytest.mark.parametrize("K,d,side", [(8, 64, 512), (12, 64, 512), (16, 128, 512), (5, 64, 1024)])
+@pytest.mark.parametrize("K,d,side", [(8, 64, 512), (12, 64, 512), (16, 128, 512), (5, 64, 1024), (12, 64, 1024), (8, 128, 1024)])
 def test_level1_sums_carried_to_the_query_block_below(K, d, side):
-    """Chains of query blocks 2 (262144 tokens) and 4 (1048576) apart, whose partials the gather finds: dV with all of dO equal to 1 sums to the
-    number of queries, and every token's dV is that of a computation in 64 bits from the lists and the logsumexp."""
-    import torch
-    from paper_2512_16615_amd import llsa
-    N, L = side * side, 2
-    gen = torch.Generator().manual_seed(K)
-    y, x = torch.meshgrid(torch.arange(side), torch.arange(side), indexing="ij")
-    wave = torch.stack([torch.sin(2 * torch.pi * (a * x + b * y) / side + c) for a, b, c in [(1, 0, 0), (0, 1, 1), (2, 1, 2), (1, 2, 3)]], -1)
-    Q, Kt = ((wave.reshape(N, 4) @ torch.randn(4, d, generator=gen) + 0.1 * torch.randn(N, d, generator=gen)).bfloat16().cuda()[None, None]
-             for _ in range(2))
-    V = torch.randn(1, 1, N, d, generator=gen).bfloat16().cuda()
-    dO = torch.ones_like(V)
-    heads = 16 if side == 512 else 8                         # heads enough for chains of at least two
-    Q, Kt, V, dO = (t.expand(1, heads, N, d).contiguous() for t in (Q, Kt, V, dO))
-    plan = llsa.Plan(1, heads, N, d, 16, K, L)
-    O, LSE, idx, ws = llsa.forward(plan, Q, Kt, V, workspace=plan.alloc_workspace(True))
-    dV = llsa.backward(plan, Q, Kt, V, O, LSE, idx, dO, ws)[2]
-    assert torch.equal(dV, dV[:, :1].expand_as(dV))
-    q, lse = Q[0, 0].double(), LSE[0, 0].double()
-    kp = [Kt[0, 0].double()] + [plan.pyramid_level(ws, 1, l)[0, 0].double() for l in (1, 2)]
-    want = [torch.zeros(N >> 4 * l, dtype=torch.float64, device="cuda") for l in range(3)]   # sum over queries of P, per token of a level
-    for l in range(3):
-        rows = N >> 4 * (l + 1) if l < L else 1
-        toks = (plan.level_indices(idx, l)[0, 0].long()[:, :, None] * 16 + torch.arange(16, device="cuda")).reshape(rows, -1) if l < L else \
-            torch.arange(N >> 4 * l, device="cuda")[None]
-        step = max(1, min(rows, (1 << 24) // (toks.shape[1] * d)))
-        for r in range(0, rows, step):
-            tk, n = toks[r:r + step], N // rows
-            for c in range(0, n, 4096):
-                qq = q.view(rows, n, d)[r:r + step, c:c + 4096]
-                z = torch.matmul(qq, kp[l][tk].transpose(1, 2).contiguous()) * d ** -0.5 + l * 2.772588722239781
-                p = torch.exp(z - lse.view(rows, n)[r:r + step, c:c + 4096, None]).sum(1)
-                want[l].index_add_(0, tk.reshape(-1), p.reshape(-1))
-    for l in (1, 0):
-        want[l] += want[l + 1].repeat_interleave(16) / 16
-    got = dV[0, 0].double()
-    assert abs(float(want[0].sum()) / N - 1) < 1e-5
-    # P rounded to bf16 (2^-9 each, of a sum of positive terms) and dV rounded once
-    assert float(((got - want[0][:, None]).abs() - 2.0 ** -8 * want[0][:, None]).max()) < 1e-3
+    """Chains of query blocks 2 (262144 tokens) and 4 (1048576) apart, whose partials the gather finds."""
+    _check_key_gradients(side * side, d, K, 2, heads=4 if side == 512 else 2, side=side)
 
 
 @pytest.mark.parametrize("N,d,K,L", [(260 * 256, 64, 4, 2), (262144, 64, 20, 4), (262144, 128, 20, 4), (36864, 64, 12, 3), (139264, 64, 16, 3)])

@@ -62,8 +62,9 @@ def test_n1048576_d64_L4():
 
 
 @pytest.mark.timeout(600)
-def test_n1048576_K16_two_upper_launches():
-    """K = 16 at L = 4: 32 listed blocks at levels 2 and 3, which the upper-level dK/dV kernel takes in two launches."""
+def test_n1048576_K16_two_upper_shares():
+    """K = 16 at L = 4: 32 listed blocks at levels 2 and 3, which two workgroups of the upper-level dK/dV kernel share, 16 each, and a
+    dense block, which the first of them takes."""
     cfg = dict(BASE, name="n1048576_K16", N=1048576, heads=1, L=4, K=16)
     _run(cfg, 0x115A2070, heads=[(0, 0)], n_row_chunks=2)
 
