@@ -13,7 +13,9 @@
 //     fetched as whole cache lines and reach the operand layouts through the wave's private LDS tiles.
 // All rows go from memory straight into LDS (load_lds): through registers and LDS writes the writes alone held the LDS for a third
 // (d = 64) to half (d = 128) of the kernel's time.  16 heads x 65536 tokens, d = 64, K = 8: 204 -> 195 us; 8 x 65536, d = 128, K = 16:
-// 362 -> 328; 8 x 262144: 1510 -> 1390.  What is left of it, d = 64: 21 % of the matrix pipe, half of the vector issue slots; level 0 by
+// 362 -> 328; 8 x 262144: 1510 -> 1390.  Not so for Gaussian inputs, whose rows come from all over the head, from 32768 tokens on and for
+// blocks of 64 with K <= 4 at 65536: the forward call takes 1 to 2 % longer (16 heads x 65536, Gaussian 348 -> 352 us), asking for K rows before
+// V's operands are read changes nothing.  What is left, d = 64: 21 % of the matrix pipe, half of the vector issue slots; level 0 by
 // itself (Le = 0) takes 162 us as before, at a third of the rate its gathers reach without any arithmetic.
 // Score tiles are computed transposed (S^T = K Q^T) so that the accumulator layout (4 keys x 1 query per
 // lane) is the B operand of O^T += V^T P^T; see mfma_common.h for the register layouts.

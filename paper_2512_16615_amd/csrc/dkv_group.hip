@@ -461,8 +461,12 @@ static int upper_G(const Plan &p) {
 // is given.
 // GS: 256 tokens of a square grid in raster order are a row's part from 262144 tokens on, and the query block next to R in the
 // list of tokens lies beside it, 256 pixels away; the one below it, which lists 90 % of the same blocks on smooth inputs where
-// the next one lists 3 to 11 %, is sqrt(N) / 256 further on.  On other grids it only costs what the shared blocks would have saved.
-// Coarse stage, before (one workgroup per query block where a row has more than 8 blocks, GS = 1) and after: 8 heads x 262144 tokens, K = 16,
+// the next one lists 3 to 11 %, is sqrt(N) / 256 further on.  GS is the power of two below that: it meets the block below on sides of
+// 256 2^k and no better one than GS = 1 on others.  In nested-patch order the next block is the nearest, and GS > 1 costs a little.
+// Backward, d = 64, K = 8, no chains / GS = 1 / 2 / 4, us: 8 heads x 512^2 raster 1974 / 1953 / 1730 / -, nested 2035 / 1887 / 1916 / -,
+// Gaussian 2157 / 2149 / 2131 / -; 4 x 1024^2 raster 4878 / 4769 / 4718 / 4320, nested 4767 / 4429 / 4485 / 4548, Gaussian
+// 4607 / 4599 / 4610 / 4595; 8 x 768^2 raster 5522 / 5449 / 5395 / - (GS = 3: 5036).
+// Coarse stage, GS = 1 (rows of more than 8 blocks: one workgroup per query block) and as it is: 8 heads x 262144 tokens, K = 16,
 // d = 128 2860 -> 2166 us; d = 64, K = 8 800 -> 587; 16 heads x 65536, K = 16 621 -> 425, Gaussian inputs 617 -> 611.
 // With chains and without, GS = 1, steps: 16 heads x 65536 tokens, smooth K = 4 958 -> 875 us, K = 6 1105 -> 1017, d = 128 2677 ->
 // 2463; Gaussian, which share few blocks: K = 4 970 -> 951, d = 128 2903 -> 2868.

@@ -362,7 +362,8 @@ int dkv_splits(const Plan &p, int l) {
 // Beyond, 4 tiles.  us at distance 1 / 4 / N / 64, smooth inputs, K = 8: 16 x 4096 tokens 34.2 / 35.3 / 28.0, 32 x 16384
 // 169 / 156 / 149, 16 x 16384 with d = 128 172 / 156 / 150, 16 x 32768 156 / 160 / 154, 16 x 65536 305 / 299 / 316, 4 x 262144
 // 349 / 312 / 472, 8 x 262144 with d = 128 and K = 16 1666 / 1634 / 2475; gaussian 8 x 16384 48.0 / 48.8 / 47.5, 16 x 65536
-// 328 / 331 / 334.
+// 328 / 331 / 334.  All of them in raster order; in nested-patch order a quarter of the head is the better one at any length (backward
+// at 8 x 262144, d = 64, K = 8: 1930 / 1922 / 1862), but the plan does not know the order.
 static unsigned fine_apart(const Plan &p) {
     const int64_t tiles = p.N / 16;
     if (p.N * p.d * 4 <= (int64_t)8 << 20) return (unsigned)(tiles / 4);

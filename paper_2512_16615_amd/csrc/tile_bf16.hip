@@ -6,7 +6,8 @@
 // instructions of 16 cycles per 32 keys where the fp32 one takes eight of 32.  One wave per tile of up to 16 queries, 32 keys at a
 // time; K and V rows are fetched whole (the operand layout straight from memory, 16 rows x half a line per instruction, caps
 // gathers at a third of what the L2 delivers: 26 us each for the figures below) and go through the wave's LDS, rows swizzled.
-// The next 32 keys' rows are in flight during the current ones' math, the list entries a chunk of 64 ahead.
+// The next 32 keys' rows are in flight during the current ones' math.  List entries are fetched for 64 blocks at a time, when the walk
+// comes to them: a list of more than 64 blocks waits for one load every 64 blocks.
 // Bound: the vector instructions (softmax and splitting, about 150 a tile) and the latency of a wave's chain.
 // 16 heads x 2704 tokens, d = 64, 297 tokens a list, against the fp32 matrix instruction on operands straight from memory: forward
 // 54 -> 23 us, dQ 82 -> 24 us.
@@ -173,8 +174,8 @@ tile_fwd_bf16_kernel(TokArgs args, const uint16_t *__restrict__ Q, uint16_t *__r
     if (g == 0) LSE[row] = add_log(m, lsum);
 }
 
-// dQ: the same walk, P from the saved logsumexp; K rows through LDS (read row-wise and transposed), V rows straight into the
-// operand.  Also produces D = rowsum(dO o O) of its queries for the key-major kernel.
+// dQ: the same walk, P from the saved logsumexp; K rows are read from LDS row-wise and transposed, V rows row-wise only.  Also
+// produces D = rowsum(dO o O) of its queries for the key-major kernel.
 template <int D>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 128 ? 2 : 4)))
 tile_dq_bf16_kernel(TokArgs args, const uint16_t *__restrict__ Q, const uint16_t *__restrict__ O, const uint16_t *__restrict__ dO,

@@ -9,8 +9,8 @@
 //     the probability of that row is register r of the lane's own score tile, so nothing moves between lanes.  The other
 //     operand is E consecutive channels of row 4g + r per lane, 16 lanes covering 16 E channels of a row.
 // Rows that are an operand of the first product go through the wave's LDS (RowTile); rows that are one of the second only are
-// fetched as they are, 256 bytes of a row per instruction.  The next tile's rows fly during the current one's math, the list
-// entries a chunk of 64 ahead.  What bounds these kernels is the matrix pipe (32 cycles an instruction: 512 per product of a
+// fetched as they are, 256 bytes of a row per instruction.  The next tile's rows fly during the current one's math; list entries
+// are fetched for 64 blocks at a time, when the walk comes to them.  What bounds these kernels is the matrix pipe (32 cycles an instruction: 512 per product of a
 // 16 x 16 x 64 tile).  16 heads x 4096 tokens, d = 64, M = 272: forward 62 -> 58 us, dQ 92 -> 75 (29 and 43 us of matrix
 // instructions; the forward without any load in its loop takes 50); 2 heads, a wave alone on its SIMD: 32 -> 28, 39 -> 34.
 #include <string.h>
