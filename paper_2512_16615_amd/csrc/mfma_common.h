@@ -147,8 +147,9 @@ template <int D> __device__ __forceinline__ TileOffsets<D> tile_offsets(int lane
 // Where the compiler has `base` in vector registers, v_readfirstlane writes it right before the asm, into which the compiler's own
 // wait states do not reach: a vector memory instruction must not read an SGPR within five wait states of the vector instruction that
 // wrote it, and the hardware does not look.  Scalar instructions may read it at once and what they write may be read at once, so the loads
-// take a scalar copy.  (s_nop 3 in its place: 0.3 to 0.6 % slower steps at 16 heads x 4096, 32 x 16384 and 16 x 65536 tokens.)
-#define LLSA_LOAD_LDS "s_mov_b64 %0, %3\n\ts_mov_b32 m0, %1\n\ts_waitcnt lgkmcnt(0)\n\tglobal_load_lds_dwordx4 %2, %0"
+// take a scalar copy.  It stands between m0 and the first load, which must not follow m0's write at once either (one wait state; an
+// s_waitcnt with nothing to wait for may be none).  (s_nop 3 in its place: 0.3 to 0.6 % slower steps at 16 heads x 4096, 32 x 16384 and 16 x 65536 tokens.)
+#define LLSA_LOAD_LDS "s_mov_b32 m0, %1\n\ts_mov_b64 %0, %3\n\ts_waitcnt lgkmcnt(0)\n\tglobal_load_lds_dwordx4 %2, %0"
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"         // m0 is on the clobber list so that nothing else is kept in it meanwhile
 template <int N> __device__ __forceinline__ void load_lds(uint64_t base, unsigned v0, unsigned v1, unsigned lds) {

@@ -1,6 +1,7 @@
 """The loads from memory straight into LDS are written in inline asm, where the compiler inserts no wait states: in the built library none of
 them may read an SGPR that a vector instruction wrote fewer than five wait states earlier (CDNA: "VALU writes SGPR", then "VMEM reads that
-SGPR": 5 wait states, no interlock).  Reads the AMD assembly of the library built here."""
+SGPR": 5 wait states, no interlock), or follow at once a scalar instruction that wrote m0, the address in LDS (1 wait
+state).  Reads the AMD assembly of the library built here."""
 import os
 import re
 import struct
@@ -48,6 +49,9 @@ def hazards(lines):
         op, _, args = text.partition(" ")
         if op.startswith("global_load_lds"):
             loads += 1
+            before = [x for x in past if x[0] != "s_waitcnt"][-1:]
+            if before and before[0][0].startswith("s_") and re.match(r"m0\b", before[0][1]):
+                found.append((kernel, text, 0, "{} {}".format(*before[0])))
             base, waited = _sgprs(args), 0
             for pop, pargs in reversed(past):
                 if waited >= NEEDED:
@@ -66,11 +70,13 @@ def test_the_rule_on_short_sequences():
     head = ["0000 <k>:"]
     early = ["v_readfirstlane_b32 s59, v9", "v_readfirstlane_b32 s58, v8", "s_mov_b32 m0, s3", "s_waitcnt lgkmcnt(0)"]
     load = ["global_load_lds_dwordx4 v1, s[58:59]"]
-    assert hazards(head + early + load)[0][0][2] == 1
+    assert hazards(head + early + load)[0][-1][2] == 1
     assert not hazards(head + early + ["s_nop 3"] + load)[0]
     assert hazards(head + early + ["s_nop 2"] + load)[0]
     assert not hazards(head + early + ["s_mov_b64 s[4:5], s[58:59]", "global_load_lds_dwordx4 v1, s[4:5]"])[0]
     assert hazards(head + ["v_cmp_eq_u32_e64 s[58:59], v0, v1"] + load)[0]
+    assert hazards(head + ["s_mov_b32 m0, s3", "s_waitcnt lgkmcnt(0)"] + load)[0]
+    assert not hazards(head + ["s_mov_b32 m0, s3", "s_mov_b64 s[58:59], s[4:5]", "s_waitcnt lgkmcnt(0)"] + load)[0]
 
 
 def test_loads_into_lds_wait_for_their_address(tmp_path):
