@@ -52,6 +52,18 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D 
     const TileOffsets<D> o = tile_offsets<D>(lane);
     const RowSource<D> src(lane);
 
+    // The lists first: everything else waits for them, and loads come back in the order in which they were asked for.
+    // Level 0, of this wave's NB query blocks: lane LL b + j holds the first token of 16-token tile j of query tile b's list (at most LL
+    // tiles; a listed block of B tokens is B / 16 consecutive tiles, and B / 16 consecutive query tiles share a row of I^(0): one list for
+    // all if GW > 0).
+    constexpr int LL = GW > 0 ? 64 : 64 / NB;
+    const int nb0 = t->lev[0].end;                                        // level-0 tiles (the list always holds level 0)
+    const int nbc = t->lev[t->nlev - 1].end - nb0;                    // coarse tiles of the list
+    const int j0_ = min(lane % LL, nb0 - 1);                              // a tile past the end is never asked for
+    const int raw0 = t->lev[0].I[(bh * t->lev[0].rows + (tile_of(min(lane / LL, NB - 1)) >> t->ls)) * t->lev[0].Kl + (j0_ >> t->ls)];
+    CoarseTable ctab;                                                  // lane j: coarse block 64 * chunk + j, of the tile issued last
+    ctab.ask<D>(t, bh, (unsigned)blk0, 0, lane);
+
     bf16x8 qop[NB][KS];
     f32x4 acc[NB][NT];
     float m[NB], lsum[NB];                                            // reference; this lane's share of the row sum
@@ -151,26 +163,11 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D 
     using Late = std::false_type;
     auto nothing = []() {};
 
-    // The level-0 lists of this wave's NB query blocks, fetched now so that phase B does not wait for them:
-    // lane LL b + j holds the first token of 16-token tile j of query tile b's list (at most LL tiles; a listed block of B
-    // tokens is B / 16 consecutive tiles, and B / 16 consecutive query tiles share a row of I^(0): one list for all if GW > 0).
-    constexpr int LL = GW > 0 ? 64 : 64 / NB;
-    const int nb0 = t->lev[0].end;                                        // level-0 tiles (the list always holds level 0)
-    int tok0 = 0;
-    {
-        const int b = lane / LL, j = lane % LL;
-        if (j < nb0) {
-            const int64_t row = tile_of(b) >> t->ls;
-            tok0 = (t->lev[0].I[(bh * t->lev[0].rows + row) * t->lev[0].Kl + (j >> t->ls)] << t->lb) + ((j & ((1 << t->ls) - 1)) << 4);
-        }
-    }
-
     // ------------------------------------------------------------------ phase A: shared coarse levels
-    const int nbc = t->lev[t->nlev - 1].end - nb0;                    // coarse tiles of the list
     const unsigned lds0 = lds_address(lds);
+    const int tok0 = (raw0 << t->lb) + ((j0_ & ((1 << t->ls) - 1)) << 4);
     if (nbc > 0) {
-        CoarseTable ctab;                                              // lane j: coarse block 64 * chunk + j, of the tile issued last
-        ctab.fill<D>(t, bh, (unsigned)blk0, 0, lane);
+        ctab.finish<D>(t);
         const bool v_wave = wave >= NW / 2;                           // this wave brings in V rows
         uint64_t rows = v_wave ? +ctab.vptr : +ctab.kptr;
         float w_now = ctab.bias2, w_next = 0.f;                       // the weights, of the tile worked on

@@ -13,10 +13,10 @@
 
 namespace llsa {
 
-__device__ __forceinline__ bf16x8 to_bf16x8(u32x4 v) {
+__device__ __forceinline__ u32x4 from_bf16x8(bf16x8 v) {
     union { u32x4 u; bf16x8 b; } c;
-    c.u = v;
-    return c.b;
+    c.b = v;
+    return c.u;
 }
 __device__ __forceinline__ float bf_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
@@ -51,33 +51,55 @@ dq_shared_kernel(ListArgs args, const uint16_t *__restrict__ Q, const uint16_t *
     const TileOffsets<D> o = tile_offsets<D>(lane);
     const RowSource<D> src(lane);
 
+    // The lists first: everything else waits for them, and loads come back in the order in which they were asked for.
+    // Level 0, of this wave's NB query blocks: lane LL b + j holds the first token of 16-token tile j of query tile b's list (as in the
+    // forward kernel).
+    constexpr int LL = GW > 0 ? 64 : 64 / NB;
+    const int nb0 = t->lev[0].end;                                        // level-0 tiles
+    const int nbc = t->lev[t->nlev - 1].end - nb0;                    // coarse tiles of the list
+    const int j0_ = min(lane % LL, nb0 - 1);                              // a tile past the end is never asked for
+    const int raw0 = t->lev[0].I[(bh * t->lev[0].rows + (tile_of(min(lane / LL, NB - 1)) >> t->ls)) * t->lev[0].Kl + (j0_ >> t->ls)];
+    CoarseTable ctab;                                                  // lane j: coarse block 64 * chunk + j, of the tile issued last
+    ctab.ask<D>(t, bh, (unsigned)blk0, 0, lane);
+
     bf16x8 qop[NB][KS], gop[NB][KS];
+    u32x4 orow[NB][KS];
     f32x4 acc[NB][NT];
     float lse2[NB];
     f32x4 ndelta[NB];                                                 // -D in every register: what dP^T's sums start from
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
         const int64_t qrow = bh * N + tile_of(b) * 16 + i16;
-        float dl = 0.f;
 #pragma unroll
         for (int s = 0; s < KS; ++s) {
             qop[b][s] = ld_bf16x8(Q + qrow * D + g * 8 + 32 * s);
-            const u32x4 gw = *reinterpret_cast<const u32x4 *>(dO + qrow * D + g * 8 + 32 * s);
-            const u32x4 ow = *reinterpret_cast<const u32x4 *>(O + qrow * D + g * 8 + 32 * s);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                dl = fmaf(bf_lo(gw[e]), bf_lo(ow[e]), dl);
-                dl = fmaf(bf_hi(gw[e]), bf_hi(ow[e]), dl);
-            }
-            gop[b][s] = to_bf16x8(gw);
+            gop[b][s] = ld_bf16x8(dO + qrow * D + g * 8 + 32 * s);
+            orow[b][s] = *reinterpret_cast<const u32x4 *>(O + qrow * D + g * 8 + 32 * s);
         }
-        dl = rows_sum(dl);
-        ndelta[b] = f32x4{-dl, -dl, -dl, -dl};
-        if (g == 0 && blk0 + NB * wave + b < nblk) Dsum[qrow] = dl;
-        lse2[b] = LSE[qrow] * kLog2e;
+        lse2[b] = LSE[qrow];
 #pragma unroll
         for (int n = 0; n < NT; ++n) acc[b][n] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
+    // D of the wave's queries, once the first tiles are on their way
+    auto deltas = [&]() {
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            float dl = 0.f;
+#pragma unroll
+            for (int s = 0; s < KS; ++s) {
+                const u32x4 gw = from_bf16x8(gop[b][s]), ow = orow[b][s];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    dl = fmaf(bf_lo(gw[e]), bf_lo(ow[e]), dl);
+                    dl = fmaf(bf_hi(gw[e]), bf_hi(ow[e]), dl);
+                }
+            }
+            dl = rows_sum(dl);
+            ndelta[b] = f32x4{-dl, -dl, -dl, -dl};
+            if (g == 0 && blk0 + NB * wave + b < nblk) Dsum[bh * N + tile_of(b) * 16 + i16] = dl;
+            lse2[b] *= kLog2e;
+        }
+    };
 
     // dS^T of query tile b for one tile of keys (dp: dP^T - D); a half of weight -inf is absent
     auto ds_of = [&](auto bsel, f32x4 s0, f32x4 s1, f32x4 dp0, f32x4 dp1, int c0, int c1, float b0, float b1) -> bf16x8 {
@@ -147,25 +169,11 @@ dq_shared_kernel(ListArgs args, const uint16_t *__restrict__ Q, const uint16_t *
     using Late = std::false_type;
     auto nothing = []() {};
 
-    // The level-0 lists of this wave's NB query blocks, fetched now so that phase B does not wait for them:
-    // lane LL b + j holds the first token of 16-token tile j of query tile b's list (as in the forward kernel).
-    constexpr int LL = GW > 0 ? 64 : 64 / NB;
-    const int nb0 = t->lev[0].end;
-    int tok0 = 0;
-    {
-        const int b = lane / LL, j = lane % LL;
-        if (j < nb0) {
-            const int64_t row = tile_of(b) >> t->ls;
-            tok0 = (t->lev[0].I[(bh * t->lev[0].rows + row) * t->lev[0].Kl + (j >> t->ls)] << t->lb) + ((j & ((1 << t->ls) - 1)) << 4);
-        }
-    }
-
     // ------------------------------------------------------------------ phase A: shared coarse levels
-    const int nbc = t->lev[t->nlev - 1].end - nb0;                    // coarse tiles of the list
     const unsigned lds0 = lds_address(lds);
+    const int tok0 = (raw0 << t->lb) + ((j0_ & ((1 << t->ls) - 1)) << 4);
     if (nbc > 0) {
-        CoarseTable ctab;                                              // lane j: coarse block 64 * chunk + j, of the tile issued last
-        ctab.fill<D>(t, bh, (unsigned)blk0, 0, lane);
+        ctab.finish<D>(t);
         const bool v_wave = wave >= NW / 2;                           // this wave brings in V rows
         uint64_t rows = v_wave ? +ctab.vptr : +ctab.kptr;
         float w_now = ctab.bias2, w_next = 0.f;                       // the weights, of the tile worked on
@@ -200,6 +208,7 @@ dq_shared_kernel(ListArgs args, const uint16_t *__restrict__ Q, const uint16_t *
             load_lds<CPW>(base + sub * 1024, src.v0, src.v1, dst);
         };
         for (int u = 0; u < RING - 1 && u < ntile; ++u) issue(u);
+        deltas();
         for (int u = 0; u < ntile; ++u) {
             // tile u is there, and tile u - 1, whose place tile u + 3 takes, has been read by every wave
             if (u + 2 < ntile) vm_wait_barrier<2 * CPW>();
@@ -214,6 +223,8 @@ dq_shared_kernel(ListArgs args, const uint16_t *__restrict__ Q, const uint16_t *
                  2 * u + 1 < nbc ? weight(2 * u + 1) : -INFINITY, nothing);
         }
         vm_wait_barrier<0>();                                         // phase A's buffers are free
+    } else {
+        deltas();
     }
 
     // ------------------------------------------------------------------ phase B: level 0

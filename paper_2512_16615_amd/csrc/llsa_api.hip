@@ -63,10 +63,12 @@ ListArgs make_list_args(const LevelTable &t) {
         v.shift = t.lb * (l + 1) - 4;
         v.bias2 = t.bias[l] * 1.4426950408889634f;
     }
+    for (int l = t.nlev; l <= kMaxL; ++l) a.lev[l].first = a.lev[l].end = INT32_MAX;
     a.nlev = t.nlev;
     a.lb = t.lb;
     a.ls = t.ls;
     a.scale = t.scale;
+    if (t.nlev > 1) a.to_v = static_cast<const char *>(t.V[1]) - static_cast<const char *>(t.K[1]);
     return a;
 }
 

@@ -78,6 +78,7 @@ struct ListArgs {
     ListLevel lev[kMaxL + 1];
     int32_t nlev, lb, ls;
     float scale;
+    int64_t to_v;                   // from a pooled level's keys to its values: the same for all of them
 };
 ListArgs make_list_args(const LevelTable &t);
 

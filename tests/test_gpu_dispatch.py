@@ -42,6 +42,27 @@ def test_lengths_that_are_no_multiple_of_64_have_fp32_probabilities(cfg):
         assert torch.equal(got[name], want[name]), name
 
 
+def test_lists_of_six_levels():
+    """Levels beyond the fourth coarse one (1048576 tokens in blocks of 16, the coarsest level a single token): the bf16 MFMA kernels
+    against the fp32-arithmetic ones, both within the bf16 bound of the same result."""
+    import torch
+    from paper_2512_16615_amd import llsa
+    from tests import harness as H
+    N, d = 16 ** 5, 64
+    gen = torch.Generator(device="cuda").manual_seed(11)
+    Q, K, V, dO = (torch.randn(1, 1, N, d, generator=gen, device="cuda").bfloat16() for _ in range(4))
+    got = []
+    for path in (0, 1):
+        plan = llsa.Plan(1, 1, N, d, 16, 2, 5, kernel_path=path)
+        O, LSE, idx, ws = llsa.forward(plan, Q, K, V, workspace=plan.alloc_workspace(True))
+        got.append((O, LSE, idx) + tuple(llsa.backward(plan, Q, K, V, O, LSE, idx, dO, ws)))
+    assert torch.equal(got[0][2], got[1][2])
+    tol = H.TOL["bf16"]["out"]
+    for name, i in (("O", 0), ("dQ", 3), ("dK", 4), ("dV", 5)):
+        assert float((got[0][i].float() - got[1][i].float()).abs().max()) <= 2 * tol, name
+    assert float((got[0][1] - got[1][1]).abs().max()) <= 1e-3
+
+
 @pytest.mark.parametrize("d,B", [(64, 16), (128, 16), (128, 32), (32, 8), (16, 16)])
 def test_bf16_tiles_round_outputs_only(d, B):
     """bf16 shapes in fp32 arithmetic, every block listed (a dense softmax): all but a few outputs are the correctly rounded result.  fp32
