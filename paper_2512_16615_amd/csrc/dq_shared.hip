@@ -9,6 +9,7 @@
 // The kernel also produces D = rowsum(dO o O) for its queries and stores it for the key-major kernels.
 #include <type_traits>
 
+#include "csc_small.h"
 #include "mfma_common.h"
 
 namespace llsa {
@@ -29,7 +30,7 @@ template <int D, int NB, int NW, int GW>
 __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 64 ? (NB == 2 ? 3 : 4) : 2)))
 dq_shared_kernel(ListArgs args, const uint16_t *__restrict__ Q, const uint16_t *__restrict__ O,
                  const uint16_t *__restrict__ dO, const float *__restrict__ LSE, float *__restrict__ Dsum,
-                 uint16_t *__restrict__ dQ, int64_t N, FastDiv groups) {
+                 uint16_t *__restrict__ dQ, int64_t N, FastDiv groups, CscSmall csc) {
     constexpr int KS = D / 32, NT = D / 16, ROWB = 2 * D, HALF = 16 * ROWB, TILE = 2 * HALF;   // 16 rows, 32 rows
     constexpr int CPH = HALF / 1024;                    // load_lds steps of 16 rows
     constexpr int CPW = 4 * CPH / NW;                   // of a [K | V] tile that the workgroup shares, per wave
@@ -41,7 +42,13 @@ dq_shared_kernel(ListArgs args, const uint16_t *__restrict__ Q, const uint16_t *
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int i16 = lane & 15, g = lane >> 4;
     const int64_t nblk = N >> 4;                                      // query tiles per head
-    const unsigned wg = xcd_contiguous32(blockIdx.x, gridDim.x);
+    // the first workgroups make the key-major lists, which nothing here reads
+    static_assert(sizeof(lds) >= kCscSmallLds, "");
+    if (blockIdx.x < csc.wgs) {
+        csc_small<64 * NW>(csc, blockIdx.x, reinterpret_cast<uint32_t *>(lds));
+        return;
+    }
+    const unsigned wg = xcd_contiguous32(blockIdx.x - csc.wgs, gridDim.x - csc.wgs);
     const int64_t bh = groups(wg), blk0 = (wg - (unsigned)bh * groups.d) * (NW * NB);   // groups.d workgroups per head
     // a spare wave of a head's last workgroup works on the head's last tile without storing it
     auto tile_of = [&](int b) { return min(blk0 + NB * wave + b, nblk - 1); };
@@ -301,15 +308,15 @@ dq_shared_kernel(ListArgs args, const uint16_t *__restrict__ Q, const uint16_t *
 }
 
 hipError_t launch_dq_shared(const Plan &p, const LevelTable &t, const void *Q, const void *O, const void *dO,
-                            const float *LSE, float *D, void *dQ, hipStream_t s) {
+                            const float *LSE, float *D, void *dQ, const CscSmall &csc, hipStream_t s) {
     const FastDiv groups((p.N + 127) / 128);
     const unsigned wgs = (unsigned)p.bh * groups.d;
     const ListArgs a = make_list_args(t);
     const int ls = p.lb - 4;
     auto go = [&](auto d, auto nb, auto gw) {
         constexpr int NB = decltype(nb)::value, NW = 8 / NB;
-        dq_shared_kernel<decltype(d)::value, NB, NW, decltype(gw)::value><<<wgs, 64 * NW, 0, s>>>(
-            a, (const uint16_t *)Q, (const uint16_t *)O, (const uint16_t *)dO, LSE, D, (uint16_t *)dQ, p.N, groups);
+        dq_shared_kernel<decltype(d)::value, NB, NW, decltype(gw)::value><<<wgs + csc.wgs, 64 * NW, 0, s>>>(
+            a, (const uint16_t *)Q, (const uint16_t *)O, (const uint16_t *)dO, LSE, D, (uint16_t *)dQ, p.N, groups, csc);
     };
     using I0 = std::integral_constant<int, 0>;
     using I1 = std::integral_constant<int, 1>;

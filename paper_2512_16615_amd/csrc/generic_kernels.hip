@@ -1,8 +1,9 @@
 // The steps around the attention, for any supported shape and both I/O types: pooling, the layer glue fused with it, the
 // portable selection, the index transpose, the mask comparator and the index reordering.
-#include "llsa_internal.h"
+#include "csc_small.h"
 
 #include <math.h>
+#include <string.h>
 
 namespace llsa {
 
@@ -401,96 +402,10 @@ struct CscLevel {
 };
 struct CscLevels { CscLevel lv[kMaxL]; };
 
-// Few rows (csc_one_launch), one launch, no scratch memory: a workgroup makes the
-// lists of kRangeKeys consecutive keys of one head.  It reads all of the head's entries (from L2: 16 KB at 512 rows of 8), marks the
-// rows that list one of its keys in a bitmap of a row per key in LDS and counts the entries of the keys below its own (their
-// number is where its lists start); then every group of lanes turns a key's bitmap into its ascending list.  Marking has no
-// order, so neither a fill in order nor a sort is needed.  Against count, scan, fill and sort in launches of their own this
-// saves four launches, which is most of the time at these sizes.  Reading grows with rows^2, hence the limit; the bitmap of 32
-// keys is 2 KB at 512 rows.
-// grid.x: ranges of level 0's heads, then level 1's, ... (also in the kernels of the segment path)
-constexpr int kRangeKeys = 32;
-struct CscRanges { CscLevel lv[kMaxL]; unsigned wg_end[kMaxL]; };
-__global__ void __launch_bounds__(256) csc_bitmap_kernel(CscRanges a) {
-    extern __shared__ __attribute__((aligned(16))) uint32_t bm[];   // [kRangeKeys][words], words = rows in 64s, times 2
-    __shared__ int32_t tot[kRangeKeys], below_sh[4];
-    int l = 0;
-    while (blockIdx.x >= a.wg_end[l]) ++l;
-    const CscLevel &L = a.lv[l];
-    const unsigned id = blockIdx.x - (l ? a.wg_end[l - 1] : 0), T = (unsigned)L.T, E = (unsigned)L.eph;
-    const unsigned ranges = (T + kRangeKeys - 1) / kRangeKeys, bh = id / ranges, r0 = (id - bh * ranges) * kRangeKeys;
-    const unsigned words = ((T + 63) >> 6) * 2;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    for (unsigned i = tid; i < kRangeKeys * words; i += 256) bm[i] = 0;
-    if (tid < kRangeKeys) tot[tid] = 0;
-    __syncthreads();
-    const int32_t *I = L.I + (int64_t)bh * E;
-    int32_t below = 0;
-    auto mark = [&](unsigned e, unsigned key) {
-        below += key < r0 ? 1 : 0;
-        if (key - r0 < (unsigned)kRangeKeys) {
-            const unsigned row = e / (unsigned)L.Kl;
-            atomicOr(&bm[(key - r0) * words + (row >> 5)], 1u << (row & 31));
-            atomicAdd(&tot[key - r0], 1);
-        }
-    };
-    unsigned e = tid;
-    for (; e + 7 * 256 < E; e += 8 * 256) {                 // eight loads in flight
-        int32_t k[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) k[u] = I[e + 256 * u];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) mark(e + 256 * u, (unsigned)k[u]);
-    }
-    for (; e < E; e += 256) mark(e, (unsigned)I[e]);
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) below += __shfl_xor(below, o, 64);
-    if (lane == 0) below_sh[wave] = below;
-    __syncthreads();
-    // every wave scans the 32 counts for itself
-    const int32_t n = lane < kRangeKeys ? tot[lane] : 0;
-    int32_t start = n;
-#pragma unroll
-    for (int o = 1; o < kRangeKeys; o <<= 1) {
-        const int32_t y = __shfl_up(start, o, 64);
-        if (lane >= o) start += y;
-    }
-    start += below_sh[0] + below_sh[1] + below_sh[2] + below_sh[3] - n;
-    int32_t *C = L.C + (int64_t)bh * (T + 1);
-    if (wave == 0 && lane < kRangeKeys && r0 + lane < T) C[r0 + lane] = start;
-    if (tid == 0 && r0 + kRangeKeys >= T) C[T] = (int32_t)E;
-    // G lanes per key, each over 64-row words G apart
-    int32_t *Iq = L.Iq + (int64_t)bh * E;
-    const unsigned w64 = words / 2;
-    int G = 1;
-    while (G < 64 && (unsigned)G < w64) G <<= 1;
-    const int sub = lane & (G - 1), per = 64 / G;           // keys of a wave at a time
-    for (int k0 = wave * per; k0 < kRangeKeys; k0 += 4 * per) {
-        const int k = k0 + lane / G;                        // 64 / G <= 32 keys or, for one word, two passes' worth of lanes
-        const int kk = min(k, kRangeKeys - 1);
-        const int32_t cnt = k < kRangeKeys ? __shfl(n, kk, 64) : 0;
-        int32_t pos = __shfl(start, kk, 64);
-        const int32_t end = pos + cnt;
-        if (__ballot(cnt > 0) == 0) continue;
-        for (unsigned w0 = 0; w0 < w64; w0 += G) {
-            uint64_t bits = 0;
-            if (cnt > 0 && w0 + sub < w64) bits = *reinterpret_cast<const uint64_t *>(&bm[kk * words + 2 * (w0 + sub)]);
-            int32_t mine = __popcll(bits), incl = mine;
-            for (int o = 1; o < G; o <<= 1) {
-                const int32_t y = __shfl_up(incl, o, 64);
-                if (sub >= o) incl += y;
-            }
-            int32_t at = pos + incl - mine;
-            while (bits) {
-                Iq[at++] = (int32_t)(64 * (w0 + sub)) + (int32_t)__builtin_ctzll(bits);
-                bits &= bits - 1;
-            }
-            pos += __shfl(incl, (lane & ~(G - 1)) + G - 1, 64);
-        }
-        // a key listed twice by one row (no valid selection has that) is marked once: fill its list with the last row
-        if (sub == 0)
-            for (; pos < end; ++pos) Iq[pos] = (int32_t)T - 1;
-    }
+// Few rows, one launch, no scratch memory (csc_small.h).
+__global__ void __launch_bounds__(256) csc_bitmap_kernel(CscSmall a) {
+    __shared__ __attribute__((aligned(16))) uint32_t lds[kCscSmallLds / 4];
+    csc_small<256>(a, blockIdx.x, lds);
 }
 
 // More rows, up to kSegRowsMax, three launches, O(T K) work: rows are taken in segments of 128, and segments in groups of 16.
@@ -504,6 +419,8 @@ __global__ void __launch_bounds__(256) csc_bitmap_kernel(CscRanges a) {
 // Each range of 1024 keys reads its rows again, so the time grows with rows^2 for few heads; the sort's grows with the lists,
 // which smooth inputs make long.  Either side of the limit, sort against segments, smooth and Gaussian inputs, K = 8: one head of
 // 17408 rows 114 : 89 and 50 : 90 us, two of 32768 rows 224 : 247 and 90 : 250, one of 65536 rows 336 : 834 and 127 : 841.
+// grid.x: ranges of level 0's heads, then level 1's, ...
+struct CscRanges { CscLevel lv[kMaxL]; unsigned wg_end[kMaxL]; };
 constexpr int kSegRowsMax = 16384, kSegR = 128, kSegPerGroup = 16, kGroupRows = kSegR * kSegPerGroup, kKeyRange = 1024;
 // every entry of rows row0 .. row1 - 1 with key - k0 < kKeyRange: f(row, key - k0)
 template <class F> __device__ __forceinline__ void range_entries(const int32_t *I, unsigned Kl, unsigned row0, unsigned row1, unsigned k0, F f) {
@@ -775,8 +692,24 @@ __global__ void __launch_bounds__(256) csc_sort_long_kernel(CscLevels a) {
     }
 }
 
-// one launch while its O(T^2) reading is cheap (measured with the dK/dV kernels it runs beside)
-static bool csc_one_launch(const Plan &p) { return p.n[1] <= 512; }
+// The workgroups' work of levels 0 .. top where there are few rows (level 0 has the most): one launch while its O(T^2) reading is cheap
+// (measured with the dK/dV kernels it runs beside).
+static bool csc_one_launch(const Plan &p) { return p.n[1] <= kSmallRows; }
+bool csc_small_args(const Plan &p, int top, const int32_t *indices, void *ws, CscSmall *a) {
+    memset(a, 0, sizeof(*a));
+    if (!csc_one_launch(p)) return false;
+    char *w = static_cast<char *>(ws);
+    int64_t wg = 0;
+    for (int l = 0; l <= top; ++l) {
+        a->lv[l] = {reinterpret_cast<const int32_t *>(reinterpret_cast<const char *>(indices) + p.idx_off[l]), (int32_t *)(w + p.C_off[l]),
+                    (int32_t *)(w + p.Iq_off[l]), (int32_t)p.n[l + 1], p.Kl[l]};
+        wg += p.bh * ((p.n[l + 1] + kRangeKeys - 1) / kRangeKeys);
+        a->wg_end[l] = (uint32_t)wg;
+    }
+    a->levels = top + 1;
+    a->wgs = (uint32_t)((wg + 7) & ~(int64_t)7);            // workgroups behind them stay on their XCDs
+    return true;
+}
 
 // bytes of scratch memory the transpose of level l needs
 size_t csc_scratch_bytes(const Plan &p, int l) {
@@ -788,6 +721,11 @@ size_t csc_scratch_bytes(const Plan &p, int l) {
 
 // Alg. 2 for levels 0 .. top (the levels whose lists the backward uses)
 hipError_t launch_csc(const Plan &p, int top, const int32_t *indices, void *ws, hipStream_t s) {
+    CscSmall few;
+    if (csc_small_args(p, top, indices, ws, &few)) {
+        csc_bitmap_kernel<<<few.wgs, 256, 0, s>>>(few);
+        return hipGetLastError();
+    }
     char *w = static_cast<char *>(ws);
     CscLevels a;
     int64_t max_nk = 0, max_total = 0;
@@ -821,12 +759,6 @@ hipError_t launch_csc(const Plan &p, int top, const int32_t *indices, void *ws, 
         }
         return (unsigned)wg;
     };
-    if (csc_one_launch(p)) {
-        const size_t lds = (size_t)kRangeKeys * ((p.n[1] + 63) / 64) * 8;
-        const unsigned wgs = ranges([](int64_t T) { return (T + kRangeKeys - 1) / kRangeKeys; });
-        csc_bitmap_kernel<<<wgs, 256, lds, s>>>(r);
-        return hipGetLastError();
-    }
     if (p.n[1] <= kSegRowsMax) {
         auto kr = [](int64_t T) { return (T + kKeyRange - 1) / kKeyRange; };
         unsigned wgs = ranges([&](int64_t T) { return kr(T) * ((T + kGroupRows - 1) / kGroupRows); });

@@ -454,7 +454,15 @@ llsa_status llsa_backward(const llsa_plan_t *plan, const void *Q, const void *K,
     float *D = reinterpret_cast<float *>(w + p.D_off);
     // Independent work goes to the plan's auxiliary stream, unless every stage is being timed one by one.
     std::lock_guard<std::mutex> lock(plan->aux.mu);
-    Aux *aux = (g_timer.on && g_timer.filter < 0) ? nullptr : aux_for_call(plan, s);
+    const int top_listed = p.Le < p.L ? p.Le : p.L - 1;    // highest level that has index lists in use
+    // Few rows: the lists are made by a few workgroups of the dQ launch, and everything stays on the caller's stream (a fork and a join
+    // take the host and the GPU some 20 us, as long as all that could run beside something: steps of 16 heads x 4096 tokens
+    // 140.9 -> 122.1 us, x 8192 200 -> 186, 4 x 1024 101 -> 70, 64 x 4096 286 -> 278, 64 x 8192 even).
+    CscSmall lists_along;
+    const bool few = csc_small_args(p, top_listed, indices, workspace, &lists_along);
+    const bool along = few && !g_timer.on && (!p.fast || dq_takes_lists(p));
+    if (!along) lists_along.wgs = 0;
+    Aux *aux = few || (g_timer.on && g_timer.filter < 0) ? nullptr : aux_for_call(plan, s);
     hipStream_t side = aux ? aux->side : s;
     // Alg. 2 needs only the indices, so it runs on the auxiliary stream beside kernels that do not read its
     // lists.  Where the coarse levels use the grouped kernels (they write per-query-block partials, need no list,
@@ -463,7 +471,7 @@ llsa_status llsa_backward(const llsa_plan_t *plan, const void *Q, const void *K,
     const bool shadow = aux && p.group;
     bool forked = false, joined = false;
     auto transpose = [&]() -> llsa_status {
-        const int top_listed = p.Le < p.L ? p.Le : p.L - 1;    // highest level that has index lists in use
+        if (along) return LLSA_OK;
         if (aux) {
             LLSA_TRY(hipEventRecord(aux->ev[0], s));
             LLSA_TRY(hipStreamWaitEvent(side, aux->ev[0], 0));
@@ -481,8 +489,8 @@ llsa_status llsa_backward(const llsa_plan_t *plan, const void *Q, const void *K,
         LevelTable t = make_level_table(p, K, V, indices, workspace);
         {
             StageScope sc(kDq, call, s);
-            if (p.fast) LLSA_TRY(launch_dq_mfma(p, t, Q, O, dO, LSE, D, dQ, s));
-            else LLSA_TRY(launch_dq_tile(p, t, Q, O, dO, LSE, D, dQ, s));   // both also write D
+            if (p.fast) LLSA_TRY(launch_dq_mfma(p, t, Q, O, dO, LSE, D, dQ, lists_along, s));
+            else LLSA_TRY(launch_dq_tile(p, t, Q, O, dO, LSE, D, dQ, lists_along, s));   // both also write D
         }
         if (shadow) LLSA_TRY_ST(transpose());
         // the caller's stream waits for the key-major lists where it first reads them (which also joins the streams)

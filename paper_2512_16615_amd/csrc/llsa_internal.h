@@ -82,6 +82,20 @@ struct ListArgs {
 };
 ListArgs make_list_args(const LevelTable &t);
 
+// Alg. 2 for a problem of at most kSmallRows level-0 rows, as workgroups that any launch can take along (csc_small.h).
+constexpr int kSmallRows = 512;
+struct CscSmallLevel {
+    const int32_t *I;               // I^(l) [bh, T, Kl]
+    int32_t *C, *Iq;
+    int32_t T, Kl;                  // keys per head = rows per head
+};
+struct CscSmall {
+    CscSmallLevel lv[kMaxL];
+    uint32_t wg_end[kMaxL];         // level l's workgroups end here
+    int32_t levels;
+    uint32_t wgs;                   // in all, rounded up to a multiple of 8; 0: none
+};
+
 LevelTable make_level_table(const Plan &p, const void *K0, const void *V0, const int32_t *indices,
                             const void *workspace);
 
@@ -94,6 +108,7 @@ hipError_t launch_qknorm_rope_pool(const Plan &p, const void *Qpre, const void *
                                    float eps, void *Qout, void *Kout, void *ws, hipStream_t s);
 hipError_t launch_select(const Plan &p, int l, const void *ws, const int32_t *parent, int32_t *out, hipStream_t s);
 hipError_t launch_csc(const Plan &p, int top_level, const int32_t *I, void *ws, hipStream_t s);  // levels 0..top_level
+bool csc_small_args(const Plan &p, int top_level, const int32_t *I, void *ws, CscSmall *a);   // false (and none): too many rows
 size_t csc_scratch_bytes(const Plan &p, int l);   // scratch memory at Iqtmp_off[l]
 // level 0's key-major lists through a dense T x T block mask (`mask`: bh * T * T bytes, rounded up to 16) instead of Alg. 2
 hipError_t launch_mask_lists(const Plan &p, const int32_t *indices, void *ws, void *mask, hipStream_t s);
@@ -104,7 +119,7 @@ hipError_t launch_reorder(int64_t bh, int64_t N, int row_bytes, int bits, int in
 // ---- attention, dQ (and D = rowsum(dO * O)) and dK / dV of every level in fp32 arithmetic (tile_kernels.hip) ----
 hipError_t launch_attn_fwd_tile(const Plan &p, const LevelTable &t, const void *Q, void *O, float *LSE, hipStream_t s);
 hipError_t launch_dq_tile(const Plan &p, const LevelTable &t, const void *Q, const void *O, const void *dO, const float *LSE,
-                          float *D, void *dQ, hipStream_t s);
+                          float *D, void *dQ, const CscSmall &csc, hipStream_t s);   // csc: the key-major lists too, in the same launch
 hipError_t launch_dkv_tile(const Plan &p, const LevelTable &t, const void *Q, const void *dO, const float *LSE, const float *D,
                            void *ws, void *dK, void *dV, hipStream_t s);
 bool dkv_tile_folds(const Plan &p);      // is there anything to fold behind it?
@@ -130,9 +145,10 @@ hipError_t launch_attn_fwd_shared(const Plan &p, const LevelTable &t, const void
                                   hipStream_t s);
 // also writes D = rowsum(dO * O) for the key-major kernels that follow
 hipError_t launch_dq_mfma(const Plan &p, const LevelTable &t, const void *Q, const void *O, const void *dO,
-                          const float *LSE, float *D, void *dQ, hipStream_t s);
+                          const float *LSE, float *D, void *dQ, const CscSmall &csc, hipStream_t s);
+bool dq_takes_lists(const Plan &p);      // does launch_dq_mfma take the key-major lists along?
 hipError_t launch_dq_shared(const Plan &p, const LevelTable &t, const void *Q, const void *O, const void *dO,
-                            const float *LSE, float *D, void *dQ, hipStream_t s);
+                            const float *LSE, float *D, void *dQ, const CscSmall &csc, hipStream_t s);
 // key-major dK/dV of level l; levels >= 1 also fold their split slabs and the level above into the
 // level's fp32 gradient buffer, so they must be launched from the coarsest level down
 hipError_t launch_dkv_mfma(const Plan &p, const LevelTable &t, int l, const void *Q, const void *dO, const float *LSE,

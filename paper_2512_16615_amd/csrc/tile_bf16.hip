@@ -11,6 +11,7 @@
 // Bound: the vector instructions (softmax and splitting, about 150 a tile) and the latency of a wave's chain.
 // 16 heads x 2704 tokens, d = 64, 297 tokens a list, against the fp32 matrix instruction on operands straight from memory: forward
 // 54 -> 23 us, dQ 82 -> 24 us.
+#include "csc_small.h"
 #include "tile_f32.h"
 
 namespace llsa {
@@ -179,14 +180,20 @@ tile_fwd_bf16_kernel(TokArgs args, const uint16_t *__restrict__ Q, uint16_t *__r
 template <int D>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 128 ? 2 : 4)))
 tile_dq_bf16_kernel(TokArgs args, const uint16_t *__restrict__ Q, const uint16_t *__restrict__ O, const uint16_t *__restrict__ dO,
-                    const float *__restrict__ LSE, float *__restrict__ Dsum, uint16_t *__restrict__ dQ, int64_t N) {
+                    const float *__restrict__ LSE, float *__restrict__ Dsum, uint16_t *__restrict__ dQ, int64_t N, CscSmall csc) {
     using S = BShape<D>;
     constexpr int TILE = 32 * S::ROWB;
     __shared__ __attribute__((aligned(16))) char lds[4][2 * TILE];   // per wave: K rows | V rows
     __shared__ __attribute__((aligned(16))) TokTable tabs[4];
+    // the first workgroups make the key-major lists, which nothing here reads
+    static_assert(sizeof(tabs) >= kCscSmallLds, "");
+    if (blockIdx.x < csc.wgs) {
+        csc_small<256>(csc, blockIdx.x, reinterpret_cast<uint32_t *>(tabs));
+        return;
+    }
     const int lane0 = threadIdx.x & 63, i16 = lane0 & 15, g = lane0 >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const unsigned tile = xcd_contiguous32(blockIdx.x, gridDim.x) * 4 + wave;
+    const unsigned tile = xcd_contiguous32(blockIdx.x - csc.wgs, gridDim.x - csc.wgs) * 4 + wave;
     if (tile >= (unsigned)args.total) return;
     const tok_args_ptr t = kernel_tok_args();
     const QTile qt = query_tile(args, tile, N);
@@ -294,10 +301,10 @@ hipError_t launch_attn_fwd_tile_bf16(const Plan &p, const TokArgs &a, const void
 }
 
 hipError_t launch_dq_tile_bf16(const Plan &p, const TokArgs &a, const void *Q, const void *O, const void *dO, const float *LSE,
-                               float *D, void *dQ, hipStream_t s) {
+                               float *D, void *dQ, const CscSmall &csc, hipStream_t s) {
     return by_d(p.d, [&](auto d) {
-        tile_dq_bf16_kernel<d.value><<<(a.total + 3) / 4, 256, 0, s>>>(a, (const uint16_t *)Q, (const uint16_t *)O, (const uint16_t *)dO,
-                                                                     LSE, D, (uint16_t *)dQ, p.N);
+        tile_dq_bf16_kernel<d.value><<<(a.total + 3) / 4 + csc.wgs, 256, 0, s>>>(a, (const uint16_t *)Q, (const uint16_t *)O, (const uint16_t *)dO,
+                                                                     LSE, D, (uint16_t *)dQ, p.N, csc);
     });
 }
 

@@ -139,6 +139,6 @@ __device__ __forceinline__ QTile query_tile(const TokArgs &a, unsigned tile, int
 // attention and dQ of the bf16 tile kernels (tile_bf16.hip)
 hipError_t launch_attn_fwd_tile_bf16(const Plan &p, const TokArgs &a, const void *Q, void *O, float *LSE, hipStream_t s);
 hipError_t launch_dq_tile_bf16(const Plan &p, const TokArgs &a, const void *Q, const void *O, const void *dO, const float *LSE,
-                               float *D, void *dQ, hipStream_t s);
+                               float *D, void *dQ, const CscSmall &csc, hipStream_t s);
 
 }  // namespace llsa

@@ -15,6 +15,7 @@
 // instructions; the forward without any load in its loop takes 50); 2 heads, a wave alone on its SIMD: 32 -> 28, 39 -> 34.
 #include <string.h>
 
+#include "csc_small.h"
 #include "tile_f32.h"
 
 namespace llsa {
@@ -116,14 +117,20 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 1
 template <int D>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 128 ? 2 : 4))) tile_dq_kernel(TokArgs args, const float *__restrict__ Q, const float *__restrict__ O,
                                                        const float *__restrict__ dO, const float *__restrict__ LSE, float *__restrict__ Dsum,
-                                                       float *__restrict__ dQ, int64_t N) {
+                                                       float *__restrict__ dQ, int64_t N, CscSmall csc) {
     using S = TShape<D>;
     using RT = RowTile<D>;
     __shared__ __attribute__((aligned(16))) TokTable tabs[4];
     __shared__ __attribute__((aligned(16))) char rows_sh[4][2 * RT::BYTES];
+    // the first workgroups make the key-major lists, which nothing here reads
+    static_assert(sizeof(tabs) >= kCscSmallLds, "");
+    if (blockIdx.x < csc.wgs) {
+        csc_small<256>(csc, blockIdx.x, reinterpret_cast<uint32_t *>(tabs));
+        return;
+    }
     const int lane = threadIdx.x & 63, i16 = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const unsigned tile = xcd_contiguous32(blockIdx.x, gridDim.x) * 4 + wave;
+    const unsigned tile = xcd_contiguous32(blockIdx.x - csc.wgs, gridDim.x - csc.wgs) * 4 + wave;
     if (tile >= (unsigned)args.total) return;
     const tok_args_ptr t = kernel_tok_args();
     const QTile qt = query_tile(args, tile, N);
@@ -243,13 +250,13 @@ hipError_t launch_attn_fwd_tile(const Plan &p, const LevelTable &t, const void *
 }
 
 hipError_t launch_dq_tile(const Plan &p, const LevelTable &t, const void *Q, const void *O, const void *dO, const float *LSE,
-                          float *D, void *dQ, hipStream_t s) {
+                          float *D, void *dQ, const CscSmall &csc, hipStream_t s) {
     if (too_many_tiles(p)) return hipErrorInvalidValue;
     const TokArgs a = tok_args(p, t);
-    if (p.elt == 2) return launch_dq_tile_bf16(p, a, Q, O, dO, LSE, D, dQ, s);
+    if (p.elt == 2) return launch_dq_tile_bf16(p, a, Q, O, dO, LSE, D, dQ, csc, s);
     return by_d(p.d, [&](auto d) {
-        tile_dq_kernel<d.value><<<(a.total + 3) / 4, 256, 0, s>>>(a, (const float *)Q, (const float *)O, (const float *)dO, LSE, D,
-                                                                 (float *)dQ, p.N);
+        tile_dq_kernel<d.value><<<(a.total + 3) / 4 + csc.wgs, 256, 0, s>>>(a, (const float *)Q, (const float *)O, (const float *)dO, LSE, D,
+                                                                 (float *)dQ, p.N, csc);
     });
 }
 

@@ -262,6 +262,39 @@ def test_index_transpose_by_size(T, K, heads):
 
 
 @pytest.mark.parametrize("cfg", [
+    # at most 512 level-0 rows: one row, a ragged range of 32 keys, the most; workgroups of eight and of four waves; blocks of 64; fp32
+    # arithmetic in both types
+    _bf16("rows_4_L1", 64, K=2, heads=1),
+    _bf16("rows_80", 1280, L=2, heads=3, K=5),
+    _bf16("rows_512", 8192, L=2, heads=2),
+    _bf16("rows_256_of_64_heads", 4096, L=2, heads=64),
+    _bf16("rows_256_B64", 16384, B=64, K=4, L=2, heads=2),
+    _bf16("rows_48_d128_Le0", 768, d=128, K=3, heads=2, Le=0),
+    _bf16("rows_169_tiles", 2704, heads=2),
+    dict(name="rows_500_f32", batch=1, heads=3, d=32, N=2000, B=4, K=3, L=2, dtype="f32", kind="gaussian"),
+], ids=lambda c: c["name"])
+def test_lists_made_along_with_dq(cfg):
+    """The key-major lists that the dQ launch makes are those of the index transpose by itself, whole numbers for whole numbers."""
+    import torch
+    from paper_2512_16615_amd import llsa
+    from tests import harness as H
+    x = H.make_inputs(cfg, 0xD16B)
+    Q, K, V, dO = (H.to_dev(x[n], cfg) for n in ("Q", "K", "V", "dO"))
+    plan = H.make_plan(cfg)
+    ws = plan.alloc_workspace(True)
+    O, LSE, idx, _ = llsa.forward(plan, Q, K, V, workspace=ws)
+    llsa.backward(plan, Q, K, V, O, LSE, idx, dO, ws)
+    levels = range(min(plan.Le + 1, plan.L))
+    got = [[t.clone() for t in plan.csc_level(ws, l)] for l in levels]
+    other = plan.alloc_workspace(True)
+    other.zero_()
+    llsa.index_transpose(plan, idx, other)
+    for l in levels:
+        for a, b in zip(got[l], plan.csc_level(other, l)):
+            assert torch.equal(a, b), f"level {l}"
+
+
+@pytest.mark.parametrize("cfg", [
     # levels >= 2 of the grouped dK/dV kernels: a dense level of two blocks (17 tokens), of 16 blocks behind no sparse level, of
     # two blocks behind 8 listed ones; its single block owned by a wave (3 and 12 listed blocks) and shared by all (8)
     _bf16("dense_17", 17 * 256, L=2, heads=2),
