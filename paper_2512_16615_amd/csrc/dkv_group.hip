@@ -106,13 +106,47 @@ template <int D> __device__ __forceinline__ void store_partial(float *dst, const
     }
 }
 
-// NW waves, NB key blocks per wave at a time
-template <int D, int NW, int NB>
+// A key block whose query tiles the NW waves of a workgroup share: their sums added in wave order through LDS (no wave reads anything
+// else there any more).
+template <int D, int NW>
+__device__ __forceinline__ void store_shared(float *dst, const BlockAcc<D> &b, char *lds, float scale, int wave, int lane) {
+    using S = GShape<D>;
+    constexpr int SLOTS = 2 * S::NT;                                  // f32x4 slots per wave: dK tiles, then dV tiles
+    float *red = reinterpret_cast<float *>(lds);                      // [wave][slot][lane] f32x4
+    static_assert(NW * SLOTS * 64 * 16 <= 2 * 256 * S::ROWB, "the reduction must fit in the staged rows' memory");
+#pragma unroll
+    for (int n = 0; n < S::NT; ++n) {
+        *reinterpret_cast<f32x4 *>(red + ((wave * SLOTS + n) * 64 + lane) * 4) = b.accK[n];
+        *reinterpret_cast<f32x4 *>(red + ((wave * SLOTS + S::NT + n) * 64 + lane) * 4) = b.accV[n];
+    }
+    __syncthreads();
+    dst += (lane & 15) * D + 4 * (lane >> 4);
+#pragma unroll
+    for (int k = 0; k < SLOTS / NW; ++k) {                            // wave w owns slots w, w + NW, ...
+        const int slot = wave + NW * k;
+        f32x4 sum = *reinterpret_cast<const f32x4 *>(red + (slot * 64 + lane) * 4);
+#pragma unroll
+        for (int w = 1; w < NW; ++w) {
+            const f32x4 x = *reinterpret_cast<const f32x4 *>(red + ((w * SLOTS + slot) * 64 + lane) * 4);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) sum[c] += x[c];
+        }
+        const bool isV = slot >= S::NT;
+        const float w = __builtin_amdgcn_exp2f(b.bias2) * (isV ? 1.f : scale);   // level weight (and scale for dK)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) sum[c] *= w;
+        *reinterpret_cast<f32x4 *>(dst + (isV ? 16 * D : 0) + (isV ? slot - S::NT : slot) * 16) = sum;
+    }
+}
+
+// NW waves, NB key blocks per wave at a time.  DENSE: the single block of a dense level 2 too, its query tiles dealt to the waves
+// (group_takes_dense).
+template <int D, int NW, int NB, bool DENSE>
 __global__ void __launch_bounds__(64 * NW) dkv_group_kernel(LevelTable t, GroupArgs a) {
     using S = GShape<D>;
-    __shared__ __attribute__((aligned(16))) char qs[256 * S::ROWB];   // Q rows of the group, chunk-swizzled
-    __shared__ __attribute__((aligned(16))) char gs[256 * S::ROWB];   // dO rows
+    __shared__ __attribute__((aligned(16))) char qs[2 * 256 * S::ROWB];   // Q rows of the group, chunk-swizzled | dO rows
     __shared__ __attribute__((aligned(16))) float st[512];            // -LSE log2(e) | -D
+    char *gs = qs + 256 * S::ROWB;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -144,6 +178,15 @@ __global__ void __launch_bounds__(64 * NW) dkv_group_kernel(LevelTable t, GroupA
 #pragma unroll
         for (int b = 0; b < NB; ++b)
             if (jb + b < nbc) store_partial(partial_ptr<D>(t, a, nlev, jb + b + c_begin, R), blk[b], a.scale, lane);
+    }
+    if constexpr (DENSE) {
+        BlockAcc<D> dn[1];
+        dn[0].load(static_cast<const char *>(t.K[2]) + bh * t.n[2] * S::ROWB, static_cast<const char *>(t.V[2]) + bh * t.n[2] * S::ROWB,
+                   (int)t.n[2], t.bias[2] * kLog2e, lane);
+        dn[0].clear();
+        for (int u = wave; u < 8; u += NW) group_tile<D, 1>(qs, gs, st, st + 256, u, o, dn, a.sc2, g);
+        __syncthreads();                                              // everyone is done with the rows
+        store_shared<D, NW>(a.slab + a.lvl_off[2] + R * S::UNIT, dn[0], qs, a.scale, wave, lane);
     }
 }
 
@@ -307,36 +350,8 @@ __global__ void __launch_bounds__(512) dkv_upper_kernel(LevelTable t, GroupArgs 
         const int jb = first + wave + 8 * s;
         if (jb < a.nbs) store_partial(partial_ptr<D>(t, a, nlev, u_begin + jb, grp), sp[s][0], a.scale, lane);
     }
-    if constexpr (DENSE) {
-        if (dense) {                                                  // the shared block: add the 8 waves' sums in wave order
-            constexpr int SLOTS = 2 * S::NT;                          // f32x4 slots per wave: dK tiles, then dV tiles
-            float *red = reinterpret_cast<float *>(lds);              // [wave][slot][lane] f32x4
-            static_assert(8 * SLOTS * 64 * 16 <= 2 * 256 * S::ROWB, "the reduction must fit in the staged rows' memory");
-#pragma unroll
-            for (int n = 0; n < S::NT; ++n) {
-                *reinterpret_cast<f32x4 *>(red + ((wave * SLOTS + n) * 64 + lane) * 4) = dn[0].accK[n];
-                *reinterpret_cast<f32x4 *>(red + ((wave * SLOTS + S::NT + n) * 64 + lane) * 4) = dn[0].accV[n];
-            }
-            __syncthreads();
-            float *dst = partial_ptr<D>(t, a, nlev, u_begin + a.nbs, grp) + i16 * D + 4 * g;
-#pragma unroll
-            for (int k = 0; k < SLOTS / 8; ++k) {                     // wave w owns slots w, w + 8, ...
-                const int slot = wave + 8 * k;
-                f32x4 sum = *reinterpret_cast<const f32x4 *>(red + (slot * 64 + lane) * 4);
-#pragma unroll
-                for (int w = 1; w < 8; ++w) {
-                    const f32x4 x = *reinterpret_cast<const f32x4 *>(red + ((w * SLOTS + slot) * 64 + lane) * 4);
-#pragma unroll
-                    for (int c = 0; c < 4; ++c) sum[c] += x[c];
-                }
-                const bool isV = slot >= S::NT;
-                const float w = __builtin_amdgcn_exp2f(dn[0].bias2) * (isV ? 1.f : a.scale);   // level weight (and scale for dK)
-#pragma unroll
-                for (int c = 0; c < 4; ++c) sum[c] *= w;
-                *reinterpret_cast<f32x4 *>(dst + (isV ? 16 * D : 0) + (isV ? slot - S::NT : slot) * 16) = sum;
-            }
-        }
-    }
+    if constexpr (DENSE)
+        if (dense) store_shared<D, 8>(partial_ptr<D>(t, a, nlev, u_begin + a.nbs, grp), dn[0], lds, a.scale, wave, lane);
 }
 
 // out[h][r][x] = sum_{c < f, f r + c < cnt_in} in[h][f r + c][x], x over `width` floats (one thread per float4)
@@ -358,6 +373,8 @@ struct GatherArgs {
     const float *part;           // [bh][cnt][nblk][UNIT]
     const int32_t *C, *Iq, *I;   // key-major lists and I^(l) (null when dense)
     const float *upK, *upV;      // gradient of level l + 1 or null
+    const float *upPart;         // or: the partials of level l + 1, dense, up_cnt per head of up_nblk blocks
+    int up_cnt, up_nblk;
     float *dstK, *dstV;          // [bh, n_l, D]
     int64_t cnt, n_l, nkb, rows; // listers per head, tokens, key blocks per head, rows of I^(l)
     int nblk, Kl, dense;
@@ -372,6 +389,16 @@ __global__ void __launch_bounds__(NT) dkv_gather_kernel(GatherArgs a) {
     f32x4 k[PER], v[PER];
 #pragma unroll
     for (int x = 0; x < PER; ++x) { k[x] = f32x4{0.f, 0.f, 0.f, 0.f}; v[x] = f32x4{0.f, 0.f, 0.f, 0.f}; }
+    f32x4 pk = {0.f, 0.f, 0.f, 0.f}, pv = {0.f, 0.f, 0.f, 0.f};       // the parent token's gradient, of this thread's channels
+    if (a.upPart) {
+        static_assert(NT % (D / 4) == 0, "a thread's rows share its channels");
+        const float *p = a.upPart + (bh * a.up_cnt * a.up_nblk + (j >> 4)) * GShape<D>::UNIT + (j & 15) * D + (tid % (D / 4)) * 4;
+#pragma unroll 4
+        for (int c = 0; c < a.up_cnt; ++c) {
+            pk += *reinterpret_cast<const f32x4 *>(p + (int64_t)c * a.up_nblk * GShape<D>::UNIT);
+            pv += *reinterpret_cast<const f32x4 *>(p + (int64_t)c * a.up_nblk * GShape<D>::UNIT + 16 * D);
+        }
+    }
     if (a.dense) {
         const f32x4 *p = part + ((bh * a.cnt) * a.nblk + j) * U4;
 #pragma unroll
@@ -419,6 +446,9 @@ __global__ void __launch_bounds__(NT) dkv_gather_kernel(GatherArgs a) {
             const int64_t up = (bh * ((a.n_l + 15) / 16) + j) * D + col;   // parent token of the block's 16 tokens
             kk += *reinterpret_cast<const f32x4 *>(a.upK + up) * 0.0625f;
             vv += *reinterpret_cast<const f32x4 *>(a.upV + up) * 0.0625f;
+        } else if (a.upPart) {
+            kk += pk * 0.0625f;
+            vv += pv * 0.0625f;
         }
         *reinterpret_cast<f32x4 *>(a.dstK + (bh * a.n_l + tok) * D + col) = kk;
         *reinterpret_cast<f32x4 *>(a.dstV + (bh * a.n_l + tok) * D + col) = vv;
@@ -495,11 +525,22 @@ static void chain_shape(const Plan &p, int *GC, int *GS) {
     *GS = gs;
 }
 
+// A dense level 2 of at most 16 tokens, d = 64: the group kernel takes its one block along, and the gather of level 1 adds up the (at most 16)
+// partials of a parent token itself: three launches less, which is what there is to save at the size.  16 heads x 4096 tokens: the upper,
+// reducing and gathering kernels of that level took 8 + 6 + 3 us, the group kernel takes 18 us with it and without (a step 122.1 ->
+// 107.0 us; 2 heads 83.1 -> 72.2).  From 1024 level-1 query blocks on the chain kernel is the better one.
+static bool group_takes_dense(const Plan &p) {
+    int nbs, nbd, gc, gs;
+    upper_blocks(p, &nbs, &nbd);
+    chain_shape(p, &gc, &gs);
+    return p.d == 64 && p.L == 2 && p.Le == 2 && nbs == 0 && nbd == 1 && gc == 1 && p.N <= 4096;
+}
+
 // partial-slab layout: level 1 has one partial per (level-1 query block, list position), levels >= 2 one per
 // (query group, list position)
 static int64_t slab_layout(const Plan &p, int64_t *lvl_off, int *nblk, int64_t *groups) {
     const int64_t NR = p.N / 256, unit = 2 * 16 * p.d;
-    const int G = upper_G(p);
+    const int G = group_takes_dense(p) ? 0 : upper_G(p);
     int64_t off = 0;
     for (int l = 0; l <= kMaxL; ++l) { lvl_off[l] = 0; nblk[l] = 0; groups[l] = 0; }
     for (int l = 1; l <= dkv_group_top(p); ++l) {
@@ -559,7 +600,10 @@ static hipError_t finish_level(const Plan &p, const LevelTable &t, const GroupAr
     ga.C = dense ? nullptr : (const int32_t *)(w + p.C_off[l]);
     ga.Iq = dense ? nullptr : (const int32_t *)(w + p.Iq_off[l]);
     ga.I = dense ? nullptr : t.I[l];
-    const bool has_up = l < p.Le;
+    const bool with_dense = l == 1 && group_takes_dense(p), has_up = l < p.Le && !with_dense;
+    ga.upPart = with_dense ? a.slab + a.lvl_off[2] : nullptr;
+    ga.up_cnt = (int)a.NR;
+    ga.up_nblk = 1;
     ga.upK = has_up ? (const float *)(w + p.dKacc_off[l + 1]) : nullptr;
     ga.upV = has_up ? (const float *)(w + p.dVacc_off[l + 1]) : nullptr;
     ga.dstK = (float *)(w + p.dKacc_off[l]);
@@ -587,8 +631,9 @@ static hipError_t launch_group_kernel(const Plan &p, const LevelTable &t, const 
         return hipGetLastError();
     }
     const dim3 grid((unsigned)(p.bh * a.NR));
-    if (p.d == 64) dkv_group_kernel<64, 4, 2><<<grid, 256, 0, s>>>(t, a);
-    else dkv_group_kernel<128, 8, 1><<<grid, 512, 0, s>>>(t, a);
+    if (group_takes_dense(p)) dkv_group_kernel<64, 4, 2, true><<<grid, 256, 0, s>>>(t, a);
+    else if (p.d == 64) dkv_group_kernel<64, 4, 2, false><<<grid, 256, 0, s>>>(t, a);
+    else dkv_group_kernel<128, 8, 1, false><<<grid, 512, 0, s>>>(t, a);
     return hipGetLastError();
 }
 
@@ -597,7 +642,8 @@ hipError_t launch_dkv_group(const Plan &p, const LevelTable &t, const void *Q, c
                             hipEvent_t upper_done) {
     char *w = static_cast<char *>(ws);
     const int64_t NR = p.N / 256;
-    const int top = dkv_group_top(p), G = upper_G(p);
+    const bool with_dense = group_takes_dense(p);          // the group kernel does all there is
+    const int top = with_dense ? 1 : dkv_group_top(p), G = with_dense ? 0 : upper_G(p);
     GroupArgs a;
     int64_t groups[kMaxL + 1];
     a.Q = (const uint16_t *)Q; a.dO = (const uint16_t *)dO; a.LSE = LSE; a.Dsum = D;

@@ -262,6 +262,20 @@ def test_index_transpose_by_size(T, K, heads):
 
 
 @pytest.mark.parametrize("cfg", [
+    # the dense level 2 in the group kernel: one token (one query block a head), a ragged tile, all 16; two passes of listed blocks behind it;
+    # the widest launch that the chain kernel does not take yet, and the first one that it does
+    _bf16("top_1", 256, L=2, heads=3, K=1),
+    _bf16("top_5_K3", 5 * 256, L=2, heads=2, K=3),
+    _bf16("top_16_K12", 4096, L=2, heads=2, K=12),
+    _bf16("top_15_K16", 15 * 256, L=2, heads=1, K=16),
+    _bf16("top_16_heads_63", 4096, L=2, heads=63, K=2),
+    _bf16("top_16_heads_64", 4096, L=2, heads=64, K=2),
+], ids=lambda c: c["name"])
+def test_dense_level_in_the_group_kernel(cfg):
+    _full_parity(cfg, 0xD16C)
+
+
+@pytest.mark.parametrize("cfg", [
     # at most 512 level-0 rows: one row, a ragged range of 32 keys, the most; workgroups of eight and of four waves; blocks of 64; fp32
     # arithmetic in both types
     _bf16("rows_4_L1", 64, K=2, heads=1),
