@@ -1,7 +1,7 @@
 // Alg. 2's key-major lists of a problem with few rows, as the work of single workgroups, which need nothing from each other: the
 // kernel of their own (generic_kernels.hip) or a few workgroups of the dQ launch, whose result they do not read.
 #pragma once
-#include "llsa_internal.h"
+#include "fine_tiles.h"
 
 namespace llsa {
 
@@ -63,6 +63,14 @@ template <int NT> __device__ __forceinline__ void csc_small(const CscSmall &a, u
     int32_t *C = L.C + (int64_t)bh * (T + 1);
     if (wave == 0 && lane < kRangeKeys && r0 + lane < T) C[r0 + lane] = start;
     if (tid == 0 && r0 + kRangeKeys >= T) C[T] = (int32_t)E;
+    if (l == 0 && a.tiles) {                                // the lists as tiles, a wave per key
+        const int64_t places = tile_places(T, E);
+        for (int k = wave; k < kRangeKeys && r0 + k < T; k += NT / 64) {
+            const int s0 = __shfl(start, k, 64), len = __shfl(n, k, 64);
+            write_tiles(a.tiles + bh * places, a.arrived + bh * piece_slots(T, E, a.lc), a.lc, (int)r0 + k, s0, len,
+                        r0 + k + 1 == T ? (int)places : tile_place(s0 + len, (int)r0 + k + 1), lane, 64);
+        }
+    }
     // G lanes per key, each over 64-row words G apart
     int32_t *Iq = L.Iq + (int64_t)bh * E;
     const unsigned w64 = words / 2;

@@ -16,7 +16,6 @@ struct DkvArgs {
     int span_shift;                       // log2 of the 16-query groups per listed query block: log2(B^(level+1) / 16)
     float inv_B;
     int Kl_cnt, dense, splits;
-    unsigned apart;                       // dkv_fine_kernel: distance of a workgroup's key blocks
     float sc2, bias2, scale;
     FastDiv blocks, split_of;             // dkv_block_kernel: key blocks per head, shares per block
 };

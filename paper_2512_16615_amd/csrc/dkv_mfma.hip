@@ -9,16 +9,17 @@
 // computes
 //   S = Q K^T, dP = dO V^T   (lane: 4 queries x 1 key)  ->  P, dS  ->
 //   dV^T += dO^T P,  dK^T += Q^T dS   (A = the Q / dO tile read transposed from LDS, B = P / dS).
-// Two kernels share that tile loop:
+// Two kernels:
 //   dkv_coarse_kernel (levels >= 1): one workgroup of 4 waves per (key block, split); the tiles of its
 //     share are dealt round-robin to the waves, whose accumulators are summed through LDS in wave order;
 //     fp32 partial sums go to one slab per split and a second kernel adds the slabs in split order (and
 //     the share of the level above, the adjoint of mean pooling).
-//   dkv_fine_kernel (level 0): lists are short (K on average), so every wave takes one key block of its
-//     own; a key block whose list is long is instead worked on by all four waves together afterwards.
-//     The epilogue adds the parent token's share and rounds once to bf16.
+//   dkv_fine_kernel (level 0): lists are short (K on average) and very different, from none to hundreds, so single waves take them from a
+//     row of tiles (fine_tiles.h), several short lists or a piece of a long one each; the epilogue adds the parent token's share and
+//     rounds once to bf16.
 // Every sum has a fixed order, so results do not depend on timing.
 #include "dkv_common.h"
+#include "fine_tiles.h"
 
 namespace llsa {
 
@@ -217,104 +218,254 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 6
 }
 
 // ---------------------------------------------------------------------------------------------- level 0
-constexpr int kSoloMax = 24;                                // longest list (16-query groups) one wave takes alone
+// A wave by itself: the lists that begin in its few places of the head's row of tiles, one after the other without a stop (the next list's
+// rows, keys and parent row are on their way while the one in hand is finished), or a piece of a list that is cut.  No wave waits for
+// another.  Rows, logsumexps, D and the parents' gradients all go straight into LDS.  XCDs take whole stretches of heads, whose rows stay in
+// their L2 (74 % of the requests hit, 0.65 GB fetched at 16 x 65536 tokens; dealt round 340 us, 1.4 GB).
+// A workgroup of four waves per four key blocks, the short lists by one wave each and the long ones by all four afterwards, with a barrier
+// between, took 295 us at 16 x 65536 tokens (now 254; Gaussian 325, 318), 150 at 32 x 16384 (133), 26 at 16 x 4096 (21), 1580 at 8 x 262144
+// with d = 128 and K = 16 (1610); with constant keys, whose lists hold every query, a step of 4 x 65536 takes 559 us instead of 1226.
+// What bounds it: a wave's chain (1700 cycles a tile alone on its SIMD: 320 in LDS reads, 170 + 430 in products and softmax, 530 in asking
+// for the next rows), three waves a SIMD (with four the registers do not suffice: 300 us), and under load the requests, which take 1280
+// cycles a tile then.  Not faster: reading all operands in front of the first product, rows from one place only (243 of then 273 us), waves
+// that draw their work from a counter (27 ns a draw, one after the other: 630 us).
+constexpr int kEmpty = 8;                                   // the key blocks that nothing lists, of this many, are one wave's work
+struct FineArgs {
+    const FineTile *tiles;
+    int32_t *arrived;
+    float *part;
+    unsigned T, places, slots, packs;                       // of a head: key blocks, places, slots of pieces, waves for tiles
+    int lc, pack;                                           // log2 of the tiles of a piece; a wave takes the lists and pieces that begin in `pack` places
+    FastDiv waves;                                          // waves of a head
+};
 
 template <int D>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 64 ? 3 : 2))) dkv_fine_kernel(DkvArgs a) {
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(D == 64 ? 3 : 2))) dkv_fine_kernel(DkvArgs a, FineArgs f) {
     using S = DkvShape<D>;
-    __shared__ __attribute__((aligned(16))) char lds[4][S::WAVE];
-    __shared__ int len_sh[4];
-    __shared__ __attribute__((aligned(16))) float par_sh[4][2 * D];   // per wave: the parent token's dK | dV
+    __shared__ __attribute__((aligned(16))) char qt[S::WAVE];         // Q rows | dO rows | LSE [32], D [32]
+    __shared__ __attribute__((aligned(16))) float par_sh[2][2 * D];   // the parent token's dK | dV: of the list in hand, of the next
+    char *gt = qt + S::TILE;
+    float *st = reinterpret_cast<float *>(gt + S::TILE);
 
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int i16 = lane & 15, g = lane >> 4;
-    const int64_t nkb = a.n_l >> 4;                        // key tiles per head (a multiple of 4)
+    const int lane = threadIdx.x, i16 = lane & 15, g = lane >> 4;
     const bool has_par = a.parK != nullptr;
-    // This workgroup's four key tiles (same head) lie a.apart tiles from each other (launch_dkv_mfma says why).
-    const unsigned per_head = (unsigned)(nkb >> 2), q = blockIdx.x % per_head;
-    const int64_t bh = blockIdx.x / per_head;
-    const unsigned j0 = q / a.apart * (4 * a.apart) + q % a.apart;
+    const unsigned id = xcd_contiguous32(blockIdx.x, gridDim.x), bh = f.waves(id), v = id - bh * f.waves.d;
+    const int64_t key0 = (int64_t)bh * f.T;
+    const int32_t *C = a.C + (int64_t)bh * (f.T + 1);
 
-    // The 16 keys of block j share one parent token (level-1 token j).  Its gradient row is fetched into
-    // registers before the tile loop (so the epilogue does not wait for memory) and handed to the epilogue's
-    // channel layout through the wave's LDS row.
-    float park[D / 64], parv[D / 64];
-    auto par_fetch = [&](int64_t j) {
+    if (v >= f.packs) {                                     // key blocks that nothing lists: the parent's share in every row
+        const unsigned j0 = kEmpty * (v - f.packs);
+        const int c0 = C[min(j0 + lane, f.T)], c1 = C[min(j0 + lane + 1, f.T)];
+        uint64_t m = __ballot(lane < kEmpty && j0 + lane < f.T && c0 == c1);
+        constexpr int CH = D / 8, RPI = 64 / CH;            // 16-byte chunks of a row, rows per store
+        const int c = lane % CH;
+        while (m) {                                         // two at a time, so that their loads fly together
+            int64_t key[2];
+            f32x4 par[2][4];
 #pragma unroll
-        for (int x = 0; x < D / 64; ++x) {
-            park[x] = has_par ? a.parK[(bh * nkb + j) * D + lane + 64 * x] : 0.f;
-            parv[x] = has_par ? a.parV[(bh * nkb + j) * D + lane + 64 * x] : 0.f;
+            for (int x = 0; x < 2; ++x) {
+                const int b = m ? (int)__builtin_ctzll(m) : -1;
+                key[x] = b < 0 ? -1 : key0 + j0 + b;
+                if (b >= 0) m &= m - 1;
+                const int64_t at = max(key[x], key[0]) * D + 8 * c;
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    par[x][q] = has_par ? *reinterpret_cast<const f32x4 *>((q < 2 ? a.parK : a.parV) + at + 4 * (q & 1)) * a.inv_B : f32x4{0.f, 0.f, 0.f, 0.f};
+            }
+#pragma unroll
+            for (int x = 0; x < 2; ++x) {
+                if (key[x] < 0) break;
+                const int64_t row = key[x] * 16 + lane / CH;
+                const bf16x8 k = pack8(par[x][0], par[x][1]), w = pack8(par[x][2], par[x][3]);
+#pragma unroll
+                for (int r = 0; r < 16; r += RPI) {
+                    *reinterpret_cast<bf16x8 *>(a.dK + (row + r) * D + 8 * c) = k;
+                    *reinterpret_cast<bf16x8 *>(a.dV + (row + r) * D + 8 * c) = w;
+                }
+            }
+        }
+        return;
+    }
+
+    // The wave's places, 32 at a time: lane 2t the key word of place base + t, lane 2t + 1 its entry word; then the entries themselves,
+    // lane 2t + x entry x (-1: there is none)
+    const int p0 = f.pack * (int)v;
+    int base = p0, word = 0, entry = 0;
+    uint64_t starts = 0, gaps = 0;
+    auto window = [&]() {
+        const int32_t *src = reinterpret_cast<const int32_t *>(f.tiles + (int64_t)bh * f.places + base);
+        word = base + (lane >> 1) < (int)f.places ? src[lane] : kGap;
+        starts = __ballot(!(lane & 1) && word >= 0);
+        gaps = __ballot(!(lane & 1) && word == kGap);
+        const int w = __shfl(word, lane | 1, 64), e = w < 0 ? ~w : w;
+        const bool there = !((gaps >> (lane & ~1)) & 1) && !(w < 0 && (lane & 1));
+        entry = there ? a.Iq[(int64_t)bh * f.T * a.Kl_cnt + e + (lane & 1)] : -1;
+    };
+    window();
+    if (!(starts & ((1ull << 2 * f.pack) - 1))) return;      // nothing begins here
+    const int first = p0 + ((int)__builtin_ctzll(starts) >> 1);
+
+    const TileOffsets<D> o = tile_offsets<D>(lane);
+    const RowSource<D> src(lane);
+    const unsigned dst = lds_address(qt), par_at = lds_address(par_sh);
+    const uint64_t Qh = reinterpret_cast<uint64_t>(a.Q + (int64_t)bh * a.N * D), Gh = reinterpret_cast<uint64_t>(a.dO + (int64_t)bh * a.N * D);
+    const float *stats = ((lane & 32) ? a.Dsum : a.LSE) + (int64_t)bh * a.N + i16;
+    const unsigned koff = (unsigned)(i16 * D + g * 8) * 2;
+    bf16x8 kop[S::KS], vop[S::KS];
+    f32x4 accK[S::NT], accV[S::NT];
+    int key = 0, next_key = 0, began = 0, turn = 0;         // key words; the place where the list or piece in hand begins
+    bool both = false;                                      // does the tile on its way have its second entry?
+    auto begins = [&](int t) { return (starts >> 2 * (t - base)) & 1; };
+    auto load_tile = [&](int t) {
+        const int e0 = __builtin_amdgcn_readlane(entry, 2 * (t - base)), e1 = __builtin_amdgcn_readlane(entry, 2 * (t - base) + 1);
+        both = e1 >= 0;
+        const int e[2] = {e0, both ? e1 : e0};              // an absent second one re-reads the first
+#pragma unroll
+        for (int x = 0; x < 2; ++x) {
+            load_lds<S::CPH>(Qh + (uint64_t)(unsigned)e[x] * (32 * D), src.v0, src.v1, dst + x * S::HALF);
+            load_lds<S::CPH>(Gh + (uint64_t)(unsigned)e[x] * (32 * D), src.v0, src.v1, dst + S::TILE + x * S::HALF);
+        }
+        load_lds_dword(stats + 16 * ((lane & 16) ? e[1] : e[0]), dst + 2 * S::TILE);
+        if (begins(t)) {                                    // the key block's rows, the parent's gradient
+            next_key = __builtin_amdgcn_readlane(word, 2 * (t - base));
+            const int64_t k = key0 + (next_key & (kPiece - 1));
+            const char *kb = reinterpret_cast<const char *>(a.Kl) + k * (32 * D), *vb = reinterpret_cast<const char *>(a.Vl) + k * (32 * D);
+#pragma unroll
+            for (int ks = 0; ks < S::KS; ++ks) {
+                kop[ks] = ld_bf16x8(kb + koff + 64 * ks);
+                vop[ks] = ld_bf16x8(vb + koff + 64 * ks);
+            }
+            turn ^= 1;
+            if (has_par)
+#pragma unroll
+                for (int x = 0; x < D / 64; ++x) {
+                    load_lds_dword(a.parK + k * D + 64 * x + lane, par_at + 8 * D * turn + 256 * x);
+                    load_lds_dword(a.parV + k * D + 64 * x + lane, par_at + 8 * D * turn + 4 * D + 256 * x);
+                }
         }
     };
-    auto par_publish = [&]() {                              // the wave's own row; its LDS operations stay in order
-#pragma unroll
-        for (int x = 0; x < D / 64; ++x) {
-            par_sh[wave][lane + 64 * x] = park[x];
-            par_sh[wave][D + lane + 64 * x] = parv[x];
-        }
-        __builtin_amdgcn_wave_barrier();
-    };
-    // level-0 epilogue: scale dK, add the parent token's share (adjoint of mean pooling), round once
-    auto emit = [&](int64_t j, int slot, f32x4 sum) {
-        const bool isV = slot >= S::NT;
-        const int n = isV ? slot - S::NT : slot;
-        const int col = n * 16 + 4 * g;                     // lane holds 4 consecutive channels of key i16
-        if (!isV)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) sum[r] *= a.scale;
+    // scale dK, add the parent token's share (adjoint of mean pooling), round once
+    auto store = [&](uint16_t *out, int64_t k, int n, f32x4 sum, const float *par) {
         if (has_par) {
-            const f32x4 pv = *reinterpret_cast<const f32x4 *>(&par_sh[wave][(isV ? D : 0) + col]);
+            const f32x4 x = *reinterpret_cast<const f32x4 *>(par + 16 * n + 4 * g);
 #pragma unroll
-            for (int r = 0; r < 4; ++r) sum[r] += pv[r] * a.inv_B;
+            for (int r = 0; r < 4; ++r) sum[r] += x[r] * a.inv_B;
         }
         u32x2 w;
         w[0] = pack_bf16(sum[0], sum[1]);
         w[1] = pack_bf16(sum[2], sum[3]);
-        *reinterpret_cast<u32x2 *>((isV ? a.dV : a.dK) + (bh * a.n_l + j * 16 + i16) * D + col) = w;
+        *reinterpret_cast<u32x2 *>(out + (k * 16 + i16) * D + n * 16 + 4 * g) = w;
     };
-
-    // ---- each wave alone on its own key block, if that block's list is short
-    {
-        const int64_t j = j0 + wave * a.apart;
-        const int32_t *Crow = a.C + bh * (a.rows + 1) + j;
-        const int32_t beg = Crow[0], len = Crow[1] - beg;   // in 16-query groups
-        if (lane == 0) len_sh[wave] = len;
-        if (len <= kSoloMax) {
-            bf16x8 kop[S::KS], vop[S::KS];
-            f32x4 accK[S::NT], accV[S::NT];
-            par_fetch(j);
+    load_tile(first);
+    int t = first, follows = 1;                             // follows: 0 nothing, 1 another tile of this list, 2 another list
+    while (follows) {
+        vm_wait<0>();
+        if (begins(t)) {
+            key = next_key;
+            began = t;
 #pragma unroll
             for (int n = 0; n < S::NT; ++n) { accK[n] = f32x4{0.f, 0.f, 0.f, 0.f}; accV[n] = f32x4{0.f, 0.f, 0.f, 0.f}; }
-            if (len > 0) {
-                dkv_load_keys<D>(a, bh * a.n_l + j * 16 + i16, lane, kop, vop);
-                dkv_tile_loop<D>(a, bh, a.Iq + bh * a.rows * a.Kl_cnt + beg, len, 0, 1, ((int64_t)len + 1) >> 1, kop, vop,
-                                 accK, accV, lds[wave], lane);
-            }
-            par_publish();
-#pragma unroll
-            for (int n = 0; n < S::NT; ++n) { emit(j, n, accK[n]); emit(j, S::NT + n, accV[n]); }
         }
-    }
-    __syncthreads();
-    // ---- long lists: all four waves together, one key block after the other
-    for (int w = 0; w < 4; ++w) {
-        const int len = len_sh[w];
-        if (len <= kSoloMax) continue;                      // uniform over the workgroup
-        const int64_t j = j0 + w * a.apart;
-        const int32_t beg = a.C[bh * (a.rows + 1) + j];
-        bf16x8 kop[S::KS], vop[S::KS];
-        f32x4 accK[S::NT], accV[S::NT];
+        f32x4 s[2], dp[2], l2[2], dl[2];
 #pragma unroll
-        for (int n = 0; n < S::NT; ++n) { accK[n] = f32x4{0.f, 0.f, 0.f, 0.f}; accV[n] = f32x4{0.f, 0.f, 0.f, 0.f}; }
-        par_fetch(j);
-        dkv_load_keys<D>(a, bh * a.n_l + j * 16 + i16, lane, kop, vop);
-        dkv_tile_loop<D>(a, bh, a.Iq + bh * a.rows * a.Kl_cnt + beg, len, wave, 4, ((int64_t)len + 1) >> 1, kop, vop, accK,
-                         accV, lds[wave], lane);
-        par_publish();
-        dkv_reduce_waves<D>(reinterpret_cast<float *>(&lds[0][0]), wave, lane, accK, accV,
-                            [&](int slot, f32x4 sum) { emit(j, slot, sum); });
-        __syncthreads();                                    // the reduction buffer is the next round's tile space
+        for (int x = 0; x < 2; ++x) {
+            s[x] = f32x4{0.f, 0.f, 0.f, 0.f};
+            dp[x] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int ks = 0; ks < S::KS; ++ks) {
+                s[x] = mfma16(ld_bf16x8(qt + x * S::HALF + o.row[ks]), kop[ks], s[x]);
+                dp[x] = mfma16(ld_bf16x8(gt + x * S::HALF + o.row[ks]), vop[ks], dp[x]);
+            }
+        }
+#pragma unroll
+        for (int x = 0; x < 2; ++x) {                       // this lane's 4 queries: rows 4g .. 4g+3
+            l2[x] = *reinterpret_cast<const f32x4 *>(st + 16 * x + 4 * g);
+            dl[x] = *reinterpret_cast<const f32x4 *>(st + 32 + 16 * x + 4 * g);
+        }
+        bf16x8 tg[S::NT], tq[S::NT];
+#pragma unroll
+        for (int n = 0; n < S::NT; ++n) {
+            tg[n] = lds_tr_pair(gt + o.tr[n], gt + S::HALF + o.tr[n]);
+            tq[n] = lds_tr_pair(qt + o.tr[n], qt + S::HALF + o.tr[n]);
+        }
+        const bool two = both;
+        // what follows: places without a tile are passed over, lists that begin behind the wave's places are another wave's
+        int next = t + 1;
+        if (next - base == 32) {                            // (a list or piece longer than the window)
+            base = next;
+            window();
+        }
+        if ((gaps >> 2 * (next - base)) & 1) {              // the list ends here; the window reaches beyond the wave's places
+            const uint64_t tiles = (~gaps & 0x5555555555555555ull) >> 2 * (next - base);
+            next = tiles ? next + ((int)__builtin_ctzll(tiles) >> 1) : (int)f.places;
+        }
+        follows = next >= (int)f.places ? 0 : !begins(next) ? 1 : next < p0 + f.pack ? 2 : 0;
+        if (follows) load_tile(next);
+#pragma unroll
+        for (int x = 0; x < 2; ++x)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const float p = __builtin_amdgcn_exp2f(fmaf(s[x][r], a.sc2, fmaf(l2[x][r], -kLog2e, a.bias2)));
+                s[x][r] = p;
+                dp[x][r] = p * (dp[x][r] - dl[x][r]);
+            }
+        if (!two) {
+            s[1] = f32x4{0.f, 0.f, 0.f, 0.f};
+            dp[1] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+        const bf16x8 pop = pack8(s[0], s[1]), dsop = pack8(dp[0], dp[1]);
+#pragma unroll
+        for (int n = 0; n < S::NT; ++n) {
+            accV[n] = mfma16(tg[n], pop, accV[n]);
+            accK[n] = mfma16(tq[n], dsop, accK[n]);
+        }
+        t = next;
+        if (follows == 1) continue;
+        const float *par = par_sh[follows ? turn ^ 1 : turn];
+        const unsigned j = (unsigned)key & (kPiece - 1);
+        if (key & kPiece) {
+            // A piece: its sums to memory, past the caches that other XCDs do not see; the wave that finds itself the last of the list adds
+            // all of them up, in order.
+            auto slot = [&](int place) { return f.part + ((int64_t)bh * f.slots + piece_slot(place, f.lc)) * (32 * D) + lane; };   // [register][lane]
+            float *p = slot(began);
+#pragma unroll
+            for (int n = 0; n < S::NT; ++n)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    __hip_atomic_store(p + 64 * (4 * n + r), accK[n][r], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    __hip_atomic_store(p + 64 * (4 * n + r) + 16 * D, accV[n][r], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
+            const int start = __builtin_amdgcn_readfirstlane(C[j]), len = __builtin_amdgcn_readfirstlane(C[j + 1]) - start;
+            const int t0 = tile_place(start, (int)j), np = piece_count((len + 1) >> 1, f.lc);
+            vm_wait<0>();
+            int before = 0;
+            if (lane == 0) before = __hip_atomic_fetch_add(f.arrived + (int64_t)bh * f.slots + piece_slot(t0, f.lc), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (__builtin_amdgcn_readfirstlane(before) != np - 1) continue;
+#pragma unroll
+            for (int n = 0; n < S::NT; ++n) { accK[n] = f32x4{0.f, 0.f, 0.f, 0.f}; accV[n] = f32x4{0.f, 0.f, 0.f, 0.f}; }
+            for (int q = 0; q < np; ++q) {
+                const float *y = slot(t0 + (q << f.lc));
+                auto add = [&](f32x4 (&acc)[S::NT], const float *from) {
+                    f32x4 x[S::NT];                         // all asked for before the first is added
+#pragma unroll
+                    for (int n = 0; n < S::NT; ++n)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) x[n][r] = __hip_atomic_load(from + 64 * (4 * n + r), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+                    for (int n = 0; n < S::NT; ++n) acc[n] += x[n];
+                };
+                add(accK, y);
+                add(accV, y + 16 * D);
+            }
+        }
+#pragma unroll
+        for (int n = 0; n < S::NT; ++n) {
+            f32x4 k = accK[n];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) k[r] *= a.scale;
+            store(a.dK, key0 + j, n, k, par);
+            store(a.dV, key0 + j, n, accV[n], par + D);
+        }
     }
 }
 
@@ -355,20 +506,17 @@ int dkv_splits(const Plan &p, int l) {
     return (int)s;
 }
 
-// How far apart the four key tiles of a dkv_fine_kernel workgroup are.  Neighbouring tiles are listed about equally often, so that
-// hot ones, one beside the other, fill whole workgroups, which hold their place until the longest list is done, while others run
-// empty.  A quarter of the head apart, lists of a workgroup are as different as they can be; but then the workgroups in flight
-// read query rows from all over the head, which only pays while a head's Q and dO stay in an XCD's 4 MB of L2, or nearly.
-// Beyond, 4 tiles.  us at distance 1 / 4 / N / 64, smooth inputs, K = 8: 16 x 4096 tokens 34.2 / 35.3 / 28.0, 32 x 16384
-// 169 / 156 / 149, 16 x 16384 with d = 128 172 / 156 / 150, 16 x 32768 156 / 160 / 154, 16 x 65536 305 / 299 / 316, 4 x 262144
-// 349 / 312 / 472, 8 x 262144 with d = 128 and K = 16 1666 / 1634 / 2475; gaussian 8 x 16384 48.0 / 48.8 / 47.5, 16 x 65536
-// 328 / 331 / 334.  All of them in raster order; in nested-patch order a quarter of the head is the better one at any length (backward
-// at 8 x 262144, d = 64, K = 8: 1930 / 1922 / 1862), but the plan does not know the order.
-static unsigned fine_apart(const Plan &p) {
-    const int64_t tiles = p.N / 16;
-    if (p.N * p.d * 4 <= (int64_t)8 << 20) return (unsigned)(tiles / 4);
-    return tiles % 16 == 0 ? 4 : 1;
-}
+bool dkv_by_tiles(const Plan &p) { return p.fast && p.B == 16; }
+
+// Tiles of a piece and places of a wave.  A cut list's sums go to memory and back, 16 KB a piece (d = 128: 32), so pieces are as long as the
+// launch's end allows: its last waves run alone while they finish one.  us at pieces of 16 / 32 / 64 tiles: 16 x 65536 tokens 266 / 254 /
+// 263, 32 x 16384 133 / 138 / 141, 8 x 262144 with d = 128, K = 16 2163 / 1604 / 1582.  Where the waves that the chip holds (3072, at d = 128 2048) have
+// eight tiles each or fewer, a wave with little to do is worth more: pieces of 8, 2 places (steps, 1 x 16384 tokens 171.7 -> 162.7 us,
+// 16 x 1472 58.3 -> 55.4; 4 x 4096 at d = 128 107.9).
+static int64_t fine_tiles(const Plan &p) { return p.bh * tile_places(p.n[1], p.n[1] * p.Kl[0]); }
+static bool few_tiles(const Plan &p) { return fine_tiles(p) <= 8 * (p.d == 128 ? 2048 : 3072); }
+int fine_piece_log2(const Plan &p) { return few_tiles(p) ? 3 : p.d == 128 ? 6 : fine_tiles(p) > 64 * 3072 ? 5 : 4; }
+static int fine_pack(const Plan &p) { return few_tiles(p) ? 2 : 8; }
 
 // level0_alone: level 0's own gradient only, without the share of its parent tokens (the pooled levels' gradients)
 hipError_t launch_dkv_mfma(const Plan &p, const LevelTable &t, int l, const void *Q, const void *dO, const float *LSE,
@@ -401,11 +549,22 @@ hipError_t launch_dkv_mfma(const Plan &p, const LevelTable &t, int l, const void
         if (l > 0) a.dK = a.dV = nullptr;
         const hipError_t e = launch_dkv_block(p, l, a, s);
         if (l == 0 || e != hipSuccess) return e;
-    } else if (l == 0) {                                    // N % 64 == 0: four key tiles per workgroup, one head
-        a.apart = fine_apart(p);
-        dim3 grid((unsigned)(key_blocks / 4));
-        if (p.d == 64) dkv_fine_kernel<64><<<grid, 256, 0, s>>>(a);
-        else dkv_fine_kernel<128><<<grid, 256, 0, s>>>(a);
+    } else if (l == 0) {
+        const int64_t T = p.n[1], E = T * p.Kl[0];
+        FineArgs f;
+        f.tiles = (const FineTile *)(w + p.tiles_off);
+        f.arrived = (int32_t *)(w + p.arrived_off);
+        f.part = (float *)(w + p.piece_off);
+        f.T = (unsigned)T;
+        f.places = (unsigned)tile_places(T, E);
+        f.lc = fine_piece_log2(p);
+        f.slots = (unsigned)piece_slots(T, E, f.lc);
+        f.pack = fine_pack(p);
+        f.packs = (f.places + f.pack - 1) / f.pack;
+        f.waves = FastDiv(f.packs + (T + kEmpty - 1) / kEmpty);
+        const unsigned wgs = (unsigned)p.bh * f.waves.d;
+        if (p.d == 64) dkv_fine_kernel<64><<<wgs, 64, 0, s>>>(a, f);
+        else dkv_fine_kernel<128><<<wgs, 64, 0, s>>>(a, f);
         return hipGetLastError();
     }
     if (!block) {

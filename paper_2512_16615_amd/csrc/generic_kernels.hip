@@ -707,6 +707,11 @@ bool csc_small_args(const Plan &p, int top, const int32_t *indices, void *ws, Cs
         a->wg_end[l] = (uint32_t)wg;
     }
     a->levels = top + 1;
+    if (dkv_by_tiles(p)) {
+        a->tiles = (FineTile *)(w + p.tiles_off);
+        a->arrived = (int32_t *)(w + p.arrived_off);
+        a->lc = fine_piece_log2(p);
+    }
     a->wgs = (uint32_t)((wg + 7) & ~(int64_t)7);            // workgroups behind them stay on their XCDs
     return true;
 }
@@ -720,6 +725,27 @@ size_t csc_scratch_bytes(const Plan &p, int l) {
 }
 
 // Alg. 2 for levels 0 .. top (the levels whose lists the backward uses)
+// level 0's lists as tiles, 16 lanes per key
+__global__ void __launch_bounds__(256) fine_tiles_kernel(const int32_t *C, FineTile *tiles, int32_t *arrived, int T, int E, int lc) {
+    const unsigned per_head = ((unsigned)T + 15u) / 16u, bh_ = blockIdx.x / per_head;
+    const int64_t bh = bh_;
+    const int j = (int)((blockIdx.x - bh_ * per_head) * 16 + (threadIdx.x >> 4));
+    if (j >= T) return;
+    const int32_t *c = C + bh * (T + 1);
+    const int start = c[j], end = c[j + 1];
+    const int64_t places = tile_places(T, E);
+    write_tiles(tiles + bh * places, arrived + bh * piece_slots(T, E, lc), lc, j, start, end - start, j + 1 == T ? (int)places : tile_place(end, j + 1),
+                (int)(threadIdx.x & 15), 16);
+}
+hipError_t launch_fine_tiles(const Plan &p, void *ws, hipStream_t s) {
+    if (!dkv_by_tiles(p)) return hipGetLastError();
+    char *w = static_cast<char *>(ws);
+    fine_tiles_kernel<<<(unsigned)((p.n[1] + 15) / 16 * p.bh), 256, 0, s>>>((const int32_t *)(w + p.C_off[0]), (FineTile *)(w + p.tiles_off),
+                                                                           (int32_t *)(w + p.arrived_off), (int)p.n[1], (int)(p.n[1] * p.Kl[0]),
+                                                                           fine_piece_log2(p));
+    return hipGetLastError();
+}
+
 hipError_t launch_csc(const Plan &p, int top, const int32_t *indices, void *ws, hipStream_t s) {
     CscSmall few;
     if (csc_small_args(p, top, indices, ws, &few)) {
@@ -766,7 +792,7 @@ hipError_t launch_csc(const Plan &p, int top, const int32_t *indices, void *ws, 
         csc_seg_scan_kernel<<<dim3(p.bh, top + 1), 256, 0, s>>>(a);
         wgs = ranges([&](int64_t T) { return kr(T) * ((T + kSegR - 1) / kSegR); });
         csc_seg_fill_kernel<<<wgs, 256, 0, s>>>(r);
-        return hipGetLastError();
+        return launch_fine_tiles(p, ws, s);
     }
     const unsigned nl = (unsigned)(top + 1);
     csc_zero_kernel<<<dim3((unsigned)((max_nk + 255) / 256), nl), 256, 0, s>>>(a);
@@ -775,7 +801,7 @@ hipError_t launch_csc(const Plan &p, int top, const int32_t *indices, void *ws, 
     csc_fill_kernel<<<dim3((unsigned)((max_total + 255) / 256), nl), 256, 0, s>>>(a);
     csc_sort_kernel<<<dim3((unsigned)((max_total + 255) / 256), nl), 256, 0, s>>>(a);
     csc_sort_long_kernel<<<dim3((unsigned)((max_nk + 255) / 256), nl), 256, 0, s>>>(a);
-    return hipGetLastError();
+    return launch_fine_tiles(p, ws, s);
 }
 
 // ------------------------------------------------------- key-major lists through a dense block mask (comparator)
@@ -863,7 +889,7 @@ hipError_t launch_mask_lists(const Plan &p, const int32_t *indices, void *ws, vo
     mask_mark_kernel<<<dim3((unsigned)((total + 255) / 256)), 256, 0, s>>>(L.I, static_cast<uint8_t *>(mask), L.cnt, T, L.Kl, total);
     csc_scan_kernel<<<dim3(p.bh, 1), kScanThreads, 0, s>>>(a);
     mask_scan_kernel<<<dim3((unsigned)((nk + 3) / 4)), 256, 0, s>>>(static_cast<const uint8_t *>(mask), L.C, L.Iq, T, eph, nk);
-    return hipGetLastError();
+    return launch_fine_tiles(p, ws, s);
 }
 
 // ---------------------------------------------------------------------------- index reordering (Sec. 5.1)

@@ -7,6 +7,7 @@
 #include <new>
 #include <vector>
 
+#include "fine_tiles.h"
 #include "llsa_internal.h"
 
 namespace llsa {
@@ -136,6 +137,13 @@ static llsa_status build_plan(const llsa_desc &d, Plan &p) {
         p.Iq_off[l] = ws;    ws = align_up(ws + ent * sizeof(int32_t));
         p.Iqtmp_off[l] = ws; ws = align_up(ws + csc_scratch_bytes(p, l));
     }
+    size_t pieces = 0;                                      // sums of the pieces of level 0's cut lists
+    if (dkv_by_tiles(p)) {
+        const int64_t E = p.n[1] * p.Kl[0], slots = p.bh * piece_slots(p.n[1], E, fine_piece_log2(p));
+        p.tiles_off = ws;   ws = align_up(ws + (size_t)p.bh * tile_places(p.n[1], E) * sizeof(FineTile));
+        p.arrived_off = ws; ws = align_up(ws + (size_t)slots * sizeof(int32_t));
+        pieces = (size_t)slots * 32 * p.d * sizeof(float);
+    }
     for (int l = 1; p.fast && l <= p.L; ++l) {
         const size_t bytes = (size_t)p.bh * p.n[l] * p.d * sizeof(float);
         p.dKacc_off[l] = ws; ws = align_up(ws + bytes);
@@ -149,10 +157,12 @@ static llsa_status build_plan(const llsa_desc &d, Plan &p) {
     if (p.group) {
         size_t slab = 0, red = 0;
         dkv_group_sizes(p, &slab, &red);
-        p.grp_slab_off = ws;   ws = align_up(ws + slab);
+        p.grp_slab_off = ws;   ws = align_up(ws + (slab > pieces ? slab : pieces));
         p.grp_red_off[0] = ws; ws = align_up(ws + red);
         p.grp_red_off[1] = ws; ws = align_up(ws + red);
     }
+    p.piece_off = p.group ? p.grp_slab_off : ws;            // the coarse levels' partials have been read when level 0 begins
+    if (!p.group) ws = align_up(ws + pieces);
     p.part_off = ws;
     p.part_bytes = p.fast ? 0 : dkv_tile_bytes(p);
     if (p.fast)

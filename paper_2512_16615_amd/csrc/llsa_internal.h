@@ -24,6 +24,7 @@ struct Plan {
     size_t pyr_off[3][kMaxL + 1];   // workspace byte offset of pooled level l (1..L) of Q/K/V
     size_t D_off;                   // [bh, N] fp32: rowsum(dO * O)
     size_t C_off[kMaxL], cnt_off[kMaxL], Iq_off[kMaxL], Iqtmp_off[kMaxL];
+    size_t tiles_off, arrived_off, piece_off;   // level 0's lists as tiles (fine_tiles.h), pieces of a cut list that are done, their sums
     size_t dKacc_off[kMaxL + 1], dVacc_off[kMaxL + 1]; // fp32 gradients of pooled level l (1..L)
     size_t part_off, part_bytes;    // partial sums of the key-major reductions
     size_t grp_slab_off, grp_red_off[2];   // partials of the query-grouped coarse dK/dV kernel and its reductions
@@ -89,11 +90,15 @@ struct CscSmallLevel {
     int32_t *C, *Iq;
     int32_t T, Kl;                  // keys per head = rows per head
 };
+struct FineTile;
 struct CscSmall {
     CscSmallLevel lv[kMaxL];
     uint32_t wg_end[kMaxL];         // level l's workgroups end here
     int32_t levels;
     uint32_t wgs;                   // in all, rounded up to a multiple of 8; 0: none
+    FineTile *tiles;                // level 0's tiles and counters (fine_tiles.h), or null
+    int32_t *arrived;
+    int32_t lc;                     // log2 of the tiles of a piece
 };
 
 LevelTable make_level_table(const Plan &p, const void *K0, const void *V0, const int32_t *indices,
@@ -153,6 +158,9 @@ hipError_t launch_dq_shared(const Plan &p, const LevelTable &t, const void *Q, c
 // level's fp32 gradient buffer, so they must be launched from the coarsest level down
 hipError_t launch_dkv_mfma(const Plan &p, const LevelTable &t, int l, const void *Q, const void *dO, const float *LSE,
                            const float *D, void *ws, void *dK, void *dV, hipStream_t s, bool level0_alone = false);
+bool dkv_by_tiles(const Plan &p);         // does level 0 take its lists as tiles (fine_tiles.h)?
+int fine_piece_log2(const Plan &p);       // in pieces of how many tiles
+hipError_t launch_fine_tiles(const Plan &p, void *ws, hipStream_t s);   // they are made from C
 int dkv_splits(const Plan &p, int l);    // workgroups sharing one key block's query list at level l
 int dkv_block_tiles(const Plan &p, int l), dkv_block_splits(const Plan &p, int l);   // the same for dkv_block.hip's levels
 // all coarse levels (dkv_group_top .. 1) at once, grouped by level-1 query block; fills the levels' fp32

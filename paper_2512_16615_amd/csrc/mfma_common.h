@@ -167,6 +167,11 @@ template <int N> __device__ __forceinline__ void load_lds(uint64_t base, unsigne
                      : "=&s"(copy) : "s"(lds), "v"(v0), "s"(base), "v"(v1) : "memory", "m0");
 }
 #undef LLSA_LOAD_LDS
+// the same with 4 bytes a lane, from an address of its own each, to 256 bytes at `lds` (behind a load_lds, whose wait for the wave's LDS reads
+// covers these too)
+__device__ __forceinline__ void load_lds_dword(const float *p, unsigned lds) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" ::"s"(lds), "v"(p) : "memory", "m0");
+}
 #pragma clang diagnostic pop
 // Rows of D bf16 brought into LDS as swz_key wants them, 1024 bytes (512 / D rows) at a time: what a lane adds to the address of the
 // first of them.  Of two 1024 bytes of a 16-row slice in turn (v0, v1): at d = 128 the second four rows have other keys.

@@ -261,6 +261,34 @@ def test_index_transpose_by_size(T, K, heads):
         assert np.array_equal(Iq[h].cpu().numpy(), iq_ref)
 
 
+@pytest.mark.parametrize("heads,N,L,d,Le", [
+    # every query lists the first K blocks: lists of all T = N / 16 query blocks beside T - K empty ones.  Pieces of 8 tiles: 4 tiles, 10 and
+    # 12 (the first that are cut), 32 and 34 (one window of places and its end), no parent; of 16; of 32; of 64 (d = 128)
+    (1, 64, 1, 64, 1), (2, 320, 1, 64, 1), (3, 384, 1, 64, 0), (1, 1024, 1, 64, 1), (2, 1088, 1, 64, 1), (1, 1088, 1, 128, 1),
+    (16, 16384, 2, 64, 2), (8, 65536, 3, 64, 3), (8, 16384, 2, 128, 2)])
+def test_level0_lists_of_every_query(heads, N, L, d, Le):
+    """dK and dV where lists are cut into pieces that several waves add up: within the bf16 kernels' rounding of the fp32-arithmetic kernels,
+    and the same bits every time, whichever wave comes last."""
+    import torch
+    from paper_2512_16615_amd import llsa
+    gen = torch.Generator(device="cuda").manual_seed(N)
+    Q, V, dO = (torch.randn(1, heads, N, d, generator=gen, device="cuda").bfloat16() for _ in range(3))
+    K = torch.ones_like(Q)
+    got = []
+    for path in (0, 1):
+        plan = llsa.Plan(1, heads, N, d, 16, 6, L, Le=Le, kernel_path=path)
+        O, LSE, idx, ws = llsa.forward(plan, Q, K, V, workspace=plan.alloc_workspace(True))
+        got.append(llsa.backward(plan, Q, K, V, O, LSE, idx, dO, ws))
+        for _ in range(3 if path == 0 else 0):
+            for a, b in zip(got[0], llsa.backward(plan, Q, K, V, O, LSE, idx, dO, ws)):
+                assert torch.equal(a, b)
+    for name, a, b in zip(("dQ", "dK", "dV"), *got):
+        if name == "dQ":
+            continue                                        # K is constant: dQ is a sum that cancels
+        rel = float((a.double() - b.double()).norm() / b.double().norm())
+        assert rel < 1e-2, (name, rel)
+
+
 @pytest.mark.parametrize("cfg", [
     # the dense level 2 in the group kernel: one token (one query block a head), a ragged tile, all 16; two passes of listed blocks behind it;
     # the widest launch that the chain kernel does not take yet, and the first one that it does
