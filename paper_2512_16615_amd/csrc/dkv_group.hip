@@ -369,6 +369,7 @@ __global__ void __launch_bounds__(256) slab_reduce_kernel(const float *in, float
 
 // One workgroup per key block j of level l: sums the partials of the query blocks that listed j, in list
 // order, adds the parent token's share and writes the level's fp32 gradient rows.
+// FLY > 1 (no chains): that many partials are asked for before the first of them is added.
 struct GatherArgs {
     const float *part;           // [bh][cnt][nblk][UNIT]
     const int32_t *C, *Iq, *I;   // key-major lists and I^(l) (null when dense)
@@ -380,7 +381,7 @@ struct GatherArgs {
     int nblk, Kl, dense;
     int chain, apart;            // chain > 1: partials come from the chain kernel, which walked `chain` listers, `apart` apart
 };
-template <int D, int NT>
+template <int D, int NT, int FLY>
 __global__ void __launch_bounds__(NT) dkv_gather_kernel(GatherArgs a) {
     constexpr int U4 = GShape<D>::UNIT / 4, H4 = U4 / 2, PER = H4 / NT;   // float4 per partial / per half / per thread and half
     const int tid = threadIdx.x;
@@ -426,12 +427,29 @@ __global__ void __launch_bounds__(NT) dkv_gather_kernel(GatherArgs a) {
                 unit[tid] = un;
             }
             __syncthreads();
-#pragma unroll 4
-            for (int32_t e = 0; e < m; ++e) {
-                if (unit[e] < 0) continue;                                // same for every thread
-                const f32x4 *p = part + unit[e];
+            if constexpr (FLY > 1) {                                      // every partial is there
+                for (int32_t e = 0; e < m; e += FLY) {
+                    f32x4 kk[FLY][PER], vv[FLY][PER];
 #pragma unroll
-                for (int x = 0; x < PER; ++x) { k[x] += p[tid + NT * x]; v[x] += p[H4 + tid + NT * x]; }
+                    for (int f = 0; f < FLY; ++f) {
+                        const f32x4 *p = part + unit[min(e + f, m - 1)];
+#pragma unroll
+                        for (int x = 0; x < PER; ++x) { kk[f][x] = p[tid + NT * x]; vv[f][x] = p[H4 + tid + NT * x]; }
+                    }
+#pragma unroll
+                    for (int f = 0; f < FLY; ++f)
+                        if (e + f < m)
+#pragma unroll
+                            for (int x = 0; x < PER; ++x) { k[x] += kk[f][x]; v[x] += vv[f][x]; }
+                }
+            } else {
+#pragma unroll 4
+                for (int32_t e = 0; e < m; ++e) {
+                    if (unit[e] < 0) continue;                            // same for every thread
+                    const f32x4 *p = part + unit[e];
+#pragma unroll
+                    for (int x = 0; x < PER; ++x) { k[x] += p[tid + NT * x]; v[x] += p[H4 + tid + NT * x]; }
+                }
             }
         }
     }
@@ -613,9 +631,19 @@ static hipError_t finish_level(const Plan &p, const LevelTable &t, const GroupAr
     ga.chain = l == 1 ? a.GC : 1;
     ga.apart = a.GS;
     const dim3 grid((unsigned)(p.bh * ga.nkb));
-    // latency-bound (lists -> rows of I -> partials): more, smaller workgroups per CU shorten the launch
-    if (p.d == 64) dkv_gather_kernel<64, 128><<<grid, 128, 0, s>>>(ga);
-    else dkv_gather_kernel<128, 256><<<grid, 256, 0, s>>>(ga);
+    // Latency-bound (lists -> rows of I -> partials).  Many key blocks: more, smaller workgroups per CU shorten the launch, and few
+    // registers let the upper levels' gathers run beside the chain kernel, which leaves no room for larger waves (8 partials in flight
+    // there: 6 us more of 1110 a step at 16 heads x 65536 tokens, 2 of 560 at 32 x 16384).  At most 1024, and no chain kernel: the launch
+    // is as long as one workgroup's chain of loads, and twice the threads with 8 partials in flight shorten that: 16 heads x 4096
+    // tokens 12.0 -> 8.8 us, steps: 100.4 -> 96.7 us, 2 heads 69.0 -> 64.9, 8 x 16384 251 -> 242, 16 x 8192 178.6 -> 176.6.
+    const bool few = grid.x <= 1024 && a.GC == 1;
+    if (p.d == 64) {
+        if (few) dkv_gather_kernel<64, 256, 8><<<grid, 256, 0, s>>>(ga);
+        else dkv_gather_kernel<64, 128, 1><<<grid, 128, 0, s>>>(ga);
+    } else {
+        if (few) dkv_gather_kernel<128, 512, 8><<<grid, 512, 0, s>>>(ga);
+        else dkv_gather_kernel<128, 256, 1><<<grid, 256, 0, s>>>(ga);
+    }
     return hipGetLastError();
 }
 

@@ -289,6 +289,15 @@ def test_level0_lists_of_every_query(heads, N, L, d, Le):
         assert rel < 1e-2, (name, rel)
 
 
+@pytest.mark.parametrize("heads,N,L,d", [
+    # partials of levels >= 1 added eight at a time: lists of 1, 7, 8, 9 and 17 query blocks beside empty ones, of more than the threads of a
+    # workgroup (272 of 256; 528 of 512 at d = 128), of an upper level; one launch of more than 1024 workgroups, which add them one by one
+    (2, 256, 2, 64), (2, 7 * 256, 2, 64), (2, 8 * 256, 2, 64), (2, 9 * 256, 2, 128), (1, 17 * 256, 2, 64), (3, 272 * 256, 2, 64),
+    (1, 528 * 256, 2, 128), (2, 16384, 3, 64), (2, 16384, 3, 128), (5, 207 * 256, 2, 64)])
+def test_gather_of_lists_of_every_query(heads, N, L, d):
+    test_level0_lists_of_every_query(heads, N, L, d, L)
+
+
 @pytest.mark.parametrize("cfg", [
     # the dense level 2 in the group kernel: one token (one query block a head), a ragged tile, all 16; two passes of listed blocks behind it;
     # the widest launch that the chain kernel does not take yet, and the first one that it does
