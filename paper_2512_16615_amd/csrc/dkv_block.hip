@@ -1,33 +1,46 @@
 // dK, dV of a key block of several 16-key tiles on bf16 MFMA, Sec. 4.3: blocks of 32 and 64 keys at every level with lists, and
 // wide dense levels (any block size), four tiles at a time.
 //
-// All tiles of a block use one query list, so its waves stage each tile of 32 queries (Q and dO rows, LSE, D) once in LDS,
-// double-buffered, and every wave runs it against its own TPW key tiles, whose K / V operands and sums stay in registers.
-// SW waves share a staged tile and together hold the block; the 4 / SW groups of a workgroup take the list's tiles in
-// turn and are added up through LDS in order.  Two tiles per group are in flight in registers.  A block of level 0 is finished here (the parent token's share added, one
-// rounding); levels >= 1 write fp32 sums, one slab per share of the list, for dkv_reduce_kernel.
-// Bound: LDS reads (16 KB per 32 x 16 score tile at TPW = 1, half of that at 2) and the latency of the gathered rows; 16 heads
-// x 65536 tokens in blocks of 64, K = 8: level 1 340 us, level 0 423 us (profiled; 224 us each at the rate of a large matrix product).  Relative to that, when written:
-// level 1 with TPW = 1 1.12 times as long, level 0 with TPW = 2 1.11 times; with one tile in flight 1.34 and 1.23; the kernels
-// of dkv_mfma.hip, which these replace here and which staged every query tile once per key tile, 1.53 and 1.54.  (Blocks of 32 at
-// d = 64: two tiles a wave would be a wave alone with 255 registers and spills.)
+// All tiles of a block use one query list, so a tile of 32 queries (Q and dO rows, LSE, D) is brought into LDS once for the SW waves that
+// together hold the block, each a share of the rows, and every wave runs it against its own TPW key tiles, whose K / V operands and sums stay
+// in registers.  The 4 / SW groups of a workgroup take the list's tiles in turn and are added up through LDS in order.  A block of level 0 is
+// finished here (the parent token's share added, one rounding); levels >= 1 write fp32 sums, one slab per share of the list, for
+// dkv_reduce_kernel.
+// Rows go straight into LDS, into a ring of places that the loop is unrolled over: a place is asked for again as soon as the barrier says
+// that every wave is done with it.  Before, two tiles were in flight in registers and stored to LDS: those registers are waves now, and the
+// stores took as long as a third of the reads.  us (profiled, before -> now): 16 heads x 65536 tokens in blocks of 64, K = 8, level 1
+// 392 -> 325, level 0 459 -> 412; in blocks of 32 306 -> 260 and 450 -> 357; 8 heads, d = 128, blocks of 64, K = 4 280 -> 192 and 421 -> 315.
+// (With the place worked out at run time, which is an addition for every LDS read, 412 and 436.)
+// Bound: LDS reads (16 KB per 32 x 16 score tile at TPW = 1, half of that at 2) and the latency of the gathered rows (224 us each at the
+// rate of a large matrix product for the first two).  TPW = 1 at level 1 and 2 at level 0 each take about 1.1 times as long.
 #include <type_traits>
 
 #include "dkv_common.h"
 
 namespace llsa {
 
+// Waves a SIMD: what the registers have room for.  Tiles of a group in LDS, the one in hand and those on their way: three where that costs no
+// wave and the lists are long (level 1 in blocks of 64: 325 us, with four 350; d = 128 and three waves 192, with two waves and four tiles 216).
+// Steps with two and with three: level 0 in blocks of 64 at d = 64 1704 and 1717 us; with two everywhere 0.4 to 1.5 % slower than as it is.
+// Level 0 in blocks of 32: two tiles and four waves 357 us, three and three 402.
+template <int D, int TPW, int SW> struct BlockShape {
+    static constexpr int WAVES = D == 64 ? (TPW == 2 ? 3 : SW == 4 ? 5 : 4) : SW == 4 ? 3 : 2;
+    static constexpr int RING = (D == 64 ? TPW == 2 : SW == 4) ? 3 : 2;
+};
+
 template <int D, int TPW, int SW>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 64 && TPW == 1 ? 3 : 2))) dkv_block_kernel(DkvArgs a) {
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BlockShape<D, TPW, SW>::WAVES))) dkv_block_kernel(DkvArgs a) {
     using S = GShape<D>;
     constexpr int TPB = TPW * SW, P = 4 / SW;              // key tiles of the block; groups of waves
-    constexpr int HALF = 32 * S::ROWB, BUF = 2 * HALF;     // one staged tile: Q rows | dO rows
-    static_assert(SW > 1, "the waves of a group meet at the workgroup's barrier");
-    constexpr int R = 2 * 32 * S::CH / (64 * SW);          // 16-byte chunks per thread
+    constexpr int RING = BlockShape<D, TPW, SW>::RING;     // tiles of a group in LDS: one in use, one or more on their way
+    constexpr int HALF = 32 * S::ROWB, BUF = 2 * HALF;     // a tile: Q rows | dO rows
+    static_assert(RING == 2 || RING == 3, "");
+    static_assert(SW == 2 || SW == 4, "the waves of a group meet at the workgroup's barrier; each brings rows of Q or of dO");
+    constexpr int SHARE = BUF / SW, LOADS = SHARE / 1024;  // a wave's part of a tile
     constexpr int SLOTS = 2 * S::NT * TPW;                 // f32x4 sums per lane
     constexpr int RED = (P - 1) * SW * SLOTS * 64 * 16;
-    __shared__ __attribute__((aligned(16))) char lds[P * 2 * BUF > RED ? P * 2 * BUF : RED];
-    __shared__ __attribute__((aligned(16))) float st_sh[P][2][64];   // -LSE log2(e) [32] | -D [32]
+    __shared__ __attribute__((aligned(16))) char lds[P * RING * BUF > RED ? P * RING * BUF : RED];
+    __shared__ __attribute__((aligned(16))) float st_sh[P][RING][64];   // LSE [32] | D [32]
 
     const int lane = threadIdx.x & 63, i16 = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -55,70 +68,65 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 6
         groups = (unsigned)(Crow[1] - beg) << a.span_shift;
         lst = a.Iq + bh * a.rows * a.Kl_cnt + beg;
     }
-    // tiles of 32 consecutive queries: a listed block has at least two groups, so only a dense level's last tile can be short
+    // tiles of 32 consecutive queries: a listed block has at least two groups, and N is a multiple of 64, so no tile is short
     const unsigned tiles = (groups + 1) >> 1, entries = groups >> a.span_shift;
     const unsigned t_beg = (unsigned)((uint64_t)tiles * split / a.splits), t_end = (unsigned)((uint64_t)tiles * (split + 1) / a.splits);
     const unsigned span_mask = (1u << a.span_shift) - 1;
 
     int ecache = 0;                                        // lane e: list entry 64 * echunk + e
     unsigned echunk = ~0u;
-    struct Staged { u32x4 r[R]; float stat; };
-    Staged even, odd;                                      // two tiles are in flight: one is not enough for the latency of L2 misses
-    auto load = [&](Staged &x, unsigned t) {
+    const RowSource<D> src(lane);
+    const unsigned row_in = (unsigned)(wig % (SW / 2)) * (SHARE / S::ROWB);   // the wave's rows of the tile: of Q, in the group's second half of dO
+    const uint64_t rows = reinterpret_cast<uint64_t>(wig < SW / 2 ? a.Q : a.dO) + ((uint64_t)bh * a.N + row_in) * S::ROWB;
+    const float *stats = ((lane & 32) ? a.Dsum : a.LSE) + (int64_t)bh * a.N + (lane & 31);
+    const unsigned ring = lds_address(lds) + (unsigned)grp * RING * BUF + (unsigned)wig * SHARE, st_ring = lds_address(st_sh[grp]);
+    auto load = [&](unsigned t, unsigned b) {
         unsigned q0 = 32 * t;
         if (!a.dense) {
             const unsigned e = (2 * t) >> a.span_shift;
             if ((e >> 6) != echunk) {
                 echunk = e >> 6;
                 ecache = 64 * echunk + lane < entries ? lst[64 * echunk + lane] : 0;
+                asm volatile("" : "+v"(ecache));           // waited for here: at its use the compiler would wait for every tile on its way, every time
             }
             q0 = 16 * (((unsigned)__builtin_amdgcn_readlane(ecache, (int)(e & 63)) << a.span_shift) + ((2 * t) & span_mask));
         }
-        const int64_t row0 = (int64_t)bh * a.N + q0;
-        const int last = (int)min((int64_t)32, a.N - q0) - 1;           // rows past the head's end re-read its last one
+        const uint64_t from = rows + (uint64_t)q0 * S::ROWB;
+        constexpr int N = LOADS < 4 ? LOADS : 4;
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const int c = 64 * (wig + SW * r) + lane;      // chunk of [Q rows | dO rows]; one of the two for the whole wave
-            const int row = (c % (32 * S::CH)) / S::CH;
-            const uint16_t *src = 64 * (wig + SW * r) >= 32 * S::CH ? a.dO : a.Q;
-            x.r[r] = *reinterpret_cast<const u32x4 *>(src + (row0 + min(row, last)) * D + (c % S::CH) * 8);
-        }
-        {
-            const int q = lane & 31;
-            const float v = (lane & 32 ? a.Dsum : a.LSE)[row0 + min(q, last)];
-            x.stat = lane & 32 ? -v : q > last ? -INFINITY : v * -kLog2e;   // an absent query: P = 0
-        }
+        for (int r = 0; r < LOADS; r += N) load_lds<N>(from + 1024 * r, src.v0, src.v1, ring + b * BUF + 1024 * r);
+        if (wig == 0) load_lds_dword(stats + q0, st_ring + 256 * b);
     };
-    auto store = [&](const Staged &x, int b) {
-        char *buf = lds + (grp * 2 + b) * BUF;
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const int c = 64 * (wig + SW * r) + lane, row = (c % (32 * S::CH)) / S::CH;
-            *reinterpret_cast<u32x4 *>(buf + (64 * (wig + SW * r) >= 32 * S::CH ? HALF : 0) + swz<D>(row, c % S::CH)) = x.r[r];
-        }
-        if (wig == 0) st_sh[grp][b][lane] = x.stat;
+    auto wait = [&](auto ahead) {                          // all but the group's last `ahead` tiles have come, in every wave
+        constexpr int n = decltype(ahead)::value;
+        if (wig == 0) vm_wait_barrier<n * (LOADS + 1)>();
+        else vm_wait_barrier<n * LOADS>();
     };
-    const unsigned turns = (t_end - t_beg + P - 1) / P;    // the same number for every wave, rounded up to pairs
+    const unsigned turns = (t_end - t_beg + P - 1) / P;    // the same number for every wave
     unsigned t = t_beg + grp;
-    auto turn = [&](Staged &x, int b) {
-        const bool have = t < t_end;
-        if (have) store(x, b);
-        __syncthreads();
-        load(x, min(t + 2 * P, t_end - 1));                // flies during this turn's math and the next one's
-        if (have) {
-            const char *buf = lds + (grp * 2 + b) * BUF;
-            group_tile<D, TPW>(buf, buf + HALF, st_sh[grp][b], st_sh[grp][b] + 32, 0, o, key, a.sc2, g);
+#pragma unroll
+    for (int x = 0; x < TPW; ++x)                          // the keys have come before the first tile is asked for (see ecache)
+#pragma unroll
+        for (int ks = 0; ks < S::KS; ++ks) asm volatile("" : "+v"(key[x].kop[ks]), "+v"(key[x].vop[ks]));
+#pragma unroll
+    for (int b = 0; b < RING - 1; ++b)
+        if (t + b * P < t_end) load(t + b * P, b);
+    auto turn = [&](auto place) {
+        constexpr int cur = decltype(place)::value;
+        if (RING == 3 && t + P < t_end) wait(std::integral_constant<int, 1>());
+        else wait(std::integral_constant<int, 0>());
+        // no wave reads the tile before this one any more: its place is the next one's
+        if (t + (RING - 1) * P < t_end) load(t + (RING - 1) * P, cur == 0 ? RING - 1 : cur - 1);
+        if (t < t_end) {
+            const char *buf = lds + (grp * RING + cur) * BUF;
+            group_tile<D, TPW, true>(buf, buf + HALF, st_sh[grp][cur], st_sh[grp][cur] + 32, 0, o, key, a.sc2, g);
         }
         t += P;
     };
-    // (loads behind a condition would make every wait one for all loads: past the end they repeat the last tile)
-    if (turns > 0) {
-        load(even, min(t, t_end - 1));
-        load(odd, min(t + P, t_end - 1));
-    }
-    for (unsigned i = 0; i < turns; i += 2) {
-        turn(even, 0);
-        turn(odd, 1);
+    for (unsigned i = 0; i < turns; i += RING) {
+        turn(std::integral_constant<int, 0>());
+        if (i + 1 < turns) turn(std::integral_constant<int, 1>());
+        if (RING == 3 && i + 2 < turns) turn(std::integral_constant<int, RING - 1>());
     }
 
     if constexpr (P > 1) {                                 // the groups' sums, in group order

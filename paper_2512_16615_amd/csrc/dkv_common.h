@@ -56,7 +56,8 @@ template <int D> struct BlockAcc {
 
 // queries 32u .. 32u+31 of the staged rows (lse: -LSE log2(e) of the rows, nd: -D) against NB key blocks:
 // accK += Q^T dS, accV += dO^T P.  Every LDS operand is read once and used for all NB blocks; the sums of dP start from -D.
-template <int D, int NB>
+// RAW: lse and nd are LSE and D as they are in memory.
+template <int D, int NB, bool RAW = false>
 __device__ __forceinline__ void group_tile(const char *qs, const char *gs, const float *lse, const float *nd, int u,
                                            const TileOffsets<D> &o, BlockAcc<D> (&blk)[NB], float sc2, int g) {
     using S = GShape<D>;
@@ -70,8 +71,11 @@ __device__ __forceinline__ void group_tile(const char *qs, const char *gs, const
             aq[ks] = *reinterpret_cast<const bf16x8 *>(qs + base + o.row[ks]);
             ag[ks] = *reinterpret_cast<const bf16x8 *>(gs + base + o.row[ks]);
         }
-        const f32x4 l2 = *reinterpret_cast<const f32x4 *>(lse + 32 * u + 16 * h + 4 * g);
-        const f32x4 ndl = *reinterpret_cast<const f32x4 *>(nd + 32 * u + 16 * h + 4 * g);
+        f32x4 l2 = *reinterpret_cast<const f32x4 *>(lse + 32 * u + 16 * h + 4 * g);
+        f32x4 ndl = *reinterpret_cast<const f32x4 *>(nd + 32 * u + 16 * h + 4 * g);
+        if constexpr (RAW)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) { l2[r] *= -kLog2e; ndl[r] = -ndl[r]; }
 #pragma unroll
         for (int b = 0; b < NB; ++b) {
             s[b][h] = f32x4{0.f, 0.f, 0.f, 0.f};

@@ -382,6 +382,33 @@ def test_key_blocks_of_several_tiles(cfg):
     _full_parity(cfg, 0xD15F)
 
 
+@pytest.mark.parametrize("heads,N,B,d,L", [
+    # every query lists the same key blocks: tiles in a ring of two or three places, taken in turn by one group of waves (blocks of 64) or two.
+    # 1 tile a group, 2, 3, 4, 5 and 7; lists of more than 64 entries, the next 64 looked up while tiles are on their way; a level 1 whose lists
+    # are shared out; d = 128
+    (2, 64, 32, 64, 1), (1, 128, 32, 64, 1), (3, 192, 32, 64, 1), (1, 448, 32, 128, 1), (1, 2112, 32, 64, 1), (2, 32768, 32, 64, 2),
+    (2, 64, 64, 64, 1), (3, 192, 64, 64, 1), (1, 320, 64, 128, 1), (1, 4160, 64, 64, 1), (1, 4160, 64, 128, 1), (2, 36864, 64, 64, 2),
+    (1, 36864, 64, 128, 2)])
+def test_key_blocks_of_several_tiles_listed_by_every_query(heads, N, B, d, L):
+    """dK and dV within the bf16 kernels' rounding of P and dS of the fp32-arithmetic kernels, and the same bits every time."""
+    import torch
+    from paper_2512_16615_amd import llsa
+    gen = torch.Generator(device="cuda").manual_seed(N + B)
+    Q, V, dO = (torch.randn(1, heads, N, d, generator=gen, device="cuda").bfloat16() for _ in range(3))
+    K = torch.ones_like(Q)
+    got = []
+    for path in (0, 1):
+        plan = llsa.Plan(1, heads, N, d, B, 6, L, kernel_path=path)
+        O, LSE, idx, ws = llsa.forward(plan, Q, K, V, workspace=plan.alloc_workspace(True))
+        got.append([x.clone() for x in llsa.backward(plan, Q, K, V, O, LSE, idx, dO, ws)])
+        for _ in range(2 if path == 0 else 0):
+            for a, b in zip(got[0], llsa.backward(plan, Q, K, V, O, LSE, idx, dO, ws)):
+                assert torch.equal(a, b)
+    for name, a, b in list(zip(("dQ", "dK", "dV"), *got))[1:]:   # K is constant: dQ is a sum that cancels
+        rel = float((a.double() - b.double()).norm() / b.double().norm())
+        assert rel < 1e-2, (name, rel)
+
+
 @pytest.mark.parametrize("cfg", [
     # the fp32-arithmetic kernels (no multiple of 64) on a chip full of query tiles, on lists of 33 blocks, on blocks of two tiles
     _bf16("B16_400_heads256", 400, heads=256),
