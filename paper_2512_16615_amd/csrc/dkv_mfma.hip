@@ -237,7 +237,13 @@ struct FineArgs {
     unsigned T, places, slots, packs;                       // of a head: key blocks, places, slots of pieces, waves for tiles
     int lc, pack;                                           // log2 of the tiles of a piece; a wave takes the lists and pieces that begin in `pack` places
     FastDiv waves;                                          // waves of a head
+    int stretch;                                            // log2 of the consecutive waves that an XCD takes at a time; -1: an eighth of all
 };
+__device__ __forceinline__ unsigned xcd_stretches(unsigned w, unsigned total, int ls) {
+    if (ls < 0) return xcd_contiguous32(w, total);
+    const unsigned r = w & ((8u << ls) - 1), w0 = w - r;
+    return w0 + (8u << ls) <= total ? w0 + ((r & 7) << ls) + (r >> 3) : w;
+}
 
 template <int D>
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(D == 64 ? 3 : 2))) dkv_fine_kernel(DkvArgs a, FineArgs f) {
@@ -249,7 +255,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(D == 64
 
     const int lane = threadIdx.x, i16 = lane & 15, g = lane >> 4;
     const bool has_par = a.parK != nullptr;
-    const unsigned id = xcd_contiguous32(blockIdx.x, gridDim.x), bh = f.waves(id), v = id - bh * f.waves.d;
+    const unsigned id = xcd_stretches(blockIdx.x, gridDim.x, f.stretch), bh = f.waves(id), v = id - bh * f.waves.d;
     const int64_t key0 = (int64_t)bh * f.T;
     const int32_t *C = a.C + (int64_t)bh * (f.T + 1);
 
@@ -518,7 +524,15 @@ bool dkv_by_tiles(const Plan &p) { return p.fast && p.B == 16; }
 static int64_t fine_tiles(const Plan &p) { return p.bh * tile_places(p.n[1], p.n[1] * p.Kl[0]); }
 static bool few_tiles(const Plan &p) { return fine_tiles(p) <= 8 * (p.d == 128 ? 2048 : 3072); }
 int fine_piece_log2(const Plan &p) { return few_tiles(p) ? 3 : p.d == 128 ? 6 : fine_tiles(p) > 64 * 3072 ? 5 : 4; }
-static int fine_pack(const Plan &p) { return few_tiles(p) ? 2 : 8; }
+// Places of a wave: more than four only where the waves have enough to do for their end not to matter (steps with 4 and 8: 4 x 110592 tokens,
+// K = 4, Gaussian 460 and 474 us, smooth 439 and 447, 4 x 65536, K = 8 417 and 425; 16 x 65536 1082 and 1070).
+static int fine_pack(const Plan &p) { return few_tiles(p) ? 2 : fine_tiles(p) <= 64 * 3072 ? 4 : 8; }
+// Whole stretches of heads keep rows that neighbouring blocks share in an XCD's L2 (dealt in stretches of 32 to 512 waves 16 x 65536 tokens, K = 8,
+// 1 to 7 % slower, 8 x 262144 at d = 128, K = 16 6 to 12).  With lists of few blocks there is less to share, and where a head's Q and dO are
+// more than 16 MB, eight XCDs in as many places are more than the cache behind L2 holds.  Steps, whole and in stretches of 64 waves, K = 4:
+// 8 x 131072 955 and 939 us, Gaussian 995 and 975, 2 x 262144 Gaussian 649 and 639, 4 x 110592 446 and 450, Gaussian 468 and 461; but 4 x 65536
+// (16 MB) 291 and 304.
+static int fine_stretch(const Plan &p) { return p.Kl[0] <= 4 && p.N * p.d * 4 > 16 << 20 ? 6 : -1; }
 
 // level0_alone: level 0's own gradient only, without the share of its parent tokens (the pooled levels' gradients)
 hipError_t launch_dkv_mfma(const Plan &p, const LevelTable &t, int l, const void *Q, const void *dO, const float *LSE,
@@ -562,6 +576,7 @@ hipError_t launch_dkv_mfma(const Plan &p, const LevelTable &t, int l, const void
         f.lc = fine_piece_log2(p);
         f.slots = (unsigned)piece_slots(T, E, f.lc);
         f.pack = fine_pack(p);
+        f.stretch = fine_stretch(p);
         f.packs = (f.places + f.pack - 1) / f.pack;
         f.waves = FastDiv(f.packs + (T + kEmpty - 1) / kEmpty);
         const unsigned wgs = (unsigned)p.bh * f.waves.d;

@@ -289,6 +289,26 @@ def test_level0_lists_of_every_query(heads, N, L, d, Le):
         assert rel < 1e-2, (name, rel)
 
 
+@pytest.mark.parametrize("heads,N,d,K", [
+    # few picks of heads of more than 16 MB of Q and dO: XCDs take 64 waves at a time, the last few hundred waves one each; and just below
+    (1, 66560, 64, 3), (3, 66560, 64, 4), (1, 33792, 128, 4), (2, 65536, 64, 4), (1, 66560, 64, 5)])
+def test_level0_waves_dealt_in_stretches(heads, N, d, K):
+    """Every row of dK and dV is written, within the bf16 kernels' rounding of P and dS of the fp32-arithmetic kernels."""
+    import torch
+    from paper_2512_16615_amd import llsa
+    gen = torch.Generator(device="cuda").manual_seed(N + K)
+    Q, Kt, V, dO = (torch.randn(1, heads, N, d, generator=gen, device="cuda").bfloat16() for _ in range(4))
+    got = []
+    for path in (0, 1):
+        plan = llsa.Plan(1, heads, N, d, 16, K, 2, kernel_path=path)
+        O, LSE, idx, ws = llsa.forward(plan, Q, Kt, V, workspace=plan.alloc_workspace(True))
+        out = [torch.full_like(Q, float("nan")) for _ in range(3)]
+        got.append(llsa.backward(plan, Q, Kt, V, O, LSE, idx, dO, ws, *out))
+    for name, a, b in list(zip(("dQ", "dK", "dV"), *got))[1:]:
+        rel = float((a.double() - b.double()).norm() / b.double().norm())
+        assert rel < 1e-2, (name, rel)
+
+
 @pytest.mark.parametrize("heads,N,L,d", [
     # partials of levels >= 1 added eight at a time: lists of 1, 7, 8, 9 and 17 query blocks beside empty ones, of more than the threads of a
     # workgroup (272 of 256; 528 of 512 at d = 128), of an upper level; one launch of more than 1024 workgroups, which add them one by one
