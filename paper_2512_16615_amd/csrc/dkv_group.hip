@@ -13,7 +13,7 @@
 //     neighbouring R and a key block listed by a run of them keeps its sums in registers: one partial per run;
 //   dkv_upper_kernel: levels >= 2 only.  The 16 level-1 blocks under one level-2 query block list the same
 //     key blocks at every level >= 2, so a workgroup of 8 waves walks G of them (G divides 16; the next one's
-//     rows are prefetched into registers) and keeps its accumulators in registers meanwhile: every wave owns
+//     rows are prefetched into registers; d = 128: dkv_upper_ring_kernel) and keeps its accumulators in registers meanwhile: every wave owns
 //     one or two of the listed blocks, and (d = 64) the single block of a coarsest level of at most 16 tokens is shared:
 //     wave w takes query tile w of every R and the 8 waves' sums are added through LDS at the end.  G times fewer partials,
 //     and no idle rounds when the number of key blocks is not a multiple of the waves.  The blocks of a larger dense level
@@ -190,6 +190,41 @@ __global__ void __launch_bounds__(64 * NW) dkv_group_kernel(LevelTable t, GroupA
     }
 }
 
+// Tiles of 32 queries (Q rows | dO rows, LSE and D) on their way from memory straight into a ring of RING places in LDS, each of a workgroup's NW
+// waves bringing a share of the rows.  All RING - 1 tiles behind the one in hand are always asked for (past the end the caller names a
+// tile again), so that a wave knows how many of its loads may still be out.
+template <int D, int NW, int RING> struct TileRing {
+    static constexpr int HALF = 32 * GShape<D>::ROWB, BUF = 2 * HALF, SHARE = BUF / NW, LOADS = SHARE / 1024;
+    uint64_t from;
+    const float *stats;
+    unsigned rows_at, stats_at;
+    RowSource<D> src;
+    int wave;
+    // lds: [RING][BUF]; st: [RING][64]; q0: first query row of what the workgroup walks
+    __device__ __forceinline__ TileRing(const GroupArgs &a, int64_t q0, const char *lds, const float *st, int wave_, int lane) : src(lane), wave(wave_) {
+        from = reinterpret_cast<uint64_t>(wave < NW / 2 ? a.Q : a.dO) + (uint64_t)(q0 + (wave % (NW / 2)) * (SHARE / GShape<D>::ROWB)) * GShape<D>::ROWB;
+        stats = ((lane & 32) ? a.Dsum : a.LSE) + q0 + (lane & 31);
+        rows_at = lds_address(lds) + (unsigned)wave * SHARE;
+        stats_at = lds_address(st);
+    }
+    __device__ __forceinline__ void load(int64_t q, int place) const {   // the tile q queries behind the first
+        load_lds<LOADS>(from + (uint64_t)q * GShape<D>::ROWB, src.v0, src.v1, rows_at + place * BUF);
+        if (wave == 0) load_lds_dword(stats + q, stats_at + 256 * place);
+    }
+    // the next tile is there, and no wave reads the one before it any more
+    __device__ __forceinline__ void wait() const {
+        if (wave == 0) vm_wait_barrier<(RING - 2) * (LOADS + 1)>();
+        else vm_wait_barrier<(RING - 2) * LOADS>();
+    }
+};
+// keys that the compiler waits for here: at their use it would wait for every tile on its way, each time
+template <int D> __device__ __forceinline__ void keys_come(BlockAcc<D> &b) {
+#pragma unroll
+    for (int ks = 0; ks < D / 32; ++ks) asm volatile("" : "+v"(b.kop[ks]), "+v"(b.vop[ks]));
+}
+
+constexpr int kChain = 8;                                              // query blocks of a chain at most
+
 // Level 1 alone, rows of I^(1) with at most NW * NB * P entries.  Neighbouring level-1 query blocks list mostly the same
 // level-1 key blocks (for spatially smooth inputs a block stays listed over many consecutive rows), and a partial per
 // (query block, listed block) then carries the same key block's sums to memory again and again.  Here a workgroup
@@ -201,16 +236,20 @@ __global__ void __launch_bounds__(64 * NW) dkv_group_kernel(LevelTable t, GroupA
 // one chain that all list the key block, and sits where the last of them would have put its own; the gather skips
 // a lister whose successor in the same chain lists the block too.  Same arithmetic per tile, fewer partials.
 // P workgroups share the slots of a row of more than NW * NB entries; each walks the same rows and keeps the same books.
+// The tiles stream through a ring in LDS that runs on from query block to query block; the rows of I^(1) are looked up once, since a load of the
+// compiler's in the walk would be waited for together with every tile on its way.  Bound: LDS reads and issue at two (d = 128: three) waves a
+// SIMD.  With all 256 rows staged in LDS by way of registers, kernel, us: 16 heads x 65536 tokens 107 -> 99, 8 x 65536, d = 128 133 -> 118,
+// 8 x 262144, d = 128, K = 16 800 -> 611; steps, 32 x 16384 527 -> 510.  (d = 64 with three waves a SIMD spills 6 registers: 103; two places 101.)
 template <int D, int NW, int NB, int P>
-__global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) dkv_chain_kernel(LevelTable t, GroupArgs a) {
+__global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW == 8 || NB == 2 ? 2 : D == 128 ? 3 : 4))) dkv_chain_kernel(LevelTable t, GroupArgs a) {
     using S = GShape<D>;
-    constexpr int SL = NW * NB * P;
-    __shared__ __attribute__((aligned(16))) char qs[256 * S::ROWB];
-    __shared__ __attribute__((aligned(16))) char gs[256 * S::ROWB];
-    __shared__ __attribute__((aligned(16))) float st[512];
+    constexpr int SL = NW * NB * P, RING = NW == 4 && D == 128 ? 2 : 4;
+    using Ring = TileRing<D, NW, RING>;
+    __shared__ __attribute__((aligned(16))) char lds[RING * Ring::BUF];
+    __shared__ __attribute__((aligned(16))) float st_sh[RING][64];    // LSE [32] | D [32]
 
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int g = lane >> 4;
     const int64_t per_head = a.NR / a.GC;
     const int64_t wg = xcd_contiguous(blockIdx.x, gridDim.x), chain = wg / P, bh = chain / per_head, c = chain % per_head;
@@ -225,22 +264,45 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2)
     float *slab1 = a.slab + a.lvl_off[1] + (bh * a.NR + R0) * Kl * S::UNIT;
     const int64_t far = (int64_t)a.GS * Kl;                           // from a row of the chain to the next
 
-    int sblk = -1, spos = 0;                                          // lane s < Kl: the block slot s holds, its place in the row
-    BlockAcc<D> blk[NB];                                              // this wave's slots slot0 ...
-    for (int r = 0; r < a.GC; ++r) {
-        StageRegs<D, 64 * NW> sr;
-        stage_load<D, 64 * NW>(sr, a, bh * a.N + (R0 + (int64_t)r * a.GS) * 256, tid);   // in flight during the bookkeeping below
-        const int nb = lane < Kl ? I1[r * far + lane] : -1;            // lane p: entry p of this query block's row
-        if (r == 0) {
-            sblk = nb;
-            spos = lane;
+    // the chain's rows of I^(1): entry e = row * Kl + place in lane e % 64 of word e / 64
+    int rows[kChain * 16 / 64];
 #pragma unroll
-            for (int b = 0; b < NB; ++b) {
-                const int64_t id = max(__builtin_amdgcn_readlane(nb, slot0 + b), 0);
-                blk[b].load(K1 + id * 16 * D * 2, V1 + id * 16 * D * 2, 16, bias2, lane);
-                blk[b].clear();
-            }
-        } else {
+    for (int x = 0; x < kChain * 16 / 64; ++x) {
+        const int e = 64 * x + lane;
+        rows[x] = e < a.GC * Kl ? I1[e / Kl * far + e % Kl] : -1;
+    }
+    auto row = [&](int r) {                                           // lane p: entry p of row r, -1 from Kl on
+        const int e = r * Kl + min(lane, Kl - 1);
+        int v = __shfl(rows[0], e & 63, 64);
+#pragma unroll
+        for (int x = 1; x < kChain * 16 / 64; ++x) {
+            const int y = __shfl(rows[x], e & 63, 64);
+            v = e >> 6 == x ? y : v;
+        }
+        return lane < Kl ? v : -1;
+    };
+    int sblk = row(0), spos = lane;                                   // lane s < Kl: the block slot s holds, its place in the row
+    BlockAcc<D> blk[NB];                                              // this wave's slots slot0 ...
+    auto take = [&](int b, int id) {
+        const int64_t at = (int64_t)max(id, 0) * 16 * D * 2;
+        blk[b].load(K1 + at, V1 + at, 16, bias2, lane);
+        blk[b].clear();
+        keys_come(blk[b]);
+    };
+#pragma unroll
+    for (int b = 0; b < NB; ++b) take(b, __builtin_amdgcn_readlane(sblk, slot0 + b));
+
+    const Ring ring(a, bh * a.N + R0 * 256, lds, &st_sh[0][0], wave, lane);
+    const int last = 8 * a.GC - 1;
+    auto load = [&](int tile, int place) {                            // tile: 8 * row of the chain + its eighth
+        tile = min(tile, last);
+        ring.load((int64_t)(tile >> 3) * a.GS * 256 + 32 * (tile & 7), place);
+    };
+#pragma unroll
+    for (int x = 0; x < RING - 1; ++x) load(x, x);
+    for (int r = 0; r < a.GC; ++r) {
+        if (r > 0) {
+            const int nb = row(r);
             bool keep = false, fresh = lane < Kl;                  // (slots without a block keep it: -1 on both sides)
             int npos = 0;
 #pragma unroll
@@ -254,33 +316,84 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2)
             uint64_t m = news;
 #pragma unroll
             for (int x = 0; x < SL; ++x) m = (x < k) ? (m & (m - 1)) : m;
-            const int src = m ? (int)__builtin_ctzll(m) : 0;
-            const int nid = __shfl(nb, src, 64);
+            const int from = m ? (int)__builtin_ctzll(m) : 0;
+            const int nid = __shfl(nb, from, 64);
 #pragma unroll
             for (int b = 0; b < NB; ++b) {
                 const int s = slot0 + b;
                 if (!((kept >> s) & 1)) {                             // wave-uniform
                     const int oldpos = __builtin_amdgcn_readlane(spos, s);
                     store_partial(slab1 + ((r - 1) * far + oldpos) * S::UNIT, blk[b], a.scale, lane);
-                    const int64_t id = __builtin_amdgcn_readlane(nid, s);
-                    blk[b].load(K1 + id * 16 * D * 2, V1 + id * 16 * D * 2, 16, bias2, lane);
-                    blk[b].clear();
+                    take(b, __builtin_amdgcn_readlane(nid, s));
                 }
             }
             sblk = keep ? sblk : nid;
-            spos = keep ? npos : src;
+            spos = keep ? npos : from;
         }
-        __syncthreads();                                              // everyone is done with the previous rows
-        stage_store<D, 64 * NW>(sr, qs, gs, st, tid);
-        __syncthreads();
-        for (int u = 0; u < 8; ++u) group_tile<D, NB>(qs, gs, st, st + 256, u, o, blk, a.sc2, g);
+        for (int u = 0; u < 8; u += RING)
+#pragma unroll
+            for (int x = 0; x < RING; ++x) {
+                ring.wait();
+                load(8 * r + u + x + RING - 1, (x + RING - 1) % RING);
+                const char *buf = lds + x * Ring::BUF;
+                group_tile<D, NB, true>(buf, buf + Ring::HALF, st_sh[x], st_sh[x] + 32, 0, o, blk, a.sc2, g);
+            }
     }
+    vm_wait<0>();                                                     // nothing may still come into LDS that is another workgroup's by then
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
         if (slot0 + b >= Kl) continue;
         const int pos = __builtin_amdgcn_readlane(spos, slot0 + b);
         store_partial(slab1 + ((a.GC - 1) * far + pos) * S::UNIT, blk[b], a.scale, lane);
     }
+}
+
+// d = 128, where a workgroup of eight waves that holds all 256 rows of Q and dO has a CU to itself, two waves a SIMD: workgroups of four, three on
+// a CU, with the tiles in a ring of two places.  A wave owns a listed block.  Bound: LDS reads and issue.  us, before -> now: 8 heads x 262144
+// tokens, K = 16 (36 blocks) 1066 -> 876 (with four places, two workgroups a CU, 1055), 8 x 65536, K = 8 104 -> 98; steps 6997 -> 6698 and
+// 1184 -> 1168 with the chain kernel's ring, 2 x 131072, K = 4 574 -> 526, Gaussian 568 -> 520.
+template <int D, int NW>
+__global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(3))) dkv_upper_ring_kernel(LevelTable t, GroupArgs a) {
+    constexpr int RING = 2;
+    using Ring = TileRing<D, NW, RING>;
+    __shared__ __attribute__((aligned(16))) char lds[RING * Ring::BUF];
+    __shared__ __attribute__((aligned(16))) float st_sh[RING][64];    // LSE [32] | D [32]
+
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int g = lane >> 4;
+    const int64_t per_head = a.NR / a.G;
+    const unsigned ngrp = gridDim.x / (unsigned)a.passes, c0 = blockIdx.x / (8u * a.passes) * 8u;   // eight groups, pass by pass
+    const unsigned width = min(8u, ngrp - c0), rem = blockIdx.x - c0 * a.passes;
+    const int jb = (int)(rem / width) * NW + wave;                    // this wave's listed block
+    const int64_t grp = c0 + rem % width;                             // query group: G consecutive level-1 query blocks
+    const int64_t bh = grp / per_head, R0 = (grp % per_head) * a.G;
+    const TileOffsets<D> o = tile_offsets<D>(lane);
+    const int nlev = min(t.nlev, a.lev_end);
+    const int u_begin = t.bseg[2];                                    // first listed block of level 2
+    const bool have = jb < a.nbs;
+    BlockAcc<D> blk[1];
+    {
+        BlockTable ctab;                                              // lane j: listed block u_begin + 64 * (jb / 64) + j
+        ctab.fill(t, bh, R0 * 16, u_begin, have ? jb >> 6 : 0, lane, D, nlev);
+        blk[0].load(have ? ctab.K(jb & 63) : nullptr, ctab.V(jb & 63), ctab.count(jb & 63), ctab.bias(jb & 63), lane);
+        blk[0].clear();
+        keys_come(blk[0]);
+    }
+    const Ring ring(a, bh * a.N + R0 * 256, lds, &st_sh[0][0], wave, lane);
+    const int last = 8 * a.G - 1;
+#pragma unroll
+    for (int x = 0; x < RING - 1; ++x) ring.load(32 * x, x);
+    for (int u = 0; u <= last; u += RING)
+#pragma unroll
+        for (int x = 0; x < RING; ++x) {
+            ring.wait();
+            ring.load(32 * (int64_t)min(u + x + RING - 1, last), (x + RING - 1) % RING);
+            const char *buf = lds + x * Ring::BUF;
+            if (have) group_tile<D, 1, true>(buf, buf + Ring::HALF, st_sh[x], st_sh[x] + 32, 0, o, blk, a.sc2, g);
+        }
+    vm_wait<0>();                                                     // nothing may still come into LDS that is another workgroup's by then
+    if (have) store_partial(partial_ptr<D>(t, a, nlev, u_begin + jb, grp), blk[0], a.scale, lane);
 }
 
 // SS = listed blocks a wave owns (block wave of the workgroup's share, + 8, ...): a workgroup takes 8 SS of them, and where a
@@ -297,7 +410,7 @@ __global__ void __launch_bounds__(512) dkv_upper_kernel(LevelTable t, GroupArgs 
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int i16 = lane & 15, g = lane >> 4;
+    const int g = lane >> 4;
     const int64_t per_head = a.NR / a.G;
     const unsigned ngrp = gridDim.x / (unsigned)a.passes, c0 = blockIdx.x / (8u * a.passes) * 8u;   // eight groups, pass by pass
     const unsigned width = min(8u, ngrp - c0), rem = blockIdx.x - c0 * a.passes;
@@ -515,7 +628,7 @@ static int upper_G(const Plan &p) {
 }
 
 // Level-1 query blocks one workgroup of the chain kernel walks (1: the plain group kernel takes level 1), and how far apart they are.
-// Rows of at most 16 level-1 blocks (beyond 8: two workgroups that stage the same rows), level 1 sparse and the only level the kernel
+// Rows of at most 16 level-1 blocks (beyond 8: several workgroups that stage the same rows), level 1 sparse and the only level the kernel
 // is given.
 // GS: 256 tokens of a square grid in raster order are a row's part from 262144 tokens on, and the query block next to R in the
 // list of tokens lies beside it, 256 pixels away; the one below it, which lists 90 % of the same blocks on smooth inputs where
@@ -530,7 +643,6 @@ static int upper_G(const Plan &p) {
 // 2463; Gaussian, which share few blocks: K = 4 970 -> 951, d = 128 2903 -> 2868.
 // Measured at 16 heads x 65536 tokens: 8 query blocks per workgroup in 512 workgroups (two per CU) 259 us for the coarse stage,
 // 4 in 1024: 275 us, 2: 297 us, 16 in 256 workgroups: 286 us, one query block per workgroup (no carrying): 357 us.
-// (Rows straight into LDS in a ring of eight tiles that runs on from query block to query block: 245 -> 272 us.)
 static void chain_shape(const Plan &p, int *GC, int *GS) {
     *GC = *GS = 1;
     if (p.L < 2 || p.Kl[1] > 16) return;
@@ -651,8 +763,11 @@ static hipError_t launch_group_kernel(const Plan &p, const LevelTable &t, const 
     if (a.GC > 1) {
         const unsigned wgs = (unsigned)(p.bh * (a.NR / a.GC));
         if (p.d == 128) {
-            if (p.Kl[1] <= 8) dkv_chain_kernel<128, 8, 1, 1><<<wgs, 512, 0, s>>>(t, a);
-            else dkv_chain_kernel<128, 8, 1, 2><<<2 * wgs, 512, 0, s>>>(t, a);
+            // workgroups of four waves, three on a CU, where they split a row of more than eight blocks (four of them 611 us, two of eight waves
+            // 742 at 8 x 262144 tokens, K = 16); for 5 to 8 blocks one of eight (steps at 8 x 65536 1200 us, two of four 1237)
+            if (p.Kl[1] <= 4) dkv_chain_kernel<128, 4, 1, 1><<<wgs, 256, 0, s>>>(t, a);
+            else if (p.Kl[1] <= 8) dkv_chain_kernel<128, 8, 1, 1><<<wgs, 512, 0, s>>>(t, a);
+            else dkv_chain_kernel<128, 4, 1, 4><<<4 * wgs, 256, 0, s>>>(t, a);
         } else if (p.Kl[1] <= 4) dkv_chain_kernel<64, 4, 1, 1><<<wgs, 256, 0, s>>>(t, a);
         else if (p.Kl[1] <= 8) dkv_chain_kernel<64, 4, 2, 1><<<wgs, 256, 0, s>>>(t, a);
         else dkv_chain_kernel<64, 4, 2, 2><<<2 * wgs, 256, 0, s>>>(t, a);
@@ -694,10 +809,11 @@ hipError_t launch_dkv_group(const Plan &p, const LevelTable &t, const void *Q, c
         // Backward, 16 / 8 to a workgroup: 8 heads x 589824 tokens (17 blocks) 5264 / 5081 us, Gaussian 5610 / 5320, 16 x 66560 (17)
         // 1198 / 1095, 16 x 69632, K = 16 (18) 1726 / 1588; 8 x 131072 (32) 1215 / 1258, 16 x 33280 (9) 309 / 323.
         const bool rest = up.nbs > 16 && (up.nbs - 1) % 16 < 8;
-        const int share = p.d == 64 && up.nbs > 8 && !rest ? 16 : 8;
+        // (d = 128: four, dkv_upper_ring_kernel)
+        const int share = p.d == 128 ? 4 : up.nbs > 8 && !rest ? 16 : 8;
         up.passes = max(1, (up.nbs + share - 1) / share);
         const dim3 grid((unsigned)(p.bh * (NR / G) * up.passes));
-        if (p.d == 128) dkv_upper_kernel<128, 1, false><<<grid, 512, 0, s>>>(t, up);
+        if (p.d == 128) dkv_upper_ring_kernel<128, 4><<<grid, 256, 0, s>>>(t, up);
         else if (share == 8) dkv_upper_kernel<64, 1, true><<<grid, 512, 0, s>>>(t, up);
         else if (up.nbd == 0) dkv_upper_kernel<64, 2, false><<<grid, 512, 0, s>>>(t, up);
         else dkv_upper_kernel<64, 2, true><<<grid, 512, 0, s>>>(t, up);

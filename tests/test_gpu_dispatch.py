@@ -477,6 +477,20 @@ def test_level1_sums_carried_along_query_blocks(cfg):
     _full_parity(cfg, 0xD161)
 
 
+@pytest.mark.parametrize("cfg", [
+    # d = 128, workgroups of four waves: level 1 of one, three and four listed blocks; levels >= 2 of 1 + 1, 5 + 1 and 9 + 1 (one share, a ragged
+    # one, three)
+    _bf16("chain_K1", 8192, L=2, heads=32, K=1, d=128),
+    _bf16("chain_K3", 8192, L=2, heads=32, K=3, d=128),
+    _bf16("chain_K4", 8192, L=2, heads=32, K=4, d=128),
+    _bf16("upper_K1", 2 * 4096, L=3, heads=2, K=1, d=128),
+    _bf16("upper_K5", 9 * 4096, L=3, heads=1, K=5, d=128),
+    _bf16("upper_K9", 10 * 4096, L=3, heads=1, K=9, d=128),
+], ids=lambda c: c["name"])
+def test_coarse_levels_of_wide_heads(cfg):
+    _full_parity(cfg, 0xD162)
+
+
 @pytest.mark.parametrize("heads,K,d", [(64, 3, 64), (64, 6, 64), (32, 8, 64), (64, 6, 128), (64, 8, 128), (64, 12, 64), (32, 16, 128)])
 def test_level1_sums_carried_through_several_query_blocks(heads, K, d):
     """Chains of 8 (heads x level-1 query blocks >= 4096) or 4 query blocks on smooth inputs, whose blocks stay listed: slots are kept,
