@@ -221,7 +221,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 6
 // A wave by itself: the lists that begin in its few places of the head's row of tiles, one after the other without a stop (the next list's
 // rows, keys and parent row are on their way while the one in hand is finished), or a piece of a list that is cut.  No wave waits for
 // another.  Rows, logsumexps, D and the parents' gradients all go straight into LDS.  XCDs take whole stretches of heads, whose rows stay in
-// their L2 (74 % of the requests hit, 0.65 GB fetched at 16 x 65536 tokens; dealt round 340 us, 1.4 GB).
+// their L2 (0.97 GB fetched from beyond at 16 x 65536 tokens; dealt round 340 us, 1.4 GB).
 // A workgroup of four waves per four key blocks, the short lists by one wave each and the long ones by all four afterwards, with a barrier
 // between, took 295 us at 16 x 65536 tokens (now 254; Gaussian 325, 318), 150 at 32 x 16384 (133), 26 at 16 x 4096 (21), 1580 at 8 x 262144
 // with d = 128 and K = 16 (1610); with constant keys, whose lists hold every query, a step of 4 x 65536 takes 559 us instead of 1226.
