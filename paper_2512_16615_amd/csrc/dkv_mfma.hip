@@ -234,9 +234,11 @@ struct FineArgs {
     const FineTile *tiles;
     int32_t *arrived;
     float *part;
-    unsigned T, places, slots, packs;                       // of a head: key blocks, places, slots of pieces, waves for tiles
+    unsigned T, places, slots;                              // of a head: key blocks, places, slots of pieces
     int lc, pack;                                           // log2 of the tiles of a piece; a wave takes the lists and pieces that begin in `pack` places
-    FastDiv waves;                                          // waves of a head
+    FastDiv packs, others;                                  // of a head: waves for tiles, waves for key blocks that nothing lists
+    FastDiv span;                                           // waves of a part of the launch: of a head, or of all of them (fine_one_part)
+    unsigned walks, dealt;                                  // waves for tiles, which come first in a part; waves that are dealt to the XCDs
     int stretch;                                            // log2 of the consecutive waves that an XCD takes at a time; -1: an eighth of all
 };
 __device__ __forceinline__ unsigned xcd_stretches(unsigned w, unsigned total, int ls) {
@@ -255,12 +257,16 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(D == 64
 
     const int lane = threadIdx.x, i16 = lane & 15, g = lane >> 4;
     const bool has_par = a.parK != nullptr;
-    const unsigned id = xcd_stretches(blockIdx.x, gridDim.x, f.stretch), bh = f.waves(id), v = id - bh * f.waves.d;
+    const unsigned id = blockIdx.x < f.dealt ? xcd_stretches(blockIdx.x, f.dealt, f.stretch) : blockIdx.x;
+    const unsigned part = f.span(id), in = id - part * f.span.d;
+    const bool walk = in < f.walks;
+    const unsigned w = walk ? in : in - f.walks, head = walk ? f.packs(w) : f.others(w), v = w - head * (walk ? f.packs.d : f.others.d);
+    const unsigned bh = part + head;                        // one head to a part, or one part
     const int64_t key0 = (int64_t)bh * f.T;
     const int32_t *C = a.C + (int64_t)bh * (f.T + 1);
 
-    if (v >= f.packs) {                                     // key blocks that nothing lists: the parent's share in every row
-        const unsigned j0 = kEmpty * (v - f.packs);
+    if (!walk) {                                            // key blocks that nothing lists: the parent's share in every row
+        const unsigned j0 = kEmpty * v;
         const int c0 = C[min(j0 + lane, f.T)], c1 = C[min(j0 + lane + 1, f.T)];
         uint64_t m = __ballot(lane < kEmpty && j0 + lane < f.T && c0 == c1);
         constexpr int CH = D / 8, RPI = 64 / CH;            // 16-byte chunks of a row, rows per store
@@ -533,6 +539,12 @@ static int fine_pack(const Plan &p) { return few_tiles(p) ? 2 : fine_tiles(p) <=
 // 8 x 131072 955 and 939 us, Gaussian 995 and 975, 2 x 262144 Gaussian 649 and 639, 4 x 110592 446 and 450, Gaussian 468 and 461; but 4 x 65536
 // (16 MB) 291 and 304.
 static int fine_stretch(const Plan &p) { return p.Kl[0] <= 4 && p.N * p.d * 4 > 16 << 20 ? 6 : -1; }
+// A head's waves for tiles stand before its waves for key blocks that nothing lists, which are much shorter.  Where an XCD's eighth is whole heads
+// that is the same for every XCD; where it is not, some have more of the long ones than others: all heads' waves for tiles come first then and
+// are dealt by themselves.  Steps, K = 8, a head at a time and like this: 4 x 262144 Gaussian 1446 and 1412 us, smooth 1178 and 1162, 6 x 196608
+// Gaussian 1671 and 1619, 6 x 249856 Gaussian 2087 and 2028, 12 x 65536 887 and 882, 3 x 65536 306 and 301.  With whole heads it costs: 32 x 16384
+// 533 and 538, in stretches 8 x 131072, K = 4 909 and 936.
+static bool fine_one_part(const Plan &p) { return p.bh % 8 != 0 && fine_stretch(p) < 0; }
 
 // level0_alone: level 0's own gradient only, without the share of its parent tokens (the pooled levels' gradients)
 hipError_t launch_dkv_mfma(const Plan &p, const LevelTable &t, int l, const void *Q, const void *dO, const float *LSE,
@@ -577,9 +589,12 @@ hipError_t launch_dkv_mfma(const Plan &p, const LevelTable &t, int l, const void
         f.slots = (unsigned)piece_slots(T, E, f.lc);
         f.pack = fine_pack(p);
         f.stretch = fine_stretch(p);
-        f.packs = (f.places + f.pack - 1) / f.pack;
-        f.waves = FastDiv(f.packs + (T + kEmpty - 1) / kEmpty);
-        const unsigned wgs = (unsigned)p.bh * f.waves.d;
+        f.packs = FastDiv((f.places + f.pack - 1) / f.pack);
+        f.others = FastDiv((T + kEmpty - 1) / kEmpty);
+        const unsigned heads = fine_one_part(p) ? (unsigned)p.bh : 1u, wgs = (unsigned)p.bh * (f.packs.d + f.others.d);
+        f.walks = heads * f.packs.d;
+        f.span = FastDiv(heads * (f.packs.d + f.others.d));
+        f.dealt = fine_one_part(p) ? f.walks : wgs;
         if (p.d == 64) dkv_fine_kernel<64><<<wgs, 64, 0, s>>>(a, f);
         else dkv_fine_kernel<128><<<wgs, 64, 0, s>>>(a, f);
         return hipGetLastError();

@@ -292,7 +292,7 @@ def test_level0_lists_of_every_query(heads, N, L, d, Le):
 @pytest.mark.parametrize("heads,N,d,K", [
     # few picks of heads of more than 16 MB of Q and dO: XCDs take 64 waves at a time, the last few hundred waves one each; and just below
     (1, 66560, 64, 3), (3, 66560, 64, 4), (1, 33792, 128, 4), (2, 65536, 64, 4), (1, 66560, 64, 5)])
-def test_level0_waves_dealt_in_stretches(heads, N, d, K):
+def test_level0_waves_dealt_in_stretches(heads, N, d, K, L=2):
     """Every row of dK and dV is written, within the bf16 kernels' rounding of P and dS of the fp32-arithmetic kernels."""
     import torch
     from paper_2512_16615_amd import llsa
@@ -300,13 +300,22 @@ def test_level0_waves_dealt_in_stretches(heads, N, d, K):
     Q, Kt, V, dO = (torch.randn(1, heads, N, d, generator=gen, device="cuda").bfloat16() for _ in range(4))
     got = []
     for path in (0, 1):
-        plan = llsa.Plan(1, heads, N, d, 16, K, 2, kernel_path=path)
+        plan = llsa.Plan(1, heads, N, d, 16, K, L, kernel_path=path)
         O, LSE, idx, ws = llsa.forward(plan, Q, Kt, V, workspace=plan.alloc_workspace(True))
         out = [torch.full_like(Q, float("nan")) for _ in range(3)]
         got.append(llsa.backward(plan, Q, Kt, V, O, LSE, idx, dO, ws, *out))
     for name, a, b in list(zip(("dQ", "dK", "dV"), *got))[1:]:
         rel = float((a.double() - b.double()).norm() / b.double().norm())
         assert rel < 1e-2, (name, rel)
+
+
+@pytest.mark.parametrize("heads,N,d,K", [
+    # no multiple of eight heads: all heads' waves for tiles, then their waves for key blocks that nothing lists (K = 1: a third of them).  Fewer
+    # waves than XCDs, a last wave with a few blocks, as many waves of one kind as of the other, lists of 12; and eight heads, one after the other
+    (1, 64, 64, 1), (3, 320, 64, 1), (7, 1088, 64, 1), (9, 1088, 128, 1), (12, 8256, 64, 1), (5, 16640, 128, 8), (2, 33024, 64, 12), (8, 1088, 64, 1)])
+def test_level0_waves_of_several_heads(heads, N, d, K):
+    """Every row of dK and dV is written, within the bf16 kernels' rounding of P and dS of the fp32-arithmetic kernels."""
+    test_level0_waves_dealt_in_stretches(heads, N, d, K, L=1 if N % 256 else 2)
 
 
 @pytest.mark.parametrize("heads,N,L,d", [
