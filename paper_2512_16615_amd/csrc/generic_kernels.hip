@@ -413,7 +413,9 @@ __global__ void __launch_bounds__(256) csc_bitmap_kernel(CscSmall a) {
 //     and the group's sum per key;
 //   scan: per head, the sums over the groups and then over the keys: C, and where each group's entries of a key start;
 //   fill: per (segment, 1024 keys) a bitmap of 128 rows per key in LDS; an entry's place is the start of its group, plus the
-//     counts of the group's earlier segments (one 16-byte load, summed bytewise), plus the marked rows below its own.
+//     counts of the group's earlier segments (one 16-byte load, summed bytewise), plus the marked rows below its own.  Level 0's tiles
+//     too: in a launch of their own they were 5 to 29 us more on the stream that the level-1 gather waits for (steps, K = 4, Gaussian,
+//     8 x 131072 tokens 964 -> 947 us, 4 x 212992 842 -> 836; smooth 8 x 131072 900 -> 888, 4 x 65536, K = 8 353 -> 349).
 // Nothing is sorted and every place follows from counts, so the lists are ascending and the same on every run.  The kernels
 // stay below 48 registers: that is what the upper-level dK/dV kernel, in whose shadow they run, leaves of a SIMD's 512.
 // Each range of 1024 keys reads its rows again, so the time grows with rows^2 for few heads; the sort's grows with the lists,
@@ -421,6 +423,18 @@ __global__ void __launch_bounds__(256) csc_bitmap_kernel(CscSmall a) {
 // 17408 rows 114 : 89 and 50 : 90 us, two of 32768 rows 224 : 247 and 90 : 250, one of 65536 rows 336 : 834 and 127 : 841.
 // grid.x: ranges of level 0's heads, then level 1's, ...
 struct CscRanges { CscLevel lv[kMaxL]; unsigned wg_end[kMaxL]; };
+// Level 0's lists as tiles (fine_tiles.h) from C, by 16 lanes for key block j of head bh.
+struct TileRows { FineTile *tiles; int32_t *arrived; int lc; };   // tiles: null if nothing takes them
+__device__ __forceinline__ void tiles_of(const TileRows &r, const int32_t *C, int64_t bh, int64_t T, int64_t E, int j, int lane) {
+    const int start = C[j], end = C[j + 1];
+    const int64_t places = tile_places(T, E);
+    write_tiles(r.tiles + bh * places, r.arrived + bh * piece_slots(T, E, r.lc), r.lc, j, start, end - start,
+                j + 1 == T ? (int)places : tile_place(end, j + 1), lane, 16);
+}
+static TileRows tile_rows(const Plan &p, char *w) {
+    if (!dkv_by_tiles(p)) return {nullptr, nullptr, 0};
+    return {(FineTile *)(w + p.tiles_off), (int32_t *)(w + p.arrived_off), fine_piece_log2(p)};
+}
 constexpr int kSegRowsMax = 16384, kSegR = 128, kSegPerGroup = 16, kGroupRows = kSegR * kSegPerGroup, kKeyRange = 1024;
 // every entry of rows row0 .. row1 - 1 with key - k0 < kKeyRange: f(row, key - k0)
 template <class F> __device__ __forceinline__ void range_entries(const int32_t *I, unsigned Kl, unsigned row0, unsigned row1, unsigned k0, F f) {
@@ -505,7 +519,7 @@ __global__ void __launch_bounds__(256) csc_seg_scan_kernel(CscLevels a) {
     }
     if (threadIdx.x == 0) Co[T] = carry;
 }
-__global__ void __launch_bounds__(256) csc_seg_fill_kernel(CscRanges a) {
+__global__ void __launch_bounds__(256) csc_seg_fill_kernel(CscRanges a, TileRows out) {
     __shared__ __attribute__((aligned(16))) uint32_t bm[kKeyRange * 4];
     int l = 0;
     while (blockIdx.x >= a.wg_end[l]) ++l;
@@ -538,6 +552,11 @@ __global__ void __launch_bounds__(256) csc_seg_fill_kernel(CscRanges a) {
         }
         Iq[at] = (int32_t)row;
     });
+    if (l == 0 && out.tiles) {                              // the range's keys are shared out among the segments' workgroups
+        const unsigned share = (kKeyRange + segs - 1) / segs, end = min(T, k0 + min((seg + 1) * share, (unsigned)kKeyRange));
+        for (unsigned j = k0 + seg * share + (threadIdx.x >> 4); j < end; j += 16)
+            tiles_of(out, L.C + (int64_t)bh * (T + 1), bh, T, L.eph, (int)j, (int)(threadIdx.x & 15));
+    }
 }
 
 // Larger levels still: count -> exclusive scan -> fill -> per-key ascending order.  Counting and filling use integer atomics; the
@@ -724,28 +743,20 @@ size_t csc_scratch_bytes(const Plan &p, int l) {
     return (size_t)p.bh * T * p.Kl[l] * sizeof(int32_t);
 }
 
-// Alg. 2 for levels 0 .. top (the levels whose lists the backward uses)
-// level 0's lists as tiles, 16 lanes per key
-__global__ void __launch_bounds__(256) fine_tiles_kernel(const int32_t *C, FineTile *tiles, int32_t *arrived, int T, int E, int lc) {
-    const unsigned per_head = ((unsigned)T + 15u) / 16u, bh_ = blockIdx.x / per_head;
-    const int64_t bh = bh_;
-    const int j = (int)((blockIdx.x - bh_ * per_head) * 16 + (threadIdx.x >> 4));
-    if (j >= T) return;
-    const int32_t *c = C + bh * (T + 1);
-    const int start = c[j], end = c[j + 1];
-    const int64_t places = tile_places(T, E);
-    write_tiles(tiles + bh * places, arrived + bh * piece_slots(T, E, lc), lc, j, start, end - start, j + 1 == T ? (int)places : tile_place(end, j + 1),
-                (int)(threadIdx.x & 15), 16);
+// level 0's lists as tiles in a launch of their own, 16 lanes per key
+__global__ void __launch_bounds__(256) fine_tiles_kernel(const int32_t *C, TileRows r, int T, int E) {
+    const unsigned per_head = ((unsigned)T + 15u) / 16u, bh = blockIdx.x / per_head;
+    const int j = (int)((blockIdx.x - bh * per_head) * 16 + (threadIdx.x >> 4));
+    if (j < T) tiles_of(r, C + (int64_t)bh * (T + 1), bh, T, E, j, (int)(threadIdx.x & 15));
 }
-hipError_t launch_fine_tiles(const Plan &p, void *ws, hipStream_t s) {
+static hipError_t launch_fine_tiles(const Plan &p, char *w, hipStream_t s) {
     if (!dkv_by_tiles(p)) return hipGetLastError();
-    char *w = static_cast<char *>(ws);
-    fine_tiles_kernel<<<(unsigned)((p.n[1] + 15) / 16 * p.bh), 256, 0, s>>>((const int32_t *)(w + p.C_off[0]), (FineTile *)(w + p.tiles_off),
-                                                                           (int32_t *)(w + p.arrived_off), (int)p.n[1], (int)(p.n[1] * p.Kl[0]),
-                                                                           fine_piece_log2(p));
+    fine_tiles_kernel<<<(unsigned)((p.n[1] + 15) / 16 * p.bh), 256, 0, s>>>((const int32_t *)(w + p.C_off[0]), tile_rows(p, w), (int)p.n[1],
+                                                                           (int)(p.n[1] * p.Kl[0]));
     return hipGetLastError();
 }
 
+// Alg. 2 for levels 0 .. top (the levels whose lists the backward uses)
 hipError_t launch_csc(const Plan &p, int top, const int32_t *indices, void *ws, hipStream_t s) {
     CscSmall few;
     if (csc_small_args(p, top, indices, ws, &few)) {
@@ -791,8 +802,8 @@ hipError_t launch_csc(const Plan &p, int top, const int32_t *indices, void *ws, 
         csc_seg_count_kernel<<<wgs, 256, 0, s>>>(r);
         csc_seg_scan_kernel<<<dim3(p.bh, top + 1), 256, 0, s>>>(a);
         wgs = ranges([&](int64_t T) { return kr(T) * ((T + kSegR - 1) / kSegR); });
-        csc_seg_fill_kernel<<<wgs, 256, 0, s>>>(r);
-        return launch_fine_tiles(p, ws, s);
+        csc_seg_fill_kernel<<<wgs, 256, 0, s>>>(r, tile_rows(p, w));
+        return hipGetLastError();
     }
     const unsigned nl = (unsigned)(top + 1);
     csc_zero_kernel<<<dim3((unsigned)((max_nk + 255) / 256), nl), 256, 0, s>>>(a);
@@ -801,7 +812,7 @@ hipError_t launch_csc(const Plan &p, int top, const int32_t *indices, void *ws, 
     csc_fill_kernel<<<dim3((unsigned)((max_total + 255) / 256), nl), 256, 0, s>>>(a);
     csc_sort_kernel<<<dim3((unsigned)((max_total + 255) / 256), nl), 256, 0, s>>>(a);
     csc_sort_long_kernel<<<dim3((unsigned)((max_nk + 255) / 256), nl), 256, 0, s>>>(a);
-    return launch_fine_tiles(p, ws, s);
+    return launch_fine_tiles(p, w, s);
 }
 
 // ------------------------------------------------------- key-major lists through a dense block mask (comparator)
@@ -889,7 +900,7 @@ hipError_t launch_mask_lists(const Plan &p, const int32_t *indices, void *ws, vo
     mask_mark_kernel<<<dim3((unsigned)((total + 255) / 256)), 256, 0, s>>>(L.I, static_cast<uint8_t *>(mask), L.cnt, T, L.Kl, total);
     csc_scan_kernel<<<dim3(p.bh, 1), kScanThreads, 0, s>>>(a);
     mask_scan_kernel<<<dim3((unsigned)((nk + 3) / 4)), 256, 0, s>>>(static_cast<const uint8_t *>(mask), L.C, L.Iq, T, eph, nk);
-    return launch_fine_tiles(p, ws, s);
+    return launch_fine_tiles(p, w, s);
 }
 
 // ---------------------------------------------------------------------------- index reordering (Sec. 5.1)

@@ -160,7 +160,6 @@ hipError_t launch_dkv_mfma(const Plan &p, const LevelTable &t, int l, const void
                            const float *D, void *ws, void *dK, void *dV, hipStream_t s, bool level0_alone = false);
 bool dkv_by_tiles(const Plan &p);         // does level 0 take its lists as tiles (fine_tiles.h)?
 int fine_piece_log2(const Plan &p);       // in pieces of how many tiles
-hipError_t launch_fine_tiles(const Plan &p, void *ws, hipStream_t s);   // they are made from C
 int dkv_splits(const Plan &p, int l);    // workgroups sharing one key block's query list at level l
 int dkv_block_tiles(const Plan &p, int l), dkv_block_splits(const Plan &p, int l);   // the same for dkv_block.hip's levels
 // all coarse levels (dkv_group_top .. 1) at once, grouped by level-1 query block; fills the levels' fp32

@@ -318,6 +318,15 @@ def test_level0_waves_of_several_heads(heads, N, d, K):
     test_level0_waves_dealt_in_stretches(heads, N, d, K, L=1 if N % 256 else 2)
 
 
+@pytest.mark.parametrize("heads,N,d,K,L", [
+    # the tiles of level 0's lists, written along with the lists from 513 to 16384 rows (516: 5 segments share 1024 keys; one range of keys and
+    # the first keys of the next; two groups of segments; all 128 segments) and by a launch of their own beyond
+    (3, 8256, 64, 1, 1), (1, 16384, 64, 8, 2), (2, 16640, 128, 3, 2), (1, 33024, 64, 8, 2), (1, 262144, 64, 2, 3), (1, 262400, 64, 2, 2)])
+def test_level0_tiles_by_number_of_rows(heads, N, d, K, L):
+    """Every row of dK and dV is written, within the bf16 kernels' rounding of P and dS of the fp32-arithmetic kernels."""
+    test_level0_waves_dealt_in_stretches(heads, N, d, K, L)
+
+
 @pytest.mark.parametrize("heads,N,L,d", [
     # partials of levels >= 1 added eight at a time: lists of 1, 7, 8, 9 and 17 query blocks beside empty ones, of more than the threads of a
     # workgroup (272 of 256; 528 of 512 at d = 128), of an upper level; one launch of more than 1024 workgroups, which add them one by one
