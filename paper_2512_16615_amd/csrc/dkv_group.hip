@@ -586,26 +586,33 @@ __global__ void __launch_bounds__(NT) dkv_gather_kernel(GatherArgs a) {
     }
 }
 
+// Level-1 query blocks one workgroup of the upper kernels walks: as many as leave one workgroup per CU (d = 128: for each share of the listed
+// blocks; steps of 8 x 65536 tokens, K = 8 and 4, with twice as many workgroups 1172 and 897 us, like this 1142 and 874, with half as many 1180 and 905).
+static int query_group(const Plan &p) {
+    const int64_t NR = p.N / 256;
+    int G = 16;                                             // divides 16, so a group never straddles a level-2 query block
+    while (G > 1 && (NR % G != 0 || (int64_t)p.bh * (NR / G) < 256)) G >>= 1;
+    return G;
+}
+
 // Highest level the grouped kernels take; levels above it go to the split key-major kernel: a wide dense coarsest
 // level (every query block would write a partial sum for every one of its key blocks, and summing over all queries
-// is what the split kernel does in registers), and at d = 128, where no registers are left for a shared block, a dense level
-// that does not fit into waves which the upper kernel's last pass has to spare.  Where it fits it costs that pass nothing, and the
-// split kernel reads all of Q and dO for it: 8 x 262144 tokens, K = 16 (20 listed blocks and one of 4 dense tokens, three
-// passes of 8 either way) 7064 -> 6950 us a step.
+// is what the split kernel does in registers), and at d = 128 a dense level of a problem whose query groups are shorter than four query
+// blocks.  There a wave owns a dense block as it does a listed one, often in a share of four waves more, which reads the group's rows
+// once more; the split kernel reads all of Q and dO too, in two launches, and leaves no partials of every group to be added.  us a step, in
+// the split kernel and in the upper one: groups of one query block, 1 x 65536 tokens, K = 8 300 and 315, 2 x 16384, K = 12 202 and 220; of
+// two, 1 x 131072 418 and 422 to 428, 2 x 65536 393 and 398, 8 x 16384 351 and 351; of four, 2 x 131072, L = 4 582 and 553, 16 x 16384, K = 4
+// 476 and 458; of more, 8 x 65536, K = 8 1157 and 1104, K = 4 934 and 872, 8 x 262144, K = 16 6900 and 6680, with 8 dense blocks (2 x 524288,
+// K = 4) 1982 and 1900, with 16 (1 x 1048576) 2236 and 2095.
 int dkv_group_top(const Plan &p) {
     if (p.Le < p.L) return p.Le;
-    const int64_t dense = (p.n[p.L] + 15) / 16;
-    if (dense > 32) return p.L - 1;
-    if (p.d == 128) {
-        int listed = 0;
-        for (int l = 2; l < p.L; ++l) listed += p.Kl[l];
-        if (listed % 8 == 0 || listed % 8 + dense > 8) return p.L - 1;
-    }
+    if ((p.n[p.L] + 15) / 16 > 32) return p.L - 1;
+    if (p.d == 128 && (p.L <= 2 || query_group(p) < 4)) return p.L - 1;   // (L <= 2: no listed blocks to go along with)
     return p.Le;
 }
 
-// Blocks of levels 2 .. top: owned by waves (nbs: the sparse levels' listed ones and a dense level's, if it has several blocks or
-// a wave has nothing else to do meanwhile) and shared by them (nbd: the block of a dense level, when the others fill all waves).
+// Blocks of levels 2 .. top: owned by waves (nbs: the sparse levels' listed ones and a dense level's, if it has several blocks, a
+// wave has nothing else to do meanwhile or, d = 128, no wave has registers for a shared one) and shared by them (nbd: the block of a dense level, when the others fill all waves).
 static void upper_blocks(const Plan &p, int *nbs, int *nbd) {
     const int top = dkv_group_top(p);
     *nbs = *nbd = 0;
@@ -613,18 +620,14 @@ static void upper_blocks(const Plan &p, int *nbs, int *nbd) {
         if (l < p.L) *nbs += p.Kl[l];
         else *nbd = (int)((p.n[l] + 15) / 16);
     }
-    if (*nbd > 1 || *nbs % 8 != 0) { *nbs += *nbd; *nbd = 0; }
+    if (*nbd > 1 || *nbs % 8 != 0 || p.d == 128) { *nbs += *nbd; *nbd = 0; }
 }
 
 // Level-1 query blocks per workgroup of the upper kernel, or 0 if the group has no level >= 2.
 static int upper_G(const Plan &p) {
     int nbs, nbd;
     upper_blocks(p, &nbs, &nbd);
-    if (dkv_group_top(p) < 2 || nbs + nbd == 0) return 0;
-    const int64_t NR = p.N / 256;
-    int G = 16;                                             // divides 16, so a group never straddles a level-2 query block
-    while (G > 1 && (NR % G != 0 || (int64_t)p.bh * (NR / G) < 256)) G >>= 1;  // one workgroup of 8 waves per CU
-    return G;
+    return dkv_group_top(p) < 2 || nbs + nbd == 0 ? 0 : query_group(p);
 }
 
 // Level-1 query blocks one workgroup of the chain kernel walks (1: the plain group kernel takes level 1), and how far apart they are.

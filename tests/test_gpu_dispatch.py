@@ -392,12 +392,17 @@ def test_lists_made_along_with_dq(cfg):
     _bf16("dense_13_K3", 13 * 4096, L=3, heads=1, K=3),
     _bf16("dense_12_K12", 12 * 4096, L=3, heads=1, K=12),
     _bf16("dense_8_K8", 8 * 4096, L=3, heads=1),
-    # d = 128: the dense level in waves that the last pass has to spare (7 of 8 taken, a ragged tile; two blocks behind 4 listed ones; the
-    # second pass), in the split kernel where it has none (8 listed)
+    # d = 128, query groups of one or two query blocks: the dense level in the split kernel
     _bf16("dense_7_K7_d128", 7 * 4096, L=3, heads=1, K=7, d=128),
     _bf16("dense_17_K4_d128", 17 * 4096, L=3, heads=1, K=4, d=128),
     _bf16("dense_12_K12_d128", 12 * 4096, L=3, heads=1, K=12, d=128),
     _bf16("dense_8_K8_d128", 8 * 4096, L=3, heads=1, d=128),
+    _bf16("dense_2_heads16_d128", 2 * 4096, L=3, heads=16, d=128),
+    # d = 128, of four: owned by waves in a share that has one to spare (a ragged tile; two blocks behind 4 listed ones: a share of their own), in
+    # a share of its own behind 8
+    _bf16("dense_7_K7_heads10_d128", 7 * 4096, L=3, heads=10, K=7, d=128),
+    _bf16("dense_17_K4_heads4_d128", 17 * 4096, L=3, heads=4, K=4, d=128),
+    _bf16("dense_8_K8_heads8_d128", 8 * 4096, L=3, heads=8, d=128),
 ], ids=lambda c: c["name"])
 def test_grouped_upper_levels(cfg):
     _full_parity(cfg, 0xD15E)
