@@ -528,17 +528,22 @@ int dkv_splits(const Plan &p, int l) {
 
 bool dkv_by_tiles(const Plan &p) { return p.fast && p.B == 16; }
 
-// Tiles of a piece and places of a wave.  A cut list's sums go to memory and back, 16 KB a piece (d = 128: 32), so pieces are as long as the
-// launch's end allows: its last waves run alone while they finish one.  us at pieces of 16 / 32 / 64 tiles: 16 x 65536 tokens 266 / 254 /
-// 263, 32 x 16384 133 / 138 / 141, 8 x 262144 with d = 128, K = 16 2163 / 1604 / 1582.  Where the waves that the chip holds (3072, at d = 128 2048) have
-// eight tiles each or fewer, a wave with little to do is worth more: pieces of 8, 2 places (steps, 1 x 16384 tokens 171.7 -> 162.7 us,
-// 16 x 1472 58.3 -> 55.4; 4 x 4096 at d = 128 107.9).
+// Tiles of a piece and places of a wave, by the tiles for each wave that the chip holds.  A cut list's sums go to memory and back, 16 KB a piece
+// (d = 128: 32), so pieces are as long as the launch's end allows: its last waves run alone while they finish one.  us at pieces of 16 / 32 / 64
+// tiles: 16 x 65536 tokens 266 / 254 / 263, 32 x 16384 133 / 138 / 141; steps at d = 128, 2 x 65536, K = 8 363 / 374 / 399 (18 tiles a wave), 4 x 65536
+// 596 / 609 / 629 (36), 8 x 65536 1088 / 1074 / 1089 (72), 8 x 65536, K = 16 1665 / 1642 / 1667 (136), 8 x 131072, K = 16 3657 / 3586 / 3571 (272),
+// 8 x 262144, K = 16 6984 / 6883 / 6876 (544).  With eight tiles each or fewer, a wave with little to do is worth more: pieces of 8, 2 places (steps,
+// 1 x 16384 tokens 171.7 -> 162.7 us, 16 x 1472 58.3 -> 55.4).
 static int64_t fine_tiles(const Plan &p) { return p.bh * tile_places(p.n[1], p.n[1] * p.Kl[0]); }
-static bool few_tiles(const Plan &p) { return fine_tiles(p) <= 8 * (p.d == 128 ? 2048 : 3072); }
-int fine_piece_log2(const Plan &p) { return few_tiles(p) ? 3 : p.d == 128 ? 6 : fine_tiles(p) > 64 * 3072 ? 5 : 4; }
-// Places of a wave: more than four only where the waves have enough to do for their end not to matter (steps with 4 and 8: 4 x 110592 tokens,
-// K = 4, Gaussian 460 and 474 us, smooth 439 and 447, 4 x 65536, K = 8 417 and 425; 16 x 65536 1082 and 1070).
-static int fine_pack(const Plan &p) { return few_tiles(p) ? 2 : fine_tiles(p) <= 64 * 3072 ? 4 : 8; }
+static int64_t fine_share(const Plan &p) { return (fine_tiles(p) - 1) / (p.d == 128 ? 2048 : 3072) + 1; }   // two and three waves a SIMD
+int fine_piece_log2(const Plan &p) {
+    const int64_t share = fine_share(p);
+    return share <= 8 ? 3 : share <= 64 ? 4 : p.d == 64 || share <= 256 ? 5 : 6;
+}
+// More than four places only where the waves have enough to do for their end not to matter (steps with 4 and 8: 4 x 110592 tokens, K = 4, Gaussian
+// 460 and 474 us, smooth 439 and 447, 4 x 65536, K = 8 417 and 425; 16 x 65536 1082 and 1070; d = 128, 4 x 131072, K = 8 Gaussian 1353 and
+// 1368, 8 x 65536 1104 and 1098, both 147456 places).
+static int fine_pack(const Plan &p) { return fine_share(p) <= 8 ? 2 : fine_tiles(p) <= 64 * 3072 ? 4 : 8; }
 // Whole stretches of heads keep rows that neighbouring blocks share in an XCD's L2 (dealt in stretches of 32 to 512 waves 16 x 65536 tokens, K = 8,
 // 1 to 7 % slower, 8 x 262144 at d = 128, K = 16 6 to 12).  With lists of few blocks there is less to share, and where a head's Q and dO are
 // more than 16 MB, eight XCDs in as many places are more than the cache behind L2 holds.  Steps, whole and in stretches of 64 waves, K = 4:

@@ -263,10 +263,11 @@ def test_index_transpose_by_size(T, K, heads):
 
 @pytest.mark.parametrize("heads,N,L,d,Le", [
     # every query lists the first K blocks: lists of all T = N / 16 query blocks beside T - K empty ones.  Pieces of 8 tiles: 4 tiles, 10 and
-    # 12 (the first that are cut), 32 and 34 (one window of places and its end), no parent; of 16, twice; of 64 (d = 128); and, in waves of eight
-    # places, of 32 and of 64 (more than 196608 places in all: 229376)
+    # 12 (the first that are cut), 32 and 34 (one window of places and its end), no parent; of 16 at either width; and, in waves of eight places,
+    # of 32 at either width (229376 places in all) and of 64 (d = 128, 573440)
     (1, 64, 1, 64, 1), (2, 320, 1, 64, 1), (3, 384, 1, 64, 0), (1, 1024, 1, 64, 1), (2, 1088, 1, 64, 1), (1, 1088, 1, 128, 1),
-    (16, 16384, 2, 64, 2), (8, 65536, 3, 64, 3), (8, 16384, 2, 128, 2), (16, 65536, 3, 64, 3), (8, 131072, 3, 128, 3)])
+    (16, 16384, 2, 64, 2), (8, 65536, 3, 64, 3), (8, 16384, 2, 128, 2), (16, 65536, 3, 64, 3), (8, 131072, 3, 128, 3),
+    (10, 262144, 3, 128, 3)])
 def test_level0_lists_of_every_query(heads, N, L, d, Le):
     """dK and dV where lists are cut into pieces that several waves add up: within the bf16 kernels' rounding of the fp32-arithmetic kernels,
     and the same bits every time, whichever wave comes last."""
