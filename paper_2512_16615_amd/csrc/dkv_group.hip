@@ -14,7 +14,7 @@
 //   dkv_upper_kernel: levels >= 2 only.  The 16 level-1 blocks under one level-2 query block list the same
 //     key blocks at every level >= 2, so a workgroup of 8 waves walks G of them (G divides 16; the next one's
 //     rows are prefetched into registers; d = 128: dkv_upper_ring_kernel) and keeps its accumulators in registers meanwhile: every wave owns
-//     one or two of the listed blocks, and (d = 64) the single block of a coarsest level of at most 16 tokens is shared:
+//     one or two of the listed blocks (d = 128: one), and (d = 64) the single block of a coarsest level of at most 16 tokens is shared:
 //     wave w takes query tile w of every R and the 8 waves' sums are added through LDS at the end.  G times fewer partials,
 //     and no idle rounds when the number of key blocks is not a multiple of the waves.  The blocks of a larger dense level
 //     are owned by waves like listed ones (N = 65536 with 256 coarsest tokens: without this, every level-1 query block
@@ -223,7 +223,7 @@ template <int D> __device__ __forceinline__ void keys_come(BlockAcc<D> &b) {
     for (int ks = 0; ks < D / 32; ++ks) asm volatile("" : "+v"(b.kop[ks]), "+v"(b.vop[ks]));
 }
 
-constexpr int kChain = 8;                                              // query blocks of a chain at most
+constexpr int kChain = 8, kChainRow = 16;                              // query blocks of a chain, listed blocks of a row at most
 
 // Level 1 alone, rows of I^(1) with at most NW * NB * P entries.  Neighbouring level-1 query blocks list mostly the same
 // level-1 key blocks (for spatially smooth inputs a block stays listed over many consecutive rows), and a partial per
@@ -265,9 +265,9 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW
     const int64_t far = (int64_t)a.GS * Kl;                           // from a row of the chain to the next
 
     // the chain's rows of I^(1): entry e = row * Kl + place in lane e % 64 of word e / 64
-    int rows[kChain * 16 / 64];
+    int rows[kChain * kChainRow / 64];
 #pragma unroll
-    for (int x = 0; x < kChain * 16 / 64; ++x) {
+    for (int x = 0; x < kChain * kChainRow / 64; ++x) {
         const int e = 64 * x + lane;
         rows[x] = e < a.GC * Kl ? I1[e / Kl * far + e % Kl] : -1;
     }
@@ -275,7 +275,7 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW
         const int e = r * Kl + min(lane, Kl - 1);
         int v = __shfl(rows[0], e & 63, 64);
 #pragma unroll
-        for (int x = 1; x < kChain * 16 / 64; ++x) {
+        for (int x = 1; x < kChain * kChainRow / 64; ++x) {
             const int y = __shfl(rows[x], e & 63, 64);
             v = e >> 6 == x ? y : v;
         }
@@ -350,7 +350,7 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW
 
 // d = 128, where a workgroup of eight waves that holds all 256 rows of Q and dO has a CU to itself, two waves a SIMD: workgroups of four, three on
 // a CU, with the tiles in a ring of two places.  A wave owns a listed block.  Bound: LDS reads and issue.  us, before -> now: 8 heads x 262144
-// tokens, K = 16 (36 blocks) 1066 -> 876 (with four places, two workgroups a CU, 1055), 8 x 65536, K = 8 104 -> 98; steps 6997 -> 6698 and
+// tokens, K = 16 (20 listed blocks and a dense one) 1066 -> 876 (with four places, two workgroups a CU, 1055), 8 x 65536, K = 8 104 -> 98; steps 6997 -> 6698 and
 // 1184 -> 1168 with the chain kernel's ring, 2 x 131072, K = 4 574 -> 526, Gaussian 568 -> 520.
 template <int D, int NW>
 __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(3))) dkv_upper_ring_kernel(LevelTable t, GroupArgs a) {
@@ -396,13 +396,14 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(3)
     if (have) store_partial(partial_ptr<D>(t, a, nlev, u_begin + jb, grp), blk[0], a.scale, lane);
 }
 
-// SS = listed blocks a wave owns (block wave of the workgroup's share, + 8, ...): a workgroup takes 8 SS of them, and where a
+// d = 64.  SS = listed blocks a wave owns (block wave of the workgroup's share, + 8, ...): a workgroup takes 8 SS of them, and where a
 // query group has more, a.passes workgroups take a share each.  All of them read the group's rows: they run at about the same
-// time, eight ids apart and so on one XCD, for the rows to come from memory once.  As launches of their own the three passes of
-// 8 x 262144 tokens, d = 128, K = 16 took 430 + 440 + 290 us and read 1.07 GB each; in one, the coarse levels' dK / dV take 2098 us
-// instead of 2185.  DENSE: may this instantiation take the shared dense block (the first pass does).
-template <int D, int SS, bool DENSE>
+// time, eight ids apart and so on one XCD, for the rows to come from memory once (as launches of their own, three passes at 8 x 262144
+// tokens, d = 128, which this kernel served then, read 1.07 GB each, and the coarse levels' dK / dV took 2185 us instead of 2098).
+// DENSE: may this instantiation take the shared dense block (the first pass does).
+template <int SS, bool DENSE>
 __global__ void __launch_bounds__(512) dkv_upper_kernel(LevelTable t, GroupArgs a) {
+    constexpr int D = 64;
     using S = GShape<D>;
     __shared__ __attribute__((aligned(16))) char lds[2 * 256 * S::ROWB];   // Q rows | dO rows; the final reduction reuses it
     __shared__ __attribute__((aligned(16))) float st[512];
@@ -648,10 +649,10 @@ static int upper_G(const Plan &p) {
 // 4 in 1024: 275 us, 2: 297 us, 16 in 256 workgroups: 286 us, one query block per workgroup (no carrying): 357 us.
 static void chain_shape(const Plan &p, int *GC, int *GS) {
     *GC = *GS = 1;
-    if (p.L < 2 || p.Kl[1] > 16) return;
+    if (p.L < 2 || p.Kl[1] > kChainRow) return;
     if (upper_G(p) == 0 && dkv_group_top(p) > 1) return;
     const int64_t NR = p.N / 256;
-    int gc = 8, gs = 1;
+    int gc = kChain, gs = 1;
     while (gc > 1 && (NR % gc != 0 || (int64_t)p.bh * (NR / gc) < 512)) gc >>= 1;   // at least two workgroups per CU
     while ((int64_t)(2 * gs) * (2 * gs) * 65536 <= p.N && NR % (2 * gs * gc) == 0) gs *= 2;
     *GC = gc;
@@ -817,9 +818,9 @@ hipError_t launch_dkv_group(const Plan &p, const LevelTable &t, const void *Q, c
         up.passes = max(1, (up.nbs + share - 1) / share);
         const dim3 grid((unsigned)(p.bh * (NR / G) * up.passes));
         if (p.d == 128) dkv_upper_ring_kernel<128, 4><<<grid, 256, 0, s>>>(t, up);
-        else if (share == 8) dkv_upper_kernel<64, 1, true><<<grid, 512, 0, s>>>(t, up);
-        else if (up.nbd == 0) dkv_upper_kernel<64, 2, false><<<grid, 512, 0, s>>>(t, up);
-        else dkv_upper_kernel<64, 2, true><<<grid, 512, 0, s>>>(t, up);
+        else if (share == 8) dkv_upper_kernel<1, true><<<grid, 512, 0, s>>>(t, up);
+        else if (up.nbd == 0) dkv_upper_kernel<2, false><<<grid, 512, 0, s>>>(t, up);
+        else dkv_upper_kernel<2, true><<<grid, 512, 0, s>>>(t, up);
         GRP_TRY(hipGetLastError());
     }
     // With a side stream (the one the lists are made on), the small reductions and gathers of levels >= 2 follow the

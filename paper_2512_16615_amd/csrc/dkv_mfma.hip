@@ -32,8 +32,8 @@ template <int D> struct DkvShape {
 // Tiles t_first, t_first + t_step, ... < t_end of one key block's query list, accumulated into accK / accV.
 // lst: the block's listed query-block rows (null when dense); groups: 16-query groups in the list.
 // Rows go from memory straight into the wave's LDS.  Every operand of a tile is read before its exponentials, so that the next
-// tile's rows, for which there is only this one place, fly during the rest: through registers 317 us at 16 x 65536 tokens, K = 8,
-// this way 309 (a second place in LDS was worth a wave less per SIMD); 8 x 262144, d = 128, K = 16: 1780 -> 1660.
+// tile's rows, for which there is only this one place, fly during the rest.  Measured when level 0 walked its lists in this loop too: through
+// registers 317 us at 16 x 65536 tokens, K = 8, this way 309 (a second place in LDS was worth a wave less per SIMD).
 template <int D>
 __device__ __forceinline__ void dkv_tile_loop(const DkvArgs &a, int64_t bh, const int32_t *lst, int64_t groups,
                                               int64_t t_first, int64_t t_step, int64_t t_end,

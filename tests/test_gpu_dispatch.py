@@ -503,8 +503,8 @@ def test_level1_sums_carried_along_query_blocks(cfg):
 
 
 @pytest.mark.parametrize("cfg", [
-    # d = 128, workgroups of four waves: level 1 of one, three and four listed blocks; levels >= 2 of 1 + 1, 5 + 1 and 9 + 1 (one share, a ragged
-    # one, three)
+    # d = 128, workgroups of four waves: level 1 of one, three and four listed blocks; levels >= 2 of 1, 5 and 9 listed blocks (one share, two and
+    # three, the last with one block)
     _bf16("chain_K1", 8192, L=2, heads=32, K=1, d=128),
     _bf16("chain_K3", 8192, L=2, heads=32, K=3, d=128),
     _bf16("chain_K4", 8192, L=2, heads=32, K=4, d=128),
@@ -602,8 +602,9 @@ def test_level1_sums_carried_to_the_query_block_below(K, d, side):
 
 @pytest.mark.parametrize("N,d,K,L", [(260 * 256, 64, 4, 2), (262144, 64, 20, 4), (262144, 128, 20, 4), (36864, 64, 12, 3), (139264, 64, 16, 3)])
 def test_listed_blocks_of_the_upper_levels_shared_by_workgroups(N, d, K, L):
-    """Listed blocks of levels >= 2 of a query group: 17 (three workgroups of eight, the last with a ragged block of four tokens), 24 and a
-    dense block that all waves share (three of eight, the first takes it), 24 at d = 128, 13 (one of 16), 18 (three of eight)."""
+    """Blocks of levels >= 2 of a query group: 17 (three workgroups of eight, the last with a ragged block of four tokens), 24 and a
+    dense block that all waves share (three of eight, the first takes it), 24 and a dense one at d = 128 (seven of four), 13 (one of 16),
+    18 (three of eight)."""
     _check_key_gradients(N, d, K, L, heads=2, side=256)
 
 

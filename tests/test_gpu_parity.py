@@ -87,7 +87,7 @@ def test_config1_n4096_bf16_all_heads():
     # left to the split kernel; then the same geometry with the list stopping at level 2
     dict(name="three_supergroups_d128", batch=1, heads=2, d=128, N=12288, B=16, K=3, L=3, dtype="bf16", kind="gaussian"),
     dict(name="Le2_d128", batch=1, heads=1, d=128, N=12288, B=16, K=3, L=3, Le=2, dtype="bf16", kind="gaussian"),
-    # d = 128, 11 listed blocks at level 2: two workgroups of the upper-level kernel share them, the second with 3 of 8 waves busy
+    # d = 128, 11 listed blocks at level 2: three workgroups of the upper-level kernel share them, the last with 3 of 4 waves busy
     dict(name="K11_d128", batch=1, heads=1, d=128, N=65536, B=16, K=11, L=3, dtype="bf16", kind="gaussian"),
     # single-level method with a coarsest level of 260 tokens: the selection takes its candidates 256 at a time (second
     # chunk: 4 candidates; last query block: 4 rows); then two full chunks at d = 128 and a top level of 272 under L = 2
