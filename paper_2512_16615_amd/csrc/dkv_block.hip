@@ -11,8 +11,10 @@
 // stores took as long as a third of the reads.  us (profiled, before -> now): 16 heads x 65536 tokens in blocks of 64, K = 8, level 1
 // 392 -> 325, level 0 459 -> 412; in blocks of 32 306 -> 260 and 450 -> 357; 8 heads, d = 128, blocks of 64, K = 4 280 -> 192 and 421 -> 315.
 // (With the place worked out at run time, which is an addition for every LDS read, 412 and 436.)
-// Bound: LDS reads (16 KB per 32 x 16 score tile at TPW = 1, half of that at 2) and the latency of the gathered rows (224 us each at the
-// rate of a large matrix product for the first two).  TPW = 1 at level 1 and 2 at level 0 each take about 1.1 times as long.
+// Bound, by counters at 16 x 65536 in blocks of 64 (share of a SIMD's cycles; 25 % would be all of the LDS that four share): level 1 issue, vector
+// ALU 45 % and MFMA 43 %, LDS 10; level 0 waits for gathered rows, 47 % of a wave's life, vector ALU 46 %, MFMA 33, scalar 20, LDS 14 (16 KB read per
+// 32 x 16 score tile at TPW = 1, half of that at 2).  (224 us each at the rate of a large matrix product.)  TPW = 1 at level 1 and 2 at
+// level 0 each take about 1.1 times as long.
 #include <type_traits>
 
 #include "dkv_common.h"

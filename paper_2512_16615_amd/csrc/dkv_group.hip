@@ -237,9 +237,10 @@ constexpr int kChain = 8, kChainRow = 16;                              // query 
 // a lister whose successor in the same chain lists the block too.  Same arithmetic per tile, fewer partials.
 // P workgroups share the slots of a row of more than NW * NB entries; each walks the same rows and keeps the same books.
 // The tiles stream through a ring in LDS that runs on from query block to query block; the rows of I^(1) are looked up once, since a load of the
-// compiler's in the walk would be waited for together with every tile on its way.  Bound: LDS reads and issue at two (d = 128: three) waves a
-// SIMD.  With all 256 rows staged in LDS by way of registers, kernel, us: 16 heads x 65536 tokens 107 -> 99, 8 x 65536, d = 128 133 -> 118,
-// 8 x 262144, d = 128, K = 16 800 -> 611; steps, 32 x 16384 527 -> 510.  (d = 64 with three waves a SIMD spills 6 registers: 103; two places 101.)
+// compiler's in the walk would be waited for together with every tile on its way.  Bound, by counters (share of a SIMD's cycles; 25 % would be
+// all of the LDS that four share): d = 64 a tile's chain at two waves a SIMD, vector ALU 36 %, MFMA 32, LDS 7, a wave waits 34 % of its life; d = 128
+// LDS reads, 19 %, and issue, vector ALU 42, MFMA 46, at three waves.  With all 256 rows staged in LDS by way of registers, kernel, us: 16 heads
+// x 65536 tokens 107 -> 99, 8 x 65536, d = 128 133 -> 118, 8 x 262144, d = 128, K = 16 800 -> 611; steps, 32 x 16384 527 -> 510.  (d = 64 with three waves a SIMD spills 6 registers: 103; two places 101.)
 template <int D, int NW, int NB, int P>
 __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW == 8 || NB == 2 ? 2 : D == 128 ? 3 : 4))) dkv_chain_kernel(LevelTable t, GroupArgs a) {
     using S = GShape<D>;
@@ -349,8 +350,9 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW
 }
 
 // d = 128, where a workgroup of eight waves that holds all 256 rows of Q and dO has a CU to itself, two waves a SIMD: workgroups of four, three on
-// a CU, with the tiles in a ring of two places.  A wave owns a listed block.  Bound: LDS reads and issue.  us, before -> now: 8 heads x 262144
-// tokens, K = 16 (20 listed blocks and a dense one) 1066 -> 876 (with four places, two workgroups a CU, 1055), 8 x 65536, K = 8 104 -> 98; steps 6997 -> 6698 and
+// a CU, with the tiles in a ring of two places.  A wave owns a listed block.  Bound, by counters: LDS reads, 18 %
+// of a SIMD's cycles of the 25 that four have of one LDS, MFMA 43, vector ALU 31, and the barriers, waits of 56 % of a wave's life.  us, before ->
+// now: 8 heads x 262144 tokens, K = 16 (20 listed blocks and a dense one) 1066 -> 876 (with four places, two workgroups a CU, 1055), 8 x 65536, K = 8 104 -> 98; steps 6997 -> 6698 and
 // 1184 -> 1168 with the chain kernel's ring, 2 x 131072, K = 4 574 -> 526, Gaussian 568 -> 520.
 template <int D, int NW>
 __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(3))) dkv_upper_ring_kernel(LevelTable t, GroupArgs a) {
