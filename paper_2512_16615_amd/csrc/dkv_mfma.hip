@@ -224,7 +224,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 6
 // their L2 (0.97 GB fetched from beyond at 16 x 65536 tokens; dealt round 340 us, 1.4 GB).
 // A workgroup of four waves per four key blocks, the short lists by one wave each and the long ones by all four afterwards, with a barrier
 // between, took 295 us at 16 x 65536 tokens (now 254; Gaussian 325, 318), 150 at 32 x 16384 (133), 26 at 16 x 4096 (21), 1580 at 8 x 262144
-// with d = 128 and K = 16 (1610); with constant keys, whose lists hold every query, a step of 4 x 65536 takes 559 us instead of 1226.
+// with d = 128 and K = 16 (1610; a step with the one and the other 6759 and 6742, Gaussian 10027 and 9711); with constant keys, whose lists hold every query, a step of 4 x 65536 takes 559 us instead of 1226.
 // What bounds it: a wave's chain (1700 cycles a tile alone on its SIMD: 320 in LDS reads, 170 + 430 in products and softmax, 530 in asking
 // for the next rows), three waves a SIMD (with four the registers do not suffice: 300 us), and under load the requests, which take 1280
 // cycles a tile then.  Not faster: reading all operands in front of the first product, rows from one place only (243 of then 273 us), waves
