@@ -17,6 +17,13 @@
 // blocks of 64 with K <= 4 at 65536: the forward call takes 1 to 2 % longer (16 heads x 65536, Gaussian 348 -> 352 us), asking for K rows before
 // V's operands are read changes nothing.  What is left, d = 64: 21 % of the matrix pipe, half of the vector issue slots; level 0 by
 // itself (Le = 0) takes 162 us as before, at a third of the rate its gathers reach without any arithmetic.
+// The ring's places are known at compile time (the loop is unrolled over it, the last tile, the only one that may be short, stands behind it), no wait
+// of the compiler's own drains it, level 0's first rows are asked for beside the last coarse tile (one more place in LDS: 40 KB at d = 64, as much as
+// four workgroups a CU leave each), and at level 0 K's place is filled again while V's is still read.  Kernel in a step, before and now, us: 16 heads x
+// 65536 tokens 213.6 -> 209.0 (Gaussian 242.5 -> 232.3), in blocks of 64 372.6 -> 353.7, 32 x 16384 95.6 -> 91.4, 8 x 65536, d = 128, K = 16
+// 346.7 -> 328.9, 8 x 262144 1413 -> 1311; the forward call of 16 x 4096 tokens 29.5 -> 28.6.  What it spends its time on, by clocks in its waves at
+// 16 x 65536 (48000 cycles a wave): start to first tile 12000, a coarse tile 2500 (barrier 300, asking for the next tile 400, scores 450,
+// exponentials 650, second product 400), a level-0 tile 1450.  Without the math of level 0 the launch takes 193 us, without its loads 177.
 // Score tiles are computed transposed (S^T = K Q^T) so that the accumulator layout (4 keys x 1 query per
 // lane) is the B operand of O^T += V^T P^T; see mfma_common.h for the register layouts.
 #include <type_traits>
@@ -37,8 +44,9 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D 
     constexpr int CPH = HALF / 1024;                    // load_lds steps of 16 rows
     constexpr int CPW = 4 * CPH / NW;                   // of a [K | V] tile that the workgroup shares, per wave
     constexpr int RING = 4, NBUF = GW > 1 ? 2 : 1;      // phase A's tiles; phase B's tiles per group of waves
-    constexpr int OWN = (GW > 0 ? NW / GW : NW) * NBUF;
-    __shared__ __attribute__((aligned(16))) char lds[(OWN > RING ? OWN : RING) * 2 * TILE];
+    constexpr int OWN = (GW > 0 ? NW / GW : NW) * NBUF; // phase B's places
+    constexpr int PLACES = (OWN > RING - 1 ? OWN : RING - 1) + 1;     // one that phase A still reads when phase B's first rows are asked for
+    __shared__ __attribute__((aligned(16))) char lds[PLACES * 2 * TILE];
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -127,13 +135,13 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D 
         return pack8(p[0], p[1]);
     };
     // Query tiles first .. first + count - 1 of the wave against one tile of 32 keys in LDS; every operand is read once for all of
-    // them.  early: V's operands are read before the scores are worked on, and `have_read` is called when LDS holds nothing
-    // more of the tile that is wanted.
-    auto tile = [&](auto first, auto count, auto early, const char *kt, const char *vt, int c0, int c1, float w0, float w1, auto have_read) {
+    // them.  alone: the tile is in the wave's own place.  `k_read` is called when LDS holds nothing more of K's rows that is wanted,
+    // `v_wanted` before V's are read, and `v_read` when all of them have been.
+    auto tile = [&](auto first, auto count, auto alone, const char *kt, const char *vt, int c0, int c1, float w0, float w1, auto k_read,
+                    auto v_wanted, auto v_read) {
         constexpr int b0 = decltype(first)::value, n = decltype(count)::value;
-        constexpr bool E = decltype(early)::value;
+        constexpr bool E = decltype(alone)::value;
         f32x4 s[n][2];
-        bf16x8 vtr[E ? NT : 1];
 #pragma unroll
         for (int h = 0; h < 2; ++h)
 #pragma unroll
@@ -142,14 +150,17 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D 
 #pragma unroll
                 for (int b = 0; b < n; ++b) s[b][h] = mfma16(kop, qop[b0 + b][ks], ks == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : s[b][h]);
             }
-        if constexpr (E) {
-#pragma unroll
-            for (int x = 0; x < NT; ++x) vtr[x] = lds_tr_pair(vt + o.tr[x], vt + HALF + o.tr[x]);
-            have_read();
-        }
+        k_read();
         bf16x8 p[n];
         p[0] = probs(first, s[0][0], s[0][1], c0, c1, w0, w1);
         if constexpr (n > 1) p[n - 1] = probs(B1{}, s[n - 1][0], s[n - 1][1], c0, c1, w0, w1);
+        v_wanted();
+        bf16x8 vtr[E ? NT : 1];
+        if constexpr (E) {
+#pragma unroll
+            for (int x = 0; x < NT; ++x) vtr[x] = lds_tr_pair(vt + o.tr[x], vt + HALF + o.tr[x]);
+            v_read();
+        }
 #pragma unroll
         for (int x = 0; x < NT; ++x) {
             const bf16x8 v = E ? vtr[E ? x : 0] : lds_tr_pair(vt + o.tr[x], vt + HALF + o.tr[x]);
@@ -159,31 +170,74 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D 
     };
     using One = std::integral_constant<int, 1>;
     using All = std::integral_constant<int, NB>;
-    using Early = std::true_type;
-    using Late = std::false_type;
+    using Alone = std::true_type;
+    using Shared = std::false_type;
     auto nothing = []() {};
 
-    // ------------------------------------------------------------------ phase A: shared coarse levels
     const unsigned lds0 = lds_address(lds);
-    const int tok0 = (raw0 << t->lb) + ((j0_ & ((1 << t->ls) - 1)) << 4);
+    const int ntile = (nbc + 1) >> 1;                                 // of the coarse levels
+    // lane LL b + j: tile j's K rows; V's rows stand to_v0 further on
+    const uint64_t row0 = reinterpret_cast<uint64_t>(t->lev[0].K) + (uint64_t)(bh * N + ((int64_t)raw0 << t->lb) + ((j0_ & ((1 << t->ls) - 1)) << 4)) * ROWB;
+    const uint64_t to_v0 = reinterpret_cast<uint64_t>(t->lev[0].V) - reinterpret_cast<uint64_t>(t->lev[0].K);
+    if (nbc > 0) ctab.finish<D>(t);
+    // The compiler counts the loads that it knows of: unless Q's rows are waited for here, it waits for them in front of every tile's first
+    // products, and with them for all tiles on their way.
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+        for (int s = 0; s < KS; ++s) asm volatile("" : "+v"(qop[b][s]));
+
+    // ------------------------------------------------------------------ phase B's loads: level 0
+    // half h of the K rows (to_v = 0) or V rows of tile j0 of the list that begins at lane l0
+    auto load_half = [&](uint64_t to_v, int l0, int j0, int h, unsigned dst) {
+        const int j = j0 + h < nb0 ? j0 + h : j0;                     // an absent second half re-reads the first
+        load_lds<CPH>(reinterpret_cast<uint64_t>(BlockTable::rl_ptr(row0, l0 + j)) + to_v, src.v0, src.v1, dst + h * HALF);
+    };
+    // place x of phase B: not the one of phase A's last tile, which other waves may still be reading
+    const int keep = (ntile + RING - 1) % RING;
+    auto place = [&](int x) { return (unsigned)(x < keep ? x : x + 1) * (2 * TILE); };
+    constexpr int SHARE = GW > 0 ? GW : 1;                            // waves that bring in a list's tiles together
+    const int own = GW > 1 ? wave / SHARE * NBUF : wave;
+    const unsigned place0 = place(own), place1 = place(own + NBUF - 1);
+    auto issue_b = [&](int u) {                                       // GW > 1: the wave's share of tile u
+        const unsigned dst = lds0 + (u & 1 ? place1 : place0);
+#pragma unroll
+        for (int x = 0; x < 4 / SHARE; ++x) {
+            const int part = wave % SHARE * (4 / SHARE) + x;          // K, K, V, V: its halves
+            load_half(part < 2 ? 0 : to_v0, 0, 2 * u, part & 1, dst + (part >> 1) * TILE);
+        }
+    };
+    auto load_rows = [&](uint64_t to_v, int l0, int j0, unsigned to) {
+        load_half(to_v, l0, j0, 0, lds0 + place0 + to);
+        load_half(to_v, l0, j0, 1, lds0 + place0 + to);
+    };
+    auto begin_b = [&]() {
+        if constexpr (GW > 1) issue_b(0);
+        else {
+            load_rows(0, 0, 0, 0);
+            load_rows(to_v0, 0, 0, TILE);
+        }
+    };
+
+    // ------------------------------------------------------------------ phase A: shared coarse levels
     if (nbc > 0) {
-        ctab.finish<D>(t);
         const bool v_wave = wave >= NW / 2;                           // this wave brings in V rows
         uint64_t rows = v_wave ? +ctab.vptr : +ctab.kptr;
-        float w_now = ctab.bias2, w_next = 0.f;                       // the weights, of the tile worked on
-        int c0 = 16, c1 = 16;                                         // rows of the last tile's halves
-        const int ntile = (nbc + 1) >> 1;                             // only the last tile may be ragged or lack its second half
+        float w_now = ctab.bias2, w_next = w_now;                     // the weights, of the tile worked on
+        int c0 = 16, c1 = 16;                                         // rows of the last tile's halves (only it may be ragged or lack its second half)
         // this wave's share of a tile: load_lds steps of one half of K or of V
         const int part = wave * CPW / CPH, sub = wave * CPW % CPH, half = part & 1;
-        auto issue = [&](int u) {                                     // coarse blocks 2u, 2u + 1
+        auto issue = [&](int u, int to) {                             // coarse blocks 2u, 2u + 1, to place `to`
             if (u > 0 && ((2 * u) & 63) == 0) {
-                ctab.fill<D>(t, bh, (unsigned)blk0, (2 * u) >> 6, lane);
+                list_args_ptr t2 = t;
+                asm volatile("" : "+s"(t2));                          // the levels' fields are not kept for this
+                ctab.fill<D>(t2, bh, (unsigned)blk0, (2 * u) >> 6, lane);
                 rows = v_wave ? +ctab.vptr : +ctab.kptr;
                 w_next = ctab.bias2;
             }
             const int j = (2 * u + half < nbc ? 2 * u + half : 2 * u) & 63;
             const uint64_t base = reinterpret_cast<uint64_t>(BlockTable::rl_ptr(rows, j));
-            const unsigned dst = lds0 + (u % RING) * (2 * TILE) + wave * CPW * 1024;
+            const unsigned dst = lds0 + to * (2 * TILE) + wave * CPW * 1024;
             if (u + 1 == ntile) {
                 const int n0 = ctab.count((2 * u) & 63), n1 = 2 * u + 1 < nbc ? ctab.count((2 * u + 1) & 63) : 16;
                 const int cnt = ctab.count(j);
@@ -201,75 +255,69 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D 
             }
             load_lds<CPW>(base + sub * 1024, src.v0, src.v1, dst);
         };
-        for (int u = 0; u < RING - 1 && u < ntile; ++u) issue(u);
-        for (int u = 0; u < ntile; ++u) {
+        auto weight = [&](int j) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w_now), j & 63)); };
+#pragma unroll
+        for (int u = 0; u < RING - 1; ++u)
+            if (u < ntile) issue(u, u);
+        // All tiles but the last, in a loop that is unrolled over the ring: the places are known, no half is short.
+        auto turn = [&](int u, auto at) {
+            constexpr int x = decltype(at)::value;
             // tile u is there, and tile u - 1, whose place tile u + 3 takes, has been read by every wave
             if (u + 2 < ntile) vm_wait_barrier<2 * CPW>();
-            else vm_wait_barrier<0>();
-            if (u + RING - 1 < ntile) issue(u + RING - 1);
-            if (u > 0 && ((2 * u) & 63) == 0) w_now = w_next;
-            auto weight = [&](int j) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w_now), j & 63)); };
-            const bool last = u + 1 == ntile;
-            const char *kt = lds + (u % RING) * (2 * TILE);
-            // an absent half: probabilities 0
-            tile(B0{}, All{}, Late{}, kt, kt + TILE, last ? c0 : 16, last ? c1 : 16, weight(2 * u),
-                 2 * u + 1 < nbc ? weight(2 * u + 1) : -INFINITY, nothing);
+            else vm_wait_barrier<CPW>();
+            if (u + RING - 1 < ntile) issue(u + RING - 1, (x + RING - 1) % RING);
+            if (x == 0 && ((2 * u) & 63) == 0) w_now = w_next;        // (a chunk of 64 blocks begins at place 0)
+            const char *kt = lds + x * (2 * TILE);
+            tile(B0{}, All{}, Shared{}, kt, kt + TILE, 16, 16, weight(2 * u), weight(2 * u + 1), nothing, nothing, nothing);
+        };
+        int u = 0;
+        for (; u + RING < ntile; u += RING) {
+            turn(u, std::integral_constant<int, 0>());
+            turn(u + 1, std::integral_constant<int, 1>());
+            turn(u + 2, std::integral_constant<int, 2>());
+            turn(u + 3, std::integral_constant<int, 3>());
         }
-        vm_wait_barrier<0>();                                         // phase A's buffers are free
+        if (u + 1 < ntile) { turn(u, std::integral_constant<int, 0>()); ++u; }
+        if (u + 1 < ntile) { turn(u, std::integral_constant<int, 1>()); ++u; }
+        if (u + 1 < ntile) { turn(u, std::integral_constant<int, 2>()); ++u; }
+        vm_wait_barrier<0>();
+        begin_b();                                                    // only the last tile's place is in use any more
+        if (((2 * u) & 63) == 0) w_now = w_next;
+        const char *kt = lds + (u % RING) * (2 * TILE);
+        // an absent half: probabilities 0
+        tile(B0{}, All{}, Shared{}, kt, kt + TILE, c0, c1, weight(2 * u), 2 * u + 1 < nbc ? weight(2 * u + 1) : -INFINITY, nothing, nothing, nothing);
+    } else {
+        begin_b();
     }
 
     // ------------------------------------------------------------------ phase B: level 0
-    // half h of the K (or V, T0) rows of tile j0 of the list that begins at lane l0, by the wave alone
-    auto load_half = [&](const void *T0, int l0, int j0, int h, unsigned dst) {
-        const int j = j0 + h < nb0 ? j0 + h : j0;                     // an absent second half re-reads the first
-        const int64_t row = bh * N + __builtin_amdgcn_readlane(tok0, l0 + j);
-        load_lds<CPH>(reinterpret_cast<uint64_t>(T0) + (uint64_t)row * ROWB, src.v0, src.v1, dst + h * HALF);
-    };
-    const void *K0 = t->lev[0].K, *V0 = t->lev[0].V;
     if constexpr (GW > 1) {
         // Blocks of 32 or 64 tokens: the B queries of a block use one level-0 list, whose tiles the GW waves that hold them bring in
         // together, double-buffered.  A list is whole blocks of B >= 32 tokens: no half of a tile is ever absent.
-        const int wg_in = wave % GW;
-        const char *buf = lds + (wave / GW) * (2 * 2 * TILE);
-        const unsigned dst = lds0 + (wave / GW) * (2 * 2 * TILE);
-        auto issue = [&](int u) {
-#pragma unroll
-            for (int x = 0; x < 4 / GW; ++x) {
-                const int part = wg_in * (4 / GW) + x;                // K, K, V, V: its halves
-                load_half(part < 2 ? K0 : V0, 0, 2 * u, part & 1, dst + (u & 1) * (2 * TILE) + (part >> 1) * TILE);
-            }
-        };
-        issue(0);
         for (int u = 0; 2 * u < nb0; ++u) {
             vm_wait_barrier<0>();
-            if (2 * u + 2 < nb0) issue(u + 1);
-            const char *kt = buf + (u & 1) * (2 * TILE);
-            tile(B0{}, All{}, Late{}, kt, kt + TILE, 16, 16, 0.f, 0.f, nothing);
+            if (2 * u + 2 < nb0) issue_b(u + 1);
+            const char *kt = lds + (u & 1 ? place1 : place0);
+            tile(B0{}, All{}, Shared{}, kt, kt + TILE, 16, 16, 0.f, 0.f, nothing, nothing, nothing);
         }
     } else {
-        // Every wave alone: the tiles of its query tiles (GW = 1: of all of them at once) form one stream.  The next tile's rows are
-        // asked for as soon as the current one's have been read, so they fly during all of its math.
-        const char *my = lds + wave * (2 * TILE);
-        const unsigned dst = lds0 + wave * (2 * TILE);
-        auto load_tile = [&](int l0, int j0) {
-            load_half(K0, l0, j0, 0, dst);
-            load_half(K0, l0, j0, 1, dst);
-            load_half(V0, l0, j0, 0, dst + TILE);
-            load_half(V0, l0, j0, 1, dst + TILE);
-        };
+        // Every wave alone: the tiles of its query tiles (GW = 1: of all of them at once) form one stream.  The next tile's K rows are asked
+        // for as soon as this tile's have been read, its V rows likewise: K's fly during the exponentials and the second product, V's
+        // during the second product, the next tile's first one and its exponentials.
+        const char *my = lds + place0;
         auto walk = [&](auto first, auto count, bool end) {
             const int l0 = LL * decltype(first)::value;
             for (int j0 = 0; j0 < nb0; j0 += 2) {
-                const bool here = j0 + 2 < nb0;
-                vm_wait<0>();
+                const bool here = j0 + 2 < nb0, more = here || !end;
+                const int nl = here ? l0 : l0 + LL, nj = here ? j0 + 2 : 0;
+                vm_wait<2 * CPH>();
                 // level-0 blocks are always full; an absent second half has weight 0
-                tile(first, count, Early{}, my, my + TILE, 16, 16, 0.f, j0 + 1 < nb0 ? 0.f : -INFINITY, [&]() {
-                    if (here) load_tile(l0, j0 + 2);
-                    else if (!end) load_tile(l0 + LL, 0);
-                });
+                tile(first, count, Alone{}, my, my + TILE, 16, 16, 0.f, j0 + 1 < nb0 ? 0.f : -INFINITY,
+                     [&]() { if (more) load_rows(0, nl, nj, 0); },
+                     [&]() { if (more) vm_wait<2 * CPH>(); else vm_wait<0>(); },
+                     [&]() { if (more) load_rows(to_v0, nl, nj, TILE); });
             }
         };
-        load_tile(0, 0);
         if constexpr (GW == 1) walk(B0{}, All{}, true);
         else {
             walk(B0{}, One{}, NB == 1);
