@@ -5,7 +5,9 @@
 // Per tile and query block:  S^T = K Q^T, dP^T = V dO^T  ->  dS^T = P^T o (dP^T - D)  ->  dQ^T += K^T dS^T,
 // with K read from LDS both row-wise (first product) and transposed (last product).
 // Rows go from memory straight into LDS, as in the forward kernel (16 heads x 65536 tokens, d = 64: 269 -> 249 us; 8 x 65536, d = 128,
-// K = 16: 447 -> 383).
+// K = 16: 447 -> 383).  The ring's places known at compile time and level 0's first rows asked for beside the last coarse tile, as there: kernel in a
+// step, us, 16 x 65536 272.1 -> 267.0 (Gaussian 304.6 -> 297.2), 16 x 4096 20.8 -> 19.8, 32 x 16384 132.1 -> 129.5, 8 x 65536, d = 128, K = 16
+// 405.4 -> 392.1, 8 x 262144 1594 -> 1526.
 // The kernel also produces D = rowsum(dO o O) for its queries and stores it for the key-major kernels.
 #include <type_traits>
 
@@ -35,8 +37,9 @@ dq_shared_kernel(ListArgs args, const uint16_t *__restrict__ Q, const uint16_t *
     constexpr int CPH = HALF / 1024;                    // load_lds steps of 16 rows
     constexpr int CPW = 4 * CPH / NW;                   // of a [K | V] tile that the workgroup shares, per wave
     constexpr int RING = 4, NBUF = GW > 1 ? 2 : 1;      // phase A's tiles; phase B's tiles per group of waves
-    constexpr int OWN = (GW > 0 ? NW / GW : NW) * NBUF;
-    __shared__ __attribute__((aligned(16))) char lds[(OWN > RING ? OWN : RING) * 2 * TILE];
+    constexpr int OWN = (GW > 0 ? NW / GW : NW) * NBUF; // phase B's places
+    constexpr int PLACES = (OWN > RING - 1 ? OWN : RING - 1) + 1;     // one that phase A still reads when phase B's first rows are asked for
+    __shared__ __attribute__((aligned(16))) char lds[PLACES * 2 * TILE];
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -135,11 +138,11 @@ dq_shared_kernel(ListArgs args, const uint16_t *__restrict__ Q, const uint16_t *
     using B0 = std::integral_constant<int, 0>;
     using B1 = std::integral_constant<int, 1>;
     // Scores, dP - D and dQ^T += K^T dS^T of query tiles first .. first + count - 1 for one tile of 32 keys in LDS: every read
-    // serves all of them.  early: K's transposed operands are read before the scores are worked on, and `have_read` is called when
-    // LDS holds nothing more of the tile that is wanted.
-    auto tile = [&](auto first, auto count, auto early, const char *kt, const char *vt, int c0, int c1, float w0, float w1, auto have_read) {
+    // serves all of them.  alone: the tile is in the wave's own place, K's transposed operands are read before the scores are worked on, and
+    // `have_read` is called when LDS holds nothing more of the tile that is wanted.
+    auto tile = [&](auto first, auto count, auto alone, const char *kt, const char *vt, int c0, int c1, float w0, float w1, auto have_read) {
         constexpr int b0 = decltype(first)::value, n = decltype(count)::value;
-        constexpr bool E = decltype(early)::value;
+        constexpr bool E = decltype(alone)::value;
         f32x4 s[n][2], dp[n][2];
         bf16x8 ktr[E ? NT : 1];
 #pragma unroll
@@ -173,31 +176,68 @@ dq_shared_kernel(ListArgs args, const uint16_t *__restrict__ Q, const uint16_t *
     };
     using One = std::integral_constant<int, 1>;
     using All = std::integral_constant<int, NB>;
-    using Early = std::true_type;
-    using Late = std::false_type;
+    using Alone = std::true_type;
+    using Shared = std::false_type;
     auto nothing = []() {};
 
-    // ------------------------------------------------------------------ phase A: shared coarse levels
     const unsigned lds0 = lds_address(lds);
-    const int tok0 = (raw0 << t->lb) + ((j0_ & ((1 << t->ls) - 1)) << 4);
+    const int ntile = (nbc + 1) >> 1;                                 // of the coarse levels
+    // lane LL b + j: tile j's K rows; V's rows stand to_v0 further on
+    const uint64_t row0 = reinterpret_cast<uint64_t>(t->lev[0].K) + (uint64_t)(bh * N + ((int64_t)raw0 << t->lb) + ((j0_ & ((1 << t->ls) - 1)) << 4)) * ROWB;
+    const uint64_t to_v0 = reinterpret_cast<uint64_t>(t->lev[0].V) - reinterpret_cast<uint64_t>(t->lev[0].K);
+    if (nbc > 0) ctab.finish<D>(t);
+
+    // ------------------------------------------------------------------ phase B's loads: level 0
+    // half h of the K rows (to_v = 0) or V rows of tile j0 of the list that begins at lane l0
+    auto load_half = [&](uint64_t to_v, int l0, int j0, int h, unsigned dst) {
+        const int j = j0 + h < nb0 ? j0 + h : j0;                     // an absent second half re-reads the first
+        load_lds<CPH>(reinterpret_cast<uint64_t>(BlockTable::rl_ptr(row0, l0 + j)) + to_v, src.v0, src.v1, dst + h * HALF);
+    };
+    // place x of phase B: not the one of phase A's last tile, which other waves may still be reading
+    const int keep = (ntile + RING - 1) % RING;
+    auto place = [&](int x) { return (unsigned)(x < keep ? x : x + 1) * (2 * TILE); };
+    constexpr int SHARE = GW > 0 ? GW : 1;                            // waves that bring in a list's tiles together
+    const int own = GW > 1 ? wave / SHARE * NBUF : wave;
+    const unsigned place0 = place(own), place1 = place(own + NBUF - 1);
+    auto issue_b = [&](int u) {                                       // GW > 1: the wave's share of tile u
+        const unsigned dst = lds0 + (u & 1 ? place1 : place0);
+#pragma unroll
+        for (int x = 0; x < 4 / SHARE; ++x) {
+            const int part = wave % SHARE * (4 / SHARE) + x;          // K, K, V, V: its halves
+            load_half(part < 2 ? 0 : to_v0, 0, 2 * u, part & 1, dst + (part >> 1) * TILE);
+        }
+    };
+    auto load_rows = [&](uint64_t to_v, int l0, int j0, unsigned to) {
+        load_half(to_v, l0, j0, 0, lds0 + place0 + to);
+        load_half(to_v, l0, j0, 1, lds0 + place0 + to);
+    };
+    auto begin_b = [&]() {
+        if constexpr (GW > 1) issue_b(0);
+        else {
+            load_rows(0, 0, 0, 0);
+            load_rows(to_v0, 0, 0, TILE);
+        }
+    };
+
+    // ------------------------------------------------------------------ phase A: shared coarse levels
     if (nbc > 0) {
-        ctab.finish<D>(t);
         const bool v_wave = wave >= NW / 2;                           // this wave brings in V rows
         uint64_t rows = v_wave ? +ctab.vptr : +ctab.kptr;
-        float w_now = ctab.bias2, w_next = 0.f;                       // the weights, of the tile worked on
-        int c0 = 16, c1 = 16;                                         // rows of the last tile's halves
-        const int ntile = (nbc + 1) >> 1;                             // only the last tile may be ragged or lack its second half
+        float w_now = ctab.bias2, w_next = w_now;                     // the weights, of the tile worked on
+        int c0 = 16, c1 = 16;                                         // rows of the last tile's halves (only it may be ragged or lack its second half)
         // this wave's share of a tile: load_lds steps of one half of K or of V
         const int part = wave * CPW / CPH, sub = wave * CPW % CPH, half = part & 1;
-        auto issue = [&](int u) {                                     // coarse blocks 2u, 2u + 1
+        auto issue = [&](int u, int to) {                             // coarse blocks 2u, 2u + 1, to place `to`
             if (u > 0 && ((2 * u) & 63) == 0) {
-                ctab.fill<D>(t, bh, (unsigned)blk0, (2 * u) >> 6, lane);
+                list_args_ptr t2 = t;
+                asm volatile("" : "+s"(t2));                          // the levels' fields are not kept for this
+                ctab.fill<D>(t2, bh, (unsigned)blk0, (2 * u) >> 6, lane);
                 rows = v_wave ? +ctab.vptr : +ctab.kptr;
                 w_next = ctab.bias2;
             }
             const int j = (2 * u + half < nbc ? 2 * u + half : 2 * u) & 63;
             const uint64_t base = reinterpret_cast<uint64_t>(BlockTable::rl_ptr(rows, j));
-            const unsigned dst = lds0 + (u % RING) * (2 * TILE) + wave * CPW * 1024;
+            const unsigned dst = lds0 + to * (2 * TILE) + wave * CPW * 1024;
             if (u + 1 == ntile) {
                 const int n0 = ctab.count((2 * u) & 63), n1 = 2 * u + 1 < nbc ? ctab.count((2 * u + 1) & 63) : 16;
                 const int cnt = ctab.count(j);
@@ -215,78 +255,71 @@ dq_shared_kernel(ListArgs args, const uint16_t *__restrict__ Q, const uint16_t *
             }
             load_lds<CPW>(base + sub * 1024, src.v0, src.v1, dst);
         };
-        for (int u = 0; u < RING - 1 && u < ntile; ++u) issue(u);
+        auto weight = [&](int j) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w_now), j & 63)); };
+#pragma unroll
+        for (int u = 0; u < RING - 1; ++u)
+            if (u < ntile) issue(u, u);
         deltas();
-        for (int u = 0; u < ntile; ++u) {
+        // All tiles but the last, in a loop that is unrolled over the ring: the places are known, no half is short.
+        auto turn = [&](int u, auto at) {
+            constexpr int x = decltype(at)::value;
             // tile u is there, and tile u - 1, whose place tile u + 3 takes, has been read by every wave
             if (u + 2 < ntile) vm_wait_barrier<2 * CPW>();
-            else vm_wait_barrier<0>();
-            if (u + RING - 1 < ntile) issue(u + RING - 1);
-            if (u > 0 && ((2 * u) & 63) == 0) w_now = w_next;
-            auto weight = [&](int j) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w_now), j & 63)); };
-            const bool last = u + 1 == ntile;
-            const char *kt = lds + (u % RING) * (2 * TILE);
-            // an absent half: P = 0
-            tile(B0{}, All{}, Late{}, kt, kt + TILE, last ? c0 : 16, last ? c1 : 16, weight(2 * u),
-                 2 * u + 1 < nbc ? weight(2 * u + 1) : -INFINITY, nothing);
+            else vm_wait_barrier<CPW>();
+            if (u + RING - 1 < ntile) issue(u + RING - 1, (x + RING - 1) % RING);
+            if (x == 0 && ((2 * u) & 63) == 0) w_now = w_next;        // (a chunk of 64 blocks begins at place 0)
+            const char *kt = lds + x * (2 * TILE);
+            tile(B0{}, All{}, Shared{}, kt, kt + TILE, 16, 16, weight(2 * u), weight(2 * u + 1), nothing);
+        };
+        int u = 0;
+        for (; u + RING < ntile; u += RING) {
+            turn(u, std::integral_constant<int, 0>());
+            turn(u + 1, std::integral_constant<int, 1>());
+            turn(u + 2, std::integral_constant<int, 2>());
+            turn(u + 3, std::integral_constant<int, 3>());
         }
-        vm_wait_barrier<0>();                                         // phase A's buffers are free
+        if (u + 1 < ntile) { turn(u, std::integral_constant<int, 0>()); ++u; }
+        if (u + 1 < ntile) { turn(u, std::integral_constant<int, 1>()); ++u; }
+        if (u + 1 < ntile) { turn(u, std::integral_constant<int, 2>()); ++u; }
+        vm_wait_barrier<0>();
+        begin_b();                                                    // only the last tile's place is in use any more
+        if (((2 * u) & 63) == 0) w_now = w_next;
+        const char *kt = lds + (u % RING) * (2 * TILE);
+        // an absent half: P = 0
+        tile(B0{}, All{}, Shared{}, kt, kt + TILE, c0, c1, weight(2 * u), 2 * u + 1 < nbc ? weight(2 * u + 1) : -INFINITY, nothing);
     } else {
+        begin_b();
         deltas();
     }
 
     // ------------------------------------------------------------------ phase B: level 0
-    // half h of the K (or V, T0) rows of tile j0 of the list that begins at lane l0, by the wave alone
-    auto load_half = [&](const void *T0, int l0, int j0, int h, unsigned dst) {
-        const int j = j0 + h < nb0 ? j0 + h : j0;                     // an absent second half re-reads the first
-        const int64_t row = bh * N + __builtin_amdgcn_readlane(tok0, l0 + j);
-        load_lds<CPH>(reinterpret_cast<uint64_t>(T0) + (uint64_t)row * ROWB, src.v0, src.v1, dst + h * HALF);
-    };
-    const void *K0 = t->lev[0].K, *V0 = t->lev[0].V;
     if constexpr (GW > 1) {
         // Blocks of 32 or 64 tokens: the B queries of a block use one level-0 list, whose tiles the GW waves that hold them bring in
         // together, double-buffered.  A list is whole blocks of B >= 32 tokens: no half of a tile is ever absent.
-        const int wg_in = wave % GW;
-        const char *buf = lds + (wave / GW) * (2 * 2 * TILE);
-        const unsigned dst = lds0 + (wave / GW) * (2 * 2 * TILE);
-        auto issue = [&](int u) {
-#pragma unroll
-            for (int x = 0; x < 4 / GW; ++x) {
-                const int part = wg_in * (4 / GW) + x;                // K, K, V, V: its halves
-                load_half(part < 2 ? K0 : V0, 0, 2 * u, part & 1, dst + (u & 1) * (2 * TILE) + (part >> 1) * TILE);
-            }
-        };
-        issue(0);
         for (int u = 0; 2 * u < nb0; ++u) {
             vm_wait_barrier<0>();
-            if (2 * u + 2 < nb0) issue(u + 1);
-            const char *kt = buf + (u & 1) * (2 * TILE);
-            tile(B0{}, All{}, Late{}, kt, kt + TILE, 16, 16, 0.f, 0.f, nothing);
+            if (2 * u + 2 < nb0) issue_b(u + 1);
+            const char *kt = lds + (u & 1 ? place1 : place0);
+            tile(B0{}, All{}, Shared{}, kt, kt + TILE, 16, 16, 0.f, 0.f, nothing);
         }
     } else {
         // Every wave alone: the tiles of its query tiles (GW = 1: of all of them at once) form one stream.  The next tile's rows are
         // asked for as soon as the current one's have been read, so they fly during all of its math.
-        const char *my = lds + wave * (2 * TILE);
-        const unsigned dst = lds0 + wave * (2 * TILE);
-        auto load_tile = [&](int l0, int j0) {
-            load_half(K0, l0, j0, 0, dst);
-            load_half(K0, l0, j0, 1, dst);
-            load_half(V0, l0, j0, 0, dst + TILE);
-            load_half(V0, l0, j0, 1, dst + TILE);
-        };
+        const char *my = lds + place0;
         auto walk = [&](auto first, auto count, bool end) {
             const int l0 = LL * decltype(first)::value;
             for (int j0 = 0; j0 < nb0; j0 += 2) {
                 const bool here = j0 + 2 < nb0;
+                const int nl = here ? l0 : l0 + LL, nj = here ? j0 + 2 : 0;
                 vm_wait<0>();
                 // level-0 blocks are always full; an absent second half has weight 0
-                tile(first, count, Early{}, my, my + TILE, 16, 16, 0.f, j0 + 1 < nb0 ? 0.f : -INFINITY, [&]() {
-                    if (here) load_tile(l0, j0 + 2);
-                    else if (!end) load_tile(l0 + LL, 0);
+                tile(first, count, Alone{}, my, my + TILE, 16, 16, 0.f, j0 + 1 < nb0 ? 0.f : -INFINITY, [&]() {
+                    if (!here && end) return;
+                    load_rows(0, nl, nj, 0);
+                    load_rows(to_v0, nl, nj, TILE);
                 });
             }
         };
-        load_tile(0, 0);
         if constexpr (GW == 1) walk(B0{}, All{}, true);
         else {
             walk(B0{}, One{}, NB == 1);
