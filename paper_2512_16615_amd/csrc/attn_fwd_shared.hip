@@ -331,14 +331,9 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D 
         const float l = rows_sum(lsum[b]);
         const float inv = 1.f / l;
         const int64_t row = bh * N + tile_of(b) * 16 + i16;
-        uint16_t *orow = O + row * D + 4 * g;
+        auto out = [&](int n) { return u32x2{pack_bf16(acc[b][n][0] * inv, acc[b][n][1] * inv), pack_bf16(acc[b][n][2] * inv, acc[b][n][3] * inv)}; };
 #pragma unroll
-        for (int n = 0; n < NT; ++n) {
-            u32x2 w;
-            w[0] = pack_bf16(acc[b][n][0] * inv, acc[b][n][1] * inv);
-            w[1] = pack_bf16(acc[b][n][2] * inv, acc[b][n][3] * inv);
-            *reinterpret_cast<u32x2 *>(orow + n * 16) = w;
-        }
+        for (int n = 0; n < NT; n += 2) store_pair(O + row * D, n, g, out(n), out(n + 1));
         if (g == 0) LSE[row] = (m[b] + __builtin_amdgcn_logf(l)) * kLn2;
     }
 }

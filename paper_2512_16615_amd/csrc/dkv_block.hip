@@ -163,21 +163,22 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BlockS
     for (int x = 0; x < TPW; ++x) {
         const int j = (int)blk * TPB + wig * TPW + x;
         if (j >= ntile || 16 * j + i16 >= a.n_l) continue;
-        const int64_t row = ((int64_t)bh * a.n_l + 16 * j + i16) * D + 4 * g;
+        const int64_t row = ((int64_t)bh * a.n_l + 16 * j + i16) * D;
+        if (a.dK) {                                        // level 0: whole tiles, all lanes are here
+            auto value = [&](f32x4 sum, const float *par, int n) {
+                if (par) sum += *reinterpret_cast<const f32x4 *>(par + ((int64_t)bh * a.blocks.d + blk) * D + n * 16 + 4 * g) * a.inv_B;
+                return u32x2{pack_bf16(sum[0], sum[1]), pack_bf16(sum[2], sum[3])};
+            };
 #pragma unroll
-        for (int n = 0; n < S::NT; ++n) {
-            f32x4 k = key[x].accK[n] * wK, v = key[x].accV[n] * wV;
-            if (a.dK) {                                    // level 0
-                if (a.parK) {
-                    const int64_t par = ((int64_t)bh * a.blocks.d + blk) * D + n * 16 + 4 * g;
-                    k += *reinterpret_cast<const f32x4 *>(a.parK + par) * a.inv_B;
-                    v += *reinterpret_cast<const f32x4 *>(a.parV + par) * a.inv_B;
-                }
-                *reinterpret_cast<u32x2 *>(a.dK + row + n * 16) = u32x2{pack_bf16(k[0], k[1]), pack_bf16(k[2], k[3])};
-                *reinterpret_cast<u32x2 *>(a.dV + row + n * 16) = u32x2{pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
-            } else {
-                *reinterpret_cast<f32x4 *>(a.partK + split * a.slab + row + n * 16) = k;
-                *reinterpret_cast<f32x4 *>(a.partV + split * a.slab + row + n * 16) = v;
+            for (int n = 0; n < S::NT; n += 2) {
+                store_pair(a.dK + row, n, g, value(key[x].accK[n] * wK, a.parK, n), value(key[x].accK[n + 1] * wK, a.parK, n + 1));
+                store_pair(a.dV + row, n, g, value(key[x].accV[n] * wV, a.parV, n), value(key[x].accV[n + 1] * wV, a.parV, n + 1));
+            }
+        } else {
+#pragma unroll
+            for (int n = 0; n < S::NT; ++n) {
+                *reinterpret_cast<f32x4 *>(a.partK + split * a.slab + row + n * 16 + 4 * g) = key[x].accK[n] * wK;
+                *reinterpret_cast<f32x4 *>(a.partV + split * a.slab + row + n * 16 + 4 * g) = key[x].accV[n] * wV;
             }
         }
     }

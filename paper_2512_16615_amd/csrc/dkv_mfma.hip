@@ -357,16 +357,13 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(D == 64
         }
     };
     // scale dK, add the parent token's share (adjoint of mean pooling), round once
-    auto store = [&](uint16_t *out, int64_t k, int n, f32x4 sum, const float *par) {
+    auto value = [&](int n, f32x4 sum, const float *par) {
         if (has_par) {
             const f32x4 x = *reinterpret_cast<const f32x4 *>(par + 16 * n + 4 * g);
 #pragma unroll
             for (int r = 0; r < 4; ++r) sum[r] += x[r] * a.inv_B;
         }
-        u32x2 w;
-        w[0] = pack_bf16(sum[0], sum[1]);
-        w[1] = pack_bf16(sum[2], sum[3]);
-        *reinterpret_cast<u32x2 *>(out + (k * 16 + i16) * D + n * 16 + 4 * g) = w;
+        return u32x2{pack_bf16(sum[0], sum[1]), pack_bf16(sum[2], sum[3])};
     };
     load_tile(first);
     int t = first, follows = 1;                             // follows: 0 nothing, 1 another tile of this list, 2 another list
@@ -477,12 +474,9 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(D == 64
             }
         }
 #pragma unroll
-        for (int n = 0; n < S::NT; ++n) {
-            f32x4 k = accK[n];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) k[r] *= a.scale;
-            store(a.dK, key0 + j, n, k, par);
-            store(a.dV, key0 + j, n, accV[n], par + D);
+        for (int n = 0; n < S::NT; n += 2) {
+            store_pair(a.dK + ((key0 + j) * 16 + i16) * D, n, g, value(n, accK[n] * a.scale, par), value(n + 1, accK[n + 1] * a.scale, par));
+            store_pair(a.dV + ((key0 + j) * 16 + i16) * D, n, g, value(n, accV[n], par + D), value(n + 1, accV[n + 1], par + D));
         }
     }
 }

@@ -330,14 +330,11 @@ dq_shared_kernel(ListArgs args, const uint16_t *__restrict__ Q, const uint16_t *
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
         if (blk0 + NB * wave + b >= nblk) break;
-        uint16_t *orow = dQ + (bh * N + (blk0 + NB * wave + b) * 16 + i16) * D + 4 * g;
+        auto out = [&](int n) {
+            return u32x2{pack_bf16(acc[b][n][0] * t->scale, acc[b][n][1] * t->scale), pack_bf16(acc[b][n][2] * t->scale, acc[b][n][3] * t->scale)};
+        };
 #pragma unroll
-        for (int n = 0; n < NT; ++n) {
-            u32x2 w;
-            w[0] = pack_bf16(acc[b][n][0] * t->scale, acc[b][n][1] * t->scale);
-            w[1] = pack_bf16(acc[b][n][2] * t->scale, acc[b][n][3] * t->scale);
-            *reinterpret_cast<u32x2 *>(orow + n * 16) = w;
-        }
+        for (int n = 0; n < NT; n += 2) store_pair(dQ + (bh * N + (blk0 + NB * wave + b) * 16 + i16) * D, n, g, out(n), out(n + 1));
     }
 }
 

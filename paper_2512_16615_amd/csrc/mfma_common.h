@@ -98,6 +98,23 @@ __device__ __forceinline__ float rows_sum(float x) {
     return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
 
+// Results of a matrix product, transposed, to a row of 16-bit values: lane 16 g + i has channels 16 n + 4 g .. + 3 of row i in `a` and
+// 16 n + 16 + 4 g .. + 3 in `b`.  The lanes of an odd g hand their `a` to the ones before them and take those lanes' `b`, so that each has 8 channels in a
+// row: 16 bytes a lane, and four lanes write 64 bytes of a row where they wrote 32.  row: channel 0 of row i.
+// The L2 takes 64 bytes a request: with 32 a sixth of the forward kernel's requests were its result.  Kernels in a step with 32 and with 64, us: 16 heads
+// x 65536 tokens forward 210.7 and 198.6, dQ 271.8 and 260.7, level-0 dK/dV 264.9 and 254.6 (Gaussian 236.6 and 225.2, 301.3 and 292.4, 323.6
+// and 305.5), 32 x 16384 97.1 and 90.6, 134.1 and 127.9, 141.5 and 134.5, 8 x 262144, d = 128 1324 and 1279, 1568 and 1539, 1646 and 1636.
+__device__ __forceinline__ void store_pair(uint16_t *row, int n, int g, u32x2 a, u32x2 b) {
+    u32x4 w;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const auto r = __builtin_amdgcn_permlane16_swap(a[k], b[k], false, false);
+        w[k] = r[0];
+        w[2 + k] = r[1];
+    }
+    *reinterpret_cast<u32x4 *>(row + 16 * (n + (g & 1)) + 8 * (g >> 1)) = w;
+}
+
 // arr[idx] for a small kernel-argument array without dynamic indexing (which would spill the table to
 // scratch memory): a chain of selects over compile-time positions.
 template <class T, int n>
