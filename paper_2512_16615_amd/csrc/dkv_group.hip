@@ -7,8 +7,7 @@
 //   S = Q K^T, dP = dO V^T (lane: 4 queries x 1 key) -> P, dS -> dV^T += dO^T P, dK^T += Q^T dS.
 // That yields, per (query group, coarse block of its list), the block's gradient restricted to the group's
 // queries: a fp32 partial of 2 x 16 x d values.  Three kernels produce the partials:
-//   dkv_group_kernel: one R per workgroup; a wave takes NB list blocks at a time (d = 64: 4 waves x 2 blocks fed
-//     from one LDS read of each tile; d = 128: 8 waves x 1 block) of the levels it is given;
+//   dkv_group_kernel: one R per workgroup of 8 waves; a wave takes one list block at a time of the levels it is given;
 //   dkv_chain_kernel: level 1 with at most 16 listed blocks.  The same tile loop, but a workgroup walks several
 //     neighbouring R and a key block listed by a run of them keeps its sums in registers: one partial per run;
 //   dkv_upper_kernel: levels >= 2 only.  The 16 level-1 blocks under one level-2 query block list the same
@@ -139,10 +138,14 @@ __device__ __forceinline__ void store_shared(float *dst, const BlockAcc<D> &b, c
     }
 }
 
-// NW waves, NB key blocks per wave at a time.  DENSE: the single block of a dense level 2 too, its query tiles dealt to the waves
-// (group_takes_dense).
-template <int D, int NW, int NB, bool DENSE>
-__global__ void __launch_bounds__(64 * NW) dkv_group_kernel(LevelTable t, GroupArgs a) {
+// NW waves, a key block each at a time.  DENSE: the single block of a dense level 2 too, its query tiles dealt to the waves
+// (group_takes_dense).  Bound: a wave's chain (rows, list, keys, eight tiles one after the other) where workgroups are few, LDS reads where they are
+// many.  Two blocks a wave read every LDS operand once for both, but there are half as many waves, of twice the length: coarse stage at d = 64, four
+// waves of two blocks and eight of one, us: 16 heads x 4096 tokens 29.3 and 27.3, K = 16 39.0 and 36.0, K = 32 38.6 and 35.4, 4 x 1024 19.4 and 17.5,
+// 32 x 4096 39.7 and 37.7, 63 x 4096 67.0 and 62.1, K = 32: 16 x 16384 204 and 200, 16 x 65536 884 and 872.  (With registers for three waves a SIMD,
+// one workgroup a CU, 63 x 4096 78.)
+template <int D, int NW, bool DENSE>
+__global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 64 ? 4 : 2))) dkv_group_kernel(LevelTable t, GroupArgs a) {
     using S = GShape<D>;
     __shared__ __attribute__((aligned(16))) char qs[2 * 256 * S::ROWB];   // Q rows of the group, chunk-swizzled | dO rows
     __shared__ __attribute__((aligned(16))) float st[512];            // -LSE log2(e) | -D
@@ -153,31 +156,31 @@ __global__ void __launch_bounds__(64 * NW) dkv_group_kernel(LevelTable t, GroupA
     const int g = lane >> 4;
     const int64_t R = xcd_contiguous(blockIdx.x, gridDim.x);
     const int64_t bh = R / a.NR, Rh = R % a.NR;
-    {
-        StageRegs<D, 64 * NW> sr;
-        stage_load<D, 64 * NW>(sr, a, bh * a.N + Rh * 256, tid);
-        stage_store<D, 64 * NW>(sr, qs, gs, st, tid);
-    }
-    __syncthreads();
-    const TileOffsets<D> o = tile_offsets<D>(lane);
-
     const int nlev = min(t.nlev, a.lev_end);
     const int c_begin = t.bseg[1], nbc = pick(t.bseg, nlev) - c_begin;
     BlockTable ctab;
-    int chunk = -1;
-    for (int jb = NB * wave; jb < nbc; jb += NB * NW) {               // blocks jb .. jb + NB - 1 (same chunk of 64: NB divides 64)
+    BlockAcc<D> blk[1];
+    auto keys = [&](int jb) {
+        blk[0].load(jb < nbc ? ctab.K(jb & 63) : nullptr, ctab.V(jb & 63), ctab.count(jb & 63), ctab.bias(jb & 63), lane);
+        blk[0].clear();
+    };
+    // d = 64: the list's blocks are looked up, and the first keys asked for, while the rows are on their way (d = 128, where the rows' registers leave no
+    // room for it, 8 x 4096 tokens 40.4 us so and 39.1 behind them)
+    StageRegs<D, 64 * NW> sr;
+    stage_load<D, 64 * NW>(sr, a, bh * a.N + Rh * 256, tid);
+    if constexpr (D == 64) { ctab.fill(t, bh, Rh * 16, c_begin, 0, lane, D, nlev); keys(wave); }
+    stage_store<D, 64 * NW>(sr, qs, gs, st, tid);
+    __syncthreads();
+    if constexpr (D != 64) { ctab.fill(t, bh, Rh * 16, c_begin, 0, lane, D, nlev); keys(wave); }
+    const TileOffsets<D> o = tile_offsets<D>(lane);
+
+    int chunk = 0;
+    for (int jb = wave; jb < nbc; jb += NW) {
         if ((jb >> 6) != chunk) { chunk = jb >> 6; ctab.fill(t, bh, Rh * 16, c_begin, chunk, lane, D, nlev); }
-        BlockAcc<D> blk[NB];
-#pragma unroll
-        for (int b = 0; b < NB; ++b) {
-            const int j = (jb + b) & 63;
-            blk[b].load(jb + b < nbc ? ctab.K(j) : nullptr, ctab.V(j), ctab.count(j), ctab.bias(j), lane);
-            blk[b].clear();
-        }
-        for (int u = 0; u < 8; ++u) group_tile<D, NB>(qs, gs, st, st + 256, u, o, blk, a.sc2, g);
-#pragma unroll
-        for (int b = 0; b < NB; ++b)
-            if (jb + b < nbc) store_partial(partial_ptr<D>(t, a, nlev, jb + b + c_begin, R), blk[b], a.scale, lane);
+        if (jb != wave) keys(jb);
+#pragma unroll 1
+        for (int u = 0; u < 8; ++u) group_tile<D, 1>(qs, gs, st, st + 256, u, o, blk, a.sc2, g);
+        store_partial(partial_ptr<D>(t, a, nlev, jb + c_begin, R), blk[0], a.scale, lane);
     }
     if constexpr (DENSE) {
         BlockAcc<D> dn[1];
@@ -780,9 +783,9 @@ static hipError_t launch_group_kernel(const Plan &p, const LevelTable &t, const 
         return hipGetLastError();
     }
     const dim3 grid((unsigned)(p.bh * a.NR));
-    if (group_takes_dense(p)) dkv_group_kernel<64, 4, 2, true><<<grid, 256, 0, s>>>(t, a);
-    else if (p.d == 64) dkv_group_kernel<64, 4, 2, false><<<grid, 256, 0, s>>>(t, a);
-    else dkv_group_kernel<128, 8, 1, false><<<grid, 512, 0, s>>>(t, a);
+    if (group_takes_dense(p)) dkv_group_kernel<64, 8, true><<<grid, 512, 0, s>>>(t, a);
+    else if (p.d == 64) dkv_group_kernel<64, 8, false><<<grid, 512, 0, s>>>(t, a);
+    else dkv_group_kernel<128, 8, false><<<grid, 512, 0, s>>>(t, a);
     return hipGetLastError();
 }
 
