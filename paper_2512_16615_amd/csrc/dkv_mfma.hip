@@ -523,21 +523,30 @@ int dkv_splits(const Plan &p, int l) {
 bool dkv_by_tiles(const Plan &p) { return p.fast && p.B == 16; }
 
 // Tiles of a piece and places of a wave, by the tiles for each wave that the chip holds.  A cut list's sums go to memory and back, 16 KB a piece
-// (d = 128: 32), so pieces are as long as the launch's end allows: its last waves run alone while they finish one.  us at pieces of 16 / 32 / 64
-// tiles: 16 x 65536 tokens 266 / 254 / 263, 32 x 16384 133 / 138 / 141; steps at d = 128, 2 x 65536, K = 8 363 / 374 / 399 (18 tiles a wave), 4 x 65536
+// (d = 128: 32), so pieces are as long as the launch's end allows: its last waves run alone while they finish one.  us at pieces of 8 / 16 / 32 / 64
+// tiles: 8 x 16384 tokens 34 / 35 (12 tiles a wave), 16 x 4096, K = 16 31.6 / 33.9 (11), 32 x 4096 33.7 / 35.0 (12), d = 128, 4 x 16384 38.2 / 40.6 (9), 8 x 12288
+// 47.5 / 51 (13); 63 x 4096 60.8 / 57.4 (24), 32 x 16384 147 / 135 (48) and, another time, - / 133 / 138 / 141; 16 x 65536 - / 266 / 254 / 263; steps at d = 128,
+// 2 x 65536, K = 8 363 / 374 / 399 (18 tiles a wave, pieces from 16 on), 4 x 65536
 // 596 / 609 / 629 (36), 8 x 65536 1088 / 1074 / 1089 (72), 8 x 65536, K = 16 1665 / 1642 / 1667 (136), 8 x 131072, K = 16 3657 / 3586 / 3571 (272),
-// 8 x 262144, K = 16 6984 / 6883 / 6876 (544).  With eight tiles each or fewer, a wave with little to do is worth more: pieces of 8, 2 places (steps,
-// 1 x 16384 tokens 171.7 -> 162.7 us, 16 x 1472 58.3 -> 55.4).
+// 8 x 262144, K = 16 6984 / 6883 / 6876 (544).
 static int64_t fine_tiles(const Plan &p) { return p.bh * tile_places(p.n[1], p.n[1] * p.Kl[0]); }
 static int64_t fine_share(const Plan &p) { return (fine_tiles(p) - 1) / (p.d == 128 ? 2048 : 3072) + 1; }   // two and three waves a SIMD
 int fine_piece_log2(const Plan &p) {
     const int64_t share = fine_share(p);
-    return share <= 8 ? 3 : share <= 64 ? 4 : p.d == 64 || share <= 256 ? 5 : 6;
+    return share <= 16 ? 3 : share <= 64 ? 4 : p.d == 64 || share <= 256 ? 5 : 6;
 }
-// More than four places only where the waves have enough to do for their end not to matter (steps with 4 and 8: 4 x 110592 tokens, K = 4, Gaussian
-// 460 and 474 us, smooth 439 and 447, 4 x 65536, K = 8 417 and 425; 16 x 65536 1082 and 1070; d = 128, 4 x 131072, K = 8 Gaussian 1353 and
+// Places: a wave starts with a chain of loads (its places, their entries, the first rows), which several lists share, but with little to do each, a wave
+// less is worth more.  us at 2 / 3 / 4 / 6 / 8 places: 2 x 4096 tokens 12.9 / 13.7 / 13.9, 4 x 1024 10.4 / 10.5 / 11.6 (one tile a wave or less), 8 x 4096 at
+// d = 128 26.0 / 24.3 / 25.6 (5), 16 x 4096 23.2 / 22.4 / 23.2, 8 x 8192 24.7 / 23.4 / 22.9 (6), 32 x 4096 35.9 / 35.0 / 33.7 / 34.8 (12), 12 x 36864, K = 4,
+// Gaussian - / - / 92.2 / 92.8 / 94.0 (23), 4 x 65536 - / - / 56.3 / 54.9 / 55.7 (24), 6 x 65536, K = 12 - / - / 132.5 / 126.8 / 125.9 (53), 32 x 16384
+// - / - / 131.4 / 127.7 / 126.0, Gaussian 141.6 / 141.0 / 141.6, 8 x 65536, Gaussian - / - / 148.4 / 149.5 / 152.2 (48).
+// More only where the waves have enough to do for their end not to matter (steps with 4 and 8: 4 x 110592 tokens, K = 4, Gaussian
+// 460 and 474 us, smooth 439 and 447; 16 x 65536 1082 and 1070; d = 128, 4 x 131072, K = 8 Gaussian 1353 and
 // 1368, 8 x 65536 1104 and 1098, both 147456 places).
-static int fine_pack(const Plan &p) { return fine_share(p) <= 8 ? 2 : fine_tiles(p) <= 64 * 3072 ? 4 : 8; }
+static int fine_pack(const Plan &p) {
+    const int64_t share = fine_share(p);
+    return share <= 2 ? 2 : share <= 8 ? 3 : share <= 24 ? 4 : fine_tiles(p) > 64 * 3072 ? 8 : p.d == 64 ? 6 : 4;
+}
 // Whole stretches of heads keep rows that neighbouring blocks share in an XCD's L2 (dealt in stretches of 32 to 512 waves 16 x 65536 tokens, K = 8,
 // 1 to 7 % slower, 8 x 262144 at d = 128, K = 16 6 to 12).  With lists of few blocks there is less to share, and where a head's Q and dO are
 // more than 16 MB, eight XCDs in as many places are more than the cache behind L2 holds.  Steps, whole and in stretches of 64 waves, K = 4:
