@@ -165,12 +165,11 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 6
     if (g == 0) LSE[bh * N + blk * 16 + i16] = (m + __builtin_amdgcn_logf(lsum)) * kLn2;
 }
 
-hipError_t launch_attn_fwd_mfma(const Plan &p, const LevelTable &t, const void *Q, void *O, float *LSE,
-                                hipStream_t s) {
+hipError_t launch_attn_fwd_mfma(const Plan &p, const LevelTable &t, const void *Q, void *O, float *LSE, const AttnSelect *select, hipStream_t s) {
     // Lengths that are no multiple of 256 (one coarse level) stay here at any list length: this kernel's P are relative to the
     // exact running maximum, so a query's largest one is 1 and takes no rounding, which the shared kernel's lazy reference gives
     // up (N = 1152 in blocks of 64, d = 128: O 2.04e-3 from a 64-bit computation here, 2.14e-3 there).
-    if (p.N % 256 == 0 && (p.Kl[0] << (p.lb - 4)) <= 64) return launch_attn_fwd_shared(p, t, Q, O, LSE, s);
+    if (p.N % 256 == 0 && (p.Kl[0] << (p.lb - 4)) <= 64) return launch_attn_fwd_shared(p, t, Q, O, LSE, select, s);
     const int64_t wgs = (int64_t)p.bh * (p.N / 64);                  // 4 query tiles per workgroup
     dim3 grid((unsigned)wgs);
     if (p.d == 64)

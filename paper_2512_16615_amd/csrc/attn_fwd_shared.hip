@@ -34,12 +34,77 @@ namespace llsa {
 
 constexpr float kMaxSum = 4096.f;   // a query's softmax reference is raised only when a tile's probabilities exceed this
 
+// Selection of the lists by the workgroup that walks them (d = 64, B = 16, K <= 8, small problems): the 8 level-1 tokens of its query tiles share their
+// candidates, and the launch that it saves costs more than the work, which two workgroups to a level-2 token then do twice.  A wave a query: the candidates'
+// rows through LDS, a score per lane by plain multiply-adds, the K-th best of two a lane by comparisons and counts (no sorted lists, whose registers
+// the attention has no room for).  Bound: a chain of loads (parent's picks, their rows) and of 32 steps per list.
+// Forward call, a launch of its own and here, us: 4 heads x 1024 tokens 19.3 and 15.3, 2 x 4096 20.7 and 16.9, 16 x 4096 28.1 and 25.9, 24 x 4096 37.5 and 35.5,
+// 30 x 4096 42.4 and 42.1, 8 x 8192, L = 3 36.3 and 34.2, 2 x 16384 30.4 and 27.3; step of 16 x 4096 92.2 and 88.7.  (Two bits a step: 16 x 4096 27.1.)
+struct SelectHere {
+    const char *Q1, *K1, *Q2, *K2;   // pooled levels 1 and 2
+    int32_t *I0, *I1;                // I^(0), written here; I^(1), read (SEL = 1) or, level 2 being the coarsest one, written (SEL = 2)
+    int32_t n1, n2, K0, K1n;         // tokens per head; picks of I^(0) and of I^(1)
+};
+constexpr int kSelPicks = 8;         // of either list at most: 128 candidates, two a lane
+
+// A score as the fp32 multiply-add chain over channels 0 .. 63 that the selection's contract states (select_mfma.hip), and as a number whose order as an
+// unsigned integer is the order of scores (-0 ties with +0).  q: the query's row, the same in every lane; k: 16 bytes u of the candidate's
+template <class K> __device__ __forceinline__ uint32_t score_key(uint64_t q, K k) {
+    const auto *qw = reinterpret_cast<const __attribute__((address_space(4))) uint32_t *>(q);
+    float acc = 0.f;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+        const u32x4 w = k(u);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const uint32_t x = qw[4 * u + i];
+            acc = fmaf(__uint_as_float(x << 16), __uint_as_float(w[i] << 16), acc);
+            acc = fmaf(__uint_as_float(x & 0xffff0000u), __uint_as_float(w[i] & 0xffff0000u), acc);
+        }
+    }
+    const uint32_t u = __float_as_uint(acc + 0.f);
+    return u ^ (uint32_t)(((int32_t)u >> 31) | (int32_t)0x80000000);
+}
+// Which of the candidates 64 x + lane < count (at least K of them) are the K best, lower positions first among equals: the K-th largest key bit by bit, each
+// bit a comparison and a count.
+template <int PER> __device__ __forceinline__ void best(uint32_t (&key)[PER], int count, int K, int lane, uint64_t (&win)[PER]) {
+    uint64_t there[PER];
+#pragma unroll
+    for (int x = 0; x < PER; ++x) {
+        there[x] = __builtin_amdgcn_ballot_w64(64 * x + lane < count);
+        key[x] = 64 * x + lane < count ? key[x] : 0u;                 // below every number that is compared with
+    }
+    uint32_t kth = 0;
+    for (int bit = 31; bit >= 0; --bit) {
+        const uint32_t t = kth | 1u << bit;
+        int n = 0;
+#pragma unroll
+        for (int x = 0; x < PER; ++x) n += __popcll(__builtin_amdgcn_ballot_w64(key[x] >= t));
+        kth = n >= K ? t : kth;
+    }
+    int left = K;
+#pragma unroll
+    for (int x = 0; x < PER; ++x) {
+        win[x] = __builtin_amdgcn_ballot_w64(key[x] > kth) & there[x];
+        left -= __popcll(win[x]);
+    }
+#pragma unroll
+    for (int x = 0; x < PER; ++x) {
+        uint64_t e = __builtin_amdgcn_ballot_w64(key[x] == kth) & there[x];
+        for (; left > 0 && e; --left) {
+            win[x] |= e & -e;
+            e &= e - 1;
+        }
+    }
+}
+
 // NB = fine query tiles per wave (1 or 2), NW = waves per workgroup (4 or 8); a workgroup owns NW * NB consecutive
-// tiles, all siblings.  GW = waves whose tiles make up a block of 32 or 64 queries and share a level-0 list (0: B = 16)
-template <int D, int NB, int NW, int GW>
+// tiles, all siblings.  GW = waves whose tiles make up a block of 32 or 64 queries and share a level-0 list (0: B = 16).  SEL: the lists of level 0 (1), of
+// level 1 too (2), are selected here
+template <int D, int NB, int NW, int GW, int SEL>
 __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 64 ? 4 : 2))) attn_fwd_shared_kernel(ListArgs args, const uint16_t *__restrict__ Q,
                                                                uint16_t *__restrict__ O, float *__restrict__ LSE,
-                                                               int64_t N, FastDiv groups) {
+                                                               int64_t N, FastDiv groups, SelectHere sel) {
     constexpr int KS = D / 32, NT = D / 16, ROWB = 2 * D, HALF = 16 * ROWB, TILE = 2 * HALF;   // 16 rows, 32 rows
     constexpr int CPH = HALF / 1024;                    // load_lds steps of 16 rows
     constexpr int CPW = 4 * CPH / NW;                   // of a [K | V] tile that the workgroup shares, per wave
@@ -68,18 +133,75 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D 
     const int nb0 = t->lev[0].end;                                        // level-0 tiles (the list always holds level 0)
     const int nbc = t->lev[t->nlev - 1].end - nb0;                    // coarse tiles of the list
     const int j0_ = min(lane % LL, nb0 - 1);                              // a tile past the end is never asked for
-    const int raw0 = t->lev[0].I[(bh * t->lev[0].rows + (tile_of(min(lane / LL, NB - 1)) >> t->ls)) * t->lev[0].Kl + (j0_ >> t->ls)];
-    CoarseTable ctab;                                                  // lane j: coarse block 64 * chunk + j, of the tile issued last
-    ctab.ask<D>(t, bh, (unsigned)blk0, 0, lane);
-
     bf16x8 qop[NB][KS];
+    auto ask_query = [&](int b) {
+        const uint16_t *qrow = Q + (bh * N + tile_of(b) * 16 + i16) * D + g * 8;
+#pragma unroll
+        for (int s = 0; s < KS; ++s) qop[b][s] = ld_bf16x8(qrow + 32 * s);
+    };
+    int raw0;
+    CoarseTable ctab;                                                  // lane j: coarse block 64 * chunk + j, of the tile issued last
+    if constexpr (SEL > 0) {
+        static_assert(D == 64 && NB == 1 && NW == kSelPicks && GW == 0, "a wave a pick's candidates, a wave a query");
+        constexpr int STRIDE = 2 * D + 16;
+        char *rows = lds + RING * 2 * TILE;                           // (phase A's ring is in front of it)
+        static_assert(sizeof(lds) >= RING * 2 * TILE + 16 * kSelPicks * STRIDE, "");
+        __shared__ int32_t pick_sh[NW][kSelPicks], list_sh[NW][kSelPicks];   // every wave's own copy of the parent's picks; its list
+        ask_query(0);
+        const int64_t tok1 = bh * sel.n1 + blk0, tok2 = bh * sel.n2 + (blk0 >> 4);   // the group's first level-1 token; its level-2 token
+        if constexpr (SEL == 2) {                                     // every wave for itself: nothing to wait for
+            const char *krow = sel.K2 + (bh * sel.n2 + min(lane, sel.n2 - 1)) * (2 * D);
+            u32x4 kreg[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) kreg[u] = gload<u32x4>(krow + 16 * u);
+            uint32_t key[1] = {score_key(reinterpret_cast<uint64_t>(sel.Q2) + tok2 * (2 * D), [&](int u) { return kreg[u]; })};
+            uint64_t win[1];
+            best<1>(key, sel.n2, sel.K1n, lane, win);
+            if ((win[0] >> lane) & 1) {
+                const int rank = __popcll(win[0] & ((1ull << lane) - 1));
+                pick_sh[wave][rank] = lane;
+                if (wave == 0 && (blk0 & 15) == 0) sel.I1[tok2 * sel.K1n + rank] = lane;
+            }
+        } else if (lane < sel.K1n) pick_sh[wave][lane] = sel.I1[tok2 * sel.K1n + lane];
+        __builtin_amdgcn_wave_barrier();                              // one wave's LDS operations stay in order
+        if (wave < sel.K1n) {                                         // the 16 candidates under the wave's pick
+            const char *from = sel.K1 + (bh * sel.n1 + (int64_t)__builtin_amdgcn_readfirstlane(pick_sh[wave][wave]) * 16) * (2 * D);
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+                *reinterpret_cast<u32x4 *>(rows + (16 * wave + 8 * u + lane / 8) * STRIDE + lane % 8 * 16) = gload<u32x4>(from + 1024 * u + 16 * lane);
+        }
+        __syncthreads();
+        uint32_t key[2];
+#pragma unroll
+        for (int x = 0; x < 2; ++x) {
+            key[x] = 0;
+            if (x == 0 || sel.K1n > 4) key[x] = score_key(reinterpret_cast<uint64_t>(sel.Q1) + (tok1 + wave) * (2 * D),
+                               [&](int u) { return *reinterpret_cast<const u32x4 *>(rows + (64 * x + lane) * STRIDE + 16 * u); });
+        }
+        uint64_t win[2];
+        best<2>(key, 16 * sel.K1n, sel.K0, lane, win);
+#pragma unroll
+        for (int x = 0; x < 2; ++x)
+            if ((win[x] >> lane) & 1) {
+                const int rank = (x ? __popcll(win[0]) : 0) + __popcll(win[x] & ((1ull << lane) - 1));
+                const int id = pick_sh[wave][4 * x + (lane >> 4)] * 16 + (lane & 15);
+                list_sh[wave][rank] = id;
+                sel.I0[(tok1 + wave) * sel.K0 + rank] = id;
+            }
+        __builtin_amdgcn_wave_barrier();
+        raw0 = list_sh[wave][j0_];
+        ctab.ask<D>(t, bh, (unsigned)blk0, 0, lane);
+        if (SEL == 2 && nbc > 0 && ctab.n < 0) ctab.raw = pick_sh[wave][ctab.k];   // (level 1: the only coarse level with lists)
+        if (nbc == 0) __syncthreads();                                       // phase B's places are where the candidates were
+    } else {
+        raw0 = t->lev[0].I[(bh * t->lev[0].rows + (tile_of(min(lane / LL, NB - 1)) >> t->ls)) * t->lev[0].Kl + (j0_ >> t->ls)];
+        ctab.ask<D>(t, bh, (unsigned)blk0, 0, lane);
+    }
     f32x4 acc[NB][NT];
     float m[NB], lsum[NB];                                            // reference; this lane's share of the row sum
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
-        const uint16_t *qrow = Q + (bh * N + tile_of(b) * 16 + i16) * D + g * 8;
-#pragma unroll
-        for (int s = 0; s < KS; ++s) qop[b][s] = ld_bf16x8(qrow + 32 * s);
+        if constexpr (SEL == 0) ask_query(b);
 #pragma unroll
         for (int n = 0; n < NT; ++n) acc[b][n] = f32x4{0.f, 0.f, 0.f, 0.f};
         m[b] = -INFINITY;
@@ -338,38 +460,57 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D 
     }
 }
 
-hipError_t launch_attn_fwd_shared(const Plan &p, const LevelTable &t, const void *Q, void *O, float *LSE,
-                                  hipStream_t s) {
+static unsigned attn_groups(const Plan &p) { return (unsigned)p.bh * (unsigned)(p.N / 128); }
+// Two query tiles per wave read every coarse operand from LDS once for both: half the LDS reads, which bound d = 128
+// (16 heads x 262144 tokens, K = 16: 1977 -> 1512 us; 4096 tokens: 33.9 -> 30.1).  At d = 64 they pay from four
+// workgroups per CU on (131072 queries: 33.6 -> 30.4 us); with fewer, eight waves with a tile each hide more of the
+// latency (65536 queries: 18.2 against 18.9, 32768: 12.6 against 14.1).  Both tiles' level-0 lists have to fit one register.
+static bool two_tiles(const Plan &p) { return p.B > 16 || (p.Kl[0] <= 32 && (p.d == 128 || attn_groups(p) >= 1024)); }
+
+// Are the lists of level 0 (1), of level 1 too (2), selected by the attention's own launch?
+int attn_selects(const Plan &p) {
+    if (!p.fast || p.desc.kernel_path != 0 || p.B != 16 || p.d != 64 || p.L < 2 || p.N % 256 != 0) return 0;
+    if (p.Kl[0] > kSelPicks || p.Kl[1] > kSelPicks || two_tiles(p)) return 0;
+    return p.L > 2 ? 1 : p.n[2] <= 64 ? 2 : 0;
+}
+
+hipError_t launch_attn_fwd_shared(const Plan &p, const LevelTable &t, const void *Q, void *O, float *LSE, const AttnSelect *select, hipStream_t s) {
     const FastDiv groups(p.N / 128);
-    const unsigned wgs = (unsigned)p.bh * groups.d;
+    const unsigned wgs = attn_groups(p);
     const ListArgs a = make_list_args(t);
     const uint16_t *q = (const uint16_t *)Q;
     uint16_t *o = (uint16_t *)O;
     const int ls = p.lb - 4;
-    auto go = [&](auto d, auto nb, auto gw) {
+    SelectHere sel = {};
+    if (select) {
+        const char *w = static_cast<const char *>(select->workspace);
+        sel = {w + p.pyr_off[0][1], w + p.pyr_off[1][1], w + p.pyr_off[0][2], w + p.pyr_off[1][2], select->I0, select->I1,
+               (int32_t)p.n[1], (int32_t)p.n[2], p.Kl[0], p.Kl[1]};
+    }
+    auto kernel = [&](auto d, auto nb, auto gw, auto how) {
         constexpr int NB = decltype(nb)::value, NW = 8 / NB;
-        attn_fwd_shared_kernel<decltype(d)::value, NB, NW, decltype(gw)::value><<<wgs, 64 * NW, 0, s>>>(a, q, o, LSE, p.N, groups);
+        attn_fwd_shared_kernel<decltype(d)::value, NB, NW, decltype(gw)::value, decltype(how)::value><<<wgs, 64 * NW, 0, s>>>(a, q, o, LSE, p.N, groups, sel);
     };
+    auto go = [&](auto d, auto nb, auto gw) { kernel(d, nb, gw, std::integral_constant<int, 0>{}); };
     using I0 = std::integral_constant<int, 0>;
     using I1 = std::integral_constant<int, 1>;
     using I2 = std::integral_constant<int, 2>;
     using D64 = std::integral_constant<int, 64>;
     using D128 = std::integral_constant<int, 128>;
-    // Two query tiles per wave read every coarse operand from LDS once for both: half the LDS reads, which bound d = 128
-    // (16 heads x 262144 tokens, K = 16: 1977 -> 1512 us; 4096 tokens: 33.9 -> 30.1).  At d = 64 they pay from four
-    // workgroups per CU on (131072 queries: 33.6 -> 30.4 us); with fewer, eight waves with a tile each hide more of the
-    // latency (65536 queries: 18.2 against 18.9, 32768: 12.6 against 14.1).  Both tiles' level-0 lists have to fit one register.
-    if (ls == 1) {
+    if (select) {
+        if (attn_selects(p) == 1) kernel(D64{}, I1{}, I0{}, I1{});
+        else kernel(D64{}, I1{}, I0{}, I2{});
+    } else if (ls == 1) {
         if (p.d == 64) go(D64{}, I2{}, I1{});
         else go(D128{}, I2{}, I1{});
     } else if (ls == 2) {
         if (p.d == 64) go(D64{}, I2{}, I2{});
         else go(D128{}, I2{}, I2{});
     } else if (p.d == 64) {
-        if (p.Kl[0] <= 32 && wgs >= 1024) go(D64{}, I2{}, I0{});
+        if (two_tiles(p)) go(D64{}, I2{}, I0{});
         else go(D64{}, I1{}, I0{});
     } else {
-        if (p.Kl[0] <= 32) go(D128{}, I2{}, I0{});
+        if (two_tiles(p)) go(D128{}, I2{}, I0{});
         else go(D128{}, I1{}, I0{});
     }
     return hipGetLastError();

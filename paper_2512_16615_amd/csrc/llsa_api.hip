@@ -361,7 +361,7 @@ llsa_status llsa_attention(const llsa_plan_t *plan, const void *Q, const void *K
     if (any_misaligned16(Q, K, V, O, LSE, indices) || misaligned(workspace, 256)) return LLSA_ERR_BAD_SHAPE;
     const Plan &p = plan->p;
     LevelTable t = make_level_table(p, K, V, indices, workspace);
-    if (p.fast) LLSA_TRY(launch_attn_fwd_mfma(p, t, Q, O, LSE, (hipStream_t)hip_stream));
+    if (p.fast) LLSA_TRY(launch_attn_fwd_mfma(p, t, Q, O, LSE, nullptr, (hipStream_t)hip_stream));
     else LLSA_TRY(launch_attn_fwd_tile(p, t, Q, O, LSE, (hipStream_t)hip_stream));
     return LLSA_OK;
 }
@@ -406,9 +406,10 @@ static llsa_status forward_impl(const llsa_plan_t *plan, const void *Q, const vo
         StageScope sc(kPool, call, s);
         LLSA_TRY(launch_pool(p, Q, K, V, workspace, true, s));
     }
-    {
+    char *idx = reinterpret_cast<char *>(indices);
+    const int here = attn_selects(p);                       // lowest levels whose lists the attention's launch makes
+    if (here < p.L) {
         StageScope sc(kSelect, call, s);
-        char *idx = reinterpret_cast<char *>(indices);
         int l = p.L;
         const bool mfma_top = select_top_fused(p);
         if (mfma_top || select_dense_top_ok(p)) {           // levels L and L-1 in one launch
@@ -417,13 +418,17 @@ static llsa_status forward_impl(const llsa_plan_t *plan, const void *Q, const vo
                             reinterpret_cast<int32_t *>(idx + p.idx_off[p.L - 1])));
             l = p.L - 2;
         }
-        for (; l >= 1; --l) {
+        for (; l > here; --l) {
             const int32_t *parent = (l < p.L) ? reinterpret_cast<const int32_t *>(idx + p.idx_off[l]) : nullptr;
             LLSA_TRY(launch_select(p, l, workspace, parent, reinterpret_cast<int32_t *>(idx + p.idx_off[l - 1]), s));
         }
     }
     StageScope sc(kAttnFwd, call, s);
-    return llsa_attention(plan, Q, K, V, indices, workspace, O, LSE, hip_stream);
+    if (!here) return llsa_attention(plan, Q, K, V, indices, workspace, O, LSE, hip_stream);
+    const AttnSelect select = {workspace, reinterpret_cast<int32_t *>(idx + p.idx_off[0]), reinterpret_cast<int32_t *>(idx + p.idx_off[1])};
+    const LevelTable t = make_level_table(p, K, V, indices, workspace);
+    LLSA_TRY(launch_attn_fwd_mfma(p, t, Q, O, LSE, &select, s));
+    return LLSA_OK;
 }
 
 // ---- forward pass for callers that cannot allocate (workspace: the static device array above) ----

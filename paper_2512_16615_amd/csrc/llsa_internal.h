@@ -144,10 +144,12 @@ hipError_t launch_select_mfma(const Plan &p, int l, const void *ws, const int32_
 bool select_top_fused(const Plan &p);
 
 // ---- bf16 MFMA kernels (B = 16 / 32 / 64, d = 64 or 128, N % 64 == 0) ----
-hipError_t launch_attn_fwd_mfma(const Plan &p, const LevelTable &t, const void *Q, void *O, float *LSE, hipStream_t s);
+// select (or null): the launch selects the lists of level 0 itself (attn_selects(p) = 1: those of level 1 are there), or those of both levels (2)
+struct AttnSelect { const void *workspace; int32_t *I0, *I1; };
+int attn_selects(const Plan &p);         // 0: it cannot, or a launch of the selection's own is faster
+hipError_t launch_attn_fwd_mfma(const Plan &p, const LevelTable &t, const void *Q, void *O, float *LSE, const AttnSelect *select, hipStream_t s);
 // variant that shares the coarse levels among the 8 or 16 sibling query blocks of a workgroup
-hipError_t launch_attn_fwd_shared(const Plan &p, const LevelTable &t, const void *Q, void *O, float *LSE,
-                                  hipStream_t s);
+hipError_t launch_attn_fwd_shared(const Plan &p, const LevelTable &t, const void *Q, void *O, float *LSE, const AttnSelect *select, hipStream_t s);
 // also writes D = rowsum(dO * O) for the key-major kernels that follow
 hipError_t launch_dq_mfma(const Plan &p, const LevelTable &t, const void *Q, const void *O, const void *dO,
                           const float *LSE, float *D, void *dQ, const CscSmall &csc, hipStream_t s);

@@ -203,6 +203,48 @@ _MANY_PICKS = [
 ]
 
 
+@pytest.mark.parametrize("heads,N,K,L,Le", [
+    (1, 256, 8, 2, 2),                                     # one level-2 token: one pick of it, 16 candidates
+    (3, 1024, 8, 2, 2),                                    # four picks: 64 candidates, one a lane
+    (2, 1280, 5, 2, 2), (16, 4096, 8, 2, 2), (5, 2304, 1, 2, 1),
+    (2, 16384, 8, 2, 2), (7, 16384, 7, 2, 2),              # 64 level-2 tokens, the most that a wave takes; the most workgroups (896)
+    (4, 1024, 4, 2, 0),                                    # no coarse level in the lists
+    (2, 4096, 8, 3, 3), (1, 12288, 3, 3, 1), (1, 65536, 8, 4, 4),   # level 1's lists come from a launch of their own
+])
+@pytest.mark.parametrize("kind", ["gaussian", "ties", "constant", "special"])
+def test_lists_selected_by_the_attention(heads, N, K, L, Le, kind):
+    """A forward call whose attention selects its own lists against the same call one step at a time: every output bit for bit, whatever the scores are."""
+    import torch
+    from paper_2512_16615_amd import llsa
+    gen = torch.Generator(device="cuda").manual_seed(N + K)
+    shape = (1, heads, N, 64)
+    if kind == "ties":                                     # pooled values and scores take few different values; zeros of both signs
+        Q, K_, V = (torch.randint(-1, 2, shape, generator=gen, device="cuda").to(torch.bfloat16) for _ in range(3))
+        Q = torch.where(torch.rand(shape, generator=gen, device="cuda") < 0.5, -0.0, Q.float()).bfloat16()
+    elif kind == "constant":
+        Q, K_, V = (torch.full(shape, 0.5, device="cuda", dtype=torch.bfloat16) for _ in range(3))
+    else:
+        Q, K_, V = (torch.randn(shape, generator=gen, device="cuda").bfloat16() for _ in range(3))
+    if kind == "special":                                  # infinite and NaN scores among the others, scores that underflow
+        K_[:, :, 5] = float("inf")
+        K_[:, :, N // 2, 3] = float("nan")
+        K_[:, 0, N // 4: N // 4 + 64] = 1e-39
+        Q[:, :, 40:60] *= 1e-38
+    plan = llsa.Plan(1, heads, N, 64, 16, K, L, Le=Le)
+    O, LSE, idx, ws = llsa.forward(plan, Q, K_, V)
+    ws1, idx1 = plan.alloc_workspace(False), plan.alloc_indices()
+    llsa.pool(plan, Q, K_, V, ws1)
+    parent = None
+    for l in range(L, 0, -1):
+        out = plan.level_indices(idx1, l - 1)
+        llsa.select_level(plan, l, ws1, parent, out)
+        parent = out
+    for l in range(L):
+        assert torch.equal(plan.level_indices(idx, l), plan.level_indices(idx1, l)), f"level {l}"
+    O1, LSE1 = llsa.attention(plan, Q, K_, V, idx1, ws1)
+    assert torch.equal(O.view(torch.int16), O1.view(torch.int16)) and torch.equal(LSE.view(torch.int32), LSE1.view(torch.int32))
+
+
 @pytest.mark.parametrize("cfg", _MANY_PICKS, ids=lambda c: c["name"])
 def test_selection_of_more_than_16(cfg):
     _full_parity(cfg, 0xD165)
