@@ -152,8 +152,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 6
 bool dq_takes_lists(const Plan &p) { return (p.Kl[0] << (p.lb - 4)) <= 64; }   // the lists dq_shared.hip takes
 
 hipError_t launch_dq_mfma(const Plan &p, const LevelTable &t, const void *Q, const void *O, const void *dO,
-                          const float *LSE, float *D, void *dQ, const CscSmall &csc, hipStream_t s) {
-    if (dq_takes_lists(p)) return launch_dq_shared(p, t, Q, O, dO, LSE, D, dQ, csc, s);
+                          const float *LSE, float *D, void *dQ, const CscSmall &csc, const GroupAlong *group, hipStream_t s) {
+    if (dq_takes_lists(p)) return launch_dq_shared(p, t, Q, O, dO, LSE, D, dQ, csc, group, s);
     const int64_t wgs = (int64_t)p.bh * (p.N / 64);
     dim3 grid((unsigned)wgs);
     if (p.d == 64)

@@ -12,7 +12,7 @@
 #include <type_traits>
 
 #include "csc_small.h"
-#include "mfma_common.h"
+#include "dkv_group.h"
 
 namespace llsa {
 
@@ -28,11 +28,14 @@ __device__ __forceinline__ float bf_hi(uint32_t w) { return __uint_as_float(w & 
 // whose tiles make up a block of 32 or 64 queries and share a level-0 list (0: B = 16; 1: one wave holds the whole block).
 // Three waves per SIMD leave two tiles at d = 64 the registers they need (four spill: 572 against 477 us at 65536 tokens in
 // blocks of 64; two: 480; with rows straight into LDS 294 against 249 at 65536 tokens in blocks of 16).
-template <int D, int NB, int NW, int GW>
+// Along: nothing, or the grouped dK / dV kernel's work (with DENSE, its dense level) in workgroups of this launch's.
+struct NothingAlong {};
+template <bool DENSE> struct WithGroup { GroupAlong g; };
+template <int D, int NB, int NW, int GW, class Along>
 __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 64 ? (NB == 2 ? 3 : 4) : 2)))
 dq_shared_kernel(ListArgs args, const uint16_t *__restrict__ Q, const uint16_t *__restrict__ O,
                  const uint16_t *__restrict__ dO, const float *__restrict__ LSE, float *__restrict__ Dsum,
-                 uint16_t *__restrict__ dQ, int64_t N, FastDiv groups, CscSmall csc) {
+                 uint16_t *__restrict__ dQ, int64_t N, FastDiv groups, CscSmall csc, Along along) {
     constexpr int KS = D / 32, NT = D / 16, ROWB = 2 * D, HALF = 16 * ROWB, TILE = 2 * HALF;   // 16 rows, 32 rows
     constexpr int CPH = HALF / 1024;                    // load_lds steps of 16 rows
     constexpr int CPW = 4 * CPH / NW;                   // of a [K | V] tile that the workgroup shares, per wave
@@ -51,7 +54,18 @@ dq_shared_kernel(ListArgs args, const uint16_t *__restrict__ Q, const uint16_t *
         csc_small<64 * NW>(csc, blockIdx.x, reinterpret_cast<uint32_t *>(lds));
         return;
     }
-    const unsigned wg = xcd_contiguous32(blockIdx.x - csc.wgs, gridDim.x - csc.wgs);
+    unsigned front = csc.wgs;
+    if constexpr (!std::is_same<Along, NothingAlong>::value) {
+        const GroupAlong &ga = along.g;
+        if (blockIdx.x < front + ga.wgs) {
+            const unsigned R = xcd_contiguous32(blockIdx.x - front, ga.wgs);
+            static_assert(sizeof(lds) >= kGroupLds<D>, "");
+            if (R < ga.groups) group_body<D, NW, std::is_same<Along, WithGroup<true>>::value, true>(ga.t, ga.a, R, lds, O);
+            return;
+        }
+        front += ga.wgs;
+    }
+    const unsigned wg = xcd_contiguous32(blockIdx.x - front, gridDim.x - front);
     const int64_t bh = groups(wg), blk0 = (wg - (unsigned)bh * groups.d) * (NW * NB);   // groups.d workgroups per head
     // a spare wave of a head's last workgroup works on the head's last tile without storing it
     auto tile_of = [&](int b) { return min(blk0 + NB * wave + b, nblk - 1); };
@@ -338,17 +352,22 @@ dq_shared_kernel(ListArgs args, const uint16_t *__restrict__ Q, const uint16_t *
     }
 }
 
+static unsigned dq_groups(const Plan &p) { return (unsigned)p.bh * (unsigned)((p.N + 127) / 128); }
+// where this launch has one query tile a wave, in workgroups of the grouped kernel's size
+bool dq_takes_group(const Plan &p) { return dq_takes_lists(p) && p.d == 64 && p.B == 16 && !(p.Kl[0] <= 32 && dq_groups(p) >= 1024); }
+
 hipError_t launch_dq_shared(const Plan &p, const LevelTable &t, const void *Q, const void *O, const void *dO,
-                            const float *LSE, float *D, void *dQ, const CscSmall &csc, hipStream_t s) {
+                            const float *LSE, float *D, void *dQ, const CscSmall &csc, const GroupAlong *group, hipStream_t s) {
     const FastDiv groups((p.N + 127) / 128);
-    const unsigned wgs = (unsigned)p.bh * groups.d;
+    const unsigned wgs = dq_groups(p);
     const ListArgs a = make_list_args(t);
     const int ls = p.lb - 4;
-    auto go = [&](auto d, auto nb, auto gw) {
+    auto launch = [&](auto d, auto nb, auto gw, auto along, unsigned more) {
         constexpr int NB = decltype(nb)::value, NW = 8 / NB;
-        dq_shared_kernel<decltype(d)::value, NB, NW, decltype(gw)::value><<<wgs + csc.wgs, 64 * NW, 0, s>>>(
-            a, (const uint16_t *)Q, (const uint16_t *)O, (const uint16_t *)dO, LSE, D, (uint16_t *)dQ, p.N, groups, csc);
+        dq_shared_kernel<decltype(d)::value, NB, NW, decltype(gw)::value, decltype(along)><<<wgs + csc.wgs + more, 64 * NW, 0, s>>>(
+            a, (const uint16_t *)Q, (const uint16_t *)O, (const uint16_t *)dO, LSE, D, (uint16_t *)dQ, p.N, groups, csc, along);
     };
+    auto go = [&](auto d, auto nb, auto gw) { launch(d, nb, gw, NothingAlong{}, 0u); };
     using I0 = std::integral_constant<int, 0>;
     using I1 = std::integral_constant<int, 1>;
     using I2 = std::integral_constant<int, 2>;
@@ -364,7 +383,11 @@ hipError_t launch_dq_shared(const Plan &p, const LevelTable &t, const void *Q, c
     // more of the latency (65536 queries: 19.9 against 21.0 us).  Both tiles' level-0 lists have to fit one register, and
     // blocks of 32 tokens at d = 128 keep one tile: with two, the wave's registers spill.
     const bool fit = ls > 0 || p.Kl[0] <= 32;
-    if (p.d == 128) {
+    if (group) {
+        using D64 = std::integral_constant<int, 64>;
+        if (group->dense) launch(D64{}, I1{}, I0{}, WithGroup<true>{*group}, group->wgs);
+        else launch(D64{}, I1{}, I0{}, WithGroup<false>{*group}, group->wgs);
+    } else if (p.d == 128) {
         using D128 = std::integral_constant<int, 128>;
         if (fit && ls == 0) go(D128{}, I2{}, I0{});
         else if (ls == 2) go(D128{}, I2{}, I2{});

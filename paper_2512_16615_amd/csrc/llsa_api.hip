@@ -7,6 +7,7 @@
 #include <new>
 #include <vector>
 
+#include "dkv_group.h"
 #include "fine_tiles.h"
 #include "llsa_internal.h"
 
@@ -502,9 +503,12 @@ llsa_status llsa_backward(const llsa_plan_t *plan, const void *Q, const void *K,
     auto enqueue = [&]() -> llsa_status {
         if (!shadow) LLSA_TRY_ST(transpose());
         LevelTable t = make_level_table(p, K, V, indices, workspace);
+        // with the lists, the grouped dK / dV kernel too, whose workgroups need nothing of dQ's but D, which they form again
+        GroupAlong group;
+        const bool taken = along && p.fast && dq_takes_group(p) && group_along(p, t, Q, dO, LSE, D, workspace, &group);
         {
             StageScope sc(kDq, call, s);
-            if (p.fast) LLSA_TRY(launch_dq_mfma(p, t, Q, O, dO, LSE, D, dQ, lists_along, s));
+            if (p.fast) LLSA_TRY(launch_dq_mfma(p, t, Q, O, dO, LSE, D, dQ, lists_along, taken ? &group : nullptr, s));
             else LLSA_TRY(launch_dq_tile(p, t, Q, O, dO, LSE, D, dQ, lists_along, s));   // both also write D
         }
         if (shadow) LLSA_TRY_ST(transpose());
@@ -530,7 +534,7 @@ llsa_status llsa_backward(const llsa_plan_t *plan, const void *Q, const void *K,
             StageScope sc(kDkvCoarse, call, s);
             if (p.group) {                                  // levels above the grouped kernel's range first
                 for (int l = p.Le; l > dkv_group_top(p); --l) LLSA_TRY(launch_dkv_mfma(p, t, l, Q, dO, LSE, D, workspace, dK, dV, s));
-                LLSA_TRY(launch_dkv_group(p, t, Q, dO, LSE, D, workspace, s, shadow ? lists : nullptr, shadow ? side : nullptr,
+                LLSA_TRY(launch_dkv_group(p, t, Q, dO, LSE, D, workspace, taken, s, shadow ? lists : nullptr, shadow ? side : nullptr,
                                           shadow ? aux->ev[2] : nullptr));
                 if (shadow) joined = true;                  // the grouped launcher waits for the lists before its gathers
             } else for (int l = p.Le; l >= 1; --l) LLSA_TRY(launch_dkv_mfma(p, t, l, Q, dO, LSE, D, workspace, dK, dV, s));

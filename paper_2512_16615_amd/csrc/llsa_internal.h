@@ -150,12 +150,14 @@ int attn_selects(const Plan &p);         // 0: it cannot, or a launch of the sel
 hipError_t launch_attn_fwd_mfma(const Plan &p, const LevelTable &t, const void *Q, void *O, float *LSE, const AttnSelect *select, hipStream_t s);
 // variant that shares the coarse levels among the 8 or 16 sibling query blocks of a workgroup
 hipError_t launch_attn_fwd_shared(const Plan &p, const LevelTable &t, const void *Q, void *O, float *LSE, const AttnSelect *select, hipStream_t s);
+struct GroupAlong;                       // dkv_group.h
 // also writes D = rowsum(dO * O) for the key-major kernels that follow
 hipError_t launch_dq_mfma(const Plan &p, const LevelTable &t, const void *Q, const void *O, const void *dO,
-                          const float *LSE, float *D, void *dQ, const CscSmall &csc, hipStream_t s);
+                          const float *LSE, float *D, void *dQ, const CscSmall &csc, const GroupAlong *group, hipStream_t s);
 bool dq_takes_lists(const Plan &p);      // does launch_dq_mfma take the key-major lists along?
 hipError_t launch_dq_shared(const Plan &p, const LevelTable &t, const void *Q, const void *O, const void *dO,
-                            const float *LSE, float *D, void *dQ, const CscSmall &csc, hipStream_t s);
+                            const float *LSE, float *D, void *dQ, const CscSmall &csc, const GroupAlong *group, hipStream_t s);
+bool dq_takes_group(const Plan &p);      // does it take the grouped dK / dV kernel's work along (dkv_group.h; with the lists)?
 // key-major dK/dV of level l; levels >= 1 also fold their split slabs and the level above into the
 // level's fp32 gradient buffer, so they must be launched from the coarsest level down
 hipError_t launch_dkv_mfma(const Plan &p, const LevelTable &t, int l, const void *Q, const void *dO, const float *LSE,
@@ -170,7 +172,7 @@ int dkv_block_tiles(const Plan &p, int l), dkv_block_splits(const Plan &p, int l
 // stream the lists are made on and a spare event; the reductions and gathers of levels >= 2 then run on `side` behind
 // the lists, beside the level-1 kernel, and `lists` is recorded once more behind them (so it still marks the end of `side`).
 hipError_t launch_dkv_group(const Plan &p, const LevelTable &t, const void *Q, const void *dO, const float *LSE,
-                            const float *D, void *ws, hipStream_t s, hipEvent_t lists, hipStream_t side = nullptr,
+                            const float *D, void *ws, bool taken, hipStream_t s, hipEvent_t lists, hipStream_t side = nullptr,
                             hipEvent_t upper_done = nullptr);
 void dkv_group_sizes(const Plan &p, size_t *slab_bytes, size_t *red_bytes);
 int dkv_group_top(const Plan &p);         // highest level the grouped kernel takes (the rest: split kernel)

@@ -245,6 +245,29 @@ def test_lists_selected_by_the_attention(heads, N, K, L, Le, kind):
     assert torch.equal(O.view(torch.int16), O1.view(torch.int16)) and torch.equal(LSE.view(torch.int32), LSE1.view(torch.int32))
 
 
+@pytest.mark.parametrize("heads,N,K,L,Le", [
+    (1, 256, 8, 1, 1), (3, 256, 4, 1, 1), (16, 512, 8, 2, 1),    # 1, 3 and 32 query blocks of 256 rows: fewer than XCDs, not a multiple of them
+    (5, 2816, 16, 2, 2), (2, 4096, 8, 2, 2), (16, 4096, 8, 2, 2), (31, 4096, 8, 2, 2), (1, 8192, 32, 2, 2),
+    (2, 4352, 8, 2, 2),                                          # 17 rows: the dense level is not taken along
+    (2, 8192, 8, 3, 3), (1, 8192, 60, 2, 2),                     # levels above in kernels of their own; a list of more than one table's blocks
+])
+def test_dq_takes_the_grouped_kernel_along(heads, N, K, L, Le):
+    """A backward pass whose dQ launch does the grouped dK / dV kernel's work too against the pass with a launch for each: every gradient bit for bit."""
+    import torch
+    from paper_2512_16615_amd import llsa
+    gen = torch.Generator(device="cuda").manual_seed(N + K + heads)
+    Q, K_, V, dO = (torch.randn((1, heads, N, 64), generator=gen, device="cuda").bfloat16() for _ in range(4))
+    plan = llsa.Plan(1, heads, N, 64, 16, K, L, Le=Le)
+    ws = plan.alloc_workspace(True)
+    O, LSE, idx, ws = llsa.forward(plan, Q, K_, V, workspace=ws)
+    grads = llsa.backward(plan, Q, K_, V, O, LSE, idx, dO, ws)
+    llsa.stage_timing_begin(-1, 1)                               # (a pass that is timed by its stages runs them one by one)
+    apart = llsa.backward(plan, Q, K_, V, O, LSE, idx, dO, ws)
+    llsa.stage_timing_end()
+    for name, x, y in zip(("dQ", "dK", "dV"), grads, apart):
+        assert torch.equal(x.view(torch.int16), y.view(torch.int16)), name
+
+
 @pytest.mark.parametrize("cfg", _MANY_PICKS, ids=lambda c: c["name"])
 def test_selection_of_more_than_16(cfg):
     _full_parity(cfg, 0xD165)
