@@ -412,11 +412,12 @@ static llsa_status forward_impl(const llsa_plan_t *plan, const void *Q, const vo
     if (here < p.L) {
         StageScope sc(kSelect, call, s);
         int l = p.L;
-        const bool mfma_top = select_top_fused(p);
-        if (mfma_top || select_dense_top_ok(p)) {           // levels L and L-1 in one launch
-            auto *launch = mfma_top ? launch_select_mfma : launch_select_dense;
-            LLSA_TRY(launch(p, p.L - 1, workspace, nullptr, reinterpret_cast<int32_t *>(idx + p.idx_off[p.L - 2]), s,
-                            reinterpret_cast<int32_t *>(idx + p.idx_off[p.L - 1])));
+        if (const int low = select_top_fused(p, here + 1)) {   // levels L .. low in one launch
+            LLSA_TRY(launch_select_mfma(p, low, workspace, nullptr, reinterpret_cast<int32_t *>(idx + p.idx_off[low - 1]), s, idx));
+            l = low - 1;
+        } else if (select_dense_top_ok(p)) {                // levels L and L-1
+            LLSA_TRY(launch_select_dense(p, p.L - 1, workspace, nullptr, reinterpret_cast<int32_t *>(idx + p.idx_off[p.L - 2]), s,
+                                         reinterpret_cast<int32_t *>(idx + p.idx_off[p.L - 1])));
             l = p.L - 2;
         }
         for (; l > here; --l) {

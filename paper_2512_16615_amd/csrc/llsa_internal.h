@@ -135,13 +135,13 @@ size_t dkv_tile_bytes(const Plan &p);    // workspace of its partial sums
 bool select_mfma_ok(const Plan &p, int l);
 bool select_dense_ok(const Plan &p, int l);
 bool select_dense_top_ok(const Plan &p);
+// top_out: l = L - 1 and the launch also does level L, writing I^(L-1) to top_out (allowed if select_dense_top_ok)
 hipError_t launch_select_dense(const Plan &p, int l, const void *ws, const int32_t *parent, int32_t *out, hipStream_t s,
                                int32_t *top_out = nullptr);
-// top_out != null (here and above): l = L - 1 and the launch also does level L, writing I^(L-1) to top_out (allowed if
-// select_top_fused, or above select_dense_top_ok)
+// above: the lists of all levels; the launch also does the levels above l, up to L (allowed at select_top_fused's l)
 hipError_t launch_select_mfma(const Plan &p, int l, const void *ws, const int32_t *parent, int32_t *out, hipStream_t s,
-                              int32_t *top_out = nullptr);
-bool select_top_fused(const Plan &p);
+                              char *above = nullptr);
+int select_top_fused(const Plan &p, int low);
 
 // ---- bf16 MFMA kernels (B = 16 / 32 / 64, d = 64 or 128, N % 64 == 0) ----
 // select (or null): the launch selects the lists of level 0 itself (attn_selects(p) = 1: those of level 1 are there), or those of both levels (2)

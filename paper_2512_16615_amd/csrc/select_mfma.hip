@@ -197,15 +197,23 @@ template <int KL, class Emit> __device__ __forceinline__ void winners(const doub
     }
 }
 
-// NW waves; ONE: at most one chunk of 64 candidates each.  TOP: the launch is level L-1 and also does level L, dense over at most 64 tokens: the first wave of every
-// workgroup scores the level-L token above its queries, which yields the row of I^(L-1) it needs; the workgroup with the
-// block's first queries also writes that row out.  One launch less on a latency-bound path.
-template <class T, int D, int KL, int NW, bool ONE, bool TOP>
-__global__ void __launch_bounds__(64 * NW) select_mfma_kernel(SelLevel a, int B, int tpb, unsigned tiles, SelLevel top) {
+// NW waves; ONE: at most one chunk of 64 candidates each.  TOP: the launch also does the level above (1) or several (2), up to level L,
+// which is dense over at most 64 tokens; the ones between have at most 64 candidates too.  The first wave of every workgroup scores the
+// tokens above its queries, level by level from the top, which yields the row of I^(l) it needs; the workgroup with a token's first queries
+// also writes the token's row out.  A level less by a launch on a latency-bound path: three levels of one head x 256 tokens, fp32, in
+// two launches and in one, a step 33.8 and 32.0 us.
+constexpr int kSelAbove = 3;
+struct SelAbove {
+    SelLevel lev[kSelAbove];         // from the level next above
+    int n;
+};
+template <class T, int D, int KL, int NW, bool ONE, int TOP>
+__global__ void __launch_bounds__(64 * NW) select_mfma_kernel(SelLevel a, int B, int tpb, unsigned tiles, SelAbove up) {
     using S = SelShape<T, D>;
     static_assert(16 * KL * 8 <= 64 * S::STRIDE, "a wave's lists must fit in its staging rows");
     __shared__ __attribute__((aligned(16))) char lds[NW * 64 * S::STRIDE];
-    __shared__ int32_t prow[64];
+    __shared__ int32_t rows[2][64];
+    int32_t *prow = rows[0];
     const int tid = threadIdx.x, lane = tid & 63, i16 = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int64_t bh = blockIdx.x / tiles;
@@ -221,28 +229,46 @@ __global__ void __launch_bounds__(64 * NW) select_mfma_kernel(SelLevel a, int B,
     char *my = lds + wave * 64 * S::STRIDE;
     const unsigned magic = 0xffffffffu / (unsigned)B + 1;        // ceil(2^32 / B), also for powers of two
 
-    if constexpr (TOP) {
-        if (wave == 0) {
-            const int q0 = (int)(blk & ~15u), nt = (int)top.n;
-            const T *tq = static_cast<const T *>(top.Q) + (bh * nt + min(q0 + i16, nt - 1)) * D;
-            const f32x16 acc = score_chunk<T, D>(tq, static_cast<const T *>(top.K) + bh * nt * D, my, lane, min(lane, nt - 1));
-            double l[KL];
+    if constexpr (TOP > 0) {
+        if (wave == 0)
+            for (int u = TOP > 1 ? up.n - 1 : 0; u >= 0; --u) {
+                const SelLevel &v = up.lev[u];
+                int q = (int)blk;                                // the token of that level above these queries
+                bool begins = sub == 0;                          // ... whose first ones they are
+                for (int x = 0; TOP > 1 && x < u; ++x) {
+                    const int above = (int)__umulhi((unsigned)q, magic);
+                    begins &= above * B == q;
+                    q = above;
+                }
+                const bool all = TOP == 1 || u == up.n - 1;
+                const int nt = (int)v.n, C = all ? nt : v.Kp * B, q0 = q & ~15;
+                const int32_t *par = rows[(u + 1) & 1];
+                int32_t *mine = rows[u & 1];
+                auto cand = [&](int p) {
+                    const int k = (int)__umulhi((unsigned)p, magic);
+                    return all ? p : par[k] * B + (p - k * B);
+                };
+                const T *tq = static_cast<const T *>(v.Q) + (bh * nt + min(q0 + i16, nt - 1)) * D;
+                __builtin_amdgcn_wave_barrier();
+                const f32x16 acc = score_chunk<T, D>(tq, static_cast<const T *>(v.K) + bh * nt * D, my, lane, cand(min(lane, C - 1)));
+                double l[KL];
 #pragma unroll
-            for (int b = 0; b < 4; ++b) {                        // the one query's scores (in the lanes of its group)
-                float sc = acc[4 * b];
+                for (int b = 0; b < 4; ++b) {                    // the one query's scores (in the lanes of its group)
+                    float sc = acc[4 * b];
 #pragma unroll
-                for (int r = 1; r < 4; ++r) sc = (int)(blk & 3) == r ? acc[4 * b + r] : sc;
-                const int p = 16 * b + i16;
-                l[b] = p < nt ? make_key(sc, (uint32_t)p) : 0.0;
+                    for (int r = 1; r < 4; ++r) sc = (q & 3) == r ? acc[4 * b + r] : sc;
+                    const int p = 16 * b + i16;
+                    l[b] = p < C ? make_key(sc, (uint32_t)p) : 0.0;
+                }
+                sort4(l[0], l[1], l[2], l[3]);
+                merge_row<4, KL>(l);
+                if (g == ((q & 15) >> 2) && i16 < 4)
+                    winners<KL>(l, i16, v.Kout, [&](int pos, int rank) {
+                        const int id = cand(pos);
+                        mine[rank] = id;
+                        if (begins) v.out[(bh * nt + q) * v.Kout + rank] = id;
+                    });
             }
-            sort4(l[0], l[1], l[2], l[3]);
-            merge_row<4, KL>(l);
-            if (g == (int)((blk & 15) >> 2) && i16 < 4)
-                winners<KL>(l, i16, top.Kout, [&](int pos, int rank) {
-                    prow[rank] = pos;
-                    if (sub == 0) top.out[(bh * nt + blk) * top.Kout + rank] = pos;
-                });
-        }
         __syncthreads();
     } else if (!dense) {
         for (int i = tid; i < a.Kp; i += 64 * NW) prow[i] = a.parent[(bh * (a.n / B) + blk) * a.Kp + i];
@@ -318,13 +344,18 @@ bool select_mfma_ok(const Plan &p, int l) {
     return p.desc.kernel_path == 0 && p.Kl[l - 1] <= 16 && C <= (int64_t)kPosMax && p.n[l] < ((int64_t)1 << 30);
 }
 
-// Can level L be done inside level L-1's launch?
-bool select_top_fused(const Plan &p) {
-    return p.L >= 2 && select_mfma_ok(p, p.L) && select_mfma_ok(p, p.L - 1) && p.n[p.L] <= 64;
+// Lowest level below L that a launch can take along with all levels above it, at least `low`, or 0.  Below level L - 1 for few workgroups, where the
+// launch is what a level costs.
+int select_top_fused(const Plan &p, int low) {
+    if (p.L <= low || !select_mfma_ok(p, p.L) || !select_mfma_ok(p, p.L - 1) || p.n[p.L] > 64) return 0;
+    int l = p.L - 1;
+    while (l > low && p.L - l < kSelAbove && select_mfma_ok(p, l - 1) && p.Kl[l] * p.B <= 64 && p.bh * p.n[l] * ((p.B + 15) / 16) <= 1024) --l;
+    return l;
 }
 
+// above: the lists of all levels, of which the launch makes those above `out` too, or null
 hipError_t launch_select_mfma(const Plan &p, int l, const void *ws, const int32_t *parent, int32_t *out, hipStream_t s,
-                              int32_t *top_out) {
+                              char *above) {
     const char *w = static_cast<const char *>(ws);
     auto level = [&](int x, const int32_t *par, int32_t *o) {
         SelLevel v;
@@ -338,10 +369,18 @@ hipError_t launch_select_mfma(const Plan &p, int l, const void *ws, const int32_
         v.Kout = p.Kl[x - 1];
         return v;
     };
-    const SelLevel a = level(l, parent, out), top = level(p.L, nullptr, top_out);
+    const SelLevel a = level(l, parent, out);
+    SelAbove up;
+    up.n = above ? p.L - l : 0;
+    for (int x = 0; x < kSelAbove; ++x) {
+        const int y = l + 1 + (x < up.n ? x : 0);
+        up.lev[x] = above ? level(y, nullptr, reinterpret_cast<int32_t *>(above + p.idx_off[y - 1])) : a;
+    }
     const int tpb = l == p.L ? 1 : (p.B + 15) / 16;
     const int64_t tiles = l == p.L ? (p.n[l] + 15) / 16 : p.n[l + 1] * tpb;
-    const int kmax = top_out && top.Kout > a.Kout ? top.Kout : a.Kout, chunks = (a.C + 63) / 64;
+    int kmax = a.Kout;
+    for (int x = 0; x < up.n; ++x) kmax = up.lev[x].Kout > kmax ? up.lev[x].Kout : kmax;
+    const int chunks = (a.C + 63) / 64;
     const unsigned grid = (unsigned)(p.bh * tiles);
     auto go = [&](auto ty, auto d, auto kl) {
         using T = decltype(ty);
@@ -349,8 +388,12 @@ hipError_t launch_select_mfma(const Plan &p, int l, const void *ws, const int32_
         auto with = [&](auto nw, auto one) {
             constexpr int NW = decltype(nw)::value;
             constexpr bool ONE = decltype(one)::value;
-            if (top_out) select_mfma_kernel<T, D, KL, NW, ONE, true><<<grid, 64 * NW, 0, s>>>(a, p.B, tpb, (unsigned)tiles, top);
-            else select_mfma_kernel<T, D, KL, NW, ONE, false><<<grid, 64 * NW, 0, s>>>(a, p.B, tpb, (unsigned)tiles, top);
+            auto run = [&](auto levels) {
+                select_mfma_kernel<T, D, KL, NW, ONE, decltype(levels)::value><<<grid, 64 * NW, 0, s>>>(a, p.B, tpb, (unsigned)tiles, up);
+            };
+            if (up.n == 0) run(std::integral_constant<int, 0>{});
+            else if (up.n == 1) run(std::integral_constant<int, 1>{});
+            else run(std::integral_constant<int, 2>{});
         };
         if (chunks == 1) with(std::integral_constant<int, 1>{}, std::true_type{});
         else if (chunks == 2) with(std::integral_constant<int, 2>{}, std::true_type{});

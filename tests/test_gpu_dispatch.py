@@ -245,6 +245,39 @@ def test_lists_selected_by_the_attention(heads, N, K, L, Le, kind):
     assert torch.equal(O.view(torch.int16), O1.view(torch.int16)) and torch.equal(LSE.view(torch.int32), LSE1.view(torch.int32))
 
 
+@pytest.mark.parametrize("dtype,heads,N,d,B,K,L", [
+    ("fp32", 1, 256, 32, 4, 2, 3), ("fp32", 3, 1024, 16, 4, 3, 4),   # one workgroup a head; three levels above
+    ("fp32", 2, 16384, 64, 8, 8, 4),                         # 64 candidates; more workgroups below than are few
+    ("bf16", 2, 4096, 64, 4, 5, 5),                          # four levels above: a launch more
+    ("bf16", 1, 8192, 32, 16, 4, 3), ("bf16", 2, 4096, 128, 2, 9, 7), ("bf16", 1, 16384, 64, 4, 16, 6),
+    ("fp32", 1, 13824, 64, 24, 2, 2), ("bf16", 1, 2 * 24 ** 3, 64, 24, 2, 3),   # rows of more than 16 tokens: two tiles a token
+])
+@pytest.mark.parametrize("kind", ["gaussian", "ties", "constant"])
+def test_levels_selected_in_one_launch(dtype, heads, N, d, B, K, L, kind):
+    """A forward call, which selects several levels in a launch where they are small, against the same selection level by level."""
+    import torch
+    from paper_2512_16615_amd import llsa
+    gen = torch.Generator(device="cuda").manual_seed(N + K)
+    shape, t = (1, heads, N, d), torch.float32 if dtype == "fp32" else torch.bfloat16
+    if kind == "ties":
+        Q, K_, V = (torch.randint(-1, 2, shape, generator=gen, device="cuda").to(t) for _ in range(3))
+    elif kind == "constant":
+        Q, K_, V = (torch.full(shape, 0.5, device="cuda", dtype=t) for _ in range(3))
+    else:
+        Q, K_, V = (torch.randn(shape, generator=gen, device="cuda").to(t) for _ in range(3))
+    plan = llsa.Plan(1, heads, N, d, B, K, L, Le=1, dtype=llsa.F32 if dtype == "fp32" else llsa.BF16)
+    O, LSE, idx, ws = llsa.forward(plan, Q, K_, V)
+    ws1, idx1 = plan.alloc_workspace(False), plan.alloc_indices()
+    llsa.pool(plan, Q, K_, V, ws1)
+    parent = None
+    for l in range(L, 0, -1):
+        out = plan.level_indices(idx1, l - 1)
+        llsa.select_level(plan, l, ws1, parent, out)
+        parent = out
+    for l in range(L):
+        assert torch.equal(plan.level_indices(idx, l), plan.level_indices(idx1, l)), f"level {l}"
+
+
 @pytest.mark.parametrize("heads,N,K,L,Le", [
     (1, 256, 8, 1, 1), (3, 256, 4, 1, 1), (16, 512, 8, 2, 1),    # 1, 3 and 32 query blocks of 256 rows: fewer than XCDs, not a multiple of them
     (5, 2816, 16, 2, 2), (2, 4096, 8, 2, 2), (16, 4096, 8, 2, 2), (31, 4096, 8, 2, 2), (1, 8192, 32, 2, 2),
