@@ -337,10 +337,11 @@ struct GatherArgs {
     const float *part;           // [bh][cnt][nblk][UNIT]
     const int32_t *C, *Iq, *I;   // key-major lists and I^(l) (null when dense)
     const float *upK, *upV;      // gradient of level l + 1 or null
-    const float *upPart;         // or: the partials of level l + 1, dense, up_cnt per head of up_nblk blocks
-    int up_cnt, up_nblk;
+    const float *upPart;         // or: the partials of level l + 1, dense in one block, up_cnt <= 16 per head
+    int up_cnt;
     float *dstK, *dstV;          // [bh, n_l, D]
-    int64_t cnt, n_l, nkb, rows; // listers per head, tokens, key blocks per head, rows of I^(l)
+    int64_t cnt, n_l, rows;      // listers per head, tokens, rows of I^(l)
+    FastDiv nkb;                 // key blocks per head
     int nblk, Kl, dense;
     int chain, apart;            // chain > 1: partials come from the chain kernel, which walked `chain` listers, `apart` apart
 };
@@ -348,20 +349,23 @@ template <int D, int NT, int FLY>
 __global__ void __launch_bounds__(NT) dkv_gather_kernel(GatherArgs a) {
     constexpr int U4 = GShape<D>::UNIT / 4, H4 = U4 / 2, PER = H4 / NT;   // float4 per partial / per half / per thread and half
     const int tid = threadIdx.x;
-    const int64_t bh = blockIdx.x / a.nkb, j = blockIdx.x % a.nkb;
+    const unsigned head = a.nkb(blockIdx.x);
+    const int64_t bh = head, j = blockIdx.x - head * a.nkb.d;
     const f32x4 *part = reinterpret_cast<const f32x4 *>(a.part);
     f32x4 k[PER], v[PER];
 #pragma unroll
     for (int x = 0; x < PER; ++x) { k[x] = f32x4{0.f, 0.f, 0.f, 0.f}; v[x] = f32x4{0.f, 0.f, 0.f, 0.f}; }
-    f32x4 pk = {0.f, 0.f, 0.f, 0.f}, pv = {0.f, 0.f, 0.f, 0.f};       // the parent token's gradient, of this thread's channels
-    if (a.upPart) {
-        static_assert(NT % (D / 4) == 0, "a thread's rows share its channels");
-        const float *p = a.upPart + (bh * a.up_cnt * a.up_nblk + (j >> 4)) * GShape<D>::UNIT + (j & 15) * D + (tid % (D / 4)) * 4;
-#pragma unroll 4
-        for (int c = 0; c < a.up_cnt; ++c) {
-            pk += *reinterpret_cast<const f32x4 *>(p + (int64_t)c * a.up_nblk * GShape<D>::UNIT);
-            pv += *reinterpret_cast<const f32x4 *>(p + (int64_t)c * a.up_nblk * GShape<D>::UNIT + 16 * D);
-        }
+    // The parent token's partials, one to each row of threads (a thread of each row for every four channels), added up behind the lists
+    constexpr int ROW = D / 4, UP = FLY > 1 ? 16 : 0;                 // (group_takes_dense: few workgroups)
+    __shared__ f32x4 up_sh[2][UP + 1][ROW];                           // dK | dV: the partials, their sum
+    const int upr = tid / ROW, upc = tid % ROW;
+    f32x4 pk, pv;
+    const bool brings = UP && a.upPart && upr < a.up_cnt;
+    if (brings) {
+        static_assert(UP * ROW <= NT, "a row of threads for every partial");
+        const float *p = a.upPart + (bh * a.up_cnt + upr) * GShape<D>::UNIT + j * D + upc * 4;
+        pk = *reinterpret_cast<const f32x4 *>(p);
+        pv = *reinterpret_cast<const f32x4 *>(p + 16 * D);
     }
     if (a.dense) {
         const f32x4 *p = part + ((bh * a.cnt) * a.nblk + j) * U4;
@@ -380,7 +384,14 @@ __global__ void __launch_bounds__(NT) dkv_gather_kernel(GatherArgs a) {
                 const int64_t r = lst[e0 + tid];
                 const int32_t *row = a.I + (bh * a.rows + r) * a.Kl;
                 int pos = 0;
-                for (int x = 0; x < a.Kl; ++x) pos += (row[x] < (int32_t)j) ? 1 : 0;   // rows are ascending
+                constexpr int AT = FLY > 1 ? 8 : 1;                        // asked for at a time
+                for (int x0 = 0; x0 < a.Kl; x0 += AT) {
+                    int32_t y[AT];
+#pragma unroll
+                    for (int x = 0; x < AT; ++x) y[x] = row[min(x0 + x, a.Kl - 1)];
+#pragma unroll
+                    for (int x = 0; x < AT; ++x) pos += (x0 + x < a.Kl && y[x] < (int32_t)j) ? 1 : 0;   // rows are ascending
+                }
                 int64_t un = ((bh * a.cnt + r) * a.nblk + pos) * U4;
                 if (a.chain > 1 && r / a.apart % a.chain != a.chain - 1) {        // carried on by the next lister of the chain?
                     bool cont = false;
@@ -416,6 +427,18 @@ __global__ void __launch_bounds__(NT) dkv_gather_kernel(GatherArgs a) {
             }
         }
     }
+    if (UP && a.upPart) {
+        if (brings) { up_sh[0][upr][upc] = pk; up_sh[1][upr][upc] = pv; }
+        __syncthreads();
+        if (tid < 2 * ROW) {
+            f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+            for (int c = 0; c < a.up_cnt; ++c) sum += up_sh[tid / ROW][c][upc];
+            up_sh[tid / ROW][UP][upc] = sum;
+        }
+        __syncthreads();
+        pk = up_sh[0][UP][upc];
+        pv = up_sh[1][UP][upc];
+    }
 #pragma unroll
     for (int x = 0; x < PER; ++x) {
         const int e4 = tid + NT * x;                                   // float4 index inside [16 keys][D channels]
@@ -427,7 +450,7 @@ __global__ void __launch_bounds__(NT) dkv_gather_kernel(GatherArgs a) {
             const int64_t up = (bh * ((a.n_l + 15) / 16) + j) * D + col;   // parent token of the block's 16 tokens
             kk += *reinterpret_cast<const f32x4 *>(a.upK + up) * 0.0625f;
             vv += *reinterpret_cast<const f32x4 *>(a.upV + up) * 0.0625f;
-        } else if (a.upPart) {
+        } else if (UP && a.upPart) {                                   // (a thread's rows share its channels)
             kk += pk * 0.0625f;
             vv += pv * 0.0625f;
         }
@@ -586,22 +609,23 @@ static hipError_t finish_level(const Plan &p, const LevelTable &t, const GroupAr
     const bool with_dense = l == 1 && group_takes_dense(p), has_up = l < p.Le && !with_dense;
     ga.upPart = with_dense ? a.slab + a.lvl_off[2] : nullptr;
     ga.up_cnt = (int)a.NR;
-    ga.up_nblk = 1;
     ga.upK = has_up ? (const float *)(w + p.dKacc_off[l + 1]) : nullptr;
     ga.upV = has_up ? (const float *)(w + p.dVacc_off[l + 1]) : nullptr;
     ga.dstK = (float *)(w + p.dKacc_off[l]);
     ga.dstV = (float *)(w + p.dVacc_off[l]);
-    ga.cnt = cnt; ga.n_l = p.n[l]; ga.nkb = (p.n[l] + 15) / 16; ga.rows = dense ? 0 : p.n[l + 1];
+    ga.cnt = cnt; ga.n_l = p.n[l]; ga.nkb = FastDiv((p.n[l] + 15) / 16); ga.rows = dense ? 0 : p.n[l + 1];
     ga.nblk = a.nblk[l]; ga.Kl = dense ? 0 : p.Kl[l];
     ga.chain = l == 1 ? a.GC : 1;
     ga.apart = a.GS;
-    const dim3 grid((unsigned)(p.bh * ga.nkb));
+    const dim3 grid((unsigned)p.bh * ga.nkb.d);
     // Latency-bound (lists -> rows of I -> partials).  Many key blocks: more, smaller workgroups per CU shorten the launch, and few
     // registers let the upper levels' gathers run beside the chain kernel, which leaves no room for larger waves (8 partials in flight
     // there: 6 us more of 1110 a step at 16 heads x 65536 tokens, 2 of 560 at 32 x 16384).  At most 1024, and no chain kernel: the launch
     // is as long as one workgroup's chain of loads, and twice the threads with 8 partials in flight shorten that: 16 heads x 4096
     // tokens 12.0 -> 8.8 us, steps: 100.4 -> 96.7 us, 2 heads 69.0 -> 64.9, 8 x 16384 251 -> 242, 16 x 8192 178.6 -> 176.6.
-    const bool few = grid.x <= 1024 && a.GC == 1;
+    // A parent token's partials: one to a row of threads, on their way with the lists, where every thread read all of them, four at a time, in
+    // front of the lists: steps of 16 x 4096 84.8 -> 83.1 us (coarse stage alone 27.3 -> 25.2; 2 heads 21.8 -> 19.9, 100 x 3840 92.5 -> 89.2).
+    const bool few = (grid.x <= 1024 || with_dense) && a.GC == 1;
     if (p.d == 64) {
         if (few) dkv_gather_kernel<64, 256, 8><<<grid, 256, 0, s>>>(ga);
         else dkv_gather_kernel<64, 128, 1><<<grid, 128, 0, s>>>(ga);
