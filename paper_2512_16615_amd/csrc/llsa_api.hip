@@ -408,7 +408,8 @@ static llsa_status forward_impl(const llsa_plan_t *plan, const void *Q, const vo
         LLSA_TRY(launch_pool(p, Q, K, V, workspace, true, s));
     }
     char *idx = reinterpret_cast<char *>(indices);
-    const int here = attn_selects(p);                       // lowest levels whose lists the attention's launch makes
+    // lowest levels whose lists the attention's launch makes (none where the stages are timed one by one)
+    const int here = g_timer.on ? 0 : attn_selects(p);
     if (here < p.L) {
         StageScope sc(kSelect, call, s);
         int l = p.L;
