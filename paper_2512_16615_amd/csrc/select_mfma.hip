@@ -203,12 +203,13 @@ template <int KL, class Emit> __device__ __forceinline__ void winners(const doub
 // also writes the token's row out.  A level less by a launch on a latency-bound path: three levels of one head x 256 tokens, fp32, in
 // two launches and in one, a step 33.8 and 32.0 us.
 constexpr int kSelAbove = 3;
-struct SelAbove {
-    SelLevel lev[kSelAbove];         // from the level next above
+template <int N> struct SelAbove {
+    SelLevel lev[N];                 // from the level next above
     int n;
 };
+template <> struct SelAbove<0> {};
 template <class T, int D, int KL, int NW, bool ONE, int TOP>
-__global__ void __launch_bounds__(64 * NW) select_mfma_kernel(SelLevel a, int B, int tpb, unsigned tiles, SelAbove up) {
+__global__ void __launch_bounds__(64 * NW) select_mfma_kernel(SelLevel a, int B, int tpb, unsigned tiles, SelAbove<(TOP < 2 ? TOP : kSelAbove)> up) {
     using S = SelShape<T, D>;
     static_assert(16 * KL * 8 <= 64 * S::STRIDE, "a wave's lists must fit in its staging rows");
     __shared__ __attribute__((aligned(16))) char lds[NW * 64 * S::STRIDE];
@@ -370,7 +371,7 @@ hipError_t launch_select_mfma(const Plan &p, int l, const void *ws, const int32_
         return v;
     };
     const SelLevel a = level(l, parent, out);
-    SelAbove up;
+    SelAbove<kSelAbove> up;
     up.n = above ? p.L - l : 0;
     for (int x = 0; x < kSelAbove; ++x) {
         const int y = l + 1 + (x < up.n ? x : 0);
@@ -388,12 +389,12 @@ hipError_t launch_select_mfma(const Plan &p, int l, const void *ws, const int32_
         auto with = [&](auto nw, auto one) {
             constexpr int NW = decltype(nw)::value;
             constexpr bool ONE = decltype(one)::value;
-            auto run = [&](auto levels) {
-                select_mfma_kernel<T, D, KL, NW, ONE, decltype(levels)::value><<<grid, 64 * NW, 0, s>>>(a, p.B, tpb, (unsigned)tiles, up);
+            auto run = [&](auto top, auto above) {
+                select_mfma_kernel<T, D, KL, NW, ONE, decltype(top)::value><<<grid, 64 * NW, 0, s>>>(a, p.B, tpb, (unsigned)tiles, above);
             };
-            if (up.n == 0) run(std::integral_constant<int, 0>{});
-            else if (up.n == 1) run(std::integral_constant<int, 1>{});
-            else run(std::integral_constant<int, 2>{});
+            if (up.n == 0) run(std::integral_constant<int, 0>{}, SelAbove<0>{});
+            else if (up.n == 1) run(std::integral_constant<int, 1>{}, SelAbove<1>{{up.lev[0]}, 1});
+            else run(std::integral_constant<int, 2>{}, up);
         };
         if (chunks == 1) with(std::integral_constant<int, 1>{}, std::true_type{});
         else if (chunks == 2) with(std::integral_constant<int, 2>{}, std::true_type{});
