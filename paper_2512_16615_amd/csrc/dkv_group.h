@@ -190,7 +190,10 @@ __device__ __forceinline__ void group_body(const LevelTable &t, const GroupArgs 
     }
 }
 
-// Does the dQ launch take the work of the grouped kernel along?  Its arguments and its workgroups (a multiple of 8).
+// The grouped kernel's work in the dQ launch: its arguments and its workgroups (a multiple of 8), which come first.  Few workgroups, each a wave's chain
+// of waits: neither kernel fills the chip, and what the grouped one needs of dQ's, D, it can form itself (O's rows, 8 MB more to read at 16 heads x 4096
+// tokens).  The two launches there took 44 us, the one 32; a step 89.3 -> 84.0 us.  Where dQ has two tiles a wave its workgroups have half the
+// threads and more registers than this work leaves two workgroups a CU.
 struct GroupAlong {
     LevelTable t;
     GroupArgs a;

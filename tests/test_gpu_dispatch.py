@@ -419,6 +419,12 @@ def test_level0_waves_of_several_heads(heads, N, d, K):
     test_level0_waves_dealt_in_stretches(heads, N, d, K, L=1 if N % 256 else 2)
 
 
+@pytest.mark.parametrize("heads,N,K", [(1, 256, 8), (3, 2816, 4), (16, 4096, 8), (73, 3840, 8)])
+def test_gather_adds_up_a_dense_parent(heads, N, K):
+    """Level 1's gather with 1, 11, 16 and 15 partials of a parent token, the last in more workgroups (1095) than are few, against the general path."""
+    test_level0_waves_dealt_in_stretches(heads, N, 64, K, L=2)
+
+
 @pytest.mark.parametrize("heads,N,d,K,L", [
     # the tiles of level 0's lists, written along with the lists from 513 to 16384 rows (516: 5 segments share 1024 keys; one range of keys and
     # the first keys of the next; two groups of segments; all 128 segments) and by a launch of their own beyond
