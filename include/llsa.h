@@ -121,7 +121,8 @@ llsa_status llsa_forward(const llsa_plan_t *plan, const void *Q, const void *K, 
  * coarse tokens (adjoint of the compression loop of Alg. 1).
  *   Q, K, V, O, LSE, indices in : as given to / produced by llsa_forward
  *   dO                       in : [batch, heads, N, d]
- *   dQ, dK, dV              out : [batch, heads, N, d]
+ *   dQ, dK, dV              out : [batch, heads, N, d]; dQ may be O's buffer, whose rows the call then reads before it
+ *                                 writes theirs; of any other overlap of an output with an input or an output nothing is promised
  *   workspace                   : >= llsa_plan_workspace_bytes(plan, 1); see desc.bwd_repool
  */
 llsa_status llsa_backward(const llsa_plan_t *plan, const void *Q, const void *K, const void *V, const void *O,

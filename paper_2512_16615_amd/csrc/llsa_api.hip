@@ -505,9 +505,12 @@ llsa_status llsa_backward(const llsa_plan_t *plan, const void *Q, const void *K,
     auto enqueue = [&]() -> llsa_status {
         if (!shadow) LLSA_TRY_ST(transpose());
         LevelTable t = make_level_table(p, K, V, indices, workspace);
-        // with the lists, the grouped dK / dV kernel too, whose workgroups need nothing of dQ's but D, which they form again
+        // With the lists, the grouped dK / dV kernel too, whose workgroups need nothing of dQ's but D, which they form again, from rows of O that
+        // other workgroups of the launch have queries of: not where dQ is written over O.
         GroupAlong group;
-        const bool taken = along && p.fast && dq_takes_group(p) && group_along(p, t, Q, dO, LSE, D, workspace, &group);
+        const size_t bytes = (size_t)p.bh * p.N * p.d * p.elt;
+        const bool over_O = static_cast<const char *>(dQ) < static_cast<const char *>(O) + bytes && static_cast<const char *>(O) < static_cast<const char *>(dQ) + bytes;
+        const bool taken = along && p.fast && !over_O && dq_takes_group(p) && group_along(p, t, Q, dO, LSE, D, workspace, &group);
         {
             StageScope sc(kDq, call, s);
             if (p.fast) LLSA_TRY(launch_dq_mfma(p, t, Q, O, dO, LSE, D, dQ, lists_along, taken ? &group : nullptr, s));

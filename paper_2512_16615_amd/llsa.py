@@ -276,7 +276,8 @@ def static_workspace_bytes() -> int:
 
 
 def backward(p: Plan, Q, K, V, O, LSE, indices, dO, workspace, dQ=None, dK=None, dV=None):
-    """``llsa_backward``: returns ``(dQ, dK, dV)``.  ``workspace`` must hold the backward size."""
+    """``llsa_backward``: returns ``(dQ, dK, dV)``.  ``workspace`` must hold the backward size.  ``dQ`` may be ``O``; no other
+    output may overlap an input or another output."""
     for t, n in ((Q, "Q"), (K, "K"), (V, "V"), (O, "O"), (dO, "dO")):
         _chk_tensor(p, t, n)
     if workspace.numel() < p.workspace_bytes(True):

@@ -301,6 +301,26 @@ def test_dq_takes_the_grouped_kernel_along(heads, N, K, L, Le):
         assert torch.equal(x.view(torch.int16), y.view(torch.int16)), name
 
 
+@pytest.mark.parametrize("heads,N,d,B,K,L,dtype", [
+    (1, 256, 64, 16, 8, 1, "bf16"), (16, 4096, 64, 16, 8, 2, "bf16"), (31, 4096, 64, 16, 8, 2, "bf16"), (2, 8192, 64, 16, 8, 3, "bf16"),   # few rows at d = 64
+    (2, 4096, 128, 16, 8, 2, "bf16"), (2, 16384, 64, 64, 4, 2, "bf16"), (2, 16640, 64, 16, 8, 2, "bf16"), (16, 16384, 64, 16, 8, 2, "bf16"), (3, 1088, 64, 16, 8, 1, "bf16"),
+    (2, 1152, 64, 64, 18, 1, "bf16"), (2, 2704, 64, 16, 8, 1, "bf16"), (2, 1024, 32, 4, 3, 3, "f32")])
+def test_dq_written_over_o(heads, N, d, B, K, L, dtype):
+    """A backward pass that writes dQ over O, by every kernel that makes dQ, against one with a buffer for it: every gradient bit for bit."""
+    import torch
+    from paper_2512_16615_amd import llsa
+    gen = torch.Generator(device="cuda").manual_seed(N + K + heads)
+    t = torch.float32 if dtype == "f32" else torch.bfloat16
+    Q, K_, V, dO = (torch.randn((1, heads, N, d), generator=gen, device="cuda").to(t) for _ in range(4))
+    plan = llsa.Plan(1, heads, N, d, B, K, L, dtype=llsa.F32 if dtype == "f32" else llsa.BF16)
+    O, LSE, idx, ws = llsa.forward(plan, Q, K_, V, workspace=plan.alloc_workspace(True))
+    apart = llsa.backward(plan, Q, K_, V, O, LSE, idx, dO, ws)
+    over = llsa.backward(plan, Q, K_, V, O, LSE, idx, dO, ws, dQ=O)
+    assert over[0].data_ptr() == O.data_ptr()
+    for name, x, y in zip(("dQ", "dK", "dV"), apart, over):
+        assert torch.equal(x, y), name
+
+
 @pytest.mark.parametrize("cfg", _MANY_PICKS, ids=lambda c: c["name"])
 def test_selection_of_more_than_16(cfg):
     _full_parity(cfg, 0xD165)
