@@ -211,7 +211,7 @@ _MANY_PICKS = [
     (4, 1024, 4, 2, 0),                                    # no coarse level in the lists
     (2, 4096, 8, 3, 3), (1, 12288, 3, 3, 1), (1, 65536, 8, 4, 4),   # level 1's lists come from a launch of their own
 ])
-@pytest.mark.parametrize("kind", ["gaussian", "ties", "constant", "special"])
+@pytest.mark.parametrize("kind", ["gaussian", "ties", "constant", "special", "nan"])
 def test_lists_selected_by_the_attention(heads, N, K, L, Le, kind):
     """A forward call whose attention selects its own lists against the same call one step at a time: every output bit for bit, whatever the scores are."""
     import torch
@@ -230,6 +230,11 @@ def test_lists_selected_by_the_attention(heads, N, K, L, Le, kind):
         K_[:, :, N // 2, 3] = float("nan")
         K_[:, 0, N // 4: N // 4 + 64] = 1e-39
         Q[:, :, 40:60] *= 1e-38
+    if kind == "nan":                                      # of both signs, several payloads, quiet and not, in single channels of either
+        bits = torch.tensor([0x7fc0, -64, 0x7f81, -127, 0x7fff, -1], dtype=torch.int16, device="cuda").view(torch.bfloat16)
+        for x, every in ((K_, 7 * 16), (Q, 11 * 16)):
+            at = torch.arange(3, N, every, device="cuda")
+            x[:, :, at, (5 * at) % 64] = bits[torch.arange(len(at), device="cuda") % 6]
     plan = llsa.Plan(1, heads, N, 64, 16, K, L, Le=Le)
     O, LSE, idx, ws = llsa.forward(plan, Q, K_, V)
     ws1, idx1 = plan.alloc_workspace(False), plan.alloc_indices()
@@ -247,12 +252,12 @@ def test_lists_selected_by_the_attention(heads, N, K, L, Le, kind):
 
 @pytest.mark.parametrize("dtype,heads,N,d,B,K,L", [
     ("fp32", 1, 256, 32, 4, 2, 3), ("fp32", 3, 1024, 16, 4, 3, 4),   # one workgroup a head; three levels above
-    ("fp32", 2, 16384, 64, 8, 8, 4),                         # 64 candidates; more workgroups below than are few
+    ("fp32", 2, 16384, 64, 8, 8, 4), ("fp32", 5, 16384, 64, 8, 8, 4),   # 64 candidates: all levels; more workgroups at level 1 (1280) than are few
     ("bf16", 2, 4096, 64, 4, 5, 5),                          # four levels above: a launch more
     ("bf16", 1, 8192, 32, 16, 4, 3), ("bf16", 2, 4096, 128, 2, 9, 7), ("bf16", 1, 16384, 64, 4, 16, 6),
     ("fp32", 1, 13824, 64, 24, 2, 2), ("bf16", 1, 2 * 24 ** 3, 64, 24, 2, 3),   # rows of more than 16 tokens: two tiles a token
 ])
-@pytest.mark.parametrize("kind", ["gaussian", "ties", "constant"])
+@pytest.mark.parametrize("kind", ["gaussian", "ties", "constant", "special"])
 def test_levels_selected_in_one_launch(dtype, heads, N, d, B, K, L, kind):
     """A forward call, which selects several levels in a launch where they are small, against the same selection level by level."""
     import torch
@@ -265,6 +270,10 @@ def test_levels_selected_in_one_launch(dtype, heads, N, d, B, K, L, kind):
         Q, K_, V = (torch.full(shape, 0.5, device="cuda", dtype=t) for _ in range(3))
     else:
         Q, K_, V = (torch.randn(shape, generator=gen, device="cuda").to(t) for _ in range(3))
+    if kind == "special":                                  # infinite and NaN scores among the others, NaN of both signs
+        K_[:, :, 5], K_[:, :, N // 4] = float("inf"), float("-inf")
+        K_[:, :, N // 2, 3], K_[:, :, N // 3, 1] = float("nan"), -float("nan")
+        Q[:, :, N // 5, 2], Q[:, :, 2 * N // 3, 7] = float("nan"), float("inf")
     plan = llsa.Plan(1, heads, N, d, B, K, L, Le=1, dtype=llsa.F32 if dtype == "fp32" else llsa.BF16)
     O, LSE, idx, ws = llsa.forward(plan, Q, K_, V)
     ws1, idx1 = plan.alloc_workspace(False), plan.alloc_indices()
@@ -282,7 +291,7 @@ def test_levels_selected_in_one_launch(dtype, heads, N, d, B, K, L, kind):
     (1, 256, 8, 1, 1), (3, 256, 4, 1, 1), (16, 512, 8, 2, 1),    # 1, 3 and 32 query blocks of 256 rows: fewer than XCDs, not a multiple of them
     (5, 2816, 16, 2, 2), (2, 4096, 8, 2, 2), (16, 4096, 8, 2, 2), (31, 4096, 8, 2, 2), (1, 8192, 32, 2, 2),
     (2, 4352, 8, 2, 2),                                          # 17 rows: the dense level is not taken along
-    (2, 8192, 8, 3, 3), (1, 8192, 60, 2, 2),                     # levels above in kernels of their own; a list of more than one table's blocks
+    (2, 8192, 8, 3, 3), (1, 8192, 60, 2, 2),                     # levels above in kernels of their own; 32 listed blocks, four to a wave
 ])
 def test_dq_takes_the_grouped_kernel_along(heads, N, K, L, Le):
     """A backward pass whose dQ launch does the grouped dK / dV kernel's work too against the pass with a launch for each: every gradient bit for bit."""
@@ -381,10 +390,10 @@ def test_index_transpose_by_size(T, K, heads):
 
 @pytest.mark.parametrize("heads,N,L,d,Le", [
     # every query lists the first K blocks: lists of all T = N / 16 query blocks beside T - K empty ones.  Pieces of 8 tiles: 4 tiles, 10 and
-    # 12 (the first that are cut), 32 and 34 (one window of places and its end), no parent; of 16 at either width; and, in waves of eight places,
-    # of 32 at either width (229376 places in all) and of 64 (d = 128, 573440)
+    # 12 (the first that are cut), 32 and 34 (one window of places and its end), no parent, of 14 tiles a wave at d = 128; of 16 at either width; and,
+    # in waves of eight places, of 32 at either width (229376 places in all) and of 64 (d = 128, 573440)
     (1, 64, 1, 64, 1), (2, 320, 1, 64, 1), (3, 384, 1, 64, 0), (1, 1024, 1, 64, 1), (2, 1088, 1, 64, 1), (1, 1088, 1, 128, 1),
-    (16, 16384, 2, 64, 2), (8, 65536, 3, 64, 3), (8, 16384, 2, 128, 2), (16, 65536, 3, 64, 3), (8, 131072, 3, 128, 3),
+    (16, 16384, 2, 64, 2), (8, 65536, 3, 64, 3), (8, 16384, 2, 128, 2), (16, 16384, 2, 128, 2), (16, 65536, 3, 64, 3), (8, 131072, 3, 128, 3),
     (10, 262144, 3, 128, 3),
     (5, 16640, 2, 64, 2), (7, 69632, 3, 64, 3)])             # waves of three places and of six, which the places are no multiple of
 def test_level0_lists_of_every_query(heads, N, L, d, Le):
