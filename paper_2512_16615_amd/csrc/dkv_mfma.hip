@@ -536,10 +536,14 @@ int fine_piece_log2(const Plan &p) {
     return share <= 16 ? 3 : share <= 64 ? 4 : p.d == 64 || share <= 256 ? 5 : 6;
 }
 // Places: a wave starts with a chain of loads (its places, their entries, the first rows), which several lists share, but with little to do each, a wave
-// less is worth more.  us at 2 / 3 / 4 / 6 / 8 places: 2 x 4096 tokens 12.9 / 13.7 / 13.9, 4 x 1024 10.4 / 10.5 / 11.6 (one tile a wave or less), 8 x 4096 at
-// d = 128 26.0 / 24.3 / 25.6 (5), 16 x 4096 23.2 / 22.4 / 23.2, 8 x 8192 24.7 / 23.4 / 22.9 (6), 32 x 4096 35.9 / 35.0 / 33.7 / 34.8 (12), 12 x 36864, K = 4,
-// Gaussian - / - / 92.2 / 92.8 / 94.0 (23), 4 x 65536 - / - / 56.3 / 54.9 / 55.7 (24), 6 x 65536, K = 12 - / - / 132.5 / 126.8 / 125.9 (53), 32 x 16384
-// - / - / 131.4 / 127.7 / 126.0, Gaussian 141.6 / 141.0 / 141.6, 8 x 65536, Gaussian - / - / 148.4 / 149.5 / 152.2 (48).
+// less is worth more.  us at 2 / 3 / 4 / 6 / 8 places (tiles a wave): 2 x 4096 tokens 12.9 / 13.7 / 13.9, 4 x 1024 10.4 / 10.5 / 11.6 (one or less),
+// 16 x 4096 23.6 / 22.7 / 23.2, 8 x 8192 22.7 / 21.7 / 22.7, Gaussian 22.4 / 22.5 / 22.3, 8 x 8192, K = 4 18.6 / 18.4 / 18.2, Gaussian 19.0 / 18.4 / 17.4 (4 to
+// 6), 5 x 16384 28.3 / 26.6 / 27.8 (8), d = 128, 8 x 4096 26.0 / 24.3 / 25.6 (5), 32 x 4096 35.9 / 35.0 / 33.7 / 34.8 (12), 16 x 16384 - / 56.3 / 55.0 / 56.0 /
+// 55.9, Gaussian 62.8 / 61.8 / 62.8 / 65.4, 4 x 65536 - / 56.4 / 56.4 / 56.1 / 56.1, Gaussian 73.6 / 75.2 / 78.6 / 82.2 (24), 20 x 16384 - / 74.0 / 73.3 / 71.2 /
+// 72.5, Gaussian 93.7 / 91.0 / 90.1 / 89.8 (30), 6 x 65536 - / 98.9 / 96.9 / 95.5 / 94.5, Gaussian 111.1 / 110.2 / 112.8 / 116.6 (36), 6 x 65536, K = 12
+// - / - / 132.5 / 126.8 / 125.9 (53).
+// Shapes of one share differ by as much as the widths do; the lines lie where the mean over them turns.  Four against three: even over eight shapes of 3 to
+// 6 tiles a wave (-6 to +7 %), +2 % at 8.  Six against four, smooth and Gaussian: +1 and +3 % at 18, 0 and +2 at 22 to 24 (seven shapes), -4 and +1 at 30 to 36.
 // More only where the waves have enough to do for their end not to matter (steps with 4 and 8: 4 x 110592 tokens, K = 4, Gaussian
 // 460 and 474 us, smooth 439 and 447; 16 x 65536 1082 and 1070; d = 128, 4 x 131072, K = 8 Gaussian 1353 and
 // 1368, 8 x 65536 1104 and 1098, both 147456 places).
