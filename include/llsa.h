@@ -231,6 +231,9 @@ llsa_status llsa_kv_backward_level0(const llsa_plan_t *plan, int32_t via_mask, c
  * 6 dK/dV of the coarse levels, 7 un-pooling, 8 dK/dV of level 0, 9 dK/dV of every level in one launch.
  * A stage that a plan's kernels do inside another one has no brackets: 3 always (dQ writes D); with the bf16 MFMA kernels 9,
  * and 7, which is part of 6 and 8; with the kernels in fp32 arithmetic 6 and 8, whose launch is 9.
+ * At few rows a call that is not timed does stages in common launches (the lowest levels of 1 in 2; 4 in 5, and with it most
+ * of 6).  While timing is on, whichever stage is bracketed, they run in launches of their own, with the same results: the stages' times
+ * add up to more than such a call takes.
  * llsa_stage_timing_begin creates HIP events (host objects, no device memory); until
  * llsa_stage_timing_end, every llsa_forward / llsa_backward call brackets stage `stage` (-1: every stage)
  * with two events on its stream, for at most `max_calls` calls of each.  llsa_stage_timing_end waits for
